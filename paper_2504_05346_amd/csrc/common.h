@@ -154,6 +154,36 @@ static inline void phase_mark(PhaseTimer* t, int phase) {
   if (t) t->mark(phase);
 }
 
+// A key whose unsigned order is the order of the floats, with -0 = +0 and NaN after everything: ranks
+// are then a permutation whatever the values are, so they can be used as addresses.
+__device__ __forceinline__ uint32_t order_key(float x) {
+  const uint32_t u = __float_as_uint(x == 0.f ? 0.f : x);
+  return x != x ? 0xffffffffu : (u & 0x80000000u) ? ~u : u | 0x80000000u;
+}
+
+// Number of elements that come before v[i] in ascending (value, index) order, computed by one
+// wavefront (every lane gets it).  All n^2 comparisons of a ranking are cheap when they are spread
+// over the chip: one thread per element used to walk all n values (5120 rows on 20 workgroups:
+// 434 us, 4096: 310 us); one wavefront per element reads them 64 at a time, four loads in flight.
+__device__ __forceinline__ int64_t wave_rank(const float* __restrict__ v, int64_t n, int64_t i) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t mine = order_key(v[i]);
+  int cnt = 0;  // this lane looks at n / 64 elements
+  auto before = [&](float x, int64_t k) {
+    const uint32_t o = order_key(x);
+    return (o < mine || (o == mine && k < i)) ? 1 : 0;
+  };
+  int64_t k = lane;
+  for (; k + 192 < n; k += 256) {
+    const float o0 = v[k], o1 = v[k + 64], o2 = v[k + 128], o3 = v[k + 192];
+    cnt += before(o0, k) + before(o1, k + 64) + before(o2, k + 128) + before(o3, k + 192);
+  }
+  for (; k < n; k += 64) cnt += before(v[k], k);
+  int64_t r = cnt;
+  for (int off = 32; off > 0; off >>= 1) r += __shfl_xor(r, off, 64);
+  return r;
+}
+
 #define THANOS_CHECK(expr)                 \
   do {                                     \
     thanos_status st_ = (expr);            \

@@ -22,7 +22,6 @@ namespace thanos {
 
 // Column losses v[j] = H[j][j] * sum over non-skipped rows of W[i][j]^2, in two steps: fp64
 // partial sums over chunks of rows (blockIdx.y), then the sum of the partials in chunk order.
-// The second step also clears the rank counters of k_col_rank.
 __global__ __launch_bounds__(256) void k_col_loss_part(const float* __restrict__ W, int64_t c,
                                                        int64_t b, int64_t rows_per_chunk,
                                                        const uint8_t* __restrict__ skip,
@@ -41,41 +40,24 @@ __global__ __launch_bounds__(256) void k_col_loss_part(const float* __restrict__
 
 __global__ __launch_bounds__(256) void k_col_loss_fin(const double* __restrict__ part,
                                                       const float* __restrict__ H, int64_t b,
-                                                      int nchunk, float* __restrict__ v,
-                                                      int* __restrict__ rank) {
+                                                      int nchunk, float* __restrict__ v) {
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (j >= b) return;
   double acc = 0.0;
   for (int ch = 0; ch < nchunk; ++ch) acc += part[(int64_t)ch * b + j];
   v[j] = (float)(acc * (double)H[j * b + j]);
-  rank[j] = 0;
 }
 
-// rank[j] = number of columns before j in ascending (v, j) order; every workgroup counts one
-// chunk of 2048 competitors (blockIdx.y) for its 256 columns (integer atomics: order-free).
+// sigma = the columns in ascending (v, j) order, rank its inverse; one wavefront per column.
 __global__ __launch_bounds__(256) void k_col_rank(const float* __restrict__ v, int64_t b,
-                                                  int* __restrict__ rank) {
-  __shared__ float vs[2048];
-  const int64_t k0 = (int64_t)blockIdx.y * 2048;
-  const int nk = (int)min((int64_t)2048, b - k0);
-  for (int e = threadIdx.x; e < nk; e += 256) vs[e] = v[k0 + e];
-  __syncthreads();
-  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+                                                  int* __restrict__ rank, int* __restrict__ sigma) {
+  const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (j >= b) return;
-  const float mine = v[j];
-  int cnt = 0;
-  for (int e = 0; e < nk; ++e) {
-    const float o = vs[e];
-    cnt += (o < mine || (o == mine && k0 + e < j)) ? 1 : 0;
+  const int64_t r = wave_rank(v, b, j);
+  if ((threadIdx.x & 63) == 0) {
+    rank[j] = (int)r;
+    sigma[r] = (int)j;
   }
-  if (cnt) atomicAdd(&rank[j], cnt);
-}
-
-// sigma[rank[j]] = j (rank is sigma's inverse).
-__global__ __launch_bounds__(256) void k_col_order(const int* __restrict__ rank, int64_t b,
-                                                   int* __restrict__ sigma) {
-  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (j < b) sigma[rank[j]] = (int)j;
 }
 
 // Hp[x][y] = H_sym[sigma[x]][sigma[y]] for y <= x (H given by its lower triangle).
@@ -219,10 +201,9 @@ thanos_status structured(hipStream_t st, const void* W_in, thanos_dtype wdt, int
     double* part = reinterpret_cast<double*>(U);
     hipLaunchKernelGGL(k_col_loss_part, dim3(bb, (unsigned)nchunk), dim3(256), 0, st, W, c, b, rpc,
                        skip_c, part);
-    hipLaunchKernelGGL(k_col_loss_fin, dim3(bb), dim3(256), 0, st, part, H, b, nchunk, v, rank);
-    hipLaunchKernelGGL(k_col_rank, dim3(bb, (unsigned)ceil_div(b, 2048)), dim3(256), 0, st, v, b,
-                       rank);
-    hipLaunchKernelGGL(k_col_order, dim3(bb), dim3(256), 0, st, rank, b, sigma);
+    hipLaunchKernelGGL(k_col_loss_fin, dim3(bb), dim3(256), 0, st, part, H, b, nchunk, v);
+    hipLaunchKernelGGL(k_col_rank, dim3((unsigned)ceil_div(b, 4)), dim3(256), 0, st, v, b, rank,
+                       sigma);
     THANOS_LAUNCH_CHECK();
   }
   hipLaunchKernelGGL(k_permute_sym, dim3(bb, (unsigned)b), dim3(256), 0, st, H, b, sigma, HB);

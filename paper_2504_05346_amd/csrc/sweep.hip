@@ -1997,21 +1997,10 @@ __global__ __launch_bounds__(256) void k_rowdot(const float* __restrict__ T,
 // skip[i] = 1 for the n_out rows with the largest (h, row) (ascending order, ties by row index).
 __global__ __launch_bounds__(256) void k_row_rank(const float* __restrict__ h, int64_t c,
                                                   int64_t n_out, uint8_t* __restrict__ skip) {
-  __shared__ float hs[2048];  // competitors, one chunk at a time
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const float mine = (i < c) ? h[i] : 0.f;
-  int64_t rank = 0;
-  for (int64_t k0 = 0; k0 < c; k0 += 2048) {
-    const int nk = (int)min((int64_t)2048, c - k0);
-    __syncthreads();
-    for (int e = threadIdx.x; e < nk; e += 256) hs[e] = h[k0 + e];
-    __syncthreads();
-    for (int e = 0; e < nk; ++e) {
-      const float o = hs[e];
-      rank += (o < mine || (o == mine && k0 + e < i)) ? 1 : 0;
-    }
-  }
-  if (i < c) skip[i] = rank >= c - n_out ? 1 : 0;
+  const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (i >= c) return;
+  const int64_t rank = wave_rank(h, c, i);
+  if ((threadIdx.x & 63) == 0) skip[i] = rank >= c - n_out ? 1 : 0;
 }
 
 // skip[i] = 1 for the n_out rows of W (c x b fp32) with the largest loss W_i H W_i^T (H: lower
@@ -2026,7 +2015,7 @@ thanos_status row_outliers(hipStream_t s, const float* W, const float* H, int64_
   if (st != THANOS_OK) return st;
   hipLaunchKernelGGL(k_rowdot, dim3((unsigned)ceil_div(c, 4)), dim3(256), 0, s, T, W, c, b, h);
   THANOS_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_row_rank, dim3((unsigned)ceil_div(c, 256)), dim3(256), 0, s, h, c,
+  hipLaunchKernelGGL(k_row_rank, dim3((unsigned)ceil_div(c, 4)), dim3(256), 0, s, h, c,
                      (int64_t)n_out, skip);
   THANOS_LAUNCH_CHECK();
   return THANOS_OK;
