@@ -471,11 +471,8 @@ static int choose_split(int ntiles, int64_t nkt) {
 thanos_status syrk_accumulate(hipStream_t s, float* H, int64_t b, const void* Xc,
                               thanos_dtype xdt, int64_t n_tok, int64_t ldx, float alpha) {
   if (n_tok == 0) return THANOS_OK;
-  if (xdt == THANOS_F32) {
-    // fp32 calibration data: plain fp32 matrix-core product, lower tiles only.
-    const float* X = reinterpret_cast<const float*>(Xc);
-    return gemm_f32(s, true, true, b, b, n_tok, alpha, X, ldx, X, ldx, 1.f, H, b, true);
-  }
+  if (xdt == THANOS_F32)
+    return syrk_f32(s, H, b, reinterpret_cast<const float*>(Xc), n_tok, ldx, alpha);
   SyrkArgs a;
   a.H = H;
   a.X = reinterpret_cast<const uint16_t*>(Xc);
