@@ -4,37 +4,36 @@
 // "channel-contiguous": the reduction index (token) is the strided one, while the 16-bit MFMA
 // wants 8 consecutive reduction values per lane.
 //
-// Workgroup = 256 threads = 4 wavefronts (2x2), tile = 256 x 256 outputs, each wavefront
-// 128 x 128 = 4x4 MFMA 32x32x16 tiles (256 accumulator registers).  Only tiles on or below the
-// diagonal are computed.  Workgroups are renumbered so that the 32 workgroups resident on one
-// XCD work on a 4 x 8 patch of neighbouring tiles and share their panels of X through that
-// XCD's L2.
+// A workgroup computes one square tile of H, or the part of one that a range of the tokens
+// contributes.  Only tiles on or below the diagonal are computed.  See plan() for the choice of
+// the tile and the number of parts, item_of() for which workgroup does what.
 //
-// Main kernel (k_syrk16_dma; 16-byte aligned rows, b % 8 == 0):
+// Main kernel (k_syrk16_dma; 16-byte aligned rows, b % 8 == 0), 8 wavefronts:
 //   * global -> LDS without registers: buffer_load_dwordx4 ... lds.  One wavefront-wide load
-//     moves one token row of both panels (2 x 256 channels = 1 KB) into one LDS row; rows past
-//     n_tok are outside the buffer descriptor and arrive as zeros.  Four stages of 32 tokens
-//     (row stride 1088 B) keep three k-steps (96 KB per workgroup) in flight.
+//     moves one token row of both panels (two rows for the 128-wide tile); rows past n_tok are
+//     outside the buffer descriptor and arrive as zeros.  Four stages (a load fills 1 KB of a
+//     1088-byte LDS row) keep three k-steps in flight.
 //   * LDS -> MFMA operand with the transposing read ds_read_b64_tr_b16: within 16 lanes, lane
 //     s fetches 8 bytes of row (s / 4), channels 4 (s % 4)..+3, and receives the four rows of
 //     ONE channel, i.e. four consecutive reduction values; two such reads make an operand.
-//     The 64-byte row padding spreads the four rows of a read over all 64 banks.
+//     The 64-byte row padding spreads the four rows of a read over all 64 banks.  (Which tokens
+//     the rows of a read are does not matter: both operands see the same ones.)
 //   * one barrier per k-step: wait for the own loads of the next step (vmcnt), barrier, then
 //     multiply with the operand reads of the following slice and the loads four steps ahead
 //     (into the stage that was consumed last) interleaved one by one between the MFMAs.
-// Fallback kernel (k_syrk16; any alignment, any b): 8x8 patches are loaded with guarded scalar
-// loads, transposed in registers (v_perm_b32) and written to LDS already k-packed; fragment f
-// of a panel is the channel set {8x + f}, which keeps both LDS directions conflict-free.
+//   * tiles of 192 and 128: the wavefronts form two groups that take the two halves of the tokens
+//     of a step and add their results through LDS at the end; the wavefront tile stays as large
+//     as 96x96 and 64x64, which is what LDS traffic per MFMA depends on.
+// Fallback kernel (k_syrk16; any alignment, any b), 4 wavefronts: 8x8 patches are loaded with
+// 16-byte loads at whatever alignment the rows have, transposed in registers (v_perm_b32) and
+// written to LDS already k-packed, swizzled so that both LDS directions are conflict-free.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "gemm_tile.h"
 
 namespace thanos {
-
-constexpr int kSyTile = 256;  // outputs per tile side
-constexpr int kSyKT = 64;     // tokens per k-step
-constexpr int kSyOct = kSyKT / 8;
 
 struct SyrkArgs {
   float* H;
@@ -43,8 +42,31 @@ struct SyrkArgs {
   float alpha;
   int nt;      // tiles per side
   int ntiles;  // nt*(nt+1)/2
-  int nsplit;  // k-chunks per tile (main kernel only); > 1: partial sums are added atomically
+  int nkt;     // k-steps per tile
+  int nsplit;  // parts a tile's k-steps are cut into; > 1: partial sums are added atomically
+  int spread;  // which workgroup does what, see item_of
 };
+
+// Work item (tile, part) of this workgroup; false: none.  Hardware deals workgroups to the 8 XCDs
+// round-robin.
+//   spread = 0: XCD x owns a contiguous range of the logical tile order and walks through it once
+//   per part, so that the 32 workgroups resident on an XCD share panels through its L2 and all
+//   XCDs are on the same tokens at the same time.
+//   spread = 1 (few items, all resident at once): the items are dealt to the XCDs part by part, so
+//   that all XCDs have work and an XCD reads few tokens.
+__device__ __forceinline__ bool item_of(const SyrkArgs& a, int& tile, int& part) {
+  const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
+  if (a.spread) {
+    const int r = xcd * (int)(gridDim.x >> 3) + local;  // gridDim.x is a multiple of 8
+    part = r / a.ntiles;
+    tile = r - part * a.ntiles;
+    return part < a.nsplit;
+  }
+  const int cnt = (a.ntiles >> 3) + (xcd < (a.ntiles & 7) ? 1 : 0);
+  part = local / max(cnt, 1);
+  tile = xcd * (a.ntiles >> 3) + min(xcd, a.ntiles & 7) + local - part * cnt;
+  return cnt > 0 && part < a.nsplit;
+}
 
 // Logical tile index -> (ti, tj), ti >= tj.  Tiles are ordered by "super-rows" of 4 tile rows,
 // column by column inside a super-row, so that 32 consecutive indices cover about 4 x 8 tiles.
@@ -96,26 +118,26 @@ struct Patch {
   u32x4 rows[8];
 };
 
-template <bool VEC>
+// Rows need no alignment (the 16-byte loads of this target take any address).  A patch that
+// reaches past the channels of a row reads the start of the next row, and one beyond the channels
+// reads any channel: those columns of the product lie outside H and are dropped.  Only the last row
+// has nothing behind it; patches that hold it, or reach past it, are loaded element by element.
 __device__ __forceinline__ void patch_load(Patch& p, const uint16_t* __restrict__ X, int64_t ldx,
                                            int64_t tok0, int64_t n_tok, int64_t ch0, int64_t b) {
+  if (tok0 + 8 < n_tok && ldx >= 8) {  // loads without conditions
+    const uint16_t* src = X + tok0 * ldx + min(ch0, b - 1);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) __builtin_memcpy(&p.rows[r], src + r * ldx, 16);
+    return;
+  }
 #pragma unroll
   for (int r = 0; r < 8; ++r) {
-    u32x4 v = {0u, 0u, 0u, 0u};
-    const int64_t t = tok0 + r;
-    if (t < n_tok && ch0 < b) {
-      const uint16_t* src = X + t * ldx + ch0;
-      if (VEC) {
-        v = *reinterpret_cast<const u32x4*>(src);
-      } else {
-        uint32_t w[4] = {0u, 0u, 0u, 0u};
+    uint32_t w[4] = {0u, 0u, 0u, 0u};
+    const uint16_t* src = X + (tok0 + r) * ldx + ch0;
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (ch0 + e < b) w[e >> 1] |= (uint32_t)src[e] << (16 * (e & 1));
-        v = u32x4{w[0], w[1], w[2], w[3]};
-      }
-    }
-    p.rows[r] = v;
+    for (int e = 0; e < 8; ++e)
+      if (tok0 + r < n_tok && ch0 + e < b) w[e >> 1] |= (uint32_t)src[e] << (16 * (e & 1));
+    p.rows[r] = u32x4{w[0], w[1], w[2], w[3]};
   }
 }
 
@@ -131,98 +153,177 @@ __device__ __forceinline__ u32x4 patch_column(const Patch& p, int i) {
   return o;
 }
 
-template <bool BF16, bool VEC>
-__global__ __launch_bounds__(256) void k_syrk16(SyrkArgs a) {
-  // stage[buf][octet][slot]: slot = side*256 + (channel%8)*32 + channel/8 within the panel
+// Adds N 32x32 tiles of the product to the lower triangle of H; at(t, i0, j0) gives the first row
+// and column of tile t.  Row addresses are uniform, the lane contributes one 32-bit offset.
+template <int N, typename Acc, typename At>
+__device__ __forceinline__ void add_to_h(const SyrkArgs& a, Acc&& acc, At&& at, int lane) {
+  const int lo = lane & 31, hi = lane >> 5;
+  const uint32_t off = (uint32_t)(4 * hi) * (uint32_t)a.b + (uint32_t)lo;
+  auto bounds = [&](int64_t i0, int64_t j0, int& rows, int& first) {
+    // rows of the tile that exist, first row of it that column j0 + lo belongs to
+    rows = (int)min((int64_t)32, max((int64_t)0, a.b - i0)) - 4 * hi;
+    first = (int)max((int64_t)0, min((int64_t)32, j0 + lo - i0)) - 4 * hi;
+  };
+  if (a.nsplit > 1) {
+    // several workgroups hold partial sums of this tile: device-scope atomics (no other access
+    // to H happens inside this launch)
+#pragma unroll
+    for (int t = 0; t < N; ++t) {
+      int64_t i0, j0;
+      int rows, first;
+      at(t, i0, j0);
+      bounds(i0, j0, rows, first);
+      float* const tile = a.H + i0 * a.b + j0;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int m = 8 * (r >> 2) + (r & 3);
+        if (m < rows && m >= first)
+          (void)__hip_atomic_fetch_add(tile + (int64_t)m * a.b + off, a.alpha * acc(t)[r],
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+    return;
+  }
+  // up to four tiles at a time: their 64 loads, then their 64 stores (a load behind a store would
+  // wait for it, and one tile at a time costs a trip to memory each)
+  constexpr int G = N < 4 ? N : 4;
+#pragma unroll
+  for (int t0 = 0; t0 < N; t0 += G) {
+    float old[G][16];
+#pragma unroll
+    for (int u = 0; u < G; ++u)
+      if (t0 + u < N) {
+        int64_t i0, j0;
+        int rows, first;
+        at(t0 + u, i0, j0);
+        bounds(i0, j0, rows, first);
+        const float* const tile = a.H + i0 * a.b + j0;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int m = 8 * (r >> 2) + (r & 3);
+          old[u][r] = (m < rows && m >= first) ? (tile + (int64_t)m * a.b)[off] : 0.f;
+        }
+      }
+#pragma unroll
+    for (int u = 0; u < G; ++u)
+      if (t0 + u < N) {
+        int64_t i0, j0;
+        int rows, first;
+        at(t0 + u, i0, j0);
+        bounds(i0, j0, rows, first);
+        float* const tile = a.H + i0 * a.b + j0;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int m = 8 * (r >> 2) + (r & 3);
+          if (m < rows && m >= first)
+            (tile + (int64_t)m * a.b)[off] = old[u][r] + a.alpha * acc(t0 + u)[r];
+        }
+      }
+  }
+}
+
+// F x F MFMA tiles per wavefront: tile of 64 F channels (F = 4: 256, F = 2: 128), 64 tokens per step.
+constexpr int kFbKT = 64, kFbOct = kFbKT / 8;
+template <int F>
+constexpr size_t kFbSmem = 2 * kFbOct * 128 * F * sizeof(u32x4);
+
+template <bool BF16, int F>
+__global__ __launch_bounds__(256, F == 4 ? 1 : 2) void k_syrk16(SyrkArgs a) {
+  constexpr int TILE = 64 * F;
+  constexpr int NG = 2 * TILE / 8;           // channel groups of both panels
+  constexpr int PPT = NG * kFbOct / 256;     // patches per thread and step
+  // stage[buf][octet][side * TILE + slot(channel)], slot swizzled inside groups of 8 channels: a
+  // store instruction (one channel of each of many groups) and a fragment read (32 channels in a
+  // row) both touch every bank equally often.
   extern __shared__ u32x4 stage[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int lo = lane & 31, hi = lane >> 5;
-
-  // XCD-aware renumbering: hardware deals workgroups to the 8 XCDs round-robin.
-  const int nwg = a.ntiles;
-  const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
-  const int logical = xcd * (nwg >> 3) + min(xcd, nwg & 7) + local;
+  int tile, part;
+  if (!item_of(a, tile, part)) return;  // uniform per workgroup, before any barrier
   int ti, tj;
-  tile_from_index(logical, a.nt, ti, tj);
-  const int64_t i0 = (int64_t)ti * kSyTile, j0 = (int64_t)tj * kSyTile;
+  tile_from_index(tile, a.nt, ti, tj);
+  const int64_t i0 = (int64_t)ti * TILE, j0 = (int64_t)tj * TILE;
+  const int64_t kbeg = (int64_t)a.nkt * part / a.nsplit, kend = (int64_t)a.nkt * (part + 1) / a.nsplit;
 
-  // producer role: this thread moves the patch (octet = wave + 4u, channel group cg)
-  const int cg = lane;  // 0..31: i-side panel, 32..63: j-side panel
-  const int64_t ch0 = (cg < 32 ? i0 : j0) + 8 * (cg & 31);
-  const int slot0 = (cg < 32 ? 0 : 256) + (cg & 31);
+  auto slot = [](int ch) { return (ch & ~7) | ((ch ^ (ch >> 3)) & 7); };
+  // producer role: this thread moves the patches (octet = oct0 + u * 256 / NG, channel group cg)
+  const int cg = tid % NG, oct0 = NG < 64 ? tid / NG : __builtin_amdgcn_readfirstlane(tid / NG);
+  const int64_t ch0 = (cg < NG / 2 ? i0 : j0) + 8 * (cg % (NG / 2));
 
-  f32x16 acc[4][4];
+  f32x16 acc[F][F];
 #pragma unroll
-  for (int f = 0; f < 4; ++f)
+  for (int f = 0; f < F; ++f)
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
+    for (int g = 0; g < F; ++g)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[f][g][r] = 0.f;
 
-  const int64_t nkt = (a.n_tok + kSyKT - 1) / kSyKT;
-  Patch p[2];
+  Patch p[PPT];
   auto load_tile = [&](int64_t kt) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
-      patch_load<VEC>(p[u], a.X, a.ldx, kt * kSyKT + 8 * (wave + 4 * u), a.n_tok, ch0, a.b);
+    for (int u = 0; u < PPT; ++u)
+      patch_load(p[u], a.X, a.ldx, kt * kFbKT + 8 * (oct0 + u * (256 / NG)), a.n_tok, ch0, a.b);
   };
   auto store_tile = [&](int buf) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      u32x4* dst = stage + ((buf * kSyOct + (wave + 4 * u)) * 512 + slot0);
+    for (int u = 0; u < PPT; ++u) {
+      u32x4* dst = stage + (buf * kFbOct + (oct0 + u * (256 / NG))) * (2 * TILE) + 8 * cg;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) dst[i * 32] = patch_column(p[u], i);
+      for (int i = 0; i < 8; ++i) dst[(i ^ cg) & 7] = patch_column(p[u], i);
     }
   };
 
-  load_tile(0);
+  load_tile(kbeg);
   store_tile(0);
   __syncthreads();
-  for (int64_t kt = 0; kt < nkt; ++kt) {
-    const int buf = (int)(kt & 1);
-    if (kt + 1 < nkt) load_tile(kt + 1);
+  for (int64_t kt = kbeg; kt < kend; ++kt) {
+    const int buf = (int)((kt - kbeg) & 1);
+    if (kt + 1 < kend) load_tile(kt + 1);
 #pragma unroll
-    for (int ks = 0; ks < kSyKT / 16; ++ks) {
-      const u32x4* base = stage + (buf * kSyOct + 2 * ks + hi) * 512;
-      u32x4 af[4], bf[4];
+    for (int ks = 0; ks < kFbKT / 16; ++ks) {
+      const u32x4* base = stage + (buf * kFbOct + 2 * ks + hi) * (2 * TILE);
+      u32x4 af[F], bf[F];
 #pragma unroll
-      for (int f = 0; f < 4; ++f) af[f] = base[(4 * wm + f) * 32 + lo];
+      for (int f = 0; f < F; ++f) af[f] = base[slot(32 * (F * wm + f) + lo)];
 #pragma unroll
-      for (int g = 0; g < 4; ++g) bf[g] = base[256 + (4 * wn + g) * 32 + lo];
+      for (int g = 0; g < F; ++g) bf[g] = base[TILE + slot(32 * (F * wn + g) + lo)];
 #pragma unroll
-      for (int f = 0; f < 4; ++f)
+      for (int f = 0; f < F; ++f)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) acc[f][g] = mfma16<BF16>(af[f], bf[g], acc[f][g]);
+        for (int g = 0; g < F; ++g) acc[f][g] = mfma16<BF16>(af[f], bf[g], acc[f][g]);
     }
-    if (kt + 1 < nkt) store_tile(buf ^ 1);
+    if (kt + 1 < kend) store_tile(buf ^ 1);
     __syncthreads();
   }
-
-  // H[i][j] += alpha * acc for i >= j.  MFMA row m <-> channel i0 + 8m + (4wm+f),
-  // MFMA column n <-> channel j0 + 8n + (4wn+g).
-#pragma unroll
-  for (int f = 0; f < 4; ++f)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int64_t j = j0 + 8 * lo + (4 * wn + g);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = 8 * (r >> 2) + 4 * hi + (r & 3);
-        const int64_t i = i0 + 8 * m + (4 * wm + f);
-        if (i < a.b && j <= i) {
-          float* ptr = a.H + i * a.b + j;
-          *ptr += a.alpha * acc[f][g][r];
-        }
-      }
-    }
+  add_to_h<F * F>(
+      a, [&](int t) -> f32x16& { return acc[t / F][t % F]; },
+      [&](int t, int64_t& r0, int64_t& c0) {
+        r0 = i0 + 32 * (F * wm + t / F);
+        c0 = j0 + 32 * (F * wn + t % F);
+      },
+      lane);
 }
 
 // ------------------------------------------------------------------------------------------
-constexpr int kDmaKT = 32;                 // tokens per k-step
 constexpr int kDmaStages = 4;
-constexpr int kDmaRow = 1024 + 64;         // bytes per LDS token row (2 x 256 channels + pad)
-constexpr int kDmaStageBytes = kDmaKT * kDmaRow;
+constexpr int kDmaRow = 1024 + 64;         // bytes from one load's LDS destination to the next (1 KB + pad)
+constexpr int kDmaStageBytes = 32 * kDmaRow;  // 32 loads per stage
+
+// Geometry of a tile width: WM x WN wavefronts in each of KG groups, KT tokens per k-step.
+template <int TILE>
+struct DmaCfg {
+  static constexpr int KG = TILE == 256 ? 1 : 2;
+  static constexpr int WM = 2, WN = TILE == 256 ? 4 : 2;
+  static constexpr int FM = TILE / 32 / WM, FN = TILE / 32 / WN;  // MFMA tiles per wavefront
+  static constexpr int KT = TILE == 128 ? 64 : 32;
+  static constexpr int TPL = KT / 32;        // token rows per load
+  static constexpr int SPG = KT / 16 / KG;   // 16-token slices per wavefront and k-step
+  static constexpr size_t ring = (size_t)kDmaStages * kDmaStageBytes;                 // 136 KB
+  static constexpr size_t merge = KG == 1 ? 0 : (size_t)TILE * TILE * sizeof(float);  // see the end
+  static constexpr size_t smem = ring > merge ? ring : merge;
+};
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
@@ -254,62 +355,59 @@ __device__ __forceinline__ void dma_row(const u32x4& rsrc, uint32_t lds_addr, ui
       : "memory");
 }
 
-// NW = 8 wavefronts (two per SIMD): wavefront tile 128 x 64, so that one wavefront of a SIMD
-// can fetch operands / wait at the barrier while the other one feeds the matrix core.
-// NW = 4: wavefront tile 128 x 128 (fewer LDS reads per MFMA, nothing to overlap with).
-template <bool BF16, int NW>
-__global__ __launch_bounds__(64 * NW, NW / 4) void k_syrk16_dma(SyrkArgs a) {
-  constexpr int WN = NW / 2;          // wavefronts along the column panel
-  constexpr int GN = 8 / WN;          // 32-wide MFMA tiles per wavefront along columns
-  constexpr int RPW = kDmaKT / NW;    // token rows each wavefront loads per k-step
+// Two wavefronts per SIMD, so that one can fetch operands / wait at the barrier while the other one
+// feeds the matrix core.
+template <bool BF16, int TILE>
+__global__ __launch_bounds__(512, 2) void k_syrk16_dma(SyrkArgs a) {
+  using C = DmaCfg<TILE>;
+  constexpr int FM = C::FM, FN = C::FN, KT = C::KT, TPL = C::TPL, SPG = C::SPG;
+  constexpr int LPW = 4;              // loads of a wavefront per k-step (32 / 8)
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WN, wn = wave % WN;
+  const int kg = wave / (C::WM * C::WN);
+  const int wm = wave / C::WN % C::WM, wn = wave % C::WN;
   const int lo = lane & 31, hi = lane >> 5;
 
-  // Work item = (tile, k-chunk).  Hardware deals workgroups to the 8 XCDs round-robin; XCD x
-  // owns a contiguous range of the logical tile order and walks through it once per k-chunk,
-  // so that the 32 workgroups resident on an XCD share panels through its L2 and all XCDs are
-  // on the same chunk of tokens at the same time.
-  const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
-  const int cnt = (a.ntiles >> 3) + (xcd < (a.ntiles & 7) ? 1 : 0);
-  if (local >= cnt * a.nsplit) return;  // uniform per workgroup, before any barrier
-  const int chunk = local / cnt;
-  const int logical = xcd * (a.ntiles >> 3) + min(xcd, a.ntiles & 7) + local % cnt;
+  int tile, part;
+  if (!item_of(a, tile, part)) return;  // uniform per workgroup, before any barrier
   int ti, tj;
-  tile_from_index(logical, a.nt, ti, tj);
-  const int64_t i0 = (int64_t)ti * kSyTile, j0 = (int64_t)tj * kSyTile;
+  tile_from_index(tile, a.nt, ti, tj);
+  const int64_t i0 = (int64_t)ti * TILE, j0 = (int64_t)tj * TILE;
 
-  // producer: lane -> 8 channels of one token row; lanes 0..31 i-panel, 32..63 j-panel
-  const int64_t ch0 = (lane < 32 ? i0 : j0) + 8 * (lane & 31);
-  const uint32_t voff = (uint32_t)(ch0 * 2);
+  // producer: lane -> 8 channels of one token row, first the i-panel, then the j-panel.  256: 64
+  // lanes a row; 192: 48 (the last 16 lanes repeat one of them, into the padding); 128: 32, two rows.
+  const int pl = TILE == 128 ? lane & 31 : min(lane, TILE / 4 - 1);
+  const int64_t ch0 = (pl < TILE / 8 ? i0 : j0) + 8 * (pl % (TILE / 8));
+  const uint32_t row_bytes = __builtin_amdgcn_readfirstlane((uint32_t)(a.ldx * 2));
+  const uint32_t voff = (uint32_t)(ch0 * 2) + (TPL == 2 && lane >= 32 ? row_bytes : 0u);
   const uint32_t lds_base =
       (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
 
   // consumer: byte offset of this lane's transposing read inside a stage, fragment 0, slice 0
   const int s16 = lane & 15, g16 = (lane & 31) >> 4;
-  const int lane_off = (8 * hi + (s16 >> 2)) * kDmaRow + (16 * g16 + 4 * (s16 & 3)) * 2;
+  const int lane_off = (TPL == 2 ? (s16 >> 2) * kDmaRow + 512 * hi : (8 * hi + (s16 >> 2)) * kDmaRow) +
+                       (16 * g16 + 4 * (s16 & 3)) * 2;
+  constexpr int kSliceBytes = 16 / TPL * kDmaRow;
 
-  f32x16 acc[4][GN];
+  f32x16 acc[FM][FN];
 #pragma unroll
-  for (int f = 0; f < 4; ++f)
+  for (int f = 0; f < FM; ++f)
 #pragma unroll
-    for (int g = 0; g < GN; ++g)
+    for (int g = 0; g < FN; ++g)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[f][g][r] = 0.f;
 
-  const int64_t nkt_all = (a.n_tok + kDmaKT - 1) / kDmaKT;
-  const int64_t kbeg = nkt_all * chunk / a.nsplit, nkt = nkt_all * (chunk + 1) / a.nsplit;
+  const int64_t kbeg = (int64_t)a.nkt * part / a.nsplit, kend = (int64_t)a.nkt * (part + 1) / a.nsplit;
 
   // Descriptor and LDS destination of this wavefront's row loads of k-step kt (scalar
   // registers).  Steps past the end get an empty descriptor: every lane is out of range, nothing
   // is read and zeros are written, so the wait counts below stay uniform.
   auto prep = [&](int64_t kt, u32x4& rs, uint32_t& dst) {
-    const int64_t t0 = kt * kDmaKT + RPW * wave;
+    const int64_t t0 = kt * KT + LPW * TPL * wave;
     int64_t rem_bytes = ((a.n_tok - t0 - 1) * a.ldx + a.b) * 2;
     const uint16_t* base = a.X + t0 * a.ldx;
-    if (t0 >= a.n_tok) {
+    if (t0 >= a.n_tok || kt >= kend) {
       rem_bytes = 0;
       base = a.X;
     }
@@ -320,152 +418,205 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void k_syrk16_dma(SyrkArgs a) {
     rs.z = __builtin_amdgcn_readfirstlane(nrec);
     rs.w = 0x00020000u;
     dst = __builtin_amdgcn_readfirstlane(
-        lds_base + (uint32_t)((int)(kt % kDmaStages) * kDmaStageBytes + (RPW * wave) * kDmaRow));
+        lds_base + (uint32_t)((int)(kt % kDmaStages) * kDmaStageBytes + (LPW * wave) * kDmaRow));
   };
-  const uint32_t row_bytes = __builtin_amdgcn_readfirstlane((uint32_t)(a.ldx * 2));
   auto issue = [&](int64_t kt) {
     u32x4 rs;
     uint32_t dst;
     prep(kt, rs, dst);
 #pragma unroll
-    for (int r = 0; r < RPW; ++r) dma_row(rs, dst + r * kDmaRow, voff, r * row_bytes);
+    for (int r = 0; r < LPW; ++r) dma_row(rs, dst + r * kDmaRow, voff, r * TPL * row_bytes);
   };
   // Fragment k of a 16-token slice, in the order the MFMAs first need them:
-  // a0, b0 .. b(GN-1), a1, a2, a3.
-  auto read_item = [&](int k, const char* st, u32x4 (&af)[4], u32x4 (&bf)[GN]) {
-    if (k == 0) af[0] = frag_read_tr(st, (32 * (4 * wm)) * 2);
-    else if (k <= GN) bf[k - 1] = frag_read_tr(st, 512 + (32 * (GN * wn + k - 1)) * 2);
-    else af[k - GN] = frag_read_tr(st, (32 * (4 * wm + k - GN)) * 2);
+  // a0, b0 .. b(FN-1), a1, a2, ...
+  auto read_item = [&](int k, const char* st, u32x4 (&af)[FM], u32x4 (&bf)[FN]) {
+    if (k == 0) af[0] = frag_read_tr(st, (32 * (FM * wm)) * 2);
+    else if (k <= FN) bf[k - 1] = frag_read_tr(st, 2 * TILE + (32 * (FN * wn + k - 1)) * 2);
+    else af[k - FN] = frag_read_tr(st, (32 * (FM * wm + k - FN)) * 2);
   };
+  const char* const lds_lane = lds + lane_off + SPG * kg * kSliceBytes;
+  auto stage = [&](int64_t kt) { return lds_lane + (int)(kt % kDmaStages) * kDmaStageBytes; };
 
-  // Schedule per k-step kt (two 16-token slices of NMF MFMAs each):
-  //   MFMAs of slice 0, with the fragment reads of slice 1 riding behind the first of them |
-  //   wait: own loads of kt+1 landed, own LDS reads done | barrier |
-  //   MFMAs of slice 1, with the fragment reads of slice 0 of kt+1 behind the first half and
-  //   the row loads of kt+4 (into the stage of kt) behind the second half.
   // All wavefronts of a workgroup leave the barrier together, so anything issued in a bunch
   // there would leave the matrix core idle on every SIMD at once; issued one or two at a time
   // behind an MFMA (32 cycles each) they cost nothing.  The scheduling barriers pin that order.
   // vmcnt(n): at most n of this wavefront's loads still pending.
-  constexpr int kWaitPrologue = (RPW * 3 & 15) | ((RPW * 3 >> 4) << 14) | 0x0F70;  // 3 steps pending
-  constexpr int kWaitLoop = (RPW * 2 & 15) | ((RPW * 2 >> 4) << 14) | 0x0070;      // 2 steps, lgkm 0
-  constexpr int NMF = 4 * GN;                      // MFMAs per slice
-  constexpr int NFR = 4 + GN;                      // operand fragments per slice
+  constexpr int kWaitPrologue = (LPW * 3 & 15) | ((LPW * 3 >> 4) << 14) | 0x0F70;  // 3 steps pending
+  constexpr int kWaitLoop = (LPW * 2 & 15) | ((LPW * 2 >> 4) << 14) | 0x0070;      // 2 steps, lgkm 0
+  constexpr int NMF = FM * FN;                     // MFMAs per slice
+  constexpr int NFR = FM + FN;                     // operand fragments per slice
   constexpr int SLOTS = NMF / 2;                   // MFMAs that carry fragment reads
   constexpr int PER = (NFR + SLOTS - 1) / SLOTS;   // fragment reads behind each of them
-  static_assert(RPW <= NMF - SLOTS, "one row load behind each MFMA of the second half");
+  constexpr int LPER = (LPW + NMF - SLOTS - 1) / (NMF - SLOTS);  // row loads behind each of the others
+  // MFMAs of one slice (ac, bc), the fragments of another one read from `st` into (an, bn) behind
+  // the first half of them, and, LOAD, the row loads of a k-step behind the second half
+  auto slice = [&](auto load, u32x4 (&ac)[FM], u32x4 (&bc)[FN], const char* st, u32x4 (&an)[FM],
+                   u32x4 (&bn)[FN], const u32x4& rs, uint32_t dst) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < NMF; ++i) {
+      acc[i / FN][i % FN] = mfma16<BF16>(ac[i / FN], bc[i % FN], acc[i / FN][i % FN]);
+#pragma unroll
+      for (int k = i * PER; k < (i + 1) * PER; ++k)
+        if (k < NFR) read_item(k, st, an, bn);
+      if (decltype(load)::value && i >= SLOTS) {
+#pragma unroll
+        for (int r = (i - SLOTS) * LPER; r < (i - SLOTS + 1) * LPER; ++r)
+          if (r < LPW) dma_row(rs, dst + r * kDmaRow, voff, r * TPL * row_bytes);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  using Yes = std::true_type;
+  using No = std::false_type;
   issue(kbeg);
   issue(kbeg + 1);
   issue(kbeg + 2);
   issue(kbeg + 3);
   __builtin_amdgcn_s_waitcnt(kWaitPrologue);
   __syncthreads();
-  u32x4 a0[4], b0[GN], a1[4], b1[GN];
-  {
-    const char* st = lds + (int)(kbeg % kDmaStages) * kDmaStageBytes + lane_off;
+  u32x4 a0[FM], b0[FN], a1[FM], b1[FN];
 #pragma unroll
-    for (int k = 0; k < NFR; ++k) read_item(k, st, a0, b0);
-  }
-  for (int64_t kt = kbeg; kt < nkt; ++kt) {
-    {
-      const char* st = lds + (int)(kt % kDmaStages) * kDmaStageBytes + lane_off + 16 * kDmaRow;
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int i = 0; i < NMF; ++i) {
-        acc[i / GN][i % GN] = mfma16<BF16>(a0[i / GN], b0[i % GN], acc[i / GN][i % GN]);
-#pragma unroll
-        for (int k = i * PER; k < (i + 1) * PER; ++k)
-          if (k < NFR) read_item(k, st, a1, b1);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    __builtin_amdgcn_s_waitcnt(kWaitLoop);
-    __syncthreads();
-    {
-      u32x4 rs;
-      uint32_t dst;
+  for (int k = 0; k < NFR; ++k) read_item(k, stage(kbeg), a0, b0);
+  u32x4 rs = {0u, 0u, 0u, 0u};
+  uint32_t dst = 0u;
+  if (SPG == 2) {
+    // k-step: MFMAs of slice 0, reading slice 1 | wait: own loads of kt+1 landed, own LDS reads
+    // done | barrier | MFMAs of slice 1, reading slice 0 of kt+1, loads of kt+4 into the stage of kt
+    for (int64_t kt = kbeg; kt < kend; ++kt) {
+      slice(No{}, a0, b0, stage(kt) + kSliceBytes, a1, b1, rs, dst);
+      __builtin_amdgcn_s_waitcnt(kWaitLoop);
+      __syncthreads();
       prep(kt + 4, rs, dst);
-      const char* st = lds + (int)((kt + 1) % kDmaStages) * kDmaStageBytes + lane_off;
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int i = 0; i < NMF; ++i) {
-        acc[i / GN][i % GN] = mfma16<BF16>(a1[i / GN], b1[i % GN], acc[i / GN][i % GN]);
-#pragma unroll
-        for (int k = i * PER; k < (i + 1) * PER; ++k)
-          if (k < NFR) read_item(k, st, a0, b0);
-        if (i >= SLOTS && i - SLOTS < RPW)
-          dma_row(rs, dst + (i - SLOTS) * kDmaRow, voff, (i - SLOTS) * row_bytes);
-        __builtin_amdgcn_sched_barrier(0);
-      }
+      slice(Yes{}, a1, b1, stage(kt + 1), a0, b0, rs, dst);
+    }
+  } else {
+    // one slice per k-step, the two sets of fragments in turn (a step past the end multiplies zeros)
+    for (int64_t kt = kbeg; kt < kend; kt += 2) {
+      __builtin_amdgcn_s_waitcnt(kWaitLoop);
+      __syncthreads();
+      prep(kt + 4, rs, dst);
+      slice(Yes{}, a0, b0, stage(kt + 1), a1, b1, rs, dst);
+      __builtin_amdgcn_s_waitcnt(kWaitLoop);
+      __syncthreads();
+      prep(kt + 5, rs, dst);
+      slice(Yes{}, a1, b1, stage(kt + 2), a0, b0, rs, dst);
     }
   }
   __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0), lgkmcnt(0): drain the look-ahead
 
-  // H[i][j] += alpha * acc for i >= j; MFMA row m <-> channel i0 + 32(4wm+f) + m,
-  // MFMA column n <-> channel j0 + 32(GN wn+g) + n: 32 lanes write 128 contiguous bytes.
-  if (a.nsplit > 1) {
-    // several workgroups hold partial sums of this tile: add them with device-scope atomics
-    // (no other access to H happens inside this launch)
+  // MFMA row m <-> channel i0 + 32 (FM wm + f) + m, MFMA column n <-> channel j0 + 32 (FN wn + g) + n:
+  // 32 lanes write 128 contiguous bytes.
+  if constexpr (C::KG == 1) {
+    add_to_h<NMF>(
+        a, [&](int t) -> f32x16& { return acc[t / FN][t % FN]; },
+        [&](int t, int64_t& r0, int64_t& c0) {
+          r0 = i0 + 32 * (FM * wm + t / FN);
+          c0 = j0 + 32 * (FN * wn + t % FN);
+        },
+        lane);
+  } else {
+    // Of the NMF tiles that a wavefront and its partner in the other group both hold, group 0 keeps
+    // the even and group 1 the odd ones; the other half goes to the partner through LDS.
+    __syncthreads();  // the ring is free
+    float* const box = reinterpret_cast<float*>(lds) + (size_t)(wm * C::WN + wn) * NMF * 1024 + lane;
 #pragma unroll
-    for (int f = 0; f < 4; ++f)
+    for (int t = 0; t < NMF; ++t)
+      if ((t & 1) != kg) {
 #pragma unroll
-      for (int g = 0; g < GN; ++g) {
-        const int64_t j = j0 + 32 * (GN * wn + g) + lo;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int m = 8 * (r >> 2) + 4 * hi + (r & 3);
-          const int64_t i = i0 + 32 * (4 * wm + f) + m;
-          if (i < a.b && j <= i)
-            (void)__hip_atomic_fetch_add(a.H + i * a.b + j, a.alpha * acc[f][g][r],
-                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        for (int r = 0; r < 16; ++r) box[t * 1024 + 64 * r] = acc[t / FN][t % FN][r];
       }
-    return;
+    __syncthreads();
+    auto finish = [&](auto odd) {
+      constexpr int O = decltype(odd)::value ? 1 : 0;
+      constexpr int N = (NMF + 1 - O) / 2;
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        const int t = 2 * u + O;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[t / FN][t % FN][r] += box[t * 1024 + 64 * r];
+      }
+      add_to_h<N>(
+          a, [&](int u) -> f32x16& { return acc[(2 * u + O) / FN][(2 * u + O) % FN]; },
+          [&](int u, int64_t& r0, int64_t& c0) {
+            r0 = i0 + 32 * (FM * wm + (2 * u + O) / FN);
+            c0 = j0 + 32 * (FN * wn + (2 * u + O) % FN);
+          },
+          lane);
+    };
+    if (kg == 0) finish(No{});
+    else finish(Yes{});
   }
-  // per 32x32 MFMA tile: 16 loads, then 16 stores (a load behind a store would wait for it)
-#pragma unroll
-  for (int f = 0; f < 4; ++f)
-#pragma unroll
-    for (int g = 0; g < GN; ++g) {
-      const int64_t j = j0 + 32 * (GN * wn + g) + lo;
-      float old[16];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = 8 * (r >> 2) + 4 * hi + (r & 3);
-        const int64_t i = i0 + 32 * (4 * wm + f) + m;
-        old[r] = (i < a.b && j <= i) ? a.H[i * a.b + j] : 0.f;
-      }
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = 8 * (r >> 2) + 4 * hi + (r & 3);
-        const int64_t i = i0 + 32 * (4 * wm + f) + m;
-        if (i < a.b && j <= i) a.H[i * a.b + j] = old[r] + a.alpha * acc[f][g][r];
-      }
-    }
 }
 
-// Number of k-chunks per tile.  One XCD (32 compute units) works through cnt*S items of
-// nkt/S k-steps each, plus a fixed cost per item (pipeline fill, write-out) of about `epi`
-// k-steps.  S = 1 keeps the plain read-modify-write (bitwise reproducible); it is given up only
-// for a gain of more than 3 %.
-static int choose_split(int ntiles, int64_t nkt) {
-  const int cnt = (ntiles + 7) / 8;
-  const double epi = 12.0;
-  auto cost = [&](int S) {
-    const int64_t rounds = ((int64_t)cnt * S + 31) / 32;
-    return (double)rounds * ((double)nkt / S + epi);
-  };
-  int best = 1;
-  double cbest = cost(1);
-  const int smax = (int)std::min<int64_t>(64, nkt / 64);
-  for (int S = 2; S <= smax; ++S) {
-    const double c = cost(S);
-    if (c < cbest * (best == 1 ? 0.97 : 1.0)) {
-      cbest = c;
-      best = S;
+// Tile width, number of parts and workgroups of a launch: the cheapest by the estimate below, in us.
+//   step   one k-step of a workgroup while the chip's power limit does not bind;
+//   work   its multiplications relative to 256 x 256 x 32 tokens (the energy they take).  Beyond about 170 busy compute
+//          units the chip clocks down in proportion (256-wide tiles of random data: 0.62 us a step on
+//          136 units, 0.92 us on 256), so work, not the number of units, sets the time;
+//   slots  workgroups the chip holds at once.
+// Per work item 4 us of pipeline fill and write-out latency (12 where the next item waits behind
+// the stores or atomics of the last one); H is read and written once (4.5 TB/s),
+// or, with parts, added to once per part with atomics (1.1 TB/s measured, which is why a narrower
+// tile is preferred to a second part).  Start of a call 4 us.  Measured, 16-bit tokens x channels:
+//                     256-wide whole tiles     chosen
+//   2048 x 4096            73 us               192, 1 part     56 us
+//   2048 x 2048            67 us               128, 1 part     26 us
+//   32768 x 768            65 us (16 parts)    128, 12 parts   40 us
+//   512 x 256              34 us               128, 4 parts    7.5 us
+//   2048 x 1365 (fallback) 551 us              128, 3 parts    27 us
+struct TileCost {
+  int tile, kt, slots;
+  double step, work;
+};
+
+static int plan(SyrkArgs& a, bool vec, unsigned& grid) {
+  static constexpr TileCost dma[] = {
+      {256, 32, 256, 0.62, 1.0}, {192, 32, 256, 0.36, 0.58}, {128, 64, 256, 0.43, 0.5}};
+  static constexpr TileCost fb[] = {{256, 64, 256, 2.6, 2.0}, {128, 64, 512, 1.2, 0.5}};
+  const TileCost* cand = vec ? dma : fb;
+  const int ncand = vec ? 3 : 2;
+  const double hbytes = 4.0 * (double)a.b * (double)a.b / 2;
+  double best = 1e300;
+  int tile = 0;
+  for (int q = 0; q < ncand; ++q) {
+    const TileCost& k = cand[q];
+    const int64_t nt = ceil_div(a.b, k.tile), ntiles = nt * (nt + 1) / 2;
+    const int64_t nkt = ceil_div(a.n_tok, k.kt);
+    const int64_t smax = std::min<int64_t>(256, std::max<int64_t>(1, nkt / 2));
+    for (int64_t S = 1; S <= smax; ++S) {
+      const bool spread = ntiles * S <= k.slots;
+      // narrow tiles read the tokens more often: only while everything is resident at once
+      if (!spread && k.tile != 256) continue;
+      const int64_t per_xcd = ceil_div(ntiles, 8) * S, slots_xcd = k.slots / 8;
+      const double steps = (double)ceil_div(nkt, S);
+      auto round_us = [&](double busy) {
+        return steps * std::max(k.step, 0.62 * k.work * busy / 170.0) + (spread ? 4.0 : 12.0);
+      };
+      const int64_t full = spread ? 0 : per_xcd / slots_xcd;
+      const int64_t left = spread ? ntiles * S : 8 * (per_xcd - full * slots_xcd);
+      const double rounds = (double)full + (left > 0 ? 1.0 : 0.0);
+      double us = (double)full * round_us((double)k.slots) + (left > 0 ? round_us((double)left) : 0.0);
+      // the workgroups of an XCD drift apart over long items and share less through its L2
+      us *= 1.0 + 0.06 * std::min(1.0, steps / 8192.0);
+      // the write-out of a round runs beside the multiplications of the next one
+      const double out = S > 1 ? (double)S * hbytes / 1.1e6 : 2.0 * hbytes / 4.5e6;
+      us = 4.0 + std::max(us + out / rounds * (rounds > 1.0 ? 0.5 : 1.0), out);
+      // one part per tile keeps the plain read-modify-write (bitwise reproducible): given up only
+      // for a gain of more than 3 %
+      if (us < best * (S == 1 ? 1.0 : 0.97)) {
+        best = us;
+        tile = k.tile;
+        a.nt = (int)nt;
+        a.ntiles = (int)ntiles;
+        a.nkt = (int)nkt;
+        a.nsplit = (int)S;
+        a.spread = spread ? 1 : 0;
+        grid = spread ? 8u * (unsigned)ceil_div(ntiles * S, 8) : 8u * (unsigned)per_xcd;
+      }
     }
   }
-  return best;
+  return tile;
 }
 
 thanos_status syrk_accumulate(hipStream_t s, float* H, int64_t b, const void* Xc,
@@ -480,24 +631,20 @@ thanos_status syrk_accumulate(hipStream_t s, float* H, int64_t b, const void* Xc
   a.n_tok = n_tok;
   a.ldx = ldx;
   a.alpha = alpha;
-  a.nt = (int)ceil_div(b, kSyTile);
-  a.ntiles = a.nt * (a.nt + 1) / 2;
-  a.nsplit = 1;
   const bool vec = (reinterpret_cast<uintptr_t>(Xc) % 16 == 0) && (ldx % 8 == 0) && (b % 8 == 0);
-  const size_t smem = vec ? (size_t)kDmaStages * kDmaStageBytes            // 136 KB
-                          : 2 * kSyOct * 512 * sizeof(u32x4);              // 128 KB
-  void (*kern)(SyrkArgs);
-  constexpr int kNW = 8;
-  if (xdt == THANOS_BF16) kern = vec ? k_syrk16_dma<true, kNW> : k_syrk16<true, false>;
-  else kern = vec ? k_syrk16_dma<false, kNW> : k_syrk16<false, false>;
+  unsigned grid = 0;
+  const int tile = plan(a, vec, grid);
+  void (*kern)(SyrkArgs) = nullptr;
+  size_t smem = 0;
+  const bool bf = xdt == THANOS_BF16;
+  if (!vec && tile == 256) kern = bf ? k_syrk16<true, 4> : k_syrk16<false, 4>, smem = kFbSmem<4>;
+  else if (!vec) kern = bf ? k_syrk16<true, 2> : k_syrk16<false, 2>, smem = kFbSmem<2>;
+  else if (tile == 256) kern = bf ? k_syrk16_dma<true, 256> : k_syrk16_dma<false, 256>, smem = DmaCfg<256>::smem;
+  else if (tile == 192) kern = bf ? k_syrk16_dma<true, 192> : k_syrk16_dma<false, 192>, smem = DmaCfg<192>::smem;
+  else kern = bf ? k_syrk16_dma<true, 128> : k_syrk16_dma<false, 128>, smem = DmaCfg<128>::smem;
   THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-  unsigned grid = (unsigned)a.ntiles;
-  if (vec) {
-    a.nsplit = choose_split(a.ntiles, (n_tok + kDmaKT - 1) / kDmaKT);
-    grid = 8u * (unsigned)((a.ntiles + 7) / 8) * (unsigned)a.nsplit;
-  }
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(vec ? 64 * kNW : 256), smem, s, a);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(vec ? 512 : 256), smem, s, a);
   THANOS_LAUNCH_CHECK();
   return THANOS_OK;
 }

@@ -77,3 +77,20 @@ def test_zero_tokens_is_noop():
     th.thanos_hessian_accumulate(H, X)
     torch.cuda.synchronize()
     assert float(H.sum()) == 64 * 64
+
+
+@pytest.mark.parametrize("b,T,dtype", [
+    (72, 17, "f16"), (128, 1000, "f16"), (136, 9000, "f16"), (1032, 2056, "f16"),   # 128-wide tiles
+    (3000, 700, "f16"), (2048, 5000, "f16"),                                        # 192-wide tiles
+    (4104, 300, "f16"),                                                             # 256-wide tiles
+    (7, 40, "f16"), (101, 3000, "f16"), (333, 9001, "f16"), (1365, 520, "f16"),     # any alignment
+    (130, 5000, "f32"), (129, 100, "f32")])                                         # fp32, in parts
+def test_tile_widths_and_token_parts(b, T, dtype):
+    """Whole tiles and tiles cut into parts of the tokens, with ragged edges of both.  Bound: T
+    products of 11 (fp32: 24) significant bits added in fp32, error ~ sqrt(T) 2^-24 relative."""
+    from tests.gpu_util import gpu_hessian
+    X = _x(b, T, dtype=dtype, seed=b)
+    print(f"hessian {dtype} b={b} T={T}", flush=True)
+    ref = orc.hessian(X)
+    H = gpu_hessian(X, alpha=0.5)
+    assert _relerr(H, 0.5 * ref) < max(1e-6, 2 * np.sqrt(T) * 2.0 ** -24)
