@@ -1258,30 +1258,34 @@ __global__ __launch_bounds__(64 * WPB, 2) void k_solve_mfma(SolveArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Mask + per-row solve for systems of 65..256 unknowns (block width <= 512): one workgroup of
-// four or eight wavefronts per row of W.  R_hat = G[q, q] is held in LDS as the lower triangle of a grid
-// of 32x32 tiles (padded with the identity past s) and factored by a right-looking blocked
-// Cholesky, R_hat = L L^T, 32 columns per step:
+// Mask + per-row solve for systems of up to 256 unknowns (block width <= 512) and beyond: one
+// workgroup of NW wavefronts per row of W.  R_hat = G[q, q], padded with the identity past s, is
+// factored tile by tile (32x32) with a right-looking blocked Cholesky, R_hat = L L^T, 32 columns
+// per step:
 //   1. one wavefront eliminates the diagonal tile with rank-1 MFMAs on its accumulator-layout
 //      copy (row k of a symmetric tile is both operands of D -= u u^T / d; two pivots per
-//      MFMA, see tl_pivots) and carries a second tile that starts as I along, which ends as
-//      T = L_pp^{-1} for a factor L_pp L_pp^T of the tile; T replaces the diagonal tile;
+//      MFMA, see tl_eliminate) and carries a second tile that starts as I along, which ends as
+//      T = L_pp^{-1} for a factor L_pp L_pp^T of the tile;
 //   2. the tiles below it become L_ip = A_ip T^T (one 32x32x32 product each), y_p = T u_p;
 //   3. the tiles right of the panel get A_il -= L_ip L_lp^T, the right-hand side u_i -= L_ip y_p;
 //      meanwhile one wavefront updates the next diagonal tile and runs step 1 on it (look-ahead:
 //      the elimination is a chain of dependent instructions, the rest is throughput work).
 // L^T lambda = y is then solved from the last tile row upwards with the same T tiles.
-// All products are fp32 MFMAs (v_mfma_f32_32x32x2_f32) on operands read from LDS.
+// All products are fp32 MFMAs (v_mfma_f32_32x32x2_f32).
+//
+// !BIG: the tiles live in the registers of the wavefronts that own them from the gather to the
+// back-substitution; LDS only carries T and the current panel.  What bounds a row is the chain of
+// eliminations (3.3 us per tile), so the number of rows in flight per compute unit is what
+// counts: a row of 256 unknowns takes 41 KB of LDS and half of the registers, two run at once;
+// with the tiles in LDS (152 KB) a row filled the unit.  4096 rows of 256 unknowns: 890 -> 530 us,
+// matrix pipes 44 % busy.  Rows of up to 128 unknowns: five per unit instead of three.
+// BIG: tiles in global memory.
 constexpr int kTlLd = 33;          // LDS row stride of a tile (conflict-free rows and columns)
 constexpr int kTlSz = 32 * kTlLd;  // floats per tile
 constexpr int kTlSmax = 256;       // largest system
 constexpr int kTlBw = 512;         // widest block
-constexpr int kTlExtra = 3 * kTlSmax + 128 + 16;  // u, lambda, q, pivot scratch, counters
 
 __host__ __device__ inline int tl_ntiles(int nt) { return nt * (nt + 1) / 2; }
-static inline size_t tl_smem_bytes(int nt) {
-  return ((size_t)tl_ntiles(nt) * kTlSz + kTlExtra) * sizeof(float);
-}
 __device__ __forceinline__ int tl_row(int r, int hi) { return 8 * (r >> 2) + 4 * hi + (r & 3); }
 __device__ __forceinline__ float* tl_tile(float* tiles, int i, int j) {
   return tiles + (i * (i + 1) / 2 + j) * kTlSz;
@@ -1299,7 +1303,7 @@ __device__ __forceinline__ void tl_mma(f32x16& acc, const float* pa, const float
   for (int e = 0; e < 16; ++e)
     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(sign * av[e], bv[e], acc, 0, 0, 0);
 }
-// Eliminates the symmetric tile D (accumulator layout) and writes T = F^{-1}, F F^T = D, to Dt.
+// Eliminates the symmetric tile D (accumulator layout) and leaves T = F^{-1}, F F^T = D, in E.
 // One wavefront.  Returns true if a pivot was not positive.
 //
 // Two pivots per MFMA.  In the accumulator layout rows k and k + 4 (k mod 8 < 4) sit in the same
@@ -1311,8 +1315,7 @@ __device__ __forceinline__ void tl_mma(f32x16& acc, const float* pa, const float
 // ones.  The same row operations applied to a tile that starts as I give T~; F is the Cholesky
 // factor in that pivot order (a row-permuted triangle).  Nothing downstream needs a triangle:
 // the panel products, the substitutions and the trailing updates only use T as a dense tile.
-__device__ __forceinline__ bool tl_pivots(f32x16 D, float* Dt, float* aux, int lo, int hi) {
-  f32x16 E;
+__device__ __forceinline__ bool tl_eliminate(f32x16 D, f32x16& E, float* aux, int lo, int hi) {
 #pragma unroll
   for (int r = 0; r < 16; ++r) E[r] = (tl_row(r, hi) == lo) ? 1.f : 0.f;
   const int pidx = 4 * (lo >> 3) + (lo & 3);  // pair that eliminates column lo
@@ -1357,8 +1360,228 @@ __device__ __forceinline__ bool tl_pivots(f32x16 D, float* Dt, float* aux, int l
   isd = fmaf(0.5f * isd, fmaf(-dl * isd, isd, 1.f), isd);
   aux[lo] = isd;  // both halves write the same value
 #pragma unroll
-  for (int r = 0; r < 16; ++r)  // F^{-1} = diag(1/sqrt(d)) T~
-    Dt[tl_row(r, hi) * kTlLd + lo] = E[r] * aux[tl_row(r, hi)];
+  for (int r = 0; r < 16; ++r) E[r] *= aux[tl_row(r, hi)];  // F^{-1} = diag(1/sqrt(d)) T~
+  return bad;
+}
+// The same with T written to the tile Dt (row stride kTlLd).
+__device__ __forceinline__ bool tl_pivots(const f32x16& D, float* Dt, float* aux, int lo, int hi) {
+  f32x16 E;
+  const bool bad = tl_eliminate(D, E, aux, lo, hi);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) Dt[tl_row(r, hi) * kTlLd + lo] = E[r];
+  return bad;
+}
+
+// ---- tiles in registers (!BIG) -------------------------------------------------------------
+// A tile X below the diagonal is held by one wavefront in OPERAND layout: register r of lane
+// (lo, hi) = X[lo][k], k = tl_row(r, hi).  That is at once what the two operands of an MFMA over k
+// look like (both sides take the k-values in the same permuted order) and, read as X^T, the
+// accumulator layout: L_ip^T = T A_ip^T and A_il^T -= L_lp L_ip^T go from registers to registers.
+// In LDS such a tile is [k / 4][row][k % 4] with kRsGroup floats per group: a lane's 16 values
+// are four 16-byte pieces, consecutive lanes are 16 bytes apart, and the 4-byte accesses of the
+// transposed view (lane <-> k) are 4 floats apart from group to group.
+// The tiles hold -A: then L' = (-A) T^T = -L, the trailing update is -A += L' L'^T without a
+// negation of an operand, u_i += L' y_p and y_j += L'^T lambda_p.
+constexpr int kRsGroup = 132;
+constexpr int kRsTile = 8 * kRsGroup;
+
+// Tiles (row << 4 | column) below the diagonal owned by each wavefront, one per byte, 0xff = none;
+// wavefront w also owns the diagonal tile w.  A wavefront never owns a tile whose column is at
+// or right of its diagonal tile (wavefront 0 apart, whose elimination comes first): when it runs
+// ahead on its diagonal tile it has no other trailing tile to update.  Within that, the tiles are
+// dealt so that the four SIMDs have about the same number of products in every step.
+__device__ const uint32_t kRsOwn8[8] = {0x76536241u, 0xffffff50u, 0xff312170u, 0x42715160u,
+                                        0x73326120u, 0x54637240u, 0x65744310u, 0x75645230u};
+__device__ const uint32_t kRsOwn4[4] = {0xffff3221u, 0xffffff20u, 0xffffff30u, 0xffff3110u};
+
+template <int NW>
+constexpr size_t rs_smem_floats() {  // panel + T, wrow, key, u, lambda, q, pivot scratch, counters
+  return (size_t)NW * kRsTile + 2 * kTlBw + 3 * 32 * NW + 64 + 2 * 8;
+}
+__device__ __forceinline__ void rs_store(float* tile, const f32x16& v, int lo, int hi) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    f32x4 x;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = v[4 * g + e];
+    *reinterpret_cast<f32x4*>(tile + (2 * g + hi) * kRsGroup + 4 * lo) = x;
+  }
+}
+// the transposed view of a tile in LDS: element (tl_row(r, hi), k = lo) is at rs_col()[rs_step(r)]
+__device__ __forceinline__ int rs_col(int lo, int hi) {
+  return (lo >> 2) * kRsGroup + (lo & 3) + 16 * hi;
+}
+__device__ __forceinline__ constexpr int rs_step(int r) { return 32 * (r >> 2) + 4 * (r & 3); }
+// acc += A B^T, A in LDS, B in LDS or in registers.  The operands come 16 bytes at a time: with
+// whole tiles of them the kernel does not fit 128 registers.
+__device__ __forceinline__ f32x4 rs_piece(const float* tile, int g, int lo, int hi) {
+  return *reinterpret_cast<const f32x4*>(tile + (2 * g + hi) * kRsGroup + 4 * lo);
+}
+__device__ __forceinline__ void rs_mma(f32x16& acc, const float* a, const float* b, int lo, int hi) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const f32x4 x = rs_piece(a, g, lo, hi), y = rs_piece(b, g, lo, hi);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], y[e], acc, 0, 0, 0);
+  }
+}
+__device__ __forceinline__ void rs_mma(f32x16& acc, const float* a, const f32x16& b, int lo, int hi) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const f32x4 x = rs_piece(a, g, lo, hi);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], b[4 * g + e], acc, 0, 0, 0);
+  }
+}
+// sum over all 32 values of tl_row(r, hi) of t[r] * v[tl_row(r, hi)], v in LDS (16-byte aligned);
+// every lane gets the sum of its column lo
+__device__ __forceinline__ float rs_sum_halves(float s) {
+  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(s), __float_as_uint(s), false, false);
+  return __uint_as_float(h[0]) + __uint_as_float(h[1]);
+}
+__device__ __forceinline__ float rs_dot(const f32x16& t, const float* v, int hi) {
+  float s = 0.f;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const f32x4 x = *reinterpret_cast<const f32x4*>(v + 8 * g + 4 * hi);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s = fmaf(t[4 * g + e], x[e], s);
+  }
+  return rs_sum_halves(s);
+}
+
+// Solves lambda R_hat = u for one row: nt tile rows, ns unknowns, R_hat[a][c] = G[q[a] * ldg + q[c]].
+// u (32 nt values, zero past ns) is overwritten, lam[0 : 32 nt] is the result.  tiles: NW * kRsTile
+// floats (and 2 * kTlBw more behind them that may be overwritten).  Called by all NW wavefronts,
+// u and q complete; barriers inside, lam is complete on return.  Returns true if a pivot was not positive.
+template <int NW>
+__device__ __forceinline__ bool rs_solve(const float* __restrict__ G, unsigned int ldg, const int* q, int ns,
+                                         int nt, float* tiles, float* u, float* lam, float* aux) {
+  constexpr int SL = NW == 8 ? 4 : 2;  // tiles below the diagonal per wavefront
+  const int lane = threadIdx.x & 63, lo = lane & 31, hi = lane >> 5;
+  // the wavefronts' parts rotate with the row, so that the eliminations of the rows that run on a
+  // compute unit at the same time do not meet on one SIMD
+  const int w = (__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) + (int)blockIdx.x) & (NW - 1);
+  const uint32_t own = (uint32_t)__builtin_amdgcn_readfirstlane((int)(NW == 8 ? kRsOwn8[w] : kRsOwn4[w]));
+  int ti[SL], tj[SL];
+#pragma unroll
+  for (int s = 0; s < SL; ++s) {
+    ti[s] = (own >> (8 * s + 4)) & 15;
+    tj[s] = (own >> (8 * s)) & 15;
+  }
+  float* Tt = tiles + (NW - 1) * kRsTile;
+
+  // ---- gather (all loads unconditional from clamped indices, masked afterwards) ----
+  f32x16 off[SL], dg;
+  auto fetch = [&](f32x16& v, int i, int j) {  // v[r] = G[q[32 j + row]][q[32 i + lo]]
+    const unsigned int qc = (unsigned int)q[min(32 * i + lo, ns - 1)];
+#pragma unroll
+    for (int r = 0; r < 16; ++r)  // 512 columns of at most 65535: the offset fits 32 bits
+      v[r] = G[(unsigned int)q[min(32 * j + tl_row(r, hi), ns - 1)] * ldg + qc];
+  };
+  if (w < nt) fetch(dg, w, w);
+#pragma unroll
+  for (int s = 0; s < SL; ++s)
+    if (ti[s] < nt) fetch(off[s], ti[s], tj[s]);
+  if (w < nt) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const bool in = 32 * w + lo < ns && 32 * w + tl_row(r, hi) < ns;
+      dg[r] = in ? -dg[r] : (tl_row(r, hi) == lo ? -1.f : 0.f);
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < SL; ++s)
+    if (ti[s] < nt) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) off[s][r] = (32 * ti[s] + lo < ns) ? -off[s][r] : 0.f;
+    }
+
+  bool bad = false;
+  __syncthreads();  // `tiles` is free (its previous contents have been read)
+  for (int p = 0; p < nt; ++p) {
+    int l = lo, h = hi;  // not known to be the same in every step: keeps lane masks and LDS addresses,
+    asm volatile("" : "+v"(l), "+v"(h));  // an instruction each, out of registers that outlive the step
+    // The owner of diagonal tile p eliminates it while the others are still in the trailing update
+    // of step p - 1 below (no barrier in between): T replaces the tile, in its registers and in LDS.
+    if (w == p) {
+      __builtin_amdgcn_s_setprio(3);  // the chain of eliminations is what the row waits for
+      f32x16 D;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) D[r] = -dg[r];
+      bad = tl_eliminate(D, dg, aux, l, h);
+      float* Tc = Tt + rs_col(l, hi);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) Tc[rs_step(r)] = dg[r];
+      __builtin_amdgcn_s_setprio(0);
+    }
+    __syncthreads();  // T_p is there; the panel of step p - 1 has been read
+#pragma unroll
+    for (int s = 0; s < SL; ++s)
+      if (tj[s] == p && ti[s] < nt) {
+        f32x16 C;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) C[r] = 0.f;
+        rs_mma(C, Tt, off[s], l, h);
+        off[s] = C;
+        rs_store(tiles + (ti[s] - 1) * kRsTile, C, l, h);
+      }
+    if (w == p) {  // y_p = T u_p
+      float y = 0.f;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x4 t = rs_piece(Tt, g, l, h);
+        const f32x4 x = *reinterpret_cast<const f32x4*>(u + 32 * p + 8 * g + 4 * h);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y = fmaf(t[e], x[e], y);
+      }
+      y = rs_sum_halves(y);
+      if (lane < 32) u[32 * p + lane] = y;
+    }
+    __syncthreads();  // panel and y_p are there
+    if (p + 1 == nt) break;
+    if (w > p && w < nt)
+      rs_mma(dg, tiles + (w - 1) * kRsTile, tiles + (w - 1) * kRsTile, l, h);
+#pragma unroll
+    for (int s = 0; s < SL; ++s) {
+      if (ti[s] < nt && tj[s] > p)
+        rs_mma(off[s], tiles + (tj[s] - 1) * kRsTile, tiles + (ti[s] - 1) * kRsTile, l, h);
+      if (ti[s] < nt && tj[s] == p) {  // u_i -= L_ip y_p (one tile per i in a step)
+        const float d = rs_dot(off[s], u + 32 * p, h);
+        if (lane < 32) u[32 * ti[s] + lane] += d;
+      }
+    }
+  }
+
+  // ---- L^T lambda = y, last tile row first.  The tiles are turned to lane <-> column first,
+  //      each wavefront through its own piece of LDS ----
+  {
+    float* mine = tiles + (threadIdx.x >> 6) * kRsTile;
+#pragma unroll
+    for (int s = 0; s < SL; ++s)
+      if (ti[s] < nt) {
+        rs_store(mine, off[s], lo, hi);
+        WAVE_SYNC();
+#pragma unroll
+        for (int r = 0; r < 16; ++r) off[s][r] = mine[rs_col(lo, hi) + rs_step(r)];
+        WAVE_SYNC();
+      }
+  }
+  for (int p = nt - 1; p >= 0; --p) {
+    if (w == p) {  // lambda_p = T^T y_p
+      const float l = rs_dot(dg, u + 32 * p, hi);
+      if (lane < 32) lam[32 * p + lane] = l;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < SL; ++s)
+      if (ti[s] == p) {  // y_j -= L_pj^T lambda_p
+        const float d = rs_dot(off[s], lam + 32 * p, hi);
+        if (lane < 32) u[32 * tj[s] + lane] += d;
+      }
+    __syncthreads();
+  }
   return bad;
 }
 
@@ -1421,14 +1644,13 @@ __device__ __forceinline__ void tl_matvec(const float* x, int bw, const float* _
   __syncthreads();
 }
 
-// BIG = false: tiles in LDS, one workgroup per row (grid = c), systems of up to 256 unknowns in
-// blocks of up to 512 columns.  BIG = true: the same algorithm for systems of up to kBigSmax
-// unknowns in blocks of up to kBigBw columns (the large blocks of the paper's block-size
-// ablation): the tile grid of a row no longer fits LDS and lives in global memory, one slot per
-// workgroup (a.tile_scratch, a.slot_floats; the slot of a workgroup stays in the caches of its
-// compute unit's XCD), and the gridDim.x workgroups walk the rows (row = blockIdx.x,
-// blockIdx.x + gridDim.x, ...).  The row's right-hand side, multipliers, indices and the
-// block's weights stay in LDS.
+// BIG = false: one workgroup per row (grid = c), systems of up to 32 NW unknowns in blocks of up to
+// 512 columns (rs_solve).  BIG = true: systems of up to kBigSmax unknowns in blocks of up to kBigBw
+// columns (the large blocks of the paper's block-size ablation): the tile grid of a row no longer
+// fits a compute unit and lives in global memory, one slot per workgroup (a.tile_scratch,
+// a.slot_floats; the slot of a workgroup stays in the caches of its compute unit's XCD), and the
+// gridDim.x workgroups walk the rows (row = blockIdx.x, blockIdx.x + gridDim.x, ...).  The row's
+// right-hand side, multipliers, indices and the block's weights stay in LDS.
 constexpr int kBigSmax = 2048;
 constexpr int kBigBw = 4096;
 static inline size_t tl_big_smem_bytes() {
@@ -1436,9 +1658,9 @@ static inline size_t tl_big_smem_bytes() {
 }
 
 template <int SEL, int NW, bool BIG = false>
-__global__ __launch_bounds__(64 * NW, (BIG ? 2 : (NW == 8 ? 4 : 3))) void k_solve_tiled(SolveArgs a) {
+__global__ __launch_bounds__(64 * NW, (BIG ? 2 : (NW == 8 ? 4 : 5))) void k_solve_tiled(SolveArgs a) {
   constexpr int NT = 64 * NW;       // threads
-  constexpr int SMAX = BIG ? kBigSmax : kTlSmax;
+  constexpr int SMAX = BIG ? kBigSmax : 32 * NW;
   constexpr int BW = BIG ? kBigBw : kTlBw;
   constexpr int CH = BW / NT;       // block columns per thread
   constexpr int RPT = 1024 / NT;    // tile elements per thread
@@ -1453,17 +1675,15 @@ __global__ __launch_bounds__(64 * NW, (BIG ? 2 : (NW == 8 ? 4 : 3))) void k_solv
     xtra = key + BW;
   } else {
     tiles = reinterpret_cast<float*>(solve_smem);
-    xtra = tiles + tl_ntiles(a.nt_max) * kTlSz;
-    // the block's weights and metric live in the tile area until the gather overwrites them, and
-    // the lambda row is assembled there after the solve (nt_max >= 3: room for 2 * kTlBw floats)
-    wrow = tiles;
-    key = tiles + BW;
+    wrow = tiles + NW * kRsTile;
+    key = wrow + BW;
+    xtra = key + BW;
   }
   float* u = xtra;                    // right-hand side, then y
   float* lam = xtra + SMAX;
   int* q = reinterpret_cast<int*>(xtra + 2 * SMAX);
   float* aux = xtra + 3 * SMAX;
-  int* cnt = reinterpret_cast<int*>(aux + 128);  // per wavefront and chunk: selected, ties
+  int* cnt = reinterpret_cast<int*>(aux + (BIG ? 128 : 64));  // per wavefront and chunk: selected, ties
   int* eqc = cnt + NC;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1566,11 +1786,11 @@ __global__ __launch_bounds__(64 * NW, (BIG ? 2 : (NW == 8 ? 4 : 3))) void k_solv
     const int col = tid + NT * ch;
     if (col < a.bw) a.mask_out[i * a.b + a.j1 + col] = sel[ch] ? 1 : 0;
   }
-  // A block may be solved by two launches with different LDS footprints: this one takes the
-  // rows with nt_lo <= ceil(ns/32) <= nt_max and leaves the others untouched.
+  // A block may be solved by two launches with different numbers of wavefronts per row: this one
+  // takes the rows with nt_lo <= ceil(ns/32) <= nt_max and leaves the others untouched.
   const int nt = (ns + 31) >> 5;
   const bool fits = ns <= SMAX;
-  if (fits ? (nt < a.nt_lo || nt > a.nt_max) : (32 * a.nt_max < SMAX)) {
+  if (fits ? (nt < a.nt_lo || nt > a.nt_max) : (32 * a.nt_max < (BIG ? SMAX : kTlSmax))) {
     if (BIG) continue;
     return;
   }
@@ -1606,9 +1826,9 @@ __global__ __launch_bounds__(64 * NW, (BIG ? 2 : (NW == 8 ? 4 : 3))) void k_solv
     return;
   }
   __syncthreads();
-  // partial sums of the complement's matrix-vector products: behind wrow and key in the tile
-  // area (nt_max >= 3: 6 tiles = 6336 floats >= 2 * 512 + 8 * 512)
-  float* part = BIG ? nullptr : tiles + 2 * BW;
+  // partial sums of the complement's matrix-vector products: in the tile area (NW * 1056 floats,
+  // of which they take NW * 512)
+  float* part = BIG ? nullptr : tiles;
   if (!comp) {
     for (int t = tid; t < 32 * nt; t += NT) u[t] = (t < s) ? wrow[q[t]] : 0.f;
   } else {
@@ -1620,15 +1840,19 @@ __global__ __launch_bounds__(64 * NW, (BIG ? 2 : (NW == 8 ? 4 : 3))) void k_solv
     tl_matvec<NW, BIG>(key, a.bw, a.Kc, a.ldk, wrow, part);
     for (int t = tid; t < 32 * nt; t += NT) u[t] = (t < ns) ? wrow[q[t]] : 0.f;
   }
-  __syncthreads();  // !BIG: wrow and key are dead from here on
+  __syncthreads();
 
+  bool bad = false;
+  // R_hat = G[q, q], or K[k, k] for the complement
+  const float* G = comp ? a.Kc : a.P + a.j1 * a.b + a.j1;
+  const int64_t ldg = comp ? (int64_t)a.ldk : a.b;
+  if constexpr (!BIG) {
+    if (ns > 0) bad = rs_solve<NW>(G, (unsigned int)ldg, q, ns, nt, tiles, u, lam, aux);
+  } else {
   // ---- gather R_hat into the tiles: thread <-> (rows tid/32 + (NT/32)e, column tid%32) of a tile;
   //      up to four tiles of a tile row are fetched together, all loads unconditional from
   //      clamped (valid) indices and masked when stored ----
   if (ns > 0) {
-    // R_hat = G[q, q], or K[k, k] for the complement
-    const float* G = comp ? a.Kc : a.P + a.j1 * a.b + a.j1;
-    const int64_t ldg = comp ? (int64_t)a.ldk : a.b;
     const int tr = tid >> 5, tc = tid & 31;
     for (int ti = 0; ti < nt; ++ti) {
       const float* grow[RPT];
@@ -1666,7 +1890,6 @@ __global__ __launch_bounds__(64 * NW, (BIG ? 2 : (NW == 8 ? 4 : 3))) void k_solv
   // ---- blocked Cholesky with look-ahead, forward substitution carried along.  The wavefront
   //      that eliminates a diagonal tile rotates, so that concurrent workgroups of a compute
   //      unit do not run this latency-bound step on the same SIMD. ----
-  bool bad = false;
   if (nt > 0 && wave == ((int)blockIdx.x & (NW - 1))) {
     f32x16 D;
 #pragma unroll
@@ -1741,7 +1964,6 @@ __global__ __launch_bounds__(64 * NW, (BIG ? 2 : (NW == 8 ? 4 : 3))) void k_solv
     }
     __syncthreads();
   }
-  if (bad && lane == 0) atomicCAS(a.info, 0, -(int32_t)min(i + 1, (int64_t)0x7fffffff));
 
   // ---- L^T lambda = y, last tile row first ----
   for (int p = nt - 1; p >= 0; --p) {
@@ -1762,6 +1984,8 @@ __global__ __launch_bounds__(64 * NW, (BIG ? 2 : (NW == 8 ? 4 : 3))) void k_solv
     }
     __syncthreads();
   }
+  }  // BIG
+  if (bad && lane == 0) atomicCAS(a.info, 0, -(int32_t)min(i + 1, (int64_t)0x7fffffff));
 
   // ---- lambda row: zeros except lambda_k at column q_k ----
   if (!comp) {
@@ -2220,33 +2444,18 @@ static void launch_solve(hipStream_t s, SolveArgs a, int smax) {
                        dim3((unsigned)std::min<int64_t>(a.c, kBigSlots)), dim3(64 * kNw),
                        tl_big_smem_bytes(), s, a);
   } else {
-    // LDS per row grows with the square of the tile rows; systems of up to 160 unknowns leave
-    // room for two workgroups per compute unit, so when s varies from row to row (and may be
-    // larger) the small rows get a launch of their own.
-    const int nt_all = std::max(3, (std::min(smax, kTlSmax) + 31) / 32);
-    constexpr int kNtTwo = 5;
-    const bool split = SEL != SEL_NM && nt_all > kNtTwo;
+    // Four wavefronts per row hold systems of up to 128 unknowns, eight up to 256.  When s varies
+    // from row to row and may be larger than 128, each size gets a launch and the rows pick theirs.
+    const size_t smem4 = rs_smem_floats<4>() * sizeof(float), smem8 = rs_smem_floats<8>() * sizeof(float);
+    const bool small = smax <= 128, varies = SEL != SEL_NM;
     a.nt_lo = 0;
-    a.nt_max = split ? kNtTwo : nt_all;
-    if (a.nt_max <= 4) {  // small footprint: three workgroups of four wavefronts per compute unit
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_solve_tiled<SEL, 4>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)tl_smem_bytes(4));
-      hipLaunchKernelGGL((k_solve_tiled<SEL, 4>), dim3((unsigned)a.c), dim3(256),
-                         tl_smem_bytes(a.nt_max), s, a);
-      return;
-    }
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_solve_tiled<SEL, 8>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)tl_smem_bytes(kTlSmax / 32));
-    hipLaunchKernelGGL((k_solve_tiled<SEL, 8>), dim3((unsigned)a.c), dim3(512),
-                       tl_smem_bytes(a.nt_max), s, a);
-    if (split) {
-      a.nt_lo = kNtTwo + 1;
-      a.nt_max = kTlSmax / 32;  // the launch that reports systems beyond the solver's limit
-      hipLaunchKernelGGL((k_solve_tiled<SEL, 8>), dim3((unsigned)a.c), dim3(512),
-                         tl_smem_bytes(a.nt_max), s, a);
-    }
+    a.nt_max = 4;
+    if (small || varies)
+      hipLaunchKernelGGL((k_solve_tiled<SEL, 4>), dim3((unsigned)a.c), dim3(256), smem4, s, a);
+    if (small) return;
+    a.nt_lo = varies ? 5 : 0;
+    a.nt_max = kTlSmax / 32;  // the launch that reports systems beyond the solver's limit
+    hipLaunchKernelGGL((k_solve_tiled<SEL, 8>), dim3((unsigned)a.c), dim3(512), smem8, s, a);
   }
 }
 

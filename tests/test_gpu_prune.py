@@ -315,6 +315,37 @@ def test_given_mask_with_empty_and_full_rows():
     assert rows.max() < 1e-3
 
 
+@pytest.mark.parametrize("given_factor", [False, True])  # with: every row direct, without: complement above half
+@pytest.mark.parametrize("B", [256, 200])
+def test_given_mask_with_every_tile_count(B, given_factor):
+    """Blocks wider than 128 columns: systems at the edges of the 32-column tiles, 0 to B unknowns."""
+    from tests.gpu_util import gpu_prune, gpu_factor
+    b = 2 * B
+    sizes = [s for t in range(0, B + 1, 32) for s in (t - 1, t, t + 1) if 0 <= s <= B] + [B - 1, B]
+    c = len(sizes)
+    W, H32 = _layer(c, b, 4 * b, "f32", seed=B)
+    g = np.random.default_rng(B)
+    M = np.zeros((c, b), np.uint8)
+    for i, s in enumerate(sizes):
+        M[i, g.permutation(B)[:s]] = 1
+        M[i, B + g.permutation(B)[:sizes[-1 - i]]] = 1
+    kw = {}
+    if given_factor:
+        U, xn2, info = gpu_factor(H32, 0.01)
+        assert info == 0
+        kw = dict(U=U, xnorm2=xn2)
+    Wg, Mg, info = gpu_prune(W, H32, mode="unstructured", p=0.5, B=B, mask_in=M, **kw)
+    assert info == 0
+    np.testing.assert_array_equal(Mg, M)
+    Wo, _ = orc.prune_fast(W, H32.astype(np.float64), mode="unstructured", p=0.5, B=B, damp=0.01,
+                           mask_in=M)
+    assert np.all(Wg[M == 1] == 0.0)
+    # fp32 solves of systems with condition numbers of some hundreds: errors of a few 1e-5 (the
+    # other parity tests of this file allow the same 1e-3)
+    rows = np.linalg.norm(Wg - Wo, axis=1) / np.maximum(np.linalg.norm(Wo, axis=1), 1e-30)
+    assert rows.max() < 1e-3
+
+
 def test_factor_reuse_matches_internal_factor():
     from tests.gpu_util import gpu_prune, gpu_factor
     W, H32 = _layer(64, 256, 1024, "f32", seed=6)
