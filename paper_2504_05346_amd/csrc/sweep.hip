@@ -37,47 +37,6 @@ __global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
   if (i < n) p[i] = v;
 }
 
-template <typename T>
-__device__ __forceinline__ float load_as_float(const T* p);
-template <>
-__device__ __forceinline__ float load_as_float<float>(const float* p) { return *p; }
-template <>
-__device__ __forceinline__ float load_as_float<__half>(const __half* p) { return __half2float(*p); }
-template <>
-__device__ __forceinline__ float load_as_float<__hip_bfloat16>(const __hip_bfloat16* p) {
-  return __bfloat162float(*p);
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void k_to_f32(const T* __restrict__ in, float* __restrict__ out,
-                                                int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) out[i] = load_as_float<T>(in + i);
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void k_from_f32(const float* __restrict__ in, T* __restrict__ out,
-                                                  int64_t n);
-template <>
-__global__ __launch_bounds__(256) void k_from_f32<__half>(const float* __restrict__ in,
-                                                          __half* __restrict__ out, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) out[i] = __float2half_rn(in[i]);
-}
-template <>
-__global__ __launch_bounds__(256) void k_from_f32<__hip_bfloat16>(const float* __restrict__ in,
-                                                                  __hip_bfloat16* __restrict__ out,
-                                                                  int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) out[i] = __float2bfloat16(in[i]);
-}
-template <>
-__global__ __launch_bounds__(256) void k_from_f32<float>(const float* __restrict__ in,
-                                                         float* __restrict__ out, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) out[i] = in[i];
-}
-
 __global__ __launch_bounds__(256) void k_sqrt(const float* __restrict__ xn2, float* __restrict__ sx,
                                               int64_t b) {
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -2235,7 +2194,7 @@ thanos_status row_outliers(hipStream_t s, const float* W, const float* H, int64_
   hipLaunchKernelGGL(k_lower_half_diag, dim3((unsigned)ceil_div(b, 256), (unsigned)b), dim3(256), 0,
                      s, H, b, Hf);
   THANOS_LAUNCH_CHECK();
-  thanos_status st = gemm_f32(s, false, true, c, b, b, 1.f, W, b, Hf, b, 0.f, T, b, false, true);
+  thanos_status st = gemm_f32(s, false, true, c, b, b, 1.f, W, b, Hf, b, 0.f, T, b, false, kTriLower);
   if (st != THANOS_OK) return st;
   hipLaunchKernelGGL(k_rowdot, dim3((unsigned)ceil_div(c, 4)), dim3(256), 0, s, T, W, c, b, h);
   THANOS_LAUNCH_CHECK();
@@ -2470,16 +2429,7 @@ thanos_status sweep_prepare(hipStream_t s, const void* W_in, thanos_dtype wdt, i
   const bool outliers = n_out > 0;
   const int smax_all = (o->mode == THANOS_NM && !o->mask_in) ? B / o->m * o->n : B;
   SweepWs w = carve_ws(ws, c, b, B, outliers, smax_all, sweep_uses_complement(o, b));
-  const int64_t n = c * b;
-  const unsigned nblk = (unsigned)ceil_div(n, 256);
-  if (wdt == THANOS_F32)
-    hipLaunchKernelGGL(k_to_f32<float>, dim3(nblk), dim3(256), 0, s, (const float*)W_in, W, n);
-  else if (wdt == THANOS_F16)
-    hipLaunchKernelGGL(k_to_f32<__half>, dim3(nblk), dim3(256), 0, s, (const __half*)W_in, W, n);
-  else
-    hipLaunchKernelGGL(k_to_f32<__hip_bfloat16>, dim3(nblk), dim3(256), 0, s,
-                       (const __hip_bfloat16*)W_in, W, n);
-  THANOS_LAUNCH_CHECK();
+  THANOS_CHECK(convert_in(s, W_in, wdt, W, c * b));
   if (outliers) {
     thanos_status st = row_outliers(s, W, H, c, b, n_out, w.Hf, w.T, w.h, w.row_skip);
     if (st != THANOS_OK) return st;
@@ -2497,8 +2447,6 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
   const int smax_all = (o->mode == THANOS_NM && !o->mask_in) ? B / o->m * o->n : B;
   const bool comp = sweep_uses_complement(o, b) && Lfac != nullptr;
   SweepWs w = carve_ws(ws, c, b, B, outliers, smax_all, sweep_uses_complement(o, b));
-  const int64_t n = c * b;
-  const unsigned nblk = (unsigned)ceil_div(n, 256);
 
   if (!prepared) {
     thanos_status st = sweep_prepare(s, W_in, wdt, c, b, H, o, n_out, W, ws);
@@ -2672,16 +2620,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
   if (pending_join >= 0) THANOS_CHECK(aux.join(pending_join));
 
   phase_mark(pt, THANOS_PHASE_FINALISE);
-  if (W_cast) {
-    if (wdt == THANOS_F32)
-      hipLaunchKernelGGL(k_from_f32<float>, dim3(nblk), dim3(256), 0, s, W, (float*)W_cast, n);
-    else if (wdt == THANOS_F16)
-      hipLaunchKernelGGL(k_from_f32<__half>, dim3(nblk), dim3(256), 0, s, W, (__half*)W_cast, n);
-    else
-      hipLaunchKernelGGL(k_from_f32<__hip_bfloat16>, dim3(nblk), dim3(256), 0, s, W,
-                         (__hip_bfloat16*)W_cast, n);
-    THANOS_LAUNCH_CHECK();
-  }
+  if (W_cast) THANOS_CHECK(convert_out(s, W, W_cast, wdt, c * b));
   return THANOS_OK;
 }
 
