@@ -18,6 +18,7 @@
 #include <algorithm>
 
 #include "gemm_tile_x3.h"
+#include "tile32.h"
 
 namespace thanos {
 
@@ -84,308 +85,257 @@ __global__ __launch_bounds__(256) void k_reverse_pad(const float* __restrict__ H
 }
 
 // ------------------------------------------------------------------------------------------
-// Cholesky factor and inverse of one NB x NB diagonal block, one workgroup of 4 wavefronts.
+// Cholesky factor and inverse of one NB x NB diagonal block, one workgroup of 8 wavefronts.
 //   in : lower triangle of A'[kb*NB .. , kb*NB ..]
-//   out: L_kk in the same place (lower triangle), Linv diagonal block = L_kk^{-1} (full
-//        square, zeros above the diagonal).
+//   out: L_kk in the same place (its diagonal 32-tiles with zeros above the diagonal, the tiles above
+//        them untouched), Linv diagonal block = L_kk^{-1} (full square, zeros above the diagonal).
 //
-// The block lives in LDS (S: A -> L, T: the inverse) and is processed in four steps of 32
-// columns.  Everything runs on the matrix cores, including the pivot loop:
-//
-//  * Pivot loop of step j (32 pivots, no barrier).  A 32x32 tile held in the accumulator
-//    layout of v_mfma_f32_32x32x2_f32 has row k in lanes (lo = column, hi = hk) of register rk.
-//    For a symmetric tile D that row is also column k, i.e. it is already laid out as BOTH
-//    operands of the rank-1 update D -= u u^T / d, u = D[k][:], d = u_k: one MFMA per pivot,
-//    no cross-lane traffic except the broadcast of d.  Column k of L is u / sqrt(d).
-//    Every wavefront keeps its own copy of the diagonal tile D and repeats that update, so
-//    that it can apply the same pivot to a second tile without talking to the others:
-//      wavefront 0     : T~ (starts as I), T~ -= (u/d) T~[k][:] for rows != k; after 32 pivots
-//                        T~ = L~^{-1} (unit lower), and L_jj^{-1} = diag(1/sqrt(d)) T~;
-//      wavefront w >= 1: the panel tile A_ij (i = j + w) held TRANSPOSED, so that its column k
-//                        is again row k of the register tile: A_ij^T -= u (A_ij[:,k] / d)^T;
-//                        column k of L_ij is A_ij[:,k] / sqrt(d).
-//  * Trailing update of the remaining lower tiles, A_il -= L_ij L_lj^T (i >= l > j), operands
-//    read from LDS.
-//  * After the four steps: the off-diagonal blocks of the inverse by recursive doubling over
-//    32- and 64-blocks, X21 = -T22 (L21 T11), with the strict upper tiles of S as scratch.
-constexpr int kCdLd = NB + 1;  // LDS row stride in floats: conflict-free rows and columns
-// S: the block (lower triangle = L in the end, strict upper 32-tiles = scratch and, later, the
-// off-diagonal tiles (1,0) and (3,2) of the inverse); Td: the four diagonal 32x32 tiles of the
-// inverse side by side (32 rows); 128 floats of scratch per wavefront.  85 KB: the kernel fits
-// next to one workgroup of the matrix-product kernels on a compute unit instead of waiting for
-// a whole unit to drain.
-constexpr size_t kCholDiagSmem = ((size_t)(NB + 32) * kCdLd + 4 * 128) * sizeof(float);
+// The whole chip waits for this kernel, so what counts is the length of its chain: four phases of
+// 32 pivots.  The block is a 4 x 4 grid of 32x32 tiles, all arithmetic is on them (tile32.h, rows and
+// columns of a tile in elimination order, so that pairs of pivots leave a true triangle).
+//   Wavefronts 0..3 (one per SIMD, raised priority) run the chain.  In phase j each holds a copy of
+//     the diagonal tile (j, j) and eliminates it with two pivots per MFMA; the same row operations
+//     turn a second tile into T_j = L_jj^{-1} (wavefront 0, from I) and into L_ij (wavefront i - j,
+//     from A_ij).  Between phases each applies L_*j to its copy of the next diagonal tile and to its
+//     next tile: registers in, registers out, one barrier per phase.
+//   Wavefronts 4..7 do the rest beside it: the trailing tiles two or more columns ahead, the stores
+//     of what is final, and the inverse by rows,
+//         X_ij = -T_i V_ij,  V_ij = sum_{j <= k < i} L_ik X_kj,  X_jj = T_j,
+//     with V of tile row i formed in phase i (before T_i is known), X of it in phase i + 1.
+// 23 us per block.  With one pivot per MFMA, LDS round trips of the tiles between the phases and the
+// inverse after them (four wavefronts) it was 34.5.
+constexpr int kCdL = 0, kCdT = 10, kCdA = 14, kCdTiles = 17;  // LDS tiles: L (i, j), T_j, A_22 A_32 A_33
+constexpr size_t kCholDiagSmem = ((size_t)kCdTiles * kRsTile + 4 * 32) * sizeof(float);
 
-__device__ __forceinline__ int cd_row(int r, int hi) { return 8 * (r >> 2) + 4 * hi + (r & 3); }
+__device__ __forceinline__ constexpr int cd_l(int i, int j) { return kCdL + i * (i + 1) / 2 + j; }
 
-// acc += sign * A[0:32, 0:32] * B, A[m][k] at pa[m*kCdLd + k];
-// B_KN: B[k][n] at pb[k*kCdLd + n], else B given as rows of n: B[k][n] at pb[n*kCdLd + k].
-// All 32 operand values of a lane are fetched before the first MFMA.
-template <bool B_KN>
-__device__ __forceinline__ void cd_tile_mma32(f32x16& acc, const float* pa, const float* pb,
-                                              float sign, int lo, int hi) {
-  float av[16], bv[16];
+// Global tile (p = its first element) <-> registers, rows and columns in elimination order.
+// nl = tl_nat(lo).
+__device__ __forceinline__ void cd_load_sym(f32x16& v, const float* p, int64_t ld, int nl, int hi) {
 #pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    av[q] = pa[lo * kCdLd + 2 * q + hi];
-    bv[q] = B_KN ? pb[(2 * q + hi) * kCdLd + lo] : pb[lo * kCdLd + 2 * q + hi];
+  for (int r = 0; r < 16; ++r) {  // only the lower triangle is valid
+    const int x = 8 * (r >> 2) + 2 * (r & 3) + hi;
+    v[r] = p[(int64_t)max(x, nl) * ld + min(x, nl)];
   }
-#pragma unroll
-  for (int q = 0; q < 16; ++q)
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(sign * av[q], bv[q], acc, 0, 0, 0);
 }
-__device__ __forceinline__ void cd_tile_load(f32x16& acc, const float* p, int lo, int hi) {
-#pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = p[cd_row(r, hi) * kCdLd + lo];
+__device__ __forceinline__ void cd_swap(float& a, float& b) {  // upper half of a <-> lower half of b
+  const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(s[0]);
+  b = __uint_as_float(s[1]);
 }
-__device__ __forceinline__ void cd_tile_store(float* p, const f32x16& acc, float scale, int lo,
-                                              int hi) {
+// operand layout; a lane reads 16-byte pieces of its row, whose even (odd) columns belong to the
+// lower (upper) half of the wavefront
+__device__ __forceinline__ void cd_load_op(f32x16& v, const float* p, int64_t ld, int nl, int hi) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) p[cd_row(r, hi) * kCdLd + lo] = scale * acc[r];
-}
-
-// The 32 pivots of one step for one wavefront.  ROLE 0: second tile is T~ (inverse of the
-// diagonal tile), ROLE 1: second tile is the transposed panel tile whose rows in S start at
-// `prow`.  `aux` points at this wavefront's 128 floats of LDS scratch.  Returns the first
-// non-positive pivot (or -1).
-//
-// A wavefront cannot overlap its own vector instructions with its own MFMAs, so the pivot loop
-// is kept to the bare chain: broadcast d, 1/d, the two operands, two MFMAs, one LDS write of
-// the UNSCALED column of L.  The scaling by 1/sqrt(d) is applied to the whole tile afterwards.
-template <int ROLE>
-__device__ __forceinline__ int cd_pivots(float* S, float* T, float* aux, int c0, int prow, int lo,
-                                         int hi) {
-  f32x16 D, E;
-  cd_tile_load(D, S + c0 * kCdLd + c0, lo, hi);
-  if (ROLE == 0) {
+  for (int g = 0; g < 4; ++g) {
+    const f32x4 f = *reinterpret_cast<const f32x4*>(p + (int64_t)nl * ld + 8 * g + 4 * hi);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) E[r] = (cd_row(r, hi) == lo) ? 1.f : 0.f;
-  } else {  // E[n][m] = A_ij[m][n]
-#pragma unroll
-    for (int r = 0; r < 16; ++r) E[r] = S[(prow + lo) * kCdLd + c0 + cd_row(r, hi)];
-  }
-  __syncthreads();  // every wavefront has its copy of D before L_jj overwrites it
-  float* ltile = S + (ROLE == 0 ? c0 : prow) * kCdLd + c0;  // the tile of L this wavefront writes
-  // key[h] = lo in the lanes that hold rows of half h (rows 4..7 mod 8 for h = 1), else -1:
-  // (key[hk] >= k) selects the lanes of row k with column >= k, (key[hk] >= 0) all of row k.
-  const int key[2] = {hi == 0 ? lo : -1, hi == 1 ? lo : -1};
-  // where column k of L goes: lane lo owns row lo of the tile; the other half writes to scratch
-  float* dst[2] = {hi == 0 ? ltile + lo * kCdLd : aux + 32 + lo,
-                   hi == 1 ? ltile + lo * kCdLd : aux + 32 + lo};
-  float dl = 1.f;  // pivot of column lo
-#pragma unroll
-  for (int k = 0; k < 32; ++k) {
-    const int rk = 4 * (k >> 3) + (k & 3), hk = (k >> 2) & 1;
-    const float d = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(D[rk]), k + 32 * hk));
-    const float rd = __builtin_amdgcn_rcpf(d);
-    const float u = (key[hk] >= k) ? D[rk] : 0.f;  // row k = column k of the reduced tile
-    const float au = -rd * u;
-    D = __builtin_amdgcn_mfma_f32_32x32x2f32(au, u, D, 0, 0, 0);
-    dl = (lo == k) ? d : dl;
-    const float ek = (key[hk] >= 0) ? E[rk] : 0.f;  // ROLE 0: T~[k][:], ROLE 1: A_ij[:, k]
-    if (ROLE == 0) {
-      const float a2 = (lo == k) ? 0.f : au;  // row k itself stays
-      dst[hk][k] = u;                         // L_jj[:, k] * sqrt(d)
-      E = __builtin_amdgcn_mfma_f32_32x32x2f32(a2, ek, E, 0, 0, 0);
-    } else {
-      dst[hk][k] = ek;                        // L_ij[:, k] * sqrt(d)
-      E = __builtin_amdgcn_mfma_f32_32x32x2f32(u, -rd * ek, E, 0, 0, 0);
+    for (int e = 0; e < 2; ++e) {
+      float a = f[2 * e], b = f[2 * e + 1];
+      cd_swap(a, b);
+      v[4 * g + e] = a;
+      v[4 * g + e + 2] = b;
     }
   }
-  // a non-positive pivot: report the first one (what was computed after it is garbage)
-  const unsigned long long badm = __ballot(!(dl > 0.f)) & 0xffffffffull;
-  const int bad = badm ? c0 + (__ffsll((long long)badm) - 1) : -1;
-  float isd = __builtin_amdgcn_rsqf(dl);
-  isd = fmaf(0.5f * isd, fmaf(-dl * isd, isd, 1.f), isd);
-  // columns of L: scale column lo by 1/sqrt(d_lo)
-  {
-    f32x16 C;
-    cd_tile_load(C, ltile, lo, hi);
-    cd_tile_store(ltile, C, isd, lo, hi);
-  }
-  if (ROLE == 0) {  // L_jj^{-1} = diag(1/sqrt(d)) T~
-    aux[lo] = isd;
+}
+__device__ __forceinline__ void cd_store_op(float* p, int64_t ld, const float* tile, int lo, int hi) {
+  const int nl = tl_nat(lo);
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
-      T[cd_row(r, hi) * kCdLd + c0 + lo] = E[r] * aux[cd_row(r, hi)];  // diagonal tile strip
+  for (int g = 0; g < 4; ++g) {
+    const f32x4 v = rs_piece(tile, g, lo, hi);
+    f32x4 f;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      float a = v[e], b = v[e + 2];
+      cd_swap(a, b);
+      f[2 * e] = a;
+      f[2 * e + 1] = b;
+    }
+    *reinterpret_cast<f32x4*>(p + (int64_t)nl * ld + 8 * g + 4 * hi) = f;
   }
-  return bad;
+}
+// accumulator layout
+__device__ __forceinline__ void cd_store_acc(float* p, int64_t ld, const f32x16& v, int nl, int hi) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+    p[(int64_t)(8 * (r >> 2) + 2 * (r & 3) + hi) * ld + nl] = v[r];
+}
+__device__ __forceinline__ f32x16 cd_get(const float* tile, int lo, int hi) {
+  f32x16 v;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const f32x4 x = rs_piece(tile, g, lo, hi);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[4 * g + e] = x[e];
+  }
+  return v;
+}
+__device__ __forceinline__ f32x16 cd_zero() {
+  f32x16 v;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) v[r] = 0.f;
+  return v;
+}
+// -T V for T in LDS (stored transposed, as it leaves the elimination) and V in accumulator layout
+__device__ __forceinline__ f32x16 cd_minus_tv(const float* T, const f32x16& V, int lo, int hi) {
+  f32x16 acc = cd_zero();
+  const float* t = T + rs_col(lo, hi);
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(-t[rs_step(r)], V[r], acc, 0, 0, 0);
+  return acc;
 }
 
-// Two wavefronts per SIMD at most: keeps the register budget at 256 so that the MFMA
-// accumulators stay in ordinary vector registers (they are read lane-wise every pivot).
-__global__ __launch_bounds__(256, 2) void k_chol_diag(float* __restrict__ Ap,
+// 512 threads at 128 registers: half of a compute unit's registers, so that the workgroup finds
+// room beside one workgroup of the matrix products.
+__global__ __launch_bounds__(512, 4) void k_chol_diag(float* __restrict__ Ap,
                                                       float* __restrict__ Linv, int64_t bp,
                                                       int kb_glob, int64_t b,
                                                       int32_t* __restrict__ info) {
   extern __shared__ __attribute__((aligned(16))) float cd_smem[];
-  float* S = cd_smem;
-  float* T = cd_smem + NB * kCdLd;  // Td: tile j of the inverse's diagonal at T + 32 j
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  float* aux = cd_smem + (NB + 32) * kCdLd + 128 * wave;  // per-wavefront scratch
-  const int lo = lane & 31, hi = lane >> 5;
+  const int lane = threadIdx.x & 63, lo = lane & 31, hi = lane >> 5, nl = tl_nat(lo);
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   float* A = Ap + ((int64_t)kb_glob * NB) * bp + (int64_t)kb_glob * NB;
   float* Li = Linv + ((int64_t)kb_glob * NB) * bp + (int64_t)kb_glob * NB;
+  auto S = [&](int t) { return cd_smem + t * kRsTile; };
+  auto Ag = [&](int i, int j) { return A + (int64_t)(32 * i) * bp + 32 * j; };
+  auto Xg = [&](int i, int j) { return Li + (int64_t)(32 * i) * bp + 32 * j; };
 
-  // lower triangle -> S, mirrored inside the diagonal 32x32 tiles (the pivot loop wants them
-  // symmetric); the strict upper 32-tiles stay undefined (scratch).  The first 32 columns are
-  // stored right away; the loads of the other 96 columns are issued now and stored to LDS after
-  // the first pivot loop, which does not touch them.
-  auto put = [&](int i, int c4, const float4& v) {
-    const float vv[4] = {v.x, v.y, v.z, v.w};
-    if (c4 <= i) {
+  if (wave < 4) {  // ------------------------------------------------------------------ chain
+    __builtin_amdgcn_s_setprio(3);
+    float* aux = cd_smem + kCdTiles * kRsTile + 32 * wave;
+    auto ident = [&]() {
+      f32x16 v;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int j = c4 + t;
-        if (j <= i) {
-          S[i * kCdLd + j] = vv[t];
-          if ((j >> 5) == (i >> 5)) S[j * kCdLd + i] = vv[t];
+      for (int r = 0; r < 16; ++r) v[r] = (tl_row(r, hi) == lo) ? 1.f : 0.f;
+      return v;
+    };
+    f32x16 D, E, D1, E1, U;
+    cd_load_sym(D, Ag(0, 0), bp, nl, hi);
+    if (wave == 0) E = ident();
+    else cd_load_op(E, Ag(wave, 0), bp, nl, hi);
+    cd_load_sym(D1, Ag(1, 1), bp, nl, hi);
+    if (wave == 0) E1 = ident();
+    else if (wave < 3) cd_load_op(E1, Ag(1 + wave, 1), bp, nl, hi);
+    int bad = -1;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      int l = lo, h = hi;  // lane masks: an instruction each, not worth registers across phases
+      asm volatile("" : "+v"(l), "+v"(h));
+      if (wave == 0) {
+        const float dl = tl_eliminate<true>(D, E, U, aux, l, h);
+        rs_store(S(cd_l(j, j)), U, lo, hi);
+        rs_store(S(kCdT + j), E, lo, hi);
+        // first non-positive pivot in the order of elimination (what follows it is garbage)
+        const float dn = __shfl(dl, (lo & ~7) + ((lo & 7) >> 1) + 4 * (lo & 1), 64);
+        const unsigned long long m = __ballot(!(dn > 0.f)) & 0xffffffffull;
+        if (m && bad < 0) bad = 32 * j + __ffsll((long long)m) - 1;
+      } else if (wave + j < 4) {
+        (void)tl_eliminate<false>(D, E, E, aux, l, h);
+        rs_store(S(cd_l(j + wave, j)), E, lo, hi);
+      }
+      __syncthreads();
+      if (j < 3) {
+        const float* Lj = S(cd_l(j + 1, j));
+        if (wave + j + 1 < 4) {  // copies of the next diagonal tile, and the next tile
+          if (j == 0) {
+            D = D1;
+            E = E1;
+          } else {
+            D = cd_get(S(j == 1 ? kCdA : kCdA + 2), lo, hi);
+            if (wave == 0) E = ident();
+            else E = cd_get(S(kCdA + 1), lo, hi);  // only j = 1, wave = 1: tile (3, 2)
+          }
+          rs_mma<true>(D, Lj, Lj, lo, hi);
+          if (wave > 0) rs_mma<true>(E, Lj, S(cd_l(j + 1 + wave, j)), lo, hi);
         }
       }
     }
-  };
-  constexpr int kVecA = NB * 8 / 256, kVecB = NB * 24 / 256;
-  float4 va[kVecA], vb[kVecB];
-#pragma unroll
-  for (int q = 0; q < kVecA; ++q) {
-    const int e = tid + 256 * q, i = e / 8, c4 = (e % 8) * 4;
-    va[q] = (c4 <= i) ? *reinterpret_cast<const float4*>(A + (int64_t)i * bp + c4)
-                      : make_float4(0.f, 0.f, 0.f, 0.f);
-  }
-#pragma unroll
-  for (int q = 0; q < kVecB; ++q) {
-    const int e = tid + 256 * q, i = e / 24, c4 = 32 + (e % 24) * 4;
-    vb[q] = (c4 <= i) ? *reinterpret_cast<const float4*>(A + (int64_t)i * bp + c4)
-                      : make_float4(0.f, 0.f, 0.f, 0.f);
-  }
-#pragma unroll
-  for (int q = 0; q < kVecA; ++q) {
-    const int e = tid + 256 * q;
-    put(e / 8, (e % 8) * 4, va[q]);
-  }
-  __syncthreads();
-
-  int badk = -1;
-  for (int j = 0; j < NB / 32; ++j) {
-    const int c0 = 32 * j;
-    const int ti = j + wave;  // panel tile row of wavefronts >= 1
-    if (wave == 0) {
-      const int bad = cd_pivots<0>(S, T, aux, c0, 0, lo, hi);
-      if (badk < 0) badk = bad;
-    } else if (ti < NB / 32) {
-      (void)cd_pivots<1>(S, T, aux, c0, 32 * ti, lo, hi);
-    } else {
-      __syncthreads();  // the barrier inside cd_pivots
+    if (bad >= 0 && lane == 0) {
+      const int64_t orig = b - ((int64_t)kb_glob * NB + bad);  // 1-based original column
+      atomicCAS(info, 0, (int32_t)(orig > 0 ? orig : 1));
     }
-    if (j == 0) {
-#pragma unroll
-      for (int q = 0; q < kVecB; ++q) {
-        const int e = tid + 256 * q;
-        put(e / 24, 32 + (e % 24) * 4, vb[q]);
-      }
-    }
-    __syncthreads();
-    // trailing tiles (i, l), j < l <= i < 4, dealt round-robin to the wavefronts
-    {
-      int t = 0;
-      for (int i = j + 1; i < NB / 32; ++i)
-        for (int l = j + 1; l <= i; ++l, ++t) {
-          if ((t & 3) != wave) continue;
-          f32x16 C;
-          float* pc = S + (32 * i) * kCdLd + 32 * l;
-          cd_tile_load(C, pc, lo, hi);
-          cd_tile_mma32<false>(C, S + (32 * i) * kCdLd + c0, S + (32 * l) * kCdLd + c0, -1.f, lo,
-                               hi);
-          cd_tile_store(pc, C, 1.f, lo, hi);
-        }
-    }
-    __syncthreads();
-  }
-  if (badk >= 0 && tid == 0) {
-    const int64_t orig = b - ((int64_t)kb_glob * NB + badk);  // 1-based original column
-    atomicCAS(info, 0, (int32_t)(orig > 0 ? orig : 1));
+    return;
   }
 
-  // inverse, 32 -> 64: pairs (0,1) and (2,3).  W = L21 T11 goes to the strict upper tile
-  // (p, p+1) of S and is then replaced, in place, by T21 = -T22 W (one wavefront, all operands
-  // are in registers before the result is stored).
-  if (wave < 2) {
-    const int p0 = 64 * wave, p1 = p0 + 32;
-    f32x16 C;
+  // --------------------------------------------------------------------------------- beside it
+  f32x16 X, V, Y;
+  if (wave == 4) cd_load_sym(X, Ag(2, 2), bp, nl, hi);
+  else if (wave == 5) cd_load_op(X, Ag(3, 2), bp, nl, hi);
+  else if (wave == 6) cd_load_sym(X, Ag(3, 3), bp, nl, hi);
+  else {
+    const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) C[r] = 0.f;
-    cd_tile_mma32<true>(C, S + p1 * kCdLd + p0, T + p0, 1.f, lo, hi);
-    float* w = S + p0 * kCdLd + p1;
-    cd_tile_store(w, C, 1.f, lo, hi);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) C[r] = 0.f;
-    cd_tile_mma32<true>(C, T + p1, w, 1.f, lo, hi);
-    cd_tile_store(w, C, -1.f, lo, hi);  // tile (1,0) of the inverse at S[0:32, 32:64], (3,2) at S[64:96, 96:128]
+    for (int q = 0; q < 24; ++q) {  // zeros of the inverse: tiles (0,1) (0,2) (0,3) (1,2) (1,3) (2,3)
+      const int t = q >> 2, i = t < 3 ? 0 : t < 5 ? 1 : 2, j = t < 3 ? t + 1 : t < 5 ? t - 1 : 3;
+      *reinterpret_cast<float4*>(Xg(i, j) + (int64_t)(8 * (q & 3) + (lane >> 3)) * bp + 4 * (lane & 7)) = z;
+    }
   }
-  __syncthreads();
-  // 64 -> 128: W = L[64:128, 0:64] T[0:64, 0:64] into S[0:64, 64:128], then
-  // T[64:128, 0:64] = -T[64:128, 64:128] W straight to global memory; one 32x32 tile per
-  // wavefront.  Tile (a, b) of a 64x64 block of the inverse: diagonal ones in the strip, the
-  // off-diagonal one in S as stored above.
-  {
-    const int ti = wave >> 1, tj = wave & 1;  // tile inside the 64x64 block
-    f32x16 C;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) C[r] = 0.f;
-    // T[0:64,0:64] is lower triangular: 32-blocks of k from tj
-    for (int kb = tj; kb < 2; ++kb) {
-      const float* t11 = (kb == tj) ? T + 32 * kb : S + 32;  // tile (kb, tj) of T[0:64, 0:64]
-      cd_tile_mma32<true>(C, S + (64 + 32 * ti) * kCdLd + 32 * kb, t11, 1.f, lo, hi);
-    }
-    cd_tile_store(S + (32 * ti) * kCdLd + 64 + 32 * tj, C, 1.f, lo, hi);
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < 16; ++r) C[r] = 0.f;
-    // T[64:128,64:128] is lower triangular: 32-blocks of k up to ti
-    for (int kb = 0; kb <= ti; ++kb) {
-      const float* t22 = (kb == ti) ? T + 64 + 32 * kb : S + 64 * kCdLd + 96;  // tile (ti, kb)
-      cd_tile_mma32<true>(C, t22, S + (32 * kb) * kCdLd + 64 + 32 * tj, 1.f, lo, hi);
-    }
-    float* g = Li + (int64_t)(64 + 32 * ti) * bp + 32 * tj;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) g[(int64_t)cd_row(r, hi) * bp + lo] = -C[r];
+  __syncthreads();  // ---- phase 1: column 0 of L and T_0 are there
+  if (wave == 4) {
+    rs_mma<true>(X, S(cd_l(2, 0)), S(cd_l(2, 0)), lo, hi);
+    rs_store(S(kCdA), X, lo, hi);
+    cd_store_acc(Xg(0, 0), bp, cd_get(S(kCdT), lo, hi), nl, hi);
+    cd_store_op(Ag(0, 0), bp, S(cd_l(0, 0)), lo, hi);
+  } else if (wave == 5) {
+    rs_mma<true>(X, S(cd_l(2, 0)), S(cd_l(3, 0)), lo, hi);
+    rs_store(S(kCdA + 1), X, lo, hi);
+    cd_store_op(Ag(1, 0), bp, S(cd_l(1, 0)), lo, hi);
+    cd_store_op(Ag(2, 0), bp, S(cd_l(2, 0)), lo, hi);
+  } else if (wave == 6) {
+    rs_mma<true>(X, S(cd_l(3, 0)), S(cd_l(3, 0)), lo, hi);
+    cd_store_op(Ag(3, 0), bp, S(cd_l(3, 0)), lo, hi);
+  } else {
+    V = cd_zero();
+    rs_mma<false>(V, S(cd_l(1, 0)), S(kCdT), lo, hi);  // V_10
   }
-  __syncthreads();
-  {
-    constexpr int kVec = NB * (NB / 4) / 256;
-    float4 l[kVec], t[kVec];
-#pragma unroll
-    for (int q = 0; q < kVec; ++q) {
-      const int e = tid + 256 * q, i = e / (NB / 4), c4 = (e % (NB / 4)) * 4;
-      float lv[4], tv[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int cc = c4 + u;
-        const bool low = cc <= i;
-        lv[u] = low ? S[i * kCdLd + cc] : 0.f;
-        // inverse: diagonal tiles from the strip, tiles (1,0) and (3,2) from the upper tiles of S
-        // (the lower left 64x64 quadrant is in global memory already and is skipped below)
-        const float* tp = ((i >> 5) == (cc >> 5)) ? T + (i & 31) * kCdLd + cc
-                                                  : S + (i - 32) * kCdLd + cc + 32;
-        tv[u] = (low && !(i >= 64 && cc < 64)) ? *tp : 0.f;
-      }
-      l[q] = make_float4(lv[0], lv[1], lv[2], lv[3]);
-      t[q] = make_float4(tv[0], tv[1], tv[2], tv[3]);
-    }
-#pragma unroll
-    for (int q = 0; q < kVec; ++q) {
-      const int e = tid + 256 * q, i = e / (NB / 4), c4 = (e % (NB / 4)) * 4;
-      if (c4 + 3 <= i) {
-        *reinterpret_cast<float4*>(A + (int64_t)i * bp + c4) = l[q];
-      } else {
-        const float lv[4] = {l[q].x, l[q].y, l[q].z, l[q].w};
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (c4 + u <= i) A[(int64_t)i * bp + c4 + u] = lv[u];
-      }
-      if (!(i >= 64 && c4 < 64)) *reinterpret_cast<float4*>(Li + (int64_t)i * bp + c4) = t[q];
-    }
+  __syncthreads();  // ---- phase 2: column 1 of L and T_1
+  if (wave == 4) {
+    V = cd_zero();
+    rs_mma<false>(V, S(cd_l(2, 1)), S(kCdT + 1), lo, hi);  // V_21
+  } else if (wave == 5) {
+    cd_store_acc(Xg(1, 1), bp, cd_get(S(kCdT + 1), lo, hi), nl, hi);
+    cd_store_op(Ag(1, 1), bp, S(cd_l(1, 1)), lo, hi);
+    cd_store_op(Ag(2, 1), bp, S(cd_l(2, 1)), lo, hi);
+    cd_store_op(Ag(3, 1), bp, S(cd_l(3, 1)), lo, hi);
+  } else if (wave == 6) {
+    rs_mma<true>(X, S(cd_l(3, 1)), S(cd_l(3, 1)), lo, hi);
+    rs_store(S(kCdA + 2), X, lo, hi);
+  } else {
+    X = cd_minus_tv(S(kCdT + 1), V, lo, hi);  // X_10
+    cd_store_acc(Xg(1, 0), bp, X, nl, hi);
+    V = cd_zero();
+    rs_mma<false>(V, S(cd_l(2, 0)), S(kCdT), lo, hi);
+    rs_mma<false>(V, S(cd_l(2, 1)), X, lo, hi);  // V_20
+  }
+  __syncthreads();  // ---- phase 3: column 2 of L and T_2
+  if (wave == 4) {
+    Y = cd_minus_tv(S(kCdT + 2), V, lo, hi);  // X_21
+    cd_store_acc(Xg(2, 1), bp, Y, nl, hi);
+    V = cd_zero();
+    rs_mma<false>(V, S(cd_l(3, 1)), S(kCdT + 1), lo, hi);
+    rs_mma<false>(V, S(cd_l(3, 2)), Y, lo, hi);  // V_31
+  } else if (wave == 5) {
+    V = cd_zero();
+    rs_mma<false>(V, S(cd_l(3, 2)), S(kCdT + 2), lo, hi);  // V_32
+  } else if (wave == 6) {
+    cd_store_acc(Xg(2, 2), bp, cd_get(S(kCdT + 2), lo, hi), nl, hi);
+    cd_store_op(Ag(2, 2), bp, S(cd_l(2, 2)), lo, hi);
+    cd_store_op(Ag(3, 2), bp, S(cd_l(3, 2)), lo, hi);
+  } else {
+    Y = cd_minus_tv(S(kCdT + 2), V, lo, hi);  // X_20
+    cd_store_acc(Xg(2, 0), bp, Y, nl, hi);
+    V = cd_zero();
+    rs_mma<false>(V, S(cd_l(3, 0)), S(kCdT), lo, hi);
+    rs_mma<false>(V, S(cd_l(3, 1)), X, lo, hi);
+    rs_mma<false>(V, S(cd_l(3, 2)), Y, lo, hi);  // V_30
+  }
+  __syncthreads();  // ---- L_33 and T_3
+  if (wave == 6) {
+    cd_store_acc(Xg(3, 3), bp, cd_get(S(kCdT + 3), lo, hi), nl, hi);
+    cd_store_op(Ag(3, 3), bp, S(cd_l(3, 3)), lo, hi);
+  } else {  // wavefronts 7, 4, 5: X_30, X_31, X_32
+    cd_store_acc(Xg(3, wave == 7 ? 0 : wave - 3), bp, cd_minus_tv(S(kCdT + 3), V, lo, hi), nl, hi);
   }
 }
 
@@ -544,7 +494,7 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
   };
   int pending_join = -1;  // event index recorded on the aux stream after the last "rest"
   for (int k = 0; k < nb; ++k) {
-    hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(256), kCholDiagSmem, s, Ap, Linv, bp, k, b, info);
+    hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(512), kCholDiagSmem, s, Ap, Linv, bp, k, b, info);
     THANOS_LAUNCH_CHECK();
     const int64_t rem = bp - (int64_t)(k + 1) * NB;
     if (rem <= 0) {

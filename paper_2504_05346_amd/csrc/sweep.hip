@@ -13,6 +13,7 @@
 #include <cmath>
 
 #include "gemm_tile_x3.h"
+#include "tile32.h"
 
 namespace thanos {
 
@@ -22,13 +23,6 @@ namespace thanos {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); \
     __builtin_amdgcn_wave_barrier();                       \
   } while (0)
-
-// The value of lane (l & 31) for every lane l: the lower half of the wavefront broadcast to the
-// upper half (one v_permlane32_swap, no trip through LDS).
-__device__ __forceinline__ float lower_half(float v) {
-  const unsigned int u = __float_as_uint(v);
-  return __uint_as_float(__builtin_amdgcn_permlane32_swap(u, u, false, false)[0]);
-}
 
 // ------------------------------------------------------------------------------------------
 // small helpers
@@ -1245,7 +1239,6 @@ constexpr int kTlSmax = 256;       // largest system
 constexpr int kTlBw = 512;         // widest block
 
 __host__ __device__ inline int tl_ntiles(int nt) { return nt * (nt + 1) / 2; }
-__device__ __forceinline__ int tl_row(int r, int hi) { return 8 * (r >> 2) + 4 * hi + (r & 3); }
 __device__ __forceinline__ float* tl_tile(float* tiles, int i, int j) {
   return tiles + (i * (i + 1) / 2 + j) * kTlSz;
 }
@@ -1262,88 +1255,23 @@ __device__ __forceinline__ void tl_mma(f32x16& acc, const float* pa, const float
   for (int e = 0; e < 16; ++e)
     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(sign * av[e], bv[e], acc, 0, 0, 0);
 }
-// Eliminates the symmetric tile D (accumulator layout) and leaves T = F^{-1}, F F^T = D, in E.
-// One wavefront.  Returns true if a pivot was not positive.
-//
-// Two pivots per MFMA.  In the accumulator layout rows k and k + 4 (k mod 8 < 4) sit in the same
-// register, in the lower and in the upper half of the wavefront: exactly where the two
-// reduction slots of v_mfma_f32_32x32x2_f32 take their operands from.  The pivots are therefore
-// taken in the order 0,4,1,5,2,6,3,7,8,12,...: with u1 = row k and u2 = row k + 4 AFTER the
-// elimination of k (u2 = D[k+4] - (D[k][k+4] / d1) u1; the lower half's row is fetched with one
-// cross-lane read), D -= u1 u1^T / d1 + u2 u2^T / d2 is one MFMA instead of two half-empty
-// ones.  The same row operations applied to a tile that starts as I give T~; F is the Cholesky
-// factor in that pivot order (a row-permuted triangle).  Nothing downstream needs a triangle:
-// the panel products, the substitutions and the trailing updates only use T as a dense tile.
-__device__ __forceinline__ bool tl_eliminate(f32x16 D, f32x16& E, float* aux, int lo, int hi) {
-#pragma unroll
-  for (int r = 0; r < 16; ++r) E[r] = (tl_row(r, hi) == lo) ? 1.f : 0.f;
-  const int pidx = 4 * (lo >> 3) + (lo & 3);  // pair that eliminates column lo
-  float dl = 1.f;                             // pivot of column lo
-#pragma unroll
-  for (int t = 0; t < 16; ++t) {              // pair t: rows k1 and k2 = k1 + 4, both in D[t]
-    const int k1 = 8 * (t >> 2) + (t & 3), k2 = k1 + 4;
-    const float v = D[t];                     // lower half: D[k1][lo], upper half: D[k2][lo]
-    const float x = lower_half(v);        // D[k1][lo] in both halves
-    const float d1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k1));
-    const float c12 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k2));
-    const float d2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32 + k2));
-    // 1 / d1 and 1 / d2' (d2' = d2 - c12^2 / d1, the pivot of k2 after the elimination of k1)
-    // from two INDEPENDENT reciprocals, of d1 and of det = d1 d2 - c12^2: d2' = det / d1.  The
-    // wavefront is alone on this chain, so its length is what counts.
-    const float det = fmaf(d1, d2, -c12 * c12);
-    const float q1 = __builtin_amdgcn_rcpf(d1);
-    const float qd = __builtin_amdgcn_rcpf(det);
-    const float r1 = fmaf(fmaf(-d1, q1, 1.f), q1, q1);
-    const float rd = fmaf(fmaf(-det, qd, 1.f), qd, qd);
-    const float m = c12 * r1;
-    const float d2p = det * r1;
-    const float r2 = d1 * rd;
-    const float mh = hi ? m : 0.f;
-    // second operands: u1 in the lower half, u2 in the upper half; columns eliminated by
-    // earlier pairs are zero, and so is column k1 of u2
-    const bool live = pidx >= t && !(hi && lo == k1);
-    const float bop = live ? fmaf(-mh, x, v) : 0.f;
-    const float aop = bop * (hi ? -r2 : -r1);
-    D = __builtin_amdgcn_mfma_f32_32x32x2f32(aop, bop, D, 0, 0, 0);
-    dl = (lo == k1) ? d1 : (lo == k2) ? d2p : dl;
-    // the same row operations on T~: row k1 as it is, row k2 after the operation of k1; the
-    // pivot rows themselves stay
-    const float ev = E[t];
-    const float xe = lower_half(ev);
-    const float be = fmaf(-mh, xe, ev);
-    const float a2 = (lo == (hi ? k2 : k1)) ? 0.f : aop;
-    E = __builtin_amdgcn_mfma_f32_32x32x2f32(a2, be, E, 0, 0, 0);
-  }
-  const bool bad = __ballot(!(dl > 0.f)) != 0ull;
-  float isd = __builtin_amdgcn_rsqf(dl);
-  isd = fmaf(0.5f * isd, fmaf(-dl * isd, isd, 1.f), isd);
-  aux[lo] = isd;  // both halves write the same value
-#pragma unroll
-  for (int r = 0; r < 16; ++r) E[r] *= aux[tl_row(r, hi)];  // F^{-1} = diag(1/sqrt(d)) T~
-  return bad;
-}
 // The same with T written to the tile Dt (row stride kTlLd).
 __device__ __forceinline__ bool tl_pivots(const f32x16& D, float* Dt, float* aux, int lo, int hi) {
   f32x16 E;
-  const bool bad = tl_eliminate(D, E, aux, lo, hi);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) E[r] = (tl_row(r, hi) == lo) ? 1.f : 0.f;
+  const float dl = tl_eliminate<false>(D, E, E, aux, lo, hi);
+  const bool bad = __ballot(!(dl > 0.f)) != 0ull;
 #pragma unroll
   for (int r = 0; r < 16; ++r) Dt[tl_row(r, hi) * kTlLd + lo] = E[r];
   return bad;
 }
 
 // ---- tiles in registers (!BIG) -------------------------------------------------------------
-// A tile X below the diagonal is held by one wavefront in OPERAND layout: register r of lane
-// (lo, hi) = X[lo][k], k = tl_row(r, hi).  That is at once what the two operands of an MFMA over k
-// look like (both sides take the k-values in the same permuted order) and, read as X^T, the
-// accumulator layout: L_ip^T = T A_ip^T and A_il^T -= L_lp L_ip^T go from registers to registers.
-// In LDS such a tile is [k / 4][row][k % 4] with kRsGroup floats per group: a lane's 16 values
-// are four 16-byte pieces, consecutive lanes are 16 bytes apart, and the 4-byte accesses of the
-// transposed view (lane <-> k) are 4 floats apart from group to group.
+// A tile below the diagonal is held by one wavefront in operand layout (tile32.h):
+// L_ip^T = T A_ip^T and A_il^T -= L_lp L_ip^T go from registers to registers.
 // The tiles hold -A: then L' = (-A) T^T = -L, the trailing update is -A += L' L'^T without a
 // negation of an operand, u_i += L' y_p and y_j += L'^T lambda_p.
-constexpr int kRsGroup = 132;
-constexpr int kRsTile = 8 * kRsGroup;
-
 // Tiles (row << 4 | column) below the diagonal owned by each wavefront, one per byte, 0xff = none;
 // wavefront w also owns the diagonal tile w.  A wavefront never owns a tile whose column is at
 // or right of its diagonal tile (wavefront 0 apart, whose elimination comes first): when it runs
@@ -1356,42 +1284,6 @@ __device__ const uint32_t kRsOwn4[4] = {0xffff3221u, 0xffffff20u, 0xffffff30u, 0
 template <int NW>
 constexpr size_t rs_smem_floats() {  // panel + T, wrow, key, u, lambda, q, pivot scratch, counters
   return (size_t)NW * kRsTile + 2 * kTlBw + 3 * 32 * NW + 64 + 2 * 8;
-}
-__device__ __forceinline__ void rs_store(float* tile, const f32x16& v, int lo, int hi) {
-#pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    f32x4 x;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) x[e] = v[4 * g + e];
-    *reinterpret_cast<f32x4*>(tile + (2 * g + hi) * kRsGroup + 4 * lo) = x;
-  }
-}
-// the transposed view of a tile in LDS: element (tl_row(r, hi), k = lo) is at rs_col()[rs_step(r)]
-__device__ __forceinline__ int rs_col(int lo, int hi) {
-  return (lo >> 2) * kRsGroup + (lo & 3) + 16 * hi;
-}
-__device__ __forceinline__ constexpr int rs_step(int r) { return 32 * (r >> 2) + 4 * (r & 3); }
-// acc += A B^T, A in LDS, B in LDS or in registers.  The operands come 16 bytes at a time: with
-// whole tiles of them the kernel does not fit 128 registers.
-__device__ __forceinline__ f32x4 rs_piece(const float* tile, int g, int lo, int hi) {
-  return *reinterpret_cast<const f32x4*>(tile + (2 * g + hi) * kRsGroup + 4 * lo);
-}
-__device__ __forceinline__ void rs_mma(f32x16& acc, const float* a, const float* b, int lo, int hi) {
-#pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    const f32x4 x = rs_piece(a, g, lo, hi), y = rs_piece(b, g, lo, hi);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], y[e], acc, 0, 0, 0);
-  }
-}
-__device__ __forceinline__ void rs_mma(f32x16& acc, const float* a, const f32x16& b, int lo, int hi) {
-#pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    const f32x4 x = rs_piece(a, g, lo, hi);
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], b[4 * g + e], acc, 0, 0, 0);
-  }
 }
 // sum over all 32 values of tl_row(r, hi) of t[r] * v[tl_row(r, hi)], v in LDS (16-byte aligned);
 // every lane gets the sum of its column lo
@@ -1469,7 +1361,9 @@ __device__ __forceinline__ bool rs_solve(const float* __restrict__ G, unsigned i
       f32x16 D;
 #pragma unroll
       for (int r = 0; r < 16; ++r) D[r] = -dg[r];
-      bad = tl_eliminate(D, dg, aux, l, h);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dg[r] = (tl_row(r, h) == l) ? 1.f : 0.f;
+      bad = __ballot(!(tl_eliminate<false>(D, dg, dg, aux, l, h) > 0.f)) != 0ull;
       float* Tc = Tt + rs_col(l, hi);
 #pragma unroll
       for (int r = 0; r < 16; ++r) Tc[rs_step(r)] = dg[r];
@@ -1482,7 +1376,7 @@ __device__ __forceinline__ bool rs_solve(const float* __restrict__ G, unsigned i
         f32x16 C;
 #pragma unroll
         for (int r = 0; r < 16; ++r) C[r] = 0.f;
-        rs_mma(C, Tt, off[s], l, h);
+        rs_mma<false>(C, Tt, off[s], l, h);
         off[s] = C;
         rs_store(tiles + (ti[s] - 1) * kRsTile, C, l, h);
       }
@@ -1501,11 +1395,11 @@ __device__ __forceinline__ bool rs_solve(const float* __restrict__ G, unsigned i
     __syncthreads();  // panel and y_p are there
     if (p + 1 == nt) break;
     if (w > p && w < nt)
-      rs_mma(dg, tiles + (w - 1) * kRsTile, tiles + (w - 1) * kRsTile, l, h);
+      rs_mma<false>(dg, tiles + (w - 1) * kRsTile, tiles + (w - 1) * kRsTile, l, h);
 #pragma unroll
     for (int s = 0; s < SL; ++s) {
       if (ti[s] < nt && tj[s] > p)
-        rs_mma(off[s], tiles + (tj[s] - 1) * kRsTile, tiles + (ti[s] - 1) * kRsTile, l, h);
+        rs_mma<false>(off[s], tiles + (tj[s] - 1) * kRsTile, tiles + (ti[s] - 1) * kRsTile, l, h);
       if (ti[s] < nt && tj[s] == p) {  // u_i -= L_ip y_p (one tile per i in a step)
         const float d = rs_dot(off[s], u + 32 * p, h);
         if (lane < 32) u[32 * ti[s] + lane] += d;

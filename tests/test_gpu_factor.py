@@ -53,3 +53,28 @@ def test_not_positive_definite_is_reported():
     H32[100, 100] = -1.0
     _, _, info = gpu_factor(H32, 0.0)
     assert info > 0
+
+
+@pytest.mark.parametrize("b", [1, 31, 33, 97, 129, 2944, 3200])
+def test_factor_tile_edges(b):
+    """One block that is mostly padding, 32-tiles cut at their edges, and the sizes at which the
+    narrow updates pass from one product kernel to the other (1024 tiles of 32 x 32)."""
+    from tests.gpu_util import gpu_factor
+    H32 = _h(b, T=2 * b + 64, seed=b)
+    U, _, info = gpu_factor(H32, 0.01)
+    assert info == 0
+    assert np.all(np.tril(U, -1) == 0.0)
+    Uref = orc.inverse_factor(orc.damped(H32.astype(np.float64), 0.01))
+    # condition numbers of some thousands at 2 b tokens: some 1e3 * 2^-24, as in the test above
+    assert np.linalg.norm(U - Uref) <= 2e-4 * np.linalg.norm(Uref)
+
+
+@pytest.mark.parametrize("col", [0, 1, 4, 5, 31, 32, 70, 127, 128, 200])
+def test_first_bad_pivot_is_named(col):
+    """The elimination runs from the last column backwards: the first pivot that fails is that of the
+    one negative entry of a diagonal matrix, wherever it sits in its pair, tile and block."""
+    from tests.gpu_util import gpu_factor
+    H32 = np.diag(np.linspace(1.0, 2.0, 256)).astype(np.float32)
+    H32[col, col] = -1.0
+    _, _, info = gpu_factor(H32, 0.0)
+    assert info == col + 1
