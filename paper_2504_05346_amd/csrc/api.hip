@@ -14,7 +14,8 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
                     const float* H, const float* U, const float* xnorm2,
                     const thanos_prune_opts* o, long long r_total, long long n_out, float* W,
                     void* W_cast, uint8_t* mask, void* ws, int32_t* info, bool single_stream,
-                    PhaseTimer* pt, const float* Lfac, int64_t ldL, bool prepared);
+                    PhaseTimer* pt, const float* Lfac, int64_t ldL, bool prepared,
+                    bool clear_info);
 thanos_status sweep_prepare(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c, int64_t b,
                             const float* H, const thanos_prune_opts* o, long long n_out, float* W,
                             void* ws);
@@ -23,7 +24,6 @@ thanos_status structured(hipStream_t st, const void* W_in, thanos_dtype wdt, int
                          const float* H, float damping, long long s_cols, long long n_out,
                          float* W, void* W_cast, uint8_t* mask, void* ws, int32_t* info,
                          bool single_stream);
-__global__ void k_zero_info(int32_t* info) { *info = 0; }
 }  // namespace thanos
 
 using namespace thanos;
@@ -359,14 +359,18 @@ static thanos_status prune_with_workspace(const void* W_in, thanos_dtype wdt, in
   // The working copy of the weights and the ranking of the row losses need nothing from the
   // factorisation: with a factor to compute they run beside it on a helper stream (the chain
   // of diagonal blocks leaves most of the chip idle) and are joined before the sweep.
-  AuxStream prep(s, (!U && !single_stream) ? 2 : 0, single_stream);
+  // Without row losses and with few weights that is a conversion of some microseconds: less than
+  // the two hops between streams (about 10 us each at the caller's end), so the sweep does it itself.
+  constexpr int64_t kPrepWeights = (int64_t)1 << 23;  // 4096 x 2048: 10 us
+  const bool beside = !U && !single_stream && (n_out > 0 || c * b > kPrepWeights);
+  AuxStream prep(s, beside ? 2 : 0, single_stream);
   if (!prep.ok) return THANOS_ERR_HIP;
   if (!U) {
     float* Uw = reinterpret_cast<float*>(p);
     p += align_up((size_t)b * b * sizeof(float), 256);
     float* xw = reinterpret_cast<float*>(p);
     p += align_up((size_t)b * sizeof(float), 256);
-    if (!single_stream) {
+    if (beside) {
       THANOS_CHECK(prep.fork(0));
       thanos_status sp = sweep_prepare(prep.stream, W_in, wdt, c, b, H, opts, n_out, W_out, sweep_ws);
       if (sp != THANOS_OK) return sp;
@@ -379,13 +383,11 @@ static thanos_status prune_with_workspace(const void* W_in, thanos_dtype wdt, in
     U = Uw;
     xn2 = xw;
     Lfac = factor_L(p, b, &ldL);
-  } else {
-    hipLaunchKernelGGL(k_zero_info, dim3(1), dim3(1), 0, s, info_dev);
-    THANOS_LAUNCH_CHECK();
   }
   phase_mark(pt, THANOS_PHASE_PREP);
   thanos_status st = sweep(s, W_in, wdt, c, b, H, U, xn2, opts, r_total, n_out, W_out, W_out_cast,
-                           mask_out, sweep_ws, info_dev, single_stream, pt, Lfac, ldL, prepared);
+                           mask_out, sweep_ws, info_dev, single_stream, pt, Lfac, ldL, prepared,
+                           opts->factor_in != nullptr);
   if (pt) {
     const thanos_status tc = pt->collect(opts->phase_ms_out);
     if (st == THANOS_OK) st = tc;

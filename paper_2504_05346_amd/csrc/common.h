@@ -207,9 +207,8 @@ struct __attribute__((aligned(4 * sizeof(T)))) Quad {
 // Four elements per thread as one load and one store where both pointers allow it (vec), else one
 // by one; one element per thread kept memory at 2.6 TB/s.
 template <typename I, typename O>
-__global__ __launch_bounds__(256) void k_convert(const I* __restrict__ in, O* __restrict__ out,
-                                                 int64_t n, int vec) {
-  const int64_t i = 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x);
+__device__ __forceinline__ void convert_quad(const I* __restrict__ in, O* __restrict__ out, int64_t i,
+                                             int64_t n, int vec) {
   if (i >= n) return;
   if (vec && i + 4 <= n) {
     const Quad<I> x = *reinterpret_cast<const Quad<I>*>(in + i);
@@ -222,26 +221,35 @@ __global__ __launch_bounds__(256) void k_convert(const I* __restrict__ in, O* __
   }
 }
 template <typename I, typename O>
-static inline void launch_convert(hipStream_t s, const void* in, void* out, int64_t n) {
-  const int vec = reinterpret_cast<uintptr_t>(in) % sizeof(Quad<I>) == 0 &&
-                  reinterpret_cast<uintptr_t>(out) % sizeof(Quad<O>) == 0;
+__global__ __launch_bounds__(256) void k_convert(const I* __restrict__ in, O* __restrict__ out,
+                                                 int64_t n, int vec) {
+  convert_quad(in, out, 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x), n, vec);
+}
+static inline int convert_vec(const void* in, thanos_dtype it, const void* out, thanos_dtype ot) {
+  const uintptr_t ia = it == THANOS_F32 ? 16 : 8, oa = ot == THANOS_F32 ? 16 : 8;
+  return reinterpret_cast<uintptr_t>(in) % ia == 0 && reinterpret_cast<uintptr_t>(out) % oa == 0;
+}
+template <typename I, typename O>
+static inline void launch_convert(hipStream_t s, const void* in, void* out, int64_t n, int vec) {
   hipLaunchKernelGGL((k_convert<I, O>), dim3((unsigned)ceil_div(n, 1024)), dim3(256), 0, s,
                      (const I*)in, (O*)out, n, vec);
 }
 // W (fp32) <- weights of the layer's type, and back
 static inline thanos_status convert_in(hipStream_t s, const void* in, thanos_dtype dt, float* out,
                                        int64_t n) {
-  if (dt == THANOS_F32) launch_convert<float, float>(s, in, out, n);
-  else if (dt == THANOS_F16) launch_convert<__half, float>(s, in, out, n);
-  else launch_convert<__hip_bfloat16, float>(s, in, out, n);
+  const int vec = convert_vec(in, dt, out, THANOS_F32);
+  if (dt == THANOS_F32) launch_convert<float, float>(s, in, out, n, vec);
+  else if (dt == THANOS_F16) launch_convert<__half, float>(s, in, out, n, vec);
+  else launch_convert<__hip_bfloat16, float>(s, in, out, n, vec);
   THANOS_LAUNCH_CHECK();
   return THANOS_OK;
 }
 static inline thanos_status convert_out(hipStream_t s, const float* in, void* out, thanos_dtype dt,
                                         int64_t n) {
-  if (dt == THANOS_F32) launch_convert<float, float>(s, in, out, n);
-  else if (dt == THANOS_F16) launch_convert<float, __half>(s, in, out, n);
-  else launch_convert<float, __hip_bfloat16>(s, in, out, n);
+  const int vec = convert_vec(in, THANOS_F32, out, dt);
+  if (dt == THANOS_F32) launch_convert<float, float>(s, in, out, n, vec);
+  else if (dt == THANOS_F16) launch_convert<float, __half>(s, in, out, n, vec);
+  else launch_convert<float, __hip_bfloat16>(s, in, out, n, vec);
   THANOS_LAUNCH_CHECK();
   return THANOS_OK;
 }

@@ -26,17 +26,6 @@ namespace thanos {
 
 // ------------------------------------------------------------------------------------------
 // small helpers
-__global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
-}
-
-__global__ __launch_bounds__(256) void k_sqrt(const float* __restrict__ xn2, float* __restrict__ sx,
-                                              int64_t b) {
-  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (j < b) sx[j] = sqrtf(xn2[j]);
-}
-
 // ------------------------------------------------------------------------------------------
 // P[(j1+m)*b + col] = sum_k U[j1+k][j1+m] * U[j1+k][col], col in [j1, b), for every block.
 struct BlockRowsArgs {
@@ -2234,18 +2223,49 @@ static int compute_units() {
   return n;
 }
 
-__global__ void k_init_state(SelState* st, long long r) {
-  st->r_rem = r;
-  st->need_eq = 0;
-  st->ties_all = 0;
-  st->deferred = 0;
-  st->tau = 0u;
-  st->none = (r <= 0) ? 1 : 0;
-  st->win_lo = 0u;
-  st->win_shift = kWinShiftMin;
-  st->pred_try = 0;
-  st->cand_overflow = 0;
-  st->arrived = st->nbin = st->bar = 0u;
+// Everything a sweep starts from, in one launch (a launch that does next to nothing costs 4.5 us, and
+// these were up to five of them): the first n_conv workgroups convert the weights, the rest take
+// square roots of the channel norms and, in unstructured mode (st), clear the selection's state.
+struct InitArgs {
+  const void* W_in;  // n weights of the layer's type -> W; n_conv == 0: already converted
+  float* W;
+  int64_t n;
+  int n_conv, vec;
+  const float* xn2;
+  float* sx;
+  int64_t b;
+  SelState* st;
+  long long r;
+  unsigned int *hist, *wgflag;
+  int32_t* info;  // cleared unless nullptr
+};
+constexpr int kInitWgs = 32;
+template <typename I>
+__global__ __launch_bounds__(256) void k_sweep_init(InitArgs a) {
+  if ((int)blockIdx.x < a.n_conv) {
+    convert_quad((const I*)a.W_in, a.W, 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x), a.n, a.vec);
+    return;
+  }
+  const int64_t i0 = (int64_t)((int)blockIdx.x - a.n_conv) * 256 + threadIdx.x;
+  if (a.info && i0 == 0) *a.info = 0;
+  for (int64_t i = i0; i < a.b; i += kInitWgs * 256) a.sx[i] = sqrtf(a.xn2[i]);
+  if (!a.st) return;
+  for (int64_t i = i0; i < 4 * 2048; i += kInitWgs * 256) a.hist[i] = 0u;
+  for (int64_t i = i0; i < kSelMaxWgs * kFlagStride; i += kInitWgs * 256) a.wgflag[i] = 0u;
+  if (i0 == 0) {
+    SelState* st = a.st;
+    st->r_rem = a.r;
+    st->need_eq = 0;
+    st->ties_all = 0;
+    st->deferred = 0;
+    st->tau = 0u;
+    st->none = (a.r <= 0) ? 1 : 0;
+    st->win_lo = 0u;
+    st->win_shift = kWinShiftMin;
+    st->pred_try = 0;
+    st->cand_overflow = 0;
+    st->arrived = st->nbin = st->bar = 0u;
+  }
 }
 
 template <int SEL>
@@ -2335,18 +2355,26 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
                     const float* H, const float* U, const float* xnorm2,
                     const thanos_prune_opts* o, long long r_total, long long n_out, float* W,
                     void* W_cast, uint8_t* mask, void* ws, int32_t* info, bool single_stream,
-                    PhaseTimer* pt, const float* Lfac, int64_t ldL, bool prepared) {
+                    PhaseTimer* pt, const float* Lfac, int64_t ldL, bool prepared,
+                    bool clear_info) {
   const int B = o->block_size;
   const bool outliers = n_out > 0;
   const int smax_all = (o->mode == THANOS_NM && !o->mask_in) ? B / o->m * o->n : B;
   const bool comp = sweep_uses_complement(o, b) && Lfac != nullptr;
   SweepWs w = carve_ws(ws, c, b, B, outliers, smax_all, sweep_uses_complement(o, b));
 
-  if (!prepared) {
-    thanos_status st = sweep_prepare(s, W_in, wdt, c, b, H, o, n_out, W, ws);
-    if (st != THANOS_OK) return st;
-  }
-  hipLaunchKernelGGL(k_sqrt, dim3((unsigned)ceil_div(b, 256)), dim3(256), 0, s, xnorm2, w.sx, b);
+  const bool unstructured = (o->mode == THANOS_UNSTRUCTURED) && o->mask_in == nullptr;
+  if (!prepared && outliers)  // the row losses need the converted weights
+    THANOS_CHECK(sweep_prepare(s, W_in, wdt, c, b, H, o, n_out, W, ws));
+  const bool conv = !prepared && !outliers;
+  const InitArgs ia{W_in, W, c * b, conv ? (int)ceil_div(c * b, 1024) : 0,
+                    conv ? convert_vec(W_in, wdt, W, THANOS_F32) : 0, xnorm2, w.sx, b,
+                    unstructured ? w.st : nullptr, r_total, w.hist, w.wgflag,
+                    clear_info ? info : nullptr};
+  const dim3 igrid((unsigned)(ia.n_conv + kInitWgs));
+  if (wdt == THANOS_F32) hipLaunchKernelGGL(k_sweep_init<float>, igrid, dim3(256), 0, s, ia);
+  else if (wdt == THANOS_F16) hipLaunchKernelGGL(k_sweep_init<__half>, igrid, dim3(256), 0, s, ia);
+  else hipLaunchKernelGGL(k_sweep_init<__hip_bfloat16>, igrid, dim3(256), 0, s, ia);
   THANOS_LAUNCH_CHECK();
 
   const bool aligned_b = (b % 4 == 0) && (B % 4 == 0);
@@ -2372,16 +2400,6 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
     }
   }
 
-  const bool unstructured = (o->mode == THANOS_UNSTRUCTURED) && o->mask_in == nullptr;
-  if (unstructured) {
-    hipLaunchKernelGGL(k_fill_u32, dim3(32), dim3(256), 0, s, w.hist, (int64_t)4 * 2048, 0u);
-    hipLaunchKernelGGL(k_fill_u32, dim3(kSelMaxWgs * kFlagStride / 256), dim3(256), 0, s, w.wgflag,
-                       (int64_t)kSelMaxWgs * kFlagStride, 0u);
-    hipLaunchKernelGGL(k_init_state, dim3(1), dim3(1), 0, s, w.st, r_total);
-    THANOS_LAUNCH_CHECK();
-  }
-
-  const unsigned rows4 = (unsigned)ceil_div(c, 4);
   const int super = unstructured ? 1 : kSuper;   // the global residual mask needs current weights
   const int ldl = B * super;
   // The update that reaches right of a super-block is split like the wide update of the
