@@ -178,9 +178,9 @@ struct BinSel {
   unsigned int count;
   long long before;
 };
-template <int NT>
-__device__ __forceinline__ BinSel block_select_bin(const unsigned int* __restrict__ hist,
-                                                   int nbins, long long rank) {
+// FRESH: the counts come from this launch's own atomics (read past the caches).
+template <int NT, bool FRESH = false>
+__device__ __forceinline__ BinSel block_select_bin(const unsigned int* hist, int nbins, long long rank) {
   __shared__ long long wtot[NT / 64];
   __shared__ BinSel res;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -190,7 +190,9 @@ __device__ __forceinline__ BinSel block_select_bin(const unsigned int* __restric
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const int idx = tid * per + e;
-    loc[e] = (e < per && idx < nbins) ? hist[idx] : 0u;
+    loc[e] = !(e < per && idx < nbins) ? 0u
+             : FRESH ? __hip_atomic_load(hist + idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                     : hist[idx];
     s += loc[e];
   }
   long long incl = s;
@@ -286,57 +288,74 @@ __device__ __forceinline__ unsigned int wait_word(const unsigned int* f, unsigne
 }
 
 // One radix pass of the calling workgroup over its rows (one wavefront per row; lanes stride
-// over the residual columns, 16 bytes per lane when aligned).  The workgroup's LDS histogram h
-// is added to hist_out at the end.
+// over the residual columns, 16 bytes per lane when aligned, four loads in flight).  The
+// workgroup's LDS histogram is added to hist_out at the end.  It has kSelCopies copies, dealt to the
+// lanes: the first pass counts exponents, a few bins for all keys, and one copy would take the 64
+// lanes of an instruction one after the other.
+constexpr int kSelCopies = 4;
 template <int PASS>
 __device__ __forceinline__ void sel_pass(const SelectArgs& a, unsigned int* h, unsigned int prefix,
                                          unsigned int* __restrict__ hist_out) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  for (int e = tid; e < 2048; e += kSelThreads) h[e] = 0u;
+  for (int e = tid; e < kSelCopies * 2048; e += kSelThreads) h[e] = 0u;
   __syncthreads();
+  unsigned int* mine = h + 2048 * (lane & (kSelCopies - 1));
   constexpr int RW = kSelThreads / 64;  // rows per workgroup and step
   for (int64_t i = (int64_t)blockIdx.x * RW + wave; i < a.c; i += (int64_t)gridDim.x * RW) {
     const float* row = a.W + i * a.b;
     int cand = 0;
     if (a.vec) {
       const int64_t nvec = (a.b - a.j1) >> 2;
-      for (int64_t v = lane; v < nvec; v += 64) {
-        const int64_t j = a.j1 + 4 * v;
-        const float4 w4 = *reinterpret_cast<const float4*>(row + j);
-        const float4 s4 = *reinterpret_cast<const float4*>(a.sx + j);
-        sel_count<PASS>(h, metric_key(w4.x, s4.x), prefix, cand);
-        sel_count<PASS>(h, metric_key(w4.y, s4.y), prefix, cand);
-        sel_count<PASS>(h, metric_key(w4.z, s4.z), prefix, cand);
-        sel_count<PASS>(h, metric_key(w4.w, s4.w), prefix, cand);
+      for (int64_t v0 = lane; v0 < nvec; v0 += 4 * 64) {
+        float4 w4[4], s4[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int64_t j = a.j1 + 4 * min(v0 + 64 * u, nvec - 1);
+          w4[u] = *reinterpret_cast<const float4*>(row + j);
+          s4[u] = *reinterpret_cast<const float4*>(a.sx + j);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (v0 + 64 * u < nvec) {
+            sel_count<PASS>(mine, metric_key(w4[u].x, s4[u].x), prefix, cand);
+            sel_count<PASS>(mine, metric_key(w4[u].y, s4[u].y), prefix, cand);
+            sel_count<PASS>(mine, metric_key(w4[u].z, s4[u].z), prefix, cand);
+            sel_count<PASS>(mine, metric_key(w4[u].w, s4[u].w), prefix, cand);
+          }
       }
       for (int64_t j = a.j1 + 4 * nvec + lane; j < a.b; j += 64)
-        sel_count<PASS>(h, metric_key(row[j], a.sx[j]), prefix, cand);
+        sel_count<PASS>(mine, metric_key(row[j], a.sx[j]), prefix, cand);
     } else {
       for (int64_t j = a.j1 + lane; j < a.b; j += 64)
-        sel_count<PASS>(h, metric_key(row[j], a.sx[j]), prefix, cand);
+        sel_count<PASS>(mine, metric_key(row[j], a.sx[j]), prefix, cand);
     }
     if (PASS == 2) {
       for (int off = 32; off > 0; off >>= 1) cand += __shfl_down(cand, off, 64);
-      if (lane == 0) a.row_cand[i] = cand;
+      if (lane == 0)
+        __hip_atomic_store(a.row_cand + i, cand, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
   __syncthreads();
-  for (int e = tid; e < 2048; e += kSelThreads)
-    if (h[e]) atomicAdd(&hist_out[e], h[e]);
+  for (int e = tid; e < 2048; e += kSelThreads) {
+    unsigned int n = 0;
+#pragma unroll
+    for (int u = 0; u < kSelCopies; ++u) n += h[2048 * u + e];
+    if (n) atomicAdd(&hist_out[e], n);
+  }
 }
 
 // All workgroups of the launch have arrived at barrier `phase` (1, 2, ...) of this block: each
 // adds itself to a counter, and the one that completes the count releases every workgroup
-// through its own word.  Release and acquire fences at device scope on both sides: what the
-// workgroups wrote before the barrier (histogram atomics, per-row counts) is read after it.
-// Returns false if the wait ran out.
+// through its own word.  No fence at device scope: what crosses the barrier (histograms, counts per
+// row) is written with atomics or atomic stores, which are complete when a wavefront's vmcnt is zero,
+// and read with atomic loads.  Such fences on both sides, one per wavefront behind the barrier, wrote
+// the L2s back thousands of times: three passes over 4096 x 4096 took 310 us, and 200 over the last
+// 128 columns (now 67 and 30).  Returns false if the wait ran out.
 __device__ __forceinline__ bool grid_barrier(const SelectArgs& a, unsigned int phase) {
   __shared__ int ok, last;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (threadIdx.x == 0) {
-    __threadfence();
-    last = atomicAdd(&a.st->bar, 1u) + 1u == phase * gridDim.x ? 1 : 0;
-  }
+  if (threadIdx.x == 0) last = atomicAdd(&a.st->bar, 1u) + 1u == phase * gridDim.x ? 1 : 0;
   __syncthreads();
   const unsigned int want = 8u * a.seq + phase;
   if (last)
@@ -346,19 +365,21 @@ __device__ __forceinline__ bool grid_barrier(const SelectArgs& a, unsigned int p
   if (threadIdx.x == 0)
     ok = wait_word(a.wgflag + (size_t)blockIdx.x * kFlagStride, want) >= want ? 1 : 0;
   __syncthreads();
-  __threadfence();
   return ok != 0;
 }
 
 // Exclusive prefix sum of row_eq over the rows by one workgroup, in place: afterwards row_eq[i]
 // = number of keys equal to tau in the rows before row i (ties are taken in (row, column) order).
-__device__ __forceinline__ void tie_prefix(int* __restrict__ row_eq, int64_t c) {
+__device__ __forceinline__ void tie_prefix(int* row_eq, int64_t c) {
   __shared__ long long wtot[kSelThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t per = (c + kSelThreads - 1) / kSelThreads;
   const int64_t lo = tid * per, hi = min(c, lo + per);
   long long s = 0;
-  for (int64_t i = lo; i < hi; ++i) s += row_eq[i];
+  auto count = [&](int64_t i) {
+    return __hip_atomic_load(row_eq + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  for (int64_t i = lo; i < hi; ++i) s += count(i);
   long long incl = s;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
@@ -370,7 +391,7 @@ __device__ __forceinline__ void tie_prefix(int* __restrict__ row_eq, int64_t c) 
   long long run = incl - s;
   for (int v = 0; v < wave; ++v) run += wtot[v];
   for (int64_t i = lo; i < hi; ++i) {
-    const int v = row_eq[i];
+    const int v = count(i);
     row_eq[i] = (int)min(run, (long long)0x7fffffff);
     run += v;
   }
@@ -409,8 +430,10 @@ __device__ __forceinline__ void publish(const SelectArgs& a, long long r_rem, bo
 }
 
 __global__ __launch_bounds__(kSelThreads) void k_select(SelectArgs a) {
-  __shared__ unsigned int h[2048];
-  __shared__ unsigned long long bins[kBinCap];  // workgroup 0: the threshold's bin
+  // workgroup 0, window hit: the threshold's bin; otherwise the histograms of the radix passes
+  __shared__ unsigned long long bins[kBinCap];
+  static_assert(sizeof(bins) == kSelCopies * 2048 * sizeof(unsigned int), "both uses fit");
+  unsigned int* h = reinterpret_cast<unsigned int*>(bins);
   __shared__ unsigned int h16[1 << kWinShiftMax];  // counts of the bin's keys by their low bits
   __shared__ unsigned int s_ok;
   SelState* st = a.st;
@@ -529,14 +552,14 @@ __global__ __launch_bounds__(kSelThreads) void k_select(SelectArgs a) {
   bool ok = true;
   sel_pass<0>(a, h, 0u, hist_a);
   ok = grid_barrier(a, 1u);
-  const BinSel r0 = block_select_bin<kSelThreads>(hist_a, 2048, r_rem);
+  const BinSel r0 = block_select_bin<kSelThreads, true>(hist_a, 2048, r_rem);
   const unsigned int prefix1 = (unsigned int)r0.bin;
   const long long rank1 = r_rem - r0.before;
   if (ok) {
     sel_pass<1>(a, h, prefix1, hist_b);
     ok = grid_barrier(a, 2u);
   }
-  const BinSel r1 = block_select_bin<kSelThreads>(hist_b, 2048, rank1);
+  const BinSel r1 = block_select_bin<kSelThreads, true>(hist_b, 2048, rank1);
   const unsigned int prefix2 = (prefix1 << 11) | (unsigned int)r1.bin;
   const long long rank2 = rank1 - r1.before;
   if (ok) {
@@ -550,7 +573,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select(SelectArgs a) {
   // The last pass resolves the key completely, so the chosen bin counts the keys equal to tau:
   // if all of them are removed (the usual case: one key at the threshold) their order does not
   // matter and nothing is ranked.
-  const BinSel r2 = block_select_bin<kSelThreads>(hist_c, 1024, rank2);
+  const BinSel r2 = block_select_bin<kSelThreads, true>(hist_c, 1024, rank2);
   const unsigned int tau = (prefix2 << 10) | (unsigned int)r2.bin;
   const long long rank_eq = rank2 - r2.before;  // keys equal to tau that are removed
   const bool all = rank_eq == (long long)r2.count;
@@ -562,7 +585,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select(SelectArgs a) {
   // their keys equal to tau over the residual row; other rows have none
   for (int64_t i = (int64_t)blockIdx.x * RW + wave; i < a.c; i += (int64_t)gridDim.x * RW) {
     int n = 0;
-    if (a.row_cand[i] != 0) {
+    if (__hip_atomic_load(a.row_cand + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
       const float* row = a.W + i * a.b;
       if (a.vec) {
         const int64_t nvec = (a.b - a.j1) >> 2;
@@ -581,7 +604,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select(SelectArgs a) {
       }
       for (int off = 32; off > 0; off >>= 1) n += __shfl_down(n, off, 64);
     }
-    if (lane == 0) a.row_eq[i] = n;
+    if (lane == 0) __hip_atomic_store(a.row_eq + i, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   if (!grid_barrier(a, 4u)) {
     if (tid == 0) atomicCAS(a.info, 0, kInfoSelectTimeout);
