@@ -18,7 +18,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
                     bool clear_info);
 thanos_status sweep_prepare(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c, int64_t b,
                             const float* H, const thanos_prune_opts* o, long long n_out, float* W,
-                            void* ws);
+                            void* ws, bool beside);
 size_t structured_workspace_bytes(int64_t c, int64_t b);
 thanos_status structured(hipStream_t st, const void* W_in, thanos_dtype wdt, int64_t c, int64_t b,
                          const float* H, float damping, long long s_cols, long long n_out,
@@ -371,13 +371,17 @@ static thanos_status prune_with_workspace(const void* W_in, thanos_dtype wdt, in
     float* xw = reinterpret_cast<float*>(p);
     p += align_up((size_t)b * sizeof(float), 256);
     if (beside) {
+      // the factorisation's first launches go ahead: behind the product of the row losses, which
+      // fills the chip, they took 420 us instead of 70 (5120 columns)
+      THANOS_CHECK(factor_begin(s, H, b, opts->damping, xw, p, info_dev));
       THANOS_CHECK(prep.fork(0));
-      thanos_status sp = sweep_prepare(prep.stream, W_in, wdt, c, b, H, opts, n_out, W_out, sweep_ws);
+      thanos_status sp = sweep_prepare(prep.stream, W_in, wdt, c, b, H, opts, n_out, W_out, sweep_ws,
+                                       true);
       if (sp != THANOS_OK) return sp;
       THANOS_CHECK(prep.record(1));
       prepared = true;
     }
-    thanos_status st = factor(s, H, b, opts->damping, Uw, xw, p, info_dev, single_stream);
+    thanos_status st = factor(s, H, b, opts->damping, Uw, xw, p, info_dev, single_stream, beside);
     if (st != THANOS_OK) return st;
     if (prepared) THANOS_CHECK(prep.join(1));
     U = Uw;

@@ -265,11 +265,12 @@ constexpr int kFactorNB = 128;  // block size of the blocked factorisation
 //   lower_only: compute only tiles with tile_row >= tile_col (C square)
 //   b_tri: op(B) (K x N, K == N) is lower triangular (zero for k < n): the reduction of an output
 //          tile starts at its first column; or upper triangular (zero for k > n): it ends at its last
+//   beside: runs next to a chain of short kernels on another stream: one workgroup per compute unit
 enum TriB { kTriNone = 0, kTriLower = 1, kTriUpper = 2 };
 thanos_status gemm_f32(hipStream_t s, bool a_kmajor, bool b_kmajor, int64_t M, int64_t N,
                        int64_t K, float alpha, const float* A, int64_t lda, const float* B,
                        int64_t ldb, float beta, float* C, int64_t ldc, bool lower_only,
-                       TriB b_tri = kTriNone);
+                       TriB b_tri = kTriNone, bool beside = false);
 
 // H (b x b, ld = b, lower tiles) += alpha * X^T X for fp32 X [n_tok, b].
 thanos_status syrk_f32(hipStream_t s, float* H, int64_t b, const float* X, int64_t n_tok, int64_t ldx,
@@ -284,11 +285,17 @@ thanos_status syrk_accumulate(hipStream_t s, float* H, int64_t b, const void* Xc
 size_t factor_workspace_bytes(int64_t b);
 // single_stream: no helper streams, everything on `s` in enqueue order (nothing is created).
 thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, float* U,
-                     float* xnorm2, void* ws, int32_t* info, bool single_stream = false);
+                     float* xnorm2, void* ws, int32_t* info, bool single_stream = false,
+                     bool begun = false);
+// Its first two launches (diagonal, damped copy), which is all of it that reads H; factor(..., begun =
+// true) goes on from there.
+thanos_status factor_begin(hipStream_t s, const float* H, int64_t b, float damping, float* xnorm2,
+                           void* ws, int32_t* info);
 const float* factor_L(const void* ws, int64_t b, int64_t* ld);
 
 // skip[i] = 1 for the n_out rows of W (c x b fp32) with the largest loss W_i H W_i^T (sweep.hip).
 thanos_status row_outliers(hipStream_t s, const float* W, const float* H, int64_t c, int64_t b,
-                           long long n_out, float* Hf, float* T, float* h, uint8_t* skip);
+                           long long n_out, float* Hf, float* T, float* h, uint8_t* skip,
+                           bool beside = false);
 
 }  // namespace thanos

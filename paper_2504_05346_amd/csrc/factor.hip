@@ -33,10 +33,20 @@ __global__ __launch_bounds__(1024) void k_diag_stats(const float* __restrict__ H
                                                      int32_t* __restrict__ info) {
   __shared__ double part[1024];
   double s = 0.0;
-  for (int64_t j = threadIdx.x; j < b; j += 1024) {
-    const float d = H[j * b + j];
-    xnorm2[j] = d;
-    s += (double)d;
+  // eight loads in flight (each touches a page of its own); added in order
+  for (int64_t j0 = threadIdx.x; j0 < b; j0 += 8 * 1024) {
+    float d[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int64_t j = min(j0 + 1024 * e, b - 1);
+      d[e] = H[j * b + j];
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (j0 + 1024 * e < b) {
+        xnorm2[j0 + 1024 * e] = d[e];
+        s += (double)d[e];
+      }
   }
   part[threadIdx.x] = s;
   __syncthreads();
@@ -402,20 +412,27 @@ size_t factor_workspace_bytes(int64_t b) {
   return 3 * (size_t)bp * bp * sizeof(float) + 256;
 }
 
-thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, float* U,
-                     float* xnorm2, void* ws, int32_t* info, bool single_stream) {
+thanos_status factor_begin(hipStream_t s, const float* H, int64_t b, float damping, float* xnorm2,
+                           void* ws, int32_t* info) {
   const int64_t bp = padded(b);
-  const int nb = (int)(bp / NB);
   float* lam = reinterpret_cast<float*>(ws);
   float* Ap = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + 256);
-  float* Linv = Ap + bp * bp;
-  float* Tb = Linv + bp * bp;
-
   hipLaunchKernelGGL(k_diag_stats, dim3(1), dim3(1024), 0, s, H, b, damping, xnorm2, lam, info);
   THANOS_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_reverse_pad, dim3((unsigned)(bp / 32), (unsigned)(bp / 32)), dim3(256), 0,
                      s, H, b, lam, Ap, bp);
   THANOS_LAUNCH_CHECK();
+  return THANOS_OK;
+}
+
+thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, float* U,
+                     float* xnorm2, void* ws, int32_t* info, bool single_stream, bool begun) {
+  const int64_t bp = padded(b);
+  const int nb = (int)(bp / NB);
+  float* Ap = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + 256);
+  float* Linv = Ap + bp * bp;
+  float* Tb = Linv + bp * bp;
+  if (!begun) THANOS_CHECK(factor_begin(s, H, b, damping, xnorm2, ws, info));
 
   // Two-level blocking: inside an outer block of kOuter factor blocks the trailing update of a
   // step only reaches the columns of that outer block (narrow, K = NB); everything to the right

@@ -90,46 +90,69 @@ __global__ __launch_bounds__(kXThreads, 4) void k_gemm_f32(GemmArgs g) {
   }
 }
 
-// C = beta C + alpha A B^T with a reduction of exactly 128: panel and narrow updates of the
+// C = beta C + alpha A B^T, reduction a multiple of 128: panel, narrow and strip updates of the
 // factorisation while few rows are left.  These launches stand in the factorisation's chain, and the
-// pipelined kernel above needs 6 us for four slabs it cannot overlap with anything.  Here a
-// wavefront owns 32 x 32 of C and fetches all its operands at once, straight into the registers the
-// MFMAs read them from (lane (lo, hi) holds k = 8 q + 4 hi + c of its row: both operands in the same
-// order), then runs 64 fp32 MFMAs: no LDS, no slabs.  A workgroup is a strip of 32 rows x 128
-// columns, so that C may be A (N = 128): every wavefront has its rows before one stores.
-__global__ __launch_bounds__(256, 2) void k_gemm_k128(GemmArgs g) {
+// pipelined kernel above needs 6 us for four slabs (1.7 for every further one) that it cannot overlap
+// with anything.  Here a wavefront owns 32 x 32 of C and fetches its operands straight into the
+// registers the MFMAs read them from (lane (lo, hi) holds k = 8 q + 4 hi + c of its row: both
+// operands in the same order), 64 k-values ahead of the fp32 MFMAs on the 64 before: no LDS.  A
+// workgroup is a strip of 32 rows x 128 columns, so that C may be A (N = K = 128): every wavefront
+// has its rows before one stores.
+__global__ __launch_bounds__(256, 2) void k_gemm_direct(GemmArgs g) {
   const int lane = threadIdx.x & 63, lo = lane & 31, hi = lane >> 5;
   const int m0 = 32 * blockIdx.y, n0 = kTN * blockIdx.x + 32 * (threadIdx.x >> 6);
   if (g.lower_only && (int)blockIdx.x > m0 / kTM) return;  // same tiles as k_gemm_f32
   const float* pa = g.A + (int64_t)(m0 + lo) * g.lda + 4 * hi;
   const float* pb = g.B + (int64_t)(n0 + lo) * g.ldb + 4 * hi;
   float* pc = g.C + (int64_t)(m0 + 4 * hi) * g.ldc + n0 + lo;
-  f32x4 a[16], b[16];
+  f32x4 a[2][8], b[2][8];
+  auto load = [&](int buf, int k) {
 #pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    a[q] = *reinterpret_cast<const f32x4*>(pa + 8 * q);
-    b[q] = *reinterpret_cast<const f32x4*>(pb + 8 * q);
-  }
+    for (int q = 0; q < 8; ++q) {
+      a[buf][q] = *reinterpret_cast<const f32x4*>(pa + k + 8 * q);
+      b[buf][q] = *reinterpret_cast<const f32x4*>(pb + k + 8 * q);
+    }
+  };
+  load(0, 0);
+  load(1, 64);
   f32x16 old, acc, acc2;  // two partial sums: a chain half as long, and half of its rounding
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     old[r] = g.beta != 0.f ? pc[(int64_t)(8 * (r >> 2) + (r & 3)) * g.ldc] : 0.f;
     acc[r] = acc2[r] = 0.f;
   }
+  auto multiply = [&](int buf) {
 #pragma unroll
-  for (int q = 0; q < 8; ++q)
+    for (int q = 0; q < 8; ++q)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q][c], b[q][c], acc, 0, 0, 0);
-      acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q + 8][c], b[q + 8][c], acc2, 0, 0, 0);
-    }
+      for (int c = 0; c < 4; c += 2) {
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[buf][q][c], b[buf][q][c], acc, 0, 0, 0);
+        acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a[buf][q][c + 1], b[buf][q][c + 1], acc2, 0, 0, 0);
+      }
+  };
+  for (int k = 128; k < g.K; k += 128) {
+    multiply(0);
+    load(0, k);
+    multiply(1);
+    load(1, k + 64);
+  }
+  multiply(0);
+  multiply(1);
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < 16; ++r)
     pc[(int64_t)(8 * (r >> 2) + (r & 3)) * g.ldc] = g.beta * old[r] + g.alpha * (acc[r] + acc2[r]);
 }
-// One 32 x 32 tile of C per SIMD: 8.5 us instead of 10 to 11.5; at 1488 tiles 15.2 against 11.9.
-constexpr int64_t kK128Tiles = 1024;
+// One 32 x 32 tile of C per SIMD.  K = 128: 8.5 us instead of 10 to 11.5, at 1488 tiles 15.2 against
+// 11.9.  K = 512: 22 instead of 29, at 1792 tiles 36 against 31.
+constexpr int64_t kDirectTiles = 1024;
+
+// A product beside the factorisation's chain takes more than half of a compute unit's LDS, so that one
+// workgroup runs per unit, and leaves room for a diagonal block (72 KB) and half of the registers.
+// Two per unit kept the chain's kernels waiting for whole tiles: its first step took 670 us next to
+// the 690 us product of 5120 columns (now 40).
+constexpr size_t kBesideSmemBytes = 84 * 1024;
+static_assert(kBesideSmemBytes >= kXSmemBytes, "the product itself fits");
 
 static inline bool vec_ok(const float* p, int64_t ld) {
   return (reinterpret_cast<uintptr_t>(p) % 16 == 0) && (ld % 4 == 0);
@@ -138,14 +161,14 @@ static inline bool vec_ok(const float* p, int64_t ld) {
 thanos_status gemm_f32(hipStream_t s, bool a_kmajor, bool b_kmajor, int64_t M, int64_t N,
                        int64_t K, float alpha, const float* A, int64_t lda, const float* B,
                        int64_t ldb, float beta, float* C, int64_t ldc, bool lower_only,
-                       TriB b_tri) {
+                       TriB b_tri, bool beside) {
   if (M <= 0 || N <= 0) return THANOS_OK;
   GemmArgs g{A, B, C, lda, ldb, ldc, (int)M, (int)N, (int)K, alpha, beta, lower_only ? 1 : 0,
              vec_ok(A, lda) ? 1 : 0, vec_ok(B, ldb) ? 1 : 0,
              (reinterpret_cast<uintptr_t>(C) % 8 == 0 && ldc % 2 == 0) ? 1 : 0, b_tri};
-  if (!a_kmajor && !b_kmajor && K == 128 && M % 32 == 0 && N % kTN == 0 && g.vec_a && g.vec_b &&
-      b_tri == kTriNone && (M / 32) * (N / 32) <= kK128Tiles) {
-    hipLaunchKernelGGL(k_gemm_k128, dim3((unsigned)(N / kTN), (unsigned)(M / 32)), dim3(256), 0, s, g);
+  if (!a_kmajor && !b_kmajor && K > 0 && K % 128 == 0 && K <= 512 && M % 32 == 0 && N % kTN == 0 &&
+      g.vec_a && g.vec_b && b_tri == kTriNone && (M / 32) * (N / 32) <= kDirectTiles) {
+    hipLaunchKernelGGL(k_gemm_direct, dim3((unsigned)(N / kTN), (unsigned)(M / 32)), dim3(256), 0, s, g);
     THANOS_LAUNCH_CHECK();
     return THANOS_OK;
   }
@@ -156,10 +179,10 @@ thanos_status gemm_f32(hipStream_t s, bool a_kmajor, bool b_kmajor, int64_t M, i
   else if (!a_kmajor && b_kmajor) kern = k_gemm_f32<false, true>;
   else if (a_kmajor && b_kmajor) kern = k_gemm_f32<true, true>;
   else kern = k_gemm_f32<true, false>;
+  const size_t smem = beside ? kBesideSmemBytes : kXSmemBytes;
   THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)kXSmemBytes));
-  hipLaunchKernelGGL(kern, grid, dim3(kXThreads), kXSmemBytes, s, g);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+  hipLaunchKernelGGL(kern, grid, dim3(kXThreads), smem, s, g);
   THANOS_LAUNCH_CHECK();
   return THANOS_OK;
 }

@@ -2096,11 +2096,12 @@ __global__ __launch_bounds__(256) void k_row_rank(const float* __restrict__ h, i
 // triangle).  Hf (b x b, receives the lower triangle with halved diagonal), T (c x b) and h (c)
 // are scratch.
 thanos_status row_outliers(hipStream_t s, const float* W, const float* H, int64_t c, int64_t b,
-                           long long n_out, float* Hf, float* T, float* h, uint8_t* skip) {
+                           long long n_out, float* Hf, float* T, float* h, uint8_t* skip, bool beside) {
   hipLaunchKernelGGL(k_lower_half_diag, dim3((unsigned)ceil_div(b, 256), (unsigned)b), dim3(256), 0,
                      s, H, b, Hf);
   THANOS_LAUNCH_CHECK();
-  thanos_status st = gemm_f32(s, false, true, c, b, b, 1.f, W, b, Hf, b, 0.f, T, b, false, kTriLower);
+  thanos_status st = gemm_f32(s, false, true, c, b, b, 1.f, W, b, Hf, b, 0.f, T, b, false, kTriLower,
+                              beside);
   if (st != THANOS_OK) return st;
   hipLaunchKernelGGL(k_rowdot, dim3((unsigned)ceil_div(c, 4)), dim3(256), 0, s, T, W, c, b, h);
   THANOS_LAUNCH_CHECK();
@@ -2361,14 +2362,14 @@ static void launch_solve(hipStream_t s, SolveArgs a, int smax) {
 // passes prepared = true to sweep().
 thanos_status sweep_prepare(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c, int64_t b,
                             const float* H, const thanos_prune_opts* o, long long n_out, float* W,
-                            void* ws) {
+                            void* ws, bool beside) {
   const int B = o->block_size;
   const bool outliers = n_out > 0;
   const int smax_all = (o->mode == THANOS_NM && !o->mask_in) ? B / o->m * o->n : B;
   SweepWs w = carve_ws(ws, c, b, B, outliers, smax_all, sweep_uses_complement(o, b));
   THANOS_CHECK(convert_in(s, W_in, wdt, W, c * b));
   if (outliers) {
-    thanos_status st = row_outliers(s, W, H, c, b, n_out, w.Hf, w.T, w.h, w.row_skip);
+    thanos_status st = row_outliers(s, W, H, c, b, n_out, w.Hf, w.T, w.h, w.row_skip, beside);
     if (st != THANOS_OK) return st;
   }
   return THANOS_OK;
@@ -2388,7 +2389,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
 
   const bool unstructured = (o->mode == THANOS_UNSTRUCTURED) && o->mask_in == nullptr;
   if (!prepared && outliers)  // the row losses need the converted weights
-    THANOS_CHECK(sweep_prepare(s, W_in, wdt, c, b, H, o, n_out, W, ws));
+    THANOS_CHECK(sweep_prepare(s, W_in, wdt, c, b, H, o, n_out, W, ws, false));
   const bool conv = !prepared && !outliers;
   const InitArgs ia{W_in, W, c * b, conv ? (int)ceil_div(c * b, 1024) : 0,
                     conv ? convert_vec(W_in, wdt, W, THANOS_F32) : 0, xnorm2, w.sx, b,
