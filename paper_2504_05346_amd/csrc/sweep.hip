@@ -843,6 +843,11 @@ __global__ __launch_bounds__(SMAX, (SMAX == 128 ? 3 : 1)) void k_solve_wide(Solv
   if (tid < a.bw) lam_g[tid] = wrow[tid];
 }
 
+// Lane `lane` (a constant) of v <- the bits s, uniform.  (The wait is for a v_readlane that has just
+// produced s, which the compiler does not look for inside the asm.)
+#define set_lane(v, s, lane) \
+  asm volatile("s_nop 1\n\tv_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(s), "i"(lane))
+
 // ------------------------------------------------------------------------------------------
 // Mask + per-row solve on the matrix cores for systems of up to 32 NTR unknowns (NTR = 2 or 3,
 // block width <= 128): one wavefront per row of W.  R_hat is held in the accumulator layout of
@@ -854,31 +859,33 @@ __global__ __launch_bounds__(SMAX, (SMAX == 128 ? 3 : 1)) void k_solve_wide(Solv
 // rows k and k + 4 share a register (lower / upper half of the wavefront), so a PAIR of pivots
 // of tile row p costs one MFMA per live tile (i, j), p <= j <= i; the cross-lane traffic is the
 // broadcast of the pivots and one cross-lane read per tile row (the second pivot's row must
-// first see the elimination of the first).  The right-hand side u is carried along (forward
-// substitution: one FMA per tile row and pair), the columns of L~ go to LDS, and
-// L~^T lambda = D^-1 y is solved afterwards by column sweeps that read one LDS row per unknown.
+// first see the elimination of the first).  The columns of -L~ go to LDS, and L~ y = u,
+// L~^T lambda = D^-1 y are solved afterwards by sweeps over them.
 // NTR = 2 serves n:m at B = 128 (s = 64 for 2:4 and 4:8); NTR = 3 the unstructured mode at
 // B = 128, where s scatters around 64.
 template <int NTR>
 struct SolveMfmaSmem {
   static constexpr int N = 32 * NTR;
-  float L[N * (N - 1) / 2 + 64];  // strict lower triangle of L~, packed by rows
-  float wrow[128];
-  float key[128];
-  unsigned char q[128];
-  float dummy[128];
+  // strict lower triangle of L~, packed by rows, and room for the lanes that have nothing to store;
+  // before the elimination and after the back-substitution the first 256 floats hold the row's
+  // weights (then lambda) and metric
+  float L[N * (N - 1) / 2 + 64];
+  float d[N];  // pivots by position
+  alignas(4) unsigned char q[128];
 };
 
 // FULL: the host knows that every row has either no unknown or exactly 32 NTR (n:m on a whole
 // block): the padding logic folds away.
 template <int SEL, int WPB, int NTR, bool FULL = false>
-__global__ __launch_bounds__(64 * WPB, 2) void k_solve_mfma(SolveArgs a) {
+__global__ __launch_bounds__(64 * WPB, NTR == 2 ? 4 : 3) void k_solve_mfma(SolveArgs a) {
   constexpr int CPL = 2;  // block width <= 128
   constexpr int NZ = (NTR + 1) / 2;  // registers holding y / d: rows 64 z + lane
   extern __shared__ __attribute__((aligned(16))) char solve_smem[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   SolveMfmaSmem<NTR>& sm = reinterpret_cast<SolveMfmaSmem<NTR>*>(solve_smem)[wave];
+  float* const wrow = sm.L;
+  float* const key = sm.L + 128;
   const int lo = lane & 31, hi = lane >> 5;
   const int64_t i = (int64_t)blockIdx.x * WPB + wave;
   if (i >= a.c) return;
@@ -891,7 +898,7 @@ __global__ __launch_bounds__(64 * WPB, 2) void k_solve_mfma(SolveArgs a) {
   for (int r = 0; r < CPL; ++r) {
     const int col = lane + 64 * r;
     wv[r] = (col < a.bw) ? wrow_g[col] : 0.f;
-    sm.wrow[col] = wv[r];
+    wrow[col] = wv[r];
     sel[r] = false;
   }
   if (SEL == SEL_GIVEN) {
@@ -904,7 +911,7 @@ __global__ __launch_bounds__(64 * WPB, 2) void k_solve_mfma(SolveArgs a) {
 #pragma unroll
     for (int r = 0; r < CPL; ++r) {
       const int col = lane + 64 * r;
-      sm.key[col] = (col < a.bw) ? fabsf(wv[r]) * a.sx[a.j1 + col] : 0.f;
+      key[col] = (col < a.bw) ? fabsf(wv[r]) * a.sx[a.j1 + col] : 0.f;
     }
     WAVE_SYNC();
 #pragma unroll
@@ -912,10 +919,10 @@ __global__ __launch_bounds__(64 * WPB, 2) void k_solve_mfma(SolveArgs a) {
       const int col = lane + 64 * r;
       if (col < a.bw) {
         const int g0 = (col / a.m) * a.m;
-        const float mine = sm.key[col];
+        const float mine = key[col];
         int rank = 0;
         for (int e = 0; e < a.m; ++e) {
-          const float o = sm.key[g0 + e];
+          const float o = key[g0 + e];
           rank += (o < mine || (o == mine && g0 + e < col)) ? 1 : 0;
         }
         sel[r] = rank < a.n;
@@ -934,9 +941,9 @@ __global__ __launch_bounds__(64 * WPB, 2) void k_solve_mfma(SolveArgs a) {
     for (int r = 0; r < CPL; ++r) {
       const int col = lane + 64 * r;
       const bool in = (col < a.bw) && !none;
-      const unsigned int key = in ? metric_key(wv[r], a.sx[a.j1 + col]) : 0xffffffffu;
-      const bool lt = in && key < tau;
-      const bool eq = in && key == tau;
+      const unsigned int mk = in ? metric_key(wv[r], a.sx[a.j1 + col]) : 0xffffffffu;
+      const bool lt = in && mk < tau;
+      const bool eq = in && mk == tau;
       const unsigned long long eqb = __ballot(eq);
       const long long my = tie_rank + __popcll(eqb & ((1ull << lane) - 1ull));
       sel[r] = lt || (eq && my < need_eq);
@@ -966,21 +973,36 @@ __global__ __launch_bounds__(64 * WPB, 2) void k_solve_mfma(SolveArgs a) {
     comp = true;
   }
   const int ns = comp ? a.bw - s : s;  // unknowns of the system solved below
-  if (comp) {  // positions of the KEPT columns of the block
+  // ---- tile grid: nt tile rows, and the PARTIAL tile comes first.  Matrix index m < 32 - pad
+  //      is unknown m, 32 - pad <= m < 32 is padding (identity, never eliminated), m >= 32 is
+  //      unknown m - pad.  A pivot costs one MFMA per live tile, most in the first tile row
+  //      (NTR (NTR + 1) / 2 of them): with the short tile row in front, a system of 66 unknowns
+  //      costs 2 * 6 + 32 * 3 + 32 MFMAs instead of 32 * 6 + 32 * 3 + 2. ----
+  const int nt = FULL ? NTR : (ns + 31) >> 5;
+  const int pad = FULL ? 0 : 32 * nt - ns;
+  auto valid = [&](int m) { return FULL || m < 32 - pad || (m >= 32 && m - pad < ns); };
+  // q[m] = block column of matrix index m (column 0 where there is none: what it fetches is in
+  // bounds and masked or never used), four of them to a word
+  if (!FULL) {
+    if (lane < 32) reinterpret_cast<unsigned int*>(sm.q)[lane] = 0u;
+    WAVE_SYNC();
+  }
+  if (comp) {  // the KEPT columns of the block
     int before = 0;
 #pragma unroll
     for (int r = 0; r < CPL; ++r) {
       const int col = lane + 64 * r;
       const bool kept = col < a.bw && !sel[r];
       const unsigned long long bal = __ballot(kept);
-      if (kept) sm.q[before + __popcll(bal & ((1ull << lane) - 1ull))] = (unsigned char)col;
+      myrank[r] = before + __popcll(bal & ((1ull << lane) - 1ull));
       before += __popcll(bal);
     }
   }
 #pragma unroll
   for (int r = 0; r < CPL; ++r) {
     const int col = lane + 64 * r;
-    if (sel[r] && !comp) sm.q[myrank[r]] = (unsigned char)col;
+    if (comp ? (col < a.bw && !sel[r]) : (sel[r] && s <= 32 * NTR))
+      sm.q[myrank[r] < 32 - pad ? myrank[r] : myrank[r] + pad] = (unsigned char)col;
     if (col < a.bw) a.mask_out[i * a.b + a.j1 + col] = sel[r] ? 1 : 0;
   }
   if (SEL == SEL_THRESHOLD) {
@@ -1014,10 +1036,10 @@ __global__ __launch_bounds__(64 * WPB, 2) void k_solve_mfma(SolveArgs a) {
   if (comp) {
     // right-hand side (w~ K)_k: w~ = the row's weights on the removed columns, zero elsewhere
 #pragma unroll
-    for (int r = 0; r < CPL; ++r) sm.key[lane + 64 * r] = sel[r] ? wv[r] : 0.f;
+    for (int r = 0; r < CPL; ++r) key[lane + 64 * r] = sel[r] ? wv[r] : 0.f;
     WAVE_SYNC();
     float t[CPL];
-    matvec_k(sm.key, t);
+    matvec_k(key, t);
     if (ns == 0) {  // the whole block goes: lambda = w~ K
 #pragma unroll
       for (int r = 0; r < CPL; ++r) {
@@ -1027,76 +1049,65 @@ __global__ __launch_bounds__(64 * WPB, 2) void k_solve_mfma(SolveArgs a) {
       return;
     }
 #pragma unroll
-    for (int r = 0; r < CPL; ++r) sm.wrow[lane + 64 * r] = t[r];  // gathered below through q
+    for (int r = 0; r < CPL; ++r) wrow[lane + 64 * r] = t[r];  // gathered below through q
   }
   WAVE_SYNC();
 
-  // ---- tile grid: nt tile rows, and the PARTIAL tile comes first.  Matrix index m < 32 - pad
-  //      is unknown m, 32 - pad <= m < 32 is padding (identity, never eliminated), m >= 32 is
-  //      unknown m - pad.  A pivot costs one MFMA per live tile, most in the first tile row
-  //      (NTR (NTR + 1) / 2 of them): with the short tile row in front, a system of 66 unknowns
-  //      costs 2 * 6 + 32 * 3 + 32 MFMAs instead of 32 * 6 + 32 * 3 + 2. ----
-  const int nt = FULL ? NTR : (ns + 31) >> 5;
-  const int pad = FULL ? 0 : 32 * nt - ns;
-  auto valid = [&](int m) { return FULL || m < 32 - pad || (m >= 32 && m - pad < ns); };
-  auto unk = [&](int m) {  // clamped: always a valid index
-    return FULL ? m : min(m < 32 ? m : m - pad, ns - 1);
-  };
-
-  // ---- gather R_hat = G[q, q] into the tiles (all loads unconditional from clamped, valid
-  //      indices, masked afterwards); right-hand side distributed by row ----
+  // ---- gather R_hat = G[q, q] into the tiles (all loads unconditional, masked afterwards: only
+  //      the first tile row holds padding); right-hand side distributed by row ----
   const float* G = comp ? a.Kc : a.P + a.j1 * a.b + a.j1;  // R_hat = G[q, q], or K[k, k]
-  const unsigned int bb = comp ? (unsigned int)a.ldk : (unsigned int)a.b;  // q * b < 2^31
+  const char* Gc = reinterpret_cast<const char*>(G);  // byte offsets of 32 bits: 128 rows of at most
+  const unsigned int bb = 4u * (comp ? (unsigned int)a.ldk : (unsigned int)a.b);  // 65535 columns
   f32x16 T[NTR][NTR];
   unsigned int qcol[NTR];
 #pragma unroll
-  for (int ti = 0; ti < NTR; ++ti) qcol[ti] = sm.q[unk(32 * ti + lo)];
+  for (int ti = 0; ti < NTR; ++ti) qcol[ti] = 4u * sm.q[32 * ti + lo];
 #pragma unroll
   for (int tj = 0; tj < NTR; ++tj) {
     if (tj < nt) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = 8 * (r >> 2) + 4 * hi + (r & 3);  // tile row held in register r
-        const unsigned int off = (unsigned int)sm.q[unk(32 * tj + row)] * bb;
+      for (int g = 0; g < 4; ++g) {  // tile rows held in registers 4 g .. 4 g + 3
+        const unsigned int q4 = reinterpret_cast<const unsigned int*>(sm.q)[8 * tj + 2 * g + hi];
 #pragma unroll
-        for (int ti = tj; ti < NTR; ++ti) T[ti][tj][r] = G[off + qcol[ti]];
+        for (int e = 0; e < 4; ++e) {
+          const unsigned int off = __umul24((q4 >> (8 * e)) & 255u, bb);
+#pragma unroll
+          for (int ti = tj; ti < NTR; ++ti) 
+            T[ti][tj][4 * g + e] = *reinterpret_cast<const float*>(Gc + (off + qcol[ti]));
+        }
       }
     }
   }
+  if (!FULL) {
 #pragma unroll
-  for (int tj = 0; tj < NTR; ++tj)
+    for (int r = 0; r < 16; ++r) {
+      const int row = 8 * (r >> 2) + 4 * hi + (r & 3);
+      const bool in = row < 32 - pad;
+      T[0][0][r] = (in && lo < 32 - pad) ? T[0][0][r] : (row == lo ? 1.f : 0.f);
 #pragma unroll
-    for (int ti = tj; ti < NTR; ++ti)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = 8 * (r >> 2) + 4 * hi + (r & 3);
-        const float ident = (ti == tj && row == lo) ? 1.f : 0.f;  // identity outside the system
-        T[ti][tj][r] = (tj < nt && ti < nt && valid(32 * tj + row) && valid(32 * ti + lo))
-                           ? T[ti][tj][r] : ident;
-      }
-  // Each half of the wavefront only sees the pivots whose row it holds, so the value of a row of
-  // the right-hand side is the SUM of its two lanes (lo and lo + 32); it starts in the lower half.
-  float uv[NTR], zz[NZ];
-#pragma unroll
-  for (int ti = 0; ti < NTR; ++ti)
-    uv[ti] = (hi == 0 && ti < nt && valid(32 * ti + lo)) ? sm.wrow[sm.q[unk(32 * ti + lo)]] : 0.f;
-#pragma unroll
-  for (int z = 0; z < NZ; ++z) zz[z] = 0.f;  // position 64 z + lane: y / d
+      for (int ti = 1; ti < NTR; ++ti) T[ti][0][r] = in ? T[ti][0][r] : 0.f;
+    }
+  }
   // Two pivots per MFMA: rows k1 and k2 = k1 + 4 (k1 mod 8 < 4) of a tile sit in the same
   // register, in the lower and in the upper half of the wavefront, where the two reduction slots
   // of v_mfma_f32_32x32x2_f32 take their operands.  The pivots of a tile are therefore taken in
   // the order 0,4,1,5,2,6,3,7,8,12,...; pair t = (k1, k2) holds POSITIONS 2t and 2t + 1 of that
-  // order.  L~ (unit lower triangular in elimination order), z and lambda are indexed by
+  // order.  L~ (unit lower triangular in elimination order), d, y and lambda are indexed by
   // position; mrow() maps a position back to its matrix index.
   const int pl = 8 * (lo >> 3) + 2 * (lo & 3) + ((lo >> 2) & 1);  // position of index lo in a tile
   auto mrow = [](int P) { return (P & ~7) + ((P & 7) >> 1) + 4 * (P & 1); };
-  // where this lane's element of a column of L~ goes: the packed row of its position; lanes
+  float u[NZ];  // right-hand side by position 64 z + lane
+#pragma unroll
+  for (int z = 0; z < NZ; ++z) {
+    const int m = mrow(64 * z + lane);
+    u[z] = (m < 32 * nt && valid(m)) ? wrow[sm.q[m & 127]] : 0.f;
+  }
+  // where this lane's element of a column of -L~ goes: the packed row of its position; lanes
   // whose element is on / above the diagonal write to scratch
   float* rowp[NTR];
 #pragma unroll
   for (int ti = 0; ti < NTR; ++ti) rowp[ti] = &sm.L[(32 * ti + pl) * (32 * ti + pl - 1) / 2];
-  float* const junk = &sm.dummy[32 + lo];
-  bool bad = false;
+  float* const junk = &sm.L[32 * NTR * (32 * NTR - 1) / 2 + lo];
 
 #pragma unroll
   for (int p = 0; p < NTR; ++p) {
@@ -1110,33 +1121,26 @@ __global__ __launch_bounds__(64 * WPB, 2) void k_solve_mfma(SolveArgs a) {
           const float d1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k1));
           const float c12 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k2));
           const float d2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32 + k2));
-          const float y1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(uv[p]), k1)) +
-                           __int_as_float(__builtin_amdgcn_readlane(__float_as_int(uv[p]), k1 + 32));
-          const float y2r = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(uv[p]), k2)) +
-                            __int_as_float(__builtin_amdgcn_readlane(__float_as_int(uv[p]), k2 + 32));
+          // 1 / d1 and 1 / d2', d2' = d2 - c12^2 / d1 = det / d1 the pivot of k2 after the elimination
+          // of k1, from two independent reciprocals (see tl_eliminate)
+          const float cc = c12 * c12;
+          const float det = fmaf(d1, d2, -cc) - fmaf(c12, c12, -cc);
           const float q1 = __builtin_amdgcn_rcpf(d1);
+          const float qd = __builtin_amdgcn_rcpf(det);
           const float r1 = fmaf(fmaf(-d1, q1, 1.f), q1, q1);
+          const float rd = fmaf(fmaf(-det, qd, 1.f), qd, qd);
           const float m = c12 * r1;
-          const float d2p = fmaf(-c12, m, d2);  // pivot of k2 after the elimination of k1
-          const float q2 = __builtin_amdgcn_rcpf(d2p);
-          const float r2 = fmaf(fmaf(-d2p, q2, 1.f), q2, q2);
-          const float y2 = fmaf(-m, y1, y2r);
-          bad = bad || !(d1 > 0.f) || !(d2p > 0.f);
           const float mh = hi ? m : 0.f;
-          const float rh = hi ? -r2 : -r1;
-          const float yh = hi ? y2 : y1;
+          const float rh = hi ? -(d1 * rd) : -r1;
+          sm.d[32 * p + 2 * t + hi] = hi ? det * r1 : d1;  // one address per half
           // u1 (lower half) and u2 = row k2 after the elimination of k1 (upper half).  Columns
           // eliminated earlier hold rounding residue instead of zero; it is not masked, because
-          // a product with it only ever lands in eliminated rows and columns of the tiles and in
-          // right-hand-side rows that have already been read.
+          // a product with it only ever lands in eliminated rows and columns of the tiles.
           const float bop = fmaf(-mh, x, v);
           const float aop = bop * rh;
           T[p][p] = __builtin_amdgcn_mfma_f32_32x32x2f32(aop, bop, T[p][p], 0, 0, 0);
-          // column 2t + hi of L~ within the tile: rows at later positions
-          (pl > 2 * t + hi ? rowp[p] + 32 * p + hi : junk)[2 * t] = -aop;
-          uv[p] = fmaf(aop, yh, uv[p]);
-          if ((lane >> 1) == (((32 * p + 2 * t) & 63) >> 1))
-            zz[(32 * p + 2 * t) >> 6] = (lane & 1) ? y2 * r2 : y1 * r1;
+          // column 2t + hi of -L~ within the tile: rows at later positions
+          (pl > 2 * t + hi ? rowp[p] + 32 * p + hi : junk)[2 * t] = aop;
           float e2[NTR], be[NTR];
 #pragma unroll
           for (int ti = p + 1; ti < NTR; ++ti) {
@@ -1147,8 +1151,7 @@ __global__ __launch_bounds__(64 * WPB, 2) void k_solve_mfma(SolveArgs a) {
               e2[ti] = fmaf(-mh, xe, ev);
               be[ti] = rh * e2[ti];
               T[ti][p] = __builtin_amdgcn_mfma_f32_32x32x2f32(bop, be[ti], T[ti][p], 0, 0, 0);
-              (rowp[ti] + 32 * p + hi)[2 * t] = -be[ti];
-              uv[ti] = fmaf(be[ti], yh, uv[ti]);
+              (rowp[ti] + 32 * p + hi)[2 * t] = be[ti];
 #pragma unroll
               for (int tj = p + 1; tj <= ti; ++tj) {
                 // transposed storage: the first operand runs over the rows of tile row tj
@@ -1160,32 +1163,83 @@ __global__ __launch_bounds__(64 * WPB, 2) void k_solve_mfma(SolveArgs a) {
       }
     }
   }
-  if (bad && lane == 0) atomicCAS(a.info, 0, -(int32_t)min(i + 1, (int64_t)0x7fffffff));
   WAVE_SYNC();
 
-  // ---- L~^T lambda = z: lambda_k is final once all rows below it are done; then column k of
-  //      L~^T (= row k of L~, one LDS row) is swept out of the rows above.  The LDS rows of eight
-  //      unknowns are fetched together, ahead of the dependent chain. ----
+  // ---- L~ y = u, then L~^T lambda = D^-1 y.  A sweep reads one unknown off its lane (y_k or lambda_k,
+  //      final by then) and adds its column of -L~ (row of -L~^T) to all others; lanes that are
+  //      already final get rubbish, their value was put aside.  The LDS reads of eight unknowns
+  //      are fetched together, ahead of the dependent chain: of a column every lane reads its own
+  //      packed row (whose starts, triangular numbers, fall on different banks), of a row
+  //      consecutive lanes read consecutive elements.
+  //      Carrying u through the elimination instead cost 19 vector instructions per pair of pivots
+  //      in a kernel that is bound by their number. ----
+  float y[NZ], dd[NZ];
+  int pofs[NZ];
+#pragma unroll
+  for (int z = 0; z < NZ; ++z) {
+    const int P = min(64 * z + lane, 32 * NTR - 1);
+    pofs[z] = P * (P - 1) / 2;
+    dd[z] = sm.d[P];
+    y[z] = 0.f;
+  }
+#pragma unroll
+  for (int k8 = 0; k8 < 32 * NTR; k8 += 8) {
+    if (k8 < 32 * nt) {
+      __builtin_amdgcn_sched_barrier(0);  // eight ahead, not all of them: registers
+      float col[8][NZ];
+#pragma unroll
+      for (int t = 0; t < 8; ++t)
+#pragma unroll
+        for (int z = 0; z < NZ; ++z)
+          col[t][z] = (64 * z + 63 > k8 + t) ? sm.L[pofs[z] + k8 + t] : 0.f;
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const int k = k8 + t;
+        if (valid(mrow(k))) {
+          const int yk = __builtin_amdgcn_readlane(__float_as_int(u[k >> 6]), k & 63);
+          set_lane(y[k >> 6], yk, k & 63);
+#pragma unroll
+          for (int z = 0; z < NZ; ++z)
+            if (64 * z + 63 > k) u[z] = fmaf(col[t][z], __int_as_float(yk), u[z]);
+        }
+      }
+    }
+  }
+  bool bad = false;
+  float lam[NZ];
+#pragma unroll
+  for (int z = 0; z < NZ; ++z) {
+    const int P = 64 * z + lane;
+    const bool in = P < 32 * nt && valid(mrow(P));
+    bad = bad || (in && !(dd[z] > 0.f));
+    const float q0 = __builtin_amdgcn_rcpf(dd[z]);
+    const float q1 = fmaf(fmaf(-dd[z], q0, 1.f), q0, q0);
+    u[z] = in ? y[z] * q1 : 0.f;
+    lam[z] = 0.f;
+  }
+  if (__ballot(bad) != 0ull && lane == 0)
+    atomicCAS(a.info, 0, -(int32_t)min(i + 1, (int64_t)0x7fffffff));
 #pragma unroll
   for (int k8 = 32 * NTR - 8; k8 >= 0; k8 -= 8) {
     if (k8 < 32 * nt) {
+      __builtin_amdgcn_sched_barrier(0);
       float row[8][NZ];
 #pragma unroll
       for (int t = 0; t < 8; ++t) {
         const int k = k8 + t;
 #pragma unroll
-        for (int z = 0; z < NZ; ++z)  // lanes past the row read beyond it: masked below
+        for (int z = 0; z < NZ; ++z)
           row[t][z] = (64 * z < k) ? sm.L[k * (k - 1) / 2 + 64 * z + lane] : 0.f;
       }
 #pragma unroll
       for (int t = 7; t >= 0; --t) {
         const int k = k8 + t;
-        if (k >= 1 && k < 32 * nt && valid(mrow(k))) {
-          const float lk =
-              __int_as_float(__builtin_amdgcn_readlane(__float_as_int(zz[k >> 6]), k & 63));
+        if (valid(mrow(k))) {
+          const int lk = __builtin_amdgcn_readlane(__float_as_int(u[k >> 6]), k & 63);
+          set_lane(lam[k >> 6], lk, k & 63);
 #pragma unroll
           for (int z = 0; z < NZ; ++z)
-            if (64 * z < k) zz[z] = fmaf(-((64 * z + lane < k) ? row[t][z] : 0.f), lk, zz[z]);
+            if (64 * z < k) u[z] = fmaf(row[t][z], __int_as_float(lk), u[z]);
         }
       }
     }
@@ -1193,21 +1247,21 @@ __global__ __launch_bounds__(64 * WPB, 2) void k_solve_mfma(SolveArgs a) {
 
   // ---- lambda row: zeros except lambda_l at column q_l ----
 #pragma unroll
-  for (int r = 0; r < CPL; ++r) sm.wrow[lane + 64 * r] = 0.f;
+  for (int r = 0; r < CPL; ++r) wrow[lane + 64 * r] = 0.f;
   WAVE_SYNC();
 #pragma unroll
   for (int z = 0; z < NZ; ++z)
     if (64 * z + lane < 32 * nt && valid(mrow(64 * z + lane)))
-      sm.wrow[sm.q[unk(mrow(64 * z + lane))]] = zz[z];
+      wrow[sm.q[mrow(64 * z + lane)]] = lam[z];
   WAVE_SYNC();
   if (comp) {
     // wrow holds y on the kept columns: lambda = ((w~ - y~) K)_q
 #pragma unroll
     for (int r = 0; r < CPL; ++r)
-      sm.key[lane + 64 * r] = (sel[r] ? wv[r] : 0.f) - sm.wrow[lane + 64 * r];
+      key[lane + 64 * r] = (sel[r] ? wv[r] : 0.f) - wrow[lane + 64 * r];
     WAVE_SYNC();
     float l[CPL];
-    matvec_k(sm.key, l);
+    matvec_k(key, l);
 #pragma unroll
     for (int r = 0; r < CPL; ++r) {
       const int col = lane + 64 * r;
@@ -1218,7 +1272,7 @@ __global__ __launch_bounds__(64 * WPB, 2) void k_solve_mfma(SolveArgs a) {
 #pragma unroll
   for (int r = 0; r < CPL; ++r) {
     const int col = lane + 64 * r;
-    if (col < a.bw) lam_g[col] = sm.wrow[col];
+    if (col < a.bw) lam_g[col] = wrow[col];
   }
 }
 
