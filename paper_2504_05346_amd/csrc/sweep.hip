@@ -627,7 +627,9 @@ __device__ __forceinline__ long long ties_before(const SelState* __restrict__ st
 // lambda R_hat = u with R_hat = G[q, q], G the block's rows of the residual inverse, q the
 // removed columns of the row (Sec. 4.5), u the removed weights.  Three kernels share the
 // arguments below and differ in how many unknowns they hold and where.
-enum { SEL_NM = 0, SEL_THRESHOLD = 1, SEL_GIVEN = 2 };
+// SEL_PICKED: k_pick has chosen the block's mask (mask_out, row_cnt) and k_lam_rows turns what the rows
+// solved through the complement leave in Z into multipliers.
+enum { SEL_NM = 0, SEL_THRESHOLD = 1, SEL_GIVEN = 2, SEL_PICKED = 3 };
 
 struct SolveArgs {
   const float* W;        // c x b, current weights
@@ -651,6 +653,9 @@ struct SolveArgs {
   const float* Kc;       // k_solve_tiled: inverse of this block's G (bw x bw, row stride ldk), or
   int ldk;               // nullptr; rows that lose more than half of the block are solved through it
   int defer_large;       // k_solve_mfma: rows with more unknowns than it holds belong to another launch
+  float* Z;              // SEL_PICKED: c x ldz, w~ on entry, (w~ - y~) of the complement rows on return
+  const float* WK;       // SEL_PICKED: c x ldz, w~ K
+  int ldz;
 };
 
 // ------------------------------------------------------------------------------------------
@@ -1627,6 +1632,12 @@ __global__ __launch_bounds__(64 * NW, (BIG ? 2 : (NW == 8 ? 4 : 5))) void k_solv
       const int col = tid + NT * ch;
       sel[ch] = (col < a.bw) && a.mask_in[i * a.b + a.j1 + col] != 0;
     }
+  } else if (SEL == SEL_PICKED) {
+#pragma unroll
+    for (int ch = 0; ch < CH; ++ch) {
+      const int col = tid + NT * ch;
+      sel[ch] = (col < a.bw) && a.mask_out[i * a.b + a.j1 + col] != 0;
+    }
   } else if (SEL == SEL_NM) {
 #pragma unroll
     for (int ch = 0; ch < CH; ++ch) {
@@ -1703,7 +1714,7 @@ __global__ __launch_bounds__(64 * NW, (BIG ? 2 : (NW == 8 ? 4 : 5))) void k_solv
 #pragma unroll
   for (int ch = 0; ch < CH; ++ch) {
     const int col = tid + NT * ch;
-    if (col < a.bw) a.mask_out[i * a.b + a.j1 + col] = sel[ch] ? 1 : 0;
+    if (SEL != SEL_PICKED && col < a.bw) a.mask_out[i * a.b + a.j1 + col] = sel[ch] ? 1 : 0;
   }
   // A block may be solved by two launches with different numbers of wavefronts per row: this one
   // takes the rows with nt_lo <= ceil(ns/32) <= nt_max and leaves the others untouched.
@@ -1750,6 +1761,8 @@ __global__ __launch_bounds__(64 * NW, (BIG ? 2 : (NW == 8 ? 4 : 5))) void k_solv
   float* part = BIG ? nullptr : tiles;
   if (!comp) {
     for (int t = tid; t < 32 * nt; t += NT) u[t] = (t < s) ? wrow[q[t]] : 0.f;
+  } else if (SEL == SEL_PICKED) {
+    for (int t = tid; t < 32 * nt; t += NT) u[t] = (t < ns) ? a.WK[i * a.ldz + q[t]] : 0.f;
   } else {
     // right-hand side (w~ K)_k: x = w~ in `key`, the product lands in `wrow` (the row's weights
     // stay in registers)
@@ -1918,6 +1931,8 @@ __global__ __launch_bounds__(64 * NW, (BIG ? 2 : (NW == 8 ? 4 : 5))) void k_solv
       const int col = tid + NT * ch;
       if (col < a.bw) lam_g[col] = wrow[col];
     }
+  } else if (SEL == SEL_PICKED) {  // w~ - y~: -y on the kept columns, w~ is there
+    for (int t = tid; t < ns; t += NT) a.Z[i * a.ldz + q[t]] = -lam[t];
   } else {
     // lambda = ((w~ - y~) K)_q: x = w on the removed columns, -y on the kept ones
     __syncthreads();
@@ -1935,6 +1950,68 @@ __global__ __launch_bounds__(64 * NW, (BIG ? 2 : (NW == 8 ? 4 : 5))) void k_solv
   }
   if (!BIG) return;  // one row per workgroup
   }  // rows of this workgroup
+}
+
+// ------------------------------------------------------------------------------------------
+// Complement form for many rows.  Its two products of every row with the block's K, w~ K before the
+// solve and (w~ - y~) K after it, are matrix products over all rows: the row solver, where each row
+// fetches K twice (512 KB at 256 columns), spent half of its time on them.
+//   k_pick       mask of the block, s per row, Z = w~ (removed weights, zero elsewhere)
+//   gemm_f32     WK = Z K
+//   k_solve_tiled<SEL_PICKED>   complement rows: Z = w~ - y~; the others: Lam
+//   k_lam_rows   complement rows: Lam = (Z K) on the removed columns, zero elsewhere
+// 8192 rows of 256 columns, 60 %: 400 -> 305 us per block.
+__global__ __launch_bounds__(256) void k_pick(SolveArgs a) {
+  const int lane = threadIdx.x & 63;
+  const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (i >= a.c) return;
+  const bool none = a.st->none != 0;
+  const unsigned int tau = a.st->tau;
+  const long long need_eq = a.st->need_eq;
+  long long tie_rank = ties_before(a.st, a.row_eq, i);
+  int s = 0;
+  for (int c0 = 0; c0 < a.bw; c0 += 64) {  // key < tau, or key == tau and among the first need_eq ties
+    const int col = c0 + lane;
+    const float w = col < a.bw ? a.W[i * a.b + a.j1 + col] : 0.f;
+    const bool in = col < a.bw && !none;
+    const unsigned int key = in ? metric_key(w, a.sx[a.j1 + col]) : 0xffffffffu;
+    const bool eq = in && key == tau;
+    const unsigned long long eqb = __ballot(eq);
+    const bool sel = (in && key < tau) ||
+                     (eq && tie_rank + __popcll(eqb & ((1ull << lane) - 1ull)) < need_eq);
+    tie_rank += __popcll(eqb);
+    s += __popcll(__ballot(sel));
+    if (col < a.bw) {
+      a.mask_out[i * a.b + a.j1 + col] = sel ? 1 : 0;
+      a.Z[i * a.ldz + col] = sel ? w : 0.f;
+    }
+  }
+  if (lane == 0) a.row_cnt[i] = s;
+}
+
+__global__ __launch_bounds__(kXThreads, 4) void k_lam_rows(SolveArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char sm[];
+  const int n0 = blockIdx.x * kTN;
+  const int64_t m0 = (int64_t)blockIdx.y * kTM;
+  const int m_ext = (int)min((int64_t)kTM, a.c - m0), n_ext = min(kTN, a.bw - n0);
+  TileAcc acc;
+  acc_zero(acc);
+  // K is symmetric: its rows serve as columns
+  gemm_tile_x3<false, false>(acc, sm, a.Z + m0 * a.ldz, a.ldz, m_ext, a.Kc + (int64_t)n0 * a.ldk, a.ldk,
+                             n_ext, 0, a.bw, true, true);
+  const float* T = x3_stage_tile(acc, sm);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int r = wave; r < m_ext; r += 8) {
+    const int64_t i = m0 + r;
+    if (2 * a.row_cnt[i] <= a.bw) continue;  // solved directly
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int col = lane + 64 * e;
+      if (col < n_ext)
+        a.Lam[i * a.ldl + n0 + col] =
+            a.mask_out[i * a.b + a.j1 + n0 + col] ? T[r * kXCLd + col] : 0.f;
+    }
+  }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2207,6 +2284,8 @@ static inline int64_t big_slot_floats(int smax) {
   return (int64_t)tl_ntiles((std::min(smax, kBigSmax) + 31) / 32) * kTlSz;
 }
 
+constexpr int64_t kPickRows = 2560;
+
 static void launch_update(hipStream_t s, UpdateArgs ua, dim3 tiles) {
   ua.gx = (int)tiles.x;
   ua.gy = (int)tiles.y;
@@ -2346,6 +2425,23 @@ __global__ __launch_bounds__(256) void k_sweep_init(InitArgs a) {
   }
 }
 
+// k_solve_tiled with the tiles in registers: systems of up to smax <= 256 unknowns.
+template <int SEL>
+static void launch_tiled(hipStream_t s, SolveArgs a, int smax) {
+  // Four wavefronts per row hold systems of up to 128 unknowns, eight up to 256.  When s varies
+  // from row to row and may be larger than 128, each size gets a launch and the rows pick theirs.
+  const size_t smem4 = rs_smem_floats<4>() * sizeof(float), smem8 = rs_smem_floats<8>() * sizeof(float);
+  const bool small = smax <= 128, varies = SEL != SEL_NM;
+  a.nt_lo = 0;
+  a.nt_max = 4;
+  if (small || varies)
+    hipLaunchKernelGGL((k_solve_tiled<SEL, 4>), dim3((unsigned)a.c), dim3(256), smem4, s, a);
+  if (small) return;
+  a.nt_lo = varies ? 5 : 0;
+  a.nt_max = kTlSmax / 32;  // the launch that reports systems beyond the solver's limit
+  hipLaunchKernelGGL((k_solve_tiled<SEL, 8>), dim3((unsigned)a.c), dim3(512), smem8, s, a);
+}
+
 template <int SEL>
 static void launch_solve(hipStream_t s, SolveArgs a, int smax) {
   // tiled solver: rows that lose more than half of the block are solved through the complement
@@ -2395,18 +2491,7 @@ static void launch_solve(hipStream_t s, SolveArgs a, int smax) {
                        dim3((unsigned)std::min<int64_t>(a.c, kBigSlots)), dim3(64 * kNw),
                        tl_big_smem_bytes(), s, a);
   } else {
-    // Four wavefronts per row hold systems of up to 128 unknowns, eight up to 256.  When s varies
-    // from row to row and may be larger than 128, each size gets a launch and the rows pick theirs.
-    const size_t smem4 = rs_smem_floats<4>() * sizeof(float), smem8 = rs_smem_floats<8>() * sizeof(float);
-    const bool small = smax <= 128, varies = SEL != SEL_NM;
-    a.nt_lo = 0;
-    a.nt_max = 4;
-    if (small || varies)
-      hipLaunchKernelGGL((k_solve_tiled<SEL, 4>), dim3((unsigned)a.c), dim3(256), smem4, s, a);
-    if (small) return;
-    a.nt_lo = varies ? 5 : 0;
-    a.nt_max = kTlSmax / 32;  // the launch that reports systems beyond the solver's limit
-    hipLaunchKernelGGL((k_solve_tiled<SEL, 8>), dim3((unsigned)a.c), dim3(512), smem8, s, a);
+    launch_tiled<SEL>(s, a, smax);
   }
 }
 
@@ -2559,12 +2644,35 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
     sa.slot_floats = big_slot_floats(smax_all);
     sa.Kc = comp ? w.Kc + blk * (int64_t)B * B : nullptr;
     sa.ldk = B;
+    sa.Z = nullptr;
+    sa.WK = nullptr;
+    sa.ldz = 0;
     if (o->mask_in) {
       launch_solve<SEL_GIVEN>(s, sa, bw);
     } else if (o->mode == THANOS_NM) {
       launch_solve<SEL_NM>(s, sa, bw / o->m * o->n);
     } else {
-      launch_solve<SEL_THRESHOLD>(s, sa, bw);
+      // Four launches instead of one pay from two rounds of rows on (five rows per compute unit), where
+      // half of the rows or more go the complement way.
+      const bool many = comp && bw > 128 && !needs_big(bw, bw / 2) && c >= kPickRows && o->sparsity >= 0.5;
+      if (many) {
+        sa.Z = w.Lam + (int64_t)c * ldl;  // behind this block's multipliers: the buffer has room for 16 blocks
+        sa.WK = sa.Z + (int64_t)c * ldl;
+        sa.ldz = ldl;
+        hipLaunchKernelGGL(k_pick, dim3((unsigned)ceil_div(c, 4)), dim3(256), 0, s, sa);
+        THANOS_LAUNCH_CHECK();
+        THANOS_CHECK(gemm_f32(s, false, false, c, bw, bw, 1.f, sa.Z, ldl, sa.Kc, B, 0.f,
+                              w.Lam + (int64_t)2 * c * ldl, ldl, false));
+        launch_tiled<SEL_PICKED>(s, sa, bw / 2);
+        THANOS_LAUNCH_CHECK();
+        THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_lam_rows),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             (int)kXSmemBytes));
+        hipLaunchKernelGGL(k_lam_rows, dim3((unsigned)ceil_div(bw, kTN), (unsigned)ceil_div(c, kTM)),
+                           dim3(kXThreads), kXSmemBytes, s, sa);
+      } else {
+        launch_solve<SEL_THRESHOLD>(s, sa, bw);
+      }
     }
     THANOS_LAUNCH_CHECK();
 

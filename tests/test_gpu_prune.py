@@ -356,6 +356,30 @@ def test_factor_reuse_matches_internal_factor():
     np.testing.assert_array_equal(a[0], b_[0])
 
 
+@pytest.mark.parametrize("c,b,B,p", [
+    (2560, 768, 256, 0.6),    # whole row tiles, last block whole
+    (2603, 700, 256, 0.75),   # ragged rows, last block 188 wide
+    (2570, 836, 512, 0.5),    # up to 256 unknowns, rows on either side of half a block
+])
+def test_complement_form_for_many_rows(c, b, B, p):
+    """From 2560 rows on the complement's products with K run as matrix products over all rows."""
+    from tests.gpu_util import gpu_prune
+    W, H32 = _layer(c, b, 4 * b, "f32", seed=c)
+    W[:3] *= 1e-3     # loses whole blocks
+    W[3:6] *= 1e3     # loses next to nothing
+    H = H32.astype(np.float64)
+    Wg, Mg, info = gpu_prune(W, H32, mode="unstructured", p=p, B=B)
+    assert info == 0
+    assert int(Mg.sum()) == orc.num_to_remove(p, c, b)
+    assert np.all(Wg[Mg == 1] == 0.0)
+    Wo, _ = orc.prune_fast(W, H, mode="unstructured", p=p, B=B, damp=0.01, mask_in=Mg)
+    some = np.linalg.norm(Wo, axis=1) > 0
+    rows = np.linalg.norm(Wg - Wo, axis=1)[some] / np.linalg.norm(Wo, axis=1)[some]
+    assert rows.max() < 1e-3  # as in the other parity tests of this file
+    _, Mo = orc.prune_fast(W, H, mode="unstructured", p=p, B=B, damp=0.01)
+    assert (Mo != Mg).mean() < 1e-4
+
+
 # --------------------------------------------------------------------------- ties
 @pytest.mark.parametrize("B", [64, 128, 256])   # one block size per per-row solver
 def test_exact_ties_follow_row_major_order(B):
