@@ -273,12 +273,18 @@ thanos_status gemm_f32(hipStream_t s, bool a_kmajor, bool b_kmajor, int64_t M, i
                        int64_t ldb, float beta, float* C, int64_t ldc, bool lower_only,
                        TriB b_tri = kTriNone, bool beside = false);
 
+// C = beta*C + alpha * A B^T for operands whose magnitude is bounded (A[m*lda + k], B[n*ldb + k]; bound_b_dev:
+// the bound of B is read from the device instead).  The same precision in half of the matrix instructions.
+thanos_status gemm_bounded(hipStream_t s, int64_t M, int64_t N, int64_t K, float alpha, const float* A,
+                           int64_t lda, float bound_a, const float* B, int64_t ldb, float bound_b,
+                           const float* bound_b_dev, float beta, float* C, int64_t ldc, bool lower_only);
+
 thanos_status syrk_accumulate(hipStream_t s, float* H, int64_t b, const void* Xc,
                               thanos_dtype xdt, int64_t n_tok, int64_t ldx, float alpha);
 
 // Damped factorisation (factor.hip).  After it the lower triangle of the reversed, padded copy
-// in the workspace holds the Cholesky factor L of J H_d J (U = J L^{-1} J): factor_L() returns
-// it and its leading dimension.
+// in the workspace holds the Cholesky factor L of J D H_d D J, D diagonal with powers of two
+// (U = J L^{-1} J D): factor_L() returns it and its leading dimension, factor_scale() the diagonal of D.
 size_t factor_workspace_bytes(int64_t b);
 // single_stream: no helper streams, everything on `s` in enqueue order (nothing is created).
 thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, float* U,
@@ -289,6 +295,7 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
 thanos_status factor_begin(hipStream_t s, const float* H, int64_t b, float damping, float* xnorm2,
                            void* ws, int32_t* info);
 const float* factor_L(const void* ws, int64_t b, int64_t* ld);
+const float* factor_scale(const void* ws, int64_t b);
 
 // skip[i] = 1 for the n_out rows of W (c x b fp32) with the largest loss W_i H W_i^T (sweep.hip).
 thanos_status row_outliers(hipStream_t s, const float* W, const float* H, int64_t c, int64_t b,

@@ -15,24 +15,44 @@
 // blocks, rank 4 NB for everything right of it); (3) L^{-1} by recursive doubling over
 // block pairs, X21 = -Linv22 * (L21 * Linv11), two products per level; (4) U = J L^{-1} J.
 // Everything is fp32.
+//
+// Ranges.  The copy of step (1) is D A' D with D diagonal, powers of two that bring the diagonal into
+// [1, 4): every value of the factorisation is then the unscaled one times a power of two, so nothing
+// changes in it, but |L_ij| <= 2 whatever the scales of the channels are (a row of L has the norm
+// sqrt(A'_ii)), and the products can split their operands into two fp16 values (gemm_tile_h2.h)
+// instead of three bf16 ones.  L^{-1} is bounded by what is written: every diagonal block and every
+// merge leaves the largest magnitude of its block column in `bounds`.  Step (4) takes D out again.
 #include <algorithm>
 
-#include "gemm_tile_x3.h"
+#include "gemm_tile_h2.h"
 #include "tile32.h"
 
 namespace thanos {
 
 constexpr int NB = kFactorNB;
+// Bounds of what the products read (see above), with room for rounding: values of the scaled matrix and
+// of its Schur complements, and of L.
+constexpr float kBoundA = 7.f, kBoundL = 3.f;
 
 // ------------------------------------------------------------------------------------------
-// xnorm2[j] = H[j][j];  lam = damping * mean_j H[j][j]  (sum in fp64, fixed order).
-// One workgroup of 1024 threads.
+// d[j], the power of two with d^2 h in [1, 4) for a damped diagonal element h (1 where h is not positive or
+// not finite: the factorisation reports those).
+__device__ __forceinline__ float diag_scale(float h) {
+  if (!(h > 0.f) || !(h < INFINITY)) return 1.f;
+  const int e = min(max(ilogbf(h), -124), 124);
+  return ldexpf(1.f, -(e >> 1));
+}
+
+// xnorm2[j] = H[j][j];  lam = damping * mean_j H[j][j]  (sum in fp64, fixed order);  d[j] = the scale of
+// channel j.  Also clears the n_bounds bounds.  One workgroup of 1024 threads.
 __global__ __launch_bounds__(1024) void k_diag_stats(const float* __restrict__ H, int64_t b,
                                                      float damping, float* __restrict__ xnorm2,
-                                                     float* __restrict__ lam_out,
+                                                     float* __restrict__ lam_out, float* __restrict__ d_out,
+                                                     float* __restrict__ bounds, int n_bounds,
                                                      int32_t* __restrict__ info) {
   __shared__ double part[1024];
   double s = 0.0;
+  for (int e = threadIdx.x; e < n_bounds; e += 1024) bounds[e] = 0.f;
   // eight loads in flight (each touches a page of its own); added in order
   for (int64_t j0 = threadIdx.x; j0 < b; j0 += 8 * 1024) {
     float d[8];
@@ -54,18 +74,28 @@ __global__ __launch_bounds__(1024) void k_diag_stats(const float* __restrict__ H
     if ((int)threadIdx.x < off) part[threadIdx.x] += part[threadIdx.x + off];
     __syncthreads();
   }
+  const float lam = (float)((double)damping * (part[0] / (double)b));
   if (threadIdx.x == 0) {
-    *lam_out = (float)((double)damping * (part[0] / (double)b));
+    *lam_out = lam;
     *info = 0;
   }
+  for (int64_t j = threadIdx.x; j < b; j += 1024) d_out[j] = diag_scale(xnorm2[j] + lam);  // its own writes
 }
 
-// A'[i][j] = H_d[b-1-i][b-1-j] for i >= j (read from the lower triangle of H as
+// *bound <- max(*bound, largest of the wavefronts' m), m >= 0 (NaN counts as large)
+__device__ __forceinline__ void raise_bound(float* bound, float m) {
+  uint32_t u = __float_as_uint(m);
+  for (int off = 32; off > 0; off >>= 1) u = max(u, (uint32_t)__shfl_xor((int)u, off, 64));
+  if ((threadIdx.x & 63) == 0) atomicMax(reinterpret_cast<unsigned int*>(bound), u);
+}
+
+// A'[i][j] = (D H_d D)[b-1-i][b-1-j] for i >= j (read from the lower triangle of H as
 // H[b-1-j][b-1-i]); identity on the padding; zero above the diagonal.  32x32 tiles through
 // LDS so that both the read of H and the write of A' are coalesced.
 __global__ __launch_bounds__(256) void k_reverse_pad(const float* __restrict__ H, int64_t b,
                                                      const float* __restrict__ lam_p,
-                                                     float* __restrict__ Ap, int64_t bp) {
+                                                     const float* __restrict__ d, float* __restrict__ Ap,
+                                                     int64_t bp) {
   __shared__ float t[32][33];
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
   const int64_t i0 = (int64_t)blockIdx.y * 32, j0 = (int64_t)blockIdx.x * 32;
@@ -84,12 +114,13 @@ __global__ __launch_bounds__(256) void k_reverse_pad(const float* __restrict__ H
   }
   __syncthreads();
   const float lam = *lam_p;
+  const float dj = d[max(b - 1 - (j0 + tx), (int64_t)0)];
   for (int r = ty; r < 32; r += 8) {
     const int64_t i = i0 + r, j = j0 + tx;
     float v;
     if (j > i) v = 0.f;
     else if (i >= b) v = (i == j) ? 1.f : 0.f;
-    else v = t[tx][r] + ((i == j) ? lam : 0.f);
+    else v = (t[tx][r] + ((i == j) ? lam : 0.f)) * (d[b - 1 - i] * dj);
     Ap[i * bp + j] = v;
   }
 }
@@ -164,11 +195,13 @@ __device__ __forceinline__ void cd_store_op(float* p, int64_t ld, const float* t
     *reinterpret_cast<f32x4*>(p + (int64_t)nl * ld + 8 * g + 4 * hi) = f;
   }
 }
-// accumulator layout
-__device__ __forceinline__ void cd_store_acc(float* p, int64_t ld, const f32x16& v, int nl, int hi) {
+// accumulator layout; top: largest magnitude stored so far
+__device__ __forceinline__ void cd_store_acc(float* p, int64_t ld, const f32x16& v, int nl, int hi, uint32_t& top) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r)
+  for (int r = 0; r < 16; ++r) {
     p[(int64_t)(8 * (r >> 2) + 2 * (r & 3) + hi) * ld + nl] = v[r];
+    top = max(top, __float_as_uint(fabsf(v[r])));
+  }
 }
 __device__ __forceinline__ f32x16 cd_get(const float* tile, int lo, int hi) {
   f32x16 v;
@@ -200,7 +233,7 @@ __device__ __forceinline__ f32x16 cd_minus_tv(const float* T, const f32x16& V, i
 // room beside one workgroup of the matrix products.
 __global__ __launch_bounds__(512, 4) void k_chol_diag(float* __restrict__ Ap,
                                                       float* __restrict__ Linv, int64_t bp,
-                                                      int kb_glob, int64_t b,
+                                                      int kb_glob, int64_t b, float* __restrict__ bound,
                                                       int32_t* __restrict__ info) {
   extern __shared__ __attribute__((aligned(16))) float cd_smem[];
   const int lane = threadIdx.x & 63, lo = lane & 31, hi = lane >> 5, nl = tl_nat(lo);
@@ -270,6 +303,7 @@ __global__ __launch_bounds__(512, 4) void k_chol_diag(float* __restrict__ Ap,
 
   // --------------------------------------------------------------------------------- beside it
   f32x16 X, V, Y;
+  uint32_t top = 0;
   if (wave == 4) cd_load_sym(X, Ag(2, 2), bp, nl, hi);
   else if (wave == 5) cd_load_op(X, Ag(3, 2), bp, nl, hi);
   else if (wave == 6) cd_load_sym(X, Ag(3, 3), bp, nl, hi);
@@ -285,7 +319,7 @@ __global__ __launch_bounds__(512, 4) void k_chol_diag(float* __restrict__ Ap,
   if (wave == 4) {
     rs_mma<true>(X, S(cd_l(2, 0)), S(cd_l(2, 0)), lo, hi);
     rs_store(S(kCdA), X, lo, hi);
-    cd_store_acc(Xg(0, 0), bp, cd_get(S(kCdT), lo, hi), nl, hi);
+    cd_store_acc(Xg(0, 0), bp, cd_get(S(kCdT), lo, hi), nl, hi, top);
     cd_store_op(Ag(0, 0), bp, S(cd_l(0, 0)), lo, hi);
   } else if (wave == 5) {
     rs_mma<true>(X, S(cd_l(2, 0)), S(cd_l(3, 0)), lo, hi);
@@ -304,7 +338,7 @@ __global__ __launch_bounds__(512, 4) void k_chol_diag(float* __restrict__ Ap,
     V = cd_zero();
     rs_mma<false>(V, S(cd_l(2, 1)), S(kCdT + 1), lo, hi);  // V_21
   } else if (wave == 5) {
-    cd_store_acc(Xg(1, 1), bp, cd_get(S(kCdT + 1), lo, hi), nl, hi);
+    cd_store_acc(Xg(1, 1), bp, cd_get(S(kCdT + 1), lo, hi), nl, hi, top);
     cd_store_op(Ag(1, 1), bp, S(cd_l(1, 1)), lo, hi);
     cd_store_op(Ag(2, 1), bp, S(cd_l(2, 1)), lo, hi);
     cd_store_op(Ag(3, 1), bp, S(cd_l(3, 1)), lo, hi);
@@ -313,7 +347,7 @@ __global__ __launch_bounds__(512, 4) void k_chol_diag(float* __restrict__ Ap,
     rs_store(S(kCdA + 2), X, lo, hi);
   } else {
     X = cd_minus_tv(S(kCdT + 1), V, lo, hi);  // X_10
-    cd_store_acc(Xg(1, 0), bp, X, nl, hi);
+    cd_store_acc(Xg(1, 0), bp, X, nl, hi, top);
     V = cd_zero();
     rs_mma<false>(V, S(cd_l(2, 0)), S(kCdT), lo, hi);
     rs_mma<false>(V, S(cd_l(2, 1)), X, lo, hi);  // V_20
@@ -321,7 +355,7 @@ __global__ __launch_bounds__(512, 4) void k_chol_diag(float* __restrict__ Ap,
   __syncthreads();  // ---- phase 3: column 2 of L and T_2
   if (wave == 4) {
     Y = cd_minus_tv(S(kCdT + 2), V, lo, hi);  // X_21
-    cd_store_acc(Xg(2, 1), bp, Y, nl, hi);
+    cd_store_acc(Xg(2, 1), bp, Y, nl, hi, top);
     V = cd_zero();
     rs_mma<false>(V, S(cd_l(3, 1)), S(kCdT + 1), lo, hi);
     rs_mma<false>(V, S(cd_l(3, 2)), Y, lo, hi);  // V_31
@@ -329,12 +363,12 @@ __global__ __launch_bounds__(512, 4) void k_chol_diag(float* __restrict__ Ap,
     V = cd_zero();
     rs_mma<false>(V, S(cd_l(3, 2)), S(kCdT + 2), lo, hi);  // V_32
   } else if (wave == 6) {
-    cd_store_acc(Xg(2, 2), bp, cd_get(S(kCdT + 2), lo, hi), nl, hi);
+    cd_store_acc(Xg(2, 2), bp, cd_get(S(kCdT + 2), lo, hi), nl, hi, top);
     cd_store_op(Ag(2, 2), bp, S(cd_l(2, 2)), lo, hi);
     cd_store_op(Ag(3, 2), bp, S(cd_l(3, 2)), lo, hi);
   } else {
     Y = cd_minus_tv(S(kCdT + 2), V, lo, hi);  // X_20
-    cd_store_acc(Xg(2, 0), bp, Y, nl, hi);
+    cd_store_acc(Xg(2, 0), bp, Y, nl, hi, top);
     V = cd_zero();
     rs_mma<false>(V, S(cd_l(3, 0)), S(kCdT), lo, hi);
     rs_mma<false>(V, S(cd_l(3, 1)), X, lo, hi);
@@ -342,11 +376,12 @@ __global__ __launch_bounds__(512, 4) void k_chol_diag(float* __restrict__ Ap,
   }
   __syncthreads();  // ---- L_33 and T_3
   if (wave == 6) {
-    cd_store_acc(Xg(3, 3), bp, cd_get(S(kCdT + 3), lo, hi), nl, hi);
+    cd_store_acc(Xg(3, 3), bp, cd_get(S(kCdT + 3), lo, hi), nl, hi, top);
     cd_store_op(Ag(3, 3), bp, S(cd_l(3, 3)), lo, hi);
   } else {  // wavefronts 7, 4, 5: X_30, X_31, X_32
-    cd_store_acc(Xg(3, wave == 7 ? 0 : wave - 3), bp, cd_minus_tv(S(kCdT + 3), V, lo, hi), nl, hi);
+    cd_store_acc(Xg(3, wave == 7 ? 0 : wave - 3), bp, cd_minus_tv(S(kCdT + 3), V, lo, hi), nl, hi, top);
   }
+  raise_bound(bound, __uint_as_float(top));
 }
 
 // ------------------------------------------------------------------------------------------
@@ -361,7 +396,16 @@ struct TrinvArgs {
   int64_t bp;
   int nb, S;
   int p0, c0;  // this launch: pairs from p0 (blockIdx.z), tile columns of a pair from c0 (blockIdx.x)
+  // Largest magnitudes by block column, nb each: of L^{-1} so far, of Tbuf at this level.  A launch reads
+  // what earlier launches of its stream have left and raises others: equal calls give equal bits.
+  float *bound_inv, *bound_T;
 };
+
+// Whole tile: C = scale * acc, and its largest magnitude into *bound.
+__device__ __forceinline__ void write_tile_bound(const TileAcc& acc, char* smem, float* C, int64_t ldc,
+                                                 float scale, float* bound) {
+  raise_bound(bound, x3_write_tile(acc, smem, C, ldc, scale));
+}
 
 __global__ __launch_bounds__(kXThreads, 4) void k_trinv_T(TrinvArgs a) {
   extern __shared__ __attribute__((aligned(16))) char sm[];
@@ -373,8 +417,10 @@ __global__ __launch_bounds__(kXThreads, 4) void k_trinv_T(TrinvArgs a) {
   const float* B = a.Linv + ((int64_t)base * NB) * a.bp + (int64_t)gj * NB;  // [k][n]
   TileAcc acc;
   acc_zero(acc);
-  gemm_tile_x3<false, true>(acc, sm, A, a.bp, NB, B, a.bp, NB, tj * NB, a.S * NB, true, true);
-  x3_write_tile(acc, sm, a.T + ((int64_t)gi * NB) * a.bp + (int64_t)gj * NB, a.bp, 1.f);
+  const float sa = h2_scale(kBoundL), sb = h2_scale(a.bound_inv[gj]);
+  gemm_tile_h2<false, true>(acc, sm, A, a.bp, NB, sa, nullptr, B, a.bp, NB, sb, tj * NB, a.S * NB, true, true);
+  write_tile_bound(acc, sm, a.T + ((int64_t)gi * NB) * a.bp + (int64_t)gj * NB, a.bp,
+                   (1.f / sa) * (1.f / sb), a.bound_T + gj);
 }
 
 __global__ __launch_bounds__(kXThreads, 4) void k_trinv_X(TrinvArgs a) {
@@ -387,17 +433,23 @@ __global__ __launch_bounds__(kXThreads, 4) void k_trinv_X(TrinvArgs a) {
   const float* B = a.T + ((int64_t)(base + a.S) * NB) * a.bp + (int64_t)gj * NB;     // [k][n]
   TileAcc acc;
   acc_zero(acc);
-  gemm_tile_x3<false, true>(acc, sm, A, a.bp, NB, B, a.bp, NB, 0, (ti + 1) * NB, true, true);
-  x3_write_tile(acc, sm, a.Linv + ((int64_t)gi * NB) * a.bp + (int64_t)gj * NB, a.bp, -1.f);
+  uint32_t ba = 0;  // bound of the part of Linv22 that this tile row reads
+  for (int e = threadIdx.x & 63; e <= ti; e += 64) ba = max(ba, __float_as_uint(a.bound_inv[base + a.S + e]));
+  for (int off = 32; off > 0; off >>= 1) ba = max(ba, (uint32_t)__shfl_xor((int)ba, off, 64));
+  const float sa = h2_scale(__uint_as_float(ba)), sb = h2_scale(a.bound_T[gj]);
+  gemm_tile_h2<false, true>(acc, sm, A, a.bp, NB, sa, nullptr, B, a.bp, NB, sb, 0, (ti + 1) * NB, true, true);
+  write_tile_bound(acc, sm, a.Linv + ((int64_t)gi * NB) * a.bp + (int64_t)gj * NB, a.bp,
+                   -(1.f / sa) * (1.f / sb), a.bound_inv + gj);
 }
 
-// U[i][j] = Linv[b-1-i][b-1-j] for j >= i, else 0.
+// U[i][j] = Linv[b-1-i][b-1-j] d[j] for j >= i, else 0.
 __global__ __launch_bounds__(256) void k_reverse_out(const float* __restrict__ Linv, int64_t bp,
-                                                     float* __restrict__ U, int64_t b) {
+                                                     const float* __restrict__ d, float* __restrict__ U,
+                                                     int64_t b) {
   const int64_t i = blockIdx.y;
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (j >= b) return;
-  U[i * b + j] = (j >= i) ? Linv[(b - 1 - i) * bp + (b - 1 - j)] : 0.f;
+  U[i * b + j] = (j >= i) ? Linv[(b - 1 - i) * bp + (b - 1 - j)] * d[j] : 0.f;
 }
 
 static inline int64_t padded(int64_t b) { return ceil_div(b, NB) * NB; }
@@ -406,6 +458,19 @@ const float* factor_L(const void* ws, int64_t b, int64_t* ld) {
   *ld = padded(b);
   return reinterpret_cast<const float*>(reinterpret_cast<const char*>(ws) + 256);
 }
+
+// The scales and the bounds live in the first 128 rows of the inverse's temporary, which no merge writes
+// (its tile rows belong to second halves): bp scales, nb bounds of L^{-1}, nb bounds of Tbuf per level.
+// 1 + 9 levels of at most 512 blocks beside 65536 scales: 128 rows of any width hold them.
+static inline float* scales(const void* ws, int64_t bp) {
+  return reinterpret_cast<float*>(const_cast<char*>(reinterpret_cast<const char*>(ws)) + 256) + 2 * bp * bp;
+}
+static inline int merge_levels(int nb) {
+  int n = 0;
+  for (int S = 1; S < nb; S *= 2) ++n;
+  return n;
+}
+const float* factor_scale(const void* ws, int64_t b) { return scales(ws, padded(b)); }
 
 size_t factor_workspace_bytes(int64_t b) {
   const int64_t bp = padded(b);
@@ -417,10 +482,13 @@ thanos_status factor_begin(hipStream_t s, const float* H, int64_t b, float dampi
   const int64_t bp = padded(b);
   float* lam = reinterpret_cast<float*>(ws);
   float* Ap = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + 256);
-  hipLaunchKernelGGL(k_diag_stats, dim3(1), dim3(1024), 0, s, H, b, damping, xnorm2, lam, info);
+  const int nb = (int)(bp / NB);
+  float* d = scales(ws, bp);
+  hipLaunchKernelGGL(k_diag_stats, dim3(1), dim3(1024), 0, s, H, b, damping, xnorm2, lam, d, d + bp,
+                     nb * (1 + merge_levels(nb)), info);
   THANOS_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_reverse_pad, dim3((unsigned)(bp / 32), (unsigned)(bp / 32)), dim3(256), 0,
-                     s, H, b, lam, Ap, bp);
+                     s, H, b, lam, d, Ap, bp);
   THANOS_LAUNCH_CHECK();
   return THANOS_OK;
 }
@@ -432,6 +500,8 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
   float* Ap = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + 256);
   float* Linv = Ap + bp * bp;
   float* Tb = Linv + bp * bp;
+  const float* d = scales(ws, bp);
+  float* bound_inv = scales(ws, bp) + bp;
   if (!begun) THANOS_CHECK(factor_begin(s, H, b, damping, xnorm2, ws, info));
 
   // Two-level blocking: inside an outer block of kOuter factor blocks the trailing update of a
@@ -486,7 +556,8 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
       THANOS_CHECK(tri.fork(tri_batches));
       ++tri_batches;
     }
-    for (int S = 1; S < nb; S *= 2) {
+    int level = 0;
+    for (int S = 1; S < nb; S *= 2, ++level) {
       for (int second = 0; second < 2; ++second) {
         int p_lo = -1, p_hi = -1;
         for (int p = 0; 2 * p * S + S < nb; ++p) {
@@ -507,7 +578,7 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
         int cols = S;
         if (kdone != nb - 1) cols = std::max(1, std::min(S, tri_cap / (rows_all * np)));
         for (int c0 = 0; c0 < S; c0 += cols) {
-          TrinvArgs a{Ap, Linv, Tb, bp, nb, S, p_lo, c0};
+          TrinvArgs a{Ap, Linv, Tb, bp, nb, S, p_lo, c0, bound_inv, bound_inv + (1 + level) * nb};
           dim3 grid((unsigned)std::min(cols, S - c0), (unsigned)rows_all, (unsigned)np);
           if (second)
             hipLaunchKernelGGL(k_trinv_X, grid, dim3(kXThreads), kXSmemBytes, ts, a);
@@ -522,7 +593,8 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
   };
   int pending_join = -1;  // event index recorded on the aux stream after the last "rest"
   for (int k = 0; k < nb; ++k) {
-    hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(512), kCholDiagSmem, s, Ap, Linv, bp, k, b, info);
+    hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(512), kCholDiagSmem, s, Ap, Linv, bp, k, b, bound_inv + k,
+                       info);
     THANOS_LAUNCH_CHECK();
     const int64_t rem = bp - (int64_t)(k + 1) * NB;
     if (rem <= 0) {
@@ -533,8 +605,8 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
     float* panel = Ap + ((int64_t)(k + 1) * NB) * bp + (int64_t)k * NB;
     const float* dinv = Linv + ((int64_t)k * NB) * bp + (int64_t)k * NB;
     // L_ik = A_ik * Linv_kk^T  (in place, all rows below the diagonal block)
-    thanos_status st = gemm_f32(s, false, false, rem, NB, NB, 1.f, panel, bp, dinv, bp, 0.f,
-                                panel, bp, false);
+    thanos_status st = gemm_bounded(s, rem, NB, NB, 1.f, panel, bp, kBoundA, dinv, bp, 0.f, bound_inv + k,
+                                    0.f, panel, bp, false);
     if (st != THANOS_OK) return st;
     if ((k + 1) % kOuter == 0) {
       st = trinv_upto(k);
@@ -547,8 +619,8 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
     const int64_t ncols = (int64_t)(ob_end - (k + 1)) * NB;
     if (ncols > 0) {
       float* trail = Ap + ((int64_t)(k + 1) * NB) * bp + (int64_t)(k + 1) * NB;
-      st = gemm_f32(s, false, false, rem, ncols, NB, -1.f, panel, bp, panel, bp, 1.f, trail, bp,
-                    true);
+      st = gemm_bounded(s, rem, ncols, NB, -1.f, panel, bp, kBoundL, panel, bp, kBoundL, nullptr, 1.f, trail,
+                        bp, true);
       if (st != THANOS_OK) return st;
     }
     // wide: after the last step of an outer block, everything right of it
@@ -566,7 +638,8 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
         const int64_t rows = bp - (int64_t)ob_end * NB;
         const int64_t cols = (int64_t)(next_end - ob_end) * NB;
         float* cs = Ap + ((int64_t)ob_end * NB) * bp + (int64_t)ob_end * NB;
-        st = gemm_f32(s, false, false, rows, cols, kk, -1.f, lp, bp, lp, bp, 1.f, cs, bp, true);
+        st = gemm_bounded(s, rows, cols, kk, -1.f, lp, bp, kBoundL, lp, bp, kBoundL, nullptr, 1.f, cs, bp,
+                          true);
         if (st != THANOS_OK) return st;
       }
       // fork: the rest (rows and columns >= next_end) on the second stream, next to the
@@ -577,8 +650,8 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
         const int64_t rest = bp - (int64_t)next_end * NB;
         const float* lr = lp + ((int64_t)(next_end - ob_end) * NB) * bp;
         float* cr = Ap + ((int64_t)next_end * NB) * bp + (int64_t)next_end * NB;
-        st = gemm_f32(aux.stream, false, false, rest, rest, kk, -1.f, lr, bp, lr, bp, 1.f, cr, bp,
-                      true);
+        st = gemm_bounded(aux.stream, rest, rest, kk, -1.f, lr, bp, kBoundL, lr, bp, kBoundL, nullptr, 1.f, cr,
+                          bp, true);
         if (st != THANOS_OK) return st;
         THANOS_CHECK(aux.record(2 * ob + 1));
         pending_join = 2 * ob + 1;
@@ -588,7 +661,7 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
   if (pending_join >= 0) THANOS_CHECK(aux.join(pending_join));
 
   hipLaunchKernelGGL(k_reverse_out, dim3((unsigned)ceil_div(b, 256), (unsigned)b), dim3(256), 0, s,
-                     Linv, bp, U, b);
+                     Linv, bp, d, U, b);
   THANOS_LAUNCH_CHECK();
   return THANOS_OK;
 }

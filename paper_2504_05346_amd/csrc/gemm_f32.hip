@@ -1,8 +1,9 @@
-// fp32 matrix product (split-bf16 arithmetic on the matrix cores, see gemm_tile_x3.h), used by
-// the factorisation, the sweep and the fp32 Hessian accumulation.
+// fp32 matrix product on the 16-bit matrix cores: split bf16 for operands of any range
+// (gemm_tile_x3.h: sweep, row losses, structured update, fp32 Hessian accumulation), split fp16 where
+// the range is known (gemm_tile_h2.h: the factorisation).
 #include <algorithm>
 
-#include "gemm_tile_x3.h"
+#include "gemm_tile_h2.h"
 
 namespace thanos {
 
@@ -16,9 +17,11 @@ struct GemmArgs {
   int lower_only;
   int vec_a, vec_b, vec_c;
   int b_tri;  // TriB
+  float sa, sb;          // H2: scales of the operands ...
+  const float* bound_b;  // ... of B from a bound on the device instead, unless nullptr
 };
 
-template <bool AK, bool BK>
+template <bool AK, bool BK, bool H2 = false>
 __global__ __launch_bounds__(kXThreads, 4) void k_gemm_f32(GemmArgs g) {
   extern __shared__ __attribute__((aligned(16))) char sm[];
   // Triangular op(B): tiles differ in the length of their reduction, and the longest go first (a
@@ -36,7 +39,14 @@ __global__ __launch_bounds__(kXThreads, 4) void k_gemm_f32(GemmArgs g) {
   acc_zero(acc);
   const int kbeg = g.b_tri == kTriLower ? n0 : 0;
   const int kend = g.b_tri == kTriUpper ? min(g.K, n0 + kTN) : g.K;
-  gemm_tile_x3<AK, BK>(acc, sm, A, g.lda, m_ext, B, g.ldb, n_ext, kbeg, kend, g.vec_a, g.vec_b);
+  if constexpr (H2) {
+    const float sb = g.bound_b ? h2_scale(*g.bound_b) : g.sb;
+    gemm_tile_h2<AK, BK>(acc, sm, A, g.lda, m_ext, g.sa, nullptr, B, g.ldb, n_ext, sb, kbeg, kend, g.vec_a,
+                         g.vec_b);
+    g.alpha *= (1.f / g.sa) * (1.f / sb);
+  } else {
+    gemm_tile_x3<AK, BK>(acc, sm, A, g.lda, m_ext, B, g.ldb, n_ext, kbeg, kend, g.vec_a, g.vec_b);
+  }
   const float* T = x3_stage_tile(acc, sm);
   // row pass: wavefront w takes rows w, w + 8, ..., lane l the columns 2l, 2l + 1
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -139,6 +149,33 @@ static inline bool vec_ok(const float* p, int64_t ld) {
   return (reinterpret_cast<uintptr_t>(p) % 16 == 0) && (ld % 4 == 0);
 }
 
+static inline bool direct_ok(const GemmArgs& g) {
+  return g.K > 0 && g.K % 128 == 0 && g.K <= 512 && g.M % 32 == 0 && g.N % kTN == 0 && g.vec_a && g.vec_b &&
+         (int64_t)(g.M / 32) * (g.N / 32) <= kDirectTiles;
+}
+static thanos_status launch_direct(hipStream_t s, const GemmArgs& g) {
+  hipLaunchKernelGGL(k_gemm_direct, dim3((unsigned)(g.N / kTN), (unsigned)(g.M / 32)), dim3(256), 0, s, g);
+  THANOS_LAUNCH_CHECK();
+  return THANOS_OK;
+}
+
+thanos_status gemm_bounded(hipStream_t s, int64_t M, int64_t N, int64_t K, float alpha, const float* A,
+                           int64_t lda, float bound_a, const float* B, int64_t ldb, float bound_b,
+                           const float* bound_b_dev, float beta, float* C, int64_t ldc, bool lower_only) {
+  if (M <= 0 || N <= 0) return THANOS_OK;
+  GemmArgs g{A, B, C, lda, ldb, ldc, (int)M, (int)N, (int)K, alpha, beta, lower_only ? 1 : 0,
+             vec_ok(A, lda) ? 1 : 0, vec_ok(B, ldb) ? 1 : 0,
+             (reinterpret_cast<uintptr_t>(C) % 8 == 0 && ldc % 2 == 0) ? 1 : 0, kTriNone,
+             h2_scale(bound_a), h2_scale(bound_b), bound_b_dev};
+  if (direct_ok(g)) return launch_direct(s, g);
+  THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_f32<false, false, true>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kXSmemBytes));
+  hipLaunchKernelGGL((k_gemm_f32<false, false, true>), dim3((unsigned)ceil_div(N, kTN), (unsigned)ceil_div(M, kTM)),
+                     dim3(kXThreads), kXSmemBytes, s, g);
+  THANOS_LAUNCH_CHECK();
+  return THANOS_OK;
+}
+
 thanos_status gemm_f32(hipStream_t s, bool a_kmajor, bool b_kmajor, int64_t M, int64_t N,
                        int64_t K, float alpha, const float* A, int64_t lda, const float* B,
                        int64_t ldb, float beta, float* C, int64_t ldc, bool lower_only,
@@ -146,13 +183,8 @@ thanos_status gemm_f32(hipStream_t s, bool a_kmajor, bool b_kmajor, int64_t M, i
   if (M <= 0 || N <= 0) return THANOS_OK;
   GemmArgs g{A, B, C, lda, ldb, ldc, (int)M, (int)N, (int)K, alpha, beta, lower_only ? 1 : 0,
              vec_ok(A, lda) ? 1 : 0, vec_ok(B, ldb) ? 1 : 0,
-             (reinterpret_cast<uintptr_t>(C) % 8 == 0 && ldc % 2 == 0) ? 1 : 0, b_tri};
-  if (!a_kmajor && !b_kmajor && K > 0 && K % 128 == 0 && K <= 512 && M % 32 == 0 && N % kTN == 0 &&
-      g.vec_a && g.vec_b && b_tri == kTriNone && (M / 32) * (N / 32) <= kDirectTiles) {
-    hipLaunchKernelGGL(k_gemm_direct, dim3((unsigned)(N / kTN), (unsigned)(M / 32)), dim3(256), 0, s, g);
-    THANOS_LAUNCH_CHECK();
-    return THANOS_OK;
-  }
+             (reinterpret_cast<uintptr_t>(C) % 8 == 0 && ldc % 2 == 0) ? 1 : 0, b_tri, 1.f, 1.f, nullptr};
+  if (!a_kmajor && !b_kmajor && b_tri == kTriNone && direct_ok(g)) return launch_direct(s, g);
   dim3 grid((unsigned)ceil_div(N, kTN), (unsigned)ceil_div(M, kTM));
   if (b_tri != kTriNone) std::swap(grid.x, grid.y);
   void (*kern)(GemmArgs);

@@ -347,17 +347,21 @@ __device__ __forceinline__ const float* x3_stage_tile(const TileAcc& acc, char* 
 }
 
 // Whole, aligned tile: C[0:128, 0:128] = scale * acc (C 8-byte aligned, ldc even).  All 512 threads.
-__device__ __forceinline__ void x3_write_tile(const TileAcc& acc, char* smem, float* C,
+// Returns the largest magnitude that the calling thread has written.
+__device__ __forceinline__ float x3_write_tile(const TileAcc& acc, char* smem, float* C,
                                               int64_t ldc, float scale) {
   const float* T = x3_stage_tile(acc, smem);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t top = 0;  // as bits: NaN counts as large
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     const int row = wave + 8 * i;
     const float2 t = *reinterpret_cast<const float2*>(T + row * kXCLd + 2 * lane);
-    *reinterpret_cast<float2*>(C + (int64_t)row * ldc + 2 * lane) =
-        make_float2(scale * t.x, scale * t.y);
+    const float2 o = make_float2(scale * t.x, scale * t.y);
+    *reinterpret_cast<float2*>(C + (int64_t)row * ldc + 2 * lane) = o;
+    top = max(top, max(__float_as_uint(fabsf(o.x)), __float_as_uint(fabsf(o.y))));
   }
+  return __uint_as_float(top);
 }
 
 }  // namespace thanos

@@ -86,13 +86,15 @@ __global__ __launch_bounds__(256) void k_gather_cols(const float* __restrict__ W
   WQ[i * s + x] = W[i * b + sigma[x]];
 }
 
-// M[x][y] = L[b-1-x][b-1-y] for x <= y, else 0 (s x s): the inverse of U'_ss.
-__global__ __launch_bounds__(256) void k_rev_L(const float* __restrict__ L, int64_t ld, int64_t b,
-                                               int64_t s, float* __restrict__ M) {
+// M[x][y] = L[b-1-x][b-1-y] / d[x] for x <= y, else 0 (s x s): the inverse of U'_ss (L is the factor of the
+// matrix scaled by d).
+__global__ __launch_bounds__(256) void k_rev_L(const float* __restrict__ L, int64_t ld,
+                                               const float* __restrict__ d, int64_t b, int64_t s,
+                                               float* __restrict__ M) {
   const int64_t y = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t x = blockIdx.y;
   if (y >= s) return;
-  M[x * s + y] = (x <= y) ? L[(b - 1 - x) * ld + (b - 1 - y)] : 0.f;
+  M[x * s + y] = (x <= y) ? L[(b - 1 - x) * ld + (b - 1 - y)] / d[x] : 0.f;
 }
 
 // Non-skipped rows: column j sits at position pos = rank[j] of the permuted order;
@@ -227,7 +229,7 @@ thanos_status structured(hipStream_t st, const void* W_in, thanos_dtype wdt, int
     int64_t ldL = 0;
     const float* L = factor_L(fws, b, &ldL);
     hipLaunchKernelGGL(k_rev_L, dim3((unsigned)ceil_div(s, 256), (unsigned)s), dim3(256), 0, st, L,
-                       ldL, b, s, HB);
+                       ldL, factor_scale(fws, b), b, s, HB);
     THANOS_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_gather_cols, dim3((unsigned)ceil_div(s, 256), (unsigned)c), dim3(256), 0,
                        st, W, b, sigma, s, WQ);

@@ -72,9 +72,11 @@ __global__ __launch_bounds__(kXThreads, 4) void k_block_rows(BlockRowsArgs a) {
 // (V[x][y] = L[b-1-x][b-1-y], L = its workspace's lower factor of the index-reversed matrix), and
 // the diagonal block of the inverse of a triangular matrix is the inverse of its diagonal block:
 // no inversion is computed.  Kc[blk][a][j] = sum_{m >= max(a, j)} V[j1+a][j1+m] V[j1+j][j1+m],
-// row stride B.  One workgroup per 32 x 32 tile of a block.
+// row stride B.  One workgroup per 32 x 32 tile of a block.  L is the factor of the scaled matrix: row
+// b-1-x of it is d[x] times that of the matrix itself.
 __global__ __launch_bounds__(256) void k_comp_blocks(const float* __restrict__ L, int64_t ldL,
-                                                     int64_t b, int B, float* __restrict__ Kc) {
+                                                     const float* __restrict__ d, int64_t b, int B,
+                                                     float* __restrict__ Kc) {
   __shared__ float Va[32][33], Vj[32][33];
   const int64_t j1 = (int64_t)blockIdx.z * B;
   const int bw = (int)min((int64_t)B, b - j1);
@@ -105,7 +107,8 @@ __global__ __launch_bounds__(256) void k_comp_blocks(const float* __restrict__ L
   float* out = Kc + (int64_t)blockIdx.z * B * B;
 #pragma unroll
   for (int e = 0; e < 4; ++e)
-    if (a0 + ty + 8 * e < bw && c0 + tx < bw) out[(int64_t)(a0 + ty + 8 * e) * B + c0 + tx] = acc[e];
+    if (a0 + ty + 8 * e < bw && c0 + tx < bw)
+      out[(int64_t)(a0 + ty + 8 * e) * B + c0 + tx] = acc[e] / d[j1 + a0 + ty + 8 * e] / d[j1 + c0 + tx];
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2513,7 +2516,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
                     const float* H, const float* U, const float* xnorm2,
                     const thanos_prune_opts* o, long long r_total, long long n_out, float* W,
                     void* W_cast, uint8_t* mask, void* ws, int32_t* info, bool single_stream,
-                    PhaseTimer* pt, const float* Lfac, int64_t ldL, bool prepared,
+                    PhaseTimer* pt, const float* Lfac, int64_t ldL, const float* Ldiag, bool prepared,
                     bool clear_info) {
   const int B = o->block_size;
   const bool outliers = n_out > 0;
@@ -2553,7 +2556,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
     if (comp) {
       const unsigned nt32 = (unsigned)ceil_div(B, 32);
       hipLaunchKernelGGL(k_comp_blocks, dim3(nt32, nt32, (unsigned)ceil_div(b, B)), dim3(256), 0, s,
-                         Lfac, ldL, b, B, w.Kc);
+                         Lfac, ldL, Ldiag, b, B, w.Kc);
       THANOS_LAUNCH_CHECK();
     }
   }

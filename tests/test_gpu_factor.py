@@ -93,3 +93,27 @@ def test_powers_of_two_scale_exactly(b, lo, hi):
     assert i1 == i2 == 0
     np.testing.assert_array_equal(xn2, np.diag(H32) * d * d)
     np.testing.assert_array_equal(U2 * d[None, :], U1)
+
+
+@pytest.mark.parametrize("b", [700, 3200])
+def test_split_products_ranges(b):
+    """The products that split their operands into two 16-bit values: merges of the inverse (700) and
+    wide updates too (3200), on channels whose scales span 2^+-20 and of which every fourth is nearly
+    the copy of its neighbour, so that the inverse of the scaled factor grows to about 2^6.  Powers of
+    two still scale exactly, and the error stays that of an fp32 factorisation: the condition number
+    of the scaled matrix is about b + 2^13 (one unit in 2^12 of a channel is its own), times 2^-24
+    and 8 for the walk of the sums."""
+    from tests.gpu_util import gpu_factor
+    g = np.random.default_rng(b)
+    X = g.standard_normal((2 * b, b))
+    k = b // 4
+    X[:, 1:4 * k:4] = X[:, 0:4 * k:4] + 2.0 ** -6 * g.standard_normal((2 * b, k))
+    H32 = (X.T @ X).astype(np.float32)
+    d = np.ldexp(np.float32(1.0), g.integers(-20, 21, size=b))
+    U1, _, i1 = gpu_factor(H32, 0.0)
+    U2, _, i2 = gpu_factor((H32 * d[:, None] * d[None, :]).astype(np.float32), 0.0)
+    assert i1 == i2 == 0
+    np.testing.assert_array_equal(U2 * d[None, :], U1)
+    Uref = orc.inverse_factor(H32.astype(np.float64))
+    assert np.abs(Uref).max() * np.sqrt(2 * b) > 2.0 ** 5
+    assert np.linalg.norm(U1 - Uref) <= 8 * (b + 2.0 ** 13) * 2.0 ** -24 * np.linalg.norm(Uref)
