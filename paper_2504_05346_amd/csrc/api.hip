@@ -14,7 +14,8 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
                     const float* H, const float* U, const float* xnorm2,
                     const thanos_prune_opts* o, long long r_total, long long n_out, float* W,
                     void* W_cast, uint8_t* mask, void* ws, int32_t* info, bool single_stream,
-                    PhaseTimer* pt, const float* Lfac, int64_t ldL, const float* Ldiag, bool prepared,
+                    PhaseTimer* pt, const float* Lfac, int64_t ldL, const float* Ldiag, const float* umax,
+                    bool prepared,
                     bool clear_info);
 thanos_status sweep_prepare(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c, int64_t b,
                             const float* H, const thanos_prune_opts* o, long long n_out, float* W,
@@ -352,6 +353,7 @@ static thanos_status prune_with_workspace(const void* W_in, thanos_dtype wdt, in
   const float* xn2 = opts->xnorm2_in;
   const float* Lfac = nullptr;  // lower factor of the index-reversed damped Hessian (this call's) ...
   const float* Ldiag = nullptr;  // ... and its scaling
+  const float* umax = nullptr;   // largest magnitudes of the columns of this call's U
   int64_t ldL = 0;
   const long long r_total =
       (opts->mode == THANOS_UNSTRUCTURED) ? num_to_remove(opts->sparsity, c, b) : 0;
@@ -389,10 +391,11 @@ static thanos_status prune_with_workspace(const void* W_in, thanos_dtype wdt, in
     xn2 = xw;
     Lfac = factor_L(p, b, &ldL);
     Ldiag = factor_scale(p, b);
+    umax = factor_umax(p, b);
   }
   phase_mark(pt, THANOS_PHASE_PREP);
   thanos_status st = sweep(s, W_in, wdt, c, b, H, U, xn2, opts, r_total, n_out, W_out, W_out_cast,
-                           mask_out, sweep_ws, info_dev, single_stream, pt, Lfac, ldL, Ldiag, prepared,
+                           mask_out, sweep_ws, info_dev, single_stream, pt, Lfac, ldL, Ldiag, umax, prepared,
                            opts->factor_in != nullptr);
   if (pt) {
     const thanos_status tc = pt->collect(opts->phase_ms_out);

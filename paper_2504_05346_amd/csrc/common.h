@@ -296,6 +296,8 @@ thanos_status factor_begin(hipStream_t s, const float* H, int64_t b, float dampi
                            void* ws, int32_t* info);
 const float* factor_L(const void* ws, int64_t b, int64_t* ld);
 const float* factor_scale(const void* ws, int64_t b);
+// largest magnitude of each column of U
+const float* factor_umax(const void* ws, int64_t b);
 
 // skip[i] = 1 for the n_out rows of W (c x b fp32) with the largest loss W_i H W_i^T (sweep.hip).
 thanos_status row_outliers(hipStream_t s, const float* W, const float* H, int64_t c, int64_t b,

@@ -418,7 +418,7 @@ __global__ __launch_bounds__(kXThreads, 4) void k_trinv_T(TrinvArgs a) {
   TileAcc acc;
   acc_zero(acc);
   const float sa = h2_scale(kBoundL), sb = h2_scale(a.bound_inv[gj]);
-  gemm_tile_h2<false, true>(acc, sm, A, a.bp, NB, sa, nullptr, B, a.bp, NB, sb, tj * NB, a.S * NB, true, true);
+  gemm_tile_h2<false, true, 1>(acc, sm, A, a.bp, NB, sa, nullptr, B, a.bp, NB, sb, nullptr, tj * NB, a.S * NB, true, true);
   write_tile_bound(acc, sm, a.T + ((int64_t)gi * NB) * a.bp + (int64_t)gj * NB, a.bp,
                    (1.f / sa) * (1.f / sb), a.bound_T + gj);
 }
@@ -437,19 +437,39 @@ __global__ __launch_bounds__(kXThreads, 4) void k_trinv_X(TrinvArgs a) {
   for (int e = threadIdx.x & 63; e <= ti; e += 64) ba = max(ba, __float_as_uint(a.bound_inv[base + a.S + e]));
   for (int off = 32; off > 0; off >>= 1) ba = max(ba, (uint32_t)__shfl_xor((int)ba, off, 64));
   const float sa = h2_scale(__uint_as_float(ba)), sb = h2_scale(a.bound_T[gj]);
-  gemm_tile_h2<false, true>(acc, sm, A, a.bp, NB, sa, nullptr, B, a.bp, NB, sb, 0, (ti + 1) * NB, true, true);
+  gemm_tile_h2<false, true, 1>(acc, sm, A, a.bp, NB, sa, nullptr, B, a.bp, NB, sb, nullptr, 0, (ti + 1) * NB, true, true);
   write_tile_bound(acc, sm, a.Linv + ((int64_t)gi * NB) * a.bp + (int64_t)gj * NB, a.bp,
                    -(1.f / sa) * (1.f / sb), a.bound_inv + gj);
 }
 
-// U[i][j] = Linv[b-1-i][b-1-j] d[j] for j >= i, else 0.
+// U[i][j] = Linv[b-1-i][b-1-j] d[j] for j >= i, else 0, and the largest magnitude of each column.  A thread
+// takes `rows` rows of a column, kOutRows of them in flight; columns whose maximum is already as large (a
+// stale value is a smaller one) are left alone.
+constexpr int kOutRows = 8;
 __global__ __launch_bounds__(256) void k_reverse_out(const float* __restrict__ Linv, int64_t bp,
                                                      const float* __restrict__ d, float* __restrict__ U,
-                                                     int64_t b) {
-  const int64_t i = blockIdx.y;
+                                                     int64_t b, int rows, float* __restrict__ umax) {
+  const int64_t i0 = (int64_t)blockIdx.y * rows, i1 = min(b, i0 + rows);
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (j >= b) return;
-  U[i * b + j] = (j >= i) ? Linv[(b - 1 - i) * bp + (b - 1 - j)] * d[j] : 0.f;
+  if (j < i0) {
+    for (int64_t i = i0; i < i1; ++i) U[i * b + j] = 0.f;
+    return;
+  }
+  const float dj = d[j];
+  uint32_t top = 0;
+  for (int64_t r = i0; r < i1; r += kOutRows) {
+    float v[kOutRows];
+#pragma unroll
+    for (int e = 0; e < kOutRows; ++e) v[e] = Linv[(b - 1 - min(r + e, j)) * bp + (b - 1 - j)];
+#pragma unroll
+    for (int e = 0; e < kOutRows; ++e) {
+      const float u = r + e <= j ? v[e] * dj : 0.f;
+      if (r + e < i1) U[(r + e) * b + j] = u;
+      top = max(top, __float_as_uint(fabsf(u)));
+    }
+  }
+  if (__float_as_uint(umax[j]) < top) atomicMax(reinterpret_cast<unsigned int*>(umax) + j, top);
 }
 
 static inline int64_t padded(int64_t b) { return ceil_div(b, NB) * NB; }
@@ -460,8 +480,9 @@ const float* factor_L(const void* ws, int64_t b, int64_t* ld) {
 }
 
 // The scales and the bounds live in the first 128 rows of the inverse's temporary, which no merge writes
-// (its tile rows belong to second halves): bp scales, nb bounds of L^{-1}, nb bounds of Tbuf per level.
-// 1 + 9 levels of at most 512 blocks beside 65536 scales: 128 rows of any width hold them.
+// (its tile rows belong to second halves): bp scales, nb bounds of L^{-1}, nb bounds of Tbuf per level,
+// the largest magnitudes of U's bp columns: at most 10 values per block of 128 columns beside twice 128, and
+// there are 128 x 128.
 static inline float* scales(const void* ws, int64_t bp) {
   return reinterpret_cast<float*>(const_cast<char*>(reinterpret_cast<const char*>(ws)) + 256) + 2 * bp * bp;
 }
@@ -470,7 +491,12 @@ static inline int merge_levels(int nb) {
   for (int S = 1; S < nb; S *= 2) ++n;
   return n;
 }
+static inline int n_bounds(int nb) { return nb * (1 + merge_levels(nb)); }
 const float* factor_scale(const void* ws, int64_t b) { return scales(ws, padded(b)); }
+const float* factor_umax(const void* ws, int64_t b) {
+  const int64_t bp = padded(b);
+  return scales(ws, bp) + bp + n_bounds((int)(bp / NB));
+}
 
 size_t factor_workspace_bytes(int64_t b) {
   const int64_t bp = padded(b);
@@ -485,7 +511,7 @@ thanos_status factor_begin(hipStream_t s, const float* H, int64_t b, float dampi
   const int nb = (int)(bp / NB);
   float* d = scales(ws, bp);
   hipLaunchKernelGGL(k_diag_stats, dim3(1), dim3(1024), 0, s, H, b, damping, xnorm2, lam, d, d + bp,
-                     nb * (1 + merge_levels(nb)), info);
+                     n_bounds(nb) + (int)bp, info);
   THANOS_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_reverse_pad, dim3((unsigned)(bp / 32), (unsigned)(bp / 32)), dim3(256), 0,
                      s, H, b, lam, d, Ap, bp);
@@ -660,8 +686,10 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
   }
   if (pending_join >= 0) THANOS_CHECK(aux.join(pending_join));
 
-  hipLaunchKernelGGL(k_reverse_out, dim3((unsigned)ceil_div(b, 256), (unsigned)b), dim3(256), 0, s,
-                     Linv, bp, d, U, b);
+  // few columns: enough workgroups; many: few updates of the maxima
+  const int out_rows = b <= 1024 ? kOutRows : 8 * kOutRows;
+  hipLaunchKernelGGL(k_reverse_out, dim3((unsigned)ceil_div(b, 256), (unsigned)ceil_div(b, out_rows)),
+                     dim3(256), 0, s, Linv, bp, d, U, b, out_rows, scales(ws, bp) + bp + n_bounds(nb));
   THANOS_LAUNCH_CHECK();
   return THANOS_OK;
 }

@@ -1,6 +1,6 @@
 // fp32 matrix product on the 16-bit matrix cores: split bf16 for operands of any range
 // (gemm_tile_x3.h: sweep, row losses, structured update, fp32 Hessian accumulation), split fp16 where
-// the range is known (gemm_tile_h2.h: the factorisation).
+// the range is known (gemm_tile_h2.h: the factorisation; the sweep's update has a kernel of its own).
 #include <algorithm>
 
 #include "gemm_tile_h2.h"
@@ -41,7 +41,7 @@ __global__ __launch_bounds__(kXThreads, 4) void k_gemm_f32(GemmArgs g) {
   const int kend = g.b_tri == kTriUpper ? min(g.K, n0 + kTN) : g.K;
   if constexpr (H2) {
     const float sb = g.bound_b ? h2_scale(*g.bound_b) : g.sb;
-    gemm_tile_h2<AK, BK>(acc, sm, A, g.lda, m_ext, g.sa, nullptr, B, g.ldb, n_ext, sb, kbeg, kend, g.vec_a,
+    gemm_tile_h2<AK, BK, 1>(acc, sm, A, g.lda, m_ext, g.sa, nullptr, B, g.ldb, n_ext, sb, nullptr, kbeg, kend, g.vec_a,
                          g.vec_b);
     g.alpha *= (1.f / g.sa) * (1.f / sb);
   } else {

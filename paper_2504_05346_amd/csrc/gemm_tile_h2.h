@@ -12,12 +12,17 @@
 // range, takes six: what is dropped is made up for by half as many roundings of the running sum.
 // 2048 x 2048 products of normal operands against float64, three-way -> two-way: K = 128 1.63 -> 1.43e-7,
 // 512 3.4 -> 2.6e-7, 1024 4.9 -> 3.6e-7, 4096 10 -> 7.1e-7; equal signs, equal operands and rows whose
-// values span e^6 also get better.  Rates, read-modify-write of C included: 10752^2 at K = 512 160 -> 230
+// values span e^6 also get better.  Below K = 96 the three-way split is the more accurate one
+// (16: 3.4 against 8.5e-8, 64: 1.10 against 1.13e-7), so short reductions stay there.  Rates, read-modify-write of C included: 10752^2 at K = 512 160 -> 230
 // TFLOP/s, 8192^2 at K = 1024 184 -> 273, K = 4096 198 -> 303.
 //
 // Same division of labour as in gemm_tile_x3.h (four multiplying, four splitting wavefronts, two
 // workgroups per compute unit); four planes instead of six in LDS, 5 instead of 11 vector instructions
-// per pair of values.
+// per pair of values.  A slab is 40 KB, so two buffers and two workgroups fill the LDS exactly, and the
+// splitting can run one slab ahead of the multiplying with one barrier per slab (NBUF = 2): 10752^2 at
+// K = 512 221 -> 238 TFLOP/s, 16384^2 at K = 128 126 -> 139, 8192^2 at K = 4096 305 -> 312.  One buffer and
+// two barriers where a workgroup has to fit beside one that takes 84 KB (the factorisation next to the
+// row losses: 5120 columns 5.23 against 5.40 ms).
 #pragma once
 #include "gemm_tile_x3.h"
 
@@ -25,11 +30,14 @@ namespace thanos {
 
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
-// LDS view: operand {a, b} x plane {x1, x2}
-__device__ __forceinline__ char* h2_plane(char* smem, int operand, int plane) {
-  return smem + (operand * 2 + plane) * kXPlane;
+// LDS view of a buffer: operand {a, b} x plane {x1, x2}
+__device__ __forceinline__ char* h2_plane(char* buf, int operand, int plane) {
+  return buf + (operand * 2 + plane) * kXPlane;
 }
-static_assert(4 * (size_t)kXPlane <= kXSmemBytes, "the staged tile is the larger use of the LDS");
+constexpr int kH2Buf = 4 * kXPlane;                 // one slab
+constexpr size_t kH2SmemBytes = 2 * (size_t)kH2Buf;  // half of a compute unit's LDS (NBUF = 1: kXSmemBytes)
+static_assert(kH2SmemBytes >= kXSmemBytes && 2 * kH2SmemBytes <= 160 * 1024, "staged tile fits, two per unit");
+static_assert(kH2Buf <= kXSmemBytes, "one buffer fits where the tile is staged");
 
 // The power of two that brings values of magnitude up to `bound` into [2^14, 2^15); finite for every bound.
 __host__ __device__ inline float h2_scale(float bound) {
@@ -43,6 +51,21 @@ __host__ __device__ inline float h2_scale(float bound) {
   return s;
 }
 
+// The power of two that brings a column whose largest magnitude is m into [1/2, 1); within 2^+-100 for every
+// m (magnitudes of U are: they are 1 / sqrt of what fp32 holds), and 1 for a column of zeros.
+__host__ __device__ inline float col_scale(float m) {
+  uint32_t u;
+  __builtin_memcpy(&u, &m, 4);
+  const int e = (int)((u >> 23) & 255u), t = 253 - e;
+  const uint32_t v = (uint32_t)(e == 0 ? 127 : t < 27 ? 27 : t > 227 ? 227 : t) << 23;
+  float s;
+  __builtin_memcpy(&s, &v, 4);
+  return s;
+}
+
+// 1 / s for a power of two between 2^-126 and 2^126
+__device__ __forceinline__ float pow2_inv(float s) { return __uint_as_float((254u << 23) - __float_as_uint(s)); }
+
 __device__ __forceinline__ void split2_h2(float x0, float x1, float s0, float s1, uint32_t (&packed)[2]) {
   const f32x2 v = {x0 * s0, x1 * s1};
   const f16x2 h = __builtin_convertvector(v, f16x2);
@@ -52,12 +75,17 @@ __device__ __forceinline__ void split2_h2(float x0, float x1, float s0, float s1
   packed[1] = __builtin_bit_cast(uint32_t, l);
 }
 
-// Scale of an operand: one for all of it, or (rows) one per row m of the tile, which only an operand with
-// A[m * ld + k] can have.
+// Scale of an operand: one for all of it, or (rows) that times one per row m of the tile.
 struct ScaleH2 {
   float all;
-  float row[8];  // of the rows (u >> 3) + 16 q of this thread's pieces
+  float row[8];  // of the rows of this thread's pieces: (u >> 3) + 16 q, KMAJOR: 4 (u & 31) + 0 .. 3
 };
+template <bool KMAJOR>
+__device__ __forceinline__ void load_rows_h2(ScaleH2& sc, const float* __restrict__ rows, int ext, int u) {
+#pragma unroll
+  for (int q = 0; q < (KMAJOR ? 4 : 8); ++q)
+    sc.row[q] = sc.all * rows[min(KMAJOR ? 4 * (u & 31) + q : (u >> 3) + 16 * q, ext - 1)];
+}
 
 template <bool KMAJOR, bool MASKED, bool ROWS>
 __device__ __forceinline__ void slab_store_h2(char* smem, int operand, const SlabRegsX3& rin,
@@ -81,7 +109,8 @@ __device__ __forceinline__ void slab_store_h2(char* smem, int operand, const Sla
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         uint32_t pk[2];
-        split2_h2(c[2 * e], c[2 * e + 1], sc.all, sc.all, pk);
+        const float s = ROWS ? sc.row[mm] : sc.all;
+        split2_h2(c[2 * e], c[2 * e + 1], s, s, pk);
         o[0][e] = pk[0];
         o[1][e] = pk[1];
       }
@@ -104,8 +133,16 @@ __device__ __forceinline__ void slab_store_h2(char* smem, int operand, const Sla
   }
 }
 
-// The producers of gemm_tile_x3.h with the two-way split.
-template <bool KMAJOR, bool ROWS>
+// Between two slabs: with two buffers the barrier says that slab it is in LDS and that slab it - 1 has been
+// read; with one the second says that slab it has been read.
+template <int NBUF>
+__device__ __forceinline__ void h2_handover() {
+  __syncthreads();
+  if (NBUF == 1) __syncthreads();
+}
+
+// The producers of gemm_tile_x3.h with the two-way split; slab it goes to buffer it % NBUF.
+template <bool KMAJOR, bool ROWS, int NBUF>
 __device__ __forceinline__ void h2_produce4(char* smem, int operand, const float* __restrict__ P, int64_t ld,
                                             int ext, int kbeg, const ScaleH2& sc, int u) {
   SlabSrcX3 src;
@@ -113,23 +150,20 @@ __device__ __forceinline__ void h2_produce4(char* smem, int operand, const float
   SlabRegsX3 r0, r1;
   slab_load_x3<KMAJOR, true>(r0, src, 0, 4 * kXK, P);
   slab_load_x3<KMAJOR, true>(r1, src, 1, 3 * kXK, P);
+  char* const second = smem + (NBUF - 1) * kH2Buf;
   slab_store_h2<KMAJOR, false, ROWS>(smem, operand, r0, sc, u);
   slab_load_x3<KMAJOR, true>(r0, src, 2, 2 * kXK, P);
-  __syncthreads();
-  __syncthreads();
-  slab_store_h2<KMAJOR, false, ROWS>(smem, operand, r1, sc, u);
+  h2_handover<NBUF>();
+  slab_store_h2<KMAJOR, false, ROWS>(second, operand, r1, sc, u);
   slab_load_x3<KMAJOR, true>(r1, src, 3, kXK, P);
-  __syncthreads();
-  __syncthreads();
+  h2_handover<NBUF>();
   slab_store_h2<KMAJOR, false, ROWS>(smem, operand, r0, sc, u);
-  __syncthreads();
-  __syncthreads();
-  slab_store_h2<KMAJOR, false, ROWS>(smem, operand, r1, sc, u);
-  __syncthreads();
-  __syncthreads();
+  h2_handover<NBUF>();
+  slab_store_h2<KMAJOR, false, ROWS>(second, operand, r1, sc, u);
+  h2_handover<NBUF>();
 }
 
-template <bool KMAJOR, bool FAST, bool MASKED, bool ROWS>
+template <bool KMAJOR, bool FAST, bool MASKED, bool ROWS, int NBUF>
 __device__ __forceinline__ void h2_produce(char* smem, int operand, const float* __restrict__ P, int64_t ld,
                                            int ext, int kbeg, int kend, int nslab, const ScaleH2& sc,
                                            int u) {
@@ -139,33 +173,33 @@ __device__ __forceinline__ void h2_produce(char* smem, int operand, const float*
   SlabRegsX3 r;
   slab_load_x3<KMAJOR, FAST>(r, src, 0, klen, P);
   for (int it = 0; it < nslab; ++it) {
-    slab_store_h2<KMAJOR, MASKED, ROWS>(smem, operand, r, sc, u);
+    if (operand == 0 && u < 64) TL_MARK(8 + 4 * it);
+    slab_store_h2<KMAJOR, MASKED, ROWS>(smem + (NBUF == 2 ? (it & 1) * kH2Buf : 0), operand, r, sc, u);
     slab_load_x3<KMAJOR, FAST>(r, src, it + 1, klen - (it + 1) * kXK, P);
-    __syncthreads();  // slab it is in LDS
-    __syncthreads();  // consumers are done with it
+    if (operand == 0 && u < 64) TL_MARK(8 + 4 * it + 1);
+    h2_handover<NBUF>();
   }
 }
 
-template <bool KMAJOR, bool ROWS>
+template <bool KMAJOR, bool ROWS, int NBUF>
 __device__ __forceinline__ void h2_producer(char* smem, int operand, const float* __restrict__ P, int64_t ld,
                                             int ext, int kbeg, int kend, bool vec, const ScaleH2& sc, int u) {
   const int nslab = (kend - kbeg + kXK - 1) / kXK;
   const bool fast = vec && (KMAJOR ? ext % 4 == 0 : (kend - kbeg) % 4 == 0);
   const bool whole = ext == 128 && (kend - kbeg) % kXK == 0;
-  if (fast && whole && kend - kbeg == 4 * kXK) h2_produce4<KMAJOR, ROWS>(smem, operand, P, ld, ext, kbeg, sc, u);
-  else if (fast && whole) h2_produce<KMAJOR, true, false, ROWS>(smem, operand, P, ld, ext, kbeg, kend, nslab, sc, u);
-  else if (fast) h2_produce<KMAJOR, true, true, ROWS>(smem, operand, P, ld, ext, kbeg, kend, nslab, sc, u);
-  else h2_produce<KMAJOR, false, false, ROWS>(smem, operand, P, ld, ext, kbeg, kend, nslab, sc, u);
+  if (fast && whole && kend - kbeg == 4 * kXK) h2_produce4<KMAJOR, ROWS, NBUF>(smem, operand, P, ld, ext, kbeg, sc, u);
+  else if (fast && whole) h2_produce<KMAJOR, true, false, ROWS, NBUF>(smem, operand, P, ld, ext, kbeg, kend, nslab, sc, u);
+  else if (fast) h2_produce<KMAJOR, true, true, ROWS, NBUF>(smem, operand, P, ld, ext, kbeg, kend, nslab, sc, u);
+  else h2_produce<KMAJOR, false, false, ROWS, NBUF>(smem, operand, P, ld, ext, kbeg, kend, nslab, sc, u);
 }
 
-// acc += (sa A)[0:128, kbeg:kend] (sb B)[kbeg:kend, 0:128]; otherwise as gemm_tile_x3().  arows: 128 scales
-// of the rows of A instead of sa (LDS or global), read for rows < m_ext only.
-template <bool A_KMAJOR, bool B_KMAJOR, bool A_ROWS = false>
+// acc += (sa A)[0:128, kbeg:kend] (sb B)[kbeg:kend, 0:128]; otherwise as gemm_tile_x3().  ROWS: further
+// scales of the m_ext rows of A (the n_ext columns of B).
+template <bool A_KMAJOR, bool B_KMAJOR, int NBUF, bool A_ROWS = false, bool B_ROWS = false>
 __device__ __forceinline__ void gemm_tile_h2(TileAcc& acc, char* smem, const float* __restrict__ A,
                                              int64_t lda, int m_ext, float sa, const float* arows,
                                              const float* __restrict__ B, int64_t ldb, int n_ext, float sb,
-                                             int kbeg, int kend, bool vec_a, bool vec_b) {
-  static_assert(!(A_KMAJOR && A_ROWS), "row scales need A[m * ld + k]");
+                                             const float* brows, int kbeg, int kend, bool vec_a, bool vec_b) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -174,15 +208,13 @@ __device__ __forceinline__ void gemm_tile_h2(TileAcc& acc, char* smem, const flo
   ScaleH2 sc;
   const int u = tid & 127;
   sc.all = wave >= 6 ? sb : sa;
-  if (A_ROWS && wave >= 4 && wave < 6) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) sc.row[q] = arows[min((u >> 3) + 16 * q, m_ext - 1)];
-  }
+  if (A_ROWS && wave >= 4 && wave < 6) load_rows_h2<A_KMAJOR>(sc, arows, m_ext, u);
+  if (B_ROWS && wave >= 6) load_rows_h2<B_KMAJOR>(sc, brows, n_ext, u);
   __syncthreads();  // previous users of the LDS buffers are done
   if (wave >= 6) {
-    h2_producer<B_KMAJOR, false>(smem, 1, B, ldb, n_ext, kbeg, kend, vec_b, sc, u);
+    h2_producer<B_KMAJOR, B_ROWS, NBUF>(smem, 1, B, ldb, n_ext, kbeg, kend, vec_b, sc, u);
   } else if (wave >= 4) {
-    h2_producer<A_KMAJOR, A_ROWS>(smem, 0, A, lda, m_ext, kbeg, kend, vec_a, sc, u);
+    h2_producer<A_KMAJOR, A_ROWS, NBUF>(smem, 0, A, lda, m_ext, kbeg, kend, vec_a, sc, u);
   } else {
     const int wm = wave >> 1, wn = wave & 1;
     const int lo = lane & 31, hi = lane >> 5;
@@ -190,6 +222,8 @@ __device__ __forceinline__ void gemm_tile_h2(TileAcc& acc, char* smem, const flo
     const int b_off = (wn * 64 + lo) * kXRow + 16 * hi;
     for (int it = 0; it < nslab; ++it) {
       __syncthreads();  // slab it is in LDS
+      if (wave == 0) TL_MARK(8 + 4 * it + 2);
+      char* const buf = smem + (NBUF == 2 ? (it & 1) * kH2Buf : 0);
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
         f16x8 af[2][2], bf[2][2];
@@ -197,8 +231,8 @@ __device__ __forceinline__ void gemm_tile_h2(TileAcc& acc, char* smem, const flo
         for (int f = 0; f < 2; ++f)
 #pragma unroll
           for (int p = 0; p < 2; ++p) {
-            af[f][p] = *reinterpret_cast<const f16x8*>(h2_plane(smem, 0, p) + a_off + f * 32 * kXRow + 32 * ks);
-            bf[f][p] = *reinterpret_cast<const f16x8*>(h2_plane(smem, 1, p) + b_off + f * 32 * kXRow + 32 * ks);
+            af[f][p] = *reinterpret_cast<const f16x8*>(h2_plane(buf, 0, p) + a_off + f * 32 * kXRow + 32 * ks);
+            bf[f][p] = *reinterpret_cast<const f16x8*>(h2_plane(buf, 1, p) + b_off + f * 32 * kXRow + 32 * ks);
           }
         // small partial products first; consecutive MFMAs go to different accumulators
         constexpr int pa[3] = {1, 0, 0};
@@ -212,9 +246,11 @@ __device__ __forceinline__ void gemm_tile_h2(TileAcc& acc, char* smem, const flo
               acc.v[f][g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[f][pa[t]], bf[g][pb[t]], acc.v[f][g],
                                                                    0, 0, 0);
       }
-      __syncthreads();  // done with it
+      if (wave == 0) TL_MARK(8 + 4 * it + 3);
+      if (NBUF == 1) __syncthreads();
     }
   }
+  if (NBUF == 2) __syncthreads();  // the LDS is free
 }
 
 }  // namespace thanos

@@ -17,11 +17,13 @@ constexpr int64_t lam_buffer_floats(int64_t c, int64_t B) { return c * B * kSupe
 // sbi alternate between the first two; behind them lie, where a super-block is one block (room for
 // 16), the operands of the complement products: every row of z is read by all column tiles of the
 // product whose results are multipliers, so the two must never share memory.
+// (rsc, one value per row, likewise: with super-blocks its two arrays are those of the selection, which
+// does not run then.)
 struct LamLayout {
-  int64_t lam, z, wk;
+  int64_t lam, z, wk, rsc;
 };
 constexpr LamLayout lam_layout(int64_t c, int64_t ldl, int64_t sbi) {
-  return {(sbi & 1) * c * ldl, 2 * c * ldl, 3 * c * ldl};
+  return {(sbi & 1) * c * ldl, 2 * c * ldl, 3 * c * ldl, 4 * c * ldl};
 }
 
 }  // namespace thanos

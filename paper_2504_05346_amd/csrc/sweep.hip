@@ -8,11 +8,17 @@
 //   Lam[i, q] = lambda, 0 elsewhere                  scattered multipliers
 //   W[:, j1:b] -= Lam * P_k                          == -u R_hat^{-1} R for every row at once
 // All P_k are produced by one batched launch before the sweep.
+//
+// Scaled coordinates.  With sc[j] the power of two that brings the largest magnitude of column j of U into
+// [1/2, 1), the sweep works with P' = S P S and u' = u S, which gives lambda' = lambda S^{-1}: the same
+// values times powers of two, so nothing changes in them, but |P'_qj| <= B for every input, and with the
+// largest |lambda'| of each row at hand (rsc) the products can split their operands into two fp16 values
+// (gemm_tile_h2.h).  W stays as it is: the update takes the scales out again.
 #include <algorithm>
 
 #include <cmath>
 
-#include "gemm_tile_x3.h"
+#include "gemm_tile_h2.h"
 #include "lam_layout.h"
 #include "tile32.h"
 
@@ -26,15 +32,17 @@ namespace thanos {
   } while (0)
 
 // ------------------------------------------------------------------------------------------
-// P[(j1+m)*b + col] = sum_k U[j1+k][j1+m] * U[j1+k][col], col in [j1, b), for every block.
+// P[(j1+m)*b + col] = sc[j1+m] sc[col] sum_k U[j1+k][j1+m] * U[j1+k][col], col in [j1, b), for every block.
 struct BlockRowsArgs {
   const float* U;
   float* P;
+  const float* sc;
   int64_t b;
   int B;
   int vec;
 };
 
+constexpr size_t kBlockRowsSmem = kXSmemBytes + kTM * sizeof(float);
 __global__ __launch_bounds__(kXThreads, 4) void k_block_rows(BlockRowsArgs a) {
   extern __shared__ __attribute__((aligned(16))) char sm[];
   const int64_t j1 = (int64_t)blockIdx.y * a.B;
@@ -48,21 +56,50 @@ __global__ __launch_bounds__(kXThreads, 4) void k_block_rows(BlockRowsArgs a) {
   const float* Bm = a.U + j1 * a.b + col0;       // (k,n) at B[k*b + n]
   TileAcc acc;
   acc_zero(acc);
-  gemm_tile_x3<true, true>(acc, sm, A, a.b, m_ext, Bm, a.b, n_ext, 0, bw, a.vec, a.vec);
-  float* Pg = a.P + (j1 + mrow0) * a.b + col0;
-  if (m_ext == kTM && n_ext == kTN && a.vec) {  // P is 256-byte aligned, b and col0 multiples of 4
-    x3_write_tile(acc, sm, Pg, a.b, 1.f);
-    return;
-  }
-  const float* T = x3_stage_tile(acc, sm);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const float s0 = a.sc[min(col0 + 2 * lane, a.b - 1)], s1 = a.sc[min(col0 + 2 * lane + 1, a.b - 1)];
+  const float mine = a.sc[min(j1 + mrow0 + ((int)threadIdx.x & (kTM - 1)), a.b - 1)];
+  gemm_tile_x3<true, true>(acc, sm, A, a.b, m_ext, Bm, a.b, n_ext, 0, bw, a.vec, a.vec);
+  float* const sr = reinterpret_cast<float*>(sm + kXSmemBytes);  // scales of the rows, behind the tile
+  if (threadIdx.x < kTM) sr[threadIdx.x] = mine;  // a barrier follows in the staging
+  const float* T = x3_stage_tile(acc, sm);
+  float* Pg = a.P + (j1 + mrow0) * a.b + col0;
+  const bool whole = m_ext == kTM && n_ext == kTN && a.vec;  // P is 256-byte aligned, b, col0 multiples of 4
+#pragma unroll
   for (int i = 0; i < 16; ++i) {
     const int row = wave + 8 * i;
-    if (row >= m_ext) break;
-#pragma unroll
-    for (int e = 0; e < 2; ++e)
-      if (2 * lane + e < n_ext) Pg[(int64_t)row * a.b + 2 * lane + e] = T[row * kXCLd + 2 * lane + e];
+    const float2 t = *reinterpret_cast<const float2*>(T + row * kXCLd + 2 * lane);
+    const float2 o = make_float2(t.x * sr[row] * s0, t.y * sr[row] * s1);
+    if (whole) {
+      *reinterpret_cast<float2*>(Pg + (int64_t)row * a.b + 2 * lane) = o;
+    } else if (row < m_ext) {
+      if (2 * lane < n_ext) Pg[(int64_t)row * a.b + 2 * lane] = o.x;
+      if (2 * lane + 1 < n_ext) Pg[(int64_t)row * a.b + 2 * lane + 1] = o.y;
+    }
   }
+}
+
+// sc from a given factor (own factors bring the largest magnitudes of their columns along): 16 threads per
+// column, eight loads in flight.
+__global__ __launch_bounds__(1024) void k_col_scales(const float* __restrict__ U, int64_t b, int B,
+                                                     float* __restrict__ sc) {
+  __shared__ float part[16][64];
+  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+  const int64_t j = (int64_t)blockIdx.x * 64 + tx, jc = min(j, b - 1);
+  const int64_t rows = min(b, ((int64_t)blockIdx.x * 64 + 63) / B * B + B);  // all that k_block_rows reads
+  float top = 0.f;
+  for (int64_t i = ty; i < rows; i += 8 * 16) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float v = fabsf(U[min(i + 16 * e, rows - 1) * b + jc]);
+      top = v > top ? v : top;
+    }
+  }
+  part[ty][tx] = top;
+  __syncthreads();
+  if (ty != 0 || j >= b) return;
+  for (int e = 1; e < 16; ++e) top = fmaxf(top, part[e][tx]);
+  sc[j] = col_scale(top);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -72,10 +109,11 @@ __global__ __launch_bounds__(kXThreads, 4) void k_block_rows(BlockRowsArgs a) {
 // (V[x][y] = L[b-1-x][b-1-y], L = its workspace's lower factor of the index-reversed matrix), and
 // the diagonal block of the inverse of a triangular matrix is the inverse of its diagonal block:
 // no inversion is computed.  Kc[blk][a][j] = sum_{m >= max(a, j)} V[j1+a][j1+m] V[j1+j][j1+m],
-// row stride B.  One workgroup per 32 x 32 tile of a block.  L is the factor of the scaled matrix: row
-// b-1-x of it is d[x] times that of the matrix itself.
+// row stride B.  One workgroup per 32 x 32 tile of a block.  L is the factor of a scaled matrix: row
+// b-1-x of it is d[x] times that of the matrix itself; Kc is in the scaled coordinates of the sweep.
 __global__ __launch_bounds__(256) void k_comp_blocks(const float* __restrict__ L, int64_t ldL,
-                                                     const float* __restrict__ d, int64_t b, int B,
+                                                     const float* __restrict__ d,
+                                                     const float* __restrict__ sc, int64_t b, int B,
                                                      float* __restrict__ Kc) {
   __shared__ float Va[32][33], Vj[32][33];
   const int64_t j1 = (int64_t)blockIdx.z * B;
@@ -108,7 +146,8 @@ __global__ __launch_bounds__(256) void k_comp_blocks(const float* __restrict__ L
 #pragma unroll
   for (int e = 0; e < 4; ++e)
     if (a0 + ty + 8 * e < bw && c0 + tx < bw)
-      out[(int64_t)(a0 + ty + 8 * e) * B + c0 + tx] = acc[e] / d[j1 + a0 + ty + 8 * e] / d[j1 + c0 + tx];
+      out[(int64_t)(a0 + ty + 8 * e) * B + c0 + tx] =
+          acc[e] / (d[j1 + a0 + ty + 8 * e] * sc[j1 + a0 + ty + 8 * e]) / (d[j1 + c0 + tx] * sc[j1 + c0 + tx]);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -637,6 +676,9 @@ struct SolveArgs {
   const float* W;        // c x b, current weights
   const float* P;        // b x b, block rows of the residual inverses
   const float* sx;       // sqrt(xnorm2)
+  const float* sc;       // scales of the columns
+  float* rsc;            // per row: scale of its multipliers for the update (the smallest of a super-block)
+  int rsc_first;         // first block of a super-block
   const uint8_t* mask_in;
   uint8_t* mask_out;     // c x b
   float* Lam;            // c x ldl
@@ -659,6 +701,37 @@ struct SolveArgs {
   const float* WK;       // SEL_PICKED: c x ldz, w~ K
   int ldz;
 };
+
+// rsc of row i, for m = the largest |lambda'| that the calling lane has written: by the one wavefront that
+// writes the row, or (rsc_clear before a barrier, then rsc_lower by every wavefront) by several.
+__device__ __forceinline__ float wave_max(float m) {  // m >= 0; in registers: the row waits for it
+  uint32_t u = __float_as_uint(m);
+#define ROW_STEP(ctrl) u = max(u, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u, ctrl, 0xf, 0xf, false))
+  ROW_STEP(0x121);  // rotations within 16 lanes, by 1, 2, 4, 8
+  ROW_STEP(0x122);
+  ROW_STEP(0x124);
+  ROW_STEP(0x128);
+#undef ROW_STEP
+  auto h = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  u = max((uint32_t)h[0], (uint32_t)h[1]);
+  h = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return __uint_as_float(max((uint32_t)h[0], (uint32_t)h[1]));
+}
+__device__ __forceinline__ float rsc_old(const SolveArgs& a, int64_t i) {
+  return a.rsc_first ? h2_scale(0.f) : a.rsc[i];
+}
+__device__ __forceinline__ void rsc_set(const SolveArgs& a, int64_t i, float m, float old) {
+  const float s = h2_scale(wave_max(m));
+  if ((threadIdx.x & 63) == 0) a.rsc[i] = fminf(old, s);
+}
+__device__ __forceinline__ void rsc_clear(const SolveArgs& a, int64_t i) {
+  if (a.rsc_first) __hip_atomic_store(a.rsc + i, h2_scale(0.f), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void rsc_lower(const SolveArgs& a, int64_t i, float m) {
+  const float s = h2_scale(wave_max(m));
+  if ((threadIdx.x & 63) == 0)  // positive floats compare as their bits
+    atomicMin(reinterpret_cast<unsigned int*>(a.rsc + i), __float_as_uint(s));
+}
 
 // ------------------------------------------------------------------------------------------
 // Mask + per-row solve for systems of up to SMAX = 128 or 256 unknowns: one workgroup of SMAX
@@ -688,7 +761,7 @@ __global__ __launch_bounds__(SMAX, (SMAX == 128 ? 3 : 1)) void k_solve_wide(Solv
   if (SEL == SEL_THRESHOLD && a.s_min > 0 && a.st->deferred == 0) return;
 
   const float w = (tid < a.bw) ? wrow_g[tid] : 0.f;
-  wrow[tid] = w;
+  wrow[tid] = (tid < a.bw) ? w * a.sc[a.j1 + tid] : 0.f;
   for (int e = tid; e < 2 * 4 * (SMAX + 32); e += SMAX) (&col[0][0][0])[e] = 0.f;
   bool sel = false;
   if (SEL == SEL_GIVEN) {
@@ -740,6 +813,7 @@ __global__ __launch_bounds__(SMAX, (SMAX == 128 ? 3 : 1)) void k_solve_wide(Solv
     if (tid == 0) a.row_cnt[i] = s;  // summed at the start of the next block
   }
   float* lam_g = a.Lam + i * a.ldl;
+  if (tid == 0) rsc_clear(a, i);
   if (s == 0) {
     if (tid < a.bw) lam_g[tid] = 0.f;
     return;
@@ -848,6 +922,7 @@ __global__ __launch_bounds__(SMAX, (SMAX == 128 ? 3 : 1)) void k_solve_wide(Solv
   if (rho < s) wrow[qr] = u * dinv;
   __syncthreads();
   if (tid < a.bw) lam_g[tid] = wrow[tid];
+  rsc_lower(a, i, fabsf(wrow[tid]));
 }
 
 // Lane `lane` (a constant) of v <- the bits s, uniform.  (The wait is for a v_readlane that has just
@@ -897,15 +972,17 @@ __global__ __launch_bounds__(64 * WPB, NTR == 2 ? 4 : 3) void k_solve_mfma(Solve
   const int64_t i = (int64_t)blockIdx.x * WPB + wave;
   if (i >= a.c) return;
   const float* wrow_g = a.W + i * a.b + a.j1;
+  const float old_rsc = rsc_old(a, i);
 
   // ---- selection of the block mask row M_i ----
   bool sel[CPL];
-  float wv[CPL];
+  float wv[CPL], us[CPL];  // weights, and in scaled coordinates
 #pragma unroll
   for (int r = 0; r < CPL; ++r) {
     const int col = lane + 64 * r;
     wv[r] = (col < a.bw) ? wrow_g[col] : 0.f;
-    wrow[col] = wv[r];
+    us[r] = (col < a.bw) ? wv[r] * a.sc[a.j1 + col] : 0.f;
+    wrow[col] = us[r];
     sel[r] = false;
   }
   if (SEL == SEL_GIVEN) {
@@ -1023,6 +1100,7 @@ __global__ __launch_bounds__(64 * WPB, NTR == 2 ? 4 : 3) void k_solve_mfma(Solve
       const int col = lane + 64 * r;
       if (col < a.bw) lam_g[col] = 0.f;
     }
+    rsc_set(a, i, 0.f, old_rsc);
     return;
   }
   // y[r] = sum_a x[a] K[a][lane + 64 r] for this wavefront (x in LDS, zeros skipped)
@@ -1043,7 +1121,7 @@ __global__ __launch_bounds__(64 * WPB, NTR == 2 ? 4 : 3) void k_solve_mfma(Solve
   if (comp) {
     // right-hand side (w~ K)_k: w~ = the row's weights on the removed columns, zero elsewhere
 #pragma unroll
-    for (int r = 0; r < CPL; ++r) key[lane + 64 * r] = sel[r] ? wv[r] : 0.f;
+    for (int r = 0; r < CPL; ++r) key[lane + 64 * r] = sel[r] ? us[r] : 0.f;
     WAVE_SYNC();
     float t[CPL];
     matvec_k(key, t);
@@ -1053,6 +1131,7 @@ __global__ __launch_bounds__(64 * WPB, NTR == 2 ? 4 : 3) void k_solve_mfma(Solve
         const int col = lane + 64 * r;
         if (col < a.bw) lam_g[col] = t[r];
       }
+      rsc_set(a, i, fmaxf(fabsf(t[0]), fabsf(t[1])), old_rsc);  // zero past the block
       return;
     }
 #pragma unroll
@@ -1267,22 +1346,30 @@ __global__ __launch_bounds__(64 * WPB, NTR == 2 ? 4 : 3) void k_solve_mfma(Solve
     // wrow holds y on the kept columns: lambda = ((w~ - y~) K)_q
 #pragma unroll
     for (int r = 0; r < CPL; ++r)
-      key[lane + 64 * r] = (sel[r] ? wv[r] : 0.f) - wrow[lane + 64 * r];
+      key[lane + 64 * r] = (sel[r] ? us[r] : 0.f) - wrow[lane + 64 * r];
     WAVE_SYNC();
     float l[CPL];
     matvec_k(key, l);
+    float top = 0.f;
 #pragma unroll
     for (int r = 0; r < CPL; ++r) {
       const int col = lane + 64 * r;
-      if (col < a.bw) lam_g[col] = sel[r] ? l[r] : 0.f;
+      if (!sel[r]) l[r] = 0.f;
+      if (col < a.bw) lam_g[col] = l[r];
+      top = fmaxf(top, fabsf(l[r]));
     }
+    rsc_set(a, i, top, old_rsc);
     return;
   }
+  float top = 0.f;
 #pragma unroll
   for (int r = 0; r < CPL; ++r) {
     const int col = lane + 64 * r;
-    if (col < a.bw) lam_g[col] = wrow[col];
+    const float l = wrow[col];  // zero past the block
+    if (col < a.bw) lam_g[col] = l;
+    top = fmaxf(top, fabsf(l));
   }
+  rsc_set(a, i, top, old_rsc);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1622,12 +1709,13 @@ __global__ __launch_bounds__(64 * NW, (BIG ? 2 : (NW == 8 ? 4 : 5))) void k_solv
 
   // ---- selection of the block mask row M_i: column col = tid + NT * ch ----
   bool sel[CH];
-  float wv[CH];
+  float wv[CH], us[CH];  // weights, and in scaled coordinates
 #pragma unroll
   for (int ch = 0; ch < CH; ++ch) {
     const int col = tid + NT * ch;
     wv[ch] = (col < a.bw) ? wrow_g[col] : 0.f;
-    wrow[col] = wv[ch];
+    us[ch] = (col < a.bw) ? wv[ch] * a.sc[a.j1 + col] : 0.f;
+    wrow[col] = us[ch];
     sel[ch] = false;
   }
   if (SEL == SEL_GIVEN) {
@@ -1749,6 +1837,7 @@ __global__ __launch_bounds__(64 * NW, (BIG ? 2 : (NW == 8 ? 4 : 5))) void k_solv
     if (ins[ch] && fits) q[before + __popcll(bal[ch] & ((1ull << lane) - 1ull))] = col;
   }
   float* lam_g = a.Lam + i * a.ldl;
+  if (SEL != SEL_PICKED && tid == 0) rsc_clear(a, i);  // k_pick has done it
   if (s == 0 || !fits) {  // !fits cannot happen for a launch chosen by the host
 #pragma unroll
     for (int ch = 0; ch < CH; ++ch) {
@@ -1771,7 +1860,7 @@ __global__ __launch_bounds__(64 * NW, (BIG ? 2 : (NW == 8 ? 4 : 5))) void k_solv
     // right-hand side (w~ K)_k: x = w~ in `key`, the product lands in `wrow` (the row's weights
     // stay in registers)
 #pragma unroll
-    for (int ch = 0; ch < CH; ++ch) key[tid + NT * ch] = sel[ch] ? wv[ch] : 0.f;
+    for (int ch = 0; ch < CH; ++ch) key[tid + NT * ch] = sel[ch] ? us[ch] : 0.f;
     __syncthreads();
     tl_matvec<NW, BIG>(key, a.bw, a.Kc, a.ldk, wrow, part);
     for (int t = tid; t < 32 * nt; t += NT) u[t] = (t < ns) ? wrow[q[t]] : 0.f;
@@ -1930,27 +2019,35 @@ __global__ __launch_bounds__(64 * NW, (BIG ? 2 : (NW == 8 ? 4 : 5))) void k_solv
     __syncthreads();
     for (int t = tid; t < s; t += NT) wrow[q[t]] = lam[t];
     __syncthreads();
+    float top = 0.f;
 #pragma unroll
     for (int ch = 0; ch < CH; ++ch) {
       const int col = tid + NT * ch;
-      if (col < a.bw) lam_g[col] = wrow[col];
+      const float l = wrow[col];  // zero past the block
+      if (col < a.bw) lam_g[col] = l;
+      top = fmaxf(top, fabsf(l));
     }
+    rsc_lower(a, i, top);
   } else if (SEL == SEL_PICKED) {  // w~ - y~: -y on the kept columns, w~ is there
     for (int t = tid; t < ns; t += NT) a.Z[i * a.ldz + q[t]] = -lam[t];
   } else {
     // lambda = ((w~ - y~) K)_q: x = w on the removed columns, -y on the kept ones
     __syncthreads();
 #pragma unroll
-    for (int ch = 0; ch < CH; ++ch) key[tid + NT * ch] = sel[ch] ? wv[ch] : 0.f;
+    for (int ch = 0; ch < CH; ++ch) key[tid + NT * ch] = sel[ch] ? us[ch] : 0.f;
     __syncthreads();
     for (int t = tid; t < ns; t += NT) key[q[t]] = -lam[t];
     __syncthreads();
     tl_matvec<NW, BIG>(key, a.bw, a.Kc, a.ldk, wrow, part);
+    float top = 0.f;
 #pragma unroll
     for (int ch = 0; ch < CH; ++ch) {
       const int col = tid + NT * ch;
-      if (col < a.bw) lam_g[col] = sel[ch] ? wrow[col] : 0.f;
+      const float l = sel[ch] ? wrow[col] : 0.f;  // nothing is removed past the block
+      if (col < a.bw) lam_g[col] = l;
+      top = fmaxf(top, fabsf(l));
     }
+    rsc_lower(a, i, top);
   }
   if (!BIG) return;  // one row per workgroup
   }  // rows of this workgroup
@@ -1987,10 +2084,13 @@ __global__ __launch_bounds__(256) void k_pick(SolveArgs a) {
     s += __popcll(__ballot(sel));
     if (col < a.bw) {
       a.mask_out[i * a.b + a.j1 + col] = sel ? 1 : 0;
-      a.Z[i * a.ldz + col] = sel ? w : 0.f;
+      a.Z[i * a.ldz + col] = sel ? w * a.sc[a.j1 + col] : 0.f;
     }
   }
-  if (lane == 0) a.row_cnt[i] = s;
+  if (lane == 0) {
+    a.row_cnt[i] = s;
+    rsc_clear(a, i);
+  }
 }
 
 __global__ __launch_bounds__(kXThreads, 4) void k_lam_rows(SolveArgs a) {
@@ -2008,13 +2108,17 @@ __global__ __launch_bounds__(kXThreads, 4) void k_lam_rows(SolveArgs a) {
   for (int r = wave; r < m_ext; r += 8) {
     const int64_t i = m0 + r;
     if (2 * a.row_cnt[i] <= a.bw) continue;  // solved directly
+    float top = 0.f;
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
       const int col = lane + 64 * e;
-      if (col < n_ext)
-        a.Lam[i * a.ldl + n0 + col] =
-            a.mask_out[i * a.b + a.j1 + n0 + col] ? T[r * kXCLd + col] : 0.f;
+      if (col < n_ext) {
+        const float l = a.mask_out[i * a.b + a.j1 + n0 + col] ? T[r * kXCLd + col] : 0.f;
+        a.Lam[i * a.ldl + n0 + col] = l;
+        top = fmaxf(top, fabsf(l));
+      }
     }
+    rsc_lower(a, i, top);
   }
 }
 
@@ -2042,12 +2146,22 @@ struct UpdateArgs {
   uint2* cand;                // ... and the keys with their rows, kCandStage slots per workgroup
   SelState* st;
   const float* sx;
+  const float* sc;            // scales of the columns ...
+  const float* rsc;           // ... and of the rows' multipliers
+  float sp;                   // scale of P (a bound of its values is the block size)
   int gx, gy;                 // tile grid (set by launch_update)
 };
 
-constexpr size_t kUpdSmemBytes = kXSmemBytes + 2048 * sizeof(unsigned int) +
-                                 16 * sizeof(unsigned int) + kCandStage * sizeof(uint2);
+// two slabs of the operands; after the product the staged tile and, behind it, the window counts
+constexpr size_t kUpdSmemBytes = kH2SmemBytes;
+static_assert(kXSmemBytes + 2048 * sizeof(unsigned int) + 16 * sizeof(unsigned int) + kCandStage * sizeof(uint2) <=
+                  kUpdSmemBytes, "both fit");
 
+// H2: two-way split of the operands.  Not for short reductions: of K products it loses the last bits once,
+// the three-way split rounds its running sum twice as often.  Relative errors of normal products, two-way and
+// three-way: K = 16 8.5 and 3.4e-8, 64 1.13 and 1.10e-7, 96 1.28 and 1.38, 128 1.43 and 1.63, 1024 3.6 and 4.9.
+constexpr int kUpdShortK = 64;
+template <bool H2>
 __global__ __launch_bounds__(kXThreads, 4) void k_update(UpdateArgs a) {
   extern __shared__ __attribute__((aligned(16))) char sm[];
   if (threadIdx.x == 0) TL_MARK(0);
@@ -2077,23 +2191,31 @@ __global__ __launch_bounds__(kXThreads, 4) void k_update(UpdateArgs a) {
   const float* Bm = a.P + a.prow0 * a.b + n0;   // (k,n) at B[k*b + n]
   // does this tile feed the next selection?  (uniform per workgroup)
   const bool win = a.hist != nullptr && !a.st->none && a.st->pred_try && n0 + n_ext > a.zj2;
-  if (win) {
-    for (int e = threadIdx.x; e < 2048; e += kXThreads) hw[e] = 0u;  // barriers follow in the product
-    if (threadIdx.x == 0) nb_wave[8] = 0u;                            // staged keys
-  }
   TileAcc acc;
   acc_zero(acc);
-  gemm_tile_x3<false, true>(acc, sm, A, a.ldl, m_ext, Bm, a.b, n_ext, 0, a.K, a.vec_a, a.vec_b);
+  const float* rsc = a.rsc + m0;
+  if constexpr (H2)
+    gemm_tile_h2<false, true, 2, true>(acc, sm, A, a.ldl, m_ext, 1.f, rsc, Bm, a.b, n_ext, a.sp, nullptr, 0, a.K,
+                                       a.vec_a, a.vec_b);
+  else
+    gemm_tile_x3<false, true>(acc, sm, A, a.ldl, m_ext, Bm, a.b, n_ext, 0, a.K, a.vec_a, a.vec_b);
   if (threadIdx.x == 0) TL_MARK(1);
+  if (win) {
+    for (int e = threadIdx.x; e < 2048; e += kXThreads) hw[e] = 0u;  // a barrier follows in the staging
+    if (threadIdx.x == 0) nb_wave[8] = 0u;                            // staged keys
+  }
   const float* T = x3_stage_tile(acc, sm);
   if (threadIdx.x == 0) TL_MARK(2);
   // row pass: wavefront w takes rows w, w + 8, ..., lane l the columns 2l, 2l + 1
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int c0 = 2 * lane;
   const int64_t cg = n0 + c0;
   const bool in_block = n0 < a.zj2 && n0 + kTN > a.zj1;  // tile overlaps the columns holding masks
   float* Wg = a.W + m0 * a.b + cg;
   const uint8_t* Mg = a.mask + m0 * a.b + cg;
+  // the scales taken out of the product again, per column and per row
+  const float fp = H2 ? pow2_inv(a.sp) : 1.f;
+  const float f0 = fp * pow2_inv(a.sc[min(cg, a.b - 1)]), f1 = fp * pow2_inv(a.sc[min(cg + 1, a.b - 1)]);
   // window count of one new weight (columns right of the block only)
   const unsigned int wlo = win ? a.st->win_lo : 0u;
   const int wsh = win ? a.st->win_shift : kWinShiftMin;
@@ -2116,9 +2238,11 @@ __global__ __launch_bounds__(kXThreads, 4) void k_update(UpdateArgs a) {
     const float sx0 = h0 ? a.sx[cg] : 0.f, sx1 = h1 ? a.sx[cg + 1] : 0.f;
     float2 old[16];
     unsigned short mk[16];
+    float fr[16];  // the row is the wavefront's: scalar loads
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int64_t off = (int64_t)(wave + 8 * i) * a.b;
+      fr[i] = H2 ? pow2_inv(rsc[wave + 8 * i]) : 1.f;
       old[i] = *reinterpret_cast<const float2*>(Wg + off);
       mk[i] = in_block ? *reinterpret_cast<const unsigned short*>(Mg + off) : (unsigned short)0;
     }
@@ -2129,8 +2253,8 @@ __global__ __launch_bounds__(kXThreads, 4) void k_update(UpdateArgs a) {
       const int row = wave + 8 * i;
       const float2 t = *reinterpret_cast<const float2*>(T + row * kXCLd + c0);
       float2 o;
-      o.x = (z0 && (mk[i] & 0xffu)) ? 0.f : old[i].x - t.x;
-      o.y = (z1 && (mk[i] >> 8)) ? 0.f : old[i].y - t.y;
+      o.x = (z0 && (mk[i] & 0xffu)) ? 0.f : fmaf(-t.x, fr[i] * f0, old[i].x);
+      o.y = (z1 && (mk[i] >> 8)) ? 0.f : fmaf(-t.y, fr[i] * f1, old[i].y);
       *reinterpret_cast<float2*>(Wg + (int64_t)row * a.b) = o;
       if (h0) count(o.x, sx0, row);
       if (h1) count(o.y, sx1, row);
@@ -2144,7 +2268,7 @@ __global__ __launch_bounds__(kXThreads, 4) void k_update(UpdateArgs a) {
         if (c0 + e < n_ext) {
           const int64_t off = (int64_t)row * a.b + e;
           const bool z = in_block && cg + e >= a.zj1 && cg + e < a.zj2 && Mg[off] != 0;
-          const float o = z ? 0.f : Wg[off] - T[row * kXCLd + c0 + e];
+          const float o = z ? 0.f : fmaf(-T[row * kXCLd + c0 + e], (e ? f1 : f0) * (H2 ? pow2_inv(rsc[row]) : 1.f), Wg[off]);
           Wg[off] = o;
           if (win && cg + e >= a.zj2) count(o, a.sx[cg + e], row);
         }
@@ -2249,6 +2373,7 @@ thanos_status row_outliers(hipStream_t s, const float* W, const float* H, int64_
 // ------------------------------------------------------------------------------------------
 struct SweepWs {
   float* sx;
+  float* sc;
   float* Lam;
   float* P;
   unsigned int* hist;
@@ -2289,7 +2414,8 @@ static void launch_update(hipStream_t s, UpdateArgs ua, dim3 tiles) {
   ua.gy = (int)tiles.y;
   const unsigned rp = (tiles.y + 7) / 8;
   const unsigned n = tiles.y >= 16 ? 8 * rp * tiles.x : tiles.x * tiles.y;
-  hipLaunchKernelGGL(k_update, dim3(n), dim3(kXThreads), kUpdSmemBytes, s, ua);
+  if (ua.K > kUpdShortK) hipLaunchKernelGGL(k_update<true>, dim3(n), dim3(kXThreads), kUpdSmemBytes, s, ua);
+  else hipLaunchKernelGGL(k_update<false>, dim3(n), dim3(kXThreads), kUpdSmemBytes, s, ua);
 }
 
 // Whether rows that lose more than half of a block are solved through K = G^{-1} (see
@@ -2313,7 +2439,7 @@ size_t sweep_workspace_bytes(int64_t c, int64_t b, int B, bool outliers, int sma
   if (comp) n += align_up((size_t)ceil_div(b, B) * B * B * 4, 256);  // K blocks
   if (needs_big(B, smax))
     n += align_up((size_t)std::min<int64_t>(c, kBigSlots) * big_slot_floats(smax) * 4, 256);
-  n += align_up((size_t)b * 4, 256);            // sx
+  n += 2 * align_up((size_t)b * 4, 256);        // sx, sc
   n += align_up((size_t)lam_buffer_floats(c, B) * 4, 256);  // Lam
   n += align_up((size_t)b * b * 4, 256);        // P
   n += align_up(4 * 2048 * 4, 256);             // hist: window + three passes
@@ -2344,6 +2470,7 @@ static SweepWs carve_ws(void* ws, int64_t c, int64_t b, int B, bool outliers, in
     w.tile_scratch = reinterpret_cast<float*>(
         carve(p, (size_t)std::min<int64_t>(c, kBigSlots) * big_slot_floats(smax) * 4));
   w.sx = reinterpret_cast<float*>(carve(p, (size_t)b * 4));
+  w.sc = reinterpret_cast<float*>(carve(p, (size_t)b * 4));
   w.Lam = reinterpret_cast<float*>(carve(p, (size_t)lam_buffer_floats(c, B) * 4));
   w.P = reinterpret_cast<float*>(carve(p, (size_t)b * b * 4));
   w.hist = reinterpret_cast<unsigned int*>(carve(p, 4 * 2048 * 4));  // window + three passes
@@ -2388,6 +2515,8 @@ struct InitArgs {
   int n_conv, vec;
   const float* xn2;
   float* sx;
+  const float* umax;  // largest magnitudes of the columns of U -> sc, unless nullptr
+  float* sc;
   int64_t b;
   SelState* st;
   long long r;
@@ -2403,7 +2532,10 @@ __global__ __launch_bounds__(256) void k_sweep_init(InitArgs a) {
   }
   const int64_t i0 = (int64_t)((int)blockIdx.x - a.n_conv) * 256 + threadIdx.x;
   if (a.info && i0 == 0) *a.info = 0;
-  for (int64_t i = i0; i < a.b; i += kInitWgs * 256) a.sx[i] = sqrtf(a.xn2[i]);
+  for (int64_t i = i0; i < a.b; i += kInitWgs * 256) {
+    a.sx[i] = sqrtf(a.xn2[i]);
+    if (a.umax) a.sc[i] = col_scale(a.umax[i]);
+  }
   if (!a.st) return;
   for (int64_t i = i0; i < 4 * 2048; i += kInitWgs * 256) a.hist[i] = 0u;
   for (int64_t i = i0; i < kSelMaxWgs * kFlagStride; i += kInitWgs * 256) a.wgflag[i] = 0u;
@@ -2516,7 +2648,8 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
                     const float* H, const float* U, const float* xnorm2,
                     const thanos_prune_opts* o, long long r_total, long long n_out, float* W,
                     void* W_cast, uint8_t* mask, void* ws, int32_t* info, bool single_stream,
-                    PhaseTimer* pt, const float* Lfac, int64_t ldL, const float* Ldiag, bool prepared,
+                    PhaseTimer* pt, const float* Lfac, int64_t ldL, const float* Ldiag, const float* umax,
+                    bool prepared,
                     bool clear_info) {
   const int B = o->block_size;
   const bool outliers = n_out > 0;
@@ -2529,7 +2662,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
     THANOS_CHECK(sweep_prepare(s, W_in, wdt, c, b, H, o, n_out, W, ws, false));
   const bool conv = !prepared && !outliers;
   const InitArgs ia{W_in, W, c * b, conv ? (int)ceil_div(c * b, 1024) : 0,
-                    conv ? convert_vec(W_in, wdt, W, THANOS_F32) : 0, xnorm2, w.sx, b,
+                    conv ? convert_vec(W_in, wdt, W, THANOS_F32) : 0, xnorm2, w.sx, umax, w.sc, b,
                     unstructured ? w.st : nullptr, r_total, w.hist, w.wgflag,
                     clear_info ? info : nullptr};
   const dim3 igrid((unsigned)(ia.n_conv + kInitWgs));
@@ -2538,25 +2671,29 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
   else hipLaunchKernelGGL(k_sweep_init<__hip_bfloat16>, igrid, dim3(256), 0, s, ia);
   THANOS_LAUNCH_CHECK();
 
+  if (!umax) {
+    hipLaunchKernelGGL(k_col_scales, dim3((unsigned)ceil_div(b, 64)), dim3(1024), 0, s, U, b, B, w.sc);
+    THANOS_LAUNCH_CHECK();
+  }
+
   const bool aligned_b = (b % 4 == 0) && (B % 4 == 0);
   const int pair_w = (aligned_b && reinterpret_cast<uintptr_t>(W) % 8 == 0 &&
                       reinterpret_cast<uintptr_t>(mask) % 2 == 0) ? 1 : 0;
   {
-    BlockRowsArgs a{U, w.P, b, B,
+    BlockRowsArgs a{U, w.P, w.sc, b, B,
                     (aligned_b && reinterpret_cast<uintptr_t>(U) % 16 == 0) ? 1 : 0};
     dim3 grid((unsigned)ceil_div(b, kTN), (unsigned)ceil_div(b, B), (unsigned)ceil_div(B, kTM));
     THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_block_rows),
                                          hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         (int)kXSmemBytes));
-    THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_update),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         (int)kUpdSmemBytes));
-    hipLaunchKernelGGL(k_block_rows, grid, dim3(kXThreads), kXSmemBytes, s, a);
+                                         (int)kBlockRowsSmem));
+    for (const void* k : {reinterpret_cast<const void*>(k_update<true>), reinterpret_cast<const void*>(k_update<false>)})
+      THANOS_HIP_CHECK(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kUpdSmemBytes));
+    hipLaunchKernelGGL(k_block_rows, grid, dim3(kXThreads), kBlockRowsSmem, s, a);
     THANOS_LAUNCH_CHECK();
     if (comp) {
       const unsigned nt32 = (unsigned)ceil_div(B, 32);
       hipLaunchKernelGGL(k_comp_blocks, dim3(nt32, nt32, (unsigned)ceil_div(b, B)), dim3(256), 0, s,
-                         Lfac, ldL, Ldiag, b, B, w.Kc);
+                         Lfac, ldL, Ldiag, w.sc, b, B, w.Kc);
       THANOS_LAUNCH_CHECK();
     }
   }
@@ -2571,6 +2708,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
   AuxStream aux(s, super > 1 ? 2 * n_super : 0, single_stream);
   if (!aux.ok) return THANOS_ERR_HIP;
   int pending_join = -1;
+  const float sp = h2_scale((float)B);
   int win_parts = 0;  // workgroups of the previous block's update (partial counts to sum)
   for (int64_t j1 = 0; j1 < b; j1 += B) {
     const int bw = (int)std::min<int64_t>(B, b - j1);
@@ -2581,6 +2719,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
     const int64_t loff = (super == 1) ? 0 : (j1 - sb_start);
     const LamLayout at = lam_layout(c, ldl, sbi);
     float* lam_sb = w.Lam + at.lam;
+    float* rsc = unstructured ? w.Lam + at.rsc : reinterpret_cast<float*>(sbi & 1 ? w.row_eq : w.row_cand);
     if (unstructured) {
       phase_mark(pt, THANOS_PHASE_MASK);
       // 16-byte loads need W + i*b + j1 and sx + j1 aligned (W, sx come 256-byte aligned)
@@ -2620,6 +2759,9 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
     sa.W = W;
     sa.P = w.P;
     sa.sx = w.sx;
+    sa.sc = w.sc;
+    sa.rsc = rsc;
+    sa.rsc_first = j1 == sb_start ? 1 : 0;
     sa.mask_in = o->mask_in;
     sa.mask_out = mask;
     sa.Lam = lam_sb + loff;
@@ -2685,7 +2827,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
       if (feed) win_parts = (int)(grid.x * grid.y);
       UpdateArgs ua{W, lam_sb + loff, w.P, mask, c, b, j1, j1, sb_end, j1, j1 + bw, bw, ldl,
                     (B % 4 == 0) ? 1 : 0, aligned_b ? 1 : 0, pair_w,
-                    feed ? w.hist : nullptr, w.below_part, w.cand_n, w.cand, w.st, w.sx};
+                    feed ? w.hist : nullptr, w.below_part, w.cand_n, w.cand, w.st, w.sx, w.sc, rsc, sp};
       launch_update(s, ua, grid);
       THANOS_LAUNCH_CHECK();
     }
@@ -2699,7 +2841,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
       {
         UpdateArgs ua{W, lam_sb, w.P, mask, c, b, sb_start, sb_end, next_end, 0, 0, kk, ldl,
                       (B % 4 == 0) ? 1 : 0, aligned_b ? 1 : 0, pair_w, nullptr, nullptr, nullptr, nullptr,
-                      nullptr, nullptr};
+                      nullptr, nullptr, w.sc, rsc, sp};
         dim3 grid((unsigned)ceil_div(next_end - sb_end, kTN), (unsigned)ceil_div(c, kTM));
         launch_update(s, ua, grid);
         THANOS_LAUNCH_CHECK();
@@ -2708,7 +2850,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
         THANOS_CHECK(aux.fork((int)(2 * sbi)));
         UpdateArgs ua{W, lam_sb, w.P, mask, c, b, sb_start, next_end, b, 0, 0, kk, ldl,
                       (B % 4 == 0) ? 1 : 0, aligned_b ? 1 : 0, pair_w, nullptr, nullptr, nullptr, nullptr,
-                      nullptr, nullptr};
+                      nullptr, nullptr, w.sc, rsc, sp};
         dim3 grid((unsigned)ceil_div(b - next_end, kTN), (unsigned)ceil_div(c, kTM));
         launch_update(aux.stream, ua, grid);
         THANOS_LAUNCH_CHECK();

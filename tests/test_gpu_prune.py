@@ -749,3 +749,43 @@ def test_nm_rows_are_independent():
     W2, M2, _ = gpu_prune(np.ascontiguousarray(W[perm]), H32, mode="nm", n=2, m=4, B=128)
     np.testing.assert_array_equal(M1[perm], M2)
     np.testing.assert_array_equal(W1[perm], W2)
+
+
+@pytest.mark.parametrize("mode,kw,c,b,B", [
+    ("nm", dict(n=2, m=4), 130, 1160, 128),            # two super-blocks, the second with one short block
+    ("nm", dict(n=4, m=8), 37, 2600, 8),               # many super-blocks of a few columns
+    ("unstructured", dict(p=0.5), 130, 520, 128),
+    ("unstructured", dict(p=0.7), 33, 650, 256),       # complement form, tiled solver
+    ("unstructured", dict(p=0.6), 2561, 512, 256),     # complement form for many rows
+    ("unstructured", dict(p=0.5), 65, 333, 100)])      # unaligned rows
+def test_scales_of_channels_and_rows(mode, kw, c, b, B):
+    """The sweep's products see scaled columns and rows.  Undamped, H -> D H D, W -> R W D^-1 with
+    powers of two changes no metric's order within a row (n:m) or at all (R = 1), and every value of the
+    result by exactly that factor: masks equal, weights equal bit for bit."""
+    from tests.gpu_util import gpu_prune
+    W, H32 = _layer(c, b, 2 * b, "f32", seed=b + c)
+    g = np.random.default_rng(c)
+    d = np.ldexp(np.float32(1.0), g.integers(-20, 21, size=b))
+    r = np.ldexp(np.float32(1.0), g.integers(-20, 21, size=c) if mode == "nm" else np.zeros(c, int))
+    W1, M1, i1 = gpu_prune(W, H32, mode=mode, B=B, damp=0.0, **kw)
+    W2, M2, i2 = gpu_prune((r[:, None] * W / d[None, :]).astype(np.float32),
+                           (H32 * d[:, None] * d[None, :]).astype(np.float32), mode=mode, B=B, damp=0.0, **kw)
+    assert i1 == i2 == 0
+    np.testing.assert_array_equal(M1, M2)
+    np.testing.assert_array_equal(W1, W2 / r[:, None] * d[None, :])
+
+
+def test_given_factor_of_any_scale():
+    """A factor of the caller whose columns differ by 2^+-40 (scales come from the factor itself)."""
+    from tests.gpu_util import gpu_prune, gpu_factor
+    c, b, B = 70, 400, 64
+    W, H32 = _layer(c, b, 4 * b, "f32", seed=11)
+    U, xn2, info = gpu_factor(H32, 0.0)
+    assert info == 0
+    d = np.ldexp(np.float32(1.0), np.random.default_rng(3).integers(-40, 41, size=b))
+    W1, M1, i1 = gpu_prune(W, H32, mode="nm", n=2, m=4, B=B, U=U, xnorm2=xn2)
+    W2, M2, i2 = gpu_prune((W / d[None, :]).astype(np.float32), H32, mode="nm", n=2, m=4, B=B, U=U / d[None, :],
+                           xnorm2=xn2 * d * d)
+    assert i1 == i2 == 0
+    np.testing.assert_array_equal(M1, M2)
+    np.testing.assert_array_equal(W1, W2 * d[None, :])
