@@ -28,8 +28,6 @@
 
 namespace thanos {
 
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-
 // LDS view of a buffer: operand {a, b} x plane {x1, x2}
 __device__ __forceinline__ char* h2_plane(char* buf, int operand, int plane) {
   return buf + (operand * 2 + plane) * kXPlane;

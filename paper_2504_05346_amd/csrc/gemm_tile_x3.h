@@ -125,7 +125,6 @@ __device__ __forceinline__ void slab_load_x3(SlabRegsX3& r, const SlabSrcX3& s, 
 }
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 // Split two floats into three packed bf16 pairs (conversion = the packed two-at-a-time
 // instruction, the way back is a shift / a mask).

@@ -1386,14 +1386,15 @@ __global__ __launch_bounds__(64 * WPB, NTR == 2 ? 4 : 3) void k_solve_mfma(Solve
 //      meanwhile one wavefront updates the next diagonal tile and runs step 1 on it (look-ahead:
 //      the elimination is a chain of dependent instructions, the rest is throughput work).
 // L^T lambda = y is then solved from the last tile row upwards with the same T tiles.
-// All products are fp32 MFMAs (v_mfma_f32_32x32x2_f32).
+// Products are fp32 MFMAs (v_mfma_f32_32x32x2_f32), those of step 3 without BIG fp16 ones (tile32.h).
 //
 // !BIG: the tiles live in the registers of the wavefronts that own them from the gather to the
 // back-substitution; LDS only carries T and the current panel.  What bounds a row is the chain of
 // eliminations (3.3 us per tile), so the number of rows in flight per compute unit is what
 // counts: a row of 256 unknowns takes 41 KB of LDS and half of the registers, two run at once;
-// with the tiles in LDS (152 KB) a row filled the unit.  4096 rows of 256 unknowns: 890 -> 530 us,
-// matrix pipes 44 % busy.  Rows of up to 128 unknowns: five per unit instead of three.
+// with the tiles in LDS (152 KB) a row filled the unit.  Panel tiles go to LDS split into fp16 pairs, once
+// for the up to seven products that read each: 6 MFMAs of 32 cycles instead of 16 of 64.  4096 rows of 256
+// unknowns: 890 -> 530 (registers) -> 460 us.  Rows of up to 128 unknowns: five per unit instead of three.
 // BIG: tiles in global memory.
 constexpr int kTlLd = 33;          // LDS row stride of a tile (conflict-free rows and columns)
 constexpr int kTlSz = 32 * kTlLd;  // floats per tile
@@ -1465,12 +1466,15 @@ __device__ __forceinline__ float rs_dot(const f32x16& t, const float* v, int hi)
 }
 
 // Solves lambda R_hat = u for one row: nt tile rows, ns unknowns, R_hat[a][c] = G[q[a] * ldg + q[c]].
-// u (32 nt values, zero past ns) is overwritten, lam[0 : 32 nt] is the result.  tiles: NW * kRsTile
+// u (32 nt values, zero past ns) is overwritten, lam[0 : 32 nt] times the returned scale is the result.
+// The matrix is scaled by a power of two that brings its largest diagonal element to [2^28, 2^29): no
+// element of the factor then exceeds 2^14.5, and the trailing products, which are most of the work, take
+// two fp16 values per operand (tile32.h).  tiles: NW * kRsTile
 // floats (and 2 * kTlBw more behind them that may be overwritten).  Called by all NW wavefronts,
-// u and q complete; barriers inside, lam is complete on return.  Returns true if a pivot was not positive.
+// u and q complete; barriers inside, lam is complete on return.  bad: a pivot was not positive.
 template <int NW>
-__device__ __forceinline__ bool rs_solve(const float* __restrict__ G, unsigned int ldg, const int* q, int ns,
-                                         int nt, float* tiles, float* u, float* lam, float* aux) {
+__device__ __forceinline__ float rs_solve(const float* __restrict__ G, unsigned int ldg, const int* q, int ns,
+                                          int nt, float* tiles, float* u, float* lam, float* aux, bool& bad) {
   constexpr int SL = NW == 8 ? 4 : 2;  // tiles below the diagonal per wavefront
   const int lane = threadIdx.x & 63, lo = lane & 31, hi = lane >> 5;
   // the wavefronts' parts rotate with the row, so that the eliminations of the rows that run on a
@@ -1497,22 +1501,33 @@ __device__ __forceinline__ bool rs_solve(const float* __restrict__ G, unsigned i
 #pragma unroll
   for (int s = 0; s < SL; ++s)
     if (ti[s] < nt) fetch(off[s], ti[s], tj[s]);
+  if (w < nt) {  // largest diagonal element of the tile; lam is free until the end
+    float top = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) top = (tl_row(r, hi) == lo && 32 * w + lo < ns) ? fmaxf(top, dg[r]) : top;
+    top = wave_max(top);
+    if (lane == 0) lam[w] = top;
+  }
+  __syncthreads();  // the maxima are there, `tiles` is free (its previous contents have been read)
+  float top = lam[0];
+  for (int t = 1; t < nt; ++t) top = fmaxf(top, lam[t]);
+  const int te = 127 + 28 + 127 - (int)(__float_as_uint(top) >> 23);
+  const float scale = __uint_as_float((uint32_t)min(max(te, 1), 253) << 23);
   if (w < nt) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const bool in = 32 * w + lo < ns && 32 * w + tl_row(r, hi) < ns;
-      dg[r] = in ? -dg[r] : (tl_row(r, hi) == lo ? -1.f : 0.f);
+      dg[r] = in ? -scale * dg[r] : (tl_row(r, hi) == lo ? -1.f : 0.f);
     }
   }
 #pragma unroll
   for (int s = 0; s < SL; ++s)
     if (ti[s] < nt) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) off[s][r] = (32 * ti[s] + lo < ns) ? -off[s][r] : 0.f;
+      for (int r = 0; r < 16; ++r) off[s][r] = (32 * ti[s] + lo < ns) ? -scale * off[s][r] : 0.f;
     }
 
-  bool bad = false;
-  __syncthreads();  // `tiles` is free (its previous contents have been read)
+  bad = false;
   for (int p = 0; p < nt; ++p) {
     int l = lo, h = hi;  // not known to be the same in every step: keeps lane masks and LDS addresses,
     asm volatile("" : "+v"(l), "+v"(h));  // an instruction each, out of registers that outlive the step
@@ -1540,7 +1555,7 @@ __device__ __forceinline__ bool rs_solve(const float* __restrict__ G, unsigned i
         for (int r = 0; r < 16; ++r) C[r] = 0.f;
         rs_mma<false>(C, Tt, off[s], l, h);
         off[s] = C;
-        rs_store(tiles + (ti[s] - 1) * kRsTile, C, l, h);
+        rs_store_h2(tiles + (ti[s] - 1) * kRsTile, C, l + 32 * h);
       }
     if (w == p) {  // y_p = T u_p
       float y = 0.f;
@@ -1557,11 +1572,11 @@ __device__ __forceinline__ bool rs_solve(const float* __restrict__ G, unsigned i
     __syncthreads();  // panel and y_p are there
     if (p + 1 == nt) break;
     if (w > p && w < nt)
-      rs_mma<false>(dg, tiles + (w - 1) * kRsTile, tiles + (w - 1) * kRsTile, l, h);
+      rs_mma_h2(dg, tiles + (w - 1) * kRsTile, tiles + (w - 1) * kRsTile, l + 32 * h);
 #pragma unroll
     for (int s = 0; s < SL; ++s) {
       if (ti[s] < nt && tj[s] > p)
-        rs_mma<false>(off[s], tiles + (tj[s] - 1) * kRsTile, tiles + (ti[s] - 1) * kRsTile, l, h);
+        rs_mma_h2(off[s], tiles + (tj[s] - 1) * kRsTile, tiles + (ti[s] - 1) * kRsTile, l + 32 * h);
       if (ti[s] < nt && tj[s] == p) {  // u_i -= L_ip y_p (one tile per i in a step)
         const float d = rs_dot(off[s], u + 32 * p, h);
         if (lane < 32) u[32 * ti[s] + lane] += d;
@@ -1597,7 +1612,7 @@ __device__ __forceinline__ bool rs_solve(const float* __restrict__ G, unsigned i
       }
     __syncthreads();
   }
-  return bad;
+  return scale;
 }
 
 // y[j] = sum_a x[a] * K[a * ldk + j], j < bw (bw a multiple of 4, K 16-byte aligned rows), for a
@@ -1868,11 +1883,12 @@ __global__ __launch_bounds__(64 * NW, (BIG ? 2 : (NW == 8 ? 4 : 5))) void k_solv
   __syncthreads();
 
   bool bad = false;
+  float ls = 1.f;  // what lam is to be multiplied by
   // R_hat = G[q, q], or K[k, k] for the complement
   const float* G = comp ? a.Kc : a.P + a.j1 * a.b + a.j1;
   const int64_t ldg = comp ? (int64_t)a.ldk : a.b;
   if constexpr (!BIG) {
-    if (ns > 0) bad = rs_solve<NW>(G, (unsigned int)ldg, q, ns, nt, tiles, u, lam, aux);
+    if (ns > 0) ls = rs_solve<NW>(G, (unsigned int)ldg, q, ns, nt, tiles, u, lam, aux, bad);
   } else {
   // ---- gather R_hat into the tiles: thread <-> (rows tid/32 + (NT/32)e, column tid%32) of a tile;
   //      up to four tiles of a tile row are fetched together, all loads unconditional from
@@ -2017,7 +2033,7 @@ __global__ __launch_bounds__(64 * NW, (BIG ? 2 : (NW == 8 ? 4 : 5))) void k_solv
 #pragma unroll
     for (int ch = 0; ch < CH; ++ch) wrow[tid + NT * ch] = 0.f;
     __syncthreads();
-    for (int t = tid; t < s; t += NT) wrow[q[t]] = lam[t];
+    for (int t = tid; t < s; t += NT) wrow[q[t]] = ls * lam[t];
     __syncthreads();
     float top = 0.f;
 #pragma unroll
@@ -2029,14 +2045,14 @@ __global__ __launch_bounds__(64 * NW, (BIG ? 2 : (NW == 8 ? 4 : 5))) void k_solv
     }
     rsc_lower(a, i, top);
   } else if (SEL == SEL_PICKED) {  // w~ - y~: -y on the kept columns, w~ is there
-    for (int t = tid; t < ns; t += NT) a.Z[i * a.ldz + q[t]] = -lam[t];
+    for (int t = tid; t < ns; t += NT) a.Z[i * a.ldz + q[t]] = -ls * lam[t];
   } else {
     // lambda = ((w~ - y~) K)_q: x = w on the removed columns, -y on the kept ones
     __syncthreads();
 #pragma unroll
     for (int ch = 0; ch < CH; ++ch) key[tid + NT * ch] = sel[ch] ? us[ch] : 0.f;
     __syncthreads();
-    for (int t = tid; t < ns; t += NT) key[q[t]] = -lam[t];
+    for (int t = tid; t < ns; t += NT) key[q[t]] = -ls * lam[t];
     __syncthreads();
     tl_matvec<NW, BIG>(key, a.bw, a.Kc, a.ldk, wrow, part);
     float top = 0.f;

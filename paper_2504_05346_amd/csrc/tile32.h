@@ -66,6 +66,41 @@ __device__ __forceinline__ void rs_mma(f32x16& acc, const float* a, const f32x16
   }
 }
 
+// ---- products on the fp16 matrix cores ----
+// x = x1 + x2 in fp16 for |x| < 2^15 (gemm_tile_h2.h), a1 b1 + a1 b2 + a2 b1: six MFMAs of 32 cycles for the
+// 32 k-values of two tiles instead of sixteen of 64.  An operand-layout tile's registers 8 m .. 8 m + 7 are
+// the k-values of MFMA m, the same ones in both operands.  In LDS a split tile is four 16-byte pieces per
+// lane (x1, x2 of m = 0, then of m = 1), in the lanes' order: kRsTile floats hold it.
+__device__ __forceinline__ void rs_store_h2(float* tile, const f32x16& v, int lane) {
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    u32x4 h, l;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const f32x2 x = {v[8 * m + 2 * e], v[8 * m + 2 * e + 1]};
+      const f16x2 x1 = __builtin_convertvector(x, f16x2);
+      const f32x2 r = {x[0] - (float)x1[0], x[1] - (float)x1[1]};
+      h[e] = __builtin_bit_cast(uint32_t, x1);
+      l[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, f16x2));
+    }
+    *reinterpret_cast<u32x4*>(tile + 256 * (2 * m) + 4 * lane) = h;
+    *reinterpret_cast<u32x4*>(tile + 256 * (2 * m + 1) + 4 * lane) = l;
+  }
+}
+// acc += A B^T, both split tiles in LDS
+__device__ __forceinline__ void rs_mma_h2(f32x16& acc, const float* a, const float* b, int lane) {
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    const f16x8 a1 = *reinterpret_cast<const f16x8*>(a + 256 * (2 * m) + 4 * lane);
+    const f16x8 a2 = *reinterpret_cast<const f16x8*>(a + 256 * (2 * m + 1) + 4 * lane);
+    const f16x8 b1 = *reinterpret_cast<const f16x8*>(b + 256 * (2 * m) + 4 * lane);
+    const f16x8 b2 = *reinterpret_cast<const f16x8*>(b + 256 * (2 * m + 1) + 4 * lane);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, b1, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, b2, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, b1, acc, 0, 0, 0);
+  }
+}
+
 // The power of two that brings a normal d > 0 to [2, 4), in one instruction.  Scaling by it is exact, and
 // keeps the determinants of pairs of pivots in the range of fp32 whenever the pivots are.
 __device__ __forceinline__ float pivot_scale(float d) {

@@ -754,6 +754,8 @@ def test_nm_rows_are_independent():
 @pytest.mark.parametrize("mode,kw,c,b,B", [
     ("nm", dict(n=2, m=4), 130, 1160, 128),            # two super-blocks, the second with one short block
     ("nm", dict(n=4, m=8), 37, 2600, 8),               # many super-blocks of a few columns
+    ("nm", dict(n=2, m=4), 40, 780, 256),              # tiled solver, four tile rows
+    ("nm", dict(n=4, m=8), 21, 1064, 512),             # eight, then one of four unknowns
     ("unstructured", dict(p=0.5), 130, 520, 128),
     ("unstructured", dict(p=0.7), 33, 650, 256),       # complement form, tiled solver
     ("unstructured", dict(p=0.6), 2561, 512, 256),     # complement form for many rows
