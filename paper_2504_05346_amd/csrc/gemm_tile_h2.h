@@ -73,6 +73,20 @@ __device__ __forceinline__ void split2_h2(float x0, float x1, float s0, float s1
   packed[1] = __builtin_bit_cast(uint32_t, l);
 }
 
+// eight values of a lane, in the order in which the MFMA takes them
+__device__ __forceinline__ void split8_h2(const f32x4& x, const f32x4& y, float s, f16x8& hi, f16x8& lo) {
+  u32x4 h, l;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    uint32_t pk[2];
+    split2_h2(e < 2 ? x[2 * e] : y[2 * e - 4], e < 2 ? x[2 * e + 1] : y[2 * e - 3], s, s, pk);
+    h[e] = pk[0];
+    l[e] = pk[1];
+  }
+  hi = __builtin_bit_cast(f16x8, h);
+  lo = __builtin_bit_cast(f16x8, l);
+}
+
 // Scale of an operand: one for all of it, or (rows) that times one per row m of the tile.
 struct ScaleH2 {
   float all;
