@@ -37,3 +37,38 @@ def test_layer_set_matches_separate_calls_and_oracle():
         # and the oracle under the same mask
         Wt, _ = orc.prune_fast(W, H, mode="nm", n=2, m=4, B=128, damp=0.01, mask_in=Mg)
         assert np.linalg.norm(Wg - Wt) <= 1e-3 * np.linalg.norm(Wt)
+
+
+@pytest.mark.parametrize("rows", [(768, 768, 768), (17, 400), (2000, 1900)])
+@pytest.mark.parametrize("mode", ["nm", "unstructured"])
+def test_sweeps_side_by_side_equal_separate_calls(mode, rows):
+    """Sweeps on streams of their own (the last pair has too many rows for that), called on a stream that
+    is not the default one and read there without further waiting: the bits of separate calls.  (Up to
+    4064 tokens the accumulation has one order.)"""
+    import torch
+    import paper_2504_05346_amd as th
+    from tests.gpu_util import dev, gpu_prune, gpu_factor
+    b, T = 512, 2048
+    X = make_calibration(LayerSpec("x", c=1, b=b, tokens=T, dtype="f16", rho=0.7, k_mix=16, seed=3))
+    Ws = [make_weight(LayerSpec("w", c=c, b=b, tokens=T, dtype="f16", seed=40 + k)) for k, c in enumerate(rows)]
+    kw = dict(n=2, m=4) if mode == "nm" else dict(sparsity=0.5)
+    Xd, Wd = dev(X), [dev(W) for W in Ws]
+    torch.cuda.synchronize()
+    with torch.cuda.stream(torch.cuda.Stream()):
+        res, Hd = th.prune_layer_set(Wd, [Xd], mode=th.THANOS_NM if mode == "nm" else th.THANOS_UNSTRUCTURED,
+                                     block_size=128, cast=True, **kw)
+        got = [{k: v.clone() for k, v in r.items()} for r in res]
+        del res
+        Hl = Hd.cpu().numpy()
+    torch.cuda.synchronize()
+    H32 = (np.tril(Hl) + np.tril(Hl, -1).T).astype(np.float32)
+    U, xn2, info = gpu_factor(H32, 0.01)
+    assert info == 0
+    kw = dict(n=2, m=4) if mode == "nm" else dict(p=0.5)
+    for W, r in zip(Ws, got):
+        assert int(r["info"].item()) == 0
+        Wg, Mg, info = gpu_prune(W, H32, mode=mode, B=128, U=U, xnorm2=xn2, **kw)
+        assert info == 0
+        np.testing.assert_array_equal(r["mask"].cpu().numpy(), Mg)
+        np.testing.assert_array_equal(r["W"].cpu().numpy(), Wg)
+        np.testing.assert_array_equal(r["W_cast"].cpu().numpy(), Wg.astype(np.float16))
