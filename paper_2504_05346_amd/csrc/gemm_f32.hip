@@ -15,7 +15,7 @@ struct GemmArgs {
   int M, N, K;
   float alpha, beta;
   int lower_only;
-  int vec_a, vec_b, vec_c;
+  int vec_a, vec_b;  // 16-byte aligned rows (k_gemm_direct)
   int b_tri;  // TriB
   float sa, sb;          // H2: scales of the operands ...
   const float* bound_b;  // ... of B from a bound on the device instead, unless nullptr
@@ -41,28 +41,28 @@ __global__ __launch_bounds__(kXThreads, 4) void k_gemm_f32(GemmArgs g) {
   const int kend = g.b_tri == kTriUpper ? min(g.K, n0 + kTN) : g.K;
   if constexpr (H2) {
     const float sb = g.bound_b ? h2_scale(*g.bound_b) : g.sb;
-    gemm_tile_h2<AK, BK, 1>(acc, sm, A, g.lda, m_ext, g.sa, nullptr, B, g.ldb, n_ext, sb, nullptr, kbeg, kend, g.vec_a,
-                         g.vec_b);
+    gemm_tile_h2<AK, BK, 1>(acc, sm, A, g.lda, m_ext, g.sa, nullptr, B, g.ldb, n_ext, sb, nullptr, kbeg, kend, true,
+                         true);
     g.alpha *= (1.f / g.sa) * (1.f / sb);
   } else {
-    gemm_tile_x3<AK, BK>(acc, sm, A, g.lda, m_ext, B, g.ldb, n_ext, kbeg, kend, g.vec_a, g.vec_b);
+    gemm_tile_x3<AK, BK>(acc, sm, A, g.lda, m_ext, B, g.ldb, n_ext, kbeg, kend, true, true);
   }
   const float* T = x3_stage_tile(acc, sm);
   // row pass: wavefront w takes rows w, w + 8, ..., lane l the columns 2l, 2l + 1
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int c0 = 2 * lane;
   float* Cg = g.C + (int64_t)m0 * g.ldc + n0 + c0;
-  if (m_ext == kTM && n_ext == kTN && g.vec_c) {  // whole tile, 8-byte aligned pairs
-    float2 old[16];
+  if (m_ext == kTM && n_ext == kTN) {  // whole tile: pairs of columns, of any alignment
+    f32x2u old[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i)
-      old[i] = g.beta != 0.f ? *reinterpret_cast<const float2*>(Cg + (int64_t)(wave + 8 * i) * g.ldc)
-                             : make_float2(0.f, 0.f);
+      old[i] = g.beta != 0.f ? *reinterpret_cast<const f32x2u*>(Cg + (int64_t)(wave + 8 * i) * g.ldc)
+                             : f32x2u{0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const float2 t = *reinterpret_cast<const float2*>(T + (wave + 8 * i) * kXCLd + c0);
-      *reinterpret_cast<float2*>(Cg + (int64_t)(wave + 8 * i) * g.ldc) =
-          make_float2(g.beta * old[i].x + g.alpha * t.x, g.beta * old[i].y + g.alpha * t.y);
+      *reinterpret_cast<f32x2u*>(Cg + (int64_t)(wave + 8 * i) * g.ldc) =
+          f32x2u{g.beta * old[i].x + g.alpha * t.x, g.beta * old[i].y + g.alpha * t.y};
     }
   } else {
     for (int i = 0; i < 16; ++i) {
@@ -188,8 +188,7 @@ thanos_status gemm_bounded(hipStream_t s, int64_t M, int64_t N, int64_t K, float
                            const float* bound_b_dev, float beta, float* C, int64_t ldc, bool lower_only) {
   if (M <= 0 || N <= 0) return THANOS_OK;
   GemmArgs g{A, B, C, lda, ldb, ldc, (int)M, (int)N, (int)K, alpha, beta, lower_only ? 1 : 0,
-             vec_ok(A, lda) ? 1 : 0, vec_ok(B, ldb) ? 1 : 0,
-             (reinterpret_cast<uintptr_t>(C) % 8 == 0 && ldc % 2 == 0) ? 1 : 0, kTriNone,
+             vec_ok(A, lda) ? 1 : 0, vec_ok(B, ldb) ? 1 : 0, kTriNone,
              h2_scale(bound_a), h2_scale(bound_b), bound_b_dev};
   if (direct_ok(g)) return launch_direct<true>(s, g);
   THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_f32<false, false, true>),
@@ -206,8 +205,7 @@ thanos_status gemm_f32(hipStream_t s, bool a_kmajor, bool b_kmajor, int64_t M, i
                        TriB b_tri, bool beside) {
   if (M <= 0 || N <= 0) return THANOS_OK;
   GemmArgs g{A, B, C, lda, ldb, ldc, (int)M, (int)N, (int)K, alpha, beta, lower_only ? 1 : 0,
-             vec_ok(A, lda) ? 1 : 0, vec_ok(B, ldb) ? 1 : 0,
-             (reinterpret_cast<uintptr_t>(C) % 8 == 0 && ldc % 2 == 0) ? 1 : 0, b_tri, 1.f, 1.f, nullptr};
+             vec_ok(A, lda) ? 1 : 0, vec_ok(B, ldb) ? 1 : 0, b_tri, 1.f, 1.f, nullptr};
   if (!a_kmajor && !b_kmajor && b_tri == kTriNone && direct_ok(g)) return launch_direct<false>(s, g);
   dim3 grid((unsigned)ceil_div(N, kTN), (unsigned)ceil_div(M, kTM));
   if (b_tri != kTriNone) std::swap(grid.x, grid.y);

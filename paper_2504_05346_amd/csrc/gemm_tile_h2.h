@@ -193,7 +193,7 @@ __device__ __forceinline__ void h2_produce(char* smem, int operand, const float*
   }
 }
 
-template <bool KMAJOR, bool ROWS, int NBUF>
+template <bool KMAJOR, bool ROWS, int NBUF, bool PIECES>
 __device__ __forceinline__ void h2_producer(char* smem, int operand, const float* __restrict__ P, int64_t ld,
                                             int ext, int kbeg, int kend, bool vec, const ScaleH2& sc, int u) {
   const int nslab = (kend - kbeg + kXK - 1) / kXK;
@@ -201,13 +201,13 @@ __device__ __forceinline__ void h2_producer(char* smem, int operand, const float
   const bool whole = ext == 128 && (kend - kbeg) % kXK == 0;
   if (fast && whole && kend - kbeg == 4 * kXK) h2_produce4<KMAJOR, ROWS, NBUF>(smem, operand, P, ld, ext, kbeg, sc, u);
   else if (fast && whole) h2_produce<KMAJOR, true, false, ROWS, NBUF>(smem, operand, P, ld, ext, kbeg, kend, nslab, sc, u);
-  else if (fast) h2_produce<KMAJOR, true, true, ROWS, NBUF>(smem, operand, P, ld, ext, kbeg, kend, nslab, sc, u);
+  else if (PIECES || fast) h2_produce<KMAJOR, true, true, ROWS, NBUF>(smem, operand, P, ld, ext, kbeg, kend, nslab, sc, u);
   else h2_produce<KMAJOR, false, false, ROWS, NBUF>(smem, operand, P, ld, ext, kbeg, kend, nslab, sc, u);
 }
 
 // acc += (sa A)[0:128, kbeg:kend] (sb B)[kbeg:kend, 0:128]; otherwise as gemm_tile_x3().  ROWS: further
-// scales of the m_ext rows of A (the n_ext columns of B).
-template <bool A_KMAJOR, bool B_KMAJOR, int NBUF, bool A_ROWS = false, bool B_ROWS = false>
+// scales of the m_ext rows of A (the n_ext columns of B).  B_PIECES: the extents of B are multiples of 4.
+template <bool A_KMAJOR, bool B_KMAJOR, int NBUF, bool A_ROWS = false, bool B_ROWS = false, bool B_PIECES = false>
 __device__ __forceinline__ void gemm_tile_h2(TileAcc& acc, char* smem, const float* __restrict__ A,
                                              int64_t lda, int m_ext, float sa, const float* arows,
                                              const float* __restrict__ B, int64_t ldb, int n_ext, float sb,
@@ -224,9 +224,9 @@ __device__ __forceinline__ void gemm_tile_h2(TileAcc& acc, char* smem, const flo
   if (B_ROWS && wave >= 6) load_rows_h2<B_KMAJOR>(sc, brows, n_ext, u);
   __syncthreads();  // previous users of the LDS buffers are done
   if (wave >= 6) {
-    h2_producer<B_KMAJOR, B_ROWS, NBUF>(smem, 1, B, ldb, n_ext, kbeg, kend, vec_b, sc, u);
+    h2_producer<B_KMAJOR, B_ROWS, NBUF, B_PIECES>(smem, 1, B, ldb, n_ext, kbeg, kend, vec_b, sc, u);
   } else if (wave >= 4) {
-    h2_producer<A_KMAJOR, A_ROWS, NBUF>(smem, 0, A, lda, m_ext, kbeg, kend, vec_a, sc, u);
+    h2_producer<A_KMAJOR, A_ROWS, NBUF, false>(smem, 0, A, lda, m_ext, kbeg, kend, vec_a, sc, u);
   } else {
     const int wm = wave >> 1, wn = wave & 1;
     const int lo = lane & 31, hi = lane >> 5;

@@ -83,7 +83,7 @@ __device__ __forceinline__ void slab_src_x3(SlabSrcX3& s, const float* __restric
 
 // Loads slab number `it` (k0 = kbeg + it*kXK); krem = kend - k0 (<= 0: nothing is read).
 // FAST: every piece is either completely inside the operand or completely outside (the caller
-// checked alignment and that the extents are multiples of 4).  The loads are then issued
+// checked that the extents are multiples of 4; the loads need no more than aligned elements).  The loads are then issued
 // unconditionally (from a safe address when outside) and outside pieces are zeroed when the
 // slab is split: straight-line code with no early use of the data, so that the compiler can
 // keep the newer of the two slabs in flight while it waits for the older one.  Conditional
@@ -98,7 +98,8 @@ __device__ __forceinline__ void slab_load_x3(SlabRegsX3& r, const SlabSrcX3& s, 
       // no use of the loaded value here: the zeroing of outside pieces happens when the slab
       // is split, so that nothing waits for these loads before then
       const bool ok = s.row_ok[q] && s.kofs[q] < krem;
-      r.v[q] = *reinterpret_cast<const float4*>(ok ? p : safe);
+      const f32x4u v = *reinterpret_cast<const f32x4u*>(ok ? p : safe);
+      r.v[q] = make_float4(v[0], v[1], v[2], v[3]);
       if (q == 0) r.ok = 0;
       r.ok |= ok ? (1u << q) : 0u;
       continue;

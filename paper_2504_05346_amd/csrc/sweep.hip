@@ -39,7 +39,6 @@ struct BlockRowsArgs {
   const float* sc;
   int64_t b;
   int B;
-  int vec;
 };
 
 constexpr size_t kBlockRowsSmem = kXSmemBytes + kTM * sizeof(float);
@@ -59,19 +58,19 @@ __global__ __launch_bounds__(kXThreads, 4) void k_block_rows(BlockRowsArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const float s0 = a.sc[min(col0 + 2 * lane, a.b - 1)], s1 = a.sc[min(col0 + 2 * lane + 1, a.b - 1)];
   const float mine = a.sc[min(j1 + mrow0 + ((int)threadIdx.x & (kTM - 1)), a.b - 1)];
-  gemm_tile_x3<true, true>(acc, sm, A, a.b, m_ext, Bm, a.b, n_ext, 0, bw, a.vec, a.vec);
+  gemm_tile_x3<true, true>(acc, sm, A, a.b, m_ext, Bm, a.b, n_ext, 0, bw, true, true);
   float* const sr = reinterpret_cast<float*>(sm + kXSmemBytes);  // scales of the rows, behind the tile
   if (threadIdx.x < kTM) sr[threadIdx.x] = mine;  // a barrier follows in the staging
   const float* T = x3_stage_tile(acc, sm);
   float* Pg = a.P + (j1 + mrow0) * a.b + col0;
-  const bool whole = m_ext == kTM && n_ext == kTN && a.vec;  // P is 256-byte aligned, b, col0 multiples of 4
+  const bool whole = m_ext == kTM && n_ext == kTN;
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     const int row = wave + 8 * i;
     const float2 t = *reinterpret_cast<const float2*>(T + row * kXCLd + 2 * lane);
-    const float2 o = make_float2(t.x * sr[row] * s0, t.y * sr[row] * s1);
+    const f32x2u o = {t.x * sr[row] * s0, t.y * sr[row] * s1};
     if (whole) {
-      *reinterpret_cast<float2*>(Pg + (int64_t)row * a.b + 2 * lane) = o;
+      *reinterpret_cast<f32x2u*>(Pg + (int64_t)row * a.b + 2 * lane) = o;
     } else if (row < m_ext) {
       if (2 * lane < n_ext) Pg[(int64_t)row * a.b + 2 * lane] = o.x;
       if (2 * lane + 1 < n_ext) Pg[(int64_t)row * a.b + 2 * lane + 1] = o.y;
@@ -2151,8 +2150,7 @@ struct UpdateArgs {
   int64_t prow0;        // first row of P (= first reduction index)
   int64_t col0, col_end;
   int64_t zj1, zj2;
-  int K, ldl, vec_a, vec_b;
-  int vec_w;            // W 8-byte and mask 2-byte aligned, b and col0 even: row pass in pairs
+  int K, ldl, vec_a;
   // Unstructured mode: while the new weights are at hand, the columns right of the block are
   // histogrammed for the NEXT block's selection (window around the current threshold, see
   // k_select); hist == nullptr switches this off.
@@ -2169,6 +2167,8 @@ struct UpdateArgs {
 };
 
 // two slabs of the operands; after the product the staged tile and, behind it, the window counts
+typedef unsigned short u16u __attribute__((aligned(1)));  // two mask bytes
+
 constexpr size_t kUpdSmemBytes = kH2SmemBytes;
 static_assert(kXSmemBytes + 2048 * sizeof(unsigned int) + 16 * sizeof(unsigned int) + kCandStage * sizeof(uint2) <=
                   kUpdSmemBytes, "both fit");
@@ -2210,11 +2210,14 @@ __global__ __launch_bounds__(kXThreads, 4) void k_update(UpdateArgs a) {
   TileAcc acc;
   acc_zero(acc);
   const float* rsc = a.rsc + m0;
+  // P is fetched 16 bytes at a time whatever its row stride: up to three columns past the last one, values of
+  // the next row or of what lies behind P in the workspace, which end in columns that are not written
+  const int n4 = (n_ext + 3) & ~3;
   if constexpr (H2)
-    gemm_tile_h2<false, true, 2, true>(acc, sm, A, a.ldl, m_ext, 1.f, rsc, Bm, a.b, n_ext, a.sp, nullptr, 0, a.K,
-                                       a.vec_a, a.vec_b);
+    gemm_tile_h2<false, true, 2, true, false, true>(acc, sm, A, a.ldl, m_ext, 1.f, rsc, Bm, a.b, n4, a.sp, nullptr, 0, a.K,
+                                       a.vec_a, true);
   else
-    gemm_tile_x3<false, true>(acc, sm, A, a.ldl, m_ext, Bm, a.b, n_ext, 0, a.K, a.vec_a, a.vec_b);
+    gemm_tile_x3<false, true>(acc, sm, A, a.ldl, m_ext, Bm, a.b, n4, 0, a.K, a.vec_a, true);
   if (threadIdx.x == 0) TL_MARK(1);
   if (win) {
     for (int e = threadIdx.x; e < 2048; e += kXThreads) hw[e] = 0u;  // a barrier follows in the staging
@@ -2247,20 +2250,20 @@ __global__ __launch_bounds__(kXThreads, 4) void k_update(UpdateArgs a) {
       if (k < (unsigned int)kCandStage) stage[k] = make_uint2(key, (unsigned int)(m0 + row));
     }
   };
-  if (m_ext == kTM && n_ext == kTN && a.vec_w) {  // whole tile, aligned pairs
+  if (m_ext == kTM && n_ext == kTN) {  // whole tile: pairs of columns, of any alignment
     const bool z0 = in_block && cg >= a.zj1 && cg < a.zj2;
     const bool z1 = in_block && cg + 1 >= a.zj1 && cg + 1 < a.zj2;
     const bool h0 = win && cg >= a.zj2, h1 = win && cg + 1 >= a.zj2;
     const float sx0 = h0 ? a.sx[cg] : 0.f, sx1 = h1 ? a.sx[cg + 1] : 0.f;
-    float2 old[16];
+    f32x2u old[16];
     unsigned short mk[16];
     float fr[16];  // the row is the wavefront's: scalar loads
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int64_t off = (int64_t)(wave + 8 * i) * a.b;
       fr[i] = H2 ? pow2_inv(rsc[wave + 8 * i]) : 1.f;
-      old[i] = *reinterpret_cast<const float2*>(Wg + off);
-      mk[i] = in_block ? *reinterpret_cast<const unsigned short*>(Mg + off) : (unsigned short)0;
+      old[i] = *reinterpret_cast<const f32x2u*>(Wg + off);
+      mk[i] = in_block ? *reinterpret_cast<const u16u*>(Mg + off) : (unsigned short)0;
     }
     TL_WAIT_LOADS();
     if (threadIdx.x == 0) TL_MARK(3);
@@ -2268,26 +2271,46 @@ __global__ __launch_bounds__(kXThreads, 4) void k_update(UpdateArgs a) {
     for (int i = 0; i < 16; ++i) {
       const int row = wave + 8 * i;
       const float2 t = *reinterpret_cast<const float2*>(T + row * kXCLd + c0);
-      float2 o;
+      f32x2u o;
       o.x = (z0 && (mk[i] & 0xffu)) ? 0.f : fmaf(-t.x, fr[i] * f0, old[i].x);
       o.y = (z1 && (mk[i] >> 8)) ? 0.f : fmaf(-t.y, fr[i] * f1, old[i].y);
-      *reinterpret_cast<float2*>(Wg + (int64_t)row * a.b) = o;
+      *reinterpret_cast<f32x2u*>(Wg + (int64_t)row * a.b) = o;
       if (h0) count(o.x, sx0, row);
       if (h1) count(o.y, sx1, row);
     }
   } else {
-    for (int i = 0; i < 16; ++i) {
-      const int row = wave + 8 * i;
-      if (row >= m_ext) break;
+    // all loads first, from clamped addresses: one at a time between the stores, rows of 1365 columns took 30
+    // us per launch instead of 17
+    const bool ok0 = c0 < n_ext, ok1 = c0 + 1 < n_ext;
+    const bool z0 = in_block && cg >= a.zj1 && cg < a.zj2, z1 = in_block && cg + 1 >= a.zj1 && cg + 1 < a.zj2;
+    const bool h0 = win && ok0 && cg >= a.zj2, h1 = win && ok1 && cg + 1 >= a.zj2;
+    const float sx0 = h0 ? a.sx[cg] : 0.f, sx1 = h1 ? a.sx[cg + 1] : 0.f;
+    const int64_t d0 = (ok0 ? 0 : n_ext - 1 - c0), d1 = (ok1 ? 1 : n_ext - 1 - c0);  // to a column that exists
+#pragma clang loop unroll(disable)
+    for (int r0 = wave; r0 < m_ext; r0 += 32) {  // four rows at a time
+      float w0[4], w1[4], fr[4];
+      uint8_t k0[4], k1[4];
 #pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        if (c0 + e < n_ext) {
-          const int64_t off = (int64_t)row * a.b + e;
-          const bool z = in_block && cg + e >= a.zj1 && cg + e < a.zj2 && Mg[off] != 0;
-          const float o = z ? 0.f : fmaf(-T[row * kXCLd + c0 + e], (e ? f1 : f0) * (H2 ? pow2_inv(rsc[row]) : 1.f), Wg[off]);
-          Wg[off] = o;
-          if (win && cg + e >= a.zj2) count(o, a.sx[cg + e], row);
-        }
+      for (int i = 0; i < 4; ++i) {
+        const int row = min(r0 + 8 * i, m_ext - 1);
+        const int64_t off = (int64_t)row * a.b;
+        fr[i] = H2 ? pow2_inv(rsc[row]) : 1.f;
+        w0[i] = Wg[off + d0];
+        w1[i] = Wg[off + d1];
+        k0[i] = in_block ? Mg[off + d0] : (uint8_t)0;
+        k1[i] = in_block ? Mg[off + d1] : (uint8_t)0;
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int row = r0 + 8 * i;
+        if (row >= m_ext) break;
+        const float2 t = *reinterpret_cast<const float2*>(T + row * kXCLd + c0);
+        const float o0 = (z0 && k0[i]) ? 0.f : fmaf(-t.x, fr[i] * f0, w0[i]);
+        const float o1 = (z1 && k1[i]) ? 0.f : fmaf(-t.y, fr[i] * f1, w1[i]);
+        if (ok0) Wg[(int64_t)row * a.b] = o0;
+        if (ok1) Wg[(int64_t)row * a.b + 1] = o1;
+        if (h0) count(o0, sx0, row);
+        if (h1) count(o1, sx1, row);
       }
     }
   }
@@ -2692,12 +2715,8 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
     THANOS_LAUNCH_CHECK();
   }
 
-  const bool aligned_b = (b % 4 == 0) && (B % 4 == 0);
-  const int pair_w = (aligned_b && reinterpret_cast<uintptr_t>(W) % 8 == 0 &&
-                      reinterpret_cast<uintptr_t>(mask) % 2 == 0) ? 1 : 0;
   {
-    BlockRowsArgs a{U, w.P, w.sc, b, B,
-                    (aligned_b && reinterpret_cast<uintptr_t>(U) % 16 == 0) ? 1 : 0};
+    BlockRowsArgs a{U, w.P, w.sc, b, B};
     dim3 grid((unsigned)ceil_div(b, kTN), (unsigned)ceil_div(b, B), (unsigned)ceil_div(B, kTM));
     THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_block_rows),
                                          hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -2842,7 +2861,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
       const bool feed = unstructured && j1 + bw < b;  // a next block exists: count its window
       if (feed) win_parts = (int)(grid.x * grid.y);
       UpdateArgs ua{W, lam_sb + loff, w.P, mask, c, b, j1, j1, sb_end, j1, j1 + bw, bw, ldl,
-                    (B % 4 == 0) ? 1 : 0, aligned_b ? 1 : 0, pair_w,
+                    (B % 4 == 0) ? 1 : 0,
                     feed ? w.hist : nullptr, w.below_part, w.cand_n, w.cand, w.st, w.sx, w.sc, rsc, sp};
       launch_update(s, ua, grid);
       THANOS_LAUNCH_CHECK();
@@ -2856,7 +2875,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
       if (pending_join >= 0) THANOS_CHECK(aux.join(pending_join));
       {
         UpdateArgs ua{W, lam_sb, w.P, mask, c, b, sb_start, sb_end, next_end, 0, 0, kk, ldl,
-                      (B % 4 == 0) ? 1 : 0, aligned_b ? 1 : 0, pair_w, nullptr, nullptr, nullptr, nullptr,
+                      (B % 4 == 0) ? 1 : 0, nullptr, nullptr, nullptr, nullptr,
                       nullptr, nullptr, w.sc, rsc, sp};
         dim3 grid((unsigned)ceil_div(next_end - sb_end, kTN), (unsigned)ceil_div(c, kTM));
         launch_update(s, ua, grid);
@@ -2865,7 +2884,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
       if (next_end < b) {  // rest: right of the next super-block, second stream
         THANOS_CHECK(aux.fork((int)(2 * sbi)));
         UpdateArgs ua{W, lam_sb, w.P, mask, c, b, sb_start, next_end, b, 0, 0, kk, ldl,
-                      (B % 4 == 0) ? 1 : 0, aligned_b ? 1 : 0, pair_w, nullptr, nullptr, nullptr, nullptr,
+                      (B % 4 == 0) ? 1 : 0, nullptr, nullptr, nullptr, nullptr,
                       nullptr, nullptr, w.sc, rsc, sp};
         dim3 grid((unsigned)ceil_div(b - next_end, kTN), (unsigned)ceil_div(c, kTM));
         launch_update(aux.stream, ua, grid);

@@ -791,3 +791,32 @@ def test_given_factor_of_any_scale():
     assert i1 == i2 == 0
     np.testing.assert_array_equal(M1, M2)
     np.testing.assert_array_equal(W1, W2 * d[None, :])
+
+
+@pytest.mark.parametrize("c,b,B", [(130, 256, 128), (70, 330, 110), (129, 390, 64)])
+@pytest.mark.parametrize("mode", ["nm", "unstructured"])
+def test_results_anywhere_in_memory(mode, c, b, B):
+    """W_out and mask_out at element-aligned addresses, rows of any length: pairs of values and 16-byte
+    pieces are fetched unaligned.  Equal bits to a call with aligned buffers, nothing written around."""
+    import torch
+    import paper_2504_05346_amd as th
+    W, H32 = _layer(c, b, 2 * b, "f32", seed=b)
+    o = th.PruneOpts(mode=th.THANOS_NM if mode == "nm" else th.THANOS_UNSTRUCTURED, sparsity=0.5, n=1, m=2,
+                     block_size=B, damping=0.01, outlier_fraction=0.1 if mode == "nm" else 0.0)
+    Wd, Hd = torch.from_numpy(W).cuda(), torch.from_numpy(H32).cuda()
+    ws = torch.empty((th.thanos_prune_workspace_bytes(c, b, o),), dtype=torch.uint8, device="cuda")
+    info = torch.zeros((1,), dtype=torch.int32, device="cuda")
+    got = []
+    for off in (0, 1, 3):
+        buf = torch.full((c * b + 8,), 7.5, device="cuda")
+        mb = torch.full((c * b + 8,), 9, dtype=torch.uint8, device="cuda")
+        out, mask = buf[off:off + c * b].view(c, b), mb[off:off + c * b].view(c, b)
+        th.thanos_prune_layer(Wd, Hd, o, out, None, mask, ws, info)
+        torch.cuda.synchronize()
+        assert int(info.item()) == 0
+        got.append((out.cpu().numpy(), mask.cpu().numpy()))
+        for t, v in ((buf, 7.5), (mb, 9)):
+            assert bool((t[:off] == v).all()) and bool((t[off + c * b:] == v).all())
+    for w, m in got[1:]:
+        np.testing.assert_array_equal(w, got[0][0])
+        np.testing.assert_array_equal(m, got[0][1])
