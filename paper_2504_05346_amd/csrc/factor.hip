@@ -90,38 +90,45 @@ __device__ __forceinline__ void raise_bound(float* bound, float m) {
 }
 
 // A'[i][j] = (D H_d D)[b-1-i][b-1-j] for i >= j (read from the lower triangle of H as
-// H[b-1-j][b-1-i]); identity on the padding; zero above the diagonal.  32x32 tiles through
-// LDS so that both the read of H and the write of A' are coalesced.
+// H[b-1-j][b-1-i]); identity on the padding; zero above the diagonal of a diagonal block (what lies right
+// of it is never read, and stays as it is).  64x64 tiles through LDS so that both the read of H and the write
+// of A' are coalesced, sixteen loads per thread in flight: 11008 columns 270 -> 135 us (before: 32x32 tiles, zeros in
+// the whole upper triangle).
+constexpr int kRpT = 64;
 __global__ __launch_bounds__(256) void k_reverse_pad(const float* __restrict__ H, int64_t b,
                                                      const float* __restrict__ lam_p,
                                                      const float* __restrict__ d, float* __restrict__ Ap,
                                                      int64_t bp) {
-  __shared__ float t[32][33];
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
-  const int64_t i0 = (int64_t)blockIdx.y * 32, j0 = (int64_t)blockIdx.x * 32;
-  if (j0 > i0 + 31) {  // tile entirely above the diagonal
-    for (int r = ty; r < 32; r += 8) Ap[(i0 + r) * bp + j0 + tx] = 0.f;
-    return;
-  }
+  __shared__ float t[kRpT][kRpT + 1];
+  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;  // 64 x 4
+  const int64_t i0 = (int64_t)blockIdx.y * kRpT, j0 = (int64_t)blockIdx.x * kRpT;
+  if (j0 >= (i0 / NB + 1) * NB) return;
   // A'[i0+r][j0+cidx] = H[b-1-(j0+cidx)][b-1-(i0+r)]: source rows are indexed by cidx,
   // source columns by r.  Load with lanes along r (source columns, contiguous, descending).
-  for (int cc = ty; cc < 32; cc += 8) {
-    const int64_t sr = b - 1 - (j0 + cc);
-    const int64_t sc = b - 1 - (i0 + tx);
-    float v = 0.f;
-    if (sr >= 0 && sc >= 0 && sr < b && sc < b && sr >= sc) v = H[sr * b + sc];
-    t[cc][tx] = v;  // t[cidx][r]
+  const int64_t sc = b - 1 - (i0 + tx);
+  float v[kRpT / 4];
+#pragma unroll
+  for (int e = 0; e < kRpT / 4; ++e) {
+    const int64_t sr = b - 1 - (j0 + ty + 4 * e);
+    v[e] = H[max(sr, (int64_t)0) * b + max(sc, (int64_t)0)];
+  }
+#pragma unroll
+  for (int e = 0; e < kRpT / 4; ++e) {
+    const int64_t sr = b - 1 - (j0 + ty + 4 * e);
+    t[ty + 4 * e][tx] = (sc >= 0 && sr >= sc) ? v[e] : 0.f;  // t[cidx][r]; only the lower triangle is valid
   }
   __syncthreads();
   const float lam = *lam_p;
-  const float dj = d[max(b - 1 - (j0 + tx), (int64_t)0)];
-  for (int r = ty; r < 32; r += 8) {
-    const int64_t i = i0 + r, j = j0 + tx;
-    float v;
-    if (j > i) v = 0.f;
-    else if (i >= b) v = (i == j) ? 1.f : 0.f;
-    else v = (t[tx][r] + ((i == j) ? lam : 0.f)) * (d[b - 1 - i] * dj);
-    Ap[i * bp + j] = v;
+  const int64_t j = j0 + tx;
+  const float dj = d[max(b - 1 - j, (int64_t)0)];
+#pragma unroll 4
+  for (int r = ty; r < kRpT; r += 4) {
+    const int64_t i = i0 + r;
+    float o;
+    if (j > i) o = 0.f;
+    else if (i >= b) o = (i == j) ? 1.f : 0.f;
+    else o = (t[tx][r] + ((i == j) ? lam : 0.f)) * (d[b - 1 - i] * dj);
+    Ap[i * bp + j] = o;
   }
 }
 
@@ -513,7 +520,7 @@ thanos_status factor_begin(hipStream_t s, const float* H, int64_t b, float dampi
   hipLaunchKernelGGL(k_diag_stats, dim3(1), dim3(1024), 0, s, H, b, damping, xnorm2, lam, d, d + bp,
                      n_bounds(nb) + (int)bp, info);
   THANOS_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_reverse_pad, dim3((unsigned)(bp / 32), (unsigned)(bp / 32)), dim3(256), 0,
+  hipLaunchKernelGGL(k_reverse_pad, dim3((unsigned)(bp / kRpT), (unsigned)(bp / kRpT)), dim3(256), 0,
                      s, H, b, lam, d, Ap, bp);
   THANOS_LAUNCH_CHECK();
   return THANOS_OK;
