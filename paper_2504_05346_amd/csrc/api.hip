@@ -384,7 +384,8 @@ static thanos_status prune_with_workspace(const void* W_in, thanos_dtype wdt, in
       THANOS_CHECK(prep.record(1));
       prepared = true;
     }
-    thanos_status st = factor(s, H, b, opts->damping, Uw, xw, p, info_dev, single_stream, beside);
+    thanos_status st = factor(s, H, b, opts->damping, Uw, xw, p, info_dev, single_stream, beside,
+                              prepared && n_out > 0);
     if (st != THANOS_OK) return st;
     if (prepared) THANOS_CHECK(prep.join(1));
     U = Uw;

@@ -282,7 +282,8 @@ thanos_status gemm_f32(hipStream_t s, bool a_kmajor, bool b_kmajor, int64_t M, i
 // the bound of B is read from the device instead).  The same precision in half of the matrix instructions.
 thanos_status gemm_bounded(hipStream_t s, int64_t M, int64_t N, int64_t K, float alpha, const float* A,
                            int64_t lda, float bound_a, const float* B, int64_t ldb, float bound_b,
-                           const float* bound_b_dev, float beta, float* C, int64_t ldc, bool lower_only);
+                           const float* bound_b_dev, float beta, float* C, int64_t ldc, bool lower_only,
+                           bool company = false);
 
 thanos_status syrk_accumulate(hipStream_t s, float* H, int64_t b, const void* Xc,
                               thanos_dtype xdt, int64_t n_tok, int64_t ldx, float alpha);
@@ -291,10 +292,11 @@ thanos_status syrk_accumulate(hipStream_t s, float* H, int64_t b, const void* Xc
 // in the workspace holds the Cholesky factor L of J D H_d D J, D diagonal with powers of two
 // (U = J L^{-1} J D): factor_L() returns it and its leading dimension, factor_scale() the diagonal of D.
 size_t factor_workspace_bytes(int64_t b);
+// company: a product with gemm_f32(.., beside) runs at the same time on another stream.
 // single_stream: no helper streams, everything on `s` in enqueue order (nothing is created).
 thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, float* U,
                      float* xnorm2, void* ws, int32_t* info, bool single_stream = false,
-                     bool begun = false);
+                     bool begun = false, bool company = false);
 // Its first two launches (diagonal, damped copy), which is all of it that reads H; factor(..., begun =
 // true) goes on from there.
 thanos_status factor_begin(hipStream_t s, const float* H, int64_t b, float damping, float* xnorm2,

@@ -414,6 +414,7 @@ __device__ __forceinline__ void write_tile_bound(const TileAcc& acc, char* smem,
   raise_bound(bound, x3_write_tile(acc, smem, C, ldc, scale));
 }
 
+template <int NBUF>
 __global__ __launch_bounds__(kXThreads, 4) void k_trinv_T(TrinvArgs a) {
   extern __shared__ __attribute__((aligned(16))) char sm[];
   const int tj = a.c0 + blockIdx.x, ti = blockIdx.y, p = a.p0 + blockIdx.z;
@@ -425,11 +426,12 @@ __global__ __launch_bounds__(kXThreads, 4) void k_trinv_T(TrinvArgs a) {
   TileAcc acc;
   acc_zero(acc);
   const float sa = h2_scale(kBoundL), sb = h2_scale(a.bound_inv[gj]);
-  gemm_tile_h2<false, true, 1>(acc, sm, A, a.bp, NB, sa, nullptr, B, a.bp, NB, sb, nullptr, tj * NB, a.S * NB, true, true);
+  gemm_tile_h2<false, true, NBUF>(acc, sm, A, a.bp, NB, sa, nullptr, B, a.bp, NB, sb, nullptr, tj * NB, a.S * NB, true, true);
   write_tile_bound(acc, sm, a.T + ((int64_t)gi * NB) * a.bp + (int64_t)gj * NB, a.bp,
                    (1.f / sa) * (1.f / sb), a.bound_T + gj);
 }
 
+template <int NBUF>
 __global__ __launch_bounds__(kXThreads, 4) void k_trinv_X(TrinvArgs a) {
   extern __shared__ __attribute__((aligned(16))) char sm[];
   const int tj = a.c0 + blockIdx.x, ti = blockIdx.y, p = a.p0 + blockIdx.z;
@@ -444,7 +446,7 @@ __global__ __launch_bounds__(kXThreads, 4) void k_trinv_X(TrinvArgs a) {
   for (int e = threadIdx.x & 63; e <= ti; e += 64) ba = max(ba, __float_as_uint(a.bound_inv[base + a.S + e]));
   for (int off = 32; off > 0; off >>= 1) ba = max(ba, (uint32_t)__shfl_xor((int)ba, off, 64));
   const float sa = h2_scale(__uint_as_float(ba)), sb = h2_scale(a.bound_T[gj]);
-  gemm_tile_h2<false, true, 1>(acc, sm, A, a.bp, NB, sa, nullptr, B, a.bp, NB, sb, nullptr, 0, (ti + 1) * NB, true, true);
+  gemm_tile_h2<false, true, NBUF>(acc, sm, A, a.bp, NB, sa, nullptr, B, a.bp, NB, sb, nullptr, 0, (ti + 1) * NB, true, true);
   write_tile_bound(acc, sm, a.Linv + ((int64_t)gi * NB) * a.bp + (int64_t)gj * NB, a.bp,
                    -(1.f / sa) * (1.f / sb), a.bound_inv + gj);
 }
@@ -527,7 +529,8 @@ thanos_status factor_begin(hipStream_t s, const float* H, int64_t b, float dampi
 }
 
 thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, float* U,
-                     float* xnorm2, void* ws, int32_t* info, bool single_stream, bool begun) {
+                     float* xnorm2, void* ws, int32_t* info, bool single_stream, bool begun,
+                     bool company) {
   const int64_t bp = padded(b);
   const int nb = (int)(bp / NB);
   float* Ap = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + 256);
@@ -562,12 +565,11 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
   // dependencies); they fill the compute units that the chain of diagonal blocks leaves idle.
   // Regions written by different merges are disjoint, and none overlaps what the
   // factorisation still writes.
-  THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_trinv_T),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)kXSmemBytes));
-  THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_trinv_X),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)kXSmemBytes));
+  auto* const kern_T = company ? k_trinv_T<1> : k_trinv_T<2>;
+  auto* const kern_X = company ? k_trinv_X<1> : k_trinv_X<2>;
+  const size_t tri_smem = company ? kXSmemBytes : kH2SmemBytes;
+  for (const void* k : {reinterpret_cast<const void*>(kern_T), reinterpret_cast<const void*>(kern_X)})
+    THANOS_HIP_CHECK(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)tri_smem));
   AuxStream tri(s, n_outer > 1 ? n_outer + 1 : 0, single_stream);
   if (!tri.ok) return THANOS_ERR_HIP;
   int tri_done = -1;  // blocks 0..tri_done have been handed to the inversion
@@ -614,9 +616,9 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
           TrinvArgs a{Ap, Linv, Tb, bp, nb, S, p_lo, c0, bound_inv, bound_inv + (1 + level) * nb};
           dim3 grid((unsigned)std::min(cols, S - c0), (unsigned)rows_all, (unsigned)np);
           if (second)
-            hipLaunchKernelGGL(k_trinv_X, grid, dim3(kXThreads), kXSmemBytes, ts, a);
+            hipLaunchKernelGGL(kern_X, grid, dim3(kXThreads), tri_smem, ts, a);
           else
-            hipLaunchKernelGGL(k_trinv_T, grid, dim3(kXThreads), kXSmemBytes, ts, a);
+            hipLaunchKernelGGL(kern_T, grid, dim3(kXThreads), tri_smem, ts, a);
           THANOS_LAUNCH_CHECK();
         }
       }
@@ -639,7 +641,7 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
     const float* dinv = Linv + ((int64_t)k * NB) * bp + (int64_t)k * NB;
     // L_ik = A_ik * Linv_kk^T  (in place, all rows below the diagonal block)
     thanos_status st = gemm_bounded(s, rem, NB, NB, 1.f, panel, bp, kBoundA, dinv, bp, 0.f, bound_inv + k,
-                                    0.f, panel, bp, false);
+                                    0.f, panel, bp, false, company);
     if (st != THANOS_OK) return st;
     if ((k + 1) % kOuter == 0) {
       st = trinv_upto(k);
@@ -653,7 +655,7 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
     if (ncols > 0) {
       float* trail = Ap + ((int64_t)(k + 1) * NB) * bp + (int64_t)(k + 1) * NB;
       st = gemm_bounded(s, rem, ncols, NB, -1.f, panel, bp, kBoundL, panel, bp, kBoundL, nullptr, 1.f, trail,
-                        bp, true);
+                        bp, true, company);
       if (st != THANOS_OK) return st;
     }
     // wide: after the last step of an outer block, everything right of it
@@ -672,7 +674,7 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
         const int64_t cols = (int64_t)(next_end - ob_end) * NB;
         float* cs = Ap + ((int64_t)ob_end * NB) * bp + (int64_t)ob_end * NB;
         st = gemm_bounded(s, rows, cols, kk, -1.f, lp, bp, kBoundL, lp, bp, kBoundL, nullptr, 1.f, cs, bp,
-                          true);
+                          true, company);
         if (st != THANOS_OK) return st;
       }
       // fork: the rest (rows and columns >= next_end) on the second stream, next to the
@@ -684,7 +686,7 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
         const float* lr = lp + ((int64_t)(next_end - ob_end) * NB) * bp;
         float* cr = Ap + ((int64_t)next_end * NB) * bp + (int64_t)next_end * NB;
         st = gemm_bounded(aux.stream, rest, rest, kk, -1.f, lr, bp, kBoundL, lr, bp, kBoundL, nullptr, 1.f, cr,
-                          bp, true);
+                          bp, true, company);
         if (st != THANOS_OK) return st;
         THANOS_CHECK(aux.record(2 * ob + 1));
         pending_join = 2 * ob + 1;

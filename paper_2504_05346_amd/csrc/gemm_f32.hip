@@ -21,7 +21,8 @@ struct GemmArgs {
   const float* bound_b;  // ... of B from a bound on the device instead, unless nullptr
 };
 
-template <bool AK, bool BK, bool H2 = false>
+// NBUF: two-way split with that many LDS buffers (0: three-way)
+template <bool AK, bool BK, int NBUF = 0>
 __global__ __launch_bounds__(kXThreads, 4) void k_gemm_f32(GemmArgs g) {
   extern __shared__ __attribute__((aligned(16))) char sm[];
   // Triangular op(B): tiles differ in the length of their reduction, and the longest go first (a
@@ -39,9 +40,9 @@ __global__ __launch_bounds__(kXThreads, 4) void k_gemm_f32(GemmArgs g) {
   acc_zero(acc);
   const int kbeg = g.b_tri == kTriLower ? n0 : 0;
   const int kend = g.b_tri == kTriUpper ? min(g.K, n0 + kTN) : g.K;
-  if constexpr (H2) {
+  if constexpr (NBUF > 0) {
     const float sb = g.bound_b ? h2_scale(*g.bound_b) : g.sb;
-    gemm_tile_h2<AK, BK, 1>(acc, sm, A, g.lda, m_ext, g.sa, nullptr, B, g.ldb, n_ext, sb, nullptr, kbeg, kend, true,
+    gemm_tile_h2<AK, BK, NBUF>(acc, sm, A, g.lda, m_ext, g.sa, nullptr, B, g.ldb, n_ext, sb, nullptr, kbeg, kend, true,
                          true);
     g.alpha *= (1.f / g.sa) * (1.f / sb);
   } else {
@@ -185,16 +186,19 @@ static thanos_status launch_direct(hipStream_t s, const GemmArgs& g) {
 
 thanos_status gemm_bounded(hipStream_t s, int64_t M, int64_t N, int64_t K, float alpha, const float* A,
                            int64_t lda, float bound_a, const float* B, int64_t ldb, float bound_b,
-                           const float* bound_b_dev, float beta, float* C, int64_t ldc, bool lower_only) {
+                           const float* bound_b_dev, float beta, float* C, int64_t ldc, bool lower_only,
+                           bool company) {
   if (M <= 0 || N <= 0) return THANOS_OK;
   GemmArgs g{A, B, C, lda, ldb, ldc, (int)M, (int)N, (int)K, alpha, beta, lower_only ? 1 : 0,
              vec_ok(A, lda) ? 1 : 0, vec_ok(B, ldb) ? 1 : 0, kTriNone,
              h2_scale(bound_a), h2_scale(bound_b), bound_b_dev};
   if (direct_ok(g)) return launch_direct<true>(s, g);
-  THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_f32<false, false, true>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kXSmemBytes));
-  hipLaunchKernelGGL((k_gemm_f32<false, false, true>), dim3((unsigned)ceil_div(N, kTN), (unsigned)ceil_div(M, kTM)),
-                     dim3(kXThreads), kXSmemBytes, s, g);
+  // two buffers unless the workgroup has to fit beside a larger one
+  auto* const kern = company ? k_gemm_f32<false, false, 1> : k_gemm_f32<false, false, 2>;
+  const size_t smem = company ? kXSmemBytes : kH2SmemBytes;
+  THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+  hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div(N, kTN), (unsigned)ceil_div(M, kTM)), dim3(kXThreads), smem, s, g);
   THANOS_LAUNCH_CHECK();
   return THANOS_OK;
 }

@@ -20,9 +20,9 @@
 // workgroups per compute unit); four planes instead of six in LDS, 5 instead of 11 vector instructions
 // per pair of values.  A slab is 40 KB, so two buffers and two workgroups fill the LDS exactly, and the
 // splitting can run one slab ahead of the multiplying with one barrier per slab (NBUF = 2): 10752^2 at
-// K = 512 221 -> 238 TFLOP/s, 16384^2 at K = 128 126 -> 139, 8192^2 at K = 4096 305 -> 312.  One buffer and
-// two barriers where a workgroup has to fit beside one that takes 84 KB (the factorisation next to the
-// row losses: 5120 columns 5.23 against 5.40 ms).
+// K = 512 221 -> 238 TFLOP/s, 16384^2 at K = 128 126 -> 139, 8192^2 at K = 4096 305 -> 312, the factorisation
+// of 11008 columns 7.01 -> 6.74 ms.  One buffer and two barriers where a workgroup has to fit beside one that
+// takes 84 KB (the factorisation next to the row losses: 5120 columns 5.23 against 5.40 ms).
 #pragma once
 #include "gemm_tile_x3.h"
 
