@@ -32,6 +32,72 @@ namespace thanos {
   } while (0)
 
 // ------------------------------------------------------------------------------------------
+// Inverses of the blocks' G matrices, for rows that lose more than half of a block.
+// With G = P_k[:, :bw] = U_bb^T U_bb (U_bb the diagonal block of the factor), K = G^{-1} =
+// V_bb V_bb^T, where V = U^{-1} is the reverse Cholesky factor the factorisation leaves behind
+// (V[x][y] = L[b-1-x][b-1-y], L = its workspace's lower factor of the index-reversed matrix), and
+// the diagonal block of the inverse of a triangular matrix is the inverse of its diagonal block:
+// no inversion is computed.  Kc[blk][a][j] = sum_{m >= max(a, j)} V[j1+a][j1+m] V[j1+j][j1+m],
+// row stride B.  One workgroup per 32 x 32 tile (a0, c0) of a block, in the launch of k_block_rows, beside
+// which it takes no time of its own (in a launch of its own 11 us: 512x512 layer 434 -> 422 us).  L is the factor of a scaled matrix: row
+// b-1-x of it is d[x] times that of the matrix itself; Kc is in the scaled coordinates of the sweep.
+struct CompArgs {
+  const float* L;  // nullptr: none wanted
+  int64_t ldL;
+  const float* d;
+  float* Kc;
+  int nt, nz;      // tiles of 32 per side of a block; blockIdx.z from nz on
+};
+__device__ __forceinline__ void comp_tile(const CompArgs& a, const float* __restrict__ sc, int64_t b, int B,
+                                          int64_t blk, int a0, int c0, char* sm) {
+  float (*Va)[33] = reinterpret_cast<float (*)[33]>(sm);
+  float (*Vj)[33] = Va + 32;
+  const int64_t j1 = blk * B;
+  const int bw = (int)min((int64_t)B, b - j1);
+  if (a0 >= bw || c0 >= bw) return;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // ty 0..15
+  float acc[2] = {0.f, 0.f};
+  // block-local indices, zero outside the upper triangle; loads from clamped addresses, a tile ahead
+  auto at = [&](int x, int y) {
+    return a.L[(b - 1 - (j1 + min(x, bw - 1))) * a.ldL + (b - 1 - (j1 + max(min(y, bw - 1), min(x, bw - 1))))];
+  };
+  auto V = [&](float v, int x, int y) { return (x >= bw || y >= bw || y < x) ? 0.f : v; };
+  float va[2], vj[2];
+  auto load = [&](int m0) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      va[e] = at(a0 + ty + 16 * e, m0 + tx);
+      vj[e] = at(c0 + ty + 16 * e, m0 + tx);
+    }
+  };
+  int m0 = max(a0, c0);
+  load(m0);
+  for (; m0 < bw; m0 += 32) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      Va[ty + 16 * e][tx] = V(va[e], a0 + ty + 16 * e, m0 + tx);
+      Vj[ty + 16 * e][tx] = V(vj[e], c0 + ty + 16 * e, m0 + tx);
+    }
+    if (m0 + 32 < bw) load(m0 + 32);
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      float t = acc[e];
+#pragma unroll
+      for (int m = 0; m < 32; ++m) t = fmaf(Va[ty + 16 * e][m], Vj[tx][m], t);
+      acc[e] = t;
+    }
+    __syncthreads();
+  }
+  float* out = a.Kc + blk * B * B;
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const int x = a0 + ty + 16 * e, y = c0 + tx;
+    if (x < bw && y < bw) out[(int64_t)x * B + y] = acc[e] / (a.d[j1 + x] * sc[j1 + x]) / (a.d[j1 + y] * sc[j1 + y]);
+  }
+}
+
+// ------------------------------------------------------------------------------------------
 // P[(j1+m)*b + col] = sc[j1+m] sc[col] sum_k U[j1+k][j1+m] * U[j1+k][col], col in [j1, b), for every block.
 struct BlockRowsArgs {
   const float* U;
@@ -39,11 +105,18 @@ struct BlockRowsArgs {
   const float* sc;
   int64_t b;
   int B;
+  CompArgs comp;
 };
 
 constexpr size_t kBlockRowsSmem = kXSmemBytes + kTM * sizeof(float);
 __global__ __launch_bounds__(kXThreads, 4) void k_block_rows(BlockRowsArgs a) {
   extern __shared__ __attribute__((aligned(16))) char sm[];
+  if (a.comp.L && (int)blockIdx.z >= a.comp.nz) {
+    const int t = ((int)blockIdx.z - a.comp.nz) * (int)gridDim.x + (int)blockIdx.x;
+    if (t < a.comp.nt * a.comp.nt)
+      comp_tile(a.comp, a.sc, a.b, a.B, blockIdx.y, 32 * (t / a.comp.nt), 32 * (t % a.comp.nt), sm);
+    return;
+  }
   const int64_t j1 = (int64_t)blockIdx.y * a.B;
   const int bw = (int)min((int64_t)a.B, a.b - j1);
   const int64_t col0 = j1 + (int64_t)blockIdx.x * kTN;
@@ -99,54 +172,6 @@ __global__ __launch_bounds__(1024) void k_col_scales(const float* __restrict__ U
   if (ty != 0 || j >= b) return;
   for (int e = 1; e < 16; ++e) top = fmaxf(top, part[e][tx]);
   sc[j] = col_scale(top);
-}
-
-// ------------------------------------------------------------------------------------------
-// Inverses of the blocks' G matrices, for rows that lose more than half of a block.
-// With G = P_k[:, :bw] = U_bb^T U_bb (U_bb the diagonal block of the factor), K = G^{-1} =
-// V_bb V_bb^T, where V = U^{-1} is the reverse Cholesky factor the factorisation leaves behind
-// (V[x][y] = L[b-1-x][b-1-y], L = its workspace's lower factor of the index-reversed matrix), and
-// the diagonal block of the inverse of a triangular matrix is the inverse of its diagonal block:
-// no inversion is computed.  Kc[blk][a][j] = sum_{m >= max(a, j)} V[j1+a][j1+m] V[j1+j][j1+m],
-// row stride B.  One workgroup per 32 x 32 tile of a block.  L is the factor of a scaled matrix: row
-// b-1-x of it is d[x] times that of the matrix itself; Kc is in the scaled coordinates of the sweep.
-__global__ __launch_bounds__(256) void k_comp_blocks(const float* __restrict__ L, int64_t ldL,
-                                                     const float* __restrict__ d,
-                                                     const float* __restrict__ sc, int64_t b, int B,
-                                                     float* __restrict__ Kc) {
-  __shared__ float Va[32][33], Vj[32][33];
-  const int64_t j1 = (int64_t)blockIdx.z * B;
-  const int bw = (int)min((int64_t)B, b - j1);
-  const int a0 = 32 * blockIdx.y, c0 = 32 * blockIdx.x;
-  if (a0 >= bw || c0 >= bw) return;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // ty 0..7
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  auto V = [&](int x, int y) -> float {  // block-local indices, zero outside the upper triangle
-    if (x >= bw || y >= bw || y < x) return 0.f;
-    return L[(b - 1 - (j1 + x)) * ldL + (b - 1 - (j1 + y))];
-  };
-  for (int m0 = (max(a0, c0) / 32) * 32; m0 < bw; m0 += 32) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      Va[ty + 8 * e][tx] = V(a0 + ty + 8 * e, m0 + tx);
-      Vj[ty + 8 * e][tx] = V(c0 + ty + 8 * e, m0 + tx);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      float t = acc[e];
-#pragma unroll
-      for (int m = 0; m < 32; ++m) t = fmaf(Va[ty + 8 * e][m], Vj[tx][m], t);
-      acc[e] = t;
-    }
-    __syncthreads();
-  }
-  float* out = Kc + (int64_t)blockIdx.z * B * B;
-#pragma unroll
-  for (int e = 0; e < 4; ++e)
-    if (a0 + ty + 8 * e < bw && c0 + tx < bw)
-      out[(int64_t)(a0 + ty + 8 * e) * B + c0 + tx] =
-          acc[e] / (d[j1 + a0 + ty + 8 * e] * sc[j1 + a0 + ty + 8 * e]) / (d[j1 + c0 + tx] * sc[j1 + c0 + tx]);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2458,7 +2483,7 @@ static void launch_update(hipStream_t s, UpdateArgs ua, dim3 tiles) {
 }
 
 // Whether rows that lose more than half of a block are solved through K = G^{-1} (see
-// k_comp_blocks, k_solve_tiled): only the tiled solver does it (blocks wider than 128 columns),
+// comp_tile, k_solve_tiled): only the tiled solver does it (blocks wider than 128 columns),
 // the blocks' K come from the factor of the same call (not available with a given factor), the
 // matrix-vector products read K in aligned groups of four columns, and n:m patterns that remove
 // at most half of every group never need it.
@@ -2716,8 +2741,13 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
   }
 
   {
-    BlockRowsArgs a{U, w.P, w.sc, b, B};
     dim3 grid((unsigned)ceil_div(b, kTN), (unsigned)ceil_div(b, B), (unsigned)ceil_div(B, kTM));
+    BlockRowsArgs a{U, w.P, w.sc, b, B, {nullptr, 0, nullptr, nullptr, 0, 0}};
+    if (comp) {
+      const int nt = (int)ceil_div(B, 32);
+      a.comp = {Lfac, ldL, Ldiag, w.Kc, nt, (int)grid.z};
+      grid.z += (unsigned)ceil_div((int64_t)nt * nt, grid.x);
+    }
     THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_block_rows),
                                          hipFuncAttributeMaxDynamicSharedMemorySize,
                                          (int)kBlockRowsSmem));
@@ -2725,12 +2755,6 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
       THANOS_HIP_CHECK(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kUpdSmemBytes));
     hipLaunchKernelGGL(k_block_rows, grid, dim3(kXThreads), kBlockRowsSmem, s, a);
     THANOS_LAUNCH_CHECK();
-    if (comp) {
-      const unsigned nt32 = (unsigned)ceil_div(B, 32);
-      hipLaunchKernelGGL(k_comp_blocks, dim3(nt32, nt32, (unsigned)ceil_div(b, B)), dim3(256), 0, s,
-                         Lfac, ldL, Ldiag, w.sc, b, B, w.Kc);
-      THANOS_LAUNCH_CHECK();
-    }
   }
 
   const int super = unstructured ? 1 : kSuper;   // the global residual mask needs current weights
