@@ -405,8 +405,12 @@ struct TrinvArgs {
   int p0, c0;  // this launch: pairs from p0 (blockIdx.z), tile columns of a pair from c0 (blockIdx.x)
   // Largest magnitudes by block column, nb each: of L^{-1} so far, of Tbuf at this level.  A launch reads
   // what earlier launches of its stream have left and raises others: equal calls give equal bits.
-  float *bound_inv, *bound_T;
+  // What the lowest level leaves has an array of its own: its workgroups read the others' block.
+  float *bound_inv, *bound_T, *bound_first;
 };
+__device__ __forceinline__ uint32_t inv_bound(const TrinvArgs& a, int j) {
+  return max(__float_as_uint(a.bound_inv[j]), __float_as_uint(a.bound_first[j]));
+}
 
 // Whole tile: C = scale * acc, and its largest magnitude into *bound.
 __device__ __forceinline__ void write_tile_bound(const TileAcc& acc, char* smem, float* C, int64_t ldc,
@@ -425,7 +429,7 @@ __global__ __launch_bounds__(kXThreads, 4) void k_trinv_T(TrinvArgs a) {
   const float* B = a.Linv + ((int64_t)base * NB) * a.bp + (int64_t)gj * NB;  // [k][n]
   TileAcc acc;
   acc_zero(acc);
-  const float sa = h2_scale(kBoundL), sb = h2_scale(a.bound_inv[gj]);
+  const float sa = h2_scale(kBoundL), sb = h2_scale(__uint_as_float(inv_bound(a, gj)));
   gemm_tile_h2<false, true, NBUF>(acc, sm, A, a.bp, NB, sa, nullptr, B, a.bp, NB, sb, nullptr, tj * NB, a.S * NB, true, true);
   write_tile_bound(acc, sm, a.T + ((int64_t)gi * NB) * a.bp + (int64_t)gj * NB, a.bp,
                    (1.f / sa) * (1.f / sb), a.bound_T + gj);
@@ -443,12 +447,76 @@ __global__ __launch_bounds__(kXThreads, 4) void k_trinv_X(TrinvArgs a) {
   TileAcc acc;
   acc_zero(acc);
   uint32_t ba = 0;  // bound of the part of Linv22 that this tile row reads
-  for (int e = threadIdx.x & 63; e <= ti; e += 64) ba = max(ba, __float_as_uint(a.bound_inv[base + a.S + e]));
+  for (int e = threadIdx.x & 63; e <= ti; e += 64) ba = max(ba, inv_bound(a, base + a.S + e));
   for (int off = 32; off > 0; off >>= 1) ba = max(ba, (uint32_t)__shfl_xor((int)ba, off, 64));
   const float sa = h2_scale(__uint_as_float(ba)), sb = h2_scale(a.bound_T[gj]);
   gemm_tile_h2<false, true, NBUF>(acc, sm, A, a.bp, NB, sa, nullptr, B, a.bp, NB, sb, nullptr, 0, (ti + 1) * NB, true, true);
   write_tile_bound(acc, sm, a.Linv + ((int64_t)gi * NB) * a.bp + (int64_t)gj * NB, a.bp,
                    -(1.f / sa) * (1.f / sb), a.bound_inv + gj);
+}
+
+// The lowest level (S = 1) in one launch: Linv21 = -Linv22 (L21 Linv11) for 128x128 blocks, of which each
+// product by itself is mostly launch and latency.  A workgroup owns 32 columns of a pair, a wavefront 32
+// rows: operands straight into the registers of the MFMAs as in k_gemm_direct, split there; the strip of
+// L21 Linv11 is in the layout of a second operand as it leaves the first product, and goes round through
+// LDS.  Its bound needs no look at it: rows of L have norms of at most 2, columns of Linv11 at most
+// sqrt(128) times their largest value.  Two launches 15 us, this one 9.
+__global__ __launch_bounds__(256, 2) void k_trinv_first(TrinvArgs a) {
+  __shared__ float strip[4][16][64];
+  const int lane = threadIdx.x & 63, lo = lane & 31, hi = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int gj = 2 * (a.p0 + (int)blockIdx.z), gi = gj + 1, n0 = 32 * blockIdx.x;
+  if (gi >= a.nb) return;
+  const float* L21 = a.L + ((int64_t)gi * NB + 32 * w + lo) * a.bp + (int64_t)gj * NB + 4 * hi;
+  const float* I11 = a.Linv + ((int64_t)gj * NB + 4 * hi) * a.bp + (int64_t)gj * NB + n0 + lo;
+  const float* I22 = a.Linv + ((int64_t)gi * NB + 32 * w + lo) * a.bp + (int64_t)gi * NB + 4 * hi;
+  f32x4 x[16], y[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {  // k = 8 q + 4 hi + c
+    x[q] = *reinterpret_cast<const f32x4*>(L21 + 8 * q);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) y[q][c] = I11[(int64_t)(8 * q + c) * a.bp];
+  }
+  const float bound = a.bound_inv[gj];
+  const float sl = h2_scale(kBoundL), si = h2_scale(bound);
+  f32x16 acc, acc2;
+  auto multiply = [&](float sx, float sy) {  // acc + acc2 = sx sy x y
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = acc2[r] = 0.f;
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      f16x8 a1, a2, b1, b2;
+      split8_h2(x[2 * m], x[2 * m + 1], sx, a1, a2);
+      split8_h2(y[2 * m], y[2 * m + 1], sy, b1, b2);
+      acc2 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, b2, acc2, 0, 0, 0);
+      acc2 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, b1, acc2, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, b1, acc, 0, 0, 0);
+      acc2 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, b2, acc2, 0, 0, 0);
+    }
+  };
+  multiply(sl, si);
+  const float f = pow2_inv(sl) * pow2_inv(si);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) strip[w][r][lane] = f * (acc[r] + acc2[r]);
+#pragma unroll
+  for (int q = 0; q < 16; ++q) x[q] = *reinterpret_cast<const f32x4*>(I22 + 8 * q);
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 16; ++q)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) y[q][c] = strip[q >> 2][4 * (q & 3) + c][lane];
+  const float s2 = h2_scale(a.bound_inv[gi]), st = h2_scale(32.f * bound);
+  multiply(s2, st);
+  const float g = -pow2_inv(s2) * pow2_inv(st);
+  float* out = a.Linv + ((int64_t)gi * NB + 32 * w + 4 * hi) * a.bp + (int64_t)gj * NB + n0 + lo;
+  uint32_t top = 0;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const float v = g * (acc[r] + acc2[r]);
+    out[(int64_t)(8 * (r >> 2) + (r & 3)) * a.bp] = v;
+    top = max(top, __float_as_uint(fabsf(v)));
+  }
+  raise_bound(a.bound_first + gj, __uint_as_float(top));
 }
 
 // U[i][j] = Linv[b-1-i][b-1-j] d[j] for j >= i, else 0, and the largest magnitude of each column.  A thread
@@ -489,7 +557,8 @@ const float* factor_L(const void* ws, int64_t b, int64_t* ld) {
 }
 
 // The scales and the bounds live in the first 128 rows of the inverse's temporary, which no merge writes
-// (its tile rows belong to second halves): bp scales, nb bounds of L^{-1}, nb bounds of Tbuf per level,
+// (its tile rows belong to second halves): bp scales, nb bounds of L^{-1}, nb bounds of Tbuf per level
+// (level 0: of what the lowest merges leave),
 // the largest magnitudes of U's bp columns: at most 10 values per block of 128 columns beside twice 128, and
 // there are 128 x 128.
 static inline float* scales(const void* ws, int64_t bp) {
@@ -538,6 +607,7 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
   float* Tb = Linv + bp * bp;
   const float* d = scales(ws, bp);
   float* bound_inv = scales(ws, bp) + bp;
+  float* bound_first = bound_inv + nb;  // the array of level 0, whose products share a launch
   if (!begun) THANOS_CHECK(factor_begin(s, H, b, damping, xnorm2, ws, info));
 
   // Two-level blocking: inside an outer block of kOuter factor blocks the trailing update of a
@@ -593,7 +663,7 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
     }
     int level = 0;
     for (int S = 1; S < nb; S *= 2, ++level) {
-      for (int second = 0; second < 2; ++second) {
+      for (int second = S == 1 ? 1 : 0; second < 2; ++second) {  // one launch does both products of S = 1
         int p_lo = -1, p_hi = -1;
         for (int p = 0; 2 * p * S + S < nb; ++p) {
           const int e = second ? std::min(2 * p * S + 2 * S, nb) - 1 : 2 * p * S + S - 1;
@@ -604,6 +674,12 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
         }
         if (p_lo < 0) continue;
         const int np = p_hi - p_lo + 1;
+        if (S == 1) {
+          TrinvArgs a{Ap, Linv, Tb, bp, nb, S, p_lo, 0, bound_inv, nullptr, bound_first};
+          hipLaunchKernelGGL(k_trinv_first, dim3(NB / 32, 1, (unsigned)np), dim3(256), 0, ts, a);
+          THANOS_LAUNCH_CHECK();
+          continue;
+        }
         // rows of the second half that exist (the last pair of a level may be cut short)
         const int rows = std::min(S, nb - (2 * p_hi * S + S));
         const int rows_all = np > 1 ? S : rows;
@@ -613,7 +689,7 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
         int cols = S;
         if (kdone != nb - 1) cols = std::max(1, std::min(S, tri_cap / (rows_all * np)));
         for (int c0 = 0; c0 < S; c0 += cols) {
-          TrinvArgs a{Ap, Linv, Tb, bp, nb, S, p_lo, c0, bound_inv, bound_inv + (1 + level) * nb};
+          TrinvArgs a{Ap, Linv, Tb, bp, nb, S, p_lo, c0, bound_inv, bound_inv + (1 + level) * nb, bound_first};
           dim3 grid((unsigned)std::min(cols, S - c0), (unsigned)rows_all, (unsigned)np);
           if (second)
             hipLaunchKernelGGL(kern_X, grid, dim3(kXThreads), tri_smem, ts, a);
