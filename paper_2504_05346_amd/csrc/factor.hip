@@ -638,8 +638,14 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
   auto* const kern_T = company ? k_trinv_T<1> : k_trinv_T<2>;
   auto* const kern_X = company ? k_trinv_X<1> : k_trinv_X<2>;
   const size_t tri_smem = company ? kXSmemBytes : kH2SmemBytes;
-  for (const void* k : {reinterpret_cast<const void*>(kern_T), reinterpret_cast<const void*>(kern_X)})
-    THANOS_HIP_CHECK(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)tri_smem));
+  THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_trinv_T<1>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kXSmemBytes));
+  THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_trinv_X<1>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kXSmemBytes));
+  THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_trinv_T<2>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kH2SmemBytes));
+  THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_trinv_X<2>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kH2SmemBytes));
   AuxStream tri(s, n_outer > 1 ? n_outer + 1 : 0, single_stream);
   if (!tri.ok) return THANOS_ERR_HIP;
   int tri_done = -1;  // blocks 0..tri_done have been handed to the inversion

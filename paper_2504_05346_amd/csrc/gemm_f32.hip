@@ -194,11 +194,16 @@ thanos_status gemm_bounded(hipStream_t s, int64_t M, int64_t N, int64_t K, float
              h2_scale(bound_a), h2_scale(bound_b), bound_b_dev};
   if (direct_ok(g)) return launch_direct<true>(s, g);
   // two buffers unless the workgroup has to fit beside a larger one
-  auto* const kern = company ? k_gemm_f32<false, false, 1> : k_gemm_f32<false, false, 2>;
-  const size_t smem = company ? kXSmemBytes : kH2SmemBytes;
-  THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-  hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div(N, kTN), (unsigned)ceil_div(M, kTM)), dim3(kXThreads), smem, s, g);
+  const dim3 grid((unsigned)ceil_div(N, kTN), (unsigned)ceil_div(M, kTM));
+  if (company) {
+    THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_f32<false, false, 1>),
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)kXSmemBytes));
+    hipLaunchKernelGGL((k_gemm_f32<false, false, 1>), grid, dim3(kXThreads), kXSmemBytes, s, g);
+  } else {
+    THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_f32<false, false, 2>),
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)kH2SmemBytes));
+    hipLaunchKernelGGL((k_gemm_f32<false, false, 2>), grid, dim3(kXThreads), kH2SmemBytes, s, g);
+  }
   THANOS_LAUNCH_CHECK();
   return THANOS_OK;
 }

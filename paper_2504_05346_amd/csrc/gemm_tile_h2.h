@@ -25,6 +25,7 @@
 // takes 84 KB (the factorisation next to the row losses: 5120 columns 5.23 against 5.40 ms).
 #pragma once
 #include "gemm_tile_x3.h"
+#include "split_scale.h"
 
 namespace thanos {
 
@@ -36,30 +37,6 @@ constexpr int kH2Buf = 4 * kXPlane;                 // one slab
 constexpr size_t kH2SmemBytes = 2 * (size_t)kH2Buf;  // half of a compute unit's LDS (NBUF = 1: kXSmemBytes)
 static_assert(kH2SmemBytes >= kXSmemBytes && 2 * kH2SmemBytes <= 160 * 1024, "staged tile fits, two per unit");
 static_assert(kH2Buf <= kXSmemBytes, "one buffer fits where the tile is staged");
-
-// The power of two that brings values of magnitude up to `bound` into [2^14, 2^15); finite for every bound.
-__host__ __device__ inline float h2_scale(float bound) {
-  uint32_t u;
-  __builtin_memcpy(&u, &bound, 4);
-  const int e = (int)((u >> 23) & 255u);                  // biased exponent of the bound
-  const int t = e == 0 ? 254 : 127 + 14 + 127 - e;        // biased exponent of the scale
-  const uint32_t v = (uint32_t)(t < 1 ? 1 : t > 253 ? 253 : t) << 23;
-  float s;
-  __builtin_memcpy(&s, &v, 4);
-  return s;
-}
-
-// The power of two that brings a column whose largest magnitude is m into [1/2, 1); within 2^+-100 for every
-// m (magnitudes of U are: they are 1 / sqrt of what fp32 holds), and 1 for a column of zeros.
-__host__ __device__ inline float col_scale(float m) {
-  uint32_t u;
-  __builtin_memcpy(&u, &m, 4);
-  const int e = (int)((u >> 23) & 255u), t = 253 - e;
-  const uint32_t v = (uint32_t)(e == 0 ? 127 : t < 27 ? 27 : t > 227 ? 227 : t) << 23;
-  float s;
-  __builtin_memcpy(&s, &v, 4);
-  return s;
-}
 
 // 1 / s for a power of two between 2^-126 and 2^126
 __device__ __forceinline__ float pow2_inv(float s) { return __uint_as_float((254u << 23) - __float_as_uint(s)); }

@@ -2751,8 +2751,10 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
     THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_block_rows),
                                          hipFuncAttributeMaxDynamicSharedMemorySize,
                                          (int)kBlockRowsSmem));
-    for (const void* k : {reinterpret_cast<const void*>(k_update<true>), reinterpret_cast<const void*>(k_update<false>)})
-      THANOS_HIP_CHECK(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kUpdSmemBytes));
+    THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_update<true>),
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)kUpdSmemBytes));
+    THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_update<false>),
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)kUpdSmemBytes));
     hipLaunchKernelGGL(k_block_rows, grid, dim3(kXThreads), kBlockRowsSmem, s, a);
     THANOS_LAUNCH_CHECK();
   }

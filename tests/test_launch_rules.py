@@ -198,3 +198,49 @@ def test_shapes_of_the_gpu_tests_reach_every_tile_width(plan):
     from tests.test_gpu_hessian import WIDTHS
     for b, T, width in WIDTHS:
         assert plan(b, T, b % 8 == 0).tile == width, (b, T)
+
+
+def test_row_scales_lie_behind_the_complement_operands(tmp_path_factory):
+    """Unstructured: one block per super-block; the scales of the rows share nothing with the two slices of
+    multipliers or with the operands of the complement products, and fit the buffer."""
+    L = _compile(tmp_path_factory, "rsc", """
+#include "lam_layout.h"
+extern "C" int ok(int64_t c, int64_t B) {
+  for (int64_t sbi = 0; sbi < 3; ++sbi) {
+    const thanos::LamLayout l = thanos::lam_layout(c, B, sbi);
+    const int64_t n = c * B;
+    if (l.rsc < l.lam + n || l.rsc < l.z + n || l.rsc < l.wk + n) return 0;
+    if (l.rsc + c > thanos::lam_buffer_floats(c, B)) return 0;
+  }
+  return 1;
+}
+""")
+    L.ok.argtypes = [ctypes.c_int64] * 2
+    for c, B in ((1, 1), (7, 3), (2560, 256), (8192, 512), (1 << 24, 1)):
+        assert L.ok(c, B) == 1
+
+
+def test_split_scales(tmp_path_factory):
+    """Scales of the two-way split: powers of two with finite inverses for every bound; bounded values
+    times their scale stay below 2^15, columns below 1."""
+    L = _compile(tmp_path_factory, "scales", """
+#include <cstdint>
+#define __host__
+#define __device__
+#include "split_scale.h"
+extern "C" float h2(float x) { return thanos::h2_scale(x); }
+extern "C" float col(float x) { return thanos::col_scale(x); }
+""")
+    for f in (L.h2, L.col):
+        f.argtypes, f.restype = [ctypes.c_float], ctypes.c_float
+    import math
+    for e in range(-149, 128):
+        for x in (math.ldexp(1.0, e), math.ldexp(1.9999, e)):
+            h, c = L.h2(x), L.col(x)
+            assert math.frexp(h)[0] == math.frexp(c)[0] == 0.5
+            assert -126 <= math.frexp(h)[1] - 1 <= 126 and -100 <= math.frexp(c)[1] - 1 <= 100
+            if -112 <= e <= 127:
+                assert 2.0 ** 14 <= x * h <= 2.0 ** 15
+            if -100 <= e <= 98:
+                assert 0.5 <= x * c < 1.0
+    assert L.h2(0.0) == 2.0 ** 126 and L.col(0.0) == 1.0
