@@ -211,6 +211,13 @@ thanos_status thanos_prune_layer_noalloc(const void* W_in, thanos_dtype wdt, int
                                          float* W_out, void* W_out_cast, uint8_t* mask_out,
                                          int32_t* info_dev, void* stream);
 
+/* A stream of the library's pool of helper streams on the current device, for a caller that runs several
+ * calls side by side.  Streams of its own would share hardware queues with those that the calls borrow.
+ * Join the work into another stream before the release: the next borrower's is queued behind it.
+ */
+thanos_status thanos_helper_acquire(void** helper, void** stream);
+void thanos_helper_release(void* helper);
+
 /* Static, NUL-terminated description of a status code (host pointer, never freed). */
 const char* thanos_status_string(thanos_status s);
 

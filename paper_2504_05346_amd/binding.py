@@ -73,6 +73,10 @@ def lib() -> ctypes.CDLL:
     L.thanos_prune_layer_noalloc.restype = ctypes.c_int
     L.thanos_prune_layer_noalloc.argtypes = [vp, ctypes.c_int, i64, i64, vp,
                                              ctypes.POINTER(PruneOpts), vp, vp, vp, vp, vp]
+    L.thanos_helper_acquire.restype = ctypes.c_int
+    L.thanos_helper_acquire.argtypes = [ctypes.POINTER(vp), ctypes.POINTER(vp)]
+    L.thanos_helper_release.restype = None
+    L.thanos_helper_release.argtypes = [vp]
     _lib = L
     return L
 

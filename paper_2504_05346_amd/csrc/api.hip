@@ -34,6 +34,7 @@ namespace {
 struct StreamPool {
   std::mutex mu;
   std::vector<StreamCtx*> idle;
+  int created = 0;
 };
 StreamPool& stream_pool() {
   static StreamPool* p = new StreamPool;  // never destroyed: no HIP call at process exit
@@ -48,15 +49,20 @@ StreamCtx* stream_ctx_acquire(int n_events) {
   {
     StreamPool& pool = stream_pool();
     std::lock_guard<std::mutex> guard(pool.mu);
+    // The oldest idle one, not the one that has waited longest: streams share four hardware queues, dealt out
+    // as the streams are made, and a call's three helpers overlap only on different ones.
+    size_t at = pool.idle.size();
     for (size_t i = 0; i < pool.idle.size(); ++i)
-      if (pool.idle[i]->device == dev) {
-        c = pool.idle[i];
-        pool.idle.erase(pool.idle.begin() + (long)i);
-        break;
-      }
+      if (pool.idle[i]->device == dev && (at == pool.idle.size() || pool.idle[i]->order < pool.idle[at]->order)) at = i;
+    if (at < pool.idle.size()) {
+      c = pool.idle[at];
+      pool.idle.erase(pool.idle.begin() + (long)at);
+    } else {
+      c = new StreamCtx;
+      c->order = pool.created++;
+    }
   }
-  if (!c) {
-    c = new StreamCtx;
+  if (!c->stream) {
     c->device = dev;
     if (hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking) != hipSuccess) {
       delete c;
@@ -254,6 +260,26 @@ static thanos_status check_opts(const thanos_prune_opts* o, int64_t c, int64_t b
 }
 
 extern "C" {
+
+thanos_status thanos_helper_acquire(void** helper, void** stream) {
+  if (!helper || !stream) return THANOS_ERR_INVALID_ARG;
+  StreamCtx* c = nullptr;
+  try {
+    c = stream_ctx_acquire(0);
+  } catch (...) {
+  }
+  if (!c) return THANOS_ERR_HIP;
+  *helper = c;
+  *stream = c->stream;
+  return THANOS_OK;
+}
+
+void thanos_helper_release(void* helper) {
+  try {
+    stream_ctx_release(static_cast<StreamCtx*>(helper));
+  } catch (...) {
+  }
+}
 
 const char* thanos_status_string(thanos_status s) {
   switch (s) {

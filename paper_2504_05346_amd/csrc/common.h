@@ -41,6 +41,7 @@ static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // caller's stream, so the next borrower's work is merely queued behind it.
 struct StreamCtx {
   int device = -1;
+  int order = 0;  // of creation: the pool lends the oldest idle context of a device
   hipStream_t stream = nullptr;
   hipEvent_t* ev = nullptr;
   int nev = 0, cap = 0;

@@ -72,3 +72,29 @@ def test_sweeps_side_by_side_equal_separate_calls(mode, rows):
         np.testing.assert_array_equal(r["mask"].cpu().numpy(), Mg)
         np.testing.assert_array_equal(r["W"].cpu().numpy(), Wg)
         np.testing.assert_array_equal(r["W_cast"].cpu().numpy(), Wg.astype(np.float16))
+
+
+def test_helper_streams_are_lent_oldest_first():
+    """Streams handed back in any order are lent again in the order in which they were made."""
+    import ctypes
+    import paper_2504_05346_amd as th
+    L = th.lib()
+
+    def take(n):
+        out = []
+        for _ in range(n):
+            h, s = ctypes.c_void_p(), ctypes.c_void_p()
+            assert L.thanos_helper_acquire(ctypes.byref(h), ctypes.byref(s)) == 0
+            assert s.value
+            out.append((h.value, s.value))
+        return out
+
+    first = take(4)
+    assert len({s for _, s in first}) == 4
+    for k in (2, 0, 3, 1):
+        L.thanos_helper_release(first[k][0])
+    again = take(4)
+    for h, _ in again:
+        L.thanos_helper_release(h)
+    assert again == first
+    assert L.thanos_helper_acquire(None, None) == 1
