@@ -307,8 +307,8 @@ def main():
         "warmup": args.warmup, "ms_per_step": main_res["ms_per_step"], "higher_is_better": False,
         "scaling": "weak", "vs_baseline": None,
         "dtype": ("f16 in / f32 accumulate (Hessian); factor, block rows and trailing update: "
-                  "f32 storage, products as 3-way split bf16 on the matrix cores (6 bf16 MFMAs "
-                  "per fp32 product); per-row solves f32"),
+                  "f32 storage, products as 2-way split fp16 (3 fp16 MFMAs per fp32 product; block "
+                  "rows: 3-way split bf16, 6 MFMAs); per-row solves f32"),
         "data": "synthetic",
         "config": {"workload": main_res["workload"], "accumulate_calls": args.chunks},
         "phases_ms": main_res["phases_ms"], "kept_fraction": main_res["kept_fraction"],
