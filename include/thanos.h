@@ -205,7 +205,7 @@ size_t thanos_prune_workspace_bytes(int64_t c, int64_t b, const thanos_prune_opt
  * kernels initialise what they read): calls that overlap on one GPU -- from two threads, or on
  * two streams without an ordering between them -- race.  Not re-entrant per device.
  */
-#define THANOS_NOALLOC_SCRATCH_BYTES (65u << 20)
+#define THANOS_NOALLOC_SCRATCH_BYTES (67u << 20)
 thanos_status thanos_prune_layer_noalloc(const void* W_in, thanos_dtype wdt, int64_t c, int64_t b,
                                          const float* H, const thanos_prune_opts* opts /* host */,
                                          float* W_out, void* W_out_cast, uint8_t* mask_out,

@@ -160,7 +160,7 @@ def thanos_prune_layer(W_in: torch.Tensor, H: Optional[torch.Tensor], opts: Prun
     _check(st, "thanos_prune_layer")
 
 
-THANOS_NOALLOC_SCRATCH_BYTES = 65 << 20
+THANOS_NOALLOC_SCRATCH_BYTES = 67 << 20
 
 
 def thanos_prune_layer_noalloc(W_in: torch.Tensor, H: Optional[torch.Tensor], opts: PruneOpts,

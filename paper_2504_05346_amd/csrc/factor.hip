@@ -430,7 +430,7 @@ __global__ __launch_bounds__(kXThreads, 4) void k_trinv_T(TrinvArgs a) {
   TileAcc acc;
   acc_zero(acc);
   const float sa = h2_scale(kBoundL), sb = h2_scale(__uint_as_float(inv_bound(a, gj)));
-  gemm_tile_h2<false, true, NBUF>(acc, sm, A, a.bp, NB, sa, nullptr, B, a.bp, NB, sb, nullptr, tj * NB, a.S * NB, true, true);
+  gemm_tile_h2<false, true, NBUF>(acc, sm, A, a.bp, NB, sa, nullptr, B, a.bp, NB, sb, {}, nullptr, tj * NB, a.S * NB, true, true);
   write_tile_bound(acc, sm, a.T + ((int64_t)gi * NB) * a.bp + (int64_t)gj * NB, a.bp,
                    (1.f / sa) * (1.f / sb), a.bound_T + gj);
 }
@@ -450,7 +450,7 @@ __global__ __launch_bounds__(kXThreads, 4) void k_trinv_X(TrinvArgs a) {
   for (int e = threadIdx.x & 63; e <= ti; e += 64) ba = max(ba, inv_bound(a, base + a.S + e));
   for (int off = 32; off > 0; off >>= 1) ba = max(ba, (uint32_t)__shfl_xor((int)ba, off, 64));
   const float sa = h2_scale(__uint_as_float(ba)), sb = h2_scale(a.bound_T[gj]);
-  gemm_tile_h2<false, true, NBUF>(acc, sm, A, a.bp, NB, sa, nullptr, B, a.bp, NB, sb, nullptr, 0, (ti + 1) * NB, true, true);
+  gemm_tile_h2<false, true, NBUF>(acc, sm, A, a.bp, NB, sa, nullptr, B, a.bp, NB, sb, {}, nullptr, 0, (ti + 1) * NB, true, true);
   write_tile_bound(acc, sm, a.Linv + ((int64_t)gi * NB) * a.bp + (int64_t)gj * NB, a.bp,
                    -(1.f / sa) * (1.f / sb), a.bound_inv + gj);
 }

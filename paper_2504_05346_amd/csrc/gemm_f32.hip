@@ -42,7 +42,7 @@ __global__ __launch_bounds__(kXThreads, 4) void k_gemm_f32(GemmArgs g) {
   const int kend = g.b_tri == kTriUpper ? min(g.K, n0 + kTN) : g.K;
   if constexpr (NBUF > 0) {
     const float sb = g.bound_b ? h2_scale(*g.bound_b) : g.sb;
-    gemm_tile_h2<AK, BK, NBUF>(acc, sm, A, g.lda, m_ext, g.sa, nullptr, B, g.ldb, n_ext, sb, nullptr, kbeg, kend, true,
+    gemm_tile_h2<AK, BK, NBUF>(acc, sm, A, g.lda, m_ext, g.sa, nullptr, B, g.ldb, n_ext, sb, {}, nullptr, kbeg, kend, true,
                          true);
     g.alpha *= (1.f / g.sa) * (1.f / sb);
   } else {

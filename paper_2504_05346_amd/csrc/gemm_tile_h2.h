@@ -64,16 +64,53 @@ __device__ __forceinline__ void split8_h2(const f32x4& x, const f32x4& y, float 
   lo = __builtin_bit_cast(f16x8, l);
 }
 
-// Scale of an operand: one for all of it, or (rows) that times one per row m of the tile.
+// Scales of the columns of B as biased exponents, n rows (>= 1) of them of stride ld: a column takes the
+// smallest.  Read four at a time at any alignment.
+struct ColScalesH2 {
+  const uint8_t* e;
+  int64_t ld;
+  int n;
+};
+// Scale of an operand: one for all of it, or (rows) that times one per row of A or column of B.
 struct ScaleH2 {
   float all;
-  float row[8];  // of the rows of this thread's pieces: (u >> 3) + 16 q, KMAJOR: 4 (u & 31) + 0 .. 3
+  float row[8];  // of this thread's pieces: rows (u >> 3) + 16 q of A, columns 4 (u & 31) + 0 .. 3 of B
+  ColScalesH2 cols;
+  uint32_t first[4];
 };
-template <bool KMAJOR>
 __device__ __forceinline__ void load_rows_h2(ScaleH2& sc, const float* __restrict__ rows, int ext, int u) {
 #pragma unroll
-  for (int q = 0; q < (KMAJOR ? 4 : 8); ++q)
-    sc.row[q] = sc.all * rows[min(KMAJOR ? 4 * (u & 31) + q : (u >> 3) + 16 * q, ext - 1)];
+  for (int q = 0; q < 8; ++q) sc.row[q] = sc.all * rows[min((u >> 3) + 16 * q, ext - 1)];
+}
+// In two steps, so that the requests for the first slab go out in between: the first four rows of exponents are
+// requested, ...
+typedef uint32_t u32u __attribute__((aligned(1)));
+__device__ __forceinline__ void load_cols_h2(ScaleH2& sc, const ColScalesH2& c, int ext4, int u) {
+  sc.cols = c;
+  sc.cols.e += min(4 * (u & 31), ext4 - 4);
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    sc.first[k] = *reinterpret_cast<const u32u*>(sc.cols.e + (int64_t)min(k, c.n - 1) * c.ld);
+}
+// ... and made into scales, with the others if there are more.
+__device__ __forceinline__ void finish_cols_h2(ScaleH2& sc) {
+  uint32_t lo[4] = {253u, 253u, 253u, 253u};
+  auto take = [&](uint32_t v) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) lo[q] = min(lo[q], (v >> (8 * q)) & 255u);
+  };
+#pragma unroll
+  for (int k = 0; k < 4; ++k) take(sc.first[k]);
+  for (int t = 4; t < sc.cols.n; t += 4) {
+    uint32_t v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      v[k] = *reinterpret_cast<const u32u*>(sc.cols.e + (int64_t)min(t + k, sc.cols.n - 1) * sc.cols.ld);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) take(v[k]);
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) sc.row[q] = exponent_scale(lo[q]);
 }
 
 template <bool KMAJOR, bool MASKED, bool ROWS>
@@ -133,12 +170,13 @@ __device__ __forceinline__ void h2_handover() {
 // The producers of gemm_tile_x3.h with the two-way split; slab it goes to buffer it % NBUF.
 template <bool KMAJOR, bool ROWS, int NBUF>
 __device__ __forceinline__ void h2_produce4(char* smem, int operand, const float* __restrict__ P, int64_t ld,
-                                            int ext, int kbeg, const ScaleH2& sc, int u) {
+                                            int ext, int kbeg, ScaleH2& sc, int u) {
   SlabSrcX3 src;
   slab_src_x3<KMAJOR>(src, P, ld, ext, kbeg, u);
   SlabRegsX3 r0, r1;
   slab_load_x3<KMAJOR, true>(r0, src, 0, 4 * kXK, P);
   slab_load_x3<KMAJOR, true>(r1, src, 1, 3 * kXK, P);
+  if (KMAJOR && ROWS) finish_cols_h2(sc);
   char* const second = smem + (NBUF - 1) * kH2Buf;
   slab_store_h2<KMAJOR, false, ROWS>(smem, operand, r0, sc, u);
   slab_load_x3<KMAJOR, true>(r0, src, 2, 2 * kXK, P);
@@ -154,13 +192,13 @@ __device__ __forceinline__ void h2_produce4(char* smem, int operand, const float
 
 template <bool KMAJOR, bool FAST, bool MASKED, bool ROWS, int NBUF>
 __device__ __forceinline__ void h2_produce(char* smem, int operand, const float* __restrict__ P, int64_t ld,
-                                           int ext, int kbeg, int kend, int nslab, const ScaleH2& sc,
-                                           int u) {
+                                           int ext, int kbeg, int kend, int nslab, ScaleH2& sc, int u) {
   SlabSrcX3 src;
   slab_src_x3<KMAJOR>(src, P, ld, ext, kbeg, u);
   const int klen = kend - kbeg;
   SlabRegsX3 r;
   slab_load_x3<KMAJOR, FAST>(r, src, 0, klen, P);
+  if (KMAJOR && ROWS) finish_cols_h2(sc);
   for (int it = 0; it < nslab; ++it) {
     if (operand == 0 && u < 64) TL_MARK(8 + 4 * it);
     slab_store_h2<KMAJOR, MASKED, ROWS>(smem + (NBUF == 2 ? (it & 1) * kH2Buf : 0), operand, r, sc, u);
@@ -172,7 +210,7 @@ __device__ __forceinline__ void h2_produce(char* smem, int operand, const float*
 
 template <bool KMAJOR, bool ROWS, int NBUF, bool PIECES>
 __device__ __forceinline__ void h2_producer(char* smem, int operand, const float* __restrict__ P, int64_t ld,
-                                            int ext, int kbeg, int kend, bool vec, const ScaleH2& sc, int u) {
+                                            int ext, int kbeg, int kend, bool vec, ScaleH2& sc, int u) {
   const int nslab = (kend - kbeg + kXK - 1) / kXK;
   const bool fast = vec && (KMAJOR ? ext % 4 == 0 : (kend - kbeg) % 4 == 0);
   const bool whole = ext == 128 && (kend - kbeg) % kXK == 0;
@@ -182,13 +220,18 @@ __device__ __forceinline__ void h2_producer(char* smem, int operand, const float
   else h2_produce<KMAJOR, false, false, ROWS, NBUF>(smem, operand, P, ld, ext, kbeg, kend, nslab, sc, u);
 }
 
-// acc += (sa A)[0:128, kbeg:kend] (sb B)[kbeg:kend, 0:128]; otherwise as gemm_tile_x3().  ROWS: further
-// scales of the m_ext rows of A (the n_ext columns of B).  B_PIECES: the extents of B are multiples of 4.
-template <bool A_KMAJOR, bool B_KMAJOR, int NBUF, bool A_ROWS = false, bool B_ROWS = false, bool B_PIECES = false>
+// acc += (sa A)[0:128, kbeg:kend] (sb B)[kbeg:kend, 0:128]; otherwise as gemm_tile_x3().  A_ROWS: further
+// scales of the m_ext rows of A.  B_COLS: of the columns of B, instead of sb; their reciprocals end in
+// inv[0:128] (LDS beyond the buffers' use after the product), complete after the next barrier.
+// B_PIECES: the extents of B are multiples of 4.
+template <bool A_KMAJOR, bool B_KMAJOR, int NBUF, bool A_ROWS = false, bool B_COLS = false, bool B_PIECES = false>
 __device__ __forceinline__ void gemm_tile_h2(TileAcc& acc, char* smem, const float* __restrict__ A,
                                              int64_t lda, int m_ext, float sa, const float* arows,
                                              const float* __restrict__ B, int64_t ldb, int n_ext, float sb,
-                                             const float* brows, int kbeg, int kend, bool vec_a, bool vec_b) {
+                                             const ColScalesH2& bcols, float* inv, int kbeg, int kend, bool vec_a,
+                                             bool vec_b) {
+  static_assert(!A_ROWS || !A_KMAJOR, "rows of A");
+  static_assert(!B_COLS || (B_KMAJOR && B_PIECES), "columns of B, four at a time");
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -197,11 +240,11 @@ __device__ __forceinline__ void gemm_tile_h2(TileAcc& acc, char* smem, const flo
   ScaleH2 sc;
   const int u = tid & 127;
   sc.all = wave >= 6 ? sb : sa;
-  if (A_ROWS && wave >= 4 && wave < 6) load_rows_h2<A_KMAJOR>(sc, arows, m_ext, u);
-  if (B_ROWS && wave >= 6) load_rows_h2<B_KMAJOR>(sc, brows, n_ext, u);
+  if (A_ROWS && wave >= 4 && wave < 6) load_rows_h2(sc, arows, m_ext, u);
+  if (B_COLS && wave >= 6) load_cols_h2(sc, bcols, n_ext, u);
   __syncthreads();  // previous users of the LDS buffers are done
   if (wave >= 6) {
-    h2_producer<B_KMAJOR, B_ROWS, NBUF, B_PIECES>(smem, 1, B, ldb, n_ext, kbeg, kend, vec_b, sc, u);
+    h2_producer<B_KMAJOR, B_COLS, NBUF, B_PIECES>(smem, 1, B, ldb, n_ext, kbeg, kend, vec_b, sc, u);
   } else if (wave >= 4) {
     h2_producer<A_KMAJOR, A_ROWS, NBUF, false>(smem, 0, A, lda, m_ext, kbeg, kend, vec_a, sc, u);
   } else {
@@ -240,6 +283,10 @@ __device__ __forceinline__ void gemm_tile_h2(TileAcc& acc, char* smem, const flo
     }
   }
   if (NBUF == 2) __syncthreads();  // the LDS is free
+  if (B_COLS && wave == 6 && u < 32) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) inv[4 * u + q] = pow2_inv(sc.row[q]);
+  }
 }
 
 }  // namespace thanos

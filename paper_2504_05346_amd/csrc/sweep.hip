@@ -11,9 +11,10 @@
 //
 // Scaled coordinates.  With sc[j] the power of two that brings the largest magnitude of column j of U into
 // [1/2, 1), the sweep works with P' = S P S and u' = u S, which gives lambda' = lambda S^{-1}: the same
-// values times powers of two, so nothing changes in them, but |P'_qj| <= B for every input, and with the
-// largest |lambda'| of each row at hand (rsc) the products can split their operands into two fp16 values
-// (gemm_tile_h2.h).  W stays as it is: the update takes the scales out again.
+// values times powers of two, so nothing changes in them, but no column of P' can outweigh the others, and with
+// the largest |lambda'| of each row (rsc) and the largest |P'| of each column of a block (pexp) at hand the
+// products can split their operands into two fp16 values (gemm_tile_h2.h).  W stays as it is: the update takes
+// the scales out again.
 #include <algorithm>
 
 #include <cmath>
@@ -103,12 +104,16 @@ struct BlockRowsArgs {
   const float* U;
   float* P;
   const float* sc;
+  uint8_t* pexp;  // scales of the update's product as biased exponents, by column and 128 rows of a block
   int64_t b;
   int B;
   CompArgs comp;
 };
 
-constexpr size_t kBlockRowsSmem = kXSmemBytes + kTM * sizeof(float);
+// Rows of pexp: block by block, a block's row tiles in order.
+constexpr int64_t block_row_tiles(int B) { return (B + kTM - 1) / kTM; }
+
+constexpr size_t kBlockRowsSmem = kXSmemBytes + (kTM + 8 * kTN) * sizeof(float);
 __global__ __launch_bounds__(kXThreads, 4) void k_block_rows(BlockRowsArgs a) {
   extern __shared__ __attribute__((aligned(16))) char sm[];
   if (a.comp.L && (int)blockIdx.z >= a.comp.nz) {
@@ -137,11 +142,16 @@ __global__ __launch_bounds__(kXThreads, 4) void k_block_rows(BlockRowsArgs a) {
   const float* T = x3_stage_tile(acc, sm);
   float* Pg = a.P + (j1 + mrow0) * a.b + col0;
   const bool whole = m_ext == kTM && n_ext == kTN;
+  uint32_t top0 = 0, top1 = 0;  // largest magnitudes as bits: NaN counts as large
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     const int row = wave + 8 * i;
     const float2 t = *reinterpret_cast<const float2*>(T + row * kXCLd + 2 * lane);
     const f32x2u o = {t.x * sr[row] * s0, t.y * sr[row] * s1};
+    if (row < m_ext) {
+      top0 = max(top0, __float_as_uint(fabsf(o.x)));
+      top1 = max(top1, __float_as_uint(fabsf(o.y)));
+    }
     if (whole) {
       *reinterpret_cast<f32x2u*>(Pg + (int64_t)row * a.b + 2 * lane) = o;
     } else if (row < m_ext) {
@@ -149,6 +159,18 @@ __global__ __launch_bounds__(kXThreads, 4) void k_block_rows(BlockRowsArgs a) {
       if (2 * lane + 1 < n_ext) Pg[(int64_t)row * a.b + 2 * lane + 1] = o.y;
     }
   }
+  if (!a.pexp) return;
+  uint32_t* const tops = reinterpret_cast<uint32_t*>(sr + kTM);
+  tops[wave * kTN + 2 * lane] = top0;
+  tops[wave * kTN + 2 * lane + 1] = top1;
+  __syncthreads();
+  const int col = threadIdx.x;
+  if (col >= n_ext) return;
+  uint32_t top = tops[col];
+#pragma unroll
+  for (int v = 1; v < 8; ++v) top = max(top, tops[v * kTN + col]);
+  const int64_t at = blockIdx.y * block_row_tiles(a.B) + blockIdx.z;
+  a.pexp[at * a.b + col0 + col] = (uint8_t)h2_exponent(__uint_as_float(top));
 }
 
 // sc from a given factor (own factors bring the largest magnitudes of their columns along): 16 threads per
@@ -2187,20 +2209,27 @@ struct UpdateArgs {
   const float* sx;
   const float* sc;            // scales of the columns ...
   const float* rsc;           // ... and of the rows' multipliers
-  float sp;                   // scale of P (a bound of its values is the block size)
+  const uint8_t* pexp;        // scales of P for the product (rows pexp_n, stride b)
+  int pexp_n;
   int gx, gy;                 // tile grid (set by launch_update)
 };
 
-// two slabs of the operands; after the product the staged tile and, behind it, the window counts
 typedef unsigned short u16u __attribute__((aligned(1)));  // two mask bytes
 
+// two slabs of the operands; after the product the staged tile and, behind it, the window counts and the
+// reciprocal scales of the columns
 constexpr size_t kUpdSmemBytes = kH2SmemBytes;
-static_assert(kXSmemBytes + 2048 * sizeof(unsigned int) + 16 * sizeof(unsigned int) + kCandStage * sizeof(uint2) <=
-                  kUpdSmemBytes, "both fit");
+constexpr size_t kUpdInvOffset = kXSmemBytes + 2048 * sizeof(unsigned int) + 16 * sizeof(unsigned int) +
+                                 kCandStage * sizeof(uint2);
+static_assert(kUpdInvOffset + kTN * sizeof(float) <= kUpdSmemBytes, "both fit");
 
 // H2: two-way split of the operands.  Not for short reductions: of K products it loses the last bits once,
-// the three-way split rounds its running sum twice as often.  Relative errors of normal products, two-way and
-// three-way: K = 16 8.5 and 3.4e-8, 64 1.13 and 1.10e-7, 96 1.28 and 1.38, 128 1.43 and 1.63, 1024 3.6 and 4.9.
+// the three-way split rounds its running sum twice as often.  Errors of this kernel's results against float64,
+// solve included, two-way and three-way: K = 16 1.83 and 1.70e-7, 48 2.77 and 2.73, 64 3.13 and 3.14, 80 3.67 and
+// 3.69, 128 4.68 and 4.74.  The scales come from the values of P (per column) and of the multipliers (per row):
+// with the block size as the bound of P, whose values get smaller as b grows, updates of 1024 to 2048 products
+// were off by 5.7e-7 at 8192 columns, B = 128, 8.2e-7 at B = 256, 2.1e-6 at 28672 columns; three-way 5.3, 6.6 and
+// 6.0e-7; now 4.4, 5.0 and 4.8e-7.  Price: 0.6 % of 4096x11008 at 50 %.
 constexpr int kUpdShortK = 64;
 template <bool H2>
 __global__ __launch_bounds__(kXThreads, 4) void k_update(UpdateArgs a) {
@@ -2238,9 +2267,10 @@ __global__ __launch_bounds__(kXThreads, 4) void k_update(UpdateArgs a) {
   // P is fetched 16 bytes at a time whatever its row stride: up to three columns past the last one, values of
   // the next row or of what lies behind P in the workspace, which end in columns that are not written
   const int n4 = (n_ext + 3) & ~3;
+  float* const inv = reinterpret_cast<float*>(sm + kUpdInvOffset);
   if constexpr (H2)
-    gemm_tile_h2<false, true, 2, true, false, true>(acc, sm, A, a.ldl, m_ext, 1.f, rsc, Bm, a.b, n4, a.sp, nullptr, 0, a.K,
-                                       a.vec_a, true);
+    gemm_tile_h2<false, true, 2, true, true, true>(acc, sm, A, a.ldl, m_ext, 1.f, rsc, Bm, a.b, n4, 1.f,
+                                                   {a.pexp + n0, a.b, a.pexp_n}, inv, 0, a.K, a.vec_a, true);
   else
     gemm_tile_x3<false, true>(acc, sm, A, a.ldl, m_ext, Bm, a.b, n4, 0, a.K, a.vec_a, true);
   if (threadIdx.x == 0) TL_MARK(1);
@@ -2258,8 +2288,11 @@ __global__ __launch_bounds__(kXThreads, 4) void k_update(UpdateArgs a) {
   float* Wg = a.W + m0 * a.b + cg;
   const uint8_t* Mg = a.mask + m0 * a.b + cg;
   // the scales taken out of the product again, per column and per row
-  const float fp = H2 ? pow2_inv(a.sp) : 1.f;
-  const float f0 = fp * pow2_inv(a.sc[min(cg, a.b - 1)]), f1 = fp * pow2_inv(a.sc[min(cg + 1, a.b - 1)]);
+  float f0 = pow2_inv(a.sc[min(cg, a.b - 1)]), f1 = pow2_inv(a.sc[min(cg + 1, a.b - 1)]);
+  if (H2) {
+    f0 *= inv[c0];
+    f1 *= inv[c0 + 1];
+  }
   // window count of one new weight (columns right of the block only)
   const unsigned int wlo = win ? a.st->win_lo : 0u;
   const int wsh = win ? a.st->win_shift : kWinShiftMin;
@@ -2440,6 +2473,7 @@ struct SweepWs {
   float* sc;
   float* Lam;
   float* P;
+  uint8_t* pexp;
   unsigned int* hist;
   SelState* st;
   int* row_cand;
@@ -2498,6 +2532,11 @@ bool sweep_uses_complement(const thanos_prune_opts* o, int64_t b) {
   return B % 4 == 0 && b % 4 == 0;
 }
 
+// Four columns at a time are read from pexp.
+static size_t pexp_bytes(int64_t b, int B) {
+  return kSuper * B > kUpdShortK ? (size_t)(ceil_div(b, B) * block_row_tiles(B) * b + 4) : 0;
+}
+
 size_t sweep_workspace_bytes(int64_t c, int64_t b, int B, bool outliers, int smax, bool comp) {
   size_t n = 0;
   if (comp) n += align_up((size_t)ceil_div(b, B) * B * B * 4, 256);  // K blocks
@@ -2506,6 +2545,7 @@ size_t sweep_workspace_bytes(int64_t c, int64_t b, int B, bool outliers, int sma
   n += 2 * align_up((size_t)b * 4, 256);        // sx, sc
   n += align_up((size_t)lam_buffer_floats(c, B) * 4, 256);  // Lam
   n += align_up((size_t)b * b * 4, 256);        // P
+  n += align_up(pexp_bytes(b, B), 256);
   n += align_up(4 * 2048 * 4, 256);             // hist: window + three passes
   n += align_up(sizeof(SelState), 256);         // state
   n += 2 * align_up((size_t)c * 4, 256);        // row_cand, row_eq
@@ -2537,6 +2577,7 @@ static SweepWs carve_ws(void* ws, int64_t c, int64_t b, int B, bool outliers, in
   w.sc = reinterpret_cast<float*>(carve(p, (size_t)b * 4));
   w.Lam = reinterpret_cast<float*>(carve(p, (size_t)lam_buffer_floats(c, B) * 4));
   w.P = reinterpret_cast<float*>(carve(p, (size_t)b * b * 4));
+  w.pexp = reinterpret_cast<uint8_t*>(carve(p, pexp_bytes(b, B)));
   w.hist = reinterpret_cast<unsigned int*>(carve(p, 4 * 2048 * 4));  // window + three passes
   w.st = reinterpret_cast<SelState*>(carve(p, sizeof(SelState)));
   w.row_cand = reinterpret_cast<int*>(carve(p, (size_t)c * 4));
@@ -2735,6 +2776,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
   else hipLaunchKernelGGL(k_sweep_init<__hip_bfloat16>, igrid, dim3(256), 0, s, ia);
   THANOS_LAUNCH_CHECK();
 
+  const int super = unstructured ? 1 : kSuper;  // the global residual mask needs current weights
   if (!umax) {
     hipLaunchKernelGGL(k_col_scales, dim3((unsigned)ceil_div(b, 64)), dim3(1024), 0, s, U, b, B, w.sc);
     THANOS_LAUNCH_CHECK();
@@ -2742,7 +2784,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
 
   {
     dim3 grid((unsigned)ceil_div(b, kTN), (unsigned)ceil_div(b, B), (unsigned)ceil_div(B, kTM));
-    BlockRowsArgs a{U, w.P, w.sc, b, B, {nullptr, 0, nullptr, nullptr, 0, 0}};
+    BlockRowsArgs a{U, w.P, w.sc, B * super > kUpdShortK ? w.pexp : nullptr, b, B, {nullptr, 0, nullptr, nullptr, 0, 0}};
     if (comp) {
       const int nt = (int)ceil_div(B, 32);
       a.comp = {Lfac, ldL, Ldiag, w.Kc, nt, (int)grid.z};
@@ -2759,7 +2801,6 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
     THANOS_LAUNCH_CHECK();
   }
 
-  const int super = unstructured ? 1 : kSuper;   // the global residual mask needs current weights
   const int ldl = B * super;
   // The update that reaches right of a super-block is split like the wide update of the
   // factorisation: the columns of the next super-block on the caller's stream, the rest on a
@@ -2769,7 +2810,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
   AuxStream aux(s, super > 1 ? 2 * n_super : 0, single_stream);
   if (!aux.ok) return THANOS_ERR_HIP;
   int pending_join = -1;
-  const float sp = h2_scale((float)B);
+  const int64_t row_tiles = block_row_tiles(B);
   int win_parts = 0;  // workgroups of the previous block's update (partial counts to sum)
   for (int64_t j1 = 0; j1 < b; j1 += B) {
     const int bw = (int)std::min<int64_t>(B, b - j1);
@@ -2888,7 +2929,8 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
       if (feed) win_parts = (int)(grid.x * grid.y);
       UpdateArgs ua{W, lam_sb + loff, w.P, mask, c, b, j1, j1, sb_end, j1, j1 + bw, bw, ldl,
                     (B % 4 == 0) ? 1 : 0,
-                    feed ? w.hist : nullptr, w.below_part, w.cand_n, w.cand, w.st, w.sx, w.sc, rsc, sp};
+                    feed ? w.hist : nullptr, w.below_part, w.cand_n, w.cand, w.st, w.sx, w.sc, rsc,
+                    w.pexp + blk * row_tiles * b, (int)ceil_div(bw, kTM)};
       launch_update(s, ua, grid);
       THANOS_LAUNCH_CHECK();
     }
@@ -2902,7 +2944,8 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
       {
         UpdateArgs ua{W, lam_sb, w.P, mask, c, b, sb_start, sb_end, next_end, 0, 0, kk, ldl,
                       (B % 4 == 0) ? 1 : 0, nullptr, nullptr, nullptr, nullptr,
-                      nullptr, nullptr, w.sc, rsc, sp};
+                      nullptr, nullptr, w.sc, rsc, w.pexp + sbi * super * row_tiles * b,
+                      (int)(super * row_tiles)};
         dim3 grid((unsigned)ceil_div(next_end - sb_end, kTN), (unsigned)ceil_div(c, kTM));
         launch_update(s, ua, grid);
         THANOS_LAUNCH_CHECK();
@@ -2911,7 +2954,8 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
         THANOS_CHECK(aux.fork((int)(2 * sbi)));
         UpdateArgs ua{W, lam_sb, w.P, mask, c, b, sb_start, next_end, b, 0, 0, kk, ldl,
                       (B % 4 == 0) ? 1 : 0, nullptr, nullptr, nullptr, nullptr,
-                      nullptr, nullptr, w.sc, rsc, sp};
+                      nullptr, nullptr, w.sc, rsc, w.pexp + sbi * super * row_tiles * b,
+                      (int)(super * row_tiles)};
         dim3 grid((unsigned)ceil_div(b - next_end, kTN), (unsigned)ceil_div(c, kTM));
         launch_update(aux.stream, ua, grid);
         THANOS_LAUNCH_CHECK();
