@@ -15,22 +15,26 @@ from .binding import (PruneOpts, _check, lib, thanos_factor, thanos_factor_works
                       thanos_prune_workspace_bytes)
 
 
-# Sweeps of few rows leave most of the chip idle and run side by side, each on a helper stream of the
-# library (and with a workspace of its own).  In the unstructured mode the selections of concurrent sweeps
+# Sweeps of few rows leave most of the chip idle and run side by side, up to _LANES at a time: on the caller's
+# stream and on helper streams of the library, each with a workspace of its own that its sweeps use in turn.  More
+# than four streams share hardware queues.  In the unstructured mode the selections of concurrent sweeps
 # wait for their own workgroups at grid barriers, one workgroup per 16 rows and at most one per compute unit,
-# so all of them together have to fit the chip: up to 15 rows per compute unit.  Whole calls on 2 b tokens,
-# one after the other -> side by side: 3 x 768 x 768 n:m 826 -> 548 us, 3 x 1280 x 5120 at 50 % 10.0 -> 6.0 ms,
-# n:m 6.7 -> 5.6, 2 x 2048 x 2048 n:m 1.94 both ways.  Wider matrices fill the chip with their own updates, and
-# a workspace holds b x b values.
+# so all of them together have to fit the chip: up to 15 rows per compute unit.  Whole calls on 2 b tokens, one,
+# two, three, four at a time: 3 x 768 x 768 at 50 % 1.42, 1.09, 0.93 ms; 4 x 512 x 2048 4.11, 2.62, 2.60, 2.22;
+# 8 x 128 x 4096 14.6, 8.6, 7.1, 5.9; 3 x 1024 x 8192 17.5, 14.3, 11.3; one and two: 2 x 2048 x 2048 2.86, 2.84.
+# Wider matrices fill the chip with their own updates.  The further workspaces (b x b values and more each) take
+# no more than the factorisation's, which has just been freed, and 64 MiB.
+_LANES = 4
 _ROWS_PER_UNIT = 15
 _SIDE_BY_SIDE_COLUMNS = 8192
+_SPARE_BYTES = 64 << 20
 
 
-def _side_by_side(weights, b, dev, stream) -> bool:
-    if stream is not None or len(weights) < 2 or b > _SIDE_BY_SIDE_COLUMNS:
-        return False
-    units = torch.cuda.get_device_properties(dev).multi_processor_count
-    return sum(-(-W.shape[0] // 16) * 16 for W in weights) <= _ROWS_PER_UNIT * units
+def _lanes(rows, b, need, freed, units) -> int:
+    """How many sweeps run at once, for matrices of `rows` rows that need workspaces of up to `need` bytes."""
+    if len(rows) < 2 or b > _SIDE_BY_SIDE_COLUMNS or sum(-(-c // 16) * 16 for c in rows) > _ROWS_PER_UNIT * units:
+        return 1
+    return min(_LANES, len(rows), 1 + (freed + _SPARE_BYTES) // need)
 
 
 def prune_layer_set(weights: Sequence[torch.Tensor], x_chunks: Iterable[torch.Tensor], *, mode: int,
@@ -53,45 +57,56 @@ def prune_layer_set(weights: Sequence[torch.Tensor], x_chunks: Iterable[torch.Te
     finfo = torch.zeros((1,), dtype=torch.int32, device=dev)
     fws = torch.empty((thanos_factor_workspace_bytes(b),), dtype=torch.uint8, device=dev)
     thanos_factor(H, damping, U, xnorm2, fws, finfo, stream)
+    freed = fws.numel()
     del fws
-    jobs, ws = [], None
-    together = _side_by_side(weights, b, dev, stream)
+    opts, results = [], []
     for W in weights:
         c = W.shape[0]
         assert W.shape[1] == b and W.device == dev
         o = PruneOpts(mode=mode, sparsity=float(sparsity), n=n, m=m, block_size=block_size,
                       damping=damping, outlier_fraction=float(outlier_fraction))
         o.factor_in, o.xnorm2_in = U.data_ptr(), xnorm2.data_ptr()
-        need = thanos_prune_workspace_bytes(c, b, o)
-        if need == 0:
-            raise ValueError("options rejected by thanos_prune_workspace_bytes")
-        if ws is None or ws.numel() < need or together:
-            ws = torch.empty((need,), dtype=torch.uint8, device=dev)
-        res = {"W": torch.empty((c, b), dtype=torch.float32, device=dev),
-               "W_cast": torch.empty((c, b), dtype=W.dtype, device=dev) if cast else None,
-               "mask": torch.empty((c, b), dtype=torch.uint8, device=dev),
-               "info": torch.zeros((1,), dtype=torch.int32, device=dev)}
-        jobs.append((W, o, res, ws))
-        if not together:
-            _sweep(H, jobs[-1], stream)
-    if together:
-        # Everything is allocated (and cleared) on the caller's stream before the fork and joined into
-        # it again, so that to the caller and its allocator the call is work on that stream.
+        opts.append(o)
+        results.append({"W": torch.empty((c, b), dtype=torch.float32, device=dev),
+                        "W_cast": torch.empty((c, b), dtype=W.dtype, device=dev) if cast else None,
+                        "mask": torch.empty((c, b), dtype=torch.uint8, device=dev),
+                        "info": torch.zeros((1,), dtype=torch.int32, device=dev)})
+    needs = [thanos_prune_workspace_bytes(W.shape[0], b, o) for W, o in zip(weights, opts)]
+    if min(needs) == 0:
+        raise ValueError("options rejected by thanos_prune_workspace_bytes")
+    lanes = 1
+    if stream is None:
+        units = torch.cuda.get_device_properties(dev).multi_processor_count
+        lanes = _lanes([W.shape[0] for W in weights], b, max(needs), freed, units)
+    # Everything is allocated (and cleared) on the caller's stream before the fork and joined into it again, so
+    # that to the caller and its allocator the call is work on that stream.
+    spaces = [torch.empty((max(needs),), dtype=torch.uint8, device=dev)]
+    try:
+        while len(spaces) < lanes:
+            spaces.append(torch.empty_like(spaces[0]))
+    except torch.OutOfMemoryError:  # fewer lanes, same results
+        pass
+    streams, helpers = [stream], []
+    if len(spaces) > 1:
         main = torch.cuda.current_stream(dev)
         ready = main.record_event()
-        sides = []
-        try:
-            for job in jobs[1:]:
+        streams = [main]
+    try:
+        for k, (W, o, res) in enumerate(zip(weights, opts, results)):
+            lane = k % len(spaces)
+            if lane == len(streams):
                 helper, side = _borrow(dev)
-                sides.append((helper, side))
+                helpers.append((helper, side))
                 side.wait_event(ready)
-                _sweep(H, job, side)
-            _sweep(H, jobs[0], main)
-        finally:
-            for helper, side in sides:
-                main.wait_stream(side)
-                lib().thanos_helper_release(helper)
-    return [job[2] for job in jobs], H
+                streams.append(side)
+            # a failed factorisation shows in finfo; the sweeps then run on a meaningless factor
+            thanos_prune_layer(W, H, o, res["W"], res["W_cast"], res["mask"], spaces[lane], res["info"],
+                               streams[lane])
+    finally:
+        for helper, side in helpers:
+            main.wait_stream(side)
+            lib().thanos_helper_release(helper)
+    return results, H
 
 
 def _borrow(dev):
@@ -103,8 +118,3 @@ def _borrow(dev):
         _check(lib().thanos_helper_acquire(ctypes.byref(helper), ctypes.byref(stream)), "thanos_helper_acquire")
     return helper, torch.cuda.ExternalStream(stream.value, device=dev)
 
-
-def _sweep(H, job, stream):
-    # a failed factorisation shows in finfo; the sweeps then run on a meaningless factor
-    W, o, res, ws = job
-    thanos_prune_layer(W, H, o, res["W"], res["W_cast"], res["mask"], ws, res["info"], stream)

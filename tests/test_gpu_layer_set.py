@@ -98,3 +98,38 @@ def test_helper_streams_are_lent_oldest_first():
         L.thanos_helper_release(h)
     assert again == first
     assert L.thanos_helper_acquire(None, None) == 1
+
+
+@pytest.mark.parametrize("mode", ["nm", "unstructured"])
+def test_many_matrices_share_four_lanes(mode, monkeypatch):
+    """Seven matrices: three helper streams are borrowed, each once, and the workspaces are used in turn; bits as
+    with one sweep after the other, also when there is no memory for a further workspace."""
+    import torch
+    import paper_2504_05346_amd as th
+    from paper_2504_05346_amd import layer_set
+    from tests.gpu_util import dev
+    b, T = 512, 2048
+    X = dev(make_calibration(LayerSpec("x", c=1, b=b, tokens=T, dtype="f16", rho=0.7, k_mix=16, seed=3)))
+    Ws = [dev(make_weight(LayerSpec("w", c=c, b=b, tokens=T, dtype="f16", seed=60 + k)))
+          for k, c in enumerate((64, 300, 17, 128, 129, 256, 33))]
+    kw = dict(mode=th.THANOS_NM, n=2, m=4) if mode == "nm" else dict(mode=th.THANOS_UNSTRUCTURED, sparsity=0.5)
+    borrowed = []
+    borrow = layer_set._borrow
+    monkeypatch.setattr(layer_set, "_borrow", lambda d: (borrowed.append(borrow(d)), borrowed[-1])[1])
+    got, _ = th.prune_layer_set(Ws, [X], **kw)
+    assert len({side.cuda_stream for _, side in borrowed}) == len(borrowed) == 3
+
+    def full(*a, **k):
+        raise torch.OutOfMemoryError("no room for another workspace")
+
+    monkeypatch.setattr(torch, "empty_like", full)
+    alone, _ = th.prune_layer_set(Ws, [X], **kw)
+    monkeypatch.undo()
+    assert len(borrowed) == 3  # none more
+    monkeypatch.setattr(layer_set, "_LANES", 1)
+    want, _ = th.prune_layer_set(Ws, [X], **kw)
+    torch.cuda.synchronize()
+    for g, a, w in zip(got, alone, want):
+        for key in ("W", "mask", "info"):
+            assert torch.equal(g[key], w[key]) and torch.equal(a[key], w[key])
+        assert int(g["info"].item()) == 0

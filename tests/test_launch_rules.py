@@ -244,3 +244,18 @@ extern "C" float col(float x) { return thanos::col_scale(x); }
             if -100 <= e <= 98:
                 assert 0.5 <= x * c < 1.0
     assert L.h2(0.0) == 2.0 ** 126 and L.col(0.0) == 1.0
+
+
+@pytest.mark.parametrize("rows,b,need,lanes", [
+    ([768] * 3, 768, 12 << 20, 3), ([17, 400], 512, 4 << 20, 2), ([2000, 1900], 512, 20 << 20, 1),
+    ([64] * 60, 8192, 270 << 20, 4),       # many experts: four workspaces, not sixty
+    ([128] * 30, 8192, 275 << 20, 4), ([500] * 4, 5120, 300 << 20, 2), ([768] * 3, 768, 80 << 20, 1),
+    ([64] * 3, 8200, 270 << 20, 1), ([64], 512, 1 << 20, 1)])
+def test_layer_sets_run_few_sweeps_at_once(rows, b, need, lanes):
+    """Streams and workspaces of a layer set are bounded whatever the number of matrices: at most four, the
+    further ones in no more memory than the factorisation had, and 64 MiB."""
+    from paper_2504_05346_amd.layer_set import _lanes
+    freed = 3 * 4 * b * b
+    got = _lanes(rows, b, need, freed, 256)
+    assert got == lanes
+    assert (got - 1) * need <= freed + (64 << 20)
