@@ -10,7 +10,7 @@ from typing import Iterable, List, Sequence, Tuple
 
 import torch
 
-from .binding import (PruneOpts, _check, lib, thanos_factor, thanos_factor_workspace_bytes,
+from .binding import (THANOS_NM, PruneOpts, _check, lib, thanos_factor, thanos_factor_workspace_bytes,
                       thanos_hessian_accumulate, thanos_prune_layer,
                       thanos_prune_workspace_bytes)
 
@@ -92,16 +92,22 @@ def prune_layer_set(weights: Sequence[torch.Tensor], x_chunks: Iterable[torch.Te
         ready = main.record_event()
         streams = [main]
     try:
+        # all lanes before the first sweep: the pool lends what a sweep has handed back, with work still queued on
+        # it, to the next that asks
+        for _ in spaces[1:]:
+            helper, side = _borrow(dev)
+            helpers.append((helper, side))
+            side.wait_event(ready)
+            streams.append(side)
         for k, (W, o, res) in enumerate(zip(weights, opts, results)):
             lane = k % len(spaces)
-            if lane == len(streams):
-                helper, side = _borrow(dev)
-                helpers.append((helper, side))
-                side.wait_event(ready)
-                streams.append(side)
             # a failed factorisation shows in finfo; the sweeps then run on a meaningless factor
             thanos_prune_layer(W, H, o, res["W"], res["W_cast"], res["mask"], spaces[lane], res["info"],
                                streams[lane])
+            if mode == THANOS_NM and b > 16 * block_size and k < len(spaces) - 1:
+                # the sweep has far updates (more than two super-blocks of eight blocks): keep the next lane's
+                # from queueing behind them
+                helpers.append(_borrow(dev))
     finally:
         for helper, side in helpers:
             main.wait_stream(side)

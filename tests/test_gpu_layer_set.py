@@ -100,9 +100,10 @@ def test_helper_streams_are_lent_oldest_first():
     assert L.thanos_helper_acquire(None, None) == 1
 
 
-@pytest.mark.parametrize("mode", ["nm", "unstructured"])
-def test_many_matrices_share_four_lanes(mode, monkeypatch):
-    """Seven matrices: three helper streams are borrowed, each once, and the workspaces are used in turn; bits as
+@pytest.mark.parametrize("mode,B", [("nm", 128), ("nm", 16), ("unstructured", 128)])
+def test_many_matrices_share_four_lanes(mode, B, monkeypatch):
+    """Seven matrices: three helper streams are borrowed as lanes and, for n:m sweeps with far updates (B = 16),
+    the helper of each of the first three sweeps until the end, all different, the lanes before the first sweep; and the workspaces are used in turn; bits as
     with one sweep after the other, also when there is no memory for a further workspace."""
     import torch
     import paper_2504_05346_amd as th
@@ -113,11 +114,18 @@ def test_many_matrices_share_four_lanes(mode, monkeypatch):
     Ws = [dev(make_weight(LayerSpec("w", c=c, b=b, tokens=T, dtype="f16", seed=60 + k)))
           for k, c in enumerate((64, 300, 17, 128, 129, 256, 33))]
     kw = dict(mode=th.THANOS_NM, n=2, m=4) if mode == "nm" else dict(mode=th.THANOS_UNSTRUCTURED, sparsity=0.5)
+    kw["block_size"] = B
     borrowed = []
     borrow = layer_set._borrow
-    monkeypatch.setattr(layer_set, "_borrow", lambda d: (borrowed.append(borrow(d)), borrowed[-1])[1])
+    order = []
+    prune = layer_set.thanos_prune_layer
+    monkeypatch.setattr(layer_set, "_borrow",
+                        lambda d: (order.append("borrow"), borrowed.append(borrow(d)), borrowed[-1])[2])
+    monkeypatch.setattr(layer_set, "thanos_prune_layer", lambda *a: (order.append("sweep"), prune(*a))[1])
     got, _ = th.prune_layer_set(Ws, [X], **kw)
-    assert len({side.cuda_stream for _, side in borrowed}) == len(borrowed) == 3
+    extra = 3 if B == 16 else 0
+    assert len({side.cuda_stream for _, side in borrowed}) == len(borrowed) == 3 + extra
+    assert order == ["borrow"] * 3 + (["sweep", "borrow"] * 3 if extra else []) + ["sweep"] * (7 - extra)
 
     def full(*a, **k):
         raise torch.OutOfMemoryError("no room for another workspace")
@@ -125,7 +133,7 @@ def test_many_matrices_share_four_lanes(mode, monkeypatch):
     monkeypatch.setattr(torch, "empty_like", full)
     alone, _ = th.prune_layer_set(Ws, [X], **kw)
     monkeypatch.undo()
-    assert len(borrowed) == 3  # none more
+    assert len(borrowed) == 3 + extra  # none more
     monkeypatch.setattr(layer_set, "_LANES", 1)
     want, _ = th.prune_layer_set(Ws, [X], **kw)
     torch.cuda.synchronize()
