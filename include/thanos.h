@@ -187,6 +187,18 @@ thanos_status thanos_prune_layer(const void* W_in, thanos_dtype wdt, int64_t c, 
 size_t thanos_prune_workspace_bytes(int64_t c, int64_t b, const thanos_prune_opts* opts /* host */);
 
 /*
+ * thanos_prune_layer for one of `sharers` (>= 1, else INVALID_ARG) calls that a caller runs at the same time on
+ * streams of its own, each with its own workspace and outputs.  Same results.  In the unstructured mode the
+ * workgroups of a call's selection wait for each other, at most one of them fits a compute unit, and a call whose
+ * wait runs out reports that through info: with this entry point all `sharers` calls together launch no more of
+ * them than the one with the most rows would by itself.
+ */
+thanos_status thanos_prune_layer_shared(const void* W_in, thanos_dtype wdt, int64_t c, int64_t b,
+                                        const float* H, const thanos_prune_opts* opts /* host */,
+                                        float* W_out, void* W_out_cast, uint8_t* mask_out, void* ws,
+                                        size_t ws_bytes, int32_t* info_dev, int32_t sharers, void* stream);
+
+/*
  * thanos_prune_layer for callers that cannot allocate: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  Same arguments, results and errors as
  * thanos_prune_layer, without ws / ws_bytes: the workspace is a static device array of

@@ -16,6 +16,7 @@ from .binding import (  # noqa: F401
     thanos_factor_workspace_bytes,
     thanos_prune_layer,
     thanos_prune_layer_noalloc,
+    thanos_prune_layer_shared,
     THANOS_NOALLOC_SCRATCH_BYTES,
     thanos_prune_workspace_bytes,
     thanos_status_string,

@@ -70,6 +70,9 @@ def lib() -> ctypes.CDLL:
     L.thanos_prune_layer.restype = ctypes.c_int
     L.thanos_prune_layer.argtypes = [vp, ctypes.c_int, i64, i64, vp, ctypes.POINTER(PruneOpts),
                                      vp, vp, vp, vp, sz, vp, vp]
+    L.thanos_prune_layer_shared.restype = ctypes.c_int
+    L.thanos_prune_layer_shared.argtypes = [vp, ctypes.c_int, i64, i64, vp, ctypes.POINTER(PruneOpts),
+                                            vp, vp, vp, vp, sz, vp, ctypes.c_int32, vp]
     L.thanos_prune_layer_noalloc.restype = ctypes.c_int
     L.thanos_prune_layer_noalloc.argtypes = [vp, ctypes.c_int, i64, i64, vp,
                                              ctypes.POINTER(PruneOpts), vp, vp, vp, vp, vp]
@@ -142,22 +145,35 @@ def thanos_prune_workspace_bytes(c: int, b: int, opts: PruneOpts) -> int:
     return int(lib().thanos_prune_workspace_bytes(c, b, ctypes.byref(opts)))
 
 
-def thanos_prune_layer(W_in: torch.Tensor, H: Optional[torch.Tensor], opts: PruneOpts,
-                       W_out: torch.Tensor, W_out_cast: Optional[torch.Tensor],
-                       mask_out: torch.Tensor, ws: torch.Tensor, info: torch.Tensor,
-                       stream=None) -> None:
-    """Block sweep on W_in (c x b); writes W_out (fp32), optional cast copy, mask (uint8)."""
+def _prune_args(W_in, H, opts, W_out, W_out_cast, mask_out, ws, info):
     c, b = W_in.shape
     assert W_in.is_contiguous() and W_out.is_contiguous() and mask_out.is_contiguous()
     assert W_out.dtype == torch.float32 and W_out.shape == (c, b)
     assert mask_out.dtype == torch.uint8 and mask_out.shape == (c, b)
     if W_out_cast is not None:
         assert W_out_cast.dtype == W_in.dtype and W_out_cast.shape == (c, b)
-    st = lib().thanos_prune_layer(_ptr(W_in), _dtype_code(W_in), c, b, _ptr(H),
-                                  ctypes.byref(opts), _ptr(W_out), _ptr(W_out_cast),
-                                  _ptr(mask_out), _ptr(ws), ws.numel() * ws.element_size(),
-                                  _ptr(info), _stream(stream))
+    return (_ptr(W_in), _dtype_code(W_in), c, b, _ptr(H), ctypes.byref(opts), _ptr(W_out), _ptr(W_out_cast),
+            _ptr(mask_out), _ptr(ws), ws.numel() * ws.element_size(), _ptr(info))
+
+
+def thanos_prune_layer(W_in: torch.Tensor, H: Optional[torch.Tensor], opts: PruneOpts,
+                       W_out: torch.Tensor, W_out_cast: Optional[torch.Tensor],
+                       mask_out: torch.Tensor, ws: torch.Tensor, info: torch.Tensor,
+                       stream=None) -> None:
+    """Block sweep on W_in (c x b); writes W_out (fp32), optional cast copy, mask (uint8)."""
+    st = lib().thanos_prune_layer(*_prune_args(W_in, H, opts, W_out, W_out_cast, mask_out, ws, info),
+                                  _stream(stream))
     _check(st, "thanos_prune_layer")
+
+
+def thanos_prune_layer_shared(W_in: torch.Tensor, H: Optional[torch.Tensor], opts: PruneOpts,
+                              W_out: torch.Tensor, W_out_cast: Optional[torch.Tensor],
+                              mask_out: torch.Tensor, ws: torch.Tensor, info: torch.Tensor,
+                              sharers: int, stream=None) -> None:
+    """thanos_prune_layer for one of `sharers` calls that run at the same time on streams of their own."""
+    st = lib().thanos_prune_layer_shared(*_prune_args(W_in, H, opts, W_out, W_out_cast, mask_out, ws, info),
+                                         sharers, _stream(stream))
+    _check(st, "thanos_prune_layer_shared")
 
 
 THANOS_NOALLOC_SCRATCH_BYTES = 67 << 20

@@ -16,7 +16,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
                     void* W_cast, uint8_t* mask, void* ws, int32_t* info, bool single_stream,
                     PhaseTimer* pt, const float* Lfac, int64_t ldL, const float* Ldiag, const float* umax,
                     bool prepared,
-                    bool clear_info);
+                    bool clear_info, int sharers);
 thanos_status sweep_prepare(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c, int64_t b,
                             const float* H, const thanos_prune_opts* o, long long n_out, float* W,
                             void* ws, bool beside);
@@ -352,7 +352,7 @@ static thanos_status prune_with_workspace(const void* W_in, thanos_dtype wdt, in
                                           const float* H, const thanos_prune_opts* opts,
                                           float* W_out, void* W_out_cast, uint8_t* mask_out,
                                           void* ws, int32_t* info_dev, hipStream_t s,
-                                          bool single_stream) {
+                                          bool single_stream, int sharers = 1) {
   if (opts->mode == THANOS_STRUCTURED) {
     if (opts->phase_ms_out) return THANOS_ERR_UNSUPPORTED;
     return structured(s, W_in, wdt, c, b, H, opts->damping,
@@ -423,7 +423,7 @@ static thanos_status prune_with_workspace(const void* W_in, thanos_dtype wdt, in
   phase_mark(pt, THANOS_PHASE_PREP);
   thanos_status st = sweep(s, W_in, wdt, c, b, H, U, xn2, opts, r_total, n_out, W_out, W_out_cast,
                            mask_out, sweep_ws, info_dev, single_stream, pt, Lfac, ldL, Ldiag, umax, prepared,
-                           opts->factor_in != nullptr);
+                           opts->factor_in != nullptr, sharers);
   if (pt) {
     const thanos_status tc = pt->collect(opts->phase_ms_out);
     if (st == THANOS_OK) st = tc;
@@ -435,12 +435,21 @@ thanos_status thanos_prune_layer(const void* W_in, thanos_dtype wdt, int64_t c, 
                                  const float* H, const thanos_prune_opts* opts, float* W_out,
                                  void* W_out_cast, uint8_t* mask_out, void* ws, size_t ws_bytes,
                                  int32_t* info_dev, void* stream) {
+  return thanos_prune_layer_shared(W_in, wdt, c, b, H, opts, W_out, W_out_cast, mask_out, ws, ws_bytes, info_dev,
+                                   1, stream);
+}
+
+thanos_status thanos_prune_layer_shared(const void* W_in, thanos_dtype wdt, int64_t c, int64_t b,
+                                        const float* H, const thanos_prune_opts* opts, float* W_out,
+                                        void* W_out_cast, uint8_t* mask_out, void* ws, size_t ws_bytes,
+                                        int32_t* info_dev, int32_t sharers, void* stream) {
+  if (sharers < 1) return THANOS_ERR_INVALID_ARG;
   thanos_status st = check_prune_args(W_in, wdt, c, b, H, opts, W_out, mask_out, info_dev);
   if (st != THANOS_OK) return st;
   if (!ws || ws_bytes < thanos_prune_workspace_bytes(c, b, opts)) return THANOS_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(ws) % 256 != 0) return THANOS_ERR_INVALID_ARG;
   return prune_with_workspace(W_in, wdt, c, b, H, opts, W_out, W_out_cast, mask_out, ws, info_dev,
-                              reinterpret_cast<hipStream_t>(stream), false);
+                              reinterpret_cast<hipStream_t>(stream), false, sharers);
 }
 
 thanos_status thanos_prune_layer_noalloc(const void* W_in, thanos_dtype wdt, int64_t c, int64_t b,

@@ -21,6 +21,7 @@
 
 #include "gemm_tile_h2.h"
 #include "lam_layout.h"
+#include "select_plan.h"
 #include "tile32.h"
 
 namespace thanos {
@@ -240,8 +241,7 @@ struct SelState {
 };
 
 constexpr int32_t kInfoSelectTimeout = -0x7ffffff0;  // info: a bounded wait of k_select ran out
-constexpr int kSelThreads = 1024;
-constexpr int kSelMaxWgs = 256;       // at most one per compute unit: all resident at once
+constexpr int kSelThreads = 64 * kSelRows;
 constexpr unsigned int kSpinMax = 1u << 21;
 constexpr int kCandStage = 384;       // window keys one update workgroup can list (two update
                                       // workgroups still fit the LDS of a compute unit)
@@ -2755,7 +2755,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
                     void* W_cast, uint8_t* mask, void* ws, int32_t* info, bool single_stream,
                     PhaseTimer* pt, const float* Lfac, int64_t ldL, const float* Ldiag, const float* umax,
                     bool prepared,
-                    bool clear_info) {
+                    bool clear_info, int sharers) {
   const int B = o->block_size;
   const bool outliers = n_out > 0;
   const int smax_all = (o->mode == THANOS_NM && !o->mask_in) ? B / o->m * o->n : B;
@@ -2851,8 +2851,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
       ga.vec = sel_vec;
       ga.seq = (unsigned int)(blk + 1);
       ga.wgflag = w.wgflag;
-      const unsigned sel_wgs = (unsigned)std::min<int64_t>(std::min(kSelMaxWgs, compute_units()),
-                                                           ceil_div(c, kSelThreads / 64));
+      const unsigned sel_wgs = (unsigned)select_workgroups(c, compute_units(), sharers);
       hipLaunchKernelGGL(k_select, dim3(sel_wgs), dim3(kSelThreads), 0, s, ga);
       THANOS_LAUNCH_CHECK();
     }

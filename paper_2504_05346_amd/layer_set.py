@@ -11,15 +11,16 @@ from typing import Iterable, List, Sequence, Tuple
 import torch
 
 from .binding import (THANOS_NM, PruneOpts, _check, lib, thanos_factor, thanos_factor_workspace_bytes,
-                      thanos_hessian_accumulate, thanos_prune_layer,
+                      thanos_hessian_accumulate, thanos_prune_layer_shared,
                       thanos_prune_workspace_bytes)
 
 
 # Sweeps of few rows leave most of the chip idle and run side by side, up to _LANES at a time: on the caller's
 # stream and on helper streams of the library, each with a workspace of its own that its sweeps use in turn.  More
 # than four streams share hardware queues.  In the unstructured mode the selections of concurrent sweeps
-# wait for their own workgroups at grid barriers, one workgroup per 16 rows and at most one per compute unit,
-# so all of them together have to fit the chip: up to 15 rows per compute unit.  Whole calls on 2 b tokens, one,
+# wait for their own workgroups at grid barriers, at most one of which fits a compute unit: together they launch no
+# more of them than the sweep with the most rows by itself (`sharers`; 3 x 768 x 768 1 % slower than with all).  From about 15 rows per compute unit on the
+# sweeps fill the chip one after the other.  Whole calls on 2 b tokens, one,
 # two, three, four at a time: 3 x 768 x 768 at 50 % 1.42, 1.09, 0.93 ms; 4 x 512 x 2048 4.11, 2.62, 2.60, 2.22;
 # 8 x 128 x 4096 14.6, 8.6, 7.1, 5.9; 3 x 1024 x 8192 17.5, 14.3, 11.3; one and two: 2 x 2048 x 2048 2.86, 2.84.
 # Wider matrices fill the chip with their own updates.  The further workspaces (b x b values and more each) take
@@ -102,8 +103,8 @@ def prune_layer_set(weights: Sequence[torch.Tensor], x_chunks: Iterable[torch.Te
         for k, (W, o, res) in enumerate(zip(weights, opts, results)):
             lane = k % len(spaces)
             # a failed factorisation shows in finfo; the sweeps then run on a meaningless factor
-            thanos_prune_layer(W, H, o, res["W"], res["W_cast"], res["mask"], spaces[lane], res["info"],
-                               streams[lane])
+            thanos_prune_layer_shared(W, H, o, res["W"], res["W_cast"], res["mask"], spaces[lane], res["info"],
+                                      len(spaces), streams[lane])
             if mode == THANOS_NM and b > 16 * block_size and k < len(spaces) - 1:
                 # the sweep has far updates (more than two super-blocks of eight blocks): keep the next lane's
                 # from queueing behind them

@@ -118,10 +118,10 @@ def test_many_matrices_share_four_lanes(mode, B, monkeypatch):
     borrowed = []
     borrow = layer_set._borrow
     order = []
-    prune = layer_set.thanos_prune_layer
+    prune = layer_set.thanos_prune_layer_shared
     monkeypatch.setattr(layer_set, "_borrow",
                         lambda d: (order.append("borrow"), borrowed.append(borrow(d)), borrowed[-1])[2])
-    monkeypatch.setattr(layer_set, "thanos_prune_layer", lambda *a: (order.append("sweep"), prune(*a))[1])
+    monkeypatch.setattr(layer_set, "thanos_prune_layer_shared", lambda *a: (order.append("sweep"), prune(*a))[1])
     got, _ = th.prune_layer_set(Ws, [X], **kw)
     extra = 3 if B == 16 else 0
     assert len({side.cuda_stream for _, side in borrowed}) == len(borrowed) == 3 + extra

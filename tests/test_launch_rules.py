@@ -259,3 +259,24 @@ def test_layer_sets_run_few_sweeps_at_once(rows, b, need, lanes):
     got = _lanes(rows, b, need, freed, 256)
     assert got == lanes
     assert (got - 1) * need <= freed + (64 << 20)
+
+
+def test_selections_side_by_side_are_as_small_as_one(tmp_path_factory):
+    """Sweeps that run at the same time: the workgroups of their selections, which wait for each other, are
+    together no more than those of the largest of them, so that two sets at once are no closer to the number of
+    compute units than two sweeps; a single workgroup waits for nobody.  One call alone: a workgroup per 16
+    rows, at most one per unit."""
+    from paper_2504_05346_amd.layer_set import _lanes
+    L = _compile(tmp_path_factory, "select", """
+#include "select_plan.h"
+extern "C" int wgs(int64_t c, int units, int sharers) { return thanos::select_workgroups(c, units, sharers); }
+""")
+    L.wgs.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int]
+    for c in (1, 16, 17, 768, 3840, 4096, 28672, 1 << 24):
+        for units in (32, 256, 304):
+            assert L.wgs(c, units, 1) == min(-(-c // 16), units, 256)
+    for rows in ([768] * 3, [17, 400], [1280] * 3, [64] * 60, [3000, 100, 200], [16, 32, 48, 8], [1920, 1920]):
+        lanes = _lanes(rows, 512, 1 << 20, 1 << 30, 256)
+        assert lanes == min(4, len(rows))
+        at_once = sorted((L.wgs(c, 256, lanes) for c in rows), reverse=True)[:lanes]
+        assert sum(n for n in at_once if n > 1) <= max(L.wgs(c, 256, 1) for c in rows)
