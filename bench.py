@@ -166,11 +166,12 @@ def phase_rooflines(args, mode, ph, M, torch):
 
     entry("factor", "mfma", (2.0 / 3.0) * b ** 3, "TFLOP/s", PEAK_MFMA_F32_TFLOPS, ph["factor"],
           note="fp32 products (Cholesky b^3/3 + triangular inverse b^3/3) against the fp32 "
-               "matrix-core peak; computed as 6 bf16 MFMAs per product")
+               "matrix-core peak; computed as 3 or 4 fp16 MFMAs per product (operands split in two)")
     upd_flops = 2.0 * c * sum(min(B, b - j1) * (b - j1) for j1 in starts)
     upd_bytes = 2.0 * 4.0 * c * resid
     entry("update", "mfma", upd_flops, "TFLOP/s", PEAK_MFMA_F32_TFLOPS, ph["update"],
-          note="rank-B update W[:, j1:] -= Lambda P_k, fp32 products as 6 bf16 MFMAs")
+          note="rank-B update W[:, j1:] -= Lambda P_k, fp32 products as 3 fp16 MFMAs (operands "
+               "split in two; 6 bf16 MFMAs for blocks of up to 64 columns)")
     entry("update", "hbm", upd_bytes, "GB/s", PEAK_HBM_GBS, ph["update"],
           note="read + write of every residual fp32 weight once per block")
     if out[-2]["frac"] is not None:
@@ -307,7 +308,7 @@ def main():
         "warmup": args.warmup, "ms_per_step": main_res["ms_per_step"], "higher_is_better": False,
         "scaling": "weak", "vs_baseline": None,
         "dtype": ("f16 in / f32 accumulate (Hessian); factor, block rows and trailing update: "
-                  "f32 storage, products as 2-way split fp16 (3 fp16 MFMAs per fp32 product; block "
+                  "f32 storage, products as 2-way split fp16 (3 or 4 fp16 MFMAs per fp32 product; block "
                   "rows: 3-way split bf16, 6 MFMAs); per-row solves f32"),
         "data": "synthetic",
         "config": {"workload": main_res["workload"], "accumulate_calls": args.chunks},

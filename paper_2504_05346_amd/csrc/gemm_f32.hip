@@ -42,11 +42,10 @@ __global__ __launch_bounds__(kXThreads, 4) void k_gemm_f32(GemmArgs g) {
   const int kend = g.b_tri == kTriUpper ? min(g.K, n0 + kTN) : g.K;
   if constexpr (NBUF > 0) {
     const float sb = g.bound_b ? h2_scale(*g.bound_b) : g.sb;
-    gemm_tile_h2<AK, BK, NBUF>(acc, sm, A, g.lda, m_ext, g.sa, nullptr, B, g.ldb, n_ext, sb, {}, nullptr, kbeg, kend, true,
-                         true);
+    gemm_tile_h2<AK, BK, NBUF>(acc, sm, A, g.lda, m_ext, g.sa, nullptr, B, g.ldb, n_ext, sb, {}, nullptr, kbeg, kend);
     g.alpha *= (1.f / g.sa) * (1.f / sb);
   } else {
-    gemm_tile_x3<AK, BK>(acc, sm, A, g.lda, m_ext, B, g.ldb, n_ext, kbeg, kend, true, true);
+    gemm_tile_x3<AK, BK>(acc, sm, A, g.lda, m_ext, B, g.ldb, n_ext, kbeg, kend);
   }
   const float* T = x3_stage_tile(acc, sm);
   // row pass: wavefront w takes rows w, w + 8, ..., lane l the columns 2l, 2l + 1

@@ -12,9 +12,13 @@
 // range, takes six: what is dropped is made up for by half as many roundings of the running sum.
 // 2048 x 2048 products of normal operands against float64, three-way -> two-way: K = 128 1.63 -> 1.43e-7,
 // 512 3.4 -> 2.6e-7, 1024 4.9 -> 3.6e-7, 4096 10 -> 7.1e-7; equal signs, equal operands and rows whose
-// values span e^6 also get better.  Below K = 96 the three-way split is the more accurate one
-// (16: 3.4 against 8.5e-8, 64: 1.10 against 1.13e-7), so short reductions stay there.  Rates, read-modify-write of C included: 10752^2 at K = 512 160 -> 230
-// TFLOP/s, 8192^2 at K = 1024 184 -> 273, K = 4096 198 -> 303.
+// values span e^6 also get better.  Shorter sums round less often, and the three-way split is the more accurate
+// one (16: 3.4 against 8.5e-8, 64: 1.10 against 1.13e-7, equal near 72): the sweep's update stays there up to 64
+// (kUpdShortK), the lowest merges of the inverse and k_gemm_direct take a2 b2 as well.  The products of 32 x 32
+// tiles inside the tiled solver (tile32.h) are parts of sums of up to 256 values and drop it.
+// The bound has to be near the values: from 2^-17 of it down an operand loses a bit per power of two.
+// Rates, read-modify-write of C included: 10752^2 at K = 512 160 -> 230 TFLOP/s, 8192^2 at K = 1024 184 -> 273,
+// K = 4096 198 -> 303.
 //
 // Same division of labour as in gemm_tile_x3.h (four multiplying, four splitting wavefronts, two
 // workgroups per compute unit); four planes instead of six in LDS, 5 instead of 11 vector instructions
@@ -210,9 +214,9 @@ __device__ __forceinline__ void h2_produce(char* smem, int operand, const float*
 
 template <bool KMAJOR, bool ROWS, int NBUF, bool PIECES>
 __device__ __forceinline__ void h2_producer(char* smem, int operand, const float* __restrict__ P, int64_t ld,
-                                            int ext, int kbeg, int kend, bool vec, ScaleH2& sc, int u) {
+                                            int ext, int kbeg, int kend, ScaleH2& sc, int u) {
   const int nslab = (kend - kbeg + kXK - 1) / kXK;
-  const bool fast = vec && (KMAJOR ? ext % 4 == 0 : (kend - kbeg) % 4 == 0);
+  const bool fast = (KMAJOR ? ext : kend - kbeg) % 4 == 0;
   const bool whole = ext == 128 && (kend - kbeg) % kXK == 0;
   if (fast && whole && kend - kbeg == 4 * kXK) h2_produce4<KMAJOR, ROWS, NBUF>(smem, operand, P, ld, ext, kbeg, sc, u);
   else if (fast && whole) h2_produce<KMAJOR, true, false, ROWS, NBUF>(smem, operand, P, ld, ext, kbeg, kend, nslab, sc, u);
@@ -228,8 +232,7 @@ template <bool A_KMAJOR, bool B_KMAJOR, int NBUF, bool A_ROWS = false, bool B_CO
 __device__ __forceinline__ void gemm_tile_h2(TileAcc& acc, char* smem, const float* __restrict__ A,
                                              int64_t lda, int m_ext, float sa, const float* arows,
                                              const float* __restrict__ B, int64_t ldb, int n_ext, float sb,
-                                             const ColScalesH2& bcols, float* inv, int kbeg, int kend, bool vec_a,
-                                             bool vec_b) {
+                                             const ColScalesH2& bcols, float* inv, int kbeg, int kend) {
   static_assert(!A_ROWS || !A_KMAJOR, "rows of A");
   static_assert(!B_COLS || (B_KMAJOR && B_PIECES), "columns of B, four at a time");
   const int tid = threadIdx.x;
@@ -244,9 +247,9 @@ __device__ __forceinline__ void gemm_tile_h2(TileAcc& acc, char* smem, const flo
   if (B_COLS && wave >= 6) load_cols_h2(sc, bcols, n_ext, u);
   __syncthreads();  // previous users of the LDS buffers are done
   if (wave >= 6) {
-    h2_producer<B_KMAJOR, B_COLS, NBUF, B_PIECES>(smem, 1, B, ldb, n_ext, kbeg, kend, vec_b, sc, u);
+    h2_producer<B_KMAJOR, B_COLS, NBUF, B_PIECES>(smem, 1, B, ldb, n_ext, kbeg, kend, sc, u);
   } else if (wave >= 4) {
-    h2_producer<A_KMAJOR, A_ROWS, NBUF, false>(smem, 0, A, lda, m_ext, kbeg, kend, vec_a, sc, u);
+    h2_producer<A_KMAJOR, A_ROWS, NBUF, false>(smem, 0, A, lda, m_ext, kbeg, kend, sc, u);
   } else {
     const int wm = wave >> 1, wn = wave & 1;
     const int lo = lane & 31, hi = lane >> 5;

@@ -245,8 +245,7 @@ __device__ __forceinline__ void x3_produce(char* smem, int operand, const float*
 template <bool A_KMAJOR, bool B_KMAJOR>
 __device__ __forceinline__ void gemm_tile_x3(TileAcc& acc, char* smem, const float* __restrict__ A,
                                              int64_t lda, int m_ext, const float* __restrict__ B,
-                                             int64_t ldb, int n_ext, int kbeg, int kend, bool vec_a,
-                                             bool vec_b) {
+                                             int64_t ldb, int n_ext, int kbeg, int kend) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -255,20 +254,19 @@ __device__ __forceinline__ void gemm_tile_x3(TileAcc& acc, char* smem, const flo
   __syncthreads();  // previous users of the LDS buffers are done
   if (wave >= 4) {
     // ---------------------------------------------------------------- producers
-    // fast path: aligned operand whose extent along the 4-element pieces is a multiple of 4
     const int u = tid & 127;
-    // fast: aligned operand whose extent along the 4-element pieces is a multiple of 4;
+    // fast: operand (of any alignment) whose extent along the 4-element pieces is a multiple of 4;
     // whole: all 128 rows exist and the k range is a whole number of slabs (nothing to zero)
     const bool ktail = (kend - kbeg) % kXK != 0;
     if (wave >= 6) {
-      const bool fast = vec_b && (B_KMAJOR ? n_ext % 4 == 0 : (kend - kbeg) % 4 == 0);
+      const bool fast = (B_KMAJOR ? n_ext : kend - kbeg) % 4 == 0;
       const bool whole = n_ext == 128 && !ktail;
       if (fast && whole && kend - kbeg == 4 * kXK) x3_produce4<B_KMAJOR>(smem, 1, B, ldb, n_ext, kbeg, u);
       else if (fast && whole) x3_produce<B_KMAJOR, true, false>(smem, 1, B, ldb, n_ext, kbeg, kend, nslab, u);
       else if (fast) x3_produce<B_KMAJOR, true, true>(smem, 1, B, ldb, n_ext, kbeg, kend, nslab, u);
       else x3_produce<B_KMAJOR, false, false>(smem, 1, B, ldb, n_ext, kbeg, kend, nslab, u);
     } else {
-      const bool fast = vec_a && (A_KMAJOR ? m_ext % 4 == 0 : (kend - kbeg) % 4 == 0);
+      const bool fast = (A_KMAJOR ? m_ext : kend - kbeg) % 4 == 0;
       const bool whole = m_ext == 128 && !ktail;
       if (fast && whole && kend - kbeg == 4 * kXK) x3_produce4<A_KMAJOR>(smem, 0, A, lda, m_ext, kbeg, u);
       else if (fast && whole) x3_produce<A_KMAJOR, true, false>(smem, 0, A, lda, m_ext, kbeg, kend, nslab, u);

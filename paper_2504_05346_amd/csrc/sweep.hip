@@ -137,7 +137,7 @@ __global__ __launch_bounds__(kXThreads, 4) void k_block_rows(BlockRowsArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const float s0 = a.sc[min(col0 + 2 * lane, a.b - 1)], s1 = a.sc[min(col0 + 2 * lane + 1, a.b - 1)];
   const float mine = a.sc[min(j1 + mrow0 + ((int)threadIdx.x & (kTM - 1)), a.b - 1)];
-  gemm_tile_x3<true, true>(acc, sm, A, a.b, m_ext, Bm, a.b, n_ext, 0, bw, true, true);
+  gemm_tile_x3<true, true>(acc, sm, A, a.b, m_ext, Bm, a.b, n_ext, 0, bw);
   float* const sr = reinterpret_cast<float*>(sm + kXSmemBytes);  // scales of the rows, behind the tile
   if (threadIdx.x < kTM) sr[threadIdx.x] = mine;  // a barrier follows in the staging
   const float* T = x3_stage_tile(acc, sm);
@@ -2164,7 +2164,7 @@ __global__ __launch_bounds__(kXThreads, 4) void k_lam_rows(SolveArgs a) {
   acc_zero(acc);
   // K is symmetric: its rows serve as columns
   gemm_tile_x3<false, false>(acc, sm, a.Z + m0 * a.ldz, a.ldz, m_ext, a.Kc + (int64_t)n0 * a.ldk, a.ldk,
-                             n_ext, 0, a.bw, true, true);
+                             n_ext, 0, a.bw);
   const float* T = x3_stage_tile(acc, sm);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int r = wave; r < m_ext; r += 8) {
@@ -2197,7 +2197,7 @@ struct UpdateArgs {
   int64_t prow0;        // first row of P (= first reduction index)
   int64_t col0, col_end;
   int64_t zj1, zj2;
-  int K, ldl, vec_a;
+  int K, ldl;
   // Unstructured mode: while the new weights are at hand, the columns right of the block are
   // histogrammed for the NEXT block's selection (window around the current threshold, see
   // k_select); hist == nullptr switches this off.
@@ -2270,9 +2270,9 @@ __global__ __launch_bounds__(kXThreads, 4) void k_update(UpdateArgs a) {
   float* const inv = reinterpret_cast<float*>(sm + kUpdInvOffset);
   if constexpr (H2)
     gemm_tile_h2<false, true, 2, true, true, true>(acc, sm, A, a.ldl, m_ext, 1.f, rsc, Bm, a.b, n4, 1.f,
-                                                   {a.pexp + n0, a.b, a.pexp_n}, inv, 0, a.K, a.vec_a, true);
+                                                   {a.pexp + n0, a.b, a.pexp_n}, inv, 0, a.K);
   else
-    gemm_tile_x3<false, true>(acc, sm, A, a.ldl, m_ext, Bm, a.b, n4, 0, a.K, a.vec_a, true);
+    gemm_tile_x3<false, true>(acc, sm, A, a.ldl, m_ext, Bm, a.b, n4, 0, a.K);
   if (threadIdx.x == 0) TL_MARK(1);
   if (win) {
     for (int e = threadIdx.x; e < 2048; e += kXThreads) hw[e] = 0u;  // a barrier follows in the staging
@@ -2927,7 +2927,6 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
       const bool feed = unstructured && j1 + bw < b;  // a next block exists: count its window
       if (feed) win_parts = (int)(grid.x * grid.y);
       UpdateArgs ua{W, lam_sb + loff, w.P, mask, c, b, j1, j1, sb_end, j1, j1 + bw, bw, ldl,
-                    (B % 4 == 0) ? 1 : 0,
                     feed ? w.hist : nullptr, w.below_part, w.cand_n, w.cand, w.st, w.sx, w.sc, rsc,
                     w.pexp + blk * row_tiles * b, (int)ceil_div(bw, kTM)};
       launch_update(s, ua, grid);
@@ -2942,7 +2941,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
       if (pending_join >= 0) THANOS_CHECK(aux.join(pending_join));
       {
         UpdateArgs ua{W, lam_sb, w.P, mask, c, b, sb_start, sb_end, next_end, 0, 0, kk, ldl,
-                      (B % 4 == 0) ? 1 : 0, nullptr, nullptr, nullptr, nullptr,
+                      nullptr, nullptr, nullptr, nullptr,
                       nullptr, nullptr, w.sc, rsc, w.pexp + sbi * super * row_tiles * b,
                       (int)(super * row_tiles)};
         dim3 grid((unsigned)ceil_div(next_end - sb_end, kTN), (unsigned)ceil_div(c, kTM));
@@ -2952,7 +2951,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
       if (next_end < b) {  // rest: right of the next super-block, second stream
         THANOS_CHECK(aux.fork((int)(2 * sbi)));
         UpdateArgs ua{W, lam_sb, w.P, mask, c, b, sb_start, next_end, b, 0, 0, kk, ldl,
-                      (B % 4 == 0) ? 1 : 0, nullptr, nullptr, nullptr, nullptr,
+                      nullptr, nullptr, nullptr, nullptr,
                       nullptr, nullptr, w.sc, rsc, w.pexp + sbi * super * row_tiles * b,
                       (int)(super * row_tiles)};
         dim3 grid((unsigned)ceil_div(b - next_end, kTN), (unsigned)ceil_div(c, kTM));
