@@ -76,7 +76,7 @@ def prune_layer_set(weights: Sequence[torch.Tensor], x_chunks: Iterable[torch.Te
     if min(needs) == 0:
         raise ValueError("options rejected by thanos_prune_workspace_bytes")
     lanes = 1
-    if stream is None:
+    if stream is None and not torch.cuda.is_current_stream_capturing():  # in a graph: one stream
         units = torch.cuda.get_device_properties(dev).multi_processor_count
         lanes = _lanes([W.shape[0] for W in weights], b, max(needs), freed, units)
     # Everything is allocated (and cleared) on the caller's stream before the fork and joined into it again, so
@@ -87,7 +87,7 @@ def prune_layer_set(weights: Sequence[torch.Tensor], x_chunks: Iterable[torch.Te
             spaces.append(torch.empty_like(spaces[0]))
     except torch.OutOfMemoryError:  # fewer lanes, same results
         pass
-    streams, helpers = [stream], []
+    streams, helpers, held = [stream], [], []
     if len(spaces) > 1:
         main = torch.cuda.current_stream(dev)
         ready = main.record_event()
@@ -108,10 +108,11 @@ def prune_layer_set(weights: Sequence[torch.Tensor], x_chunks: Iterable[torch.Te
             if mode == THANOS_NM and b > 16 * block_size and k < len(spaces) - 1:
                 # the sweep has far updates (more than two super-blocks of eight blocks): keep the next lane's
                 # from queueing behind them
-                helpers.append(_borrow(dev))
+                held.append(_borrow(dev))
     finally:
         for helper, side in helpers:
             main.wait_stream(side)
+        for helper, _ in helpers + held:  # the sweeps have joined what they put on the held ones
             lib().thanos_helper_release(helper)
     return results, H
 
