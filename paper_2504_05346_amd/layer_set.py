@@ -17,14 +17,15 @@ from .binding import (THANOS_NM, PruneOpts, _check, lib, thanos_factor, thanos_f
 
 # Sweeps of few rows leave most of the chip idle and run side by side, up to _LANES at a time: on the caller's
 # stream and on helper streams of the library, each with a workspace of its own that its sweeps use in turn.  More
-# than four streams share hardware queues.  In the unstructured mode the selections of concurrent sweeps
-# wait for their own workgroups at grid barriers, at most one of which fits a compute unit: together they launch no
-# more of them than the sweep with the most rows by itself (`sharers`; 3 x 768 x 768 1 % slower than with all).  From about 15 rows per compute unit on the
-# sweeps fill the chip one after the other.  Whole calls on 2 b tokens, one,
-# two, three, four at a time: 3 x 768 x 768 at 50 % 1.42, 1.09, 0.93 ms; 4 x 512 x 2048 4.11, 2.62, 2.60, 2.22;
-# 8 x 128 x 4096 14.6, 8.6, 7.1, 5.9; 3 x 1024 x 8192 17.5, 14.3, 11.3; one and two: 2 x 2048 x 2048 2.86, 2.84.
-# Wider matrices fill the chip with their own updates.  The further workspaces (b x b values and more each) take
-# no more than the factorisation's, which has just been freed, and 64 MiB.
+# than four streams share hardware queues.  In the unstructured mode the selections of concurrent sweeps wait for
+# their own workgroups at grid barriers, at most one of which fits a compute unit: together they launch no more
+# of them than the sweep with the most rows by itself (`sharers`; 3 x 768 x 768 1 % slower than with all of them).
+# Whole calls on 2 b tokens, one, two, three, four at a time: at 50 % 3 x 768 x 768 1.42, 1.09, 0.93 ms, 4 x 512 x 2048
+# 4.11, 2.62, 2.60, 2.22, 8 x 128 x 4096 14.6, 8.6, 7.1, 5.9, 3 x 1024 x 8192 17.5, 14.3, 11.3; n:m one and all:
+# 3 x 768 x 768 0.82, 0.59, 3 x 1280 x 5120 6.7, 4.7, 60 x 64 x 8192 137, 100.  From about 15 rows per compute unit
+# in all on, the sweeps fill the chip by themselves (2 x 2048 x 2048 2.86 and 2.84 ms, n:m 1.90 and 1.89).  The further
+# workspaces (b x b values and more each, hence the limit on b) take no more than the factorisation's, which
+# has just been freed, and 64 MiB.
 _LANES = 4
 _ROWS_PER_UNIT = 15
 _SIDE_BY_SIDE_COLUMNS = 8192
