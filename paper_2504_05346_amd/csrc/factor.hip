@@ -54,8 +54,10 @@ __global__ __launch_bounds__(1024) void k_diag_stats(const float* __restrict__ H
   double s = 0.0;
   for (int e = threadIdx.x; e < n_bounds; e += 1024) bounds[e] = 0.f;
   // eight loads in flight (each touches a page of its own); added in order
+  float d[8];
+  int64_t last = 0;  // what d holds: threadIdx.x + last + 1024 e
   for (int64_t j0 = threadIdx.x; j0 < b; j0 += 8 * 1024) {
-    float d[8];
+    last = j0 - threadIdx.x;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const int64_t j = min(j0 + 1024 * e, b - 1);
@@ -79,7 +81,12 @@ __global__ __launch_bounds__(1024) void k_diag_stats(const float* __restrict__ H
     *lam_out = lam;
     *info = 0;
   }
-  for (int64_t j = threadIdx.x; j < b; j += 1024) d_out[j] = diag_scale(xnorm2[j] + lam);  // its own writes
+  for (int64_t j = threadIdx.x; j < last; j += 1024) d_out[j] = diag_scale(xnorm2[j] + lam);  // its own writes
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int64_t j = threadIdx.x + last + 1024 * e;
+    if (j < b) d_out[j] = diag_scale(d[e] + lam);
+  }
 }
 
 // *bound <- max(*bound, largest of the wavefronts' m), m >= 0 (NaN counts as large)
@@ -93,41 +100,47 @@ __device__ __forceinline__ void raise_bound(float* bound, float m) {
 // H[b-1-j][b-1-i]); identity on the padding; zero above the diagonal of a diagonal block (what lies right
 // of it is never read, and stays as it is).  64x64 tiles through LDS so that both the read of H and the write
 // of A' are coalesced, sixteen loads per thread in flight: 11008 columns 270 -> 135 us (before: 32x32 tiles, zeros in
-// the whole upper triangle).
+// the whole upper triangle).  R rows of threads: with few columns, where the launch waits for its own loads, 16 rows of
+// them have four loads and stores each instead of sixteen (KRP_FIG).
 constexpr int kRpT = 64;
-__global__ __launch_bounds__(256) void k_reverse_pad(const float* __restrict__ H, int64_t b,
-                                                     const float* __restrict__ lam_p,
-                                                     const float* __restrict__ d, float* __restrict__ Ap,
-                                                     int64_t bp) {
+constexpr int64_t kRpFew = 1024;
+template <int R>
+__global__ __launch_bounds__(64 * R) void k_reverse_pad(const float* __restrict__ H, int64_t b,
+                                                        const float* __restrict__ lam_p,
+                                                        const float* __restrict__ d, float* __restrict__ Ap,
+                                                        int64_t bp) {
   __shared__ float t[kRpT][kRpT + 1];
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;  // 64 x 4
+  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;  // 64 x R
   const int64_t i0 = (int64_t)blockIdx.y * kRpT, j0 = (int64_t)blockIdx.x * kRpT;
   if (j0 >= (i0 / NB + 1) * NB) return;
   // A'[i0+r][j0+cidx] = H[b-1-(j0+cidx)][b-1-(i0+r)]: source rows are indexed by cidx,
   // source columns by r.  Load with lanes along r (source columns, contiguous, descending).
   const int64_t sc = b - 1 - (i0 + tx);
-  float v[kRpT / 4];
+  float v[kRpT / R], di[kRpT / R];
 #pragma unroll
-  for (int e = 0; e < kRpT / 4; ++e) {
-    const int64_t sr = b - 1 - (j0 + ty + 4 * e);
+  for (int e = 0; e < kRpT / R; ++e) {
+    const int64_t sr = b - 1 - (j0 + ty + R * e);
     v[e] = H[max(sr, (int64_t)0) * b + max(sc, (int64_t)0)];
   }
 #pragma unroll
-  for (int e = 0; e < kRpT / 4; ++e) {
-    const int64_t sr = b - 1 - (j0 + ty + 4 * e);
-    t[ty + 4 * e][tx] = (sc >= 0 && sr >= sc) ? v[e] : 0.f;  // t[cidx][r]; only the lower triangle is valid
-  }
-  __syncthreads();
+  for (int e = 0; e < kRpT / R; ++e) di[e] = d[max(b - 1 - (i0 + ty + R * e), (int64_t)0)];
   const float lam = *lam_p;
   const int64_t j = j0 + tx;
   const float dj = d[max(b - 1 - j, (int64_t)0)];
-#pragma unroll 4
-  for (int r = ty; r < kRpT; r += 4) {
+#pragma unroll
+  for (int e = 0; e < kRpT / R; ++e) {
+    const int64_t sr = b - 1 - (j0 + ty + R * e);
+    t[ty + R * e][tx] = (sc >= 0 && sr >= sc) ? v[e] : 0.f;  // t[cidx][r]; only the lower triangle is valid
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < kRpT / R; ++e) {
+    const int r = ty + R * e;
     const int64_t i = i0 + r;
     float o;
     if (j > i) o = 0.f;
     else if (i >= b) o = (i == j) ? 1.f : 0.f;
-    else o = (t[tx][r] + ((i == j) ? lam : 0.f)) * (d[b - 1 - i] * dj);
+    else o = (t[tx][r] + ((i == j) ? lam : 0.f)) * (di[e] * dj);
     Ap[i * bp + j] = o;
   }
 }
@@ -591,8 +604,9 @@ thanos_status factor_begin(hipStream_t s, const float* H, int64_t b, float dampi
   hipLaunchKernelGGL(k_diag_stats, dim3(1), dim3(1024), 0, s, H, b, damping, xnorm2, lam, d, d + bp,
                      n_bounds(nb) + (int)bp, info);
   THANOS_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_reverse_pad, dim3((unsigned)(bp / kRpT), (unsigned)(bp / kRpT)), dim3(256), 0,
-                     s, H, b, lam, d, Ap, bp);
+  const dim3 tiles((unsigned)(bp / kRpT), (unsigned)(bp / kRpT));
+  if (b <= kRpFew) hipLaunchKernelGGL(k_reverse_pad<16>, tiles, dim3(1024), 0, s, H, b, lam, d, Ap, bp);
+  else hipLaunchKernelGGL(k_reverse_pad<4>, tiles, dim3(256), 0, s, H, b, lam, d, Ap, bp);
   THANOS_LAUNCH_CHECK();
   return THANOS_OK;
 }
