@@ -19,22 +19,27 @@ from .binding import (THANOS_NM, PruneOpts, _check, lib, thanos_factor, thanos_f
 # stream and on helper streams of the library, each with a workspace of its own that its sweeps use in turn.  More
 # than four streams share hardware queues.  In the unstructured mode the selections of concurrent sweeps wait for
 # their own workgroups at grid barriers, at most one of which fits a compute unit: together they launch no more
-# of them than the sweep with the most rows by itself (`sharers`; 3 x 768 x 768 1 % slower than with all of them).
+# of them than the sweep with the most rows by itself (`sharers`; 3 x 768 x 768 0.76 -> 0.77 ms a call, 3 x 64 x 1024,
+# where that is one workgroup per sweep, 0.94 -> 1.00).
 # Whole calls on 2 b tokens, one, two, three, four at a time: at 50 % 3 x 768 x 768 1.42, 1.09, 0.93 ms, 4 x 512 x 2048
 # 4.11, 2.62, 2.60, 2.22, 8 x 128 x 4096 14.6, 8.6, 7.1, 5.9, 3 x 1024 x 8192 17.5, 14.3, 11.3; n:m one and all:
 # 3 x 768 x 768 0.82, 0.59, 3 x 1280 x 5120 6.7, 4.7, 60 x 64 x 8192 137, 100.  From about 15 rows per compute unit
 # in all on, the sweeps fill the chip by themselves (2 x 2048 x 2048 2.86 and 2.84 ms, n:m 1.90 and 1.89).  The further
 # workspaces (b x b values and more each, hence the limit on b) take no more than the factorisation's, which
 # has just been freed, and 64 MiB.
+# A sweep of one block is over before the next lane has been set up: 3 x 768 x 128 n:m 0.24 ms one after the other, 0.27
+# side by side, 3 x 768 x 256 0.33 both ways.
 _LANES = 4
 _ROWS_PER_UNIT = 15
 _SIDE_BY_SIDE_COLUMNS = 8192
 _SPARE_BYTES = 64 << 20
 
 
-def _lanes(rows, b, need, freed, units) -> int:
+def _lanes(rows, b, block, need, freed, units) -> int:
     """How many sweeps run at once, for matrices of `rows` rows that need workspaces of up to `need` bytes."""
-    if len(rows) < 2 or b > _SIDE_BY_SIDE_COLUMNS or sum(-(-c // 16) * 16 for c in rows) > _ROWS_PER_UNIT * units:
+    if len(rows) < 2 or not 2 * block <= b <= _SIDE_BY_SIDE_COLUMNS:
+        return 1
+    if sum(-(-c // 16) * 16 for c in rows) > _ROWS_PER_UNIT * units:
         return 1
     return min(_LANES, len(rows), 1 + (freed + _SPARE_BYTES) // need)
 
@@ -61,38 +66,49 @@ def prune_layer_set(weights: Sequence[torch.Tensor], x_chunks: Iterable[torch.Te
     thanos_factor(H, damping, U, xnorm2, fws, finfo, stream)
     freed = fws.numel()
     del fws
-    opts, results = [], []
     for W in weights:
-        c = W.shape[0]
         assert W.shape[1] == b and W.device == dev
-        o = PruneOpts(mode=mode, sparsity=float(sparsity), n=n, m=m, block_size=block_size,
-                      damping=damping, outlier_fraction=float(outlier_fraction))
-        o.factor_in, o.xnorm2_in = U.data_ptr(), xnorm2.data_ptr()
-        opts.append(o)
-        results.append({"W": torch.empty((c, b), dtype=torch.float32, device=dev),
-                        "W_cast": torch.empty((c, b), dtype=W.dtype, device=dev) if cast else None,
-                        "mask": torch.empty((c, b), dtype=torch.uint8, device=dev),
-                        "info": torch.zeros((1,), dtype=torch.int32, device=dev)})
-    needs = [thanos_prune_workspace_bytes(W.shape[0], b, o) for W, o in zip(weights, opts)]
-    if min(needs) == 0:
+    rows = [W.shape[0] for W in weights]
+    o = PruneOpts(mode=mode, sparsity=float(sparsity), n=n, m=m, block_size=block_size, damping=damping,
+                  outlier_fraction=float(outlier_fraction))
+    o.factor_in, o.xnorm2_in = U.data_ptr(), xnorm2.data_ptr()
+    need = max(thanos_prune_workspace_bytes(c, b, o) for c in rows)
+    if need == 0:
         raise ValueError("options rejected by thanos_prune_workspace_bytes")
     lanes = 1
     if stream is None and not torch.cuda.is_current_stream_capturing():  # in a graph: one stream
         units = torch.cuda.get_device_properties(dev).multi_processor_count
-        lanes = _lanes([W.shape[0] for W in weights], b, max(needs), freed, units)
+        lanes = _lanes(rows, b, block_size, need, freed, units)
+    spaces = [torch.empty((need,), dtype=torch.uint8, device=dev)]
+
+    def result(W):
+        return {"W": torch.empty(W.shape, dtype=torch.float32, device=dev),
+                "W_cast": torch.empty(W.shape, dtype=W.dtype, device=dev) if cast else None,
+                "mask": torch.empty(W.shape, dtype=torch.uint8, device=dev),
+                "info": torch.zeros((1,), dtype=torch.int32, device=dev)}
+
+    def sweep(W, res, lane, on):
+        # a failed factorisation shows in finfo; the sweeps then run on a meaningless factor
+        thanos_prune_layer_shared(W, H, o, res["W"], res["W_cast"], res["mask"], spaces[lane], res["info"],
+                                  len(spaces), on)
+
+    results = []
+    if lanes == 1:
+        for W in weights:
+            results.append(result(W))
+            sweep(W, results[-1], 0, stream)
+        return results, H
     # Everything is allocated (and cleared) on the caller's stream before the fork and joined into it again, so
     # that to the caller and its allocator the call is work on that stream.
-    spaces = [torch.empty((max(needs),), dtype=torch.uint8, device=dev)]
+    results = [result(W) for W in weights]
     try:
         while len(spaces) < lanes:
             spaces.append(torch.empty_like(spaces[0]))
     except torch.OutOfMemoryError:  # fewer lanes, same results
         pass
-    streams, helpers, held = [stream], [], []
-    if len(spaces) > 1:
-        main = torch.cuda.current_stream(dev)
-        ready = main.record_event()
-        streams = [main]
+    main = torch.cuda.current_stream(dev)
+    ready = main.record_event()
+    streams, helpers, held = [main], [], []
     try:
         # all lanes before the first sweep: the pool lends what a sweep has handed back, with work still queued on
         # it, to the next that asks
@@ -101,11 +117,9 @@ def prune_layer_set(weights: Sequence[torch.Tensor], x_chunks: Iterable[torch.Te
             helpers.append((helper, side))
             side.wait_event(ready)
             streams.append(side)
-        for k, (W, o, res) in enumerate(zip(weights, opts, results)):
+        for k, (W, res) in enumerate(zip(weights, results)):
             lane = k % len(spaces)
-            # a failed factorisation shows in finfo; the sweeps then run on a meaningless factor
-            thanos_prune_layer_shared(W, H, o, res["W"], res["W_cast"], res["mask"], spaces[lane], res["info"],
-                                      len(spaces), streams[lane])
+            sweep(W, res, lane, streams[lane])
             if mode == THANOS_NM and b > 16 * block_size and k < len(spaces) - 1:
                 # the sweep has far updates (more than two super-blocks of eight blocks): keep the next lane's
                 # from queueing behind them

@@ -250,13 +250,14 @@ extern "C" float col(float x) { return thanos::col_scale(x); }
     ([768] * 3, 768, 12 << 20, 3), ([17, 400], 512, 4 << 20, 2), ([2000, 1900], 512, 20 << 20, 1),
     ([64] * 60, 8192, 270 << 20, 4),       # many experts: four workspaces, not sixty
     ([128] * 30, 8192, 275 << 20, 4), ([500] * 4, 5120, 300 << 20, 2), ([768] * 3, 768, 80 << 20, 1),
-    ([64] * 3, 8200, 270 << 20, 1), ([64], 512, 1 << 20, 1)])
+    ([64] * 3, 8200, 270 << 20, 1), ([64], 512, 1 << 20, 1),
+    ([256] * 3, 255, 1 << 20, 1), ([256] * 3, 256, 1 << 20, 3)])  # one block and a little, two blocks
 def test_layer_sets_run_few_sweeps_at_once(rows, b, need, lanes):
     """Streams and workspaces of a layer set are bounded whatever the number of matrices: at most four, the
     further ones in no more memory than the factorisation had, and 64 MiB."""
     from paper_2504_05346_amd.layer_set import _lanes
     freed = 3 * 4 * b * b
-    got = _lanes(rows, b, need, freed, 256)
+    got = _lanes(rows, b, 128, need, freed, 256)
     assert got == lanes
     assert (got - 1) * need <= freed + (64 << 20)
 
@@ -276,7 +277,7 @@ extern "C" int wgs(int64_t c, int units, int sharers) { return thanos::select_wo
         for units in (32, 256, 304):
             assert L.wgs(c, units, 1) == min(-(-c // 16), units, 256)
     for rows in ([768] * 3, [17, 400], [1280] * 3, [64] * 60, [3000, 100, 200], [16, 32, 48, 8], [1920, 1920]):
-        lanes = _lanes(rows, 512, 1 << 20, 1 << 30, 256)
+        lanes = _lanes(rows, 512, 128, 1 << 20, 1 << 30, 256)
         assert lanes == min(4, len(rows))
         at_once = sorted((L.wgs(c, 256, lanes) for c in rows), reverse=True)[:lanes]
         assert sum(n for n in at_once if n > 1) <= max(L.wgs(c, 256, 1) for c in rows)
