@@ -85,14 +85,14 @@ def measure(torch) -> dict:
     its = 17
     p0, p1 = us[:, 8:8 + 4 * its:4], us[:, 9:9 + 4 * its:4]
     c0, c1 = us[:, 10:10 + 4 * its:4], us[:, 11:11 + 4 * its:4]
-    nxt = us[:, 12:12 + 4 * its:4]
     sl = slice(2, its - 1)
     out["nm_far_update_K1024"] = {
         "workgroups": int(len(us)), "launch_span_us": float(us[:, 5].max()),
         "per_slab_of_32_k_us": {"producer_fill_split_store_request": _med((p1 - p0)[:, sl]),
-                                "barrier_to_multiply": _med((c0 - p1)[:, sl]),
-                                "multiply_48_mfma_per_wavefront": _med((c1 - c0)[:, sl]),
-                                "barrier_to_next_fill": _med((nxt[:, :-1] - c1[:, :-1])[:, sl]),
+                                # with two buffers the multiply of a slab runs beside the fill of the next
+                                "barrier_to_next_fill": _med((p0[:, 1:] - p1[:, :-1])[:, sl]),
+                                "multiply_24_mfma_per_wavefront": _med((c1 - c0)[:, sl]),
+                                "wait_for_next_slab": _med((c0[:, 1:] - c1[:, :-1])[:, sl]),
                                 "slab_period": _med(np.diff(p0, axis=1)[:, sl])},
         "per_workgroup_us": {"product_K1024": _med(us[:, 1] - us[:, 0]),
                              "total": _med(us[:, 5] - us[:, 0])}}
