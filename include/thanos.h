@@ -150,9 +150,10 @@ thanos_status thanos_hessian_accumulate(float* H, int64_t b, const void* Xc, tha
  * triangle set to 0) and xnorm2 (b).  U must not alias H.  ws: thanos_factor_workspace_bytes(b)
  * bytes of scratch.  info_dev: device int32; set to 0, or to k > 0 if the pivot of column k
  * (1-based; columns are eliminated from the last to the first) was not positive, in which
- * case U is meaningless.  Arithmetic: fp32 storage; matrix products are computed on the bf16
- * matrix cores from operands split into three bf16 terms each (six partial products summed in
- * fp32, error of the order of one fp32 rounding per product), everything else in plain fp32.
+ * case U is meaningless.  Arithmetic: fp32 storage; matrix products are computed on the fp16
+ * matrix cores from operands scaled by powers of two and split into two fp16 terms each (three or
+ * four partial products summed in fp32, error of the order of one fp32 rounding per product),
+ * everything else in plain fp32.
  */
 thanos_status thanos_factor(const float* H, int64_t b, float damping, float* U, float* xnorm2,
                             void* ws, size_t ws_bytes, int32_t* info_dev, void* stream);
