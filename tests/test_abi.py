@@ -130,3 +130,16 @@ def test_no_oracle_import_in_product():
             if f.endswith((".py", ".hip", ".h")):
                 src = open(os.path.join(dirpath, f)).read()
                 assert "oracle" not in src.replace("CPU oracle", ""), f
+
+
+def test_shared_call_checks_its_arguments(L):
+    """thanos_prune_layer_shared: at least one sharer; everything else as in thanos_prune_layer."""
+    import paper_2504_05346_amd as t
+    fake = ctypes.c_void_p(1 << 20)
+    o = t.PruneOpts(mode=t.THANOS_NM, n=2, m=4, block_size=128, damping=0.01)
+    call = L.thanos_prune_layer_shared
+    for sharers in (0, -3):
+        assert call(fake, t.THANOS_F16, 64, 256, fake, ctypes.byref(o), fake, None, fake, fake, 1 << 30, fake,
+                    sharers, None) == 1
+    assert call(fake, t.THANOS_F16, 64, 256, fake, ctypes.byref(o), fake, None, fake, fake, 16, fake, 3, None) == 3
+    assert call(None, t.THANOS_F16, 64, 256, fake, ctypes.byref(o), fake, None, fake, fake, 1 << 30, fake, 3, None) == 1
