@@ -70,7 +70,7 @@ constexpr int64_t syrk_launch_tokens(int64_t b, int64_t n_tok) {
 // per part with atomics (1.1 TB/s measured, which is why a narrower tile is preferred to a second
 // part).  Start of a call 4 us.  Measured, 16-bit tokens x channels:
 //                     256-wide whole tiles     chosen
-//   2048 x 4096            73 us               192, 1 part     56 us
+//   2048 x 4096            73 us               192, 1 part     47 us
 //   2048 x 2048            67 us               128, 1 part     26 us
 //   32768 x 768            65 us (16 parts)    128, 11 parts   40 us
 // aligned: 16-byte aligned rows (k_syrk16_dma), else k_syrk16.  Rows of any alignment are summed up

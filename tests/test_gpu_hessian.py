@@ -158,3 +158,25 @@ def test_rows_inside_a_wider_matrix(b, T, ldx, col, dtype):
     th.thanos_hessian_accumulate(H, buf[:, col:col + b])
     torch.cuda.synchronize()
     assert _relerr(np.tril(H.cpu().numpy().astype(np.float64)), np.tril(orc.hessian(X))) < 1e-6
+
+
+@pytest.mark.parametrize("b,T", [(1416, 33), (2568, 65), (3080, 40), (4104, 100), (8200, 40)])
+def test_old_values_at_the_edges_of_tiles(b, T):
+    """Tiles that reach past the diagonal or the last row, one part: the lower triangle is added to, what lies
+    above it (read with the tile, here NaN) and behind H stays as it is.  A sum of T products and one old value:
+    at most sqrt(T) + 2 roundings of 2^-24 add up."""
+    import torch
+    import paper_2504_05346_amd as th
+    gen = torch.Generator(device="cuda").manual_seed(b)
+    X = torch.randn((T, b), generator=gen, device="cuda").half()
+    room = torch.full((b * b + 4096,), float("nan"), device="cuda")
+    H = room[:b * b].view(b, b)
+    low = torch.ones((b, b), dtype=torch.bool, device="cuda").tril()
+    H0 = torch.randn((b, b), generator=gen, device="cuda")
+    H[low] = H0[low]
+    print(f"hessian edges b={b} T={T}", flush=True)
+    th.thanos_hessian_accumulate(H, X)
+    torch.cuda.synchronize()
+    want = (H0.double() + X.double().T @ X.double())[low]
+    assert float((H[low] - want).norm() / want.norm()) <= (T ** 0.5 + 2) * 2.0 ** -24
+    assert bool(H[~low].isnan().all()) and bool(room[b * b:].isnan().all())
