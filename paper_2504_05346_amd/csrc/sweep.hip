@@ -346,7 +346,8 @@ struct SelectArgs {
   const unsigned int* below_part;  // keys below the window, one count per update workgroup
   int n_part;                      // update workgroups (tiles) of the previous block
   const unsigned int* cand_n;      // per tile: keys inside the window
-  const uint2* cand;               // per tile: kCandStage x (key, row)
+  const uint2* cand;               // per tile: cand_cap x (key, row)
+  int cand_cap;
   unsigned long long* binlist;     // kBinCap x (row << 32 | key): the threshold's bin
   const int* row_cnt;              // weights the previous block removed from each row
   int* row_cand;                   // per row: keys sharing the bits resolved before the last pass
@@ -556,11 +557,11 @@ __global__ __launch_bounds__(kSelThreads) void k_select(SelectArgs a) {
       //      holds at most kCandStage entries, i.e. up to 6 independent loads per lane ----
       const unsigned int prefix28 = win_lo + (unsigned int)r.bin;
       for (int t = (int)blockIdx.x * RW + wave; t < a.n_part; t += (int)gridDim.x * RW) {
-        const unsigned int n = min(a.cand_n[t], (unsigned int)kCandStage);
-        const uint2* list = a.cand + (size_t)t * kCandStage;
+        const unsigned int n = min(a.cand_n[t], (unsigned int)a.cand_cap);
+        const uint2* list = a.cand + (size_t)t * a.cand_cap;
         uint2 kr[kCandStage / 64];
 #pragma unroll
-        for (int u = 0; u < kCandStage / 64; ++u) kr[u] = list[min(64 * u + lane, kCandStage - 1)];
+        for (int u = 0; u < kCandStage / 64; ++u) kr[u] = list[min(64 * u + lane, a.cand_cap - 1)];
 #pragma unroll
         for (int u = 0; u < kCandStage / 64; ++u)
           if ((unsigned int)(64 * u + lane) < n && (kr[u].x >> wsh) == prefix28) {
@@ -2220,6 +2221,7 @@ struct UpdateArgs {
   const uint8_t* pexp;        // scales of P for the product (rows pexp_n, stride b)
   int pexp_n;
   int gx, gy;                 // tile grid (set by launch_update)
+  int cand_cap;               // entries of a list (k_update: kCandStage)
 };
 
 typedef unsigned short u16u __attribute__((aligned(1)));  // two mask bytes
@@ -2419,6 +2421,157 @@ __global__ __launch_bounds__(kXThreads, 4) void k_update(UpdateArgs a) {
   if (threadIdx.x == 0) TL_MARK(5);
 }
 
+// The same where few tiles are left (two-way split, reduction a multiple of 128).  The kernel above needs 12 us for one
+// round of tiles, most of it the phases of a tile behind each other, while 16 of 256 compute units work at 512 x
+// 512.  Here a wavefront owns 32 x 32 of W and requests all it reads at the start: its operands straight into
+// the registers that the MFMAs read them from, as in k_gemm_direct (lane (lo, hi) holds k = 8 q + 4 hi + c
+// of its row of multipliers and of its column of P), and the old values, which it changes where the sums are.
+// All four partial products: the matrix pipes are idle.  A workgroup is a strip of 32 rows x 128 columns with a
+// count and a list of window keys of its own.  Whole passes: 256 x 256 2:4 146.8 -> 143.0 us, 512 x 512 at 50 % 409 ->
+// 395, 1111 x 1365 1324 -> 1277, three of 768 x 768 1057 -> 1037.
+__global__ __launch_bounds__(256, 2) void k_update_direct(UpdateArgs a) {
+  __shared__ unsigned int below[4], listed;
+  const int lane = threadIdx.x & 63, lo = lane & 31, hi = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int by = (int)blockIdx.x / a.gx, bx = (int)blockIdx.x - by * a.gx;
+  const int64_t m0 = 32 * (int64_t)by, n0 = a.col0 + (int64_t)kTN * bx;
+  const int64_t cg = n0 + 32 * wave + lo, cc = min(cg, a.col_end - 1);  // this lane's column, and one that exists
+  const int rows = (int)min((int64_t)32, a.c - m0);
+  const bool win = a.hist != nullptr && !a.st->none && a.st->pred_try && min(n0 + kTN, a.col_end) > a.zj2;
+  const bool in_block = n0 < a.zj2 && n0 + kTN > a.zj1;
+  if (threadIdx.x == 0) listed = 0u;
+  const float* pa = a.Lam + (m0 + min(lo, rows - 1)) * a.ldl + 4 * hi;
+  const float* pb = a.P + a.prow0 * a.b;  // uniform; the lane's offset has 32 bits
+  const uint32_t ob = (uint32_t)(4 * hi) * (uint32_t)a.b + (uint32_t)cc;
+  f32x4 x[2][8], y[2][8];
+  auto load = [&](int buf, int k) {
+    const float* pk = pb + k * a.b;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      x[buf][q] = *reinterpret_cast<const f32x4u*>(pa + k + 8 * q);
+#pragma unroll
+      for (int e = 0; e < 4; ++e, pk += a.b) y[buf][q][e] = pk[ob];
+      pk += 4 * a.b;
+    }
+  };
+  // what is needed first is requested first (loads return in order)
+  const float sa = a.rsc[m0 + min(lo, rows - 1)];
+  uint32_t ex = 253u;  // a column takes the smallest of its exponents, one per block and 128 rows of it
+  for (int t = 4; t < a.pexp_n; ++t) ex = min(ex, (uint32_t)a.pexp[t * a.b + cc]);
+  uint32_t e4[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) e4[e] = a.pexp[min(e, a.pexp_n - 1) * a.b + cc];
+  const float scol = a.sc[cc];
+  const float sxj = win ? a.sx[cc] : 0.f;
+  load(0, 0);
+  load(1, 64);
+  float old[16];
+  uint8_t mk[16];
+  auto row_of = [&](int r) { return 8 * (r >> 2) + 4 * hi + (r & 3); };
+  float* const Wt = a.W + m0 * a.b;
+  const uint8_t* const Mt = a.mask + m0 * a.b;
+  uint32_t at[16];  // 32 rows of at most 65535 columns
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    at[r] = (uint32_t)min(row_of(r), rows - 1) * (uint32_t)a.b + (uint32_t)cc;
+    old[r] = Wt[at[r]];
+  }
+  if (in_block) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mk[r] = Mt[at[r]];
+  } else {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mk[r] = 0;
+  }
+  const float sb = exponent_scale(min(min(min(e4[0], e4[1]), min(e4[2], e4[3])), ex));
+  f32x16 acc, acc2;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = acc2[r] = 0.f;
+  auto multiply = [&](int buf) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      f16x8 a1, a2, b1, b2;
+      split8_h2(x[buf][2 * m], x[buf][2 * m + 1], sa, a1, a2);
+      split8_h2(y[buf][2 * m], y[buf][2 * m + 1], sb, b1, b2);
+      acc2 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, b2, acc2, 0, 0, 0);
+      acc2 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, b1, acc2, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, b1, acc, 0, 0, 0);
+      acc2 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, b2, acc2, 0, 0, 0);
+    }
+  };
+  for (int k = 128; k < a.K; k += 128) {
+    multiply(0);
+    load(0, k);
+    multiply(1);
+    load(1, k + 64);
+  }
+  multiply(0);
+  multiply(1);
+  const float f = pow2_inv(scol) * pow2_inv(sb);
+  const bool there = cg < a.col_end;
+  const bool z = in_block && cg >= a.zj1 && cg < a.zj2, h = win && there && cg >= a.zj2;
+  const unsigned int wlo = win ? a.st->win_lo : 0u;
+  const int wsh = win ? a.st->win_shift : kWinShiftMin;
+  uint2* const list = a.cand + (size_t)blockIdx.x * a.cand_cap;
+  unsigned int nb = 0;
+  __syncthreads();  // listed == 0
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int row = row_of(r);
+    const float fr = pow2_inv(__shfl(sa, row, 64));
+    const float o = (z && mk[r]) ? 0.f : fmaf(-(acc[r] + acc2[r]), fr * f, old[r]);
+    if (there && row < rows) {
+      Wt[at[r]] = o;
+      if (h) {
+        const unsigned int key = metric_key(o, sxj), bin = key >> wsh;
+        if (bin < wlo) {
+          ++nb;
+        } else if (bin - wlo < 2048u) {
+          atomicAdd(&a.hist[bin - wlo], 1u);
+          const unsigned int k = atomicAdd(&listed, 1u);
+          if (k < (unsigned int)a.cand_cap) list[k] = make_uint2(key, (unsigned int)(m0 + row));
+        }
+      }
+    }
+  }
+  if (a.hist == nullptr) return;
+  for (int off = 32; off > 0; off >>= 1) nb += __shfl_down(nb, off, 64);
+  if (lane == 0) below[wave] = nb;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    a.below_part[blockIdx.x] = below[0] + below[1] + below[2] + below[3];
+    unsigned int n = listed;
+    if (n > (unsigned int)a.cand_cap) {  // no prediction
+      a.st->cand_overflow = 1;
+      n = 0u;
+    }
+    a.cand_n[blockIdx.x] = n;
+  }
+  if (blockIdx.x == 0) {  // as in k_update
+    for (int e = threadIdx.x; e < 3 * 2048; e += 256) a.hist[2048 + e] = 0u;
+    if (threadIdx.x == 0) a.st->arrived = a.st->nbin = a.st->bar = 0u;
+  }
+}
+// 32 x 32 tiles: every operand row is fetched once per tile of 32 columns instead of 128, which pays while the launch
+// waits for its latency.  Limits of 1024, 2048 and 4096: 1111 x 1365 1289, 1277 and 1278 us, 5120 x 5120 4:8 4948, 4988
+// and 5031 (one run to the other 0.6 %).
+constexpr int64_t kUpdDirectTiles = 2048;
+// Counts and lists of its workgroups, four for every tile of the array that k_update keeps its lists in (tiles of them).
+struct DirectLists {
+  unsigned int *below_part, *cand_n;
+  uint2* cand;
+  static constexpr int cap = kCandStage / 4 - 1;
+};
+static inline DirectLists direct_lists(uint2* cand, int64_t tiles) {
+  unsigned int* const n = reinterpret_cast<unsigned int*>(cand);
+  return {n, n + 4 * tiles, cand + 4 * tiles};
+}
+static_assert(4 * (2 * sizeof(unsigned int) + DirectLists::cap * sizeof(uint2)) <= kCandStage * sizeof(uint2), "they fit");
+// Columns of the update from col0 on.
+static inline bool update_direct_ok(int64_t c, int64_t cols, int K) {
+  return K > kUpdShortK && K % 128 == 0 && K <= 512 && ceil_div(c, 32) * ceil_div(cols, kTN) * 4 <= kUpdDirectTiles;
+}
+
 // ------------------------------------------------------------------------------------------
 // Outlier rows (App. G.4.4 / Sec. 4.7): h_i = ||W_i X||^2 = W_i H W_i^T; the ceil(alpha c) rows
 // with the largest h are left untouched.
@@ -2517,6 +2670,10 @@ constexpr int64_t kPickRows = 2560;
 
 static void launch_update(hipStream_t s, UpdateArgs ua, dim3 tiles) {
   ua.gx = (int)tiles.x;
+  if (update_direct_ok(ua.c, ua.col_end - ua.col0, ua.K)) {
+    hipLaunchKernelGGL(k_update_direct, dim3(tiles.x * (unsigned)ceil_div(ua.c, 32)), dim3(256), 0, s, ua);
+    return;
+  }
   ua.gy = (int)tiles.y;
   const unsigned rp = (tiles.y + 7) / 8;
   const unsigned n = tiles.y >= 16 ? 8 * rp * tiles.x : tiles.x * tiles.y;
@@ -2819,7 +2976,9 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
   if (!aux.ok) return THANOS_ERR_HIP;
   int pending_join = -1;
   const int64_t row_tiles = block_row_tiles(B);
-  int win_parts = 0;  // workgroups of the previous block's update (partial counts to sum)
+  int win_parts = 0;  // workgroups of the previous block's update (partial counts to sum) ...
+  DirectLists lists = {w.below_part, w.cand_n, w.cand};  // ... their counts and lists
+  int cand_cap = kCandStage;
   for (int64_t j1 = 0; j1 < b; j1 += B) {
     const int bw = (int)std::min<int64_t>(B, b - j1);
     const int64_t blk = j1 / B;
@@ -2842,10 +3001,11 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
       ga.sx = w.sx;
       ga.st = w.st;
       ga.hist = w.hist;
-      ga.below_part = w.below_part;
+      ga.below_part = lists.below_part;
       ga.n_part = win_parts;
-      ga.cand_n = w.cand_n;
-      ga.cand = w.cand;
+      ga.cand_n = lists.cand_n;
+      ga.cand = lists.cand;
+      ga.cand_cap = cand_cap;
       ga.binlist = w.binlist;
       ga.row_cnt = w.row_cand;
       ga.row_cand = w.row_cand;
@@ -2933,10 +3093,16 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
     {  // this block's update, up to the end of its super-block
       dim3 grid((unsigned)ceil_div(sb_end - j1, kTN), (unsigned)ceil_div(c, kTM));
       const bool feed = unstructured && j1 + bw < b;  // a next block exists: count its window
-      if (feed) win_parts = (int)(grid.x * grid.y);
+      if (feed) {
+        const bool direct = update_direct_ok(c, sb_end - j1, bw);
+        win_parts = (int)(grid.x * (direct ? ceil_div(c, 32) : grid.y));
+        lists = direct ? direct_lists(w.cand, ceil_div(b, kTN) * ceil_div(c, kTM))
+                       : DirectLists{w.below_part, w.cand_n, w.cand};
+        cand_cap = direct ? DirectLists::cap : kCandStage;
+      }
       UpdateArgs ua{W, lam_sb + loff, w.P, mask, c, b, j1, j1, sb_end, j1, j1 + bw, bw, ldl,
-                    feed ? w.hist : nullptr, w.below_part, w.cand_n, w.cand, w.st, w.sx, w.sc, rsc,
-                    w.pexp + blk * row_tiles * b, (int)ceil_div(bw, kTM)};
+                    feed ? w.hist : nullptr, lists.below_part, lists.cand_n, lists.cand, w.st, w.sx, w.sc, rsc,
+                    w.pexp + blk * row_tiles * b, (int)ceil_div(bw, kTM), 0, 0, cand_cap};
       launch_update(s, ua, grid);
       THANOS_LAUNCH_CHECK();
     }
@@ -2951,7 +3117,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
         UpdateArgs ua{W, lam_sb, w.P, mask, c, b, sb_start, sb_end, next_end, 0, 0, kk, ldl,
                       nullptr, nullptr, nullptr, nullptr,
                       nullptr, nullptr, w.sc, rsc, w.pexp + sbi * super * row_tiles * b,
-                      (int)(super * row_tiles)};
+                      (int)(super * row_tiles), 0, 0, 0};
         dim3 grid((unsigned)ceil_div(next_end - sb_end, kTN), (unsigned)ceil_div(c, kTM));
         launch_update(s, ua, grid);
         THANOS_LAUNCH_CHECK();
@@ -2961,7 +3127,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
         UpdateArgs ua{W, lam_sb, w.P, mask, c, b, sb_start, next_end, b, 0, 0, kk, ldl,
                       nullptr, nullptr, nullptr, nullptr,
                       nullptr, nullptr, w.sc, rsc, w.pexp + sbi * super * row_tiles * b,
-                      (int)(super * row_tiles)};
+                      (int)(super * row_tiles), 0, 0, 0};
         dim3 grid((unsigned)ceil_div(b - next_end, kTN), (unsigned)ceil_div(c, kTM));
         launch_update(aux.stream, ua, grid);
         THANOS_LAUNCH_CHECK();

@@ -904,3 +904,33 @@ def test_factor_beside_the_row_losses_has_the_same_bits():
     assert i1 == i2 == 0 and (M1.sum(axis=1) == 0).sum() == 10
     np.testing.assert_array_equal(M1, M2)
     np.testing.assert_array_equal(W1, W2)
+
+
+@pytest.mark.parametrize("mode,kw,c,b,B", [
+    ("nm", dict(n=2, m=4), 31, 129 * 4, 128),          # fewer rows than a tile, 516 columns: 4 in the last strip
+    ("nm", dict(n=2, m=4), 33, 640, 16),               # right of the super-block: eight exponents per column of P
+    ("nm", dict(n=2, m=4), 65, 1300, 128),             # a super-block and a bit
+    ("nm", dict(n=4, m=8), 64, 1024, 512),             # reductions of 512
+    ("unstructured", dict(p=0.5), 1, 384, 128),
+    ("unstructured", dict(p=0.5), 97, 515, 128),       # rows of any alignment, ragged last block
+    ("unstructured", dict(p=0.4), 130, 768, 256),
+    ("unstructured", dict(p=0.5), 1024, 1029, 128)])   # 32 x 9 strips in the first block: 1152 tiles
+def test_update_of_few_tiles(mode, kw, c, b, B):
+    """What the sweep adds to the kept weights, relative to float64 under the same mask, where every update is a
+    launch of few tiles: well-conditioned H, so that factor, block rows, solve and update are off by some 2^-24
+    each, in sums of up to b values of either sign; 2^-20 as for single blocks, times two for the blocks in turn."""
+    from tests.gpu_util import gpu_prune
+    H32 = _near_identity(b, seed=b + B)
+    W = np.random.default_rng(c).standard_normal((c, b)).astype(np.float32)
+    W /= np.sqrt(np.diag(H32))
+    print(f"few tiles {mode} {c}x{b} B={B}", flush=True)
+    Wg, Mg, info = gpu_prune(W, H32, mode=mode, B=B, damp=0.0, **kw)
+    assert info == 0
+    if mode == "unstructured":
+        assert int(Mg.sum()) == orc.num_to_remove(kw["p"], c, b)
+    Wt, _ = orc.prune_fast(W, H32.astype(np.float64), mode="unstructured", p=0.0, B=B, damp=0.0, mask_in=Mg)
+    kept = Mg == 0
+    d = np.sqrt(np.diag(H32).astype(np.float64))[None, :]
+    e = np.linalg.norm(((Wg - Wt) * d)[kept]) / np.linalg.norm(((Wt - W) * d)[kept])
+    print(f"  {e:.2e}", flush=True)
+    assert np.all(Wg[Mg == 1] == 0.0) and e <= 2.0 ** -19
