@@ -469,6 +469,80 @@ __global__ __launch_bounds__(kXThreads, 4) void k_trinv_X(TrinvArgs a) {
                    -(1.f / sa) * (1.f / sb), a.bound_inv + gj);
 }
 
+// The same products where a launch has few tiles, as in k_gemm_direct: a wavefront owns 32 x 32 of the result and
+// fetches its operands straight into the registers that the MFMAs read them from, 64 k-values ahead.  For the last
+// merges of a factorisation, which have nothing beside them: a layer of 512 columns 393 -> 388 us, 5120 4997 -> 4957.
+template <bool SECOND>
+__global__ __launch_bounds__(256, 2) void k_trinv_direct(TrinvArgs a) {
+  const int lane = threadIdx.x & 63, lo = lane & 31, hi = lane >> 5;
+  const int tj = a.c0 + blockIdx.x, ti = blockIdx.y >> 2, p = a.p0 + blockIdx.z;
+  const int base = 2 * p * a.S;
+  const int gi = base + a.S + ti, gj = base + tj;
+  if (gi >= a.nb) return;
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int64_t i0 = (int64_t)gi * NB + 32 * (blockIdx.y & 3), j0 = (int64_t)gj * NB + 32 * w;
+  const int kb = SECOND ? base + a.S : base;  // factor block where the reduction index starts
+  const float* pa = (SECOND ? a.Linv : a.L) + (i0 + lo) * a.bp + (int64_t)kb * NB + 4 * hi;
+  const float* pb = (SECOND ? a.T : a.Linv) + (int64_t)kb * NB * a.bp + j0;  // uniform; the lane's offset has 32 bits
+  const uint32_t ob = (uint32_t)(4 * hi) * (uint32_t)a.bp + (uint32_t)lo;
+  const int kbeg = SECOND ? 0 : tj * NB, kend = SECOND ? (ti + 1) * NB : a.S * NB;
+  f32x4 x[2][8], y[2][8];
+  auto load = [&](int buf, int k) {
+    const float* pk = pb + k * a.bp;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      x[buf][q] = *reinterpret_cast<const f32x4*>(pa + k + 8 * q);
+#pragma unroll
+      for (int e = 0; e < 4; ++e, pk += a.bp) y[buf][q][e] = pk[ob];
+      pk += 4 * a.bp;
+    }
+  };
+  uint32_t ba = SECOND && lane <= ti ? inv_bound(a, base + a.S + lane) : 0;  // the part of Linv22 that is read
+  load(0, kbeg);
+  load(1, kbeg + 64);
+  if (SECOND)
+    for (int off = 32; off > 0; off >>= 1) ba = max(ba, (uint32_t)__shfl_xor((int)ba, off, 64));
+  const float sa = SECOND ? h2_scale(__uint_as_float(ba)) : h2_scale(kBoundL);
+  const float sb = SECOND ? h2_scale(a.bound_T[gj]) : h2_scale(__uint_as_float(inv_bound(a, gj)));
+  f32x16 acc, acc2;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = acc2[r] = 0.f;
+  auto multiply = [&](int buf) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      f16x8 a1, a2, b1, b2;
+      split8_h2(x[buf][2 * m], x[buf][2 * m + 1], sa, a1, a2);
+      split8_h2(y[buf][2 * m], y[buf][2 * m + 1], sb, b1, b2);
+      acc2 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, b2, acc2, 0, 0, 0);
+      acc2 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, b1, acc2, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, b1, acc, 0, 0, 0);
+      acc2 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, b2, acc2, 0, 0, 0);
+    }
+  };
+#pragma clang loop unroll(disable)
+  for (int k = kbeg + 128; k < kend; k += 128) {
+    multiply(0);
+    __builtin_amdgcn_sched_barrier(0);
+    load(0, k);
+    multiply(1);
+    __builtin_amdgcn_sched_barrier(0);
+    load(1, k + 64);
+  }
+  multiply(0);
+  multiply(1);
+  const float f = (SECOND ? -1.f : 1.f) * pow2_inv(sa) * pow2_inv(sb);
+  float* out = (SECOND ? a.Linv : a.T) + (i0 + 4 * hi) * a.bp + j0 + lo;
+  uint32_t top = 0;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const float v = f * (acc[r] + acc2[r]);
+    out[(int64_t)(8 * (r >> 2) + (r & 3)) * a.bp] = v;
+    top = max(top, __float_as_uint(fabsf(v)));
+  }
+  raise_bound((SECOND ? a.bound_inv : a.bound_T) + gj, __uint_as_float(top));
+}
+constexpr int kTriDirectTiles = 1024, kTriDirectS = 4;  // tiles and reductions as in direct_ok (gemm_f32.hip)
+
 // The lowest level (S = 1) in one launch: Linv21 = -Linv22 (L21 Linv11) for 128x128 blocks, of which each
 // product by itself is mostly launch and latency.  A workgroup owns 32 columns of a pair, a wavefront 32
 // rows: operands straight into the registers of the MFMAs as in k_gemm_direct, split there; the strip of
@@ -707,8 +781,16 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
         // while the factorisation runs, a launch takes at most tri_cap workgroups (one round of
         // the chip's workgroup slots), so that the short kernels of the chain are not queued
         // behind thousands of long-running tiles
+        const bool last = kdone == nb - 1;
+        if (last && S <= kTriDirectS && 16 * S * rows_all * np <= kTriDirectTiles) {
+          const TrinvArgs a{Ap, Linv, Tb, bp, nb, S, p_lo, 0, bound_inv, bound_inv + (1 + level) * nb, bound_first};
+          const dim3 grid((unsigned)S, 4u * (unsigned)rows_all, (unsigned)np);
+          hipLaunchKernelGGL(second ? k_trinv_direct<true> : k_trinv_direct<false>, grid, dim3(256), 0, ts, a);
+          THANOS_LAUNCH_CHECK();
+          continue;
+        }
         int cols = S;
-        if (kdone != nb - 1) cols = std::max(1, std::min(S, tri_cap / (rows_all * np)));
+        if (!last) cols = std::max(1, std::min(S, tri_cap / (rows_all * np)));
         for (int c0 = 0; c0 < S; c0 += cols) {
           TrinvArgs a{Ap, Linv, Tb, bp, nb, S, p_lo, c0, bound_inv, bound_inv + (1 + level) * nb, bound_first};
           dim3 grid((unsigned)std::min(cols, S - c0), (unsigned)rows_all, (unsigned)np);
