@@ -14,12 +14,13 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
                     const float* H, const float* U, const float* xnorm2,
                     const thanos_prune_opts* o, long long r_total, long long n_out, float* W,
                     void* W_cast, uint8_t* mask, void* ws, int32_t* info, bool single_stream,
-                    PhaseTimer* pt, const float* Lfac, int64_t ldL, const float* Ldiag, const float* umax,
+                    PhaseTimer* pt, const float* Lfac, int64_t ldL, const float* Ldiag, const float* Hscale,
+                    const float* umax,
                     bool prepared,
                     bool clear_info, int sharers);
 thanos_status sweep_prepare(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c, int64_t b,
                             const float* H, const thanos_prune_opts* o, long long n_out, float* W,
-                            void* ws, bool beside);
+                            void* ws, const float* d, bool beside);
 size_t structured_workspace_bytes(int64_t c, int64_t b);
 thanos_status structured(hipStream_t st, const void* W_in, thanos_dtype wdt, int64_t c, int64_t b,
                          const float* H, float damping, long long s_cols, long long n_out,
@@ -379,6 +380,7 @@ static thanos_status prune_with_workspace(const void* W_in, thanos_dtype wdt, in
   const float* xn2 = opts->xnorm2_in;
   const float* Lfac = nullptr;  // lower factor of the index-reversed damped Hessian (this call's) ...
   const float* Ldiag = nullptr;  // ... and its scaling
+  const float* Hscale = nullptr;  // scaling of H itself
   const float* umax = nullptr;   // largest magnitudes of the columns of this call's U
   int64_t ldL = 0;
   const long long r_total =
@@ -405,7 +407,7 @@ static thanos_status prune_with_workspace(const void* W_in, thanos_dtype wdt, in
       THANOS_CHECK(factor_begin(s, H, b, opts->damping, xw, p, info_dev));
       THANOS_CHECK(prep.fork(0));
       thanos_status sp = sweep_prepare(prep.stream, W_in, wdt, c, b, H, opts, n_out, W_out, sweep_ws,
-                                       true);
+                                       factor_scale_undamped(p, b), true);
       if (sp != THANOS_OK) return sp;
       THANOS_CHECK(prep.record(1));
       prepared = true;
@@ -418,11 +420,12 @@ static thanos_status prune_with_workspace(const void* W_in, thanos_dtype wdt, in
     xn2 = xw;
     Lfac = factor_L(p, b, &ldL);
     Ldiag = factor_scale(p, b);
+    Hscale = factor_scale_undamped(p, b);
     umax = factor_umax(p, b);
   }
   phase_mark(pt, THANOS_PHASE_PREP);
   thanos_status st = sweep(s, W_in, wdt, c, b, H, U, xn2, opts, r_total, n_out, W_out, W_out_cast,
-                           mask_out, sweep_ws, info_dev, single_stream, pt, Lfac, ldL, Ldiag, umax, prepared,
+                           mask_out, sweep_ws, info_dev, single_stream, pt, Lfac, ldL, Ldiag, Hscale, umax, prepared,
                            opts->factor_in != nullptr, sharers);
   if (pt) {
     const thanos_status tc = pt->collect(opts->phase_ms_out);

@@ -191,6 +191,14 @@ __device__ __forceinline__ int64_t wave_rank(const float* __restrict__ v, int64_
   return r;
 }
 
+// d[j], the power of two with d^2 h in [1, 4) for a diagonal element h (1 where h is not positive or
+// not finite: the factorisation reports those).
+__device__ __forceinline__ float diag_scale(float h) {
+  if (!(h > 0.f) || !(h < INFINITY)) return 1.f;
+  const int e = min(max(ilogbf(h), -124), 124);
+  return ldexpf(1.f, -(e >> 1));
+}
+
 #define THANOS_CHECK(expr)                 \
   do {                                     \
     thanos_status st_ = (expr);            \
@@ -265,19 +273,18 @@ static inline thanos_status convert_out(hipStream_t s, const float* in, void* ou
 namespace thanos {
 
 constexpr int kFactorNB = 128;  // block size of the blocked factorisation
+// Bounds of a symmetric positive definite matrix scaled to a diagonal in [1, 4), of its Schur complements, and of its
+// factor, with room for rounding.
+constexpr float kBoundA = 7.f, kBoundL = 3.f;
+constexpr int kShortK = 64;      // reductions up to here stay on the three-way split (gemm_tile_h2.h)
 
 // C[M x N] (ldc) = beta*C + alpha * op(A) * op(B), fp32 on the matrix cores, 128x128 tiles.
 //   a_kmajor: element (m,k) of op(A) is A[k*lda + m], else A[m*lda + k]
 //   b_kmajor: element (k,n) of op(B) is B[k*ldb + n], else B[n*ldb + k]
 //   lower_only: compute only tiles with tile_row >= tile_col (C square)
-//   b_tri: op(B) (K x N, K == N) is lower triangular (zero for k < n): the reduction of an output
-//          tile starts at its first column; or upper triangular (zero for k > n): it ends at its last
-//   beside: runs next to a chain of short kernels on another stream: one workgroup per compute unit
-enum TriB { kTriNone = 0, kTriLower = 1, kTriUpper = 2 };
 thanos_status gemm_f32(hipStream_t s, bool a_kmajor, bool b_kmajor, int64_t M, int64_t N,
                        int64_t K, float alpha, const float* A, int64_t lda, const float* B,
-                       int64_t ldb, float beta, float* C, int64_t ldc, bool lower_only,
-                       TriB b_tri = kTriNone, bool beside = false);
+                       int64_t ldb, float beta, float* C, int64_t ldc, bool lower_only);
 
 // C = beta*C + alpha * A B^T for operands whose magnitude is bounded (A[m*lda + k], B[n*ldb + k]; bound_b_dev:
 // the bound of B is read from the device instead).  The same precision in half of the matrix instructions.
@@ -286,6 +293,18 @@ thanos_status gemm_bounded(hipStream_t s, int64_t M, int64_t N, int64_t K, float
                            const float* bound_b_dev, float beta, float* C, int64_t ldc, bool lower_only,
                            bool company = false);
 
+// C[M x N] = A B (A[m*lda + k], B[k*ldb + n]) likewise, for an A whose largest magnitudes are known by row (a_top)
+// and a B whose are known by column (b_top) or bounded (bound_b).
+//   b_tri: B (K x N, K == N) is bounded and lower triangular (zero for k < n): the reduction of an output tile
+//          starts at its first column; or upper triangular (zero for k > n): it ends at its last
+//   kd: with kTriLower: A diag(kd)^-1 in the place of A, kd powers of two; a_top is its
+//   row_top: the rows of C raise theirs there (zeroed before), unless nullptr
+//   beside: runs next to a chain of short kernels on another stream: one workgroup per compute unit
+enum TriB { kTriNone = 0, kTriLower = 1, kTriUpper = 2 };
+thanos_status gemm_topped(hipStream_t s, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
+                          const float* a_top, const float* B, int64_t ldb, const float* b_top, float bound_b,
+                          float* C, int64_t ldc, TriB b_tri, const float* kd, float* row_top, bool beside);
+
 thanos_status syrk_accumulate(hipStream_t s, float* H, int64_t b, const void* Xc,
                               thanos_dtype xdt, int64_t n_tok, int64_t ldx, float alpha);
 
@@ -293,7 +312,7 @@ thanos_status syrk_accumulate(hipStream_t s, float* H, int64_t b, const void* Xc
 // in the workspace holds the Cholesky factor L of J D H_d D J, D diagonal with powers of two
 // (U = J L^{-1} J D): factor_L() returns it and its leading dimension, factor_scale() the diagonal of D.
 size_t factor_workspace_bytes(int64_t b);
-// company: a product with gemm_f32(.., beside) runs at the same time on another stream.
+// company: a product with gemm_topped(.., beside) runs at the same time on another stream.
 // single_stream: no helper streams, everything on `s` in enqueue order (nothing is created).
 thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, float* U,
                      float* xnorm2, void* ws, int32_t* info, bool single_stream = false,
@@ -304,12 +323,15 @@ thanos_status factor_begin(hipStream_t s, const float* H, int64_t b, float dampi
                            void* ws, int32_t* info);
 const float* factor_L(const void* ws, int64_t b, int64_t* ld);
 const float* factor_scale(const void* ws, int64_t b);
+// the same for H without damping
+const float* factor_scale_undamped(const void* ws, int64_t b);
 // largest magnitude of each column of U
 const float* factor_umax(const void* ws, int64_t b);
 
-// skip[i] = 1 for the n_out rows of W (c x b fp32) with the largest loss W_i H W_i^T (sweep.hip).
+// skip[i] = 1 for the n_out rows of W (c x b fp32) with the largest loss W_i H W_i^T (sweep.hip).  d: the
+// factorisation's undamped scales for this H; nullptr: they are worked out into d_room (b floats).
 thanos_status row_outliers(hipStream_t s, const float* W, const float* H, int64_t c, int64_t b,
-                           long long n_out, float* Hf, float* T, float* h, uint8_t* skip,
-                           bool beside = false);
+                           long long n_out, float* Hf, float* T, float* h, const float* d, float* d_room,
+                           uint8_t* skip, bool beside = false);
 
 }  // namespace thanos

@@ -30,24 +30,13 @@
 namespace thanos {
 
 constexpr int NB = kFactorNB;
-// Bounds of what the products read (see above), with room for rounding: values of the scaled matrix and
-// of its Schur complements, and of L.
-constexpr float kBoundA = 7.f, kBoundL = 3.f;
-
 // ------------------------------------------------------------------------------------------
-// d[j], the power of two with d^2 h in [1, 4) for a damped diagonal element h (1 where h is not positive or
-// not finite: the factorisation reports those).
-__device__ __forceinline__ float diag_scale(float h) {
-  if (!(h > 0.f) || !(h < INFINITY)) return 1.f;
-  const int e = min(max(ilogbf(h), -124), 124);
-  return ldexpf(1.f, -(e >> 1));
-}
-
 // xnorm2[j] = H[j][j];  lam = damping * mean_j H[j][j]  (sum in fp64, fixed order);  d[j] = the scale of
-// channel j.  Also clears the n_bounds bounds.  One workgroup of 1024 threads.
+// channel j, d0[j] = the same without the damping.  Also clears the n_bounds bounds.  One workgroup of 1024 threads.
 __global__ __launch_bounds__(1024) void k_diag_stats(const float* __restrict__ H, int64_t b,
                                                      float damping, float* __restrict__ xnorm2,
                                                      float* __restrict__ lam_out, float* __restrict__ d_out,
+                                                     float* __restrict__ d0,
                                                      float* __restrict__ bounds, int n_bounds,
                                                      int32_t* __restrict__ info) {
   __shared__ double part[1024];
@@ -81,11 +70,17 @@ __global__ __launch_bounds__(1024) void k_diag_stats(const float* __restrict__ H
     *lam_out = lam;
     *info = 0;
   }
-  for (int64_t j = threadIdx.x; j < last; j += 1024) d_out[j] = diag_scale(xnorm2[j] + lam);  // its own writes
+  for (int64_t j = threadIdx.x; j < last; j += 1024) {  // its own writes
+    d_out[j] = diag_scale(xnorm2[j] + lam);
+    d0[j] = diag_scale(xnorm2[j]);
+  }
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const int64_t j = threadIdx.x + last + 1024 * e;
-    if (j < b) d_out[j] = diag_scale(d[e] + lam);
+    if (j < b) {
+      d_out[j] = diag_scale(d[e] + lam);
+      d0[j] = diag_scale(d[e]);
+    }
   }
 }
 
@@ -647,7 +642,8 @@ const float* factor_L(const void* ws, int64_t b, int64_t* ld) {
 // The scales and the bounds live in the first 128 rows of the inverse's temporary, which no merge writes
 // (its tile rows belong to second halves): bp scales, nb bounds of L^{-1}, nb bounds of Tbuf per level
 // (level 0: of what the lowest merges leave),
-// the largest magnitudes of U's bp columns: at most 10 values per block of 128 columns beside twice 128, and
+// the largest magnitudes of U's bp columns, the scales without damping: at most 10 values per block of 128 columns beside
+// three times 128, and
 // there are 128 x 128.
 static inline float* scales(const void* ws, int64_t bp) {
   return reinterpret_cast<float*>(const_cast<char*>(reinterpret_cast<const char*>(ws)) + 256) + 2 * bp * bp;
@@ -664,6 +660,8 @@ const float* factor_umax(const void* ws, int64_t b) {
   return scales(ws, bp) + bp + n_bounds((int)(bp / NB));
 }
 
+const float* factor_scale_undamped(const void* ws, int64_t b) { return factor_umax(ws, b) + padded(b); }
+
 size_t factor_workspace_bytes(int64_t b) {
   const int64_t bp = padded(b);
   return 3 * (size_t)bp * bp * sizeof(float) + 256;
@@ -676,8 +674,8 @@ thanos_status factor_begin(hipStream_t s, const float* H, int64_t b, float dampi
   float* Ap = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + 256);
   const int nb = (int)(bp / NB);
   float* d = scales(ws, bp);
-  hipLaunchKernelGGL(k_diag_stats, dim3(1), dim3(1024), 0, s, H, b, damping, xnorm2, lam, d, d + bp,
-                     n_bounds(nb) + (int)bp, info);
+  hipLaunchKernelGGL(k_diag_stats, dim3(1), dim3(1024), 0, s, H, b, damping, xnorm2, lam, d,
+                     d + 2 * bp + n_bounds(nb), d + bp, n_bounds(nb) + (int)bp, info);
   THANOS_LAUNCH_CHECK();
   const dim3 tiles((unsigned)(bp / kRpT), (unsigned)(bp / kRpT));
   if (b <= kRpFew) hipLaunchKernelGGL(k_reverse_pad<16>, tiles, dim3(1024), 0, s, H, b, lam, d, Ap, bp);

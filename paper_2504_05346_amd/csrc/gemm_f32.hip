@@ -1,6 +1,6 @@
 // fp32 matrix product on the 16-bit matrix cores: split bf16 for operands of any range
-// (gemm_tile_x3.h: sweep, row losses, structured update, fp32 Hessian accumulation), split fp16 where
-// the range is known (gemm_tile_h2.h: the factorisation; the sweep's update has a kernel of its own).
+// (gemm_tile_x3.h: sweep, fp32 Hessian accumulation), split fp16 where the range is known (gemm_tile_h2.h: the
+// factorisation, row losses, structured update; the sweep's update has a kernel of its own).
 #include <algorithm>
 
 #include "gemm_tile_h2.h"
@@ -16,7 +16,6 @@ struct GemmArgs {
   float alpha, beta;
   int lower_only;
   int vec_a, vec_b;  // 16-byte aligned rows (k_gemm_direct)
-  int b_tri;  // TriB
   float sa, sb;          // H2: scales of the operands ...
   const float* bound_b;  // ... of B from a bound on the device instead, unless nullptr
 };
@@ -25,12 +24,7 @@ struct GemmArgs {
 template <bool AK, bool BK, int NBUF = 0>
 __global__ __launch_bounds__(kXThreads, 4) void k_gemm_f32(GemmArgs g) {
   extern __shared__ __attribute__((aligned(16))) char sm[];
-  // Triangular op(B): tiles differ in the length of their reduction, and the longest go first (a
-  // whole column of tiles at a time), so that the short ones fill the last round: 4096^3, lower
-  // triangle, 619 -> 392 us against tiles in row order.
-  const int tn = g.b_tri == kTriNone ? blockIdx.x
-                 : g.b_tri == kTriLower ? blockIdx.y : gridDim.y - 1 - blockIdx.y;
-  const int tm = g.b_tri == kTriNone ? blockIdx.y : blockIdx.x;
+  const int tn = blockIdx.x, tm = blockIdx.y;
   if (g.lower_only && tn > tm) return;
   const int m0 = tm * kTM, n0 = tn * kTN;
   const int m_ext = min(kTM, g.M - m0), n_ext = min(kTN, g.N - n0);
@@ -38,14 +32,12 @@ __global__ __launch_bounds__(kXThreads, 4) void k_gemm_f32(GemmArgs g) {
   const float* B = BK ? g.B + n0 : g.B + (int64_t)n0 * g.ldb;
   TileAcc acc;
   acc_zero(acc);
-  const int kbeg = g.b_tri == kTriLower ? n0 : 0;
-  const int kend = g.b_tri == kTriUpper ? min(g.K, n0 + kTN) : g.K;
   if constexpr (NBUF > 0) {
     const float sb = g.bound_b ? h2_scale(*g.bound_b) : g.sb;
-    gemm_tile_h2<AK, BK, NBUF>(acc, sm, A, g.lda, m_ext, g.sa, nullptr, B, g.ldb, n_ext, sb, {}, nullptr, kbeg, kend);
+    gemm_tile_h2<AK, BK, NBUF>(acc, sm, A, g.lda, m_ext, g.sa, nullptr, B, g.ldb, n_ext, sb, {}, nullptr, 0, g.K);
     g.alpha *= (1.f / g.sa) * (1.f / sb);
   } else {
-    gemm_tile_x3<AK, BK>(acc, sm, A, g.lda, m_ext, B, g.ldb, n_ext, kbeg, kend);
+    gemm_tile_x3<AK, BK>(acc, sm, A, g.lda, m_ext, B, g.ldb, n_ext, 0, g.K);
   }
   const float* T = x3_stage_tile(acc, sm);
   // row pass: wavefront w takes rows w, w + 8, ..., lane l the columns 2l, 2l + 1
@@ -78,6 +70,70 @@ __global__ __launch_bounds__(kXThreads, 4) void k_gemm_f32(GemmArgs g) {
       }
     }
   }
+}
+
+// C = A B (B[k*ldb + n]) on the two-way split, the scales from the largest magnitudes of the rows of A and, of B, from
+// those of its columns (not triangular) or from a bound (triangular).  Lower triangle: A diag(kd)^-1 in the place of
+// A.  row_top: the largest magnitudes of the rows of C are raised there, unless nullptr.
+struct ToppedArgs {
+  const float *A, *B;
+  float* C;
+  int64_t lda, ldb, ldc;
+  int M, N, K;
+  const float *a_top, *b_top, *kd;
+  float sb, *row_top;
+};
+constexpr size_t kToppedInv = kXSmemBytes;  // reciprocal scales of the columns, behind the staged tile
+static_assert(kToppedInv + kTN * sizeof(float) <= kH2SmemBytes, "both fit");
+template <TriB TRI>
+__global__ __launch_bounds__(kXThreads, 4) void k_gemm_topped(ToppedArgs g) {
+  extern __shared__ __attribute__((aligned(16))) char sm[];
+  // Triangular B: tiles differ in the length of their reduction, and the longest go first (a
+  // whole column of tiles at a time), so that the short ones fill the last round: 4096^3, lower
+  // triangle, 619 -> 392 us against tiles in row order (three-way split).
+  const int tn = TRI == kTriNone ? blockIdx.x : TRI == kTriLower ? blockIdx.y : gridDim.y - 1 - blockIdx.y;
+  const int tm = TRI == kTriNone ? blockIdx.y : blockIdx.x;
+  const int m0 = tm * kTM, n0 = tn * kTN;
+  const int m_ext = min(kTM, g.M - m0), n_ext = min(kTN, g.N - n0);
+  const int kbeg = TRI == kTriLower ? n0 : 0;
+  const int kend = TRI == kTriUpper ? min(g.K, n0 + kTN) : g.K;
+  float* const inv = reinterpret_cast<float*>(sm + kToppedInv);
+  TileAcc acc;
+  acc_zero(acc);
+  constexpr bool kCols = TRI == kTriNone;
+  gemm_tile_h2<false, true, 2, true, kCols, false, true, TRI == kTriLower>(
+      acc, sm, g.A + (int64_t)m0 * g.lda, g.lda, m_ext, 1.f, g.a_top + m0, g.B + n0, g.ldb, n_ext, g.sb, {}, inv, kbeg,
+      kend, g.b_top + n0, g.kd);
+  const float* T = x3_stage_tile(acc, sm);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int c0 = 2 * lane;
+  const float f0 = kCols ? inv[c0] : pow2_inv(g.sb), f1 = kCols ? inv[c0 + 1] : f0;
+  float* Cg = g.C + (int64_t)m0 * g.ldc + n0 + c0;
+  const bool ok0 = c0 < n_ext, ok1 = c0 + 1 < n_ext;
+  uint32_t u[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int row = wave + 8 * i;
+    const float fr = pow2_inv(h2_scale(g.a_top[m0 + min(row, m_ext - 1)]));  // the wavefront's: scalar loads
+    const float2 t = *reinterpret_cast<const float2*>(T + row * kXCLd + c0);
+    const float o0 = t.x * fminf(fr, f0) * fmaxf(fr, f0), o1 = t.y * fminf(fr, f1) * fmaxf(fr, f1);
+    u[i] = max(ok0 ? __float_as_uint(fabsf(o0)) : 0u, ok1 ? __float_as_uint(fabsf(o1)) : 0u);
+    float* p = Cg + (int64_t)row * g.ldc;
+    if (row < m_ext) {
+      if (ok1) *reinterpret_cast<f32x2u*>(p) = f32x2u{o0, o1};
+      else if (ok0) *p = o0;
+    }
+  }
+  if (!g.row_top) return;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) u[i] = max(u[i], (uint32_t)__shfl_xor((int)u[i], off, 64));
+  uint32_t mine = u[0];  // lane i has row wave + 8 i
+#pragma unroll
+  for (int i = 1; i < 16; ++i) mine = lane == i ? u[i] : mine;
+  if (lane < 16 && wave + 8 * lane < m_ext)
+    atomicMax(reinterpret_cast<unsigned int*>(g.row_top) + m0 + wave + 8 * lane, mine);
 }
 
 // C = beta C + alpha A B^T, reduction a multiple of 128: panel, narrow and strip updates of the
@@ -166,7 +222,7 @@ constexpr int64_t kDirectTiles = 1024;
 // Two per unit kept the chain's kernels waiting for whole tiles: its first step took 670 us next to
 // the 690 us product of 5120 columns (now 40).
 constexpr size_t kBesideSmemBytes = 84 * 1024;
-static_assert(kBesideSmemBytes >= kXSmemBytes, "the product itself fits");
+static_assert(kBesideSmemBytes >= kXSmemBytes && kBesideSmemBytes >= kH2SmemBytes, "the products themselves fit");
 
 static inline bool vec_ok(const float* p, int64_t ld) {
   return (reinterpret_cast<uintptr_t>(p) % 16 == 0) && (ld % 4 == 0);
@@ -189,7 +245,7 @@ thanos_status gemm_bounded(hipStream_t s, int64_t M, int64_t N, int64_t K, float
                            bool company) {
   if (M <= 0 || N <= 0) return THANOS_OK;
   GemmArgs g{A, B, C, lda, ldb, ldc, (int)M, (int)N, (int)K, alpha, beta, lower_only ? 1 : 0,
-             vec_ok(A, lda) ? 1 : 0, vec_ok(B, ldb) ? 1 : 0, kTriNone,
+             vec_ok(A, lda) ? 1 : 0, vec_ok(B, ldb) ? 1 : 0,
              h2_scale(bound_a), h2_scale(bound_b), bound_b_dev};
   if (direct_ok(g)) return launch_direct<true>(s, g);
   // two buffers unless the workgroup has to fit beside a larger one
@@ -207,26 +263,42 @@ thanos_status gemm_bounded(hipStream_t s, int64_t M, int64_t N, int64_t K, float
   return THANOS_OK;
 }
 
-thanos_status gemm_f32(hipStream_t s, bool a_kmajor, bool b_kmajor, int64_t M, int64_t N,
-                       int64_t K, float alpha, const float* A, int64_t lda, const float* B,
-                       int64_t ldb, float beta, float* C, int64_t ldc, bool lower_only,
-                       TriB b_tri, bool beside) {
+thanos_status gemm_topped(hipStream_t s, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
+                          const float* a_top, const float* B, int64_t ldb, const float* b_top, float bound_b,
+                          float* C, int64_t ldc, TriB b_tri, const float* kd, float* row_top, bool beside) {
   if (M <= 0 || N <= 0) return THANOS_OK;
-  GemmArgs g{A, B, C, lda, ldb, ldc, (int)M, (int)N, (int)K, alpha, beta, lower_only ? 1 : 0,
-             vec_ok(A, lda) ? 1 : 0, vec_ok(B, ldb) ? 1 : 0, b_tri, 1.f, 1.f, nullptr};
-  if (!a_kmajor && !b_kmajor && b_tri == kTriNone && direct_ok(g)) return launch_direct<false>(s, g);
+  if ((b_tri == kTriLower) != (kd != nullptr) || (b_tri == kTriNone) != (b_top != nullptr))
+    return THANOS_ERR_UNSUPPORTED;  // no caller
+  const ToppedArgs g{A, B, C, lda, ldb, ldc, (int)M, (int)N, (int)K, a_top, b_top, kd, h2_scale(bound_b), row_top};
   dim3 grid((unsigned)ceil_div(N, kTN), (unsigned)ceil_div(M, kTM));
   if (b_tri != kTriNone) std::swap(grid.x, grid.y);
-  void (*kern)(GemmArgs);
-  if (!a_kmajor && !b_kmajor) kern = k_gemm_f32<false, false>;
-  else if (!a_kmajor && b_kmajor) kern = k_gemm_f32<false, true>;
-  else if (a_kmajor && b_kmajor) kern = k_gemm_f32<true, true>;
-  else kern = k_gemm_f32<true, false>;
+  auto* const kern = b_tri == kTriLower ? k_gemm_topped<kTriLower>
+                     : b_tri == kTriUpper ? k_gemm_topped<kTriUpper> : k_gemm_topped<kTriNone>;
   // the limit belongs to the kernel, not to the launch: the same value whoever sets it, or another thread's
   // launch could find it lowered
   THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBesideSmemBytes));
-  hipLaunchKernelGGL(kern, grid, dim3(kXThreads), beside ? kBesideSmemBytes : kXSmemBytes, s, g);
+  hipLaunchKernelGGL(kern, grid, dim3(kXThreads), beside ? kBesideSmemBytes : kH2SmemBytes, s, g);
+  THANOS_LAUNCH_CHECK();
+  return THANOS_OK;
+}
+
+thanos_status gemm_f32(hipStream_t s, bool a_kmajor, bool b_kmajor, int64_t M, int64_t N,
+                       int64_t K, float alpha, const float* A, int64_t lda, const float* B,
+                       int64_t ldb, float beta, float* C, int64_t ldc, bool lower_only) {
+  if (M <= 0 || N <= 0) return THANOS_OK;
+  GemmArgs g{A, B, C, lda, ldb, ldc, (int)M, (int)N, (int)K, alpha, beta, lower_only ? 1 : 0,
+             vec_ok(A, lda) ? 1 : 0, vec_ok(B, ldb) ? 1 : 0, 1.f, 1.f, nullptr};
+  if (!a_kmajor && !b_kmajor && direct_ok(g)) return launch_direct<false>(s, g);
+  const dim3 grid((unsigned)ceil_div(N, kTN), (unsigned)ceil_div(M, kTM));
+  void (*kern)(GemmArgs);
+  if (!a_kmajor && !b_kmajor) kern = k_gemm_f32<false, false>;
+  else if (!a_kmajor) kern = k_gemm_f32<false, true>;
+  else if (b_kmajor) kern = k_gemm_f32<true, true>;
+  else return THANOS_ERR_UNSUPPORTED;  // no caller
+  THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kXSmemBytes));
+  hipLaunchKernelGGL(kern, grid, dim3(kXThreads), kXSmemBytes, s, g);
   THANOS_LAUNCH_CHECK();
   return THANOS_OK;
 }

@@ -14,7 +14,7 @@
 // 512 3.4 -> 2.6e-7, 1024 4.9 -> 3.6e-7, 4096 10 -> 7.1e-7; equal signs, equal operands and rows whose
 // values span e^6 also get better.  Shorter sums round less often, and the three-way split is the more accurate
 // one (16: 3.4 against 8.5e-8, 64: 1.10 against 1.13e-7, equal near 72): the sweep's update stays there up to 64
-// (kUpdShortK), the lowest merges of the inverse and k_gemm_direct take a2 b2 as well.  The products of 32 x 32
+// (kShortK), the lowest merges of the inverse and k_gemm_direct take a2 b2 as well.  The products of 32 x 32
 // tiles inside the tiled solver (tile32.h) are parts of sums of up to 256 values and drop it.
 // The bound has to be near the values: from 2^-17 of it down an operand loses a bit per power of two.
 // Rates, read-modify-write of C included: 10752^2 at K = 512 160 -> 230 TFLOP/s, 8192^2 at K = 1024 184 -> 273,
@@ -82,9 +82,18 @@ struct ScaleH2 {
   ColScalesH2 cols;
   uint32_t first[4];
 };
+template <bool TOPS>
 __device__ __forceinline__ void load_rows_h2(ScaleH2& sc, const float* __restrict__ rows, int ext, int u) {
 #pragma unroll
-  for (int q = 0; q < 8; ++q) sc.row[q] = sc.all * rows[min((u >> 3) + 16 * q, ext - 1)];
+  for (int q = 0; q < 8; ++q) {
+    const float v = rows[min((u >> 3) + 16 * q, ext - 1)];
+    sc.row[q] = TOPS ? h2_scale(v) : sc.all * v;
+  }
+}
+// TOPS, columns of B: from their largest magnitudes (n_ext of them).
+__device__ __forceinline__ void load_col_tops_h2(ScaleH2& sc, const float* __restrict__ tops, int n_ext, int u) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) sc.row[q] = h2_scale(tops[min(4 * (u & 31) + q, n_ext - 1)]);
 }
 // In two steps, so that the requests for the first slab go out in between: the first four rows of exponents are
 // requested, ...
@@ -117,10 +126,16 @@ __device__ __forceinline__ void finish_cols_h2(ScaleH2& sc) {
   for (int q = 0; q < 4; ++q) sc.row[q] = exponent_scale(lo[q]);
 }
 
-template <bool KMAJOR, bool MASKED, bool ROWS>
+// KF: the k-values of a row-major operand are multiplied by kf first (this thread's four of the slab).
+template <bool KMAJOR, bool MASKED, bool ROWS, bool KF>
 __device__ __forceinline__ void slab_store_h2(char* smem, int operand, const SlabRegsX3& rin,
-                                              const ScaleH2& sc, int u) {
+                                              const ScaleH2& sc, int u, const f32x4& kf) {
   SlabRegsX3 r = rin;
+  if (KF) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      r.v[q] = make_float4(r.v[q].x * kf[0], r.v[q].y * kf[1], r.v[q].z * kf[2], r.v[q].w * kf[3]);
+  }
   if (MASKED) {
 #pragma unroll
     for (int q = 0; q < 8; ++q)
@@ -171,70 +186,98 @@ __device__ __forceinline__ void h2_handover() {
   if (NBUF == 1) __syncthreads();
 }
 
+// Reciprocals of this thread's four k-values' divisors in slab it (KF).
+template <bool KF>
+__device__ __forceinline__ f32x4 slab_factors_h2(const float* __restrict__ kd, int it, int klen, int u) {
+  f32x4 f{};
+  if (!KF) return f;
+  const int k = it * kXK + 4 * (u & 7);
+  if ((klen & 3) == 0) {
+    f = *reinterpret_cast<const f32x4u*>(kd + min(k, klen - 4));
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) f[e] = kd[min(k + e, klen - 1)];
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) f[e] = pow2_inv(f[e]);
+  return f;
+}
+
 // The producers of gemm_tile_x3.h with the two-way split; slab it goes to buffer it % NBUF.
-template <bool KMAJOR, bool ROWS, int NBUF>
+template <bool KMAJOR, bool ROWS, int NBUF, bool TOPS, bool KF>
 __device__ __forceinline__ void h2_produce4(char* smem, int operand, const float* __restrict__ P, int64_t ld,
-                                            int ext, int kbeg, ScaleH2& sc, int u) {
+                                            int ext, int kbeg, ScaleH2& sc, int u, const float* __restrict__ kd) {
   SlabSrcX3 src;
   slab_src_x3<KMAJOR>(src, P, ld, ext, kbeg, u);
   SlabRegsX3 r0, r1;
   slab_load_x3<KMAJOR, true>(r0, src, 0, 4 * kXK, P);
   slab_load_x3<KMAJOR, true>(r1, src, 1, 3 * kXK, P);
-  if (KMAJOR && ROWS) finish_cols_h2(sc);
+  f32x4 f[4];
+#pragma unroll
+  for (int it = 0; it < 4; ++it) f[it] = slab_factors_h2<KF>(kd, it, 4 * kXK, u);
+  if (KMAJOR && ROWS && !TOPS) finish_cols_h2(sc);
   char* const second = smem + (NBUF - 1) * kH2Buf;
-  slab_store_h2<KMAJOR, false, ROWS>(smem, operand, r0, sc, u);
+  slab_store_h2<KMAJOR, false, ROWS, KF>(smem, operand, r0, sc, u, f[0]);
   slab_load_x3<KMAJOR, true>(r0, src, 2, 2 * kXK, P);
   h2_handover<NBUF>();
-  slab_store_h2<KMAJOR, false, ROWS>(second, operand, r1, sc, u);
+  slab_store_h2<KMAJOR, false, ROWS, KF>(second, operand, r1, sc, u, f[1]);
   slab_load_x3<KMAJOR, true>(r1, src, 3, kXK, P);
   h2_handover<NBUF>();
-  slab_store_h2<KMAJOR, false, ROWS>(smem, operand, r0, sc, u);
+  slab_store_h2<KMAJOR, false, ROWS, KF>(smem, operand, r0, sc, u, f[2]);
   h2_handover<NBUF>();
-  slab_store_h2<KMAJOR, false, ROWS>(second, operand, r1, sc, u);
+  slab_store_h2<KMAJOR, false, ROWS, KF>(second, operand, r1, sc, u, f[3]);
   h2_handover<NBUF>();
 }
 
-template <bool KMAJOR, bool FAST, bool MASKED, bool ROWS, int NBUF>
+template <bool KMAJOR, bool FAST, bool MASKED, bool ROWS, int NBUF, bool TOPS, bool KF>
 __device__ __forceinline__ void h2_produce(char* smem, int operand, const float* __restrict__ P, int64_t ld,
-                                           int ext, int kbeg, int kend, int nslab, ScaleH2& sc, int u) {
+                                           int ext, int kbeg, int kend, int nslab, ScaleH2& sc, int u,
+                                           const float* __restrict__ kd) {
   SlabSrcX3 src;
   slab_src_x3<KMAJOR>(src, P, ld, ext, kbeg, u);
   const int klen = kend - kbeg;
   SlabRegsX3 r;
   slab_load_x3<KMAJOR, FAST>(r, src, 0, klen, P);
-  if (KMAJOR && ROWS) finish_cols_h2(sc);
+  f32x4 f = slab_factors_h2<KF>(kd, 0, klen, u);
+  if (KMAJOR && ROWS && !TOPS) finish_cols_h2(sc);
   for (int it = 0; it < nslab; ++it) {
     if (operand == 0 && u < 64) TL_MARK(8 + 4 * it);
-    slab_store_h2<KMAJOR, MASKED, ROWS>(smem + (NBUF == 2 ? (it & 1) * kH2Buf : 0), operand, r, sc, u);
+    slab_store_h2<KMAJOR, MASKED, ROWS, KF>(smem + (NBUF == 2 ? (it & 1) * kH2Buf : 0), operand, r, sc, u, f);
     slab_load_x3<KMAJOR, FAST>(r, src, it + 1, klen - (it + 1) * kXK, P);
+    f = slab_factors_h2<KF>(kd, it + 1, klen, u);
     if (operand == 0 && u < 64) TL_MARK(8 + 4 * it + 1);
     h2_handover<NBUF>();
   }
 }
 
-template <bool KMAJOR, bool ROWS, int NBUF, bool PIECES>
+template <bool KMAJOR, bool ROWS, int NBUF, bool PIECES, bool TOPS, bool KF>
 __device__ __forceinline__ void h2_producer(char* smem, int operand, const float* __restrict__ P, int64_t ld,
-                                            int ext, int kbeg, int kend, ScaleH2& sc, int u) {
+                                            int ext, int kbeg, int kend, ScaleH2& sc, int u,
+                                            const float* __restrict__ kd) {
   const int nslab = (kend - kbeg + kXK - 1) / kXK;
   const bool fast = (KMAJOR ? ext : kend - kbeg) % 4 == 0;
   const bool whole = ext == 128 && (kend - kbeg) % kXK == 0;
-  if (fast && whole && kend - kbeg == 4 * kXK) h2_produce4<KMAJOR, ROWS, NBUF>(smem, operand, P, ld, ext, kbeg, sc, u);
-  else if (fast && whole) h2_produce<KMAJOR, true, false, ROWS, NBUF>(smem, operand, P, ld, ext, kbeg, kend, nslab, sc, u);
-  else if (PIECES || fast) h2_produce<KMAJOR, true, true, ROWS, NBUF>(smem, operand, P, ld, ext, kbeg, kend, nslab, sc, u);
-  else h2_produce<KMAJOR, false, false, ROWS, NBUF>(smem, operand, P, ld, ext, kbeg, kend, nslab, sc, u);
+  if (fast && whole && kend - kbeg == 4 * kXK) h2_produce4<KMAJOR, ROWS, NBUF, TOPS, KF>(smem, operand, P, ld, ext, kbeg, sc, u, kd);
+  else if (fast && whole) h2_produce<KMAJOR, true, false, ROWS, NBUF, TOPS, KF>(smem, operand, P, ld, ext, kbeg, kend, nslab, sc, u, kd);
+  else if (PIECES || fast) h2_produce<KMAJOR, true, true, ROWS, NBUF, TOPS, KF>(smem, operand, P, ld, ext, kbeg, kend, nslab, sc, u, kd);
+  else h2_produce<KMAJOR, false, false, ROWS, NBUF, TOPS, KF>(smem, operand, P, ld, ext, kbeg, kend, nslab, sc, u, kd);
 }
 
 // acc += (sa A)[0:128, kbeg:kend] (sb B)[kbeg:kend, 0:128]; otherwise as gemm_tile_x3().  A_ROWS: further
 // scales of the m_ext rows of A.  B_COLS: of the columns of B, instead of sb; their reciprocals end in
 // inv[0:128] (LDS beyond the buffers' use after the product), complete after the next barrier.
-// B_PIECES: the extents of B are multiples of 4.
-template <bool A_KMAJOR, bool B_KMAJOR, int NBUF, bool A_ROWS = false, bool B_COLS = false, bool B_PIECES = false>
+// B_PIECES: the extents of B are multiples of 4.  TOPS: what arows and btops (n_ext values) hold are the largest
+// magnitudes of the rows and columns, not their scales.  KF: column k of A is divided by kd[k], a power of two
+// (arows belongs to the result).
+template <bool A_KMAJOR, bool B_KMAJOR, int NBUF, bool A_ROWS = false, bool B_COLS = false, bool B_PIECES = false,
+          bool TOPS = false, bool KF = false>
 __device__ __forceinline__ void gemm_tile_h2(TileAcc& acc, char* smem, const float* __restrict__ A,
                                              int64_t lda, int m_ext, float sa, const float* arows,
                                              const float* __restrict__ B, int64_t ldb, int n_ext, float sb,
-                                             const ColScalesH2& bcols, float* inv, int kbeg, int kend) {
+                                             const ColScalesH2& bcols, float* inv, int kbeg, int kend,
+                                             const float* btops = nullptr, const float* kd = nullptr) {
   static_assert(!A_ROWS || !A_KMAJOR, "rows of A");
-  static_assert(!B_COLS || (B_KMAJOR && B_PIECES), "columns of B, four at a time");
+  static_assert(!B_COLS || (B_KMAJOR && (B_PIECES || TOPS)), "columns of B, four at a time");
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -243,13 +286,16 @@ __device__ __forceinline__ void gemm_tile_h2(TileAcc& acc, char* smem, const flo
   ScaleH2 sc;
   const int u = tid & 127;
   sc.all = wave >= 6 ? sb : sa;
-  if (A_ROWS && wave >= 4 && wave < 6) load_rows_h2(sc, arows, m_ext, u);
-  if (B_COLS && wave >= 6) load_cols_h2(sc, bcols, n_ext, u);
+  if (A_ROWS && wave >= 4 && wave < 6) load_rows_h2<TOPS>(sc, arows, m_ext, u);
+  if (B_COLS && wave >= 6) {
+    if (TOPS) load_col_tops_h2(sc, btops, n_ext, u);
+    else load_cols_h2(sc, bcols, n_ext, u);
+  }
   __syncthreads();  // previous users of the LDS buffers are done
   if (wave >= 6) {
-    h2_producer<B_KMAJOR, B_COLS, NBUF, B_PIECES>(smem, 1, B, ldb, n_ext, kbeg, kend, sc, u);
+    h2_producer<B_KMAJOR, B_COLS, NBUF, B_PIECES, TOPS, false>(smem, 1, B, ldb, n_ext, kbeg, kend, sc, u, nullptr);
   } else if (wave >= 4) {
-    h2_producer<A_KMAJOR, A_ROWS, NBUF, false>(smem, 0, A, lda, m_ext, kbeg, kend, sc, u);
+    h2_producer<A_KMAJOR, A_ROWS, NBUF, false, TOPS, KF>(smem, 0, A, lda, m_ext, kbeg, kend, sc, u, KF ? kd + kbeg : nullptr);
   } else {
     const int wm = wave >> 1, wn = wave & 1;
     const int lo = lane & 31, hi = lane >> 5;

@@ -20,6 +20,9 @@
 
 namespace thanos {
 
+constexpr int64_t kRowLds = 32 * 1024;  // columns of a row that goes through LDS: 128 KB
+constexpr int64_t kFewCols = 1024;      // a row is a wavefront's work, four go through LDS at a time
+
 // Column losses v[j] = H[j][j] * sum over non-skipped rows of W[i][j]^2, in two steps: fp64
 // partial sums over chunks of rows (blockIdx.y), then the sum of the partials in chunk order.
 __global__ __launch_bounds__(256) void k_col_loss_part(const float* __restrict__ W, int64_t c,
@@ -76,25 +79,59 @@ __global__ __launch_bounds__(256) void k_permute_sym(const float* __restrict__ H
   Hp[x * b + y] = (sx >= sy) ? H[sx * b + sy] : H[sy * b + sx];
 }
 
-// WQ[i][x] = W[i][sigma[x]], x < s.
-__global__ __launch_bounds__(256) void k_gather_cols(const float* __restrict__ W, int64_t b,
-                                                     const int* __restrict__ sigma, int64_t s,
-                                                     float* __restrict__ WQ) {
-  const int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t i = blockIdx.y;
-  if (x >= s) return;
-  WQ[i * s + x] = W[i * b + sigma[x]];
+// WQ[i][x] = W[i][sigma[x]] / d[x], x < s, zeros up to sp, and the largest magnitude of each row (d powers of two:
+// exact); clears z_top.  TPR threads per row: 256, or 64 for rows of up to kFewCols columns.  staged: the row goes
+// through LDS, which takes any order of columns at its own rate: 4096 x 1365 of 4096 47 -> 22 us.
+template <int TPR>
+__global__ __launch_bounds__(256) void k_gather_cols(const float* __restrict__ W, int64_t c, int64_t b,
+                                                     const int* __restrict__ sigma, const float* __restrict__ d,
+                                                     int64_t s, int64_t sp, float* __restrict__ WQ,
+                                                     float* __restrict__ q_top, float* __restrict__ z_top, int staged) {
+  extern __shared__ float row_lds[];
+  __shared__ uint32_t tops[4];
+  const int t = threadIdx.x & (TPR - 1), sub = (int)threadIdx.x / TPR;
+  const int64_t i = (int64_t)blockIdx.x * (256 / TPR) + sub, ic = min(i, c - 1);
+  const float* row = W + ic * b;
+  float* lds = row_lds + sub * b;
+  if (staged) {
+    for (int64_t j = t; j < b; j += 8 * TPR) {
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = row[min(j + TPR * e, b - 1)];
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (j + TPR * e < b) lds[j + TPR * e] = v[e];
+    }
+    __syncthreads();
+  }
+  uint32_t u = 0;
+  if (i < c)
+    for (int64_t x = t; x < sp; x += TPR) {
+      const int col = sigma[x];  // sp <= b
+      const float v = x < s ? (staged ? lds[col] : row[col]) / d[x] : 0.f;
+      WQ[i * sp + x] = v;
+      u = max(u, __float_as_uint(fabsf(v)));
+    }
+  for (int off = 32; off > 0; off >>= 1) u = max(u, (uint32_t)__shfl_xor((int)u, off, 64));
+  if (TPR > 64) {
+    if ((threadIdx.x & 63) == 0) tops[threadIdx.x >> 6] = u;
+    __syncthreads();
+    u = max(max(tops[0], tops[1]), max(tops[2], tops[3]));
+  }
+  if (t == 0 && i < c) {
+    q_top[i] = __uint_as_float(u);
+    z_top[i] = 0.f;
+  }
 }
 
-// M[x][y] = L[b-1-x][b-1-y] / d[x] for x <= y, else 0 (s x s): the inverse of U'_ss (L is the factor of the
-// matrix scaled by d).
-__global__ __launch_bounds__(256) void k_rev_L(const float* __restrict__ L, int64_t ld,
-                                               const float* __restrict__ d, int64_t b, int64_t s,
-                                               float* __restrict__ M) {
+// M[x][y] = L[b-1-x][b-1-y] for x <= y < s, else 0 (sp x sp): the inverse of U'_ss times d[x] in its rows (L is the factor
+// of the matrix scaled by d).
+__global__ __launch_bounds__(256) void k_rev_L(const float* __restrict__ L, int64_t ld, int64_t b, int64_t s,
+                                               int64_t sp, float* __restrict__ M) {
   const int64_t y = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t x = blockIdx.y;
-  if (y >= s) return;
-  M[x * s + y] = (x <= y) ? L[(b - 1 - x) * ld + (b - 1 - y)] / d[x] : 0.f;
+  if (y >= sp) return;
+  M[x * sp + y] = (x <= y && y < s) ? L[(b - 1 - x) * ld + (b - 1 - y)] : 0.f;
 }
 
 // Non-skipped rows: column j sits at position pos = rank[j] of the permuted order;
@@ -202,7 +239,7 @@ thanos_status structured(hipStream_t st, const void* W_in, thanos_dtype wdt, int
 
   const uint8_t* skip_c = nullptr;
   if (n_out > 0) {
-    thanos_status e = row_outliers(st, W, H, c, b, n_out, HB, T, h, skip);
+    thanos_status e = row_outliers(st, W, H, c, b, n_out, HB, T, h, nullptr, v, skip);
     if (e != THANOS_OK) return e;
     skip_c = skip;
   }
@@ -220,27 +257,46 @@ thanos_status structured(hipStream_t st, const void* W_in, thanos_dtype wdt, int
                        sigma);
     THANOS_LAUNCH_CHECK();
   }
+  const int staged = b <= kRowLds ? 1 : 0;
   hipLaunchKernelGGL(k_permute_sym, dim3(bb, (unsigned)b), dim3(256), 0, st, H, b, sigma, HB);
   THANOS_LAUNCH_CHECK();
   thanos_status e = factor(st, HB, b, damping, U, xn2, fws, info, single_stream);
   if (e != THANOS_OK) return e;
-  if (s_cols > 0) {
+  if (s_cols > 0 && s_cols < b) {  // (no kept column: nothing to update)
     const int64_t s = s_cols;
+    // reductions in whole slabs of 32, where that leaves a column of W_Q's buffer free
+    const int64_t s32 = ceil_div(s, 32) * 32, sp = s32 < b ? s32 : s;
     int64_t ldL = 0;
     const float* L = factor_L(fws, b, &ldL);
-    hipLaunchKernelGGL(k_rev_L, dim3((unsigned)ceil_div(s, 256), (unsigned)s), dim3(256), 0, st, L,
-                       ldL, factor_scale(fws, b), b, s, HB);
+    hipLaunchKernelGGL(k_rev_L, dim3((unsigned)ceil_div(sp, 256), (unsigned)sp), dim3(256), 0, st, L,
+                       ldL, b, s, sp, HB);
     THANOS_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_gather_cols, dim3((unsigned)ceil_div(s, 256), (unsigned)c), dim3(256), 0,
-                       st, W, b, sigma, s, WQ);
+    float* const z_top = WQ + c * sp;
+    if (b <= kFewCols) {
+      hipLaunchKernelGGL(k_gather_cols<64>, dim3((unsigned)ceil_div(c, 4)), dim3(256), (size_t)b * 4 * sizeof(float), st,
+                         W, c, b, sigma, factor_scale(fws, b), s, sp, WQ, h, z_top, staged);
+    } else {
+      THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gather_cols<256>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)(kRowLds * sizeof(float))));
+      hipLaunchKernelGGL(k_gather_cols<256>, dim3((unsigned)c), dim3(256), staged ? (size_t)b * sizeof(float) : 0, st,
+                         W, c, b, sigma, factor_scale(fws, b), s, sp, WQ, h, z_top, staged);
+    }
     THANOS_LAUNCH_CHECK();
-    // Z = W_Q U'_ss^{-1}  (c x s), T = Z U'[0:s, :]  (c x b).  The first s columns of T are the removed
-    // ones, which become exact zeros: only the tiles that hold a kept column are computed.
-    e = gemm_f32(st, false, true, c, s, s, 1.f, WQ, s, HB, s, 0.f, Z, s, false, kTriUpper);
-    if (e != THANOS_OK) return e;
+    // Z = W_Q U'_ss^{-1}  (c x s), T = Z U'[0:s, :]  (c x b), on the two-way split: W_Q without the scales of the
+    // factorisation, which are in U'_ss^{-1} (4096 x 4096, 1366 removed, 363 -> 197 us).  The first s columns of T are the
+    // removed ones, which become exact zeros: only the tiles that hold a kept column are computed.
+    // Short reductions stay on the three-way split, which is the more accurate one there (gemm_tile_h2.h): what 300
+    // rows of 128 columns gain, 39 removed, is off float64 by 8.67e-7 and 8.74e-7 with the two-way one.
     const int64_t n0 = s / 128 * 128;
-    e = gemm_f32(st, false, true, c, b - n0, s, 1.f, Z, s, U + n0, b, 0.f, T + n0, b, false);
-    if (e != THANOS_OK) return e;
+    if (sp <= kShortK) {
+      THANOS_CHECK(gemm_f32(st, false, true, c, sp, sp, 1.f, WQ, sp, HB, sp, 0.f, Z, sp, false));
+      THANOS_CHECK(gemm_f32(st, false, true, c, b - n0, sp, 1.f, Z, sp, U + n0, b, 0.f, T + n0, b, false));
+    } else {
+      THANOS_CHECK(gemm_topped(st, c, sp, sp, WQ, sp, h, HB, sp, nullptr, kBoundL, Z, sp, kTriUpper, nullptr, z_top, false));
+      THANOS_CHECK(gemm_topped(st, c, b - n0, sp, Z, sp, z_top, U + n0, b, factor_umax(fws, b) + n0, 0.f, T + n0, b,
+                               kTriNone, nullptr, nullptr, false));
+    }
   }
   const int64_t s = s_cols;
   if (wdt == THANOS_F32)

@@ -2240,7 +2240,6 @@ static_assert(kUpdInvOffset + kTN * sizeof(float) <= kUpdSmemBytes, "both fit");
 // with the block size as the bound of P, whose values get smaller as b grows, updates of 1024 to 2048 products
 // were off by 5.7e-7 at 8192 columns, B = 128, 8.2e-7 at B = 256, 2.1e-6 at 28672 columns; three-way 5.3, 6.6 and
 // 6.0e-7; now 4.4, 5.0 and 4.8e-7.  Price: 0.6 % of 4096x11008 at 50 %.
-constexpr int kUpdShortK = 64;
 template <bool H2>
 __global__ __launch_bounds__(kXThreads, 4) void k_update(UpdateArgs a) {
   extern __shared__ __attribute__((aligned(16))) char sm[];
@@ -2569,7 +2568,7 @@ static inline DirectLists direct_lists(uint2* cand, int64_t tiles) {
 static_assert(4 * (2 * sizeof(unsigned int) + DirectLists::cap * sizeof(uint2)) <= kCandStage * sizeof(uint2), "they fit");
 // Columns of the update from col0 on.
 static inline bool update_direct_ok(int64_t c, int64_t cols, int K) {
-  return K > kUpdShortK && K % 128 == 0 && K <= 512 && ceil_div(c, 32) * ceil_div(cols, kTN) * 4 <= kUpdDirectTiles;
+  return K > kShortK && K % 128 == 0 && K <= 512 && ceil_div(c, 32) * ceil_div(cols, kTN) * 4 <= kUpdDirectTiles;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2578,24 +2577,70 @@ static inline bool update_direct_ok(int64_t c, int64_t cols, int K) {
 // W_i H W_i^T = 2 sum_n W_in sum_{k >= n} W_ik Hl_kn with Hl = the lower triangle of H with its
 // diagonal halved and zeros above it: the product T = W Hl only needs the reduction range
 // k >= n of every output column, i.e. half of the full product.
-__global__ __launch_bounds__(256) void k_lower_half_diag(const float* __restrict__ H, int64_t b,
-                                                         float* __restrict__ Hl) {
-  const int64_t i = blockIdx.y;
+// Channels are scaled by powers of two d as in the factorisation, W' = W D^-1, H' = D H D with a diagonal in [1, 4):
+// nothing changes in the losses, and the product's operands have a known range (gemm_tile_h2.h) whatever the scales
+// of the channels are (undamped: a channel far below the damping keeps its bits).  Where there is no factorisation to
+// take d from:
+__global__ __launch_bounds__(256) void k_loss_scales(const float* __restrict__ H, int64_t b, float* __restrict__ d) {
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (j >= b) return;
-  const float v = (j <= i) ? H[i * b + j] : 0.f;
-  Hl[i * b + j] = (j == i) ? 0.5f * v : v;
+  if (j < b) d[j] = diag_scale(H[j * b + j]);
+}
+// The first nt workgroups (tiles of kHalfRows x 256): Hl, scaled, in the tiles of 128 on and below the diagonal, which
+// are all that the product reads; a thread takes kHalfRows rows of a column, eight in flight.  The others: the largest
+// magnitudes of the rows of W' (NaN counts as large), one wavefront per row.
+constexpr int kHalfRows = 64;
+static_assert(kTN % kHalfRows == 0, "the rows of a thread lie in one tile row");
+__global__ __launch_bounds__(256) void k_loss_prep(const float* __restrict__ H, const float* __restrict__ W, int64_t c,
+                                                   int64_t b, const float* __restrict__ d, float* __restrict__ Hl,
+                                                   float* __restrict__ top, int nx, int nt) {
+  if ((int)blockIdx.x < nt) {
+    const int64_t i0 = (int64_t)(blockIdx.x / nx) * kHalfRows, i1 = min(b, i0 + kHalfRows);
+    const int64_t j = (int64_t)(blockIdx.x % nx) * 256 + threadIdx.x;
+    if (j >= b || j / kTN > i0 / kTN) return;
+    const float dj = d[j];
+    for (int64_t r = i0; r < i1; r += 8) {
+      float v[8], di[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        v[e] = H[max(min(r + e, b - 1), j) * b + j];  // never above the diagonal
+        di[e] = d[min(r + e, b - 1)];
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int64_t i = r + e;
+        if (i < i1) Hl[i * b + j] = j > i ? 0.f : v[e] * (dj * di[e]) * (j == i ? 0.5f : 1.f);
+      }
+    }
+    return;
+  }
+  const int lane = threadIdx.x & 63;
+  const int64_t i = (int64_t)((int)blockIdx.x - nt) * 4 + (threadIdx.x >> 6);
+  if (i >= c) return;
+  const float* row = W + i * b;
+  uint32_t u = 0;
+  for (int64_t j = lane; j < b; j += 8 * 64) {
+    float v[8], g[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      v[e] = row[min(j + 64 * e, b - 1)];
+      g[e] = d[min(j + 64 * e, b - 1)];
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) u = max(u, __float_as_uint(fabsf(v[e] * pow2_inv(g[e]))));
+  }
+  for (int off = 32; off > 0; off >>= 1) u = max(u, (uint32_t)__shfl_xor((int)u, off, 64));
+  if (lane == 0) top[i] = __uint_as_float(u);
 }
 
-// h[i] = 2 sum_j T[i][j] * W[i][j]; one wavefront per row, fp64 sum in a fixed order.
-__global__ __launch_bounds__(256) void k_rowdot(const float* __restrict__ T,
-                                                const float* __restrict__ W, int64_t c, int64_t b,
+// h[i] = 2 sum_j T[i][j] * W[i][j] / d[j]; one wavefront per row, fp64 sum in a fixed order.
+__global__ __launch_bounds__(256) void k_rowdot(const float* __restrict__ T, const float* __restrict__ W,
+                                                const float* __restrict__ d, int64_t c, int64_t b,
                                                 float* __restrict__ h) {
   const int lane = threadIdx.x & 63;
   const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (i >= c) return;
   double acc = 0.0;
-  for (int64_t j = lane; j < b; j += 64) acc += (double)T[i * b + j] * (double)W[i * b + j];
+  for (int64_t j = lane; j < b; j += 64) acc += (double)T[i * b + j] * (double)(W[i * b + j] * pow2_inv(d[j]));
   for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
   if (lane == 0) h[i] = (float)(2.0 * acc);
 }
@@ -2610,17 +2655,23 @@ __global__ __launch_bounds__(256) void k_row_rank(const float* __restrict__ h, i
 }
 
 // skip[i] = 1 for the n_out rows of W (c x b fp32) with the largest loss W_i H W_i^T (H: lower
-// triangle).  Hf (b x b, receives the lower triangle with halved diagonal), T (c x b) and h (c)
-// are scratch.
+// triangle).  Hf (b x b, receives the scaled lower triangle with halved diagonal), T (c x b) and h (c) are
+// scratch.  The product takes the two-way split: errors of the losses against float64, three-way -> two-way, 0.8 ->
+// 0.75e-7 at 64 columns, 1.7 -> 1.4 at 512, 2.1 -> 1.6 at 1364, 2.7 -> 2.1e-7 at 4096; 4096 x 4096
+// 390 -> 252 us, 5120 x 5120 4:8 beside the factorisation 930 -> 640, 4950 -> 4800 us for the whole call.
 thanos_status row_outliers(hipStream_t s, const float* W, const float* H, int64_t c, int64_t b,
-                           long long n_out, float* Hf, float* T, float* h, uint8_t* skip, bool beside) {
-  hipLaunchKernelGGL(k_lower_half_diag, dim3((unsigned)ceil_div(b, 256), (unsigned)b), dim3(256), 0,
-                     s, H, b, Hf);
+                           long long n_out, float* Hf, float* T, float* h, const float* d, float* d_room,
+                           uint8_t* skip, bool beside) {
+  if (!d) {
+    hipLaunchKernelGGL(k_loss_scales, dim3((unsigned)ceil_div(b, 256)), dim3(256), 0, s, H, b, d_room);
+    THANOS_LAUNCH_CHECK();
+    d = d_room;
+  }
+  const int nx = (int)ceil_div(b, 256), nt = nx * (int)ceil_div(b, kHalfRows);
+  hipLaunchKernelGGL(k_loss_prep, dim3((unsigned)(nt + ceil_div(c, 4))), dim3(256), 0, s, H, W, c, b, d, Hf, h, nx, nt);
   THANOS_LAUNCH_CHECK();
-  thanos_status st = gemm_f32(s, false, true, c, b, b, 1.f, W, b, Hf, b, 0.f, T, b, false, kTriLower,
-                              beside);
-  if (st != THANOS_OK) return st;
-  hipLaunchKernelGGL(k_rowdot, dim3((unsigned)ceil_div(c, 4)), dim3(256), 0, s, T, W, c, b, h);
+  THANOS_CHECK(gemm_topped(s, c, b, b, W, b, h, Hf, b, nullptr, kBoundA, T, b, kTriLower, d, nullptr, beside));
+  hipLaunchKernelGGL(k_rowdot, dim3((unsigned)ceil_div(c, 4)), dim3(256), 0, s, T, W, d, c, b, h);
   THANOS_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_row_rank, dim3((unsigned)ceil_div(c, 4)), dim3(256), 0, s, h, c,
                      (int64_t)n_out, skip);
@@ -2677,7 +2728,7 @@ static void launch_update(hipStream_t s, UpdateArgs ua, dim3 tiles) {
   ua.gy = (int)tiles.y;
   const unsigned rp = (tiles.y + 7) / 8;
   const unsigned n = tiles.y >= 16 ? 8 * rp * tiles.x : tiles.x * tiles.y;
-  if (ua.K > kUpdShortK) hipLaunchKernelGGL(k_update<true>, dim3(n), dim3(kXThreads), kUpdSmemBytes, s, ua);
+  if (ua.K > kShortK) hipLaunchKernelGGL(k_update<true>, dim3(n), dim3(kXThreads), kUpdSmemBytes, s, ua);
   else hipLaunchKernelGGL(k_update<false>, dim3(n), dim3(kXThreads), kUpdSmemBytes, s, ua);
 }
 
@@ -2699,7 +2750,7 @@ bool sweep_uses_complement(const thanos_prune_opts* o, int64_t b) {
 
 // Four columns at a time are read from pexp.
 static size_t pexp_bytes(int64_t b, int B) {
-  return kSuper * B > kUpdShortK ? (size_t)(ceil_div(b, B) * block_row_tiles(B) * b + 4) : 0;
+  return kSuper * B > kShortK ? (size_t)(ceil_div(b, B) * block_row_tiles(B) * b + 4) : 0;
 }
 
 size_t sweep_workspace_bytes(int64_t c, int64_t b, int B, bool outliers, int smax, bool comp) {
@@ -2901,14 +2952,14 @@ static void launch_solve(hipStream_t s, SolveArgs a, int smax) {
 // passes prepared = true to sweep().
 thanos_status sweep_prepare(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c, int64_t b,
                             const float* H, const thanos_prune_opts* o, long long n_out, float* W,
-                            void* ws, bool beside) {
+                            void* ws, const float* d, bool beside) {
   const int B = o->block_size;
   const bool outliers = n_out > 0;
   const int smax_all = (o->mode == THANOS_NM && !o->mask_in) ? B / o->m * o->n : B;
   SweepWs w = carve_ws(ws, c, b, B, outliers, smax_all, sweep_uses_complement(o, b));
   THANOS_CHECK(convert_in(s, W_in, wdt, W, c * b));
   if (outliers) {
-    thanos_status st = row_outliers(s, W, H, c, b, n_out, w.Hf, w.T, w.h, w.row_skip, beside);
+    thanos_status st = row_outliers(s, W, H, c, b, n_out, w.Hf, w.T, w.h, d, w.sx, w.row_skip, beside);
     if (st != THANOS_OK) return st;
   }
   return THANOS_OK;
@@ -2918,7 +2969,8 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
                     const float* H, const float* U, const float* xnorm2,
                     const thanos_prune_opts* o, long long r_total, long long n_out, float* W,
                     void* W_cast, uint8_t* mask, void* ws, int32_t* info, bool single_stream,
-                    PhaseTimer* pt, const float* Lfac, int64_t ldL, const float* Ldiag, const float* umax,
+                    PhaseTimer* pt, const float* Lfac, int64_t ldL, const float* Ldiag, const float* Hscale,
+                    const float* umax,
                     bool prepared,
                     bool clear_info, int sharers) {
   const int B = o->block_size;
@@ -2929,7 +2981,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
 
   const bool unstructured = (o->mode == THANOS_UNSTRUCTURED) && o->mask_in == nullptr;
   if (!prepared && outliers)  // the row losses need the converted weights
-    THANOS_CHECK(sweep_prepare(s, W_in, wdt, c, b, H, o, n_out, W, ws, false));
+    THANOS_CHECK(sweep_prepare(s, W_in, wdt, c, b, H, o, n_out, W, ws, Hscale, false));
   const bool conv = !prepared && !outliers;
   const InitArgs ia{W_in, W, c * b, conv ? (int)ceil_div(c * b, 1024) : 0,
                     conv ? convert_vec(W_in, wdt, W, THANOS_F32) : 0, xnorm2, w.sx, umax, w.sc, b,
@@ -2949,7 +3001,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
 
   {
     dim3 grid((unsigned)ceil_div(b, kTN), (unsigned)ceil_div(b, B), (unsigned)ceil_div(B, kTM));
-    BlockRowsArgs a{U, w.P, w.sc, B * super > kUpdShortK ? w.pexp : nullptr, b, B, {nullptr, 0, nullptr, nullptr, 0, 0}};
+    BlockRowsArgs a{U, w.P, w.sc, B * super > kShortK ? w.pexp : nullptr, b, B, {nullptr, 0, nullptr, nullptr, 0, 0}};
     if (comp) {
       const int nt = (int)ceil_div(B, 32);
       a.comp = {Lfac, ldL, Ldiag, w.Kc, nt, (int)grid.z};

@@ -934,3 +934,62 @@ def test_update_of_few_tiles(mode, kw, c, b, B):
     e = np.linalg.norm(((Wg - Wt) * d)[kept]) / np.linalg.norm(((Wt - W) * d)[kept])
     print(f"  {e:.2e}", flush=True)
     assert np.all(Wg[Mg == 1] == 0.0) and e <= 2.0 ** -19
+
+
+@pytest.mark.parametrize("c,b,s", [
+    (130, 200, 1), (33, 200, 64), (130, 200, 65),     # reductions up to 64: three-way split; then two-way
+    (64, 300, 290), (1, 257, 256),                    # no room for whole slabs of 32 in the buffer of the removed columns
+    (131, 1029, 400), (257, 1300, 1000)])             # more columns than the short routes of the gathers take
+def test_structured_update_is_as_exact_as_fp32(c, b, s):
+    """What the update adds to the kept columns, relative to float64 with the same columns removed, on a
+    well-conditioned H: factor and two products of up to 1000 values round at 2^-24 each, sums of either sign gain
+    less than 16 times that; and the kept weights themselves are rounded once more, at 2^-24 of their own size (with
+    one column removed they are 60 times as large as what is added)."""
+    from tests.gpu_util import gpu_prune
+    H32 = _near_identity(b, seed=b + s)
+    W = np.random.default_rng(c).standard_normal((c, b)).astype(np.float32)
+    W /= np.sqrt(np.diag(H32))
+    print(f"structured {c}x{b} s={s}", flush=True)
+    Wg, Mg, info = gpu_prune(W, H32, mode="structured", p=(s - 0.5) / b, damp=0.0)
+    assert info == 0 and (Mg == Mg[0]).all() and Mg[0].sum() == s
+    Q, K = Mg[0] == 1, Mg[0] == 0
+    Hi = np.linalg.inv(H32.astype(np.float64))
+    D = -np.linalg.solve(Hi[np.ix_(Q, Q)].T, W[:, Q].astype(np.float64).T).T @ Hi[np.ix_(Q, K)]
+    d = np.sqrt(np.diag(H32).astype(np.float64))[K]
+    e = np.linalg.norm((Wg[:, K] - (W[:, K] + D)) * d) / np.linalg.norm(D * d)
+    print(f"  {e:.2e}", flush=True)
+    assert np.all(Wg[:, Q] == 0.0)
+    assert e <= 2.0 ** -20 + 2.0 ** -24 * np.linalg.norm(W[:, K] * d) / np.linalg.norm(D * d)
+
+
+@pytest.mark.parametrize("mode,kw,c,b", [
+    ("nm", dict(n=2, m=4, B=128), 130, 516), ("nm", dict(n=2, m=4, B=128), 40, 1300),
+    ("structured", dict(p=0.3), 130, 515), ("structured", dict(p=0.4), 70, 1101)])
+def test_row_losses_of_channels_of_any_scale(mode, kw, c, b):
+    """Outlier rows, undamped: H -> D H D, W -> W D^-1 with powers of two over 2^+-20 leaves every loss as it is, so the
+    same rows stay, and every weight changes by its factor, bit for bit."""
+    from tests.gpu_util import gpu_prune
+    W, H32 = _layer(c, b, 2 * b, "f32", seed=b)
+    d = np.ldexp(np.float32(1.0), np.random.default_rng(c).integers(-20, 21, size=b))
+    print(f"row losses {mode} {c}x{b}", flush=True)
+    W1, M1, i1 = gpu_prune(W, H32, mode=mode, alpha=0.25, damp=0.0, **kw)
+    W2, M2, i2 = gpu_prune((W / d[None, :]).astype(np.float32), (H32 * d[:, None] * d[None, :]).astype(np.float32),
+                           mode=mode, alpha=0.25, damp=0.0, **kw)
+    assert i1 == i2 == 0
+    h = orc.row_losses(W.astype(np.float64), H32.astype(np.float64))
+    stay = ~M1.any(axis=1)
+    assert stay.sum() == orc.num_outlier_rows(0.25, c) and h[stay].min() > h[~stay].max() * (1 - 1e-6)
+    np.testing.assert_array_equal(M1, M2)
+    np.testing.assert_array_equal(W1, W2 * d[None, :])
+
+
+def test_structured_with_every_column_removed():
+    from tests.gpu_util import gpu_prune
+    c, b = 64, 200
+    W, H32 = _layer(c, b, 2 * b, "f32", seed=2)
+    Wg, Mg, info = gpu_prune(W, H32, mode="structured", p=0.5, alpha=0.5)
+    assert info == 0
+    gone = Mg.any(axis=1)
+    assert gone.sum() == 32 and Mg[gone].all()
+    np.testing.assert_array_equal(Wg[gone], 0.0)
+    np.testing.assert_array_equal(Wg[~gone], W[~gone])
