@@ -52,7 +52,14 @@ __global__ __launch_bounds__(256) void k_col_loss_fin(const double* __restrict__
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (j >= b) return;
   double acc = 0.0;
-  for (int ch = 0; ch < nchunk; ++ch) acc += part[(int64_t)ch * b + j];
+  for (int c0 = 0; c0 < nchunk; c0 += 16) {  // sixteen in flight, added in order
+    double p[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) p[e] = part[(int64_t)min(c0 + e, nchunk - 1) * b + j];
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+      if (c0 + e < nchunk) acc += p[e];
+  }
   v[j] = (float)(acc * (double)H[j * b + j]);
 }
 
@@ -68,15 +75,59 @@ __global__ __launch_bounds__(256) void k_col_rank(const float* __restrict__ v, i
   }
 }
 
-// Hp[x][y] = H_sym[sigma[x]][sigma[y]] for y <= x (H given by its lower triangle).
-__global__ __launch_bounds__(256) void k_permute_sym(const float* __restrict__ H, int64_t b,
-                                                     const int* __restrict__ sigma,
-                                                     float* __restrict__ Hp) {
-  const int64_t y = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t x = blockIdx.y;
-  if (y > x || y >= b) return;
-  const int64_t sx = sigma[x], sy = sigma[y];
-  Hp[x * b + y] = (sx >= sy) ? H[sx * b + sy] : H[sy * b + sx];
+// S = the symmetric matrix whose lower triangle is H's, in 64 x 64 tiles on and below the diagonal: a tile goes out
+// as it is and transposed.
+__global__ __launch_bounds__(256) void k_mirror(const float* __restrict__ H, int64_t b, float* __restrict__ S) {
+  __shared__ float t[64][65];
+  if (blockIdx.x > blockIdx.y) return;
+  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+  const int64_t i0 = 64 * (int64_t)blockIdx.y, j0 = 64 * (int64_t)blockIdx.x;
+  const bool diag = i0 == j0;
+  float v[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {  // never above the diagonal
+    const int64_t i = min(i0 + ty + 4 * e, b - 1), j = min(j0 + tx, b - 1);
+    v[e] = H[max(i, j) * b + min(i, j)];
+  }
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int64_t i = i0 + ty + 4 * e, j = j0 + tx;
+    if (i < b && j < b) S[i * b + j] = v[e];
+    t[ty + 4 * e][tx] = v[e];
+  }
+  if (diag) return;
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int64_t i = j0 + ty + 4 * e, j = i0 + tx;
+    if (i < b && j < b) S[i * b + j] = t[tx][ty + 4 * e];
+  }
+}
+
+// Hp[x][y] = S[sigma[x]][sigma[y]] for y <= x, one workgroup per row, which goes through LDS (staged).  Taken from
+// the lower triangle of H, half of the values are columns of it, a cache line each: 4096 columns 82 us, with the
+// mirroring 45.  Few columns (S = H, whole = 0) fit the caches and save a launch.
+__global__ __launch_bounds__(256) void k_permute_sym(const float* __restrict__ S, int64_t b,
+                                                     const int* __restrict__ sigma, float* __restrict__ Hp,
+                                                     int whole, int staged) {
+  extern __shared__ float row_lds[];
+  const int64_t x = blockIdx.x, sx = sigma[x];
+  const float* row = S + sx * b;
+  if (staged) {
+    for (int64_t j = threadIdx.x; j < b; j += 8 * 256) {
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = row[min(j + 256 * e, b - 1)];
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (j + 256 * e < b) row_lds[j + 256 * e] = v[e];
+    }
+    __syncthreads();
+  }
+  for (int64_t y = threadIdx.x; y <= x; y += 256) {
+    const int64_t sy = sigma[y];
+    Hp[x * b + y] = staged ? row_lds[sy] : whole || sx >= sy ? row[sy] : S[sy * b + sx];
+  }
 }
 
 // WQ[i][x] = W[i][sigma[x]] / d[x], x < s, zeros up to sp, and the largest magnitude of each row (d powers of two:
@@ -245,8 +296,10 @@ thanos_status structured(hipStream_t st, const void* W_in, thanos_dtype wdt, int
   }
   const unsigned bb = (unsigned)ceil_div(b, 256);
   {
-    // partial sums live in the (still unused) buffer of U': nchunk * b doubles <= b * b floats
-    int nchunk = (int)std::max<int64_t>(1, std::min<int64_t>(32, c / 64));
+    // chunks for about 1024 workgroups, 32 at least (17664 x 128 54 -> 28 us); the partial sums live in the
+    // (still unused) buffer of U': nchunk * b doubles <= b * b floats
+    const int64_t want = std::max<int64_t>(32, 1024 / bb);
+    int nchunk = (int)std::max<int64_t>(1, std::min<int64_t>(want, c / 64));
     nchunk = (int)std::min<int64_t>(nchunk, std::max<int64_t>(1, b / 2));
     const int64_t rpc = ceil_div(c, nchunk);
     double* part = reinterpret_cast<double*>(U);
@@ -258,7 +311,16 @@ thanos_status structured(hipStream_t st, const void* W_in, thanos_dtype wdt, int
     THANOS_LAUNCH_CHECK();
   }
   const int staged = b <= kRowLds ? 1 : 0;
-  hipLaunchKernelGGL(k_permute_sym, dim3(bb, (unsigned)b), dim3(256), 0, st, H, b, sigma, HB);
+  if (b <= kFewCols) {
+    hipLaunchKernelGGL(k_permute_sym, dim3((unsigned)b), dim3(256), 0, st, H, b, sigma, HB, 0, 0);
+  } else {
+    const unsigned t64 = (unsigned)ceil_div(b, 64);  // into the buffer of U', which the factorisation writes last
+    hipLaunchKernelGGL(k_mirror, dim3(t64, t64), dim3(256), 0, st, H, b, U);
+    THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_permute_sym),
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kRowLds * sizeof(float))));
+    hipLaunchKernelGGL(k_permute_sym, dim3((unsigned)b), dim3(256), staged ? (size_t)b * sizeof(float) : 0, st, U, b,
+                       sigma, HB, 1, staged);
+  }
   THANOS_LAUNCH_CHECK();
   thanos_status e = factor(st, HB, b, damping, U, xn2, fws, info, single_stream);
   if (e != THANOS_OK) return e;
