@@ -98,14 +98,17 @@ __global__ __launch_bounds__(kXThreads, 4) void k_gemm_topped(ToppedArgs g) {
   const int kbeg = TRI == kTriLower ? n0 : 0;
   const int kend = TRI == kTriUpper ? min(g.K, n0 + kTN) : g.K;
   float* const inv = reinterpret_cast<float*>(sm + kToppedInv);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   TileAcc acc;
   acc_zero(acc);
+  float a_top[16];  // of the rows that this wavefront writes out: scalar loads, done by then
+#pragma unroll
+  for (int i = 0; i < 16; ++i) a_top[i] = g.a_top[m0 + min(wave + 8 * i, m_ext - 1)];
   constexpr bool kCols = TRI == kTriNone;
   gemm_tile_h2<false, true, 2, true, kCols, false, true, TRI == kTriLower>(
       acc, sm, g.A + (int64_t)m0 * g.lda, g.lda, m_ext, 1.f, g.a_top + m0, g.B + n0, g.ldb, n_ext, g.sb, {}, inv, kbeg,
       kend, g.b_top + n0, g.kd);
   const float* T = x3_stage_tile(acc, sm);
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int c0 = 2 * lane;
   const float f0 = kCols ? inv[c0] : pow2_inv(g.sb), f1 = kCols ? inv[c0 + 1] : f0;
   float* Cg = g.C + (int64_t)m0 * g.ldc + n0 + c0;
@@ -114,7 +117,7 @@ __global__ __launch_bounds__(kXThreads, 4) void k_gemm_topped(ToppedArgs g) {
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     const int row = wave + 8 * i;
-    const float fr = pow2_inv(h2_scale(g.a_top[m0 + min(row, m_ext - 1)]));  // the wavefront's: scalar loads
+    const float fr = pow2_inv(h2_scale(a_top[i]));
     const float2 t = *reinterpret_cast<const float2*>(T + row * kXCLd + c0);
     const float o0 = t.x * fminf(fr, f0) * fmaxf(fr, f0), o1 = t.y * fminf(fr, f1) * fmaxf(fr, f1);
     u[i] = max(ok0 ? __float_as_uint(fabsf(o0)) : 0u, ok1 ? __float_as_uint(fabsf(o1)) : 0u);

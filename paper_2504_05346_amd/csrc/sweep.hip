@@ -2580,36 +2580,40 @@ static inline bool update_direct_ok(int64_t c, int64_t cols, int K) {
 // Channels are scaled by powers of two d as in the factorisation, W' = W D^-1, H' = D H D with a diagonal in [1, 4):
 // nothing changes in the losses, and the product's operands have a known range (gemm_tile_h2.h) whatever the scales
 // of the channels are (undamped: a channel far below the damping keeps its bits).  Where there is no factorisation to
-// take d from:
+// take d from, and too many columns for k_loss_prep to look at the diagonal itself:
 __global__ __launch_bounds__(256) void k_loss_scales(const float* __restrict__ H, int64_t b, float* __restrict__ d) {
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (j < b) d[j] = diag_scale(H[j * b + j]);
 }
+constexpr int64_t kLossFewCols = 1024;  // a launch less: 4 of the 112 us of 64 x 128
 // The first nt workgroups (tiles of kHalfRows x 256): Hl, scaled, in the tiles of 128 on and below the diagonal, which
-// are all that the product reads; a thread takes kHalfRows rows of a column, eight in flight.  The others: the largest
-// magnitudes of the rows of W' (NaN counts as large), one wavefront per row.
-constexpr int kHalfRows = 64;
+// are all that the product reads; a thread takes kHalfRows rows of a column, all in flight (64 x 128: with 64 rows,
+// eight at a time, 14.8 us).  The others: the largest magnitudes of the rows of W' (NaN counts as large), one wavefront
+// per row.
+constexpr int kHalfRows = 8;
 static_assert(kTN % kHalfRows == 0, "the rows of a thread lie in one tile row");
+// d_out: d is made from the diagonal of H, and left there.
 __global__ __launch_bounds__(256) void k_loss_prep(const float* __restrict__ H, const float* __restrict__ W, int64_t c,
                                                    int64_t b, const float* __restrict__ d, float* __restrict__ Hl,
-                                                   float* __restrict__ top, int nx, int nt) {
+                                                   float* __restrict__ top, int nx, int nt, float* __restrict__ d_out) {
+  auto raw = [&](int64_t j) { return d_out ? H[j * b + j] : d[j]; };
+  auto scale = [&](float v) { return d_out ? diag_scale(v) : v; };
   if ((int)blockIdx.x < nt) {
     const int64_t i0 = (int64_t)(blockIdx.x / nx) * kHalfRows, i1 = min(b, i0 + kHalfRows);
     const int64_t j = (int64_t)(blockIdx.x % nx) * 256 + threadIdx.x;
     if (j >= b || j / kTN > i0 / kTN) return;
-    const float dj = d[j];
-    for (int64_t r = i0; r < i1; r += 8) {
-      float v[8], di[8];
+    const float dj = scale(raw(j));
+    if (d_out && j >= i0 && j < i1) d_out[j] = dj;
+    float v[kHalfRows], di[kHalfRows];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        v[e] = H[max(min(r + e, b - 1), j) * b + j];  // never above the diagonal
-        di[e] = d[min(r + e, b - 1)];
-      }
+    for (int e = 0; e < kHalfRows; ++e) {
+      v[e] = H[max(min(i0 + e, b - 1), j) * b + j];  // never above the diagonal
+      di[e] = raw(min(i0 + e, b - 1));
+    }
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int64_t i = r + e;
-        if (i < i1) Hl[i * b + j] = j > i ? 0.f : v[e] * (dj * di[e]) * (j == i ? 0.5f : 1.f);
-      }
+    for (int e = 0; e < kHalfRows; ++e) {
+      const int64_t i = i0 + e;
+      if (i < i1) Hl[i * b + j] = j > i ? 0.f : v[e] * (dj * scale(di[e])) * (j == i ? 0.5f : 1.f);
     }
     return;
   }
@@ -2623,10 +2627,10 @@ __global__ __launch_bounds__(256) void k_loss_prep(const float* __restrict__ H, 
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       v[e] = row[min(j + 64 * e, b - 1)];
-      g[e] = d[min(j + 64 * e, b - 1)];
+      g[e] = raw(min(j + 64 * e, b - 1));
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) u = max(u, __float_as_uint(fabsf(v[e] * pow2_inv(g[e]))));
+    for (int e = 0; e < 8; ++e) u = max(u, __float_as_uint(fabsf(v[e] * pow2_inv(scale(g[e])))));
   }
   for (int off = 32; off > 0; off >>= 1) u = max(u, (uint32_t)__shfl_xor((int)u, off, 64));
   if (lane == 0) top[i] = __uint_as_float(u);
@@ -2662,13 +2666,19 @@ __global__ __launch_bounds__(256) void k_row_rank(const float* __restrict__ h, i
 thanos_status row_outliers(hipStream_t s, const float* W, const float* H, int64_t c, int64_t b,
                            long long n_out, float* Hf, float* T, float* h, const float* d, float* d_room,
                            uint8_t* skip, bool beside) {
+  float* d_out = nullptr;
   if (!d) {
-    hipLaunchKernelGGL(k_loss_scales, dim3((unsigned)ceil_div(b, 256)), dim3(256), 0, s, H, b, d_room);
-    THANOS_LAUNCH_CHECK();
+    if (b <= kLossFewCols) {
+      d_out = d_room;
+    } else {
+      hipLaunchKernelGGL(k_loss_scales, dim3((unsigned)ceil_div(b, 256)), dim3(256), 0, s, H, b, d_room);
+      THANOS_LAUNCH_CHECK();
+    }
     d = d_room;
   }
   const int nx = (int)ceil_div(b, 256), nt = nx * (int)ceil_div(b, kHalfRows);
-  hipLaunchKernelGGL(k_loss_prep, dim3((unsigned)(nt + ceil_div(c, 4))), dim3(256), 0, s, H, W, c, b, d, Hf, h, nx, nt);
+  hipLaunchKernelGGL(k_loss_prep, dim3((unsigned)(nt + ceil_div(c, 4))), dim3(256), 0, s, H, W, c, b, d, Hf, h, nx, nt,
+                     d_out);
   THANOS_LAUNCH_CHECK();
   THANOS_CHECK(gemm_topped(s, c, b, b, W, b, h, Hf, b, nullptr, kBoundA, T, b, kTriLower, d, nullptr, beside));
   hipLaunchKernelGGL(k_rowdot, dim3((unsigned)ceil_div(c, 4)), dim3(256), 0, s, T, W, d, c, b, h);
