@@ -39,6 +39,18 @@ constexpr bool syrk_rows_aligned(uintptr_t X, int64_t ldx, int64_t b) {
   return X % 16 == 0 && ldx % 8 == 0 && b % 8 == 0 && ldx < (int64_t)1 << 28;
 }
 
+// What a wavefront reads of H (b x b) around the 32 x 32 tile at (i0, j0): from element `first` on, `bytes` bytes, which
+// end where H ends, or none (zeros are read instead).  A tile whose one row is the last of H and whose columns are
+// all past the last one starts behind H.
+struct HWindow {
+  int64_t first;
+  uint32_t bytes;
+};
+constexpr HWindow h_window(int64_t b, int64_t i0, int64_t j0) {
+  const int64_t left = i0 < b ? 4 * ((b - i0) * b - j0) : 0;
+  return left > 0 ? HWindow{i0 * b + j0, (uint32_t)std::min<int64_t>(left, 0xffffffffll)} : HWindow{0, 0};
+}
+
 // Parts that fill whole rounds of the 32 compute units of an XCD with 256-wide tiles (12 k-steps per item
 // for its fill and write-out).
 inline int64_t round_parts(int64_t b, int64_t n_tok) {

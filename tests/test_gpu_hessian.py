@@ -160,7 +160,8 @@ def test_rows_inside_a_wider_matrix(b, T, ldx, col, dtype):
     assert _relerr(np.tril(H.cpu().numpy().astype(np.float64)), np.tril(orc.hessian(X))) < 1e-6
 
 
-@pytest.mark.parametrize("b,T", [(1416, 33), (2568, 65), (3080, 40), (4104, 100), (8200, 40)])
+@pytest.mark.parametrize("b,T", [(1416, 33), (2568, 65), (3080, 40), (4104, 100), (8200, 40),
+                                 (1409, 40), (1441, 65), (1537, 33), (5121, 2048)])  # k_syrk16, one last row: 128- and 256-wide
 def test_old_values_at_the_edges_of_tiles(b, T):
     """Tiles that reach past the diagonal or the last row, one part: the lower triangle is added to, what lies
     above it (read with the tile, here NaN) and behind H stays as it is.  A sum of T products and one old value:

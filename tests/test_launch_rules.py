@@ -170,6 +170,38 @@ def test_sums_over_rows_of_any_alignment_are_short(plan):
             assert n <= 8192 if p.tile == 256 else n <= 4096 * sums, (b, T)
 
 
+def test_old_values_are_read_from_inside_h(tmp_path_factory, plan):
+    """What the accumulation reads of H around each 32 x 32 part of a tile ends with H, whatever the size leaves of
+    the last tile, and holds all that the part adds to."""
+    L = _compile(tmp_path_factory, "window", """
+#include "syrk_plan.h"
+// parts of the tiles of one row of tiles; 0, or 1 + the first part that reads outside of H or lacks a value
+extern "C" int64_t check(int64_t b, int64_t tile, int64_t ti) {
+  int64_t n = 0;
+  for (int64_t tj = 0; tj <= ti; tj += tj + 2 < ti ? ti - 1 - tj : 1)  // the first, the last two
+    for (int64_t i0 = ti * tile; i0 < (ti + 1) * tile; i0 += 32)
+      for (int64_t j0 = tj * tile; j0 < (tj + 1) * tile; j0 += 32) {
+        ++n;
+        const thanos::HWindow w = thanos::h_window(b, i0, j0);
+        if (w.first < 0 || 4 * (__int128)w.first + w.bytes > 4 * (__int128)b * b) return n;
+        for (int64_t i = i0; i < i0 + 32 && i < b; ++i) {
+          const int64_t j = i < j0 + 31 ? i : j0 + 31;  // the last value of the row that is added to
+          if (j >= j0 && (w.first != i0 * b + j0 || 4 * ((i - i0) * b + j - j0) + 4 > w.bytes)) return n;
+        }
+      }
+  return 0;
+}
+""")
+    L.check.argtypes = [ctypes.c_int64] * 3
+    L.check.restype = ctypes.c_int64
+    sizes = list(range(1409, 1409 + 768)) + [4001, 5121, 8193, 11008, 28672, 28673, 65505, 65535]
+    for b in sizes:
+        for tile in (128, 192, 256):
+            nt = -(-b // tile)
+            for ti in (0, nt // 2, nt - 1):
+                assert L.check(b, tile, ti) == 0, (b, tile, ti)
+
+
 def test_few_channels_take_narrow_tiles(plan):
     """The 32- and 64-wide tiles are for calls whose tiles run all at once, in one part."""
     for b in CHANNELS + [704, 705, 1408, 1409]:
