@@ -199,6 +199,10 @@ __device__ __forceinline__ float diag_scale(float h) {
   return ldexpf(1.f, -(e >> 1));
 }
 
+// The same for the row losses, which take H without damping.  Channels without activations add nothing to a loss
+// whatever their weights are: divided by the largest of the scales, these do not set the scale of a row.
+__device__ __forceinline__ float loss_scale(float h) { return h == 0.f ? 0x1p62f : diag_scale(h); }
+
 #define THANOS_CHECK(expr)                 \
   do {                                     \
     thanos_status st_ = (expr);            \

@@ -32,7 +32,8 @@ namespace thanos {
 constexpr int NB = kFactorNB;
 // ------------------------------------------------------------------------------------------
 // xnorm2[j] = H[j][j];  lam = damping * mean_j H[j][j]  (sum in fp64, fixed order);  d[j] = the scale of
-// channel j, d0[j] = the same without the damping.  Also clears the n_bounds bounds.  One workgroup of 1024 threads.
+// channel j, d0[j] = that of the row losses (without the damping).  Also clears the n_bounds bounds.  One workgroup
+// of 1024 threads.
 __global__ __launch_bounds__(1024) void k_diag_stats(const float* __restrict__ H, int64_t b,
                                                      float damping, float* __restrict__ xnorm2,
                                                      float* __restrict__ lam_out, float* __restrict__ d_out,
@@ -72,14 +73,14 @@ __global__ __launch_bounds__(1024) void k_diag_stats(const float* __restrict__ H
   }
   for (int64_t j = threadIdx.x; j < last; j += 1024) {  // its own writes
     d_out[j] = diag_scale(xnorm2[j] + lam);
-    d0[j] = diag_scale(xnorm2[j]);
+    d0[j] = loss_scale(xnorm2[j]);
   }
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const int64_t j = threadIdx.x + last + 1024 * e;
     if (j < b) {
       d_out[j] = diag_scale(d[e] + lam);
-      d0[j] = diag_scale(d[e]);
+      d0[j] = loss_scale(d[e]);
     }
   }
 }

@@ -2579,11 +2579,12 @@ static inline bool update_direct_ok(int64_t c, int64_t cols, int K) {
 // k >= n of every output column, i.e. half of the full product.
 // Channels are scaled by powers of two d as in the factorisation, W' = W D^-1, H' = D H D with a diagonal in [1, 4):
 // nothing changes in the losses, and the product's operands have a known range (gemm_tile_h2.h) whatever the scales
-// of the channels are (undamped: a channel far below the damping keeps its bits).  Where there is no factorisation to
-// take d from, and too many columns for k_loss_prep to look at the diagonal itself:
+// of the channels are (undamped: a channel far below the damping keeps its bits; loss_scale for those without any
+// activations).  Where there is no factorisation to take d from, and too many columns for k_loss_prep to look at the
+// diagonal itself:
 __global__ __launch_bounds__(256) void k_loss_scales(const float* __restrict__ H, int64_t b, float* __restrict__ d) {
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (j < b) d[j] = diag_scale(H[j * b + j]);
+  if (j < b) d[j] = loss_scale(H[j * b + j]);
 }
 constexpr int64_t kLossFewCols = 1024;  // a launch less: 4 of the 112 us of 64 x 128
 // The first nt workgroups (tiles of kHalfRows x 256): Hl, scaled, in the tiles of 128 on and below the diagonal, which
@@ -2597,7 +2598,7 @@ __global__ __launch_bounds__(256) void k_loss_prep(const float* __restrict__ H, 
                                                    int64_t b, const float* __restrict__ d, float* __restrict__ Hl,
                                                    float* __restrict__ top, int nx, int nt, float* __restrict__ d_out) {
   auto raw = [&](int64_t j) { return d_out ? H[j * b + j] : d[j]; };
-  auto scale = [&](float v) { return d_out ? diag_scale(v) : v; };
+  auto scale = [&](float v) { return d_out ? loss_scale(v) : v; };
   if ((int)blockIdx.x < nt) {
     const int64_t i0 = (int64_t)(blockIdx.x / nx) * kHalfRows, i1 = min(b, i0 + kHalfRows);
     const int64_t j = (int64_t)(blockIdx.x % nx) * 256 + threadIdx.x;

@@ -983,6 +983,39 @@ def test_row_losses_of_channels_of_any_scale(mode, kw, c, b):
     np.testing.assert_array_equal(W1, W2 * d[None, :])
 
 
+def _same_rows_stay(W, H32, M, alpha):
+    """The rows that were left alone are those with the largest losses in float64 (ties to 1e-6)."""
+    h = orc.row_losses(W.astype(np.float64), H32.astype(np.float64))
+    stay = ~M.any(axis=1)
+    assert stay.sum() == orc.num_outlier_rows(alpha, W.shape[0])
+    assert h[stay].min() > h[~stay].max() * (1 - 1e-6)
+
+
+@pytest.mark.parametrize("mode,kw,c,b,given", [
+    ("nm", dict(n=2, m=4, B=128), 130, 516, False), ("nm", dict(n=2, m=4, B=128), 40, 1300, False),
+    ("nm", dict(n=2, m=4, B=128), 130, 516, True), ("nm", dict(n=2, m=4, B=128), 40, 1300, True),
+    ("structured", dict(p=0.3), 130, 515, False), ("structured", dict(p=0.4), 70, 1101, False)])
+def test_row_losses_beside_channels_without_activations(mode, kw, c, b, given):
+    """Zero rows and columns of H under large weights, the others' values 2^-60 times as large as they were: what a
+    channel without activations weighs has no part in a loss, and none in its rounding."""
+    from tests.gpu_util import gpu_factor, gpu_prune
+    W, H32 = _layer(c, b, 2 * b, "f32", seed=b)
+    g = np.random.default_rng(c)
+    dead = g.permutation(b)[:b // 50]
+    W[:, dead] = 50 * g.standard_normal((c, dead.size))
+    H32[dead] = H32[:, dead] = 0.0
+    H32 *= np.float32(2.0 ** -60)
+    how = dict(kw)
+    if given:
+        U, xn2, info = gpu_factor(H32, 0.01)
+        assert info == 0
+        how.update(U=U, xnorm2=xn2)
+    print(f"no activations {mode} {c}x{b} given={given}", flush=True)
+    _, M, info = gpu_prune(W, H32, mode=mode, alpha=0.25, damp=0.01, **how)
+    assert info == 0
+    _same_rows_stay(W, H32, M, 0.25)
+
+
 def test_structured_with_every_column_removed():
     from tests.gpu_util import gpu_prune
     c, b = 64, 200
