@@ -2638,16 +2638,44 @@ __global__ __launch_bounds__(256) void k_loss_prep(const float* __restrict__ H, 
 }
 
 // h[i] = 2 sum_j T[i][j] * W[i][j] / d[j]; one wavefront per row, fp64 sum in a fixed order.
+// H' = D H D is bounded where H is a Gram matrix.  A caller's own H need not be positive semidefinite before it is
+// damped: elements of H' from 16 on are infinite in the split, and so, or NaN, are the sums of all rows.  Such rows of
+// finite weights take their losses straight from H (lower triangle, in its own scales).
 __global__ __launch_bounds__(256) void k_rowdot(const float* __restrict__ T, const float* __restrict__ W,
-                                                const float* __restrict__ d, int64_t c, int64_t b,
-                                                float* __restrict__ h) {
+                                                const float* __restrict__ d, const float* __restrict__ H, int64_t c,
+                                                int64_t b, float* __restrict__ h) {
   const int lane = threadIdx.x & 63;
   const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (i >= c) return;
+  const float* const row = W + i * b;
   double acc = 0.0;
-  for (int64_t j = lane; j < b; j += 64) acc += (double)T[i * b + j] * (double)(W[i * b + j] * pow2_inv(d[j]));
-  for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
-  if (lane == 0) h[i] = (float)(2.0 * acc);
+  for (int64_t j = lane; j < b; j += 64) acc += (double)T[i * b + j] * (double)(row[j] * pow2_inv(d[j]));
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+  acc *= 2.0;
+  if (!(fabs(acc) < (double)INFINITY)) {
+    bool finite = true;
+    for (int64_t j = lane; j < b; j += 64) finite = finite && fabsf(row[j]) < INFINITY;
+    if (__all(finite)) {
+      acc = 0.0;
+      for (int64_t k = 0; k < b && __all(fabs(acc) < (double)INFINITY); ++k) {
+        double part = 0.0;
+        for (int64_t n = lane; n <= k; n += 256) {
+          float v[4], w[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int64_t m = min(n + 64 * e, k);
+            v[e] = H[k * b + m];
+            w[e] = n + 64 * e > k ? 0.f : row[m];
+          }
+#pragma unroll
+          for (int e = 0; e < 4; ++e) part += (n + 64 * e == k ? 1.0 : 2.0) * (double)v[e] * (double)w[e];
+        }
+        acc += part * (double)row[k];
+      }
+      for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    }
+  }
+  if (lane == 0) h[i] = (float)acc;
 }
 
 // skip[i] = 1 for the n_out rows with the largest (h, row) (ascending order, ties by row index).
@@ -2682,7 +2710,7 @@ thanos_status row_outliers(hipStream_t s, const float* W, const float* H, int64_
                      d_out);
   THANOS_LAUNCH_CHECK();
   THANOS_CHECK(gemm_topped(s, c, b, b, W, b, h, Hf, b, nullptr, kBoundA, T, b, kTriLower, d, nullptr, beside));
-  hipLaunchKernelGGL(k_rowdot, dim3((unsigned)ceil_div(c, 4)), dim3(256), 0, s, T, W, d, c, b, h);
+  hipLaunchKernelGGL(k_rowdot, dim3((unsigned)ceil_div(c, 4)), dim3(256), 0, s, T, W, d, H, c, b, h);
   THANOS_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_row_rank, dim3((unsigned)ceil_div(c, 4)), dim3(256), 0, s, h, c,
                      (int64_t)n_out, skip);

@@ -988,7 +988,7 @@ def _same_rows_stay(W, H32, M, alpha):
     h = orc.row_losses(W.astype(np.float64), H32.astype(np.float64))
     stay = ~M.any(axis=1)
     assert stay.sum() == orc.num_outlier_rows(alpha, W.shape[0])
-    assert h[stay].min() > h[~stay].max() * (1 - 1e-6)
+    assert h[stay].min() > h[~stay].max() - 1e-6 * np.abs(h).max()
 
 
 @pytest.mark.parametrize("mode,kw,c,b,given", [
@@ -1012,6 +1012,33 @@ def test_row_losses_beside_channels_without_activations(mode, kw, c, b, given):
         how.update(U=U, xnorm2=xn2)
     print(f"no activations {mode} {c}x{b} given={given}", flush=True)
     _, M, info = gpu_prune(W, H32, mode=mode, alpha=0.25, damp=0.01, **how)
+    assert info == 0
+    _same_rows_stay(W, H32, M, 0.25)
+
+
+@pytest.mark.parametrize("mode,kw,c,b,given", [
+    ("nm", dict(n=2, m=4, B=128), 130, 516, False), ("nm", dict(n=2, m=4, B=128), 41, 1300, True),
+    ("structured", dict(p=0.3), 131, 515, False), ("structured", dict(p=0.4), 70, 1101, False)])
+def test_row_losses_of_an_indefinite_hessian(mode, kw, c, b, given):
+    """Elements of H that are far larger than their channels' diagonal, one of it zero and one negative: positive
+    definite only with its damping.  The losses are what H gives, of either sign."""
+    from tests.gpu_util import gpu_factor, gpu_prune
+    W, H32 = _layer(c, b, 2 * b, "f32", seed=b)
+    g = np.random.default_rng(c)
+    at = g.permutation(b)[:8].reshape(4, 2)
+    top = float(np.diag(H32).max())
+    for k, (i, j) in enumerate(at):
+        H32[i, j] = H32[j, i] = (-1) ** k * 300.0 * top
+    H32[at[0, 0], at[0, 0]] = 0.0
+    H32[at[1, 1], at[1, 1]] *= -1.0
+    damp = 2000.0 * top / float(np.diag(H32).mean())
+    how = dict(kw)
+    if given:
+        U, xn2, info = gpu_factor(H32, damp)
+        assert info == 0
+        how.update(U=U, xnorm2=xn2)
+    print(f"indefinite {mode} {c}x{b} given={given}", flush=True)
+    _, M, info = gpu_prune(W, H32, mode=mode, alpha=0.25, damp=damp, **how)
     assert info == 0
     _same_rows_stay(W, H32, M, 0.25)
 
