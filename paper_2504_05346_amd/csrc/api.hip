@@ -380,7 +380,7 @@ static thanos_status prune_with_workspace(const void* W_in, thanos_dtype wdt, in
   const float* xn2 = opts->xnorm2_in;
   const float* Lfac = nullptr;  // lower factor of the index-reversed damped Hessian (this call's) ...
   const float* Ldiag = nullptr;  // ... and its scaling
-  const float* Hscale = nullptr;  // scaling of H itself
+  const float* Hscale = nullptr;  // scales of the row losses
   const float* umax = nullptr;   // largest magnitudes of the columns of this call's U
   int64_t ldL = 0;
   const long long r_total =
@@ -401,18 +401,19 @@ static thanos_status prune_with_workspace(const void* W_in, thanos_dtype wdt, in
     p += align_up((size_t)b * b * sizeof(float), 256);
     float* xw = reinterpret_cast<float*>(p);
     p += align_up((size_t)b * sizeof(float), 256);
+    THANOS_CHECK(factor_begin(s, H, b, opts->damping, xw, p, info_dev, n_out > 0));
+    if (n_out > 0) Hscale = factor_loss_scale(p, b);
     if (beside) {
-      // the factorisation's first launches go ahead: behind the product of the row losses, which
+      // the factorisation's first launches went ahead: behind the product of the row losses, which
       // fills the chip, they took 420 us instead of 70 (5120 columns)
-      THANOS_CHECK(factor_begin(s, H, b, opts->damping, xw, p, info_dev));
       THANOS_CHECK(prep.fork(0));
       thanos_status sp = sweep_prepare(prep.stream, W_in, wdt, c, b, H, opts, n_out, W_out, sweep_ws,
-                                       factor_scale_undamped(p, b), true);
+                                       Hscale, true);
       if (sp != THANOS_OK) return sp;
       THANOS_CHECK(prep.record(1));
       prepared = true;
     }
-    thanos_status st = factor(s, H, b, opts->damping, Uw, xw, p, info_dev, single_stream, beside,
+    thanos_status st = factor(s, H, b, opts->damping, Uw, xw, p, info_dev, single_stream, true,
                               prepared && n_out > 0);
     if (st != THANOS_OK) return st;
     if (prepared) THANOS_CHECK(prep.join(1));
@@ -420,7 +421,6 @@ static thanos_status prune_with_workspace(const void* W_in, thanos_dtype wdt, in
     xn2 = xw;
     Lfac = factor_L(p, b, &ldL);
     Ldiag = factor_scale(p, b);
-    Hscale = factor_scale_undamped(p, b);
     umax = factor_umax(p, b);
   }
   phase_mark(pt, THANOS_PHASE_PREP);

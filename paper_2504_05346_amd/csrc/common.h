@@ -322,18 +322,19 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
                      float* xnorm2, void* ws, int32_t* info, bool single_stream = false,
                      bool begun = false, bool company = false);
 // Its first two launches (diagonal, damped copy), which is all of it that reads H; factor(..., begun =
-// true) goes on from there.
+// true) goes on from there.  losses: the scales of the row losses as well (a microsecond of a launch that all others
+// wait for).
 thanos_status factor_begin(hipStream_t s, const float* H, int64_t b, float damping, float* xnorm2,
-                           void* ws, int32_t* info);
+                           void* ws, int32_t* info, bool losses);
 const float* factor_L(const void* ws, int64_t b, int64_t* ld);
 const float* factor_scale(const void* ws, int64_t b);
-// the same for H without damping
-const float* factor_scale_undamped(const void* ws, int64_t b);
+// loss_scale() of the diagonal of H (factor_begin(.., losses = true))
+const float* factor_loss_scale(const void* ws, int64_t b);
 // largest magnitude of each column of U
 const float* factor_umax(const void* ws, int64_t b);
 
 // skip[i] = 1 for the n_out rows of W (c x b fp32) with the largest loss W_i H W_i^T (sweep.hip).  d: the
-// factorisation's undamped scales for this H; nullptr: they are worked out into d_room (b floats).
+// factorisation's scales of the row losses for this H; nullptr: they are worked out into d_room (b floats).
 thanos_status row_outliers(hipStream_t s, const float* W, const float* H, int64_t c, int64_t b,
                            long long n_out, float* Hf, float* T, float* h, const float* d, float* d_room,
                            uint8_t* skip, bool beside = false);

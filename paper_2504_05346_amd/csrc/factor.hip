@@ -32,8 +32,8 @@ namespace thanos {
 constexpr int NB = kFactorNB;
 // ------------------------------------------------------------------------------------------
 // xnorm2[j] = H[j][j];  lam = damping * mean_j H[j][j]  (sum in fp64, fixed order);  d[j] = the scale of
-// channel j, d0[j] = that of the row losses (without the damping).  Also clears the n_bounds bounds.  One workgroup
-// of 1024 threads.
+// channel j, d0[j] = that of the row losses (without the damping; nullptr where there are none).  Also clears the
+// n_bounds bounds.  One workgroup of 1024 threads.
 __global__ __launch_bounds__(1024) void k_diag_stats(const float* __restrict__ H, int64_t b,
                                                      float damping, float* __restrict__ xnorm2,
                                                      float* __restrict__ lam_out, float* __restrict__ d_out,
@@ -73,14 +73,14 @@ __global__ __launch_bounds__(1024) void k_diag_stats(const float* __restrict__ H
   }
   for (int64_t j = threadIdx.x; j < last; j += 1024) {  // its own writes
     d_out[j] = diag_scale(xnorm2[j] + lam);
-    d0[j] = loss_scale(xnorm2[j]);
+    if (d0) d0[j] = loss_scale(xnorm2[j]);
   }
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const int64_t j = threadIdx.x + last + 1024 * e;
     if (j < b) {
       d_out[j] = diag_scale(d[e] + lam);
-      d0[j] = loss_scale(d[e]);
+      if (d0) d0[j] = loss_scale(d[e]);
     }
   }
 }
@@ -642,10 +642,8 @@ const float* factor_L(const void* ws, int64_t b, int64_t* ld) {
 
 // The scales and the bounds live in the first 128 rows of the inverse's temporary, which no merge writes
 // (its tile rows belong to second halves): bp scales, nb bounds of L^{-1}, nb bounds of Tbuf per level
-// (level 0: of what the lowest merges leave),
-// the largest magnitudes of U's bp columns, the scales without damping: at most 10 values per block of 128 columns beside
-// three times 128, and
-// there are 128 x 128.
+// (level 0: of what the lowest merges leave), the largest magnitudes of U's bp columns, the scales of the row losses: at
+// most 10 values per block of 128 columns beside three times 128, and there are 128 x 128.
 static inline float* scales(const void* ws, int64_t bp) {
   return reinterpret_cast<float*>(const_cast<char*>(reinterpret_cast<const char*>(ws)) + 256) + 2 * bp * bp;
 }
@@ -661,7 +659,7 @@ const float* factor_umax(const void* ws, int64_t b) {
   return scales(ws, bp) + bp + n_bounds((int)(bp / NB));
 }
 
-const float* factor_scale_undamped(const void* ws, int64_t b) { return factor_umax(ws, b) + padded(b); }
+const float* factor_loss_scale(const void* ws, int64_t b) { return factor_umax(ws, b) + padded(b); }
 
 size_t factor_workspace_bytes(int64_t b) {
   const int64_t bp = padded(b);
@@ -669,14 +667,14 @@ size_t factor_workspace_bytes(int64_t b) {
 }
 
 thanos_status factor_begin(hipStream_t s, const float* H, int64_t b, float damping, float* xnorm2,
-                           void* ws, int32_t* info) {
+                           void* ws, int32_t* info, bool losses) {
   const int64_t bp = padded(b);
   float* lam = reinterpret_cast<float*>(ws);
   float* Ap = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + 256);
   const int nb = (int)(bp / NB);
   float* d = scales(ws, bp);
   hipLaunchKernelGGL(k_diag_stats, dim3(1), dim3(1024), 0, s, H, b, damping, xnorm2, lam, d,
-                     d + 2 * bp + n_bounds(nb), d + bp, n_bounds(nb) + (int)bp, info);
+                     losses ? d + 2 * bp + n_bounds(nb) : nullptr, d + bp, n_bounds(nb) + (int)bp, info);
   THANOS_LAUNCH_CHECK();
   const dim3 tiles((unsigned)(bp / kRpT), (unsigned)(bp / kRpT));
   if (b <= kRpFew) hipLaunchKernelGGL(k_reverse_pad<16>, tiles, dim3(1024), 0, s, H, b, lam, d, Ap, bp);
@@ -696,7 +694,7 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
   const float* d = scales(ws, bp);
   float* bound_inv = scales(ws, bp) + bp;
   float* bound_first = bound_inv + nb;  // the array of level 0, whose products share a launch
-  if (!begun) THANOS_CHECK(factor_begin(s, H, b, damping, xnorm2, ws, info));
+  if (!begun) THANOS_CHECK(factor_begin(s, H, b, damping, xnorm2, ws, info, false));
 
   // Two-level blocking: inside an outer block of kOuter factor blocks the trailing update of a
   // step only reaches the columns of that outer block (narrow, K = NB); everything to the right
