@@ -2233,6 +2233,8 @@ constexpr size_t kUpdInvOffset = kXSmemBytes + 2048 * sizeof(unsigned int) + 16 
                                  kCandStage * sizeof(uint2);
 static_assert(kUpdInvOffset + kTN * sizeof(float) <= kUpdSmemBytes, "both fit");
 
+constexpr int kUpdXcdRows = 16;  // tile rows from which on k_update deals them out to the XCDs
+
 // H2: two-way split of the operands.  Not for short reductions: of K products it loses the last bits once,
 // the three-way split rounds its running sum twice as often.  Errors of this kernel's results against float64,
 // solve included, two-way and three-way: K = 16 1.83 and 1.70e-7, 48 2.77 and 2.73, 64 3.13 and 3.14, 80 3.67 and
@@ -2252,7 +2254,7 @@ __global__ __launch_bounds__(kXThreads, 4) void k_update(UpdateArgs a) {
   // column, so that it reads one eighth of the multipliers and every tile of P_k once.
   // (With fewer than 16 row tiles the XCDs would not get equal shares: plain order.)
   int bx, by;
-  if (a.gy >= 16) {
+  if (a.gy >= kUpdXcdRows) {
     const int rp = (a.gy + 7) >> 3;
     const int slot = (int)blockIdx.x >> 3;
     bx = slot / rp;
@@ -2551,10 +2553,6 @@ __global__ __launch_bounds__(256, 2) void k_update_direct(UpdateArgs a) {
     if (threadIdx.x == 0) a.st->arrived = a.st->nbin = a.st->bar = 0u;
   }
 }
-// 32 x 32 tiles: every operand row is fetched once per tile of 32 columns instead of 128, which pays while the launch
-// waits for its latency.  Limits of 1024, 2048 and 4096: 1111 x 1365 1289, 1277 and 1278 us, 5120 x 5120 4:8 4948, 4988
-// and 5031 (one run to the other 0.6 %).
-constexpr int64_t kUpdDirectTiles = 2048;
 // Counts and lists of its workgroups, four for every tile of the array that k_update keeps its lists in (tiles of them).
 struct DirectLists {
   unsigned int *below_part, *cand_n;
@@ -2566,9 +2564,24 @@ static inline DirectLists direct_lists(uint2* cand, int64_t tiles) {
   return {n, n + 4 * tiles, cand + 4 * tiles};
 }
 static_assert(4 * (2 * sizeof(unsigned int) + DirectLists::cap * sizeof(uint2)) <= kCandStage * sizeof(uint2), "they fit");
+// Every operand row is fetched once per tile of 32 columns instead of 128, which pays while the launch waits for its
+// latency: up to one workgroup per compute unit, and up to two where the keys of the next selection are counted
+// (window) and k_update has too few tile rows to deal them out to the XCDs.  us a launch of k_update -> of this one:
+//   rows, reduction     512 workgroups (or)       256 (or)                128
+//   1000, 128, window   18.6 -> 15.7              15.9 -> 11.1            15.8 -> 9.7
+//   1536, 128, window   16.4 -> 16.1 (480)        14.4 -> 11.1 (240)
+//   2048, 128, window   13.9 -> 14.8              13.6 -> 11.8            13.0 -> 9.8
+//   3000, 128, window   14.3 -> 14.8 (470)        13.4 -> 10.8 (188)
+//   1536, 128           11.3 -> 11.3 (384)        10.7 -> 10.1 (240)       9.7 -> 8.0 (96)
+//   2048, 128           10.2 -> 13.4 (448)         9.7 -> 10.6             9.5 -> 8.6
+//   3000, 128           11.6 -> 12.6 (376)        11.0 ->  8.8 (188)
+//   2048, 256           15.3 -> 18.0              14.4 -> 13.7            14.4 -> 13.2
+//   2048, 512           23.5 -> 27.8              22.4 -> 19.5
+constexpr int64_t kUpdDirectWgs = 256, kUpdDirectWgsWindow = 512;
 // Columns of the update from col0 on.
-static inline bool update_direct_ok(int64_t c, int64_t cols, int K) {
-  return K > kShortK && K % 128 == 0 && K <= 512 && ceil_div(c, 32) * ceil_div(cols, kTN) * 4 <= kUpdDirectTiles;
+static inline bool update_direct_ok(int64_t c, int64_t cols, int K, bool window) {
+  const int64_t most = window && ceil_div(c, kTM) < kUpdXcdRows ? kUpdDirectWgsWindow : kUpdDirectWgs;
+  return K > kShortK && K % 128 == 0 && K <= 512 && ceil_div(c, 32) * ceil_div(cols, kTN) <= most;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2760,13 +2773,13 @@ constexpr int64_t kPickRows = 2560;
 
 static void launch_update(hipStream_t s, UpdateArgs ua, dim3 tiles) {
   ua.gx = (int)tiles.x;
-  if (update_direct_ok(ua.c, ua.col_end - ua.col0, ua.K)) {
+  if (update_direct_ok(ua.c, ua.col_end - ua.col0, ua.K, ua.hist != nullptr)) {
     hipLaunchKernelGGL(k_update_direct, dim3(tiles.x * (unsigned)ceil_div(ua.c, 32)), dim3(256), 0, s, ua);
     return;
   }
   ua.gy = (int)tiles.y;
   const unsigned rp = (tiles.y + 7) / 8;
-  const unsigned n = tiles.y >= 16 ? 8 * rp * tiles.x : tiles.x * tiles.y;
+  const unsigned n = tiles.y >= kUpdXcdRows ? 8 * rp * tiles.x : tiles.x * tiles.y;
   if (ua.K > kShortK) hipLaunchKernelGGL(k_update<true>, dim3(n), dim3(kXThreads), kUpdSmemBytes, s, ua);
   else hipLaunchKernelGGL(k_update<false>, dim3(n), dim3(kXThreads), kUpdSmemBytes, s, ua);
 }
@@ -3185,7 +3198,7 @@ thanos_status sweep(hipStream_t s, const void* W_in, thanos_dtype wdt, int64_t c
       dim3 grid((unsigned)ceil_div(sb_end - j1, kTN), (unsigned)ceil_div(c, kTM));
       const bool feed = unstructured && j1 + bw < b;  // a next block exists: count its window
       if (feed) {
-        const bool direct = update_direct_ok(c, sb_end - j1, bw);
+        const bool direct = update_direct_ok(c, sb_end - j1, bw, true);
         win_parts = (int)(grid.x * (direct ? ceil_div(c, 32) : grid.y));
         lists = direct ? direct_lists(w.cand, ceil_div(b, kTN) * ceil_div(c, kTM))
                        : DirectLists{w.below_part, w.cand_n, w.cand};
