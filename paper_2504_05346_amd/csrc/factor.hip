@@ -32,8 +32,9 @@ namespace thanos {
 constexpr int NB = kFactorNB;
 // ------------------------------------------------------------------------------------------
 // xnorm2[j] = H[j][j];  lam = damping * mean_j H[j][j]  (sum in fp64, fixed order);  d[j] = the scale of
-// channel j, d0[j] = that of the row losses (without the damping; nullptr where there are none).  Also clears the
-// n_bounds bounds.  One workgroup of 1024 threads.
+// channel j, d0[j] = that of the row losses (LOSSES; without the damping).  Also clears the n_bounds bounds.  One
+// workgroup of 1024 threads.
+template <bool LOSSES>
 __global__ __launch_bounds__(1024) void k_diag_stats(const float* __restrict__ H, int64_t b,
                                                      float damping, float* __restrict__ xnorm2,
                                                      float* __restrict__ lam_out, float* __restrict__ d_out,
@@ -73,14 +74,14 @@ __global__ __launch_bounds__(1024) void k_diag_stats(const float* __restrict__ H
   }
   for (int64_t j = threadIdx.x; j < last; j += 1024) {  // its own writes
     d_out[j] = diag_scale(xnorm2[j] + lam);
-    if (d0) d0[j] = loss_scale(xnorm2[j]);
+    if (LOSSES) d0[j] = loss_scale(xnorm2[j]);
   }
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const int64_t j = threadIdx.x + last + 1024 * e;
     if (j < b) {
       d_out[j] = diag_scale(d[e] + lam);
-      if (d0) d0[j] = loss_scale(d[e]);
+      if (LOSSES) d0[j] = loss_scale(d[e]);
     }
   }
 }
@@ -673,8 +674,8 @@ thanos_status factor_begin(hipStream_t s, const float* H, int64_t b, float dampi
   float* Ap = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + 256);
   const int nb = (int)(bp / NB);
   float* d = scales(ws, bp);
-  hipLaunchKernelGGL(k_diag_stats, dim3(1), dim3(1024), 0, s, H, b, damping, xnorm2, lam, d,
-                     losses ? d + 2 * bp + n_bounds(nb) : nullptr, d + bp, n_bounds(nb) + (int)bp, info);
+  hipLaunchKernelGGL(losses ? k_diag_stats<true> : k_diag_stats<false>, dim3(1), dim3(1024), 0, s, H, b, damping, xnorm2,
+                     lam, d, d + 2 * bp + n_bounds(nb), d + bp, n_bounds(nb) + (int)bp, info);
   THANOS_LAUNCH_CHECK();
   const dim3 tiles((unsigned)(bp / kRpT), (unsigned)(bp / kRpT));
   if (b <= kRpFew) hipLaunchKernelGGL(k_reverse_pad<16>, tiles, dim3(1024), 0, s, H, b, lam, d, Ap, bp);
