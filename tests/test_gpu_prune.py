@@ -1043,6 +1043,79 @@ def test_row_losses_of_an_indefinite_hessian(mode, kw, c, b, given):
     _same_rows_stay(W, H32, M, 0.25)
 
 
+def test_structured_update_of_groups_of_different_size():
+    """Two groups of channels that do not correlate, and rows whose weights in one of them are 2^15 times smaller:
+    what these gain is as exact as in test_structured_update_is_as_exact_as_fp32 (the split keeps all of a value
+    down to 2^-17 of its row's largest)."""
+    from tests.gpu_util import gpu_prune
+    c, b, s = 64, 512, 205
+    g = np.random.default_rng(5)
+    H32 = _near_identity(b, seed=3)
+    first = np.zeros(b, dtype=bool)
+    first[g.permutation(b)[:b // 2]] = True
+    H32[np.ix_(first, ~first)] = H32[np.ix_(~first, first)] = 0
+    W = (g.standard_normal((c, b)) / np.sqrt(np.diag(H32))).astype(np.float32)
+    even = np.arange(c) % 2 == 0
+    W[np.ix_(even, ~first)] *= np.float32(2.0 ** -15)
+    W[np.ix_(~even, first)] *= np.float32(2.0 ** -15)
+    Wg, Mg, info = gpu_prune(W, H32, mode="structured", p=(s - 0.5) / b, damp=0.0)
+    assert info == 0 and (Mg == Mg[0]).all() and Mg[0].sum() == s
+    Q, K = Mg[0] == 1, Mg[0] == 0
+    assert (Q & first).sum() > 64 and (Q & ~first).sum() > 64
+    Hi = np.linalg.inv(H32.astype(np.float64))
+    D = -np.linalg.solve(Hi[np.ix_(Q, Q)].T, W[:, Q].astype(np.float64).T).T @ Hi[np.ix_(Q, K)]
+    d = np.sqrt(np.diag(H32).astype(np.float64))[K]
+    for rows, chans in ((even, ~first[K]), (~even, first[K])):  # the small weights
+        at = np.ix_(rows, chans)
+        e = np.linalg.norm(((Wg[:, K] - (W[:, K] + D)) * d)[at])
+        added, kept = np.linalg.norm((D * d)[at]), np.linalg.norm((W[:, K] * d)[at])
+        print(f"  {e / added:.2e}", flush=True)
+        assert e / added <= 2.0 ** -20 + 2.0 ** -24 * kept / added
+
+
+def test_structured_and_row_losses_beyond_32768_columns():
+    """Rows that do not fit the LDS: permuted and gathered from memory.  H = E + v v^T with E diagonal, for which
+    everything has a closed form: the losses of columns and rows, and the update W_Q H_QK H_KK^-1 of the kept columns,
+    which is v_Q v_K^T E_K^-1 / (1 + v_K^T E_K^-1 v_K).  Weights along E^-1 v, so that the update is about as large
+    as they are; its sums over 10^4 values of one sign, 600 partial sums of 16, round by up to sqrt(600 / 3) 2^-24 in
+    each of the two products and about as much in the factor: 2^-19 instead of the 2^-20 of sums of either sign."""
+    import torch
+    import paper_2504_05346_amd as th
+    c, b, p, alpha = 40, 33001, 0.3, 0.1
+    gen = torch.Generator(device="cuda").manual_seed(33)
+    E = torch.exp(torch.randn(b, generator=gen, device="cuda"))
+    v = torch.randn(b, generator=gen, device="cuda").sign() * E.sqrt() * (2.0 / b ** 0.5)  # v^T E^-1 v = 4
+    H = torch.diag(E).addr_(v, v)
+    E = H.diagonal().double() - v.double() ** 2  # what the rounded diagonal stands for
+    W = torch.randn((c, b), generator=gen, device="cuda") * (0.5 / E.float().sqrt())
+    W += torch.randn((c, 1), generator=gen, device="cuda") * (v / E.float()) * b ** 0.5 / 2
+    o = th.PruneOpts(mode=th.THANOS_STRUCTURED, sparsity=p, damping=0.0, outlier_fraction=alpha, block_size=128)
+    ws = torch.empty((th.thanos_prune_workspace_bytes(c, b, o),), dtype=torch.uint8, device="cuda")
+    Wo, M = torch.empty((c, b), device="cuda"), torch.empty((c, b), dtype=torch.uint8, device="cuda")
+    info = torch.full((1,), -7, dtype=torch.int32, device="cuda")
+    print(f"structured {c}x{b}", flush=True)
+    th.thanos_prune_layer(W, H, o, Wo, None, M, ws, info)
+    torch.cuda.synchronize()
+    assert int(info) == 0
+    W, Wo, E, v = (t.double().cpu().numpy() for t in (W, Wo, E, v))
+    M = M.cpu().numpy().astype(bool)
+    h = (W * W) @ E + (W @ v) ** 2
+    rows = M.any(axis=1)
+    assert (~rows).sum() == orc.num_outlier_rows(alpha, c) and h[~rows].min() > h[rows].max() * (1 - 1e-6)
+    Q, K = M[rows][0], ~M[rows][0]
+    assert (M[rows] == Q).all()
+    col = (E + v * v) * (W[rows] ** 2).sum(axis=0)
+    assert col[Q].max() < col[K].min() * (1 + 1e-6)
+    np.testing.assert_array_equal(Wo[~rows], W[~rows])
+    assert np.all(Wo[rows][:, Q] == 0.0)
+    D = np.outer(W[rows][:, Q] @ v[Q], v[K] / E[K]) / (1 + (v[K] ** 2 / E[K]).sum())
+    d = np.sqrt(E + v * v)[K]
+    e = np.linalg.norm((Wo[rows][:, K] - (W[rows][:, K] + D)) * d) / np.linalg.norm(D * d)
+    kept = np.linalg.norm(W[rows][:, K] * d) / np.linalg.norm(D * d)
+    print(f"  {e:.2e}, kept weights {kept:.2f} times what is added", flush=True)
+    assert e <= 2.0 ** -19 + 2.0 ** -24 * kept
+
+
 def test_structured_with_every_column_removed():
     from tests.gpu_util import gpu_prune
     c, b = 64, 200
