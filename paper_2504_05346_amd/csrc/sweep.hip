@@ -2704,7 +2704,7 @@ __global__ __launch_bounds__(256) void k_row_rank(const float* __restrict__ h, i
 // triangle).  Hf (b x b, receives the scaled lower triangle with halved diagonal), T (c x b) and h (c) are
 // scratch.  The product takes the two-way split: errors of the losses against float64, three-way -> two-way, 0.8 ->
 // 0.75e-7 at 64 columns, 1.7 -> 1.4 at 512, 2.1 -> 1.6 at 1364, 2.7 -> 2.1e-7 at 4096; 4096 x 4096
-// 390 -> 252 us, 5120 x 5120 4:8 beside the factorisation 930 -> 640, 4950 -> 4800 us for the whole call.
+// 390 -> 252 us, 5120 x 5120 4:8 beside the factorisation 930 -> 640, 4940 -> 4800 us for the whole call.
 thanos_status row_outliers(hipStream_t s, const float* W, const float* H, int64_t c, int64_t b,
                            long long n_out, float* Hf, float* T, float* h, const float* d, float* d_room,
                            uint8_t* skip, bool beside) {
