@@ -108,16 +108,40 @@ __global__ __launch_bounds__(kXThreads, 4) void k_gemm_topped(ToppedArgs g) {
   gemm_tile_h2<false, true, 2, true, kCols, false, true, TRI == kTriLower>(
       acc, sm, g.A + (int64_t)m0 * g.lda, g.lda, m_ext, 1.f, g.a_top + m0, g.B + n0, g.ldb, n_ext, g.sb, {}, inv, kbeg,
       kend, g.b_top + n0, g.kd);
+  // Lower triangle: the row losses, whose H' need not be bounded (elements from 16 on are infinite in the split, and
+  // every sum they enter is infinite or NaN).  Such a tile is computed again on the three-way split: calls with one
+  // such element 4096 x 4096 3375 us, without 3360.
+  constexpr bool kAgain = TRI == kTriLower;
+  uint32_t* const bad = reinterpret_cast<uint32_t*>(inv);  // a word of each multiplying wavefront
+  if (kAgain && wave < 4) {
+    bool b = false;
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) b = b || !(fabsf(acc.v[f][h][r]) < INFINITY);
+    const uint32_t any = __any(b) ? 1u : 0u;
+    if (lane == 0) bad[wave] = any;
+  }
   const float* T = x3_stage_tile(acc, sm);
+  bool again = false;
+  if (kAgain && (bad[0] | bad[1] | bad[2] | bad[3]) != 0u) {
+    again = true;
+    acc_zero(acc);
+    gemm_tile_x3<false, true, true>(acc, sm, g.A + (int64_t)m0 * g.lda, g.lda, m_ext, g.B + n0, g.ldb, n_ext, kbeg, kend,
+                                    g.kd);
+    T = x3_stage_tile(acc, sm);
+  }
   const int c0 = 2 * lane;
-  const float f0 = kCols ? inv[c0] : pow2_inv(g.sb), f1 = kCols ? inv[c0 + 1] : f0;
+  const float f0 = kCols ? inv[c0] : again ? 1.f : pow2_inv(g.sb), f1 = kCols ? inv[c0 + 1] : f0;
   float* Cg = g.C + (int64_t)m0 * g.ldc + n0 + c0;
   const bool ok0 = c0 < n_ext, ok1 = c0 + 1 < n_ext;
   uint32_t u[16];
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     const int row = wave + 8 * i;
-    const float fr = pow2_inv(h2_scale(a_top[i]));
+    const float fr = again ? 1.f : pow2_inv(h2_scale(a_top[i]));
     const float2 t = *reinterpret_cast<const float2*>(T + row * kXCLd + c0);
     const float o0 = t.x * fminf(fr, f0) * fmaxf(fr, f0), o1 = t.y * fminf(fr, f1) * fmaxf(fr, f1);
     u[i] = max(ok0 ? __float_as_uint(fabsf(o0)) : 0u, ok1 ? __float_as_uint(fabsf(o1)) : 0u);

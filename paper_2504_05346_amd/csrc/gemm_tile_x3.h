@@ -240,12 +240,39 @@ __device__ __forceinline__ void x3_produce(char* smem, int operand, const float*
   }
 }
 
+// The same for a row-major operand whose column k is divided by kd[k], a power of two (kd: from kbeg on); for tiles that
+// are rarely computed, element by element.
+__device__ __forceinline__ void x3_produce_divided(char* smem, int operand, const float* __restrict__ P, int64_t ld,
+                                                   int ext, int kbeg, int kend, int nslab, int u,
+                                                   const float* __restrict__ kd) {
+  SlabSrcX3 src;
+  slab_src_x3<false>(src, P, ld, ext, kbeg, u);
+  const int klen = kend - kbeg;
+#pragma clang loop unroll(disable)
+  for (int it = 0; it < nslab; ++it) {
+    SlabRegsX3 r;
+    slab_load_x3<false, false>(r, src, it, klen - it * kXK, P);
+    float f[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) f[e] = kd[min(it * kXK + 4 * (u & 7) + e, klen - 1)];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      r.v[q] = make_float4(r.v[q].x / f[0], r.v[q].y / f[1], r.v[q].z / f[2], r.v[q].w / f[3]);
+    slab_store_x3<false, false>(smem, 0, operand, r, u);
+    __syncthreads();
+    __syncthreads();
+  }
+}
+
 // acc += op(A)[0:128, kbeg:kend] * op(B)[kbeg:kend, 0:128]; arguments as in gemm_tile(), smem =
-// kXSmemBytes of LDS, called by all 512 threads; the result is in wavefronts 0..3.
-template <bool A_KMAJOR, bool B_KMAJOR>
+// kXSmemBytes of LDS, called by all 512 threads; the result is in wavefronts 0..3.  KF: column k of A is divided by
+// kd[k], a power of two.
+template <bool A_KMAJOR, bool B_KMAJOR, bool KF = false>
 __device__ __forceinline__ void gemm_tile_x3(TileAcc& acc, char* smem, const float* __restrict__ A,
                                              int64_t lda, int m_ext, const float* __restrict__ B,
-                                             int64_t ldb, int n_ext, int kbeg, int kend) {
+                                             int64_t ldb, int n_ext, int kbeg, int kend,
+                                             const float* kd = nullptr) {
+  static_assert(!KF || !A_KMAJOR, "rows of A");
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -265,6 +292,8 @@ __device__ __forceinline__ void gemm_tile_x3(TileAcc& acc, char* smem, const flo
       else if (fast && whole) x3_produce<B_KMAJOR, true, false>(smem, 1, B, ldb, n_ext, kbeg, kend, nslab, u);
       else if (fast) x3_produce<B_KMAJOR, true, true>(smem, 1, B, ldb, n_ext, kbeg, kend, nslab, u);
       else x3_produce<B_KMAJOR, false, false>(smem, 1, B, ldb, n_ext, kbeg, kend, nslab, u);
+    } else if constexpr (KF) {
+      x3_produce_divided(smem, 0, A, lda, m_ext, kbeg, kend, nslab, u, kd + kbeg);
     } else {
       const bool fast = (A_KMAJOR ? m_ext : kend - kbeg) % 4 == 0;
       const bool whole = m_ext == 128 && !ktail;

@@ -2593,8 +2593,9 @@ static inline bool update_direct_ok(int64_t c, int64_t cols, int K, bool window)
 // Channels are scaled by powers of two d as in the factorisation, W' = W D^-1, H' = D H D with a diagonal in [1, 4):
 // nothing changes in the losses, and the product's operands have a known range (gemm_tile_h2.h) whatever the scales
 // of the channels are (undamped: a channel far below the damping keeps its bits; loss_scale for those without any
-// activations).  Where there is no factorisation to take d from, and too many columns for k_loss_prep to look at the
-// diagonal itself:
+// activations).  A caller's own H need not be positive semidefinite before it is damped; larger elements of H' than a
+// Gram matrix has are looked after where they overflow (k_gemm_topped, k_rowdot).  Where there is no factorisation to
+// take d from, and too many columns for k_loss_prep to look at the diagonal itself:
 __global__ __launch_bounds__(256) void k_loss_scales(const float* __restrict__ H, int64_t b, float* __restrict__ d) {
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (j < b) d[j] = loss_scale(H[j * b + j]);
@@ -2651,9 +2652,8 @@ __global__ __launch_bounds__(256) void k_loss_prep(const float* __restrict__ H, 
 }
 
 // h[i] = 2 sum_j T[i][j] * W[i][j] / d[j]; one wavefront per row, fp64 sum in a fixed order.
-// H' = D H D is bounded where H is a Gram matrix.  A caller's own H need not be positive semidefinite before it is
-// damped: elements of H' from 16 on are infinite in the split, and so, or NaN, are the sums of all rows.  Such rows of
-// finite weights take their losses straight from H (lower triangle, in its own scales).
+// A loss that fp32 does not hold in the scaled coordinates (a caller's own H with elements between channels whose diagonal
+// is zero) is taken straight from H, lower triangle, where the weights of the row are finite: slow, and rare.
 __global__ __launch_bounds__(256) void k_rowdot(const float* __restrict__ T, const float* __restrict__ W,
                                                 const float* __restrict__ d, const float* __restrict__ H, int64_t c,
                                                 int64_t b, float* __restrict__ h) {

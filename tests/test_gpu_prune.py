@@ -1019,9 +1019,11 @@ def test_row_losses_beside_channels_without_activations(mode, kw, c, b, given):
 @pytest.mark.parametrize("mode,kw,c,b,given", [
     ("nm", dict(n=2, m=4, B=128), 130, 516, False), ("nm", dict(n=2, m=4, B=128), 41, 1300, True),
     ("structured", dict(p=0.3), 131, 515, False), ("structured", dict(p=0.4), 70, 1101, False)])
-def test_row_losses_of_an_indefinite_hessian(mode, kw, c, b, given):
-    """Elements of H that are far larger than their channels' diagonal, one of it zero and one negative: positive
-    definite only with its damping.  The losses are what H gives, of either sign."""
+@pytest.mark.parametrize("zeros", [False, True])
+def test_row_losses_of_an_indefinite_hessian(mode, kw, c, b, given, zeros):
+    """Elements of H that are far larger than their channels' diagonal, some of it zero and one negative: positive
+    definite only with its damping.  The losses are what H gives, of either sign.  zeros: an element between two
+    channels of zero diagonal, which no scale of theirs brings into the range of fp32."""
     from tests.gpu_util import gpu_factor, gpu_prune
     W, H32 = _layer(c, b, 2 * b, "f32", seed=b)
     g = np.random.default_rng(c)
@@ -1029,6 +1031,8 @@ def test_row_losses_of_an_indefinite_hessian(mode, kw, c, b, given):
     top = float(np.diag(H32).max())
     for k, (i, j) in enumerate(at):
         H32[i, j] = H32[j, i] = (-1) ** k * 300.0 * top
+    if zeros:
+        H32[at[2, 0], at[2, 0]] = H32[at[2, 1], at[2, 1]] = 0.0
     H32[at[0, 0], at[0, 0]] = 0.0
     H32[at[1, 1], at[1, 1]] *= -1.0
     damp = 2000.0 * top / float(np.diag(H32).mean())
