@@ -2554,6 +2554,9 @@ __global__ __launch_bounds__(256, 2) void k_update_direct(UpdateArgs a) {
   }
 }
 // Counts and lists of its workgroups, four for every tile of the array that k_update keeps its lists in (tiles of them).
+// A list is a quarter as long and overflows no sooner on the data tried: rows of equal scale, or of scales over e^+-2 at
+// random, sorted, by strips of 32 or in one strip of four, 512 x 512 to 2048 x 2048: the selections of a pass take what they
+// take with lists of 384 (512 x 512 58 to 75 us, 2048 x 2048 193 to 222 of 196 to 225).
 struct DirectLists {
   unsigned int *below_part, *cand_n;
   uint2* cand;

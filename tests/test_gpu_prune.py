@@ -914,10 +914,12 @@ def test_factor_beside_the_row_losses_has_the_same_bits():
     ("unstructured", dict(p=0.5), 1, 384, 128),
     ("unstructured", dict(p=0.5), 97, 515, 128),       # rows of any alignment, ragged last block
     ("unstructured", dict(p=0.4), 130, 768, 256),
-    ("unstructured", dict(p=0.5), 1024, 1029, 128)])   # 32 x 9 strips in the first block: 1152 tiles
+    ("unstructured", dict(p=0.5), 1024, 1029, 128),    # 32 x 9 strips in the first block
+    ("nm", dict(n=2, m=4), 1056, 1024, 128),           # 33 x 8 strips, then 33 x 7: both kernels
+    ("unstructured", dict(p=0.5), 1921, 640, 128)])    # 61 x 5, then 61 x 4, with 16 tile rows: both kernels
 def test_update_of_few_tiles(mode, kw, c, b, B):
-    """What the sweep adds to the kept weights, relative to float64 under the same mask, where every update is a
-    launch of few tiles: well-conditioned H, so that factor, block rows, solve and update are off by some 2^-24
+    """What the sweep adds to the kept weights, relative to float64 under the same mask, where the updates are
+    launches of few tiles: well-conditioned H, so that factor, block rows, solve and update are off by some 2^-24
     each, in sums of up to b values of either sign; 2^-20 as for single blocks, times two for the blocks in turn."""
     from tests.gpu_util import gpu_prune
     H32 = _near_identity(b, seed=b + B)
