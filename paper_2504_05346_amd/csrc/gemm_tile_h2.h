@@ -42,13 +42,18 @@ constexpr size_t kH2SmemBytes = 2 * (size_t)kH2Buf;  // half of a compute unit's
 static_assert(kH2SmemBytes >= kXSmemBytes && 2 * kH2SmemBytes <= 160 * 1024, "staged tile fits, two per unit");
 static_assert(kH2Buf <= kXSmemBytes, "one buffer fits where the tile is staged");
 
+constexpr float kWideH2 = 0x1p11f;
+
 // 1 / s for a power of two between 2^-126 and 2^126
 __device__ __forceinline__ float pow2_inv(float s) { return __uint_as_float((254u << 23) - __float_as_uint(s)); }
 
+// WIDE: the second term is 2^11 times as large.
+template <bool WIDE = false>
 __device__ __forceinline__ void split2_h2(float x0, float x1, float s0, float s1, uint32_t (&packed)[2]) {
   const f32x2 v = {x0 * s0, x1 * s1};
   const f16x2 h = __builtin_convertvector(v, f16x2);
-  const f32x2 r = {fmaf(x0, s0, -(float)h[0]), fmaf(x1, s1, -(float)h[1])};
+  f32x2 r = {fmaf(x0, s0, -(float)h[0]), fmaf(x1, s1, -(float)h[1])};
+  if (WIDE) r *= kWideH2;
   const f16x2 l = __builtin_convertvector(r, f16x2);
   packed[0] = __builtin_bit_cast(uint32_t, h);
   packed[1] = __builtin_bit_cast(uint32_t, l);
@@ -127,7 +132,7 @@ __device__ __forceinline__ void finish_cols_h2(ScaleH2& sc) {
 }
 
 // KF: the k-values of a row-major operand are multiplied by kf first (this thread's four of the slab).
-template <bool KMAJOR, bool MASKED, bool ROWS, bool KF>
+template <bool KMAJOR, bool MASKED, bool ROWS, bool KF, bool WIDE>
 __device__ __forceinline__ void slab_store_h2(char* smem, int operand, const SlabRegsX3& rin,
                                               const ScaleH2& sc, int u, const f32x4& kf) {
   SlabRegsX3 r = rin;
@@ -168,8 +173,8 @@ __device__ __forceinline__ void slab_store_h2(char* smem, int operand, const Sla
     for (int q = 0; q < 8; ++q) {
       const float s = ROWS ? sc.row[q] : sc.all;
       uint32_t lo2[2], hi2[2];
-      split2_h2(r.v[q].x, r.v[q].y, s, s, lo2);
-      split2_h2(r.v[q].z, r.v[q].w, s, s, hi2);
+      split2_h2<WIDE>(r.v[q].x, r.v[q].y, s, s, lo2);
+      split2_h2<WIDE>(r.v[q].z, r.v[q].w, s, s, hi2);
       const int off = ((u >> 3) + 16 * q) * kXRow + 8 * (u & 7);
 #pragma unroll
       for (int p = 0; p < 2; ++p)
@@ -217,15 +222,15 @@ __device__ __forceinline__ void h2_produce4(char* smem, int operand, const float
   for (int it = 0; it < 4; ++it) f[it] = slab_factors_h2<KF>(kd, it, 4 * kXK, u);
   if (KMAJOR && ROWS && !TOPS) finish_cols_h2(sc);
   char* const second = smem + (NBUF - 1) * kH2Buf;
-  slab_store_h2<KMAJOR, false, ROWS, KF>(smem, operand, r0, sc, u, f[0]);
+  slab_store_h2<KMAJOR, false, ROWS, KF, TOPS && !KF && !KMAJOR>(smem, operand, r0, sc, u, f[0]);
   slab_load_x3<KMAJOR, true>(r0, src, 2, 2 * kXK, P);
   h2_handover<NBUF>();
-  slab_store_h2<KMAJOR, false, ROWS, KF>(second, operand, r1, sc, u, f[1]);
+  slab_store_h2<KMAJOR, false, ROWS, KF, TOPS && !KF && !KMAJOR>(second, operand, r1, sc, u, f[1]);
   slab_load_x3<KMAJOR, true>(r1, src, 3, kXK, P);
   h2_handover<NBUF>();
-  slab_store_h2<KMAJOR, false, ROWS, KF>(smem, operand, r0, sc, u, f[2]);
+  slab_store_h2<KMAJOR, false, ROWS, KF, TOPS && !KF && !KMAJOR>(smem, operand, r0, sc, u, f[2]);
   h2_handover<NBUF>();
-  slab_store_h2<KMAJOR, false, ROWS, KF>(second, operand, r1, sc, u, f[3]);
+  slab_store_h2<KMAJOR, false, ROWS, KF, TOPS && !KF && !KMAJOR>(second, operand, r1, sc, u, f[3]);
   h2_handover<NBUF>();
 }
 
@@ -242,7 +247,7 @@ __device__ __forceinline__ void h2_produce(char* smem, int operand, const float*
   if (KMAJOR && ROWS && !TOPS) finish_cols_h2(sc);
   for (int it = 0; it < nslab; ++it) {
     if (operand == 0 && u < 64) TL_MARK(8 + 4 * it);
-    slab_store_h2<KMAJOR, MASKED, ROWS, KF>(smem + (NBUF == 2 ? (it & 1) * kH2Buf : 0), operand, r, sc, u, f);
+    slab_store_h2<KMAJOR, MASKED, ROWS, KF, TOPS && !KF && !KMAJOR>(smem + (NBUF == 2 ? (it & 1) * kH2Buf : 0), operand, r, sc, u, f);
     slab_load_x3<KMAJOR, FAST>(r, src, it + 1, klen - (it + 1) * kXK, P);
     f = slab_factors_h2<KF>(kd, it + 1, klen, u);
     if (operand == 0 && u < 64) TL_MARK(8 + 4 * it + 1);
@@ -268,7 +273,9 @@ __device__ __forceinline__ void h2_producer(char* smem, int operand, const float
 // inv[0:128] (LDS beyond the buffers' use after the product), complete after the next barrier.
 // B_PIECES: the extents of B are multiples of 4.  TOPS: what arows and btops (n_ext values) hold are the largest
 // magnitudes of the rows and columns, not their scales.  KF: column k of A is divided by kd[k], a power of two
-// (arows belongs to the result).
+// (arows belongs to the result).  TOPS without KF: the values of a row of A may lie further apart than those of B.
+// Their second terms are 2^11 times as large, which would be subnormal from 2^-17 of the row's largest value down (now
+// from 2^-28), and meet first terms of B that are as much smaller: 4096 x 1366 times 1366 x 2730 125 -> 128 us.
 template <bool A_KMAJOR, bool B_KMAJOR, int NBUF, bool A_ROWS = false, bool B_COLS = false, bool B_PIECES = false,
           bool TOPS = false, bool KF = false>
 __device__ __forceinline__ void gemm_tile_h2(TileAcc& acc, char* smem, const float* __restrict__ A,
@@ -315,6 +322,11 @@ __device__ __forceinline__ void gemm_tile_h2(TileAcc& acc, char* smem, const flo
             af[f][p] = *reinterpret_cast<const f16x8*>(h2_plane(buf, 0, p) + a_off + f * 32 * kXRow + 32 * ks);
             bf[f][p] = *reinterpret_cast<const f16x8*>(h2_plane(buf, 1, p) + b_off + f * 32 * kXRow + 32 * ks);
           }
+        f16x8 b1[2] = {bf[0][0], bf[1][0]};
+        if (TOPS && !KF) {
+#pragma unroll
+          for (int g = 0; g < 2; ++g) b1[g] *= (_Float16)(1.f / kWideH2);
+        }
         // small partial products first; consecutive MFMAs go to different accumulators
         constexpr int pa[3] = {1, 0, 0};
         constexpr int pb[3] = {0, 1, 0};
@@ -324,8 +336,8 @@ __device__ __forceinline__ void gemm_tile_h2(TileAcc& acc, char* smem, const flo
           for (int f = 0; f < 2; ++f)
 #pragma unroll
             for (int g = 0; g < 2; ++g)
-              acc.v[f][g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[f][pa[t]], bf[g][pb[t]], acc.v[f][g],
-                                                                   0, 0, 0);
+              acc.v[f][g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[f][pa[t]], t == 0 ? b1[g] : bf[g][pb[t]],
+                                                                   acc.v[f][g], 0, 0, 0);
       }
       if (wave == 0) TL_MARK(8 + 4 * it + 3);
       if (NBUF == 1) __syncthreads();

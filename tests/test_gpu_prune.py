@@ -1049,10 +1049,10 @@ def test_row_losses_of_an_indefinite_hessian(mode, kw, c, b, given, zeros):
     _same_rows_stay(W, H32, M, 0.25)
 
 
-def test_structured_update_of_groups_of_different_size():
-    """Two groups of channels that do not correlate, and rows whose weights in one of them are 2^15 times smaller:
-    what these gain is as exact as in test_structured_update_is_as_exact_as_fp32 (the split keeps all of a value
-    down to 2^-17 of its row's largest)."""
+@pytest.mark.parametrize("e", [15, 20, 24])
+def test_structured_update_of_groups_of_different_size(e):
+    """Two groups of channels that do not correlate, and rows whose weights in one of them are 2^e times smaller:
+    what these gain is as exact as in test_structured_update_is_as_exact_as_fp32."""
     from tests.gpu_util import gpu_prune
     c, b, s = 64, 512, 205
     g = np.random.default_rng(5)
@@ -1062,8 +1062,9 @@ def test_structured_update_of_groups_of_different_size():
     H32[np.ix_(first, ~first)] = H32[np.ix_(~first, first)] = 0
     W = (g.standard_normal((c, b)) / np.sqrt(np.diag(H32))).astype(np.float32)
     even = np.arange(c) % 2 == 0
-    W[np.ix_(even, ~first)] *= np.float32(2.0 ** -15)
-    W[np.ix_(~even, first)] *= np.float32(2.0 ** -15)
+    W[np.ix_(even, ~first)] *= np.float32(2.0 ** -e)
+    W[np.ix_(~even, first)] *= np.float32(2.0 ** -e)
+    print(f"groups 2^{e} apart", flush=True)
     Wg, Mg, info = gpu_prune(W, H32, mode="structured", p=(s - 0.5) / b, damp=0.0)
     assert info == 0 and (Mg == Mg[0]).all() and Mg[0].sum() == s
     Q, K = Mg[0] == 1, Mg[0] == 0
@@ -1073,10 +1074,10 @@ def test_structured_update_of_groups_of_different_size():
     d = np.sqrt(np.diag(H32).astype(np.float64))[K]
     for rows, chans in ((even, ~first[K]), (~even, first[K])):  # the small weights
         at = np.ix_(rows, chans)
-        e = np.linalg.norm(((Wg[:, K] - (W[:, K] + D)) * d)[at])
+        err = np.linalg.norm(((Wg[:, K] - (W[:, K] + D)) * d)[at])
         added, kept = np.linalg.norm((D * d)[at]), np.linalg.norm((W[:, K] * d)[at])
-        print(f"  {e / added:.2e}", flush=True)
-        assert e / added <= 2.0 ** -20 + 2.0 ** -24 * kept / added
+        print(f"  {err / added:.2e}", flush=True)
+        assert err / added <= 2.0 ** -20 + 2.0 ** -24 * kept / added
 
 
 def test_structured_and_row_losses_beyond_32768_columns():
