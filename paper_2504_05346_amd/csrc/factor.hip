@@ -30,6 +30,13 @@
 namespace thanos {
 
 constexpr int NB = kFactorNB;
+// Block rows that are factored with one launch per step (k_chol_step): up to kStepAll all of them, of more the last
+// kStepLast.  A step updates every tile, (rows)^2 / 2 of them in 10 us a round of 512, beside a diagonal block of 20; from
+// about 40 rows on the tiles are the longer part, and the two-level updates move less.  Whole factorisations with the last 16,
+// 24, 32, 40, 48, 64 blocks in such steps, us: 3000 columns 910, 768, 768, ..; 4096 1277, 1166, 1058, ..; 5120 1803, 1697, 1638, 1607,
+// 1606, 1608; 6144 2355, 2284, 2250, 2245, 2340, 2338; 8192 3630, 3530, 3570, 3645, 3785, 4450; 11008 6625, 6560, 6500, 6510,
+// 6580, 7290 (before: 4096 1694, 5120 2114, 8192 4255, 11008 6875).
+constexpr int kStepAll = 40, kStepLast = 32;
 // ------------------------------------------------------------------------------------------
 // xnorm2[j] = H[j][j];  lam = damping * mean_j H[j][j]  (sum in fp64, fixed order);  d[j] = the scale of
 // channel j, d0[j] = that of the row losses (LOSSES; without the damping).  Also clears the n_bounds bounds.  One
@@ -94,7 +101,8 @@ __device__ __forceinline__ void raise_bound(float* bound, float m) {
 }
 
 // A'[i][j] = (D H_d D)[b-1-i][b-1-j] for i >= j (read from the lower triangle of H as
-// H[b-1-j][b-1-i]); identity on the padding; zero above the diagonal of a diagonal block (what lies right
+// H[b-1-j][b-1-i]); identity on the padding; its mirror image above the diagonal of the 64x64 tiles on it
+// (cd_load_op reads whole tiles), zero in the rest of a diagonal block (what lies right
 // of it is never read, and stays as it is).  64x64 tiles through LDS so that both the read of H and the write
 // of A' are coalesced, sixteen loads per thread in flight: 11008 columns 270 -> 135 us (before: 32x32 tiles, zeros in
 // the whole upper triangle).  R rows of threads: with few columns, where the launch waits for its own loads, 16 rows of
@@ -136,7 +144,7 @@ __global__ __launch_bounds__(64 * R) void k_reverse_pad(const float* __restrict_
     const int r = ty + R * e;
     const int64_t i = i0 + r;
     float o;
-    if (j > i) o = 0.f;
+    if (j > i) o = i0 == j0 && j < b ? t[r][tx] * (di[e] * dj) : 0.f;
     else if (i >= b) o = (i == j) ? 1.f : 0.f;
     else o = (t[tx][r] + ((i == j) ? lam : 0.f)) * (di[e] * dj);
     Ap[i * bp + j] = o;
@@ -145,7 +153,7 @@ __global__ __launch_bounds__(64 * R) void k_reverse_pad(const float* __restrict_
 
 // ------------------------------------------------------------------------------------------
 // Cholesky factor and inverse of one NB x NB diagonal block, one workgroup of 8 wavefronts.
-//   in : lower triangle of A'[kb*NB .. , kb*NB ..]
+//   in : A'[kb*NB .. , kb*NB ..], of its diagonal 32-tiles both triangles, of the others the lower ones
 //   out: L_kk in the same place (its diagonal 32-tiles with zeros above the diagonal, the tiles above
 //        them untouched), Linv diagonal block = L_kk^{-1} (full square, zeros above the diagonal).
 //
@@ -161,41 +169,45 @@ __global__ __launch_bounds__(64 * R) void k_reverse_pad(const float* __restrict_
 //     of what is final, and the inverse by rows,
 //         X_ij = -T_i V_ij,  V_ij = sum_{j <= k < i} L_ik X_kj,  X_jj = T_j,
 //     with V of tile row i formed in phase i (before T_i is known), X of it in phase i + 1.
-// 23.5 us per block.  With one pivot per MFMA, LDS round trips of the tiles between the phases and the
-// inverse after them (four wavefronts) it was 34.5.
+// 17.5 us per block by itself, 14.5 inside k_chol_step.  Four unrolled phases, fp32 MFMAs between them and the most
+// products beside the longest chain: 23.5.  With one pivot per MFMA, LDS round trips of the tiles between the phases and the
+// inverse after them (four wavefronts): 34.5.
 constexpr int kCdL = 0, kCdT = 10, kCdA = 14, kCdTiles = 17;  // LDS tiles: L (i, j), T_j, A_22 A_32 A_33
+constexpr int kCdB = 9, kCdB1 = 8, kCdB2 = 5;  // A_11 A_21 A_31, in the place of L tiles of phases 2 and 3
 constexpr size_t kCholDiagSmem = ((size_t)kCdTiles * kRsTile + 4 * 32) * sizeof(float);
 
 __device__ __forceinline__ constexpr int cd_l(int i, int j) { return kCdL + i * (i + 1) / 2 + j; }
 
 // Global tile (p = its first element) <-> registers, rows and columns in elimination order.
 // nl = tl_nat(lo).
-__device__ __forceinline__ void cd_load_sym(f32x16& v, const float* p, int64_t ld, int nl, int hi) {
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {  // only the lower triangle is valid
-    const int x = 8 * (r >> 2) + 2 * (r & 3) + hi;
-    v[r] = p[(int64_t)max(x, nl) * ld + min(x, nl)];
-  }
-}
 __device__ __forceinline__ void cd_swap(float& a, float& b) {  // upper half of a <-> lower half of b
   const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
   a = __uint_as_float(s[0]);
   b = __uint_as_float(s[1]);
 }
-// operand layout; a lane reads 16-byte pieces of its row, whose even (odd) columns belong to the
-// lower (upper) half of the wavefront
-__device__ __forceinline__ void cd_load_op(f32x16& v, const float* p, int64_t ld, int nl, int hi) {
+// operand layout (of a symmetric tile: accumulator layout); a lane reads 16-byte pieces of its row, whose even (odd)
+// columns belong to the lower (upper) half of the wavefront
+__device__ __forceinline__ void cd_load_rows(f32x4 (&x)[4], const float* p, int64_t ld, int nl, int hi) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+    x[g] = *reinterpret_cast<const f32x4*>(p + 8 * g + ((uint32_t)nl * (uint32_t)ld + 4 * hi));
+}
+__device__ __forceinline__ void cd_from_rows(f32x16& v, const f32x4 (&x)[4]) {
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
-    const f32x4 f = *reinterpret_cast<const f32x4*>(p + (int64_t)nl * ld + 8 * g + 4 * hi);
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
-      float a = f[2 * e], b = f[2 * e + 1];
+      float a = x[g][2 * e], b = x[g][2 * e + 1];
       cd_swap(a, b);
       v[4 * g + e] = a;
       v[4 * g + e + 2] = b;
     }
   }
+}
+__device__ __forceinline__ void cd_load_op(f32x16& v, const float* p, int64_t ld, int nl, int hi) {
+  f32x4 x[4];
+  cd_load_rows(x, p, ld, nl, hi);
+  cd_from_rows(v, x);
 }
 __device__ __forceinline__ void cd_store_op(float* p, int64_t ld, const float* tile, int lo, int hi) {
   const int nl = tl_nat(lo);
@@ -247,17 +259,42 @@ __device__ __forceinline__ f32x16 cd_minus_tv(const float* T, const f32x16& V, i
   return acc;
 }
 
-// 512 threads at 128 registers: half of a compute unit's registers, so that the workgroup finds
-// room beside one workgroup of the matrix products.
-__global__ __launch_bounds__(512, 4) void k_chol_diag(float* __restrict__ Ap,
-                                                      float* __restrict__ Linv, int64_t bp,
-                                                      int kb_glob, int64_t b, float* __restrict__ bound,
-                                                      int32_t* __restrict__ info) {
-  extern __shared__ __attribute__((aligned(16))) float cd_smem[];
+// v -= A B^T for tiles of L in LDS, on the two-way split (|L| <= kBoundL), which is made here: a tile is read
+// by three products at most.  Eight MFMAs of 32 cycles and 112 vector instructions where 16 fp32 MFMAs take 64 each.
+struct CdSplit {
+  f16x8 h[2], l[2];
+};
+__device__ __forceinline__ CdSplit cd_split(const float* tile, int lo, int hi) {
+  CdSplit t;
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+    split8_h2(rs_piece(tile, 2 * m, lo, hi), rs_piece(tile, 2 * m + 1, lo, hi), h2_scale(kBoundL), t.h[m], t.l[m]);
+  return t;
+}
+__device__ __forceinline__ void cd_sub(f32x16& v, const CdSplit& a, const CdSplit& b) {
+  f32x16 acc = cd_zero();
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a.l[m], b.l[m], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a.l[m], b.h[m], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a.h[m], b.l[m], acc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int m = 0; m < 2; ++m) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a.h[m], b.h[m], acc, 0, 0, 0);
+  const float f = -pow2_inv(h2_scale(kBoundL)) * pow2_inv(h2_scale(kBoundL));
+#pragma unroll
+  for (int r = 0; r < 16; ++r) v[r] = fmaf(f, acc[r], v[r]);
+}
+
+// The block itself: A, Li point at it in A' and in the inverse.  sym(v, i) and op(v, i, j) give tile (i, i) in
+// accumulator and tile (i, j) in operand layout; all_have() is reached by every wavefront once it has its first ones (by
+// the chain in the middle of phase 0), before anything is written to LDS.
+template <typename Sym, typename Op, typename All>
+__device__ __forceinline__ void cd_block(float* cd_smem, float* A, float* Li, int64_t bp, int kb_glob, int64_t b,
+                                         float* bound, int32_t* info, const Sym& sym, const Op& op,
+                                         const All& all_have) {
   const int lane = threadIdx.x & 63, lo = lane & 31, hi = lane >> 5, nl = tl_nat(lo);
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  float* A = Ap + ((int64_t)kb_glob * NB) * bp + (int64_t)kb_glob * NB;
-  float* Li = Linv + ((int64_t)kb_glob * NB) * bp + (int64_t)kb_glob * NB;
   auto S = [&](int t) { return cd_smem + t * kRsTile; };
   auto Ag = [&](int i, int j) { return A + (int64_t)(32 * i) * bp + 32 * j; };
   auto Xg = [&](int i, int j) { return Li + (int64_t)(32 * i) * bp + 32 * j; };
@@ -271,46 +308,41 @@ __global__ __launch_bounds__(512, 4) void k_chol_diag(float* __restrict__ Ap,
       for (int r = 0; r < 16; ++r) v[r] = (tl_row(r, hi) == lo) ? 1.f : 0.f;
       return v;
     };
-    f32x16 D, E, D1, E1, U;
-    cd_load_sym(D, Ag(0, 0), bp, nl, hi);
+    f32x16 D, E, U;
+    sym(D, 0);
     if (wave == 0) E = ident();
-    else cd_load_op(E, Ag(wave, 0), bp, nl, hi);
-    cd_load_sym(D1, Ag(1, 1), bp, nl, hi);
-    if (wave == 0) E1 = ident();
-    else if (wave < 3) cd_load_op(E1, Ag(1 + wave, 1), bp, nl, hi);
+    else op(E, wave, 0);
     int bad = -1;
-#pragma unroll
+    // a loop, not four copies: the code of an elimination is 6 KB, and a copy that is met for the first time waits
+    // for its instructions (2000 of 8000 cycles)
+#pragma clang loop unroll(disable)
     for (int j = 0; j < 4; ++j) {
-      int l = lo, h = hi;  // lane masks: an instruction each, not worth registers across phases
-      asm volatile("" : "+v"(l), "+v"(h));
-      if (wave == 0) {
-        const float dl = tl_eliminate<true>(D, E, U, aux, l, h);
-        rs_store(S(cd_l(j, j)), U, lo, hi);
-        rs_store(S(kCdT + j), E, lo, hi);
-        // first non-positive pivot in the order of elimination (what follows it is garbage)
-        const float dn = __shfl(dl, (lo & ~7) + ((lo & 7) >> 1) + 4 * (lo & 1), 64);
-        const unsigned long long m = __ballot(!(dn > 0.f)) & 0xffffffffull;
-        if (m && bad < 0) bad = 32 * j + __ffsll((long long)m) - 1;
-      } else if (wave + j < 4) {
-        (void)tl_eliminate<false>(D, E, E, aux, l, h);
-        rs_store(S(cd_l(j + wave, j)), E, lo, hi);
-      }
-      __syncthreads();
-      if (j < 3) {
-        const float* Lj = S(cd_l(j + 1, j));
-        if (wave + j + 1 < 4) {  // copies of the next diagonal tile, and the next tile
-          if (j == 0) {
-            D = D1;
-            E = E1;
+      if (wave + j < 4) {
+        if (j > 0) {  // copies of the diagonal tile, and the next tile
+          const float* Lj = S(cd_l(j, j - 1));
+          D = cd_get(S(j == 1 ? kCdB : j == 2 ? kCdA : kCdA + 2), lo, hi);
+          const CdSplit x = cd_split(Lj, lo, hi);
+          cd_sub(D, x, x);
+          if (wave == 0) {
+            E = ident();
           } else {
-            D = cd_get(S(j == 1 ? kCdA : kCdA + 2), lo, hi);
-            if (wave == 0) E = ident();
-            else E = cd_get(S(kCdA + 1), lo, hi);  // only j = 1, wave = 1: tile (3, 2)
+            E = cd_get(S(j == 2 ? kCdA + 1 : wave == 1 ? kCdB1 : kCdB2), lo, hi);  // j = 2: tile (3, 2)
+            cd_sub(E, x, cd_split(S(cd_l(j + wave, j - 1)), lo, hi));
           }
-          rs_mma<true>(D, Lj, Lj, lo, hi);
-          if (wave > 0) rs_mma<true>(E, Lj, S(cd_l(j + 1 + wave, j)), lo, hi);
+        }
+        const float dl = tl_eliminate<true>(D, E, U, aux, lo, hi, [&] {
+          if (j == 0) all_have();
+        });
+        rs_store(S(wave == 0 ? kCdT + j : cd_l(j + wave, j)), E, lo, hi);
+        if (wave == 0) {
+          rs_store(S(cd_l(j, j)), U, lo, hi);
+          // first non-positive pivot in the order of elimination (what follows it is garbage)
+          const float dn = __shfl(dl, (lo & ~7) + ((lo & 7) >> 1) + 4 * (lo & 1), 64);
+          const unsigned long long m = __ballot(!(dn > 0.f)) & 0xffffffffull;
+          if (m && bad < 0) bad = 32 * j + __ffsll((long long)m) - 1;
         }
       }
+      __syncthreads();
     }
     if (bad >= 0 && lane == 0) {
       const int64_t orig = b - ((int64_t)kb_glob * NB + bad);  // 1-based original column
@@ -320,12 +352,26 @@ __global__ __launch_bounds__(512, 4) void k_chol_diag(float* __restrict__ Ap,
   }
 
   // --------------------------------------------------------------------------------- beside it
+  // Wavefront 4 shares its SIMD with the longest chain and has the fewest products; what needs most of them is
+  // where the chains end first (wavefront 7, then 6).
   f32x16 X, V, Y;
   uint32_t top = 0;
-  if (wave == 4) cd_load_sym(X, Ag(2, 2), bp, nl, hi);
-  else if (wave == 5) cd_load_op(X, Ag(3, 2), bp, nl, hi);
-  else if (wave == 6) cd_load_sym(X, Ag(3, 3), bp, nl, hi);
-  else {
+  if (wave == 4) {
+    sym(X, 3);
+  } else if (wave == 5) {
+    op(Y, 2, 1);
+    op(X, 3, 2);
+  } else if (wave == 6) {
+    sym(Y, 1);
+    sym(X, 2);
+  } else {
+    op(Y, 3, 1);
+  }
+  all_have();
+  if (wave == 6) rs_store(S(kCdB), Y, lo, hi);
+  if (wave == 5) rs_store(S(kCdB1), Y, lo, hi);
+  if (wave == 7) rs_store(S(kCdB2), Y, lo, hi);
+  if (wave == 4) {
     const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int q = 0; q < 24; ++q) {  // zeros of the inverse: tiles (0,1) (0,2) (0,3) (1,2) (1,3) (2,3)
@@ -335,34 +381,37 @@ __global__ __launch_bounds__(512, 4) void k_chol_diag(float* __restrict__ Ap,
   }
   __syncthreads();  // ---- phase 1: column 0 of L and T_0 are there
   if (wave == 4) {
-    rs_mma<true>(X, S(cd_l(2, 0)), S(cd_l(2, 0)), lo, hi);
-    rs_store(S(kCdA), X, lo, hi);
-    cd_store_acc(Xg(0, 0), bp, cd_get(S(kCdT), lo, hi), nl, hi, top);
-    cd_store_op(Ag(0, 0), bp, S(cd_l(0, 0)), lo, hi);
+    const CdSplit x = cd_split(S(cd_l(3, 0)), lo, hi);
+    cd_sub(X, x, x);
+    cd_store_op(Ag(3, 0), bp, S(cd_l(3, 0)), lo, hi);
   } else if (wave == 5) {
-    rs_mma<true>(X, S(cd_l(2, 0)), S(cd_l(3, 0)), lo, hi);
+    cd_sub(X, cd_split(S(cd_l(2, 0)), lo, hi), cd_split(S(cd_l(3, 0)), lo, hi));
     rs_store(S(kCdA + 1), X, lo, hi);
     cd_store_op(Ag(1, 0), bp, S(cd_l(1, 0)), lo, hi);
     cd_store_op(Ag(2, 0), bp, S(cd_l(2, 0)), lo, hi);
   } else if (wave == 6) {
-    rs_mma<true>(X, S(cd_l(3, 0)), S(cd_l(3, 0)), lo, hi);
-    cd_store_op(Ag(3, 0), bp, S(cd_l(3, 0)), lo, hi);
+    const CdSplit x = cd_split(S(cd_l(2, 0)), lo, hi);
+    cd_sub(X, x, x);
+    rs_store(S(kCdA), X, lo, hi);
+    cd_store_acc(Xg(0, 0), bp, cd_get(S(kCdT), lo, hi), nl, hi, top);
+    cd_store_op(Ag(0, 0), bp, S(cd_l(0, 0)), lo, hi);
   } else {
     V = cd_zero();
     rs_mma<false>(V, S(cd_l(1, 0)), S(kCdT), lo, hi);  // V_10
   }
   __syncthreads();  // ---- phase 2: column 1 of L and T_1
   if (wave == 4) {
-    V = cd_zero();
-    rs_mma<false>(V, S(cd_l(2, 1)), S(kCdT + 1), lo, hi);  // V_21
+    const CdSplit x = cd_split(S(cd_l(3, 1)), lo, hi);
+    cd_sub(X, x, x);
+    rs_store(S(kCdA + 2), X, lo, hi);
   } else if (wave == 5) {
     cd_store_acc(Xg(1, 1), bp, cd_get(S(kCdT + 1), lo, hi), nl, hi, top);
     cd_store_op(Ag(1, 1), bp, S(cd_l(1, 1)), lo, hi);
     cd_store_op(Ag(2, 1), bp, S(cd_l(2, 1)), lo, hi);
     cd_store_op(Ag(3, 1), bp, S(cd_l(3, 1)), lo, hi);
   } else if (wave == 6) {
-    rs_mma<true>(X, S(cd_l(3, 1)), S(cd_l(3, 1)), lo, hi);
-    rs_store(S(kCdA + 2), X, lo, hi);
+    V = cd_zero();
+    rs_mma<false>(V, S(cd_l(2, 1)), S(kCdT + 1), lo, hi);  // V_21
   } else {
     X = cd_minus_tv(S(kCdT + 1), V, lo, hi);  // X_10
     cd_store_acc(Xg(1, 0), bp, X, nl, hi, top);
@@ -372,18 +421,18 @@ __global__ __launch_bounds__(512, 4) void k_chol_diag(float* __restrict__ Ap,
   }
   __syncthreads();  // ---- phase 3: column 2 of L and T_2
   if (wave == 4) {
+    cd_store_acc(Xg(2, 2), bp, cd_get(S(kCdT + 2), lo, hi), nl, hi, top);
+    cd_store_op(Ag(2, 2), bp, S(cd_l(2, 2)), lo, hi);
+    cd_store_op(Ag(3, 2), bp, S(cd_l(3, 2)), lo, hi);
+  } else if (wave == 5) {
+    V = cd_zero();
+    rs_mma<false>(V, S(cd_l(3, 2)), S(kCdT + 2), lo, hi);  // V_32
+  } else if (wave == 6) {
     Y = cd_minus_tv(S(kCdT + 2), V, lo, hi);  // X_21
     cd_store_acc(Xg(2, 1), bp, Y, nl, hi, top);
     V = cd_zero();
     rs_mma<false>(V, S(cd_l(3, 1)), S(kCdT + 1), lo, hi);
     rs_mma<false>(V, S(cd_l(3, 2)), Y, lo, hi);  // V_31
-  } else if (wave == 5) {
-    V = cd_zero();
-    rs_mma<false>(V, S(cd_l(3, 2)), S(kCdT + 2), lo, hi);  // V_32
-  } else if (wave == 6) {
-    cd_store_acc(Xg(2, 2), bp, cd_get(S(kCdT + 2), lo, hi), nl, hi, top);
-    cd_store_op(Ag(2, 2), bp, S(cd_l(2, 2)), lo, hi);
-    cd_store_op(Ag(3, 2), bp, S(cd_l(3, 2)), lo, hi);
   } else {
     Y = cd_minus_tv(S(kCdT + 2), V, lo, hi);  // X_20
     cd_store_acc(Xg(2, 0), bp, Y, nl, hi, top);
@@ -393,13 +442,304 @@ __global__ __launch_bounds__(512, 4) void k_chol_diag(float* __restrict__ Ap,
     rs_mma<false>(V, S(cd_l(3, 2)), Y, lo, hi);  // V_30
   }
   __syncthreads();  // ---- L_33 and T_3
-  if (wave == 6) {
+  if (wave == 4) {
     cd_store_acc(Xg(3, 3), bp, cd_get(S(kCdT + 3), lo, hi), nl, hi, top);
     cd_store_op(Ag(3, 3), bp, S(cd_l(3, 3)), lo, hi);
-  } else {  // wavefronts 7, 4, 5: X_30, X_31, X_32
-    cd_store_acc(Xg(3, wave == 7 ? 0 : wave - 3), bp, cd_minus_tv(S(kCdT + 3), V, lo, hi), nl, hi, top);
+  } else {  // wavefronts 7, 6, 5: X_30, X_31, X_32
+    cd_store_acc(Xg(3, 7 - wave), bp, cd_minus_tv(S(kCdT + 3), V, lo, hi), nl, hi, top);
   }
   raise_bound(bound, __uint_as_float(top));
+}
+
+// 512 threads at 128 registers: half of a compute unit's registers, so that the workgroup finds
+// room beside one workgroup of the matrix products.
+__global__ __launch_bounds__(512, 4) void k_chol_diag(float* __restrict__ Ap, float* __restrict__ Linv, int64_t bp,
+                                                      int kb_glob, int64_t b, float* __restrict__ bound,
+                                                      int32_t* __restrict__ info) {
+  extern __shared__ __attribute__((aligned(16))) float cd_smem[];
+  const int lane = threadIdx.x & 63, nl = tl_nat(lane & 31), hi = lane >> 5;
+  float* A = Ap + ((int64_t)kb_glob * NB) * bp + (int64_t)kb_glob * NB;
+  float* Li = Linv + ((int64_t)kb_glob * NB) * bp + (int64_t)kb_glob * NB;
+  cd_block(
+      cd_smem, A, Li, bp, kb_glob, b, bound, info,
+      [&](f32x16& v, int i) { cd_load_op(v, A + (int64_t)(32 * i) * (bp + 1), bp, nl, hi); },
+      [&](f32x16& v, int i, int j) { cd_load_op(v, A + (int64_t)(32 * i) * bp + 32 * j, bp, nl, hi); }, [] {});
+}
+
+// ------------------------------------------------------------------------------------------
+// A whole step of the factorisation in one launch, for the last block rows: workgroup 0 goes from block
+// column k to the next diagonal block,
+//     L_{k+1,k} = A_{k+1,k} Linv_kk^T,  A_{k+1,k+1} -= L_{k+1,k} L_{k+1,k}^T,  cd_block(k + 1),
+// and every other workgroup updates one tile right of it, A_ij -= L_ik L_jk^T (i >= j > k), with L_ik and L_jk worked
+// out for itself: the tiles of a step need no launch between panel and update, and with up to 40 block rows they take no
+// longer than the diagonal block.  A step is 22.5 us (2.5 for its first loads, 2.3 panel, 2.5 update, 14.5 block); as
+// separate launches it was 41 (block 23.5, panel 8.5, update 8.5), and 22 to 31 more for the strip of every fourth:
+// 512 columns 173 -> 129 us, 2048 822 -> 504, 4096 1694 -> 1058.
+//
+// What a launch reads of A_ik no workgroup of it may overwrite, so tiles of the column that comes next (j = k + 1) do not
+// go to their place in A', which takes L_ij in the next launch, but to block (j, i), right of the diagonal, where
+// nothing else lives; and in the form that their only reader wants: split into fp16 pairs in the layout of the
+// operands (512 consecutive bytes per half wavefront and load).  STORED: the first launch, whose panel is in A'.
+//
+// Products as in k_gemm_direct: two-way split, all four partial products, two partial sums.
+struct StepArgs {
+  float *Ap, *Linv;
+  int64_t bp, b;
+  int k, nb;
+  float* bound_inv;
+  int32_t* info;
+};
+struct SplitTile {  // 32 x 32 in operand layout: x1 and x2 of registers 0 .. 7, then of 8 .. 15
+  u32x4 p[4];
+};
+__device__ __forceinline__ SplitTile st_split(const f32x4 (&x)[4], float s) {
+  SplitTile t;
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    f16x8 h, l;
+    split8_h2(x[2 * m], x[2 * m + 1], s, h, l);
+    t.p[2 * m] = __builtin_bit_cast(u32x4, h);
+    t.p[2 * m + 1] = __builtin_bit_cast(u32x4, l);
+  }
+  return t;
+}
+// rows of a matrix <-> operand layout; p is uniform, at = lo * ld + 4 * hi the lane's offset (32 bits: one register)
+__device__ __forceinline__ void st_rows(f32x4 (&x)[4], const float* p, uint32_t at) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) x[q] = *reinterpret_cast<const f32x4*>(p + 8 * q + at);
+}
+__device__ __forceinline__ void st_rows_out(float* p, const f32x4 (&x)[4], uint32_t at) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) *reinterpret_cast<f32x4*>(p + 8 * q + at) = x[q];
+}
+// A split tile in LDS, 4 KB, pieces in the order of the lanes.  First the ten of the inverse; the tiles (r, 2) and (r, 3)
+// of L_jk behind them, as soon as they are there, (r, 0) and (r, 1) in their place.
+constexpr int kStTile = 1024;
+__device__ __forceinline__ int st_slot(int r, int n) { return (n >= 2 ? 10 + 2 * r : 2 * r) + (n == 1 || n == 2 ? 1 : 0); }
+constexpr size_t kStepSmem = 18 * kStTile * sizeof(float);
+static_assert(kStepSmem >= kCholDiagSmem, "the diagonal block is done in the same launch");
+__device__ __forceinline__ void st_put(float* t, const SplitTile& v, int lane) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) *reinterpret_cast<u32x4*>(t + 256 * e + 4 * lane) = v.p[e];
+}
+__device__ __forceinline__ SplitTile st_get(const float* t, int lane) {
+  SplitTile v;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v.p[e] = *reinterpret_cast<const u32x4*>(t + 256 * e + 4 * lane);
+  return v;
+}
+// tile (r, kt) of a block that waits right of the diagonal (p: the block): a piece is two rows of 512 bytes; at = hi * ld
+// + 4 * lo
+__device__ __forceinline__ int64_t st_parked(int r, int kt, int e, int64_t ld) { return (8 * (4 * r + kt) + 2 * e) * ld; }
+__device__ __forceinline__ SplitTile st_fetch(const float* p, int r, int kt, int64_t ld, uint32_t at) {
+  SplitTile v;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v.p[e] = *reinterpret_cast<const u32x4*>(p + st_parked(r, kt, e, ld) + at);
+  return v;
+}
+// 16 of the 32 columns of a split tile: of one in LDS, of one in registers
+struct SplitHalf {
+  f16x8 h, l;
+};
+__device__ __forceinline__ SplitHalf st_half(const float* t, int m, int lane) {
+  return {*reinterpret_cast<const f16x8*>(t + 512 * m + 4 * lane),
+          *reinterpret_cast<const f16x8*>(t + 512 * m + 256 + 4 * lane)};
+}
+__device__ __forceinline__ SplitHalf st_half(const SplitTile& t, int m) {
+  return {__builtin_bit_cast(f16x8, t.p[2 * m]), __builtin_bit_cast(f16x8, t.p[2 * m + 1])};
+}
+// (acc + acc2)[x][y] = sum over 32 KT values k of a[x][k] b[y][k]; in registers x, y the lane.  a(kt, m), b(kt, m):
+// halves of the operands' tiles, fetched a tile at a time (all of them at once are spilled).
+template <int KT, typename A, typename B>
+__device__ __forceinline__ void st_product(f32x16& acc, f32x16& acc2, const A& a, const B& b) {
+  acc = cd_zero();
+  acc2 = cd_zero();
+#pragma unroll
+  for (int kt = 0; kt < KT; ++kt) {
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      const SplitHalf x = a(kt, m), y = b(kt, m);
+      acc2 = __builtin_amdgcn_mfma_f32_32x32x16_f16(x.l, y.l, acc2, 0, 0, 0);
+      acc2 = __builtin_amdgcn_mfma_f32_32x32x16_f16(x.h, y.l, acc2, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(x.h, y.h, acc, 0, 0, 0);
+      acc2 = __builtin_amdgcn_mfma_f32_32x32x16_f16(x.l, y.h, acc2, 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+// L tile from its rows of A (split, k-tiles 0 .. n) and tile row n of the inverse in LDS
+template <int KT>
+__device__ __forceinline__ void st_panel(f32x4 (&x)[4], const SplitTile (&R)[4], const float* inv, float f, int lane) {
+  constexpr int n = KT - 1;
+  f32x16 acc, acc2;
+  st_product<KT>(
+      acc, acc2, [&](int kt, int m) { return st_half(inv + (n * (n + 1) / 2 + kt) * kStTile, m, lane); },
+      [&](int kt, int m) { return st_half(R[kt], m); });
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[q][e] = f * (acc[4 * q + e] + acc2[4 * q + e]);
+}
+
+template <bool STORED>
+__global__ __launch_bounds__(512, 4) void k_chol_step(StepArgs g) {
+  extern __shared__ __attribute__((aligned(16))) float cd_smem[];
+  const int lane = threadIdx.x & 63, lo = lane & 31, hi = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int64_t bp = g.bp;
+  const int k = g.k;
+  // tile 0 is the diagonal block; column by column behind it
+  int i = (int)blockIdx.x, j = k + 1;
+  for (; i >= g.nb - j; ++j) i -= g.nb - j;
+  i += j;
+  const bool diag = blockIdx.x == 0, next = j == k + 1;
+  auto blk = [&](int r, int c) { return g.Ap + (int64_t)r * NB * bp + (int64_t)c * NB; };
+  const float sl = h2_scale(kBoundL);
+  const int r = wave >> 1, half = wave & 1;
+  const uint32_t at_row = (uint32_t)lo * (uint32_t)bp + 4 * hi, at_parked = (uint32_t)hi * (uint32_t)bp + 4 * lo;
+
+  // ---- L_jk into LDS as split tiles [row tile][k-tile]; a wavefront makes two of a row, five k-tiles in all
+  f32x4 x[4];
+  SplitTile p1;
+  const int n0 = half ? 2 : 3, n1 = half ? 1 : 0;
+  float fp = 0.f;
+  // a line of the next diagonal block per thread: its tiles come from the L2 later on (its loads in front of
+  // their products waited 2 us for memory)
+  float touch = 0.f;
+  if (diag) touch = blk(j, j)[(int64_t)(threadIdx.x >> 2) * bp + 32 * (threadIdx.x & 3)];
+  if constexpr (STORED) {
+    const float* Lj = blk(j, k) + (int64_t)(32 * r) * bp;
+    f32x4 y[4];
+    st_rows(x, Lj + 32 * n0, at_row);
+    st_rows(y, Lj + 32 * n1, at_row);
+    st_put(cd_smem + st_slot(r, n0) * kStTile, st_split(x, sl), lane);
+    p1 = st_split(y, sl);
+  } else {
+    const float sa = h2_scale(kBoundA), si = h2_scale(g.bound_inv[k]);
+    fp = pow2_inv(sa) * pow2_inv(si);
+    const float* Li = g.Linv + (int64_t)k * NB * (bp + 1);
+    const float* Rj = blk(k, j);
+    SplitTile R[4];
+    // the inverse's tiles, in rows: 0 | 1 2 | 3 4 5 | 6 7 8 9
+    const int e0 = wave, t0 = e0 < 1 ? 0 : e0 < 3 ? 1 : e0 < 6 ? 2 : 3, c0 = e0 - t0 * (t0 + 1) / 2;
+    f32x4 y[4];
+    st_rows(x, Li + (int64_t)(32 * t0) * bp + 32 * c0, at_row);
+    if (wave < 2) st_rows(y, Li + (int64_t)96 * bp + 32 * (2 + wave), at_row);
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt)
+      if (kt <= n0) R[kt] = st_fetch(Rj, r, kt, bp, at_parked);
+    st_put(cd_smem + e0 * kStTile, st_split(x, si), lane);
+    if (wave < 2) st_put(cd_smem + (8 + wave) * kStTile, st_split(y, si), lane);
+    __syncthreads();
+    float* Lj = blk(j, k) + (int64_t)(32 * r) * bp;
+    auto keep = [&](int n) {
+      if (diag) st_rows_out(Lj + 32 * n, x, at_row);
+    };
+    if (half == 0) {
+      st_panel<4>(x, R, cd_smem, fp, lane);
+      keep(3);
+      st_put(cd_smem + st_slot(r, n0) * kStTile, st_split(x, sl), lane);
+      st_panel<1>(x, R, cd_smem, fp, lane);
+      keep(0);
+    } else {
+      st_panel<3>(x, R, cd_smem, fp, lane);
+      keep(2);
+      st_put(cd_smem + st_slot(r, n0) * kStTile, st_split(x, sl), lane);
+      st_panel<2>(x, R, cd_smem, fp, lane);
+      keep(1);
+    }
+    p1 = st_split(x, sl);
+  }
+  auto put_panel = [&]() {
+    if (!STORED) __syncthreads();  // the inverse has been read
+    st_put(cd_smem + st_slot(r, n1) * kStTile, p1, lane);
+    __syncthreads();
+  };
+  const float fl = -pow2_inv(sl) * pow2_inv(sl);
+
+  if (diag) {
+    float* A = blk(j, j);
+    const int nl = tl_nat(lo), lp = nl + 32 * hi;  // rows in elimination order
+    asm volatile("" ::"v"(touch));
+    put_panel();
+    auto minus = [&](f32x16& v, int ti, int tj) {
+      f32x4 old[4];
+      cd_load_rows(old, A + (int64_t)(32 * ti) * bp + 32 * tj, bp, nl, hi);
+      f32x16 acc, acc2;
+      st_product<4>(
+          acc, acc2, [&](int kt, int m) { return st_half(cd_smem + st_slot(tj, kt) * kStTile, m, lp); },
+          [&](int kt, int m) { return st_half(cd_smem + st_slot(ti, kt) * kStTile, m, lp); });
+      cd_from_rows(v, old);
+#pragma unroll
+      for (int e = 0; e < 16; ++e) v[e] += fl * (acc[e] + acc2[e]);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    cd_block(
+        cd_smem, A, g.Linv + (int64_t)j * NB * (bp + 1), bp, j, g.b, g.bound_inv + j, g.info,
+        [&](f32x16& v, int t) { minus(v, t, t); }, [&](f32x16& v, int ti, int tj) { minus(v, ti, tj); },
+        [] { __syncthreads(); });
+    return;
+  }
+
+  // ---- tile (i, j): a wavefront has 32 rows of it and two of the column tiles; L_ik of its rows in registers
+  SplitTile P[4];
+  if (i != j) {
+    if constexpr (STORED) {
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        st_rows(x, blk(i, k) + (int64_t)(32 * r) * bp + 32 * n, at_row);
+        P[n] = st_split(x, sl);
+      }
+    } else {
+      const float* Ri = blk(k, i);
+      SplitTile R[4];
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt) R[kt] = st_fetch(Ri, r, kt, bp, at_parked);
+      float* Lik = blk(i, k) + (int64_t)(32 * r) * bp;
+      auto keep = [&](int n) {  // the tiles of the next column have all rows; two k-tiles per wavefront
+        if (next && (n >> 1) == half) st_rows_out(Lik + 32 * n, x, at_row);
+      };
+      st_panel<4>(x, R, cd_smem, fp, lane);
+      keep(3);
+      P[3] = st_split(x, sl);
+      st_panel<3>(x, R, cd_smem, fp, lane);
+      keep(2);
+      P[2] = st_split(x, sl);
+      st_panel<2>(x, R, cd_smem, fp, lane);
+      keep(1);
+      P[1] = st_split(x, sl);
+      st_panel<1>(x, R, cd_smem, fp, lane);
+      keep(0);
+      P[0] = st_split(x, sl);
+    }
+  }
+  put_panel();
+  if (i == j) {
+#pragma unroll
+    for (int n = 0; n < 4; ++n) P[n] = st_get(cd_smem + st_slot(r, n) * kStTile, lane);
+  }
+  float* C = blk(i, j) + (int64_t)(32 * r) * bp;
+  float* parked = blk(j, i);
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int c = 2 * half + h;
+    f32x16 acc, acc2;
+    st_product<4>(
+        acc, acc2, [&](int n, int m) { return st_half(cd_smem + st_slot(c, n) * kStTile, m, lane); },
+        [&](int n, int m) { return st_half(P[n], m); });
+    st_rows(x, C + 32 * c, at_row);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[q][e] += fl * (acc[4 * q + e] + acc2[4 * q + e]);
+    if (next) {
+      const SplitTile t = st_split(x, h2_scale(kBoundA));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) *reinterpret_cast<u32x4*>(parked + st_parked(r, c, e, bp) + at_parked) = t.p[e];
+    } else {
+      st_rows_out(C + 32 * c, x, at_row);
+    }
+  }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -708,6 +1048,10 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
   THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_chol_diag),
                                        hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)kCholDiagSmem));
+  THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_chol_step<true>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStepSmem));
+  THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_chol_step<false>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStepSmem));
   constexpr int kOuter = 4;
   const int n_outer = (nb + kOuter - 1) / kOuter;
   AuxStream aux(s, n_outer > 2 ? 2 * n_outer : 0, single_stream);
@@ -804,6 +1148,8 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
     return THANOS_OK;
   };
   int pending_join = -1;  // event index recorded on the aux stream after the last "rest"
+  // the last block rows: one launch per step, every tile updated in every step
+  const int first_step = nb <= kStepAll ? 0 : (nb - kStepLast + kOuter - 1) / kOuter * kOuter;
   for (int k = 0; k < nb; ++k) {
     hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(512), kCholDiagSmem, s, Ap, Linv, bp, k, b, bound_inv + k,
                        info);
@@ -820,6 +1166,20 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
     thanos_status st = gemm_bounded(s, rem, NB, NB, 1.f, panel, bp, kBoundA, dinv, bp, 0.f, bound_inv + k,
                                     0.f, panel, bp, false, company);
     if (st != THANOS_OK) return st;
+    if (k == first_step) {
+      if (pending_join >= 0) THANOS_CHECK(aux.join(pending_join));
+      pending_join = -1;
+      for (int t = k; t + 1 < nb; ++t) {
+        const StepArgs a{Ap, Linv, bp, b, t, nb, bound_inv, info};
+        const int rows = nb - 1 - t;
+        hipLaunchKernelGGL(t == k ? k_chol_step<true> : k_chol_step<false>, dim3((unsigned)(rows * (rows + 1) / 2)),
+                           dim3(512), kStepSmem, s, a);
+        THANOS_LAUNCH_CHECK();
+        if ((t + 1) % kOuter == 0 && t + 2 < nb) THANOS_CHECK(trinv_upto(t));
+      }
+      THANOS_CHECK(trinv_upto(nb - 1));
+      break;
+    }
     if ((k + 1) % kOuter == 0) {
       st = trinv_upto(k);
       if (st != THANOS_OK) return st;

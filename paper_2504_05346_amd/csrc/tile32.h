@@ -123,24 +123,35 @@ __device__ __forceinline__ float pivot_scale(float d) {
 // cross-lane read), D -= u1 u1^T / d1 + u2 u2^T / d2 is one MFMA instead of two half-empty
 // ones.  F is the Cholesky factor in that pivot order: a row-permuted triangle, or a triangle if
 // the tile was loaded with its rows and columns in the order tl_nat.
-template <bool KEEP_F>
+// mid() is called half way.
+struct TlNothing {
+  __device__ __forceinline__ void operator()() const {}
+};
+template <bool KEEP_F, typename Mid = TlNothing>
 __device__ __forceinline__ float tl_eliminate(f32x16 D, f32x16& E, f32x16& U, float* aux, int lo,
-                                              int hi) {
-  const int pidx = 4 * (lo >> 3) + (lo & 3);  // pair that eliminates column lo
-  float dl = 1.f;                             // pivot of column lo
+                                              int hi, const Mid& mid = Mid()) {
+  // place of column lo in the order of elimination, one less in the upper half: what a half of the second operand
+  // keeps; and the column whose pivot the half takes, shifted to k1
+  const int rank = 2 * (4 * (lo >> 3) + (lo & 3)) + ((lo >> 2) & 1) - hi, own = lo - 4 * hi;
+  float exponents = __uint_as_float(0x7f800000u);
+  asm volatile("" : "+v"(exponents));
+  float dl = 1.f;                             // pivot of column lo, in the half that takes it
 #pragma unroll
   for (int t = 0; t < 16; ++t) {              // pair t: rows k1 and k2 = k1 + 4, both in D[t]
+    if (t == 8) mid();
     const int k1 = 8 * (t >> 2) + (t & 3), k2 = k1 + 4;
     const float v = D[t];                     // lower half: D[k1][lo], upper half: D[k2][lo]
-    const float x = lower_half(v);        // D[k1][lo] in both halves
+    const float x = lower_half(v);            // D[k1][lo] in both halves
     const float d1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k1));
     const float c12 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k2));
     const float d2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32 + k2));
     // 1 / d1 and 1 / d2' (d2' = d2 - c12^2 / d1, the pivot of k2 after the elimination of k1)
     // from two INDEPENDENT reciprocals, of d1 and of det = d1 d2 - c12^2: d2' = det / d1, row k1
     // scaled to a pivot e1 = ps d1 near one.  The wavefront is alone on this chain, so its length is
-    // what counts.
-    const float ps = pivot_scale(d1);
+    // what counts: every instruction is 4 cycles, an MFMA 64 (the wavefront's own vector instructions wait for it), and
+    // a detour of a value through the scalar unit 14.
+    float ps;                                 // pivot_scale(d1), without that detour
+    asm("v_bfi_b32 %0, %1, 0, %2" : "=v"(ps) : "s"(d1), "v"(exponents));
     const float e1 = ps * d1, e12 = ps * c12;
     const float cc = e12 * c12;
     const float det = fmaf(e1, d2, -cc) - fmaf(e12, c12, -cc);
@@ -155,20 +166,23 @@ __device__ __forceinline__ float tl_eliminate(f32x16 D, f32x16& E, f32x16& U, fl
     const float mh = hi ? m : 0.f;
     // second operands: u1 in the lower half, u2 in the upper half; columns eliminated by
     // earlier pairs are zero, and so is column k1 of u2
-    const bool live = pidx >= t && !(hi && lo == k1);
-    const float bop = live ? fmaf(-mh, x, v) : 0.f;
+    float bop = fmaf(-mh, x, v);
+    bop = rank >= 2 * t ? bop : 0.f;
     const float aop = bop * (hi ? -r2 : -r1);
     D = __builtin_amdgcn_mfma_f32_32x32x2f32(aop, bop, D, 0, 0, 0);
-    dl = (lo == k1) ? d1 : (lo == k2) ? d2p : dl;
     if (KEEP_F) U[t] = bop;
     // the same row operations on E: row k1 as it is, row k2 after the operation of k1; the
     // pivot rows themselves stay
     const float ev = E[t];
     const float xe = lower_half(ev);
     const float be = fmaf(-mh, xe, ev);
-    const float a2 = (lo == (hi ? k2 : k1)) ? 0.f : aop;
+    const bool mine = own == k1;
+    const float a2 = mine ? 0.f : aop;
+    dl = mine ? (hi ? d2p : d1) : dl;
     E = __builtin_amdgcn_mfma_f32_32x32x2f32(a2, be, E, 0, 0, 0);
   }
+  const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(dl), __float_as_uint(dl), false, false);
+  dl = __uint_as_float((lo >> 2) & 1 ? halves[1] : halves[0]);
   float isd = __builtin_amdgcn_rsqf(dl);
   isd = fmaf(0.5f * isd, fmaf(-dl * isd, isd, 1.f), isd);
   aux[lo] = isd;  // both halves write the same value
