@@ -972,10 +972,17 @@ __global__ __launch_bounds__(SMAX, (SMAX == 128 ? 3 : 1)) void k_solve_wide(Solv
   rsc_lower(a, i, fabsf(wrow[tid]));
 }
 
-// Lane `lane` (a constant) of v <- the bits s, uniform.  (The wait is for a v_readlane that has just
-// produced s, which the compiler does not look for inside the asm.)
-#define set_lane(v, s, lane) \
-  asm volatile("s_nop 1\n\tv_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(s), "i"(lane))
+// Lanes l .. l + 7 (constants) of v <- the bits s[0 .. 7], uniform.  (The wait is for the v_readlane that has just
+// produced the last of them, which the compiler does not look for inside the asm; one wait for each of them was a third
+// of a sweep.)
+#define set_lanes8(v, s, l)                                                                                        \
+  asm volatile(                                                                                                    \
+      "s_nop 1\n\tv_writelane_b32 %0, %1, %9\n\tv_writelane_b32 %0, %2, %10\n\tv_writelane_b32 %0, %3, %11\n\t"        \
+      "v_writelane_b32 %0, %4, %12\n\tv_writelane_b32 %0, %5, %13\n\tv_writelane_b32 %0, %6, %14\n\t"                  \
+      "v_writelane_b32 %0, %7, %15\n\tv_writelane_b32 %0, %8, %16"                                                 \
+      : "+v"(v)                                                                                                    \
+      : "s"(s[0]), "s"(s[1]), "s"(s[2]), "s"(s[3]), "s"(s[4]), "s"(s[5]), "s"(s[6]), "s"(s[7]), "i"(l), "i"((l) + 1), \
+        "i"((l) + 2), "i"((l) + 3), "i"((l) + 4), "i"((l) + 5), "i"((l) + 6), "i"((l) + 7))
 
 // ------------------------------------------------------------------------------------------
 // Mask + per-row solve on the matrix cores for systems of up to 32 NTR unknowns (NTR = 2 or 3,
@@ -990,23 +997,26 @@ __global__ __launch_bounds__(SMAX, (SMAX == 128 ? 3 : 1)) void k_solve_wide(Solv
 // broadcast of the pivots and one cross-lane read per tile row (the second pivot's row must
 // first see the elimination of the first).  The columns of -L~ go to LDS, and L~ y = u,
 // L~^T lambda = D^-1 y are solved afterwards by sweeps over them.
-// NTR = 2 serves n:m at B = 128 (s = 64 for 2:4 and 4:8); NTR = 3 the unstructured mode at
-// B = 128, where s scatters around 64.
+// NTR = 2 serves n:m at B = 128 (s = 64 for 2:4 and 4:8), and the unstructured mode at B = 128, where s scatters around
+// 64, for more rows than NTR = 3 can run at once: rows with more than 64 go through the complement.
+// A row waits for itself most of its 27000 cycles, so what counts for many rows is how many a compute unit holds: 8 KB
+// of LDS each and at most 102 registers, sixteen or twenty.  4096 rows at 50 %: 35 us per block instead of 53 (NTR = 3, eight).
 template <int NTR>
 struct SolveMfmaSmem {
   static constexpr int N = 32 * NTR;
   // strict lower triangle of L~, packed by rows, and room for the lanes that have nothing to store;
   // before the elimination and after the back-substitution the first 256 floats hold the row's
   // weights (then lambda) and metric
-  float L[N * (N - 1) / 2 + 64];
-  float d[N];  // pivots by position
-  alignas(4) unsigned char q[128];
+  float L[N * (N - 1) / 2 + 16];
+  alignas(4) unsigned char q[NTR == 2 ? 64 : 128];
 };
+
+static_assert(sizeof(SolveMfmaSmem<2>) == 8192, "five rows to a quarter of a compute unit's LDS");
 
 // FULL: the host knows that every row has either no unknown or exactly 32 NTR (n:m on a whole
 // block): the padding logic folds away.
 template <int SEL, int WPB, int NTR, bool FULL = false>
-__global__ __launch_bounds__(64 * WPB, NTR == 2 ? 4 : 3) void k_solve_mfma(SolveArgs a) {
+__global__ __launch_bounds__(64 * WPB, NTR == 2 ? 5 : 3) void k_solve_mfma(SolveArgs a) {
   constexpr int CPL = 2;  // block width <= 128
   constexpr int NZ = (NTR + 1) / 2;  // registers holding y / d: rows 64 z + lane
   extern __shared__ __attribute__((aligned(16))) char solve_smem[];
@@ -1112,13 +1122,27 @@ __global__ __launch_bounds__(64 * WPB, NTR == 2 ? 4 : 3) void k_solve_mfma(Solve
   const int nt = FULL ? NTR : (ns + 31) >> 5;
   const int pad = FULL ? 0 : 32 * nt - ns;
   auto valid = [&](int m) { return FULL || m < 32 - pad || (m >= 32 && m - pad < ns); };
+  // whether positions k .. k + 7 (k a multiple of 8; the same indices) are eliminated: asked of the first tile row only
+  auto eliminated = [&](int k) { return FULL || k >= 32 || k < 32 - pad; };
   // q[m] = block column of matrix index m (column 0 where there is none: what it fetches is in
   // bounds and masked or never used), four of them to a word
   if (!FULL) {
-    if (lane < 32) reinterpret_cast<unsigned int*>(sm.q)[lane] = 0u;
+    if (lane < (int)sizeof(sm.q) / 4) reinterpret_cast<unsigned int*>(sm.q)[lane] = 0u;
     WAVE_SYNC();
   }
-  if (comp) {  // the KEPT columns of the block
+  if (comp) {  // the removed columns as a list, with their weights; then the KEPT columns of the block
+#pragma unroll
+    for (int r = 0; r < CPL; ++r) {
+      key[lane + 64 * r] = 0.f;
+      reinterpret_cast<unsigned char*>(wrow)[lane + 64 * r] = 0;
+    }
+    WAVE_SYNC();
+#pragma unroll
+    for (int r = 0; r < CPL; ++r)
+      if (sel[r]) {
+        key[myrank[r]] = us[r];
+        reinterpret_cast<unsigned char*>(wrow)[myrank[r]] = (unsigned char)(lane + 64 * r);
+      }
     int before = 0;
 #pragma unroll
     for (int r = 0; r < CPL; ++r) {
@@ -1150,39 +1174,54 @@ __global__ __launch_bounds__(64 * WPB, NTR == 2 ? 4 : 3) void k_solve_mfma(Solve
     rsc_set(a, i, 0.f, old_rsc);
     return;
   }
-  // y[r] = sum_a x[a] K[a][lane + 64 r] for this wavefront (x in LDS, zeros skipped)
-  auto matvec_k = [&](const float* x, float (&y)[CPL]) {
+  // (y[0], y[1]) = sum over e < n of x[e] K[idx[e]][2 lane, 2 lane + 1], x and idx in LDS, filled up with zeros to a
+  // multiple of 16; sixteen rows of K in flight.  A complement row reads every row of K once: the removed ones for w~ K, the
+  // kept ones for y~ K.  (All rows for both, 32 in flight: 4096 x 4096 at 50 % 8.53 ms; rows found bit by bit in the
+  // masks 8.83.)
+  auto matvec_k = [&](const float* x, const unsigned char* idx, int n) {
+    const unsigned int at = min(2 * lane, (a.bw - 1) & ~1);  // at the end of an odd block one value past it is read
+    f32x2 y = {0.f, 0.f};
+#pragma clang loop unroll(disable)
+    for (int e0 = 0; e0 < n; e0 += 16) {
+      f32x2 k[16];
 #pragma unroll
-    for (int r = 0; r < CPL; ++r) y[r] = 0.f;
-    for (int aa = 0; aa < a.bw; ++aa) {
-      const float xa = x[aa];
-      if (xa == 0.f) continue;
-      const float* kr = a.Kc + (int64_t)aa * a.ldk;
+      for (int e4 = 0; e4 < 4; ++e4) {
+        const unsigned int i4 = reinterpret_cast<const unsigned int*>(idx + e0)[e4];
 #pragma unroll
-      for (int r = 0; r < CPL; ++r) {
-        const int col = lane + 64 * r;
-        if (col < a.bw) y[r] = fmaf(xa, kr[col], y[r]);
+        for (int e = 0; e < 4; ++e)
+          k[4 * e4 + e] = *reinterpret_cast<const f32x2u*>(
+              a.Kc + (__umul24((i4 >> (8 * e)) & 255u, (unsigned int)a.ldk) + at));
+      }
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        y[0] = fmaf(x[e0 + e], k[e][0], y[0]);
+        y[1] = fmaf(x[e0 + e], k[e][1], y[1]);
       }
     }
+    return y;
   };
+  f32x2 wk = {0.f, 0.f};  // w~ K, columns 2 lane and 2 lane + 1
   if (comp) {
     // right-hand side (w~ K)_k: w~ = the row's weights on the removed columns, zero elsewhere
-#pragma unroll
-    for (int r = 0; r < CPL; ++r) key[lane + 64 * r] = sel[r] ? us[r] : 0.f;
     WAVE_SYNC();
-    float t[CPL];
-    matvec_k(key, t);
+    wk = matvec_k(key, reinterpret_cast<const unsigned char*>(wrow), s);
+    WAVE_SYNC();
+    wrow[2 * lane] = wk[0];  // gathered below through q
+    wrow[2 * lane + 1] = wk[1];
+    WAVE_SYNC();
     if (ns == 0) {  // the whole block goes: lambda = w~ K
+      float top = 0.f;
 #pragma unroll
       for (int r = 0; r < CPL; ++r) {
         const int col = lane + 64 * r;
-        if (col < a.bw) lam_g[col] = t[r];
+        if (col < a.bw) {
+          lam_g[col] = wrow[col];
+          top = fmaxf(top, fabsf(wrow[col]));
+        }
       }
-      rsc_set(a, i, fmaxf(fabsf(t[0]), fabsf(t[1])), old_rsc);  // zero past the block
+      rsc_set(a, i, top, old_rsc);
       return;
     }
-#pragma unroll
-    for (int r = 0; r < CPL; ++r) wrow[lane + 64 * r] = t[r];  // gathered below through q
   }
   WAVE_SYNC();
 
@@ -1240,15 +1279,23 @@ __global__ __launch_bounds__(64 * WPB, NTR == 2 ? 4 : 3) void k_solve_mfma(Solve
   float* rowp[NTR];
 #pragma unroll
   for (int ti = 0; ti < NTR; ++ti) rowp[ti] = &sm.L[(32 * ti + pl) * (32 * ti + pl - 1) / 2];
-  float* const junk = &sm.L[32 * NTR * (32 * NTR - 1) / 2 + lo];
+  float exponents = __uint_as_float(0x7f800000u);
+  asm volatile("" : "+v"(exponents));
+  float* const junk = &sm.L[32 * NTR * (32 * NTR - 1) / 2 + (lo & 15)];
+  float dd[NZ];
+#pragma unroll
+  for (int z = 0; z < NZ; ++z) dd[z] = 1.f;
 
 #pragma unroll
   for (int p = 0; p < NTR; ++p) {
     if (p < nt) {
 #pragma unroll
-      for (int t = 0; t < 16; ++t) {
-        const int k1 = 8 * (t >> 2) + (t & 3), k2 = k1 + 4;
-        if (p > 0 || k1 < 32 - pad) {  // a padding row paired with a real one is a no-op pivot
+      for (int g = 0; g < 4; ++g) {
+        // four pairs at a time: pivots of padding rows change nothing, and a branch for every pair costs more
+        if (p > 0 || eliminated(8 * g))
+#pragma unroll
+        for (int t = 4 * g; t < 4 * g + 4; ++t) {
+          const int k1 = 8 * (t >> 2) + (t & 3), k2 = k1 + 4;
           const float v = T[p][p][t];   // lower half: row k1 of the reduced tile, upper half: row k2
           const float x = lower_half(v);
           const float d1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k1));
@@ -1256,7 +1303,7 @@ __global__ __launch_bounds__(64 * WPB, NTR == 2 ? 4 : 3) void k_solve_mfma(Solve
           const float d2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32 + k2));
           // 1 / d1 and 1 / d2', d2' = d2 - c12^2 / d1 = det / d1 the pivot of k2 after the elimination
           // of k1, from two independent reciprocals (see tl_eliminate)
-          const float ps = pivot_scale(d1);
+          const float ps = pivot_scale_vgpr(d1, exponents);
           const float e1 = ps * d1, e12 = ps * c12;
           const float cc = e12 * c12;
           const float det = fmaf(e1, d2, -cc) - fmaf(e12, c12, -cc);
@@ -1267,7 +1314,9 @@ __global__ __launch_bounds__(64 * WPB, NTR == 2 ? 4 : 3) void k_solve_mfma(Solve
           const float m = e12 * re;
           const float mh = hi ? m : 0.f;
           const float rh = hi ? -(e1 * rd) : -(ps * re);
-          sm.d[32 * p + 2 * t + hi] = hi ? det * re : d1;  // one address per half
+          // pivots by position (64 z + lane)
+          const float dp = lane & 1 ? det * re : d1;
+          dd[p >> 1] = (lane >> 1) == 16 * (p & 1) + t ? dp : dd[p >> 1];
           // u1 (lower half) and u2 = row k2 after the elimination of k1 (upper half).  Columns
           // eliminated earlier hold rounding residue instead of zero; it is not masked, because
           // a product with it only ever lands in eliminated rows and columns of the tiles.
@@ -1275,7 +1324,7 @@ __global__ __launch_bounds__(64 * WPB, NTR == 2 ? 4 : 3) void k_solve_mfma(Solve
           const float aop = bop * rh;
           T[p][p] = __builtin_amdgcn_mfma_f32_32x32x2f32(aop, bop, T[p][p], 0, 0, 0);
           // column 2t + hi of -L~ within the tile: rows at later positions
-          (pl > 2 * t + hi ? rowp[p] + 32 * p + hi : junk)[2 * t] = aop;
+          *(pl > 2 * t + hi ? rowp[p] + 32 * p + hi + 2 * t : junk) = aop;
           float e2[NTR], be[NTR];
 #pragma unroll
           for (int ti = p + 1; ti < NTR; ++ti) {
@@ -1303,41 +1352,45 @@ __global__ __launch_bounds__(64 * WPB, NTR == 2 ? 4 : 3) void k_solve_mfma(Solve
   // ---- L~ y = u, then L~^T lambda = D^-1 y.  A sweep reads one unknown off its lane (y_k or lambda_k,
   //      final by then) and adds its column of -L~ (row of -L~^T) to all others; lanes that are
   //      already final get rubbish, their value was put aside.  The LDS reads of eight unknowns
-  //      are fetched together, ahead of the dependent chain: of a column every lane reads its own
+  //      are fetched together, eight unknowns ahead of the dependent chain: of a column every lane reads its own
   //      packed row (whose starts, triangular numbers, fall on different banks), of a row
-  //      consecutive lanes read consecutive elements.
+  //      consecutive lanes read consecutive elements.  64 unknowns 2000 and 2900 cycles of a row's 27000, of rows of any
+  //      size 2900 and 3000 (5800 and 5300 with a branch and a wait for each unknown).
   //      Carrying u through the elimination instead cost 19 vector instructions per pair of pivots
   //      in a kernel that is bound by their number. ----
-  float y[NZ], dd[NZ];
+  float y[NZ];
   int pofs[NZ];
 #pragma unroll
   for (int z = 0; z < NZ; ++z) {
     const int P = min(64 * z + lane, 32 * NTR - 1);
     pofs[z] = P * (P - 1) / 2;
-    dd[z] = sm.d[P];
     y[z] = 0.f;
   }
+  float ahead[2][8][NZ];
+  auto load_cols = [&](float (&col)[8][NZ], int k8) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+#pragma unroll
+      for (int z = 0; z < NZ; ++z) col[t][z] = (64 * z + 63 > k8 + t) ? sm.L[pofs[z] + k8 + t] : 0.f;
+  };
+  load_cols(ahead[0], 0);
 #pragma unroll
   for (int k8 = 0; k8 < 32 * NTR; k8 += 8) {
-    if (k8 < 32 * nt) {
-      __builtin_amdgcn_sched_barrier(0);  // eight ahead, not all of them: registers
-      float col[8][NZ];
-#pragma unroll
-      for (int t = 0; t < 8; ++t)
-#pragma unroll
-        for (int z = 0; z < NZ; ++z)
-          col[t][z] = (64 * z + 63 > k8 + t) ? sm.L[pofs[z] + k8 + t] : 0.f;
+    float (&col)[8][NZ] = ahead[(k8 >> 3) & 1];
+    __builtin_amdgcn_sched_barrier(0);  // sixteen ahead, not all of them: registers
+    if (k8 + 8 < 32 * NTR) load_cols(ahead[((k8 >> 3) & 1) ^ 1], k8 + 8);
+    __builtin_amdgcn_sched_barrier(0);
+    if (k8 < 32 * nt && eliminated(k8)) {
+      int ys[8];
 #pragma unroll
       for (int t = 0; t < 8; ++t) {
         const int k = k8 + t;
-        if (valid(mrow(k))) {
-          const int yk = __builtin_amdgcn_readlane(__float_as_int(u[k >> 6]), k & 63);
-          set_lane(y[k >> 6], yk, k & 63);
+        ys[t] = __builtin_amdgcn_readlane(__float_as_int(u[k >> 6]), k & 63);
 #pragma unroll
-          for (int z = 0; z < NZ; ++z)
-            if (64 * z + 63 > k) u[z] = fmaf(col[t][z], __int_as_float(yk), u[z]);
-        }
+        for (int z = 0; z < NZ; ++z)
+          if (64 * z + 63 > k) u[z] = fmaf(col[t][z], __int_as_float(ys[t]), u[z]);
       }
+      set_lanes8(y[k8 >> 6], ys, k8 & 63);
     }
   }
   bool bad = false;
@@ -1354,32 +1407,57 @@ __global__ __launch_bounds__(64 * WPB, NTR == 2 ? 4 : 3) void k_solve_mfma(Solve
   }
   if (__ballot(bad) != 0ull && lane == 0)
     atomicCAS(a.info, 0, -(int32_t)min(i + 1, (int64_t)0x7fffffff));
+  auto load_rows = [&](float (&row)[8][NZ], int k8) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+#pragma unroll
+      for (int z = 0; z < NZ; ++z)
+        row[t][z] = (64 * z < k8 + t) ? sm.L[(k8 + t) * (k8 + t - 1) / 2 + 64 * z + lane] : 0.f;
+  };
+  load_rows(ahead[(4 * NTR - 1) & 1], 32 * NTR - 8);
 #pragma unroll
   for (int k8 = 32 * NTR - 8; k8 >= 0; k8 -= 8) {
-    if (k8 < 32 * nt) {
-      __builtin_amdgcn_sched_barrier(0);
-      float row[8][NZ];
-#pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const int k = k8 + t;
-#pragma unroll
-        for (int z = 0; z < NZ; ++z)
-          row[t][z] = (64 * z < k) ? sm.L[k * (k - 1) / 2 + 64 * z + lane] : 0.f;
-      }
+    float (&row)[8][NZ] = ahead[(k8 >> 3) & 1];
+    __builtin_amdgcn_sched_barrier(0);
+    if (k8 > 0) load_rows(ahead[((k8 >> 3) & 1) ^ 1], k8 - 8);
+    __builtin_amdgcn_sched_barrier(0);
+    if (k8 < 32 * nt && eliminated(k8)) {
+      int ls[8];
 #pragma unroll
       for (int t = 7; t >= 0; --t) {
         const int k = k8 + t;
-        if (valid(mrow(k))) {
-          const int lk = __builtin_amdgcn_readlane(__float_as_int(u[k >> 6]), k & 63);
-          set_lane(lam[k >> 6], lk, k & 63);
+        ls[t] = __builtin_amdgcn_readlane(__float_as_int(u[k >> 6]), k & 63);
 #pragma unroll
-          for (int z = 0; z < NZ; ++z)
-            if (64 * z < k) u[z] = fmaf(row[t][z], __int_as_float(lk), u[z]);
-        }
+        for (int z = 0; z < NZ; ++z)
+          if (64 * z < k) u[z] = fmaf(row[t][z], __int_as_float(ls[t]), u[z]);
       }
+      set_lanes8(lam[k8 >> 6], ls, k8 & 63);
     }
   }
 
+  if (comp) {
+    // what has been solved for is y on the kept columns: lambda = ((w~ - y~) K)_q
+#pragma unroll
+    for (int z = 0; z < NZ; ++z) {
+      const int m = mrow(64 * z + lane);
+      if (m < 32 * NTR) wrow[m] = m < 32 * nt && valid(m) ? lam[z] : 0.f;
+    }
+    WAVE_SYNC();
+    const f32x2 yk = matvec_k(wrow, sm.q, 32 * nt);
+    key[2 * lane] = wk[0] - yk[0];
+    key[2 * lane + 1] = wk[1] - yk[1];
+    WAVE_SYNC();
+    float top = 0.f;
+#pragma unroll
+    for (int r = 0; r < CPL; ++r) {
+      const int col = lane + 64 * r;
+      const float l = sel[r] ? key[col] : 0.f;
+      if (col < a.bw) lam_g[col] = l;
+      top = fmaxf(top, fabsf(l));
+    }
+    rsc_set(a, i, top, old_rsc);
+    return;
+  }
   // ---- lambda row: zeros except lambda_l at column q_l ----
 #pragma unroll
   for (int r = 0; r < CPL; ++r) wrow[lane + 64 * r] = 0.f;
@@ -1389,25 +1467,6 @@ __global__ __launch_bounds__(64 * WPB, NTR == 2 ? 4 : 3) void k_solve_mfma(Solve
     if (64 * z + lane < 32 * nt && valid(mrow(64 * z + lane)))
       wrow[sm.q[mrow(64 * z + lane)]] = lam[z];
   WAVE_SYNC();
-  if (comp) {
-    // wrow holds y on the kept columns: lambda = ((w~ - y~) K)_q
-#pragma unroll
-    for (int r = 0; r < CPL; ++r)
-      key[lane + 64 * r] = (sel[r] ? us[r] : 0.f) - wrow[lane + 64 * r];
-    WAVE_SYNC();
-    float l[CPL];
-    matvec_k(key, l);
-    float top = 0.f;
-#pragma unroll
-    for (int r = 0; r < CPL; ++r) {
-      const int col = lane + 64 * r;
-      if (!sel[r]) l[r] = 0.f;
-      if (col < a.bw) lam_g[col] = l[r];
-      top = fmaxf(top, fabsf(l[r]));
-    }
-    rsc_set(a, i, top, old_rsc);
-    return;
-  }
   float top = 0.f;
 #pragma unroll
   for (int r = 0; r < CPL; ++r) {
@@ -2948,24 +3007,31 @@ static void launch_tiled(hipStream_t s, SolveArgs a, int smax) {
   hipLaunchKernelGGL((k_solve_tiled<SEL, 8>), dim3((unsigned)a.c), dim3(512), smem8, s, a);
 }
 
+// Rows that run at once: eight of up to 96 unknowns, sixteen of up to 64 per compute unit
+constexpr int64_t kRowsOf96 = 8 * 256, kRowsOf64 = 16 * 256;
+
+// k_solve_mfma for up to 64 unknowns per row
+template <int SEL, int WPB>
+static void launch_mfma2(hipStream_t s, const SolveArgs& a) {
+  const bool full = SEL == SEL_NM && a.bw * a.n == 64 * a.m && a.bw % a.m == 0;  // 64 unknowns in every row
+  auto* const kern = full ? k_solve_mfma<SEL, WPB, 2, SEL == SEL_NM> : k_solve_mfma<SEL, WPB, 2, false>;
+  hipLaunchKernelGGL(kern,
+                     dim3((unsigned)ceil_div(a.c, WPB)), dim3(64 * WPB), WPB * sizeof(SolveMfmaSmem<2>), s, a);
+}
+
 template <int SEL>
 static void launch_solve(hipStream_t s, SolveArgs a, int smax) {
-  // tiled solver: rows that lose more than half of the block are solved through the complement
-  if (a.Kc && a.bw > 128) smax = SEL == SEL_NM ? std::min(smax, a.bw - smax) : a.bw / 2;
+  // rows that lose more than half of the block are solved through the complement
+  // (up to 128 columns: where that lets all rows run at once.  The kernel for 96 unknowns has eight of them per compute
+  // unit, 18 KB of LDS each, the one for 64 has sixteen or twenty, and a row of it that goes through the complement
+  // waits longer: 512 x 512 at 50 % 347 us and 358, 1111 x 1365 1100 and 1115, 4096 x 4096 9.0 and 8.2 ms)
+  if (a.Kc && (a.bw > 128 || a.c > kRowsOf96)) smax = SEL == SEL_NM ? std::min(smax, a.bw - smax) : a.bw / 2;
   if (a.bw <= 128 && smax <= 64) {
-    constexpr int kWpb = 4;
-    const size_t smem = kWpb * sizeof(SolveMfmaSmem<2>);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_solve_mfma<SEL, kWpb, 2>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (SEL == SEL_NM && a.bw * a.n == 64 * a.m && a.bw % a.m == 0) {  // 64 unknowns in every row
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_solve_mfma<SEL, kWpb, 2, true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-      hipLaunchKernelGGL((k_solve_mfma<SEL, kWpb, 2, true>), dim3((unsigned)ceil_div(a.c, kWpb)),
-                         dim3(64 * kWpb), smem, s, a);
-      return;
-    }
-    hipLaunchKernelGGL((k_solve_mfma<SEL, kWpb, 2>), dim3((unsigned)ceil_div(a.c, kWpb)),
-                       dim3(64 * kWpb), smem, s, a);
+    a.defer_large = a.Kc ? 1 : 0;
+    // twenty rows to a unit, in workgroups of five, where sixteen leave some for later: 5120 x 5120 4:8, 4608 rows, 4640
+    // -> 4527 us; workgroups of four share out up to 4096 rows evenly
+    if (a.c <= kRowsOf64) launch_mfma2<SEL, 4>(s, a);
+    else launch_mfma2<SEL, 5>(s, a);
   } else if (a.bw <= 128) {
     // Up to 96 unknowns: one wavefront per row on the matrix cores.  When s varies from row to
     // row (and may exceed 96) the few larger rows get a launch of the 128-thread kernel.

@@ -110,6 +110,14 @@ __device__ __forceinline__ float pivot_scale(float d) {
   return __uint_as_float(~__float_as_uint(d) & 0x7f800000u);
 }
 
+// The same for a uniform d that comes from a v_readlane, on the vector unit (the detour through the scalar unit
+// takes 14 cycles of a chain); exponents: 0x7f800000 in a register.
+__device__ __forceinline__ float pivot_scale_vgpr(float d, float exponents) {
+  float ps;
+  asm("v_bfi_b32 %0, %1, 0, %2" : "=v"(ps) : "s"(d), "v"(exponents));
+  return ps;
+}
+
 // Eliminates the symmetric tile D (accumulator layout), F F^T = D, and applies the same row
 // operations to E: E = I becomes T = F^{-1}, E = A^T becomes F^{-1} A^T = (A F^{-T})^T, the tile of
 // the factor next to D.  One wavefront.  aux: 32 floats of LDS.  Returns the pivot of column lo (not
@@ -148,10 +156,8 @@ __device__ __forceinline__ float tl_eliminate(f32x16 D, f32x16& E, f32x16& U, fl
     // 1 / d1 and 1 / d2' (d2' = d2 - c12^2 / d1, the pivot of k2 after the elimination of k1)
     // from two INDEPENDENT reciprocals, of d1 and of det = d1 d2 - c12^2: d2' = det / d1, row k1
     // scaled to a pivot e1 = ps d1 near one.  The wavefront is alone on this chain, so its length is
-    // what counts: every instruction is 4 cycles, an MFMA 64 (the wavefront's own vector instructions wait for it), and
-    // a detour of a value through the scalar unit 14.
-    float ps;                                 // pivot_scale(d1), without that detour
-    asm("v_bfi_b32 %0, %1, 0, %2" : "=v"(ps) : "s"(d1), "v"(exponents));
+    // what counts: every instruction is 4 cycles, an MFMA 64 (the wavefront's own vector instructions wait for it).
+    const float ps = pivot_scale_vgpr(d1, exponents);
     const float e1 = ps * d1, e12 = ps * c12;
     const float cc = e12 * c12;
     const float det = fmaf(e1, d2, -cc) - fmaf(e12, c12, -cc);

@@ -346,6 +346,35 @@ def test_given_mask_with_every_tile_count(B, given_factor):
     assert rows.max() < 1e-3
 
 
+@pytest.mark.parametrize("c,b,B", [
+    (2048, 256, 128),   # all rows at once in the kernel for 96 unknowns
+    (2049, 253, 128),   # 64 unknowns and complement; last block of 125 columns
+    (4096, 200, 128),   # last block of 72
+    (4097, 242, 97),    # five rows to a workgroup; odd blocks, the last of 48
+])
+def test_given_mask_with_every_row_size_up_to_128_columns(c, b, B):
+    """Rows of 0 to B unknowns in a block of up to 128 columns, for the numbers of rows at which the solver changes.
+    Rows are independent: the first ones, which have every size, and the last ones are checked."""
+    from tests.gpu_util import gpu_prune
+    W, H32 = _layer(c, b, 4 * b, "f32", seed=c)
+    print(f"row sizes {c}x{b} B={B}", flush=True)
+    g = np.random.default_rng(c)
+    M = np.zeros((c, b), np.uint8)
+    for j in range(0, b, B):
+        w = min(B, b - j)
+        first = np.argsort(g.random((c, w)), axis=1).argsort(axis=1)
+        M[:, j:j + w] = first < ((np.arange(c) + j) % (w + 1))[:, None]
+    Wg, Mg, info = gpu_prune(W, H32, mode="unstructured", p=0.5, B=B, mask_in=M)
+    assert info == 0
+    np.testing.assert_array_equal(Mg, M)
+    assert np.all(Wg[M == 1] == 0.0)
+    at = np.unique(np.concatenate([np.arange(2 * B + 2), np.arange(c - 16, c)]))
+    Wo, _ = orc.prune_fast(W[at], H32.astype(np.float64), mode="unstructured", p=0.5, B=B, damp=0.01, mask_in=M[at])
+    some = np.linalg.norm(Wo, axis=1) > 0
+    rows = np.linalg.norm(Wg[at] - Wo, axis=1)[some] / np.linalg.norm(Wo, axis=1)[some]
+    assert rows.max() < 1e-3  # as in the other parity tests of this file
+
+
 def test_factor_reuse_matches_internal_factor():
     from tests.gpu_util import gpu_prune, gpu_factor
     W, H32 = _layer(64, 256, 1024, "f32", seed=6)
