@@ -108,13 +108,16 @@ __device__ __forceinline__ void raise_bound(float* bound, float m) {
 // the whole upper triangle).  R rows of threads: with few columns, where the launch waits for its own loads, 16 rows of
 // them have four loads and stores each instead of sixteen: 128 columns
 // 35.0 and 33.5 us for the factorisation, 512 179.3 and 177.8, 1024 389.7 and 389; 2048 equal.
+// tile (r, kt) of a block that waits right of the diagonal (p: the block): a piece is two rows of 512 bytes; at = hi * ld
+// + 4 * lo
+__device__ __forceinline__ int64_t st_parked(int r, int kt, int e, int64_t ld) { return (8 * (4 * r + kt) + 2 * e) * ld; }
 constexpr int kRpT = 64;
 constexpr int64_t kRpFew = 1024;
 template <int R>
 __global__ __launch_bounds__(64 * R) void k_reverse_pad(const float* __restrict__ H, int64_t b,
                                                         const float* __restrict__ lam_p,
                                                         const float* __restrict__ d, float* __restrict__ Ap,
-                                                        int64_t bp) {
+                                                        int64_t bp, int parked) {
   __shared__ float t[kRpT][kRpT + 1];
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;  // 64 x R
   const int64_t i0 = (int64_t)blockIdx.y * kRpT, j0 = (int64_t)blockIdx.x * kRpT;
@@ -137,6 +140,33 @@ __global__ __launch_bounds__(64 * R) void k_reverse_pad(const float* __restrict_
   for (int e = 0; e < kRpT / R; ++e) {
     const int64_t sr = b - 1 - (j0 + ty + R * e);
     t[ty + R * e][tx] = (sc >= 0 && sr >= sc) ? v[e] : 0.f;  // t[cidx][r]; only the lower triangle is valid
+  }
+  if (parked && j0 < NB && i0 >= NB) {  // below the first diagonal block
+    __syncthreads();
+    __shared__ float ds[2 * kRpT];  // scales of the tile's rows, then of its columns; zero on the padding
+    if (ty < 2) {
+      const int64_t at = b - 1 - ((ty == 0 ? i0 : j0) + tx);
+      ds[kRpT * ty + tx] = at >= 0 ? d[at] : 0.f;
+    }
+    __syncthreads();
+    float* const block = Ap + (i0 / NB) * NB;
+    const float sa = h2_scale(kBoundA);
+    for (int v = threadIdx.x; v < kRpT * kRpT / 8; v += 64 * R) {  // pieces of 16 bytes: eight values of a row
+      const int lo = v & 31, hi = (v >> 5) & 1, m = (v >> 6) & 1, kt = (v >> 7) & 1, rt = v >> 8;
+      const int r = 32 * rt + lo;
+      f32x4 x[2];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int k = 32 * kt + tl_row(8 * m + e, hi);
+        x[e >> 2][e & 3] = t[k][r] * (ds[r] * ds[kRpT + k]);
+      }
+      f16x8 h, l;
+      split8_h2(x[0], x[1], sa, h, l);
+      float* const at = block + st_parked((int)(i0 % NB) / 32 + rt, (int)j0 / 32 + kt, 2 * m, bp) + (hi * bp + 4 * lo);
+      *reinterpret_cast<f16x8*>(at) = h;
+      *reinterpret_cast<f16x8*>(at + 2 * bp) = l;
+    }
+    return;
   }
   __syncthreads();
 #pragma unroll
@@ -479,7 +509,9 @@ __global__ __launch_bounds__(512, 4) void k_chol_diag(float* __restrict__ Ap, fl
 // What a launch reads of A_ik no workgroup of it may overwrite, so tiles of the column that comes next (j = k + 1) do not
 // go to their place in A', which takes L_ij in the next launch, but to block (j, i), right of the diagonal, where
 // nothing else lives; and in the form that their only reader wants: split into fp16 pairs in the layout of the
-// operands (512 consecutive bytes per half wavefront and load).  STORED: the first launch, whose panel is in A'.
+// operands (512 consecutive bytes per half wavefront and load).  STORED: the first launch behind two-level updates, whose
+// panel is in A'; of a factorisation that begins with steps, k_reverse_pad leaves the first column like that (the launch of its
+// panel, 7 to 9 us, is gone).
 //
 // Products as in k_gemm_direct: two-way split, all four partial products, two partial sums.
 struct StepArgs {
@@ -528,9 +560,6 @@ __device__ __forceinline__ SplitTile st_get(const float* t, int lane) {
   for (int e = 0; e < 4; ++e) v.p[e] = *reinterpret_cast<const u32x4*>(t + 256 * e + 4 * lane);
   return v;
 }
-// tile (r, kt) of a block that waits right of the diagonal (p: the block): a piece is two rows of 512 bytes; at = hi * ld
-// + 4 * lo
-__device__ __forceinline__ int64_t st_parked(int r, int kt, int e, int64_t ld) { return (8 * (4 * r + kt) + 2 * e) * ld; }
 __device__ __forceinline__ SplitTile st_fetch(const float* p, int r, int kt, int64_t ld, uint32_t at) {
   SplitTile v;
 #pragma unroll
@@ -1018,8 +1047,9 @@ thanos_status factor_begin(hipStream_t s, const float* H, int64_t b, float dampi
                      lam, d, d + 2 * bp + n_bounds(nb), d + bp, n_bounds(nb) + (int)bp, info);
   THANOS_LAUNCH_CHECK();
   const dim3 tiles((unsigned)(bp / kRpT), (unsigned)(bp / kRpT));
-  if (b <= kRpFew) hipLaunchKernelGGL(k_reverse_pad<16>, tiles, dim3(1024), 0, s, H, b, lam, d, Ap, bp);
-  else hipLaunchKernelGGL(k_reverse_pad<4>, tiles, dim3(256), 0, s, H, b, lam, d, Ap, bp);
+  const int parked = nb <= kStepAll ? 1 : 0;
+  if (b <= kRpFew) hipLaunchKernelGGL(k_reverse_pad<16>, tiles, dim3(1024), 0, s, H, b, lam, d, Ap, bp, parked);
+  else hipLaunchKernelGGL(k_reverse_pad<4>, tiles, dim3(256), 0, s, H, b, lam, d, Ap, bp, parked);
   THANOS_LAUNCH_CHECK();
   return THANOS_OK;
 }
@@ -1149,12 +1179,29 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
   };
   int pending_join = -1;  // event index recorded on the aux stream after the last "rest"
   // the last block rows: one launch per step, every tile updated in every step
-  const int first_step = nb <= kStepAll ? 0 : (nb - kStepLast + kOuter - 1) / kOuter * kOuter;
+  const int first_step = (nb - kStepLast + kOuter - 1) / kOuter * kOuter;
+  auto steps = [&](int k, bool stored) -> thanos_status {
+    if (pending_join >= 0) THANOS_CHECK(aux.join(pending_join));
+    pending_join = -1;
+    for (int t = k; t + 1 < nb; ++t) {
+      const StepArgs a{Ap, Linv, bp, b, t, nb, bound_inv, info};
+      const int rows = nb - 1 - t;
+      hipLaunchKernelGGL(t == k && stored ? k_chol_step<true> : k_chol_step<false>,
+                         dim3((unsigned)(rows * (rows + 1) / 2)), dim3(512), kStepSmem, s, a);
+      THANOS_LAUNCH_CHECK();
+      if ((t + 1) % kOuter == 0 && t + 2 < nb) THANOS_CHECK(trinv_upto(t));
+    }
+    return trinv_upto(nb - 1);
+  };
   for (int k = 0; k < nb; ++k) {
     hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(512), kCholDiagSmem, s, Ap, Linv, bp, k, b, bound_inv + k,
                        info);
     THANOS_LAUNCH_CHECK();
     const int64_t rem = bp - (int64_t)(k + 1) * NB;
+    if (nb <= kStepAll) {  // the first panel waits where a step looks for it (k_reverse_pad)
+      THANOS_CHECK(steps(0, false));
+      break;
+    }
     if (rem <= 0) {
       thanos_status st = trinv_upto(k);
       if (st != THANOS_OK) return st;
@@ -1167,17 +1214,7 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
                                     0.f, panel, bp, false, company);
     if (st != THANOS_OK) return st;
     if (k == first_step) {
-      if (pending_join >= 0) THANOS_CHECK(aux.join(pending_join));
-      pending_join = -1;
-      for (int t = k; t + 1 < nb; ++t) {
-        const StepArgs a{Ap, Linv, bp, b, t, nb, bound_inv, info};
-        const int rows = nb - 1 - t;
-        hipLaunchKernelGGL(t == k ? k_chol_step<true> : k_chol_step<false>, dim3((unsigned)(rows * (rows + 1) / 2)),
-                           dim3(512), kStepSmem, s, a);
-        THANOS_LAUNCH_CHECK();
-        if ((t + 1) % kOuter == 0 && t + 2 < nb) THANOS_CHECK(trinv_upto(t));
-      }
-      THANOS_CHECK(trinv_upto(nb - 1));
+      THANOS_CHECK(steps(k, true));
       break;
     }
     if ((k + 1) % kOuter == 0) {
