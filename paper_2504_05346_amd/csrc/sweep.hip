@@ -1544,10 +1544,13 @@ __device__ __forceinline__ bool tl_pivots(const f32x16& D, float* Dt, float* aux
 // Tiles (row << 4 | column) below the diagonal owned by each wavefront, one per byte, 0xff = none;
 // wavefront w also owns the diagonal tile w.  A wavefront never owns a tile whose column is at
 // or right of its diagonal tile (wavefront 0 apart, whose elimination comes first): when it runs
-// ahead on its diagonal tile it has no other trailing tile to update.  Within that, the tiles are
-// dealt so that the four SIMDs have about the same number of products in every step.
-__device__ const uint32_t kRsOwn8[8] = {0x76536241u, 0xffffff50u, 0xff312170u, 0x42715160u,
-                                        0x73326120u, 0x54637240u, 0x65744310u, 0x75645230u};
+// ahead on its diagonal tile it has no other trailing tile to update.  Of eight, the first of a wavefront's
+// tiles is the one left of its diagonal tile: what that tile adds to the diagonal one goes from registers to registers, in
+// front of the barrier that the others wait for (4096 rows of 256 unknowns 430 -> 420 us; of four, with five rows per
+// compute unit, 8192 rows of about 102 222 -> 229: the others wait for that wavefront).  Within that, the tiles are dealt so that the four SIMDs have about the same number
+// of products in every step.
+__device__ const uint32_t kRsOwn8[8] = {0x75746031u, 0xffffff10u, 0xff705021u, 0x41402032u,
+                                        0x62513043u, 0x63614254u, 0x72645365u, 0x73715276u};
 __device__ const uint32_t kRsOwn4[4] = {0xffff3221u, 0xffffff20u, 0xffffff30u, 0xffff3110u};
 
 template <int NW>
@@ -1572,7 +1575,7 @@ __device__ __forceinline__ float rs_dot(const f32x16& t, const float* v, int hi)
 }
 
 // Solves lambda R_hat = u for one row: nt tile rows, ns unknowns, R_hat[a][c] = G[q[a] * ldg + q[c]].
-// u (32 nt values, zero past ns) is overwritten, lam[0 : 32 nt] times the returned scale is the result.
+// u and q (32 nt values, zero past ns): u is overwritten, lam[0 : 32 nt] times the returned scale is the result.
 // The matrix is scaled by a power of two that brings its largest diagonal element to [2^28, 2^29): no
 // element of the factor then exceeds 2^14.5, and the trailing products, which are most of the work, take
 // two fp16 values per operand (tile32.h).  tiles: NW * kRsTile
@@ -1582,6 +1585,7 @@ template <int NW>
 __device__ __forceinline__ float rs_solve(const float* __restrict__ G, unsigned int ldg, const int* q, int ns,
                                           int nt, float* tiles, float* u, float* lam, float* aux, bool& bad) {
   constexpr int SL = NW == 8 ? 4 : 2;  // tiles below the diagonal per wavefront
+  constexpr bool kOwnLeft = NW == 8;   // the first of them is the one left of the diagonal tile
   const int lane = threadIdx.x & 63, lo = lane & 31, hi = lane >> 5;
   // the wavefronts' parts rotate with the row, so that the eliminations of the rows that run on a
   // compute unit at the same time do not meet on one SIMD
@@ -1595,13 +1599,16 @@ __device__ __forceinline__ float rs_solve(const float* __restrict__ G, unsigned 
   }
   float* Tt = tiles + (NW - 1) * kRsTile;
 
-  // ---- gather (all loads unconditional from clamped indices, masked afterwards) ----
+  // ---- gather (all loads unconditional, of column 0 past ns, masked afterwards) ----
   f32x16 off[SL], dg;
   auto fetch = [&](f32x16& v, int i, int j) {  // v[r] = G[q[32 j + row]][q[32 i + lo]]
-    const unsigned int qc = (unsigned int)q[min(32 * i + lo, ns - 1)];
+    const unsigned int qc = (unsigned int)q[32 * i + lo];
 #pragma unroll
-    for (int r = 0; r < 16; ++r)  // 512 columns of at most 65535: the offset fits 32 bits
-      v[r] = G[(unsigned int)q[min(32 * j + tl_row(r, hi), ns - 1)] * ldg + qc];
+    for (int g = 0; g < 4; ++g) {  // 512 columns of at most 65535: the offset fits 32 bits, its factors 24
+      const u32x4 rows = *reinterpret_cast<const u32x4*>(q + 32 * j + 8 * g + 4 * hi);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[4 * g + e] = G[__umul24(rows[e], ldg) + qc];
+    }
   };
   if (w < nt) fetch(dg, w, w);
 #pragma unroll
@@ -1661,9 +1668,16 @@ __device__ __forceinline__ float rs_solve(const float* __restrict__ G, unsigned 
         for (int r = 0; r < 16; ++r) C[r] = 0.f;
         rs_mma<false>(C, Tt, off[s], l, h);
         off[s] = C;
-        rs_store_h2(tiles + (ti[s] - 1) * kRsTile, C, l + 32 * h);
+        const RsSplit x = rs_split_h2(C);
+        rs_store_h2(tiles + (ti[s] - 1) * kRsTile, x, l + 32 * h);
+        if (kOwnLeft && s == 0 && w == p + 1) rs_mma_h2(dg, x);  // the next diagonal tile
       }
-    if (w == p) {  // y_p = T u_p
+    if (w == p) {  // u_p -= L_p,p-1 y_p-1, left over from the step before; y_p = T u_p
+      if (kOwnLeft && p > 0) {
+        const float d = rs_dot(off[0], u + 32 * (p - 1), h);
+        if (lane < 32) u[32 * p + lane] += d;
+        WAVE_SYNC();
+      }
       float y = 0.f;
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
@@ -1677,13 +1691,13 @@ __device__ __forceinline__ float rs_solve(const float* __restrict__ G, unsigned 
     }
     __syncthreads();  // panel and y_p are there
     if (p + 1 == nt) break;
-    if (w > p && w < nt)
+    if (w > (kOwnLeft ? p + 1 : p) && w < nt)
       rs_mma_h2(dg, tiles + (w - 1) * kRsTile, tiles + (w - 1) * kRsTile, l + 32 * h);
 #pragma unroll
     for (int s = 0; s < SL; ++s) {
       if (ti[s] < nt && tj[s] > p)
         rs_mma_h2(off[s], tiles + (tj[s] - 1) * kRsTile, tiles + (ti[s] - 1) * kRsTile, l + 32 * h);
-      if (ti[s] < nt && tj[s] == p) {  // u_i -= L_ip y_p (one tile per i in a step)
+      if (ti[s] < nt && tj[s] == p && !(kOwnLeft && s == 0 && w == p + 1)) {  // u_i -= L_ip y_p (one tile per i in a step)
         const float d = rs_dot(off[s], u + 32 * p, h);
         if (lane < 32) u[32 * ti[s] + lane] += d;
       }
@@ -1973,6 +1987,7 @@ __global__ __launch_bounds__(64 * NW, (BIG ? 2 : (NW == 8 ? 4 : 5))) void k_solv
   // partial sums of the complement's matrix-vector products: in the tile area (NW * 1056 floats,
   // of which they take NW * 512)
   float* part = BIG ? nullptr : tiles;
+  for (int t = ns + tid; t < 32 * nt; t += NT) q[t] = 0;
   if (!comp) {
     for (int t = tid; t < 32 * nt; t += NT) u[t] = (t < s) ? wrow[q[t]] : 0.f;
   } else if (SEL == SEL_PICKED) {

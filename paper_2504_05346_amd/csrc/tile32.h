@@ -74,7 +74,11 @@ __device__ __forceinline__ void rs_mma(f32x16& acc, const float* a, const f32x16
 // 32 k-values of two tiles instead of sixteen of 64.  An operand-layout tile's registers 8 m .. 8 m + 7 are
 // the k-values of MFMA m, the same ones in both operands.  In LDS a split tile is four 16-byte pieces per
 // lane (x1, x2 of m = 0, then of m = 1), in the lanes' order: kRsTile floats hold it.
-__device__ __forceinline__ void rs_store_h2(float* tile, const f32x16& v, int lane) {
+struct RsSplit {
+  f16x8 x1[2], x2[2];
+};
+__device__ __forceinline__ RsSplit rs_split_h2(const f32x16& v) {
+  RsSplit s;
 #pragma unroll
   for (int m = 0; m < 2; ++m) {
     u32x4 h, l;
@@ -86,8 +90,25 @@ __device__ __forceinline__ void rs_store_h2(float* tile, const f32x16& v, int la
       h[e] = __builtin_bit_cast(uint32_t, x1);
       l[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, f16x2));
     }
-    *reinterpret_cast<u32x4*>(tile + 256 * (2 * m) + 4 * lane) = h;
-    *reinterpret_cast<u32x4*>(tile + 256 * (2 * m + 1) + 4 * lane) = l;
+    s.x1[m] = __builtin_bit_cast(f16x8, h);
+    s.x2[m] = __builtin_bit_cast(f16x8, l);
+  }
+  return s;
+}
+__device__ __forceinline__ void rs_store_h2(float* tile, const RsSplit& s, int lane) {
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    *reinterpret_cast<f16x8*>(tile + 256 * (2 * m) + 4 * lane) = s.x1[m];
+    *reinterpret_cast<f16x8*>(tile + 256 * (2 * m + 1) + 4 * lane) = s.x2[m];
+  }
+}
+// acc += A A^T, A in registers; the same sums as rs_mma_h2
+__device__ __forceinline__ void rs_mma_h2(f32x16& acc, const RsSplit& a) {
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a.x2[m], a.x1[m], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a.x1[m], a.x2[m], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a.x1[m], a.x1[m], acc, 0, 0, 0);
   }
 }
 // acc += A B^T, both split tiles in LDS
