@@ -35,8 +35,10 @@ constexpr int NB = kFactorNB;
 // about 40 rows on the tiles are the longer part, and the two-level updates move less.  Whole factorisations with the last 16,
 // 24, 32, 40, 48, 64 blocks in such steps, us: 3000 columns 910, 768, 768, ..; 4096 1277, 1166, 1058, ..; 5120 1803, 1697, 1638, 1607,
 // 1606, 1608; 6144 2355, 2284, 2250, 2245, 2340, 2338; 8192 3630, 3530, 3570, 3645, 3785, 4450; 11008 6625, 6560, 6500, 6510,
-// 6580, 7290 (before: 4096 1694, 5120 2114, 8192 4255, 11008 6875).
-constexpr int kStepAll = 40, kStepLast = 32;
+// 6580, 7290 (before: 4096 1694, 5120 2114, 8192 4255, 11008 6875).  Next to the row losses, whose product leaves half of
+// every compute unit, fewer are better: 5120 x 5120 4:8 with 16, 24, 32, 40 of 40 blocks 4581, 4520, 4581, 4700 us (4096: 2974,
+// 2901, 2908 of 32).  The same numbers for both, so that a factor has the same bits whatever runs beside it.
+constexpr int kStepAll = 32, kStepLast = 24;
 // ------------------------------------------------------------------------------------------
 // xnorm2[j] = H[j][j];  lam = damping * mean_j H[j][j]  (sum in fp64, fixed order);  d[j] = the scale of
 // channel j, d0[j] = that of the row losses (LOSSES; without the damping).  Also clears the n_bounds bounds.  One
@@ -501,7 +503,7 @@ __global__ __launch_bounds__(512, 4) void k_chol_diag(float* __restrict__ Ap, fl
 // column k to the next diagonal block,
 //     L_{k+1,k} = A_{k+1,k} Linv_kk^T,  A_{k+1,k+1} -= L_{k+1,k} L_{k+1,k}^T,  cd_block(k + 1),
 // and every other workgroup updates one tile right of it, A_ij -= L_ik L_jk^T (i >= j > k), with L_ik and L_jk worked
-// out for itself: the tiles of a step need no launch between panel and update, and with up to 40 block rows they take no
+// out for itself: the tiles of a step need no launch between panel and update, and with up to 32 block rows they take hardly
 // longer than the diagonal block.  A step is 22.5 us (2.5 for its first loads, 2.3 panel, 2.5 update, 14.5 block); as
 // separate launches it was 41 (block 23.5, panel 8.5, update 8.5), and 22 to 31 more for the strip of every fourth:
 // 512 columns 173 -> 129 us, 2048 822 -> 504, 4096 1694 -> 1058.

@@ -55,10 +55,10 @@ def test_not_positive_definite_is_reported():
     assert info > 0
 
 
-@pytest.mark.parametrize("b", [1, 31, 33, 97, 129, 2944, 3200, 5120, 5130])
+@pytest.mark.parametrize("b", [1, 31, 33, 97, 129, 2944, 3200, 4096, 4100])
 def test_factor_tile_edges(b):
     """One block that is mostly padding, 32-tiles cut at their edges, and the sizes around which the factorisation
-    passes from one launch per step to two-level updates in front of such steps (40 blocks of 128)."""
+    passes from one launch per step to two-level updates in front of such steps (32 blocks of 128)."""
     from tests.gpu_util import gpu_factor
     H32 = _h(b, T=2 * b + 64, seed=b)
     U, _, info = gpu_factor(H32, 0.01)
