@@ -909,7 +909,9 @@ __global__ __launch_bounds__(256, 2) void k_trinv_direct(TrinvArgs a) {
   }
   raise_bound((SECOND ? a.bound_inv : a.bound_T) + gj, __uint_as_float(top));
 }
-constexpr int kTriDirectTiles = 1024, kTriDirectS = 4;  // tiles and reductions as in direct_ok (gemm_f32.hip)
+// Up to 1024 tiles as in direct_ok (gemm_f32.hip), reductions of up to 1024: the factor of 1152 columns 328 us with up to
+// 512, 320 with up to 1024, of 2048 495 and 484, of 4096 1072 and 1062.
+constexpr int kTriDirectTiles = 1024, kTriDirectS = 8;
 
 // The lowest level (S = 1) in one launch: Linv21 = -Linv22 (L21 Linv11) for 128x128 blocks, of which each
 // product by itself is mostly launch and latency.  A workgroup owns 32 columns of a pair, a wavefront 32
