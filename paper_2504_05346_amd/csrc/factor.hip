@@ -12,7 +12,7 @@
 // factor block NB = 128); (2) right-looking blocked Cholesky: diagonal block in one workgroup
 // (which also produces the inverse of the diagonal block), panel = product with that inverse,
 // trailing update on the matrix cores, two-level (rank NB inside an outer block of 4 factor
-// blocks, rank 4 NB for everything right of it); (3) L^{-1} by recursive doubling over
+// blocks, rank 4 NB for everything right of it) while many block rows are left, then one launch per step (k_chol_step); (3) L^{-1} by recursive doubling over
 // block pairs, X21 = -Linv22 * (L21 * Linv11), two products per level; (4) U = J L^{-1} J.
 // Storage and chains are fp32; the products split their operands into two fp16 values (below).
 //

@@ -1303,7 +1303,7 @@ __global__ __launch_bounds__(64 * WPB, NTR == 2 ? 5 : 3) void k_solve_mfma(Solve
           const float d2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32 + k2));
           // 1 / d1 and 1 / d2', d2' = d2 - c12^2 / d1 = det / d1 the pivot of k2 after the elimination
           // of k1, from two independent reciprocals (see tl_eliminate)
-          const float ps = pivot_scale_vgpr(d1, exponents);
+          const float ps = pivot_scale(d1, exponents);
           const float e1 = ps * d1, e12 = ps * c12;
           const float cc = e12 * c12;
           const float det = fmaf(e1, d2, -cc) - fmaf(e12, c12, -cc);
@@ -1496,11 +1496,11 @@ __global__ __launch_bounds__(64 * WPB, NTR == 2 ? 5 : 3) void k_solve_mfma(Solve
 //
 // !BIG: the tiles live in the registers of the wavefronts that own them from the gather to the
 // back-substitution; LDS only carries T and the current panel.  What bounds a row is the chain of
-// eliminations (3.3 us per tile), so the number of rows in flight per compute unit is what
+// eliminations (2.7 us per tile by itself), so the number of rows in flight per compute unit is what
 // counts: a row of 256 unknowns takes 41 KB of LDS and half of the registers, two run at once;
 // with the tiles in LDS (152 KB) a row filled the unit.  Panel tiles go to LDS split into fp16 pairs, once
 // for the up to seven products that read each: 6 MFMAs of 32 cycles instead of 16 of 64.  4096 rows of 256
-// unknowns: 890 -> 530 (registers) -> 460 us.  Rows of up to 128 unknowns: five per unit instead of three.
+// unknowns: 890 -> 530 (registers) -> 460 -> 426 us.  Rows of up to 128 unknowns: five per unit instead of three.
 // BIG: tiles in global memory.
 constexpr int kTlLd = 33;          // LDS row stride of a tile (conflict-free rows and columns)
 constexpr int kTlSz = 32 * kTlLd;  // floats per tile

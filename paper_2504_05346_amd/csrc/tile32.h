@@ -125,15 +125,10 @@ __device__ __forceinline__ void rs_mma_h2(f32x16& acc, const float* a, const flo
   }
 }
 
-// The power of two that brings a normal d > 0 to [2, 4), in one instruction.  Scaling by it is exact, and
-// keeps the determinants of pairs of pivots in the range of fp32 whenever the pivots are.
-__device__ __forceinline__ float pivot_scale(float d) {
-  return __uint_as_float(~__float_as_uint(d) & 0x7f800000u);
-}
-
-// The same for a uniform d that comes from a v_readlane, on the vector unit (the detour through the scalar unit
-// takes 14 cycles of a chain); exponents: 0x7f800000 in a register.
-__device__ __forceinline__ float pivot_scale_vgpr(float d, float exponents) {
+// The power of two that brings a normal uniform d > 0, from a v_readlane, to [2, 4), in one instruction on the vector unit
+// (the detour through the scalar unit takes 14 cycles of a chain).  Scaling by it is exact, and keeps the determinants of
+// pairs of pivots in the range of fp32 whenever the pivots are.  exponents: 0x7f800000 in a register.
+__device__ __forceinline__ float pivot_scale(float d, float exponents) {
   float ps;
   asm("v_bfi_b32 %0, %1, 0, %2" : "=v"(ps) : "s"(d), "v"(exponents));
   return ps;
@@ -178,7 +173,7 @@ __device__ __forceinline__ float tl_eliminate(f32x16 D, f32x16& E, f32x16& U, fl
     // from two INDEPENDENT reciprocals, of d1 and of det = d1 d2 - c12^2: d2' = det / d1, row k1
     // scaled to a pivot e1 = ps d1 near one.  The wavefront is alone on this chain, so its length is
     // what counts: every instruction is 4 cycles, an MFMA 64 (the wavefront's own vector instructions wait for it).
-    const float ps = pivot_scale_vgpr(d1, exponents);
+    const float ps = pivot_scale(d1, exponents);
     const float e1 = ps * d1, e12 = ps * c12;
     const float cc = e12 * c12;
     const float det = fmaf(e1, d2, -cc) - fmaf(e12, c12, -cc);
