@@ -125,12 +125,14 @@ __device__ __forceinline__ void rs_mma_h2(f32x16& acc, const float* a, const flo
   }
 }
 
-// The power of two that brings a normal uniform d > 0, from a v_readlane, to [2, 4), in one instruction on the vector unit
-// (the detour through the scalar unit takes 14 cycles of a chain).  Scaling by it is exact, and keeps the determinants of
-// pairs of pivots in the range of fp32 whenever the pivots are.  exponents: 0x7f800000 in a register.
+// The power of two that brings a normal uniform d > 0, from a v_readlane, to [2, 4), on the vector unit (the detour through
+// the scalar unit takes 14 cycles of a chain).  Scaling by it is exact, and keeps the determinants of pairs of pivots in
+// the range of fp32 whenever the pivots are.  exponents: 0x7f800000 in a register.  d comes in a vector register: a
+// vector instruction may read what v_readlane has written only two wait states later, which the compiler sees to for
+// its own move, not for an instruction in here.  (With the scalar register and s_nop 1 in here the same times.)
 __device__ __forceinline__ float pivot_scale(float d, float exponents) {
   float ps;
-  asm("v_bfi_b32 %0, %1, 0, %2" : "=v"(ps) : "s"(d), "v"(exponents));
+  asm("v_bfi_b32 %0, %1, 0, %2" : "=v"(ps) : "v"(d), "v"(exponents));
   return ps;
 }
 
