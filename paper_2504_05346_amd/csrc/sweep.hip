@@ -1004,10 +1004,13 @@ __global__ __launch_bounds__(SMAX, (SMAX == 128 ? 3 : 1)) void k_solve_wide(Solv
 template <int NTR>
 struct SolveMfmaSmem {
   static constexpr int N = 32 * NTR;
-  // strict lower triangle of L~, packed by rows, and room for the lanes that have nothing to store;
+  // strict lower triangle of L~, packed by rows, and room for the lanes that have nothing to store (16) and for what the
+  // sweeps over it read past its end, for lanes that are final: of the last row a whole wavefront's values;
   // before the elimination and after the back-substitution the first 256 floats hold the row's
   // weights (then lambda) and metric
-  float L[N * (N - 1) / 2 + 16];
+  static constexpr int kLen = N * (N - 1) / 2 + (NTR == 2 ? 16 : 48);
+  static_assert((N - 1) * (N - 2) / 2 + 64 * ((N - 2) / 64) + 63 < kLen, "the sweeps read L up to here");
+  float L[kLen];
   alignas(4) unsigned char q[NTR == 2 ? 64 : 128];
 };
 
