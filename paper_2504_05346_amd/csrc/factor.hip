@@ -24,6 +24,7 @@
 // merge leaves the largest magnitude of its block column in `bounds`.  Step (4) takes D out again.
 #include <algorithm>
 
+#include "factor_plan.h"
 #include "gemm_tile_h2.h"
 #include "tile32.h"
 
@@ -38,7 +39,6 @@ constexpr int NB = kFactorNB;
 // 6580, 7290 (before: 4096 1694, 5120 2114, 8192 4255, 11008 6875).  Next to the row losses, whose product leaves half of
 // every compute unit, fewer are better: 5120 x 5120 4:8 with 16, 24, 32, 40 of 40 blocks 4581, 4520, 4581, 4700 us (4096: 2974,
 // 2901, 2908 of 32).  The same numbers for both, so that a factor has the same bits whatever runs beside it.
-constexpr int kStepAll = 32, kStepLast = 24;
 // ------------------------------------------------------------------------------------------
 // xnorm2[j] = H[j][j];  lam = damping * mean_j H[j][j]  (sum in fp64, fixed order);  d[j] = the scale of
 // channel j, d0[j] = that of the row losses (LOSSES; without the damping).  Also clears the n_bounds bounds.  One
@@ -1051,7 +1051,7 @@ thanos_status factor_begin(hipStream_t s, const float* H, int64_t b, float dampi
                      lam, d, d + 2 * bp + n_bounds(nb), d + bp, n_bounds(nb) + (int)bp, info);
   THANOS_LAUNCH_CHECK();
   const dim3 tiles((unsigned)(bp / kRpT), (unsigned)(bp / kRpT));
-  const int parked = nb <= kStepAll ? 1 : 0;
+  const int parked = factor_first_step(nb) == 0 ? 1 : 0;
   if (b <= kRpFew) hipLaunchKernelGGL(k_reverse_pad<16>, tiles, dim3(1024), 0, s, H, b, lam, d, Ap, bp, parked);
   else hipLaunchKernelGGL(k_reverse_pad<4>, tiles, dim3(256), 0, s, H, b, lam, d, Ap, bp, parked);
   THANOS_LAUNCH_CHECK();
@@ -1086,7 +1086,7 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStepSmem));
   THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_chol_step<false>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStepSmem));
-  constexpr int kOuter = 4;
+  const int first_step = factor_first_step(nb);
   const int n_outer = (nb + kOuter - 1) / kOuter;
   AuxStream aux(s, n_outer > 2 ? 2 * n_outer : 0, single_stream);
   if (!aux.ok) return THANOS_ERR_HIP;
@@ -1182,52 +1182,26 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
     return THANOS_OK;
   };
   int pending_join = -1;  // event index recorded on the aux stream after the last "rest"
-  // the last block rows: one launch per step, every tile updated in every step
-  const int first_step = (nb - kStepLast + kOuter - 1) / kOuter * kOuter;
-  auto steps = [&](int k, bool stored) -> thanos_status {
-    if (pending_join >= 0) THANOS_CHECK(aux.join(pending_join));
-    pending_join = -1;
-    for (int t = k; t + 1 < nb; ++t) {
-      const StepArgs a{Ap, Linv, bp, b, t, nb, bound_inv, info};
-      const int rows = nb - 1 - t;
-      hipLaunchKernelGGL(t == k && stored ? k_chol_step<true> : k_chol_step<false>,
-                         dim3((unsigned)(rows * (rows + 1) / 2)), dim3(512), kStepSmem, s, a);
-      THANOS_LAUNCH_CHECK();
-      if ((t + 1) % kOuter == 0 && t + 2 < nb) THANOS_CHECK(trinv_upto(t));
-    }
-    return trinv_upto(nb - 1);
-  };
-  for (int k = 0; k < nb; ++k) {
+  for (int k = 0; k <= first_step; ++k) {
     hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(512), kCholDiagSmem, s, Ap, Linv, bp, k, b, bound_inv + k,
                        info);
     THANOS_LAUNCH_CHECK();
+    if (first_step == 0) break;  // the first panel waits where a step looks for it (k_reverse_pad)
     const int64_t rem = bp - (int64_t)(k + 1) * NB;
-    if (nb <= kStepAll) {  // the first panel waits where a step looks for it (k_reverse_pad)
-      THANOS_CHECK(steps(0, false));
-      break;
-    }
-    if (rem <= 0) {
-      thanos_status st = trinv_upto(k);
-      if (st != THANOS_OK) return st;
-      break;
-    }
     float* panel = Ap + ((int64_t)(k + 1) * NB) * bp + (int64_t)k * NB;
     const float* dinv = Linv + ((int64_t)k * NB) * bp + (int64_t)k * NB;
     // L_ik = A_ik * Linv_kk^T  (in place, all rows below the diagonal block)
     thanos_status st = gemm_bounded(s, rem, NB, NB, 1.f, panel, bp, kBoundA, dinv, bp, 0.f, bound_inv + k,
                                     0.f, panel, bp, false, company);
     if (st != THANOS_OK) return st;
-    if (k == first_step) {
-      THANOS_CHECK(steps(k, true));
-      break;
-    }
+    if (k == first_step) break;
     if ((k + 1) % kOuter == 0) {
       st = trinv_upto(k);
       if (st != THANOS_OK) return st;
     }
     const int ob = k / kOuter;
     const int ob_begin = ob * kOuter;
-    const int ob_end = std::min(nb, ob_begin + kOuter);
+    const int ob_end = ob_begin + kOuter;  // at least a step's rows follow (factor_first_step), also behind the next one
     // narrow: A_ij -= L_ik L_jk^T for block columns k < j < ob_end, lower tiles
     const int64_t ncols = (int64_t)(ob_end - (k + 1)) * NB;
     if (ncols > 0) {
@@ -1237,8 +1211,8 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
       if (st != THANOS_OK) return st;
     }
     // wide: after the last step of an outer block, everything right of it
-    if (k + 1 == ob_end && ob_end < nb) {
-      const int next_end = std::min(nb, ob_end + kOuter);
+    if (k + 1 == ob_end) {
+      const int next_end = ob_end + kOuter;
       const int64_t kk = (int64_t)(ob_end - ob_begin) * NB;
       const float* lp = Ap + ((int64_t)ob_end * NB) * bp + (int64_t)ob_begin * NB;
       // The strip of the next outer block first: it is on the critical path (the next diagonal
@@ -1258,20 +1232,28 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
       // fork: the rest (rows and columns >= next_end) on the second stream, next to the
       // latency-bound chain of the next outer block (the fork point lies behind the strip, which
       // costs the rest nothing: the two write disjoint columns)
-      if (next_end < nb) {
-        THANOS_CHECK(aux.fork(2 * ob));
-        const int64_t rest = bp - (int64_t)next_end * NB;
-        const float* lr = lp + ((int64_t)(next_end - ob_end) * NB) * bp;
-        float* cr = Ap + ((int64_t)next_end * NB) * bp + (int64_t)next_end * NB;
-        st = gemm_bounded(aux.stream, rest, rest, kk, -1.f, lr, bp, kBoundL, lr, bp, kBoundL, nullptr, 1.f, cr,
-                          bp, true, company);
-        if (st != THANOS_OK) return st;
-        THANOS_CHECK(aux.record(2 * ob + 1));
-        pending_join = 2 * ob + 1;
-      }
+      THANOS_CHECK(aux.fork(2 * ob));
+      const int64_t rest = bp - (int64_t)next_end * NB;
+      const float* lr = lp + ((int64_t)(next_end - ob_end) * NB) * bp;
+      float* cr = Ap + ((int64_t)next_end * NB) * bp + (int64_t)next_end * NB;
+      st = gemm_bounded(aux.stream, rest, rest, kk, -1.f, lr, bp, kBoundL, lr, bp, kBoundL, nullptr, 1.f, cr,
+                        bp, true, company);
+      if (st != THANOS_OK) return st;
+      THANOS_CHECK(aux.record(2 * ob + 1));
+      pending_join = 2 * ob + 1;
     }
   }
   if (pending_join >= 0) THANOS_CHECK(aux.join(pending_join));
+  // the last block rows: one launch per step, every tile updated in every step
+  for (int k = first_step; k + 1 < nb; ++k) {
+    const StepArgs a{Ap, Linv, bp, b, k, nb, bound_inv, info};
+    const int rows = nb - 1 - k;
+    hipLaunchKernelGGL(k == first_step && first_step > 0 ? k_chol_step<true> : k_chol_step<false>,
+                       dim3((unsigned)(rows * (rows + 1) / 2)), dim3(512), kStepSmem, s, a);
+    THANOS_LAUNCH_CHECK();
+    if ((k + 1) % kOuter == 0 && k + 2 < nb) THANOS_CHECK(trinv_upto(k));
+  }
+  THANOS_CHECK(trinv_upto(nb - 1));
 
   // few columns: enough workgroups; many: few updates of the maxima.  Whole factorisation, 8 rows and 64 per
   // thread: 128 columns 36.3 and 42.0 us, 512 180.6 and 185.8, 1024 391 and 397, 1365 545.5 and 546, 2048 831 and

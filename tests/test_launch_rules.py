@@ -313,3 +313,24 @@ extern "C" int wgs(int64_t c, int units, int sharers) { return thanos::select_wo
         assert lanes == min(4, len(rows))
         at_once = sorted((L.wgs(c, 256, lanes) for c in rows), reverse=True)[:lanes]
         assert sum(n for n in at_once if n > 1) <= max(L.wgs(c, 256, 1) for c in rows)
+
+
+# --------------------------------------------------------------------------- factorisation
+@pytest.fixture(scope="module")
+def order(tmp_path_factory):
+    L = _compile(tmp_path_factory, "factor_plan", """
+#include "factor_plan.h"
+extern "C" int first_step(int nb) { return thanos::factor_first_step(nb); }
+""")
+    return L
+
+
+def test_steps_follow_whole_outer_blocks(order):
+    """Up to 32 block columns are left with one launch per step from the first one on; of more, two-level updates come
+    first, in outer blocks of four, and both block columns behind the last of these and rows for its rest are there."""
+    for nb in range(1, 513):
+        first = order.first_step(nb)
+        if nb <= 32:
+            assert first == 0
+        else:
+            assert first > 0 and first % 4 == 0 and 21 <= nb - first <= 24, nb
