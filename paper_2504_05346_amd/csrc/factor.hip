@@ -1087,8 +1087,7 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
   THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_chol_step<false>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStepSmem));
   const int first_step = factor_first_step(nb);
-  const int n_outer = (nb + kOuter - 1) / kOuter;
-  AuxStream aux(s, n_outer > 2 ? 2 * n_outer : 0, single_stream);
+  AuxStream aux(s, 2 * factor_rests(nb), single_stream);
   if (!aux.ok) return THANOS_ERR_HIP;
 
   // The inverse of L (recursive doubling, see k_trinv_T / k_trinv_X) does not wait for the end
@@ -1111,7 +1110,8 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kH2SmemBytes));
   THANOS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_trinv_X<2>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kH2SmemBytes));
-  AuxStream tri(s, n_outer > 1 ? n_outer + 1 : 0, single_stream);
+  const int n_batches = factor_tri_batches(nb);
+  AuxStream tri(s, n_batches > 0 ? n_batches + 1 : 0, single_stream);
   if (!tri.ok) return THANOS_ERR_HIP;
   int tri_done = -1;  // blocks 0..tri_done have been handed to the inversion
   int tri_batches = 0;
@@ -1124,8 +1124,8 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
     hipStream_t ts = tri.stream;
     if (kdone == nb - 1) {
       if (tri_batches > 0) {
-        THANOS_CHECK(tri.record(n_outer));
-        THANOS_CHECK(tri.join(n_outer));
+        THANOS_CHECK(tri.record(n_batches));
+        THANOS_CHECK(tri.join(n_batches));
       }
       ts = s;
     } else {

@@ -321,6 +321,8 @@ def order(tmp_path_factory):
     L = _compile(tmp_path_factory, "factor_plan", """
 #include "factor_plan.h"
 extern "C" int first_step(int nb) { return thanos::factor_first_step(nb); }
+extern "C" int rests(int nb) { return thanos::factor_rests(nb); }
+extern "C" int tri_batches(int nb) { return thanos::factor_tri_batches(nb); }
 """)
     return L
 
@@ -334,3 +336,14 @@ def test_steps_follow_whole_outer_blocks(order):
             assert first == 0
         else:
             assert first > 0 and first % 4 == 0 and 21 <= nb - first <= 24, nb
+
+
+def test_factorisation_borrows_the_helpers_it_uses(order):
+    """Events of the two helper streams: none, and so no stream, where nothing is forked onto it."""
+    for nb in range(1, 513):
+        first = order.first_step(nb)
+        rests = sum(1 for k in range(first) if k % 4 == 3)  # wide updates, one behind each outer block
+        batches = sum(1 for k in range(nb) if k % 4 == 3 and k + 2 < nb)  # merges beside the chain; the last are not
+        assert (order.rests(nb), order.tri_batches(nb)) == (rests, batches), nb
+    assert [order.rests(nb) for nb in (9, 32, 33)] == [0, 0, 3]
+    assert [order.tri_batches(nb) for nb in (1, 5, 6, 9, 10)] == [0, 0, 1, 1, 2]
