@@ -15,8 +15,9 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libthanos.so")
 SOURCES = ["api.hip", "syrk.hip", "gemm_f32.hip", "factor.hip", "sweep.hip", "structured.hip"]
-HEADERS = ["common.h", "factor_plan.h", "gemm_tile.h", "gemm_tile_h2.h", "gemm_tile_x3.h", "lam_layout.h", "select_plan.h",
-           "split_scale.h", "syrk_plan.h", "tile32.h", "timeline.h", os.path.join("..", "..", "include", "thanos.h")]
+HEADERS = ["common.h", "factor_plan.h", "gemm_tile.h", "gemm_tile_h2.h", "gemm_tile_x3.h", "lam_layout.h",
+           "select_plan.h", "solve_plan.h", "split_scale.h", "syrk_plan.h", "tile32.h",
+           "timeline.h", os.path.join("..", "..", "include", "thanos.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -22,6 +22,7 @@
 #include "gemm_tile_h2.h"
 #include "lam_layout.h"
 #include "select_plan.h"
+#include "solve_plan.h"
 #include "tile32.h"
 
 namespace thanos {
@@ -3025,16 +3026,11 @@ static void launch_tiled(hipStream_t s, SolveArgs a, int smax) {
   hipLaunchKernelGGL((k_solve_tiled<SEL, 8>), dim3((unsigned)a.c), dim3(512), smem8, s, a);
 }
 
-// Rows that run at once: eight of up to 96 unknowns, sixteen of up to 64 per compute unit
-constexpr int64_t kRowsOf96 = 8 * 256, kRowsOf64 = 16 * 256;
-
 // k_solve_mfma for up to 64 unknowns per row
 template <int SEL, int WPB>
-static void launch_mfma2(hipStream_t s, const SolveArgs& a) {
-  const bool full = SEL == SEL_NM && a.bw * a.n == 64 * a.m && a.bw % a.m == 0;  // 64 unknowns in every row
+static void launch_mfma2(hipStream_t s, const SolveArgs& a, bool full) {
   auto* const kern = full ? k_solve_mfma<SEL, WPB, 2, SEL == SEL_NM> : k_solve_mfma<SEL, WPB, 2, false>;
-  hipLaunchKernelGGL(kern,
-                     dim3((unsigned)ceil_div(a.c, WPB)), dim3(64 * WPB), WPB * sizeof(SolveMfmaSmem<2>), s, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div(a.c, WPB)), dim3(64 * WPB), WPB * sizeof(SolveMfmaSmem<2>), s, a);
 }
 
 template <int SEL>
@@ -3046,10 +3042,9 @@ static void launch_solve(hipStream_t s, SolveArgs a, int smax) {
   if (a.Kc && (a.bw > 128 || a.c > kRowsOf96)) smax = SEL == SEL_NM ? std::min(smax, a.bw - smax) : a.bw / 2;
   if (a.bw <= 128 && smax <= 64) {
     a.defer_large = a.Kc ? 1 : 0;
-    // twenty rows to a unit, in workgroups of five, where sixteen leave some for later: 5120 x 5120 4:8, 4608 rows, 4640
-    // -> 4527 us; workgroups of four share out up to 4096 rows evenly
-    if (a.c <= kRowsOf64) launch_mfma2<SEL, 4>(s, a);
-    else launch_mfma2<SEL, 5>(s, a);
+    const bool full = SEL == SEL_NM && a.bw * a.n == 64 * a.m && a.bw % a.m == 0;  // 64 unknowns in every row, or none
+    if (solve_rows_per_group(a.c, full && !a.row_skip) == 5) launch_mfma2<SEL, 5>(s, a, full);
+    else launch_mfma2<SEL, 4>(s, a, full);
   } else if (a.bw <= 128) {
     // Up to 96 unknowns: one wavefront per row on the matrix cores.  When s varies from row to
     // row (and may exceed 96) the few larger rows get a launch of the 128-thread kernel.

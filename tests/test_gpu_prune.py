@@ -351,6 +351,8 @@ def test_given_mask_with_every_tile_count(B, given_factor):
     (2049, 253, 128),   # 64 unknowns and complement; last block of 125 columns
     (4096, 200, 128),   # last block of 72
     (4097, 242, 97),    # five rows to a workgroup; odd blocks, the last of 48
+    (5120, 128, 128),   # the last number of rows with five
+    (5121, 189, 128),   # four again; last block of 61
 ])
 def test_given_mask_with_every_row_size_up_to_128_columns(c, b, B):
     """Rows of 0 to B unknowns in a block of up to 128 columns, for the numbers of rows at which the solver changes.

@@ -347,3 +347,16 @@ def test_factorisation_borrows_the_helpers_it_uses(order):
         assert (order.rests(nb), order.tri_batches(nb)) == (rests, batches), nb
     assert [order.rests(nb) for nb in (9, 32, 33)] == [0, 0, 3]
     assert [order.tri_batches(nb) for nb in (1, 5, 6, 9, 10)] == [0, 0, 1, 1, 2]
+
+
+# --------------------------------------------------------------------------- row solver
+def test_rows_to_a_workgroup_of_the_small_solver(tmp_path_factory):
+    """Five only where sixteen rows per compute unit leave some for a second round and twenty do not; four where all rows
+    have 64 unknowns."""
+    L = _compile(tmp_path_factory, "solve_plan", """
+#include "solve_plan.h"
+extern "C" int rows(int64_t c, int all_full) { return thanos::solve_rows_per_group(c, all_full != 0); }
+""")
+    L.rows.argtypes = [ctypes.c_int64, ctypes.c_int]
+    assert [L.rows(c, 0) for c in (1, 4096, 4097, 5120, 5121, 8192, 8193, 10240, 1 << 20)] == [4, 4, 5, 5, 4, 4, 4, 4, 4]
+    assert all(L.rows(c, 1) == 4 for c in (1, 4096, 4097, 5120, 5121, 1 << 20))
