@@ -31,14 +31,6 @@
 namespace thanos {
 
 constexpr int NB = kFactorNB;
-// Block rows that are factored with one launch per step (k_chol_step): up to kStepAll all of them, of more the last
-// kStepLast.  A step updates every tile, (rows)^2 / 2 of them in 10 us a round of 512, beside a diagonal block of 20; from
-// about 40 rows on the tiles are the longer part, and the two-level updates move less.  Whole factorisations with the last 16,
-// 24, 32, 40, 48, 64 blocks in such steps, us: 3000 columns 910, 768, 768, ..; 4096 1277, 1166, 1058, ..; 5120 1803, 1697, 1638, 1607,
-// 1606, 1608; 6144 2355, 2284, 2250, 2245, 2340, 2338; 8192 3630, 3530, 3570, 3645, 3785, 4450; 11008 6625, 6560, 6500, 6510,
-// 6580, 7290 (before: 4096 1694, 5120 2114, 8192 4255, 11008 6875).  Next to the row losses, whose product leaves half of
-// every compute unit, fewer are better: 5120 x 5120 4:8 with 16, 24, 32, 40 of 40 blocks 4581, 4520, 4581, 4700 us (4096: 2974,
-// 2901, 2908 of 32).  The same numbers for both, so that a factor has the same bits whatever runs beside it.
 // ------------------------------------------------------------------------------------------
 // xnorm2[j] = H[j][j];  lam = damping * mean_j H[j][j]  (sum in fp64, fixed order);  d[j] = the scale of
 // channel j, d0[j] = that of the row losses (LOSSES; without the damping).  Also clears the n_bounds bounds.  One
@@ -102,17 +94,19 @@ __device__ __forceinline__ void raise_bound(float* bound, float m) {
   if ((threadIdx.x & 63) == 0) atomicMax(reinterpret_cast<unsigned int*>(bound), u);
 }
 
+// Split tiles right of the diagonal (see k_chol_step): offset of piece e of tile (r, kt) from the first element of its block;
+// ld: the matrix's.  A piece is two rows of 512 bytes; lane (lo, hi) has its 16 bytes hi * ld + 4 * lo further on.
+__device__ __forceinline__ int64_t st_parked(int r, int kt, int e, int64_t ld) { return (8 * (4 * r + kt) + 2 * e) * ld; }
+
 // A'[i][j] = (D H_d D)[b-1-i][b-1-j] for i >= j (read from the lower triangle of H as
 // H[b-1-j][b-1-i]); identity on the padding; its mirror image above the diagonal of the 64x64 tiles on it
-// (cd_load_op reads whole tiles), zero in the rest of a diagonal block (what lies right
-// of it is never read, and stays as it is).  64x64 tiles through LDS so that both the read of H and the write
-// of A' are coalesced, sixteen loads per thread in flight: 11008 columns 270 -> 135 us (before: 32x32 tiles, zeros in
-// the whole upper triangle).  R rows of threads: with few columns, where the launch waits for its own loads, 16 rows of
-// them have four loads and stores each instead of sixteen: 128 columns
-// 35.0 and 33.5 us for the factorisation, 512 179.3 and 177.8, 1024 389.7 and 389; 2048 equal.
-// tile (r, kt) of a block that waits right of the diagonal (p: the block): a piece is two rows of 512 bytes; at = hi * ld
-// + 4 * lo
-__device__ __forceinline__ int64_t st_parked(int r, int kt, int e, int64_t ld) { return (8 * (4 * r + kt) + 2 * e) * ld; }
+// (cd_load_op reads whole tiles), zero in the rest of a diagonal block.  What lies right of the diagonal blocks is room for
+// the split tiles of the steps and is written by them; of a factorisation that begins with steps (parked), what
+// belongs below the first diagonal block is left there in that form and not in its place.  64x64 tiles through LDS so that
+// both the read of H and the write of A' are coalesced, sixteen loads per thread in flight: 11008 columns 270 -> 135 us
+// (before: 32x32 tiles, zeros in the whole upper triangle).  R rows of threads: with few columns, where the launch waits for
+// its own loads, 16 rows of them have four loads and stores each instead of sixteen: 128 columns 35.0 and 33.5 us for the
+// factorisation, 512 179.3 and 177.8, 1024 389.7 and 389; 2048 equal.
 constexpr int kRpT = 64;
 constexpr int64_t kRpFew = 1024;
 template <int R>
@@ -293,6 +287,11 @@ __device__ __forceinline__ f32x16 cd_minus_tv(const float* T, const f32x16& V, i
 
 // v -= A B^T for tiles of L in LDS, on the two-way split (|L| <= kBoundL), which is made here: a tile is read
 // by three products at most.  Eight MFMAs of 32 cycles and 112 vector instructions where 16 fp32 MFMAs take 64 each.
+// The operands have 22 bits or more here instead of 24; all four partial products are summed in fp32, in eight MFMAs of 16
+// values instead of 16 of two.  Whole factors against float64 with fp32 MFMAs here and with these, damping 1e-2: 64
+// columns 1.69 and 1.42e-7, 128 2.90 and 1.86, 512 3.42 and 3.07, 1024 4.12 and 3.83, 4096 6.93 and 6.81, 5120 28.6 both; with
+// channels 100 times as large and damping 1e-4 128 columns 2.86 and 1.79, 1024 4.32 and 4.12, 4096 7.21 and 7.10; no size
+// from 33 to 5120 columns was further off.  128 columns 29.1 and 27.3 us, 512 130.5 and 124.7, 4096 1093 and 1067.
 struct CdSplit {
   f16x8 h[2], l[2];
 };
@@ -506,7 +505,8 @@ __global__ __launch_bounds__(512, 4) void k_chol_diag(float* __restrict__ Ap, fl
 // out for itself: the tiles of a step need no launch between panel and update, and with up to 32 block rows they take hardly
 // longer than the diagonal block.  A step is 22.5 us (2.5 for its first loads, 2.3 panel, 2.5 update, 14.5 block); as
 // separate launches it was 41 (block 23.5, panel 8.5, update 8.5), and 22 to 31 more for the strip of every fourth:
-// 512 columns 173 -> 129 us, 2048 822 -> 504, 4096 1694 -> 1058.
+// whole factorisations 512 columns 174 -> 125 us, 2048 818 -> 485, 4096 1696 -> 1037.  128 registers, so that two
+// workgroups share a compute unit when there are many tiles; 25 are spilled for it (STORED: 34).
 //
 // What a launch reads of A_ik no workgroup of it may overwrite, so tiles of the column that comes next (j = k + 1) do not
 // go to their place in A', which takes L_ij in the next launch, but to block (j, i), right of the diagonal, where
@@ -1115,8 +1115,8 @@ thanos_status factor(hipStream_t s, const float* H, int64_t b, float damping, fl
   if (!tri.ok) return THANOS_ERR_HIP;
   int tri_done = -1;  // blocks 0..tri_done have been handed to the inversion
   int tri_batches = 0;
-  constexpr int tri_cap = 512;  // workgroups of one launch while the factorisation runs (256 or
-                                // 384 measured the same, 192 and fewer slower)
+  constexpr int tri_cap = 512;  // workgroups of one launch while the factorisation runs (256 or 384 measured the same,
+                                // 192 and fewer slower, next to two-level updates; not measured next to steps)
   auto trinv_upto = [&](int kdone) -> thanos_status {
     // blocks <= kdone: diagonal inverse known, panel below solved (recorded on s by the caller)
     // The last batch runs on the caller's stream, behind the earlier ones: one hop between streams
