@@ -119,7 +119,7 @@ def test_split_products_ranges(b):
     assert np.linalg.norm(U1 - Uref) <= 8 * (b + 2.0 ** 13) * 2.0 ** -24 * np.linalg.norm(Uref)
 
 
-@pytest.mark.parametrize("b", [128, 256, 300, 512, 1365, 3200])
+@pytest.mark.parametrize("b", [128, 256, 300, 512, 1365, 3200, 4096, 4100])
 def test_well_conditioned_factor_is_as_exact_as_fp32(b):
     """H = D (I + E) D with eigenvalues of I + E between 1/2 and 3/2: no condition number hides the products'
     own errors.  The values right of the diagonal of U D are, relative to their column, within 2^-20 of float64 (sums of up

@@ -372,9 +372,14 @@ def test_given_mask_with_every_row_size_up_to_128_columns(c, b, B):
     assert np.all(Wg[M == 1] == 0.0)
     at = np.unique(np.concatenate([np.arange(2 * B + 2), np.arange(c - 16, c)]))
     Wo, _ = orc.prune_fast(W[at], H32.astype(np.float64), mode="unstructured", p=0.5, B=B, damp=0.01, mask_in=M[at])
-    some = np.linalg.norm(Wo, axis=1) > 0
-    rows = np.linalg.norm(Wg[at] - Wo, axis=1)[some] / np.linalg.norm(Wo, axis=1)[some]
-    assert rows.max() < 1e-3  # as in the other parity tests of this file
+    # of the row that came in: what is left of one that loses all but a weight or two is a difference of values of that size
+    rows = np.linalg.norm(Wg[at] - Wo, axis=1) / np.linalg.norm(W[at], axis=1)
+    # two systems of the condition number of the scaled matrix (50 to 80), the factor and the row, each at 2^-24; products
+    # of operands without their lower halves, 11 bits, are off by hundreds of times as much
+    Hd = orc.damped(H32.astype(np.float64), 0.01)
+    kappa = np.linalg.cond(Hd / np.sqrt(np.outer(np.diag(Hd), np.diag(Hd))))
+    print(f"worst row {rows.max():.2e}, allowed {2 * kappa * 2.0 ** -24:.2e}", flush=True)
+    assert rows.max() < 2 * kappa * 2.0 ** -24
 
 
 def test_factor_reuse_matches_internal_factor():
